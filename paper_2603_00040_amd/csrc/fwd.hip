@@ -4,7 +4,9 @@
 // of them.  Key tiles of B_k = 64 keys are visited in increasing order; K and V^T tiles
 // are copied global->LDS directly (global_load_lds, double buffered, XOR-swizzled rows)
 // and shared by the eight waves.  Waves 0-3 and waves 4-7 run half an iteration apart
-// (vector phase / matrix phase, separated by barriers).
+// (vector phase / matrix phase, separated by barriers).  Problems that do not fill the chip with
+// such workgroups run four waves and 128 rows (fwd_narrow_kernel, chosen by narrow_workgroups):
+// the same arithmetic in the same order, one barrier per tile, two workgroups per compute unit.
 //
 // MFMA shapes (v_mfma_f32_32x32x16_f16, fp32 accumulate).  All operands are the
 // dequantized NVFP4 values s*c, which fp16 represents exactly, so the products are those
@@ -28,19 +30,51 @@ struct FwdSmem {
     half_t v[2][D * 64];      // V^T tile [d][key], likewise
 };
 
+// Work item of a four-wave workgroup when every sequence has its own number of keys (serving).  A unit is a (sequence, kv head):
+// its G query heads x nqt tiles read the same K and V^T and stay on one XCD.  Units are dealt to the XCDs row by row, the longest
+// sequences first and every other row backwards, so that each XCD gets its share of long ones; inside an XCD the second round of
+// its 32 compute units runs backwards too (see longest_first).  The order of the sequences comes from their lengths here, on the
+// device (up to 64 of them; beyond that the order they have).  The grid is rounded up to whole rows of units: false for an item
+// that does not exist.  (8 sequences of 2k - 16k keys, 512-position chunks: 884 us on paired 256-row workgroups, head after head -> 629 us.)
+__device__ inline bool varlen_item(int block, const int* __restrict__ kv_lens, int B, int Hq, int G, int nqt, int& bh, int& tile)
+{
+    const int x = block & 7, Hkv = Hq / G, per_unit = G * nqt, units = B * Hkv;
+    int s = block >> 3;
+    if ((s >> 5) == 1 && 64 <= (units >> 3) * per_unit) s = 95 - s;
+    const int row = s / per_unit, t = s % per_unit;
+    const int unit = row * 8 + ((row & 1) ? 7 - x : x);
+    if (unit >= units) return false;
+    int b = unit / Hkv;
+    if (B > 1 && B <= 64) {
+        const int lane = (int)(threadIdx.x & 63);
+        const int len = lane < B ? kv_lens[lane] : -1;
+        int rank = lane < B ? 0 : 64;
+        for (int j = 0; j < B; ++j) {
+            const int lj = __builtin_amdgcn_readlane(len, j);
+            rank += (lj > len || (lj == len && j < lane)) ? 1 : 0;
+        }
+        b = (int)__builtin_ctzll(__builtin_amdgcn_ballot_w64(rank == b));
+    }
+    bh = b * Hq + (unit % Hkv) * G + t % G;
+    tile = t / G;
+    return true;
+}
+
 // PQ, the format of P-tilde in the P V product: 0 NVFP4, 1 MX, 2 NVFP4 with the two-level row factor,
 // 3 bf16 with V left in bf16 as well (the mixed recipe "NVFP4 Q K^T, BF16 P V" of Sec. 2.5; the tile buffer of V^T then
 // holds bf16 bit patterns and the P V products are bf16 MFMAs; inference only).
 // VARLEN (serving): every sequence b has its own number of keys kv_lens[b] (read here, on the device), the copies of K and V^T
 // are laid out for Lkp positions per head, and the L query rows are the LAST L positions of their sequence: under the causal
 // mask query i sees keys 0 .. kv_lens[b] - L + i (a chunk of a prefill; needs kv_lens[b] >= L).
-template <int D, bool TRAIN, bool CAUSAL, bool DUMP, int PQ, bool VARLEN = false>
-__global__ __launch_bounds__(512, 2) void fwd_kernel(
+template <int D, bool TRAIN, bool CAUSAL, bool DUMP, int PQ, bool VARLEN, int NW>
+__device__ __forceinline__ void fwd_body(
     const half_t* __restrict__ Qh, const half_t* __restrict__ Kh, const half_t* __restrict__ Vt,
     uint16_t* __restrict__ O, float* __restrict__ lse, float* __restrict__ Ohp,
     int L, int Lp, int Hq, int G, float c /* log2(e)/sqrt(d) */, int dump_row0, float* __restrict__ pdump,
-    int Lkp_arg, const int* __restrict__ kv_lens, const uint32_t* __restrict__ Qsc)
+    int Lkp_arg, const int* __restrict__ kv_lens, const uint32_t* __restrict__ Qsc, int B /* batch (VARLEN: sequences) */)
 {
+    constexpr int QT = 32 * NW;     // query rows of a workgroup
+    constexpr bool PHASES = NW == 8, PAIRED = CAUSAL && NW == 8;
     // PQ == 1 (MX): S = Q^F K^F^T comes from the E2M1 codes and E8M0 scales by v_mfma_scale_f32_32x32x64_f8f6f4 (a quarter of
     // the matrix time of the 16-bit products, a quarter of the K bytes through LDS).  Qh then holds the Q operands of that
     // instruction (64 d per step: lane (row, half) has d-slots 64 ks + 32 half .. + 31 of its row) with one dword of scale
@@ -53,8 +87,8 @@ __global__ __launch_bounds__(512, 2) void fwd_kernel(
     constexpr int DS = D / 16;      // contraction steps of S
     constexpr int MB = D / 32;      // 32-row blocks of O^T
     constexpr int KCH = D / 8;      // 16-byte chunks per K row
-    constexpr int KLD = KCH / 8;    // 1 KiB wave-loads per wave for the K tile (8 waves)
-    constexpr int VLD = D / 64;     // ... for the V^T tile
+    constexpr int KLD = KCH / NW;   // 1 KiB wave-loads per wave for the K tile
+    constexpr int VLD = D / 8 / NW; // ... for the V^T tile
     extern __shared__ __align__(256) unsigned char smem_raw[];   // the XORs of address bits 5..7 commute with adding this base
     FwdSmem<D>& sm = *reinterpret_cast<FwdSmem<D>*>(smem_raw);
 
@@ -62,15 +96,19 @@ __global__ __launch_bounds__(512, 2) void fwd_kernel(
     // visits 4 qt + 4 key tiles, so a workgroup takes a pair, tile nqt - 1 - p and then tile p: every workgroup then does
     // the same amount of work (no tail of long tiles at the end of a head) and there are half as many workgroups, each of
     // which costs the CU a fixed 20 - 30 us of start-up and wind-down that nothing overlaps at one workgroup per CU.
-    const int nqt = (Lp + 255) / 256;
-    const int per_head = CAUSAL ? (nqt + 1) / 2 : nqt;
+    // Four waves (128 rows): one tile per workgroup, the longest first under a causal mask.
+    const int nqt = (Lp + QT - 1) / QT, nheads = B * Hq;
+    const int per_head = PAIRED ? (nqt + 1) / 2 : nqt;
     int bh, qt0;
-    head_tile_of_block(blockIdx.x, gridDim.x / per_head, per_head, bh, qt0);
-    const int nitems = (CAUSAL && nqt - 1 - qt0 != qt0) ? 2 : 1;
+    if constexpr (VARLEN && NW == 4) {
+        if (!varlen_item(blockIdx.x, kv_lens, B, Hq, G, nqt, bh, qt0)) return;
+    } else if (CAUSAL && NW == 4) longest_first(blockIdx.x, nheads, per_head, bh, qt0);
+    else head_tile_of_block(blockIdx.x, nheads, per_head, bh, qt0);
+    const int nitems = (PAIRED && nqt - 1 - qt0 != qt0) ? 2 : 1;
     const int b = bh / Hq, h = bh % Hq;
     const int bhkv = b * (Hq / G) + h / G;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);        // scalar: LDS destinations and branches use it
-    const bool late = wave >= 4;                         // the group that runs one phase behind
+    const bool late = PHASES && wave >= 4;               // the group that runs one phase behind
     // keys of this sequence, row stride of the K / V^T copies, and how far the causal diagonal is shifted
     const int Lk = VARLEN ? max(1, min(kv_lens[b], Lkp_arg)) : L;
     const int Lkp = VARLEN ? Lkp_arg : Lp;
@@ -93,14 +131,17 @@ __global__ __launch_bounds__(512, 2) void fwd_kernel(
     const unsigned char* vbase = reinterpret_cast<const unsigned char*>(&sm.v[0][0]);
 
     // direct-to-LDS tile loads: wave-uniform tile base + this lane's byte offset inside the tile
-    uint32_t k_ld[KLD], v_ld[VLD];
+    // (four waves: a wave's copies of a tile differ by whole 1 KiB steps in the row and by one swizzle bit pair, so one offset
+    //  register each for K and V^T serves all of them: the training kernel has none to spare)
+    constexpr bool ONE_OFF = NW == 4;
+    uint32_t k_ld[ONE_OFF ? 1 : KLD], v_ld[ONE_OFF ? 1 : VLD];
 #pragma unroll
-    for (int i = 0; i < KLD; ++i) {
+    for (int i = 0; i < (ONE_OFF ? 1 : KLD); ++i) {
         const int slot = 64 * (wave * KLD + i) + lane, r = slot / KCH, pc = slot % KCH;
         k_ld[i] = 2u * (uint32_t)(r * D + 8 * swz<KCH>(r, pc));
     }
 #pragma unroll
-    for (int i = 0; i < VLD; ++i) {
+    for (int i = 0; i < (ONE_OFF ? 1 : VLD); ++i) {
         const int slot = 64 * (wave * VLD + i) + lane, r = slot / 8, pc = slot % 8;
         v_ld[i] = 2u * ((uint32_t)r * (uint32_t)Lkp + 8u * (uint32_t)swz<8>(r, pc));
     }
@@ -109,21 +150,40 @@ __global__ __launch_bounds__(512, 2) void fwd_kernel(
     const unsigned char* k_recs = reinterpret_cast<const unsigned char*>(Kh) + (size_t)bhkv * (Lkp / 64) * KREC;
     auto issue_k = [&](int buf, int jt) __attribute__((always_inline)) {
         if constexpr (MXS) {      // a record is KREC / 1024 wave copies of 1 KiB
-            if (wave < KREC / 1024)
-                async_copy16(k_recs + (size_t)jt * KREC, (uint32_t)(wave * 1024 + lane * 16), reinterpret_cast<unsigned char*>(&sm.k[buf][0]) + wave * 1024);
+#pragma unroll
+            for (int i = 0; i < (KREC / 1024 + NW - 1) / NW; ++i) {
+                const int ch = wave + i * NW;
+                if (ch < KREC / 1024)
+                    async_copy16(k_recs + (size_t)jt * KREC, (uint32_t)(ch * 1024 + lane * 16), reinterpret_cast<unsigned char*>(&sm.k[buf][0]) + ch * 1024);
+            }
+        } else if constexpr (ONE_OFF) {
+            // the next 1 KiB of the tile is 4 (D = 128) or 8 (D = 64) rows further: swizzle key bits 0-1 or bit 2 of the chunk
+            uint32_t off0 = k_ld[0];
+            asm volatile("" : "+v"(off0));
+#pragma unroll
+            for (int i = 0; i < KLD; ++i)
+                async_copy16(k_head + (size_t)jt * (64 * D) + i * 512, off0 ^ (uint32_t)(KCH == 16 ? (i << 4) : ((i & 1) << 6)), &sm.k[buf][512 * (wave * KLD + i)]);
         } else {
 #pragma unroll
             for (int i = 0; i < KLD; ++i) async_copy16(k_head + (size_t)jt * (64 * D), k_ld[i], &sm.k[buf][512 * (wave * KLD + i)]);
         }
     };
     auto issue_v = [&](int buf, int jt) __attribute__((always_inline)) {
+        if constexpr (ONE_OFF) {
+            uint32_t off0 = v_ld[0];
+            asm volatile("" : "+v"(off0));
+#pragma unroll
+            for (int i = 0; i < VLD; ++i)
+                async_copy16(v_head + (size_t)jt * 64 + (size_t)(8 * i) * Lkp, off0 ^ (uint32_t)((i & 1) << 6), &sm.v[buf][512 * (wave * VLD + i)]);
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < VLD; ++i) async_copy16(v_head + (size_t)jt * 64, v_ld[i], &sm.v[buf][512 * (wave * VLD + i)]);
     };
 
-    const int qt = CAUSAL ? (item == 0 ? nqt - 1 - qt0 : qt0) : qt0;
-    const int row0_w = qt * 256 + wave * 32;
-    const bool has_rows = row0_w < Lp;                   // false only in the last tile of a head
+    const int qt = CAUSAL ? (item == 0 ? nqt - 1 - qt0 : qt0) : qt0;      // (four waves: item is 0)
+    const int row0_w = qt * QT + wave * 32;
+    const bool has_rows = !PHASES || row0_w < Lp;        // false only in the last tile of a head (Lp is a multiple of 128)
     const int q_row = row0_w + ln;
 
     // Q^F operand: this lane's query row, d-slots 16*ds + 8*hf .. +7
@@ -141,7 +201,7 @@ __global__ __launch_bounds__(512, 2) void fwd_kernel(
 #pragma unroll
         for (int ds = 0; ds < DS; ++ds) qreg[ds] = *reinterpret_cast<const half8*>(qp + 16 * ds);
     }
-    const int nkt = CAUSAL ? min((qt * 256 + 255 + off) / 64 + 1, nkt_all) : nkt_all;     // key tiles this item visits
+    const int nkt = CAUSAL ? min((qt * QT + QT - 1 + off) / 64 + 1, nkt_all) : nkt_all;     // key tiles this item visits
     const int wave_qmax = row0_w + 31 + off;             // the last key that a row of this wave sees
 
     floatx16 o[MB], op[TRAIN ? MB : 1];
@@ -230,6 +290,7 @@ __global__ __launch_bounds__(512, 2) void fwd_kernel(
     __syncthreads();
     if (has_rows) scores(0);
     if (late) __builtin_amdgcn_s_barrier();              // one phase behind from here on
+    if constexpr (!PHASES) __builtin_amdgcn_s_barrier(); // everyone is past the scores of tile 0: K(2) may take its buffer
 
     // Two phases per key tile, separated by barriers; waves 0-3 are in the vector phase while waves
     // 4-7 are in the matrix phase and vice versa, so every SIMD holds one wave of each kind:
@@ -295,6 +356,8 @@ __global__ __launch_bounds__(512, 2) void fwd_kernel(
                 else                  rp[i & 3] += s[kb][i];
             }
         lsum = lsum * alpha + ((rp[0] + rp[1]) + (rp[2] + rp[3]));          // un-quantized P-tilde
+        // (pinned: the compiler otherwise sinks the additions to the end of the tile and keeps P-tilde alive beside the next S)
+        if constexpr (!PHASES) asm volatile("" : "+v"(lsum));
         // rescale: exact no-op unless some row of this wave moved its maximum (rare after the
         // first tiles), so it lives on the cold path
         float inv1 = 1.0f;
@@ -488,7 +551,8 @@ __global__ __launch_bounds__(512, 2) void fwd_kernel(
     // starts at the workgroup's first row included; rows inside it are masked in the vector phase), and only the last
     // three have waves that skip.  The two kinds of tile get loops of their own: the form with the skipping branch
     // schedules markedly worse (17 % slower on tiles where nobody skips), so it only runs where somebody does.
-    const int j_all = CAUSAL ? min(nkt, (qt * 256 + 31 + off) / 64 + 1) : nkt;
+    if constexpr (PHASES) {
+    const int j_all = CAUSAL ? min(nkt, (qt * QT + 31 + off) / 64 + 1) : nkt;
     for (int j = 0; j < j_all; ++j) {
         const int k0 = j * 64;
         float bsc[4], binv[4];
@@ -528,6 +592,31 @@ __global__ __launch_bounds__(512, 2) void fwd_kernel(
         }
     }
     if (!late) __builtin_amdgcn_s_barrier();             // pairs with the late group's extra barrier
+    } else {
+        // Four waves run in step, one barrier per key tile: at the top of tile j every wave is past the scores of tile j (the last
+        // reads of the K buffer that K(j+2) goes to) and past the products of tile j-1 (the V^T buffer of V(j+1)).  The second
+        // workgroup of the compute unit is what fills the SIMDs while this one waits.
+        auto step = [&](int j, bool active, bool next_active) __attribute__((always_inline)) {
+            request_tiles(j);
+            if (active) {
+                float bsc[4], binv[4];
+                vector_phase(j, bsc, binv);
+                __builtin_amdgcn_sched_barrier(0);
+                __builtin_amdgcn_s_setprio(1);
+                matrix_phase(j, bsc, binv);
+            }
+            if (next_active) scores((j + 1) & 1);
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_setprio(0);
+            __builtin_amdgcn_s_waitcnt(0);
+            __builtin_amdgcn_s_barrier();
+        };
+        // (the last two tiles under a causal mask are the ones that some waves skip; as above, that form gets its own loop)
+        const int j_all = CAUSAL ? min(nkt, (qt * QT + 31 + off) / 64 + 1) : nkt;
+        for (int j = 0; j < j_all; ++j) step(j, true, j + 1 < nkt && (!CAUSAL || j * 64 + 64 <= wave_qmax));
+        if constexpr (CAUSAL)
+            for (int j = j_all; j < nkt; ++j) step(j, j * 64 <= wave_qmax, j + 1 < nkt && j * 64 + 64 <= wave_qmax);
+    }
 
     // ---- epilogue: O /= l, O' /= l, L = m + log l
     const float l = xhalf_sum(lsum);
@@ -558,6 +647,45 @@ __global__ __launch_bounds__(512, 2) void fwd_kernel(
     }
 }
 
+#define AQ_FWD_ARGS \
+    const half_t* __restrict__ Qh, const half_t* __restrict__ Kh, const half_t* __restrict__ Vt, \
+    uint16_t* __restrict__ O, float* __restrict__ lse, float* __restrict__ Ohp, \
+    int L, int Lp, int Hq, int G, float c, int dump_row0, float* __restrict__ pdump, \
+    int Lkp, const int* __restrict__ kv_lens, const uint32_t* __restrict__ Qsc, int B
+template <int D, bool TRAIN, bool CAUSAL, bool DUMP, int PQ, bool VARLEN = false>
+__global__ __launch_bounds__(512, 2) void fwd_kernel(AQ_FWD_ARGS)
+{
+    fwd_body<D, TRAIN, CAUSAL, DUMP, PQ, VARLEN, 8>(Qh, Kh, Vt, O, lse, Ohp, L, Lp, Hq, G, c, dump_row0, pdump, Lkp, kv_lens, Qsc, B);
+}
+template <int D, bool TRAIN, bool CAUSAL, int PQ, bool VARLEN = false>
+__global__ __launch_bounds__(256, 2) void fwd_narrow_kernel(AQ_FWD_ARGS)
+{
+    fwd_body<D, TRAIN, CAUSAL, false, PQ, VARLEN, 4>(Qh, Kh, Vt, O, lse, Ohp, L, Lp, Hq, G, c, dump_row0, pdump, Lkp, kv_lens, Qsc, B);
+}
+#undef AQ_FWD_ARGS
+
+// Which of the two workgroup shapes.  The eight-wave one (256 rows, one workgroup per compute unit) makes half the tile copies
+// per row and runs its two halves in opposite phases; at equal fill it is 2 - 3 % faster at d = 128.  The four-wave one (128 rows,
+// two per compute unit) fills the chip with half the rows and leaves a smaller last round.
+// Without a mask all workgroups cost the same and rounds can be counted: a round of eight-wave workgroups costs 100, two four-wave
+// ones sharing a unit 102, one alone on its unit 80.  Measured, training forward, eight -> four waves: 12 heads, L = 1560 (84 against
+// 156 workgroups) 75 -> 61 us; L = 6240 (300 / 588) 483 -> 435 us; L = 3120 (156 / 300) 122 -> 122 us; 40 heads, L = 1560 (280 / 520)
+// 123 -> 125 us; 24 heads, L = 8192 (768 / 1536) 1033 -> 1050 us.
+// Under a causal mask an eight-wave workgroup pairs a long with a short tile, so that all cost the same, while four-wave workgroups
+// are ordered by length (longest_first) and balance themselves: they win wherever the pairs do not fill whole rounds (64 pairs,
+// 32 heads, L = 777: 71 -> 34 us; 192 pairs, L = 3001: 163 -> 127 us; 564 pairs, L = 24000: 2969 -> 2322 us).  Full rounds of long
+// pairs are even at 4096 positions (1024 pairs: 804 and 808 us) and 0 - 3 % faster on eight waves from 16384 on; d = 64 runs three
+// of the small workgroups per compute unit and always gains (16 heads, L = 32000: 3624 -> 3348 us).
+static bool narrow_workgroups(int heads, int Lp, int D, bool causal)
+{
+    const long long cus = device_cu_count(), n4 = (long long)heads * (Lp / 128);
+    const long long per_head = (Lp + 255) / 256, n8 = heads * (causal ? (per_head + 1) / 2 : per_head);
+    const long long rounds8 = (n8 + cus - 1) / cus;
+    if (causal) return D != 128 || Lp < 4096 || n8 * 100 < rounds8 * cus * 96;
+    const long long rest = n4 % (2 * cus);
+    return n4 / (2 * cus) * 102 + (rest == 0 ? 0 : rest <= cus ? 80 : 102) < rounds8 * 100;
+}
+
 template <int D, bool TRAIN, bool CAUSAL, bool DUMP, int PQ, bool VARLEN = false>
 static int launch_t(const void* qh, const void* kh, const void* vt, int B, int Hq, int Hkv, int L,
                     void* o, float* lse, float* o_hp, int dump_row0, float* p_dump, hipStream_t st,
@@ -568,14 +696,23 @@ static int launch_t(const void* qh, const void* kh, const void* vt, int B, int H
     const int nqt = (Lp + 255) / 256;
     const int per_head = CAUSAL ? (nqt + 1) / 2 : nqt;         // under a causal mask a workgroup takes a long and a short tile
     const size_t smem = sizeof(FwdSmem<D>);
-    auto kern = fwd_kernel<D, TRAIN, CAUSAL, DUMP, PQ, VARLEN>;
-    static unsigned long long lds_set = 0;          // one per instantiation
-    if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)smem, lds_set)) return -1;
     const float c = 1.4426950408889634f / sqrtf((float)D);
-    hipLaunchKernelGGL(kern, dim3((unsigned)(B * Hq * per_head)), dim3(512), smem, st,
-                       (const half_t*)qh, (const half_t*)kh, (const half_t*)vt, (uint16_t*)o, lse, o_hp,
-                       L, Lp, Hq, Hq / Hkv, c, dump_row0, p_dump, Lkp, kv_lens, (const uint32_t*)qsc);
-    return hipGetLastError() == hipSuccess ? 0 : -1;
+    auto go = [&](auto kern, unsigned grid, unsigned block, unsigned long long& lds_set) -> int {
+        if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)smem, lds_set)) return -1;
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(block), smem, st,
+                           (const half_t*)qh, (const half_t*)kh, (const half_t*)vt, (uint16_t*)o, lse, o_hp,
+                           L, Lp, Hq, Hq / Hkv, c, dump_row0, p_dump, Lkp, kv_lens, (const uint32_t*)qsc, B);
+        return hipGetLastError() == hipSuccess ? 0 : -1;
+    };
+    if constexpr (!DUMP) {
+        static unsigned long long lds_set_narrow = 0;      // one per instantiation
+        if (narrow_workgroups(B * Hq, Lp, D, CAUSAL)) {
+            const int groups = VARLEN ? round_up(B * Hkv, 8) : B * Hkv;       // (see varlen_item)
+            return go(fwd_narrow_kernel<D, TRAIN, CAUSAL, PQ, VARLEN>, (unsigned)(groups * (Hq / Hkv) * (Lp / 128)), 256, lds_set_narrow);
+        }
+    }
+    static unsigned long long lds_set = 0;          // one per instantiation
+    return go(fwd_kernel<D, TRAIN, CAUSAL, DUMP, PQ, VARLEN>, (unsigned)(B * Hq * per_head), 512, lds_set);
 }
 
 template <int D, int PQ>
