@@ -174,15 +174,20 @@ MxWs carve_mx(void* ws, int B, int Hq, int Hkv, int L, int d, bool fp8v = false)
     return w;
 }
 
-// phi of one input tensor and its layout copies (xr row-major, xt transposed; either may be null).
-// NVFP4: one fused kernel.  MX: the MX fake-quantizer writes the dequantized bf16 tensor to tmp (blocks along d,
-// or along the sequence for V), then the layout copy runs without quantizing.
-int quant_copy(const void* x, int BH, int L, int d, bool mx, int mx_axis, bool out_f16, void* xr, void* xt, void* tmp, hipStream_t st,
-               const float* sub = nullptr)
+// The MX phi of one input tensor and its layout copies (xr row-major, xt transposed; either may be null): the fake-quantizer
+// writes the dequantized bf16 tensor to tmp (blocks along d, or along the sequence for V), then the layout copy runs.
+int quant_copy(const void* x, int BH, int L, int d, int mx_axis, bool out_f16, void* xr, void* xt, void* tmp, hipStream_t st)
 {
-    if (!mx) return launch_prep(x, BH, L, d, true, out_f16, nullptr, nullptr, nullptr, xr, xt, st, sub);
     if (launch_mx_quant(x, BH, L, d, mx_axis, 0, false, nullptr, nullptr, tmp, st)) return -1;
     return launch_prep(tmp, BH, L, d, false, out_f16, nullptr, nullptr, nullptr, xr, xt, st);
+}
+
+// What the forward prepares: phi(Q), phi(K), phi(V) (Alg. 1 line "phi(Q), phi(K), phi(V)" / Alg. 2 line "Q^F, K^F, V^F").
+PrepGroup group_of(int B, int Hq, int Hkv, int L, int d)
+{
+    PrepGroup g{};
+    g.BHq = B * Hq; g.BHkv = B * Hkv; g.L = g.L_kv = L; g.Lp = g.Lp_kv = round_up(L, kRowPad); g.D = d; g.v_quant = true;
+    return g;
 }
 
 int fwd_common(const void* q, const void* k, const void* v, int B, int Hq, int Hkv, int L, int d,
@@ -199,30 +204,28 @@ int fwd_common(const void* q, const void* k, const void* v, int B, int Hq, int H
     if (!workspace || workspace_bytes < w.bytes) return ATTNQAT_EWORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     prof_begin(st);
-    // Alg. 1 line "phi(Q), phi(K), phi(V)" / Alg. 2 line "Q^F, K^F, V^F"
     if (mx) {
         // Q and K as operands of the scaled FP4 instruction (the scores are computed from the codes), V^F^T as the fp16 copy
         if (launch_mx_quant(q, B * Hq, L, d, 0, 1, false, (unsigned char*)w.qh, (unsigned char*)w.qsc, nullptr, st)) return ATTNQAT_ELAUNCH;
         if (launch_mx_quant(k, B * Hkv, L, d, 0, 3, false, (unsigned char*)w.kh, nullptr, nullptr, st)) return ATTNQAT_ELAUNCH;
-        if (quant_copy(v, B * Hkv, L, d, true, 1, true, nullptr, w.vt, w.tmp, st)) return ATTNQAT_ELAUNCH;
+        if (quant_copy(v, B * Hkv, L, d, 1, true, nullptr, w.vt, w.tmp, st)) return ATTNQAT_ELAUNCH;
         prof_mark("prep_qkv", st);
         if (launch_fwd(w.qh, w.kh, w.vt, B, Hq, Hkv, L, d, causal != 0, train, 1, o, lse, o_hp, dump_row0, p_dump, st, w.qsc))
             return ATTNQAT_ELAUNCH;
         prof_mark(train ? "fwd_train" : "fwd_infer", st);
         return ATTNQAT_OK;
     }
-    if (quant_copy(q, B * Hq, L, d, mx, 0, true, w.qh, nullptr, w.tmp, st)) return ATTNQAT_ELAUNCH;
-    const float* kmean = nullptr;
+    PrepGroup g = group_of(B, Hq, Hkv, L, d);
+    g.q = (const uint16_t*)q; g.k = (const uint16_t*)k; g.v = (const uint16_t*)v;
+    g.q_out = (uint16_t*)w.qh; g.k_out = (uint16_t*)w.kh; g.v_out = (uint16_t*)w.vt;
+    g.v_quant = !bf16pv;                           // Sec. 2.5, NVFP4 Q K^T with BF16 P V: V only changes layout
     if (options & ATTNQAT_OPT_SMOOTH_K) {          // K minus its token mean (Sec. 2.1), then phi
         if (launch_colmean(k, B * Hkv, L, d, w.kpart, w.kmean, st)) return ATTNQAT_ELAUNCH;
-        kmean = w.kmean;
+        g.k_sub = w.kmean;
     }
-    if (quant_copy(k, B * Hkv, L, d, mx, 0, true, w.kh, nullptr, w.tmp, st, kmean)) return ATTNQAT_ELAUNCH;
-    if (bf16pv) {      // Sec. 2.5, NVFP4 Q K^T with BF16 P V: V only changes layout
-        if (launch_prep(v, B * Hkv, L, d, false, false, nullptr, nullptr, nullptr, nullptr, w.vt, st)) return ATTNQAT_ELAUNCH;
-    } else if (quant_copy(v, B * Hkv, L, d, mx, 1, true, nullptr, w.vt, w.tmp, st)) return ATTNQAT_ELAUNCH;
+    if (launch_prep_group(g, st)) return ATTNQAT_ELAUNCH;
     prof_mark("prep_qkv", st);
-    const int p_quant = mx ? 1 : bf16pv ? 3 : (options & ATTNQAT_OPT_TWO_LEVEL_P) ? 2 : 0;
+    const int p_quant = bf16pv ? 3 : (options & ATTNQAT_OPT_TWO_LEVEL_P) ? 2 : 0;
     if (launch_fwd(w.qh, w.kh, w.vt, B, Hq, Hkv, L, d, causal != 0, train, p_quant, o, lse, o_hp, dump_row0, p_dump, st))
         return ATTNQAT_ELAUNCH;
     prof_mark(train ? "fwd_train" : "fwd_infer", st);
@@ -489,9 +492,12 @@ int paged_common(const void* q, int B, int Hq, int Hkv, int Lq, int d, int causa
     }
     if (dec_ws) *dec_ws = nullptr;
     // phi(Q); K^F and V^F are in the cache already and only change layout
-    if (launch_prep(q, B * Hq, Lq, d, true, true, nullptr, nullptr, nullptr, w.qh, nullptr, st)) return ATTNQAT_ELAUNCH;
-    if (launch_unpack_pages(cache, page_table, kv_lens, B, Hkv, max_pages, num_pages, d, 0, w.kh, nullptr, st)) return ATTNQAT_ELAUNCH;
-    if (launch_unpack_pages(cache, page_table, kv_lens, B, Hkv, max_pages, num_pages, d, 1, nullptr, w.vt, st)) return ATTNQAT_ELAUNCH;
+    PrepGroup g = group_of(B, Hq, Hkv, Lq, d);
+    g.q = (const uint16_t*)q;
+    g.ps = PagedSrc{(const unsigned char*)cache, page_table, kv_lens, max_pages, num_pages, Hkv, 0};
+    g.L_kv = max_pages * 128; g.Lp_kv = w.Lkp;
+    g.q_out = (uint16_t*)w.qh; g.k_out = (uint16_t*)w.kh; g.v_out = (uint16_t*)w.vt;
+    if (launch_prep_group(g, st)) return ATTNQAT_ELAUNCH;
     prof_mark("prep_q_unpack_pages", st);
     if (launch_fwd_varlen(w.qh, w.kh, w.vt, B, Hq, Hkv, Lq, w.Lkp, d, causal != 0, kv_lens, o, lse, st)) return ATTNQAT_ELAUNCH;
     prof_mark("fwd_infer_paged", st);
@@ -622,9 +628,11 @@ int attnqat_fwd_infer_packed(const uint8_t* q_codes, const uint8_t* q_scales, co
     hipStream_t st = (hipStream_t)stream;
     prof_begin(st);
     // Alg. 1 takes the quantized tensors: only the layout copies remain to be made
-    if (launch_unpack(q_codes, q_scales, B * Hq, L, d, true, w.qh, nullptr, st)) return ATTNQAT_ELAUNCH;
-    if (launch_unpack(k_codes, k_scales, B * Hkv, L, d, true, w.kh, nullptr, st)) return ATTNQAT_ELAUNCH;
-    if (launch_unpack(v_codes, v_scales, B * Hkv, L, d, true, nullptr, w.vt, st)) return ATTNQAT_ELAUNCH;
+    PrepGroup g = group_of(B, Hq, Hkv, L, d);
+    g.codes[0] = q_codes; g.codes[1] = k_codes; g.codes[2] = v_codes;
+    g.scales[0] = q_scales; g.scales[1] = k_scales; g.scales[2] = v_scales;
+    g.q_out = (uint16_t*)w.qh; g.k_out = (uint16_t*)w.kh; g.v_out = (uint16_t*)w.vt;
+    if (launch_prep_group(g, st)) return ATTNQAT_ELAUNCH;
     prof_mark("unpack_qkv", st);
     if (launch_fwd(w.qh, w.kh, w.vt, B, Hq, Hkv, L, d, causal != 0, false, 0, o, lse, nullptr, 0, nullptr, st)) return ATTNQAT_ELAUNCH;
     prof_mark("fwd_infer", st);
@@ -714,39 +722,45 @@ static int bwd_common(const void* q, const void* k, const void* v, const void* d
     if (!workspace || workspace_bytes < w.bytes) return ATTNQAT_EWORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     prof_begin(st);
-    if (packed) {
-        // the saved quantized tensors of the forward (appendix "Detailed Training Setup": the extra buffers for the
-        // fake-quantized Q, K, V): only the layout copies remain to be made
-        if (launch_unpack(packed->qc, packed->qs, B * Hq, L, d, true, w.qb, nullptr, st)) return ATTNQAT_ELAUNCH;
-        if (launch_unpack(packed->kc, packed->ks, B * Hkv, L, d, true, w.kb, nullptr, st)) return ATTNQAT_ELAUNCH;
-        if (launch_unpack(packed->vc, packed->vs, B * Hkv, L, d, false, w.vb, nullptr, st)) return ATTNQAT_ELAUNCH;
-    } else {
-    // Q^F, K^F, V^F again (bit-identical to the forward's) and a zero-padded copy of dO
-    if (quant_copy(q, B * Hq, L, d, mx, 0, true, w.qb, nullptr, w.tmp, st)) return ATTNQAT_ELAUNCH;
-    const float* kmean = nullptr;
-    if (options & ATTNQAT_OPT_SMOOTH_K) {          // the same centred K as the forward (deterministic mean)
-        if (launch_colmean(k, B * Hkv, L, d, w.kpart, w.kmean, st)) return ATTNQAT_ELAUNCH;
-        kmean = w.kmean;
-    }
-    if (quant_copy(k, B * Hkv, L, d, mx, 0, true, w.kb, nullptr, w.tmp, st, kmean)) return ATTNQAT_ELAUNCH;
-    if (quant_copy(v, B * Hkv, L, d, mx, 1, false, w.vb, nullptr, w.tmp, st)) return ATTNQAT_ELAUNCH;
-    }
-    if (launch_prep(d_o, B * Hq, L, d, false, false, nullptr, nullptr, nullptr, w.dob, nullptr, st)) return ATTNQAT_ELAUNCH;
+    // Q^F, K^F, V^F again (bit-identical to the forward's), D, the bounds of |dS|, and dO: the attention passes read it as it is
+    // where its rows need no padding (and lie as the 16-byte copies to LDS want them), otherwise from a zero-padded copy
+    PrepGroup g = group_of(B, Hq, Hkv, L, d);
+    g.v_out = (uint16_t*)w.vb;
+    g.d_o = (const uint16_t*)d_o; g.o_acc = o_acc; g.o_is_bf16 = o_is_bf16; g.lse = lse; g.rs = 1.0f / sqrtf((float)d);
+    g.rowstat = (float2*)w.rowstat; g.bounds = w.bounds;
+    const bool pad_do = L % kRowPad != 0 || ((uintptr_t)d_o & 15) != 0;
+    g.dob = pad_do ? (uint16_t*)w.dob : nullptr;
+    const void* dob = pad_do ? w.dob : d_o;
     MxScoreOps mxo{w.qops, w.qsc, w.kops, w.ksc, w.krec};
     if (mx) {
+        if (quant_copy(q, B * Hq, L, d, 0, true, w.qb, nullptr, w.tmp, st)) return ATTNQAT_ELAUNCH;
+        if (quant_copy(k, B * Hkv, L, d, 0, true, w.kb, nullptr, w.tmp, st)) return ATTNQAT_ELAUNCH;
+        if (launch_mx_quant(v, B * Hkv, L, d, 1, 0, false, nullptr, nullptr, w.tmp, st)) return ATTNQAT_ELAUNCH;
         if (launch_mx_quant(q, B * Hq, L, d, 0, 1, false, (unsigned char*)w.qops, (unsigned char*)w.qsc, nullptr, st)) return ATTNQAT_ELAUNCH;
         if (launch_mx_quant(k, B * Hkv, L, d, 0, 1, false, (unsigned char*)w.kops, (unsigned char*)w.ksc, nullptr, st)) return ATTNQAT_ELAUNCH;
         if (launch_mx_quant(k, B * Hkv, L, d, 0, 3, false, (unsigned char*)w.krec, nullptr, nullptr, st)) return ATTNQAT_ELAUNCH;
+        g.v = (const uint16_t*)w.tmp; g.v_quant = false;
+    } else {
+        g.q_out = (uint16_t*)w.qb; g.k_out = (uint16_t*)w.kb;
+        if (packed) {
+            // the saved quantized tensors of the forward (appendix "Detailed Training Setup": the extra buffers for the
+            // fake-quantized Q, K, V): only the layout copies remain to be made
+            g.codes[0] = packed->qc; g.codes[1] = packed->kc; g.codes[2] = packed->vc;
+            g.scales[0] = packed->qs; g.scales[1] = packed->ks; g.scales[2] = packed->vs;
+        } else {
+            g.q = (const uint16_t*)q; g.k = (const uint16_t*)k; g.v = (const uint16_t*)v;
+            if (options & ATTNQAT_OPT_SMOOTH_K) {          // the same centred K as the forward (deterministic mean)
+                if (launch_colmean(k, B * Hkv, L, d, w.kpart, w.kmean, st)) return ATTNQAT_ELAUNCH;
+                g.k_sub = w.kmean;
+            }
+        }
     }
+    if (launch_prep_group(g, st)) return ATTNQAT_ELAUNCH;
     prof_mark("prep_qkvdo", st);
-    if (launch_delta(d_o, o_acc, o_is_bf16, lse, B * Hq, L, d, w.rowstat, st)) return ATTNQAT_ELAUNCH;
-    prof_mark("delta", st);
-    if (launch_bounds(w.vb, w.dob, w.rowstat, B * Hkv, B * Hq, L, d, w.bounds, st)) return ATTNQAT_ELAUNCH;
-    prof_mark("bounds", st);
-    if (launch_bwd_dq(w.qb, w.kb, w.vb, w.dob, w.rowstat, w.bounds, B, Hq, Hkv, L, d, causal != 0, dq, st, mx ? &mxo : nullptr))
+    if (launch_bwd_dq(w.qb, w.kb, w.vb, dob, w.rowstat, w.bounds, B, Hq, Hkv, L, d, causal != 0, dq, st, mx ? &mxo : nullptr))
         return ATTNQAT_ELAUNCH;
     prof_mark("bwd_dq", st);
-    if (launch_bwd_dkdv(w.qb, w.kb, w.vb, w.dob, w.rowstat, w.bounds, B, Hq, Hkv, L, d, causal != 0, dk, dv,
+    if (launch_bwd_dkdv(w.qb, w.kb, w.vb, dob, w.rowstat, w.bounds, B, Hq, Hkv, L, d, causal != 0, dk, dv,
                         dkdv_counts_of(st), p_quant, st, p_dump, dump_row0, mx ? &mxo : nullptr))
         return ATTNQAT_ELAUNCH;
     prof_mark("bwd_dkdv", st);

@@ -1,6 +1,5 @@
-// Backward of Attn-QAT on gfx950 (Alg. 3), as four kernels:
-//   delta      D = rowsum(dO o O') and the per-row {L, D} pairs   (first line of Alg. 3; HBM bound)
-//   bounds     per-head maxima of |dO_i|, |V^F_j| and |D_i|: they bound |dS|   (HBM bound)
+// Backward of Attn-QAT on gfx950 (Alg. 3), as two kernels behind the preparing one (prep_group_kernel: the copies of
+// Q, K, V and dO, D = rowsum(dO o O') and the per-row {L, D} pairs, per-head maxima of |dO_i|, |V^F_j| and |D_i|):
 //   bwd_dq     query-stationary: S, P, dP, dS, dQ += dS K^F
 //   bwd_dkdv   key-stationary:   S, P, P^F, dP, dS, dV += P^F^T dO, dK += dS^T Q^F
 // The paper's single loop nest accumulates dQ across key tiles; here dQ gets its own pass
@@ -60,128 +59,12 @@ __device__ inline float ds_scale_for(float bound) {
 }
 __device__ inline uint4v join(uint2v a, uint2v b) { uint4v r; r[0] = a[0]; r[1] = a[1]; r[2] = b[0]; r[3] = b[1]; return r; }
 
-// ------------------------------------------------------------------ per-row statistics
-// rowstat[bh*Lp + l] = { L_l * log2(e), D_l / sqrt(d) } with D = rowsum(dO o O'); rows l >= L
-// (padding) hold {0, 0}.  Both attention passes read them as they are.
-template <int D, bool LOWP /* ablation: O' is given as bf16 */>
-__global__ __launch_bounds__(256) void delta_kernel(const uint16_t* __restrict__ dO, const void* __restrict__ Ohp_,
-                                                    const float* __restrict__ lse,
-                                                    int L, int Lp, long nrows_p, float rs, float2* __restrict__ rowstat)
-{
-    constexpr int TPR = D / 8;                 // threads per row
-    const long r = (long)blockIdx.x * (256 / TPR) + threadIdx.x / TPR;    // padded row id: bh*Lp + l
-    const int c = threadIdx.x % TPR;
-    if (r >= nrows_p) return;
-    const long bh = r / Lp; const int l = (int)(r % Lp);
-    float acc = 0.0f;
-    if (l < L) {
-        const size_t off = ((size_t)bh * L + l) * D + 8 * c;
-        const uint4v g = *reinterpret_cast<const uint4v*>(dO + off);
-        floatx4 o0, o1;
-        if constexpr (LOWP) {
-            const uint4v w = *reinterpret_cast<const uint4v*>(static_cast<const uint16_t*>(Ohp_) + off);
-            o0[0] = bf16_lo_f32(w[0]); o0[1] = bf16_hi_f32(w[0]); o0[2] = bf16_lo_f32(w[1]); o0[3] = bf16_hi_f32(w[1]);
-            o1[0] = bf16_lo_f32(w[2]); o1[1] = bf16_hi_f32(w[2]); o1[2] = bf16_lo_f32(w[3]); o1[3] = bf16_hi_f32(w[3]);
-        } else {
-            const float* Ohp = static_cast<const float*>(Ohp_);
-            o0 = *reinterpret_cast<const floatx4*>(Ohp + off);
-            o1 = *reinterpret_cast<const floatx4*>(Ohp + off + 4);
-        }
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            acc += bf16_lo_f32(g[i]) * o0[2 * i] + bf16_hi_f32(g[i]) * o0[2 * i + 1];
-            acc += bf16_lo_f32(g[2 + i]) * o1[2 * i] + bf16_hi_f32(g[2 + i]) * o1[2 * i + 1];
-        }
-    }
-#pragma unroll
-    for (int w = TPR / 2; w >= 1; w >>= 1) acc += __shfl_xor(acc, w);
-    if (c == 0) rowstat[r] = make_float2(l < L ? lse[(size_t)bh * L + l] * 1.4426950408889634f : 0.0f, acc * rs);
-}
-
-int launch_delta(const void* d_o, const void* o_acc, bool o_is_bf16, const float* lse, int BHq, int L, int D,
-                 float* rowstat, hipStream_t st)
-{
-    const int Lp = round_up(L, kRowPad);
-    const long nrows_p = (long)BHq * Lp;
-    const int rpb = 256 / (D / 8);
-    const unsigned grid = (unsigned)((nrows_p + rpb - 1) / rpb);
-    const float rs = 1.0f / sqrtf((float)D);
-    auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, (const uint16_t*)d_o, o_acc, lse, L, Lp, nrows_p, rs, (float2*)rowstat);
-    };
-    if (D == 128) { if (o_is_bf16) go(delta_kernel<128, true>); else go(delta_kernel<128, false>); }
-    else          { if (o_is_bf16) go(delta_kernel<64, true>);  else go(delta_kernel<64, false>); }
-    return hipGetLastError() == hipSuccess ? 0 : -1;
-}
-
-// ------------------------------------------------------------------ bounds of |dS|
-// part[(which*NH + head)*kBoundParts + chunk]: maxima over the chunk's rows of
-//   which 0: |V^F_j|_2 (kv heads)   1: |dO_i|_2 (query heads)   2: |D_i|/sqrt(d) (query heads)
-// No atomics and no initialisation: the consumers reduce the kBoundParts partial maxima.
-constexpr int kBoundParts = 64;
-
-template <int D>
-__global__ __launch_bounds__(256) void bounds_kernel(const uint16_t* __restrict__ Vb, const uint16_t* __restrict__ dOb,
-                                                     const float2* __restrict__ rowstat, int Lp, int NHkv, int NHq,
-                                                     float* __restrict__ part)
-{
-    constexpr int TPR = D / 8, RPP = 256 / TPR;      // threads per row, rows per pass
-    __shared__ float red[2][4];
-    const int head = blockIdx.x / kBoundParts, chunk = blockIdx.x % kBoundParts;      // 1-D grid: no 65535 limit on the heads
-    const bool is_v = head < NHkv;
-    const int h = is_v ? head : head - NHkv;
-    const uint16_t* src = (is_v ? Vb : dOb) + (size_t)h * Lp * D;
-    const int rows_per = (Lp + kBoundParts - 1) / kBoundParts;
-    const int r_begin = chunk * rows_per, r_end = min(Lp, r_begin + rows_per);
-    const int c = threadIdx.x % TPR;
-    float nmax = 0.0f, dmax = 0.0f;
-    for (int r = r_begin + threadIdx.x / TPR; r < r_end; r += RPP) {
-        const uint4v g = *reinterpret_cast<const uint4v*>(src + (size_t)r * D + 8 * c);
-        float acc = 0.0f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float lo = bf16_lo_f32(g[i]), hi = bf16_hi_f32(g[i]);
-            acc = fmaf(lo, lo, fmaf(hi, hi, acc));
-        }
-#pragma unroll
-        for (int w = TPR / 2; w >= 1; w >>= 1) acc += __shfl_xor(acc, w);
-        nmax = fmaxf(nmax, acc);
-        if (!is_v && c == 0) dmax = fmaxf(dmax, fabsf(rowstat[(size_t)h * Lp + r].y));
-    }
-#pragma unroll
-    for (int w = 32; w >= 1; w >>= 1) { nmax = fmaxf(nmax, __shfl_xor(nmax, w)); dmax = fmaxf(dmax, __shfl_xor(dmax, w)); }
-    if ((threadIdx.x & 63) == 0) { red[0][threadIdx.x >> 6] = nmax; red[1][threadIdx.x >> 6] = dmax; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        nmax = fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3]));
-        dmax = fmaxf(fmaxf(red[1][0], red[1][1]), fmaxf(red[1][2], red[1][3]));
-        const float nrm = sqrtf(nmax) * 1.0001f;     // rounded up a little: it is an upper bound
-        if (is_v) part[(size_t)h * kBoundParts + chunk] = nrm;
-        else {
-            part[((size_t)NHq + h) * kBoundParts + chunk] = nrm;
-            part[((size_t)2 * NHq + h) * kBoundParts + chunk] = dmax;
-        }
-    }
-}
-
 // One of the three maxima of a head: every lane gets the maximum of the head's partial values.
 __device__ inline float bound_of(const float* __restrict__ part, int NHq, int which, int head) {
     float v = part[((size_t)which * NHq + head) * kBoundParts + (threadIdx.x & 63)];
 #pragma unroll
     for (int w = 32; w >= 1; w >>= 1) v = fmaxf(v, __shfl_xor(v, w));
     return v;
-}
-
-int launch_bounds(const void* vb, const void* dob, const float* rowstat, int BHkv, int BHq, int L, int D,
-                  float* part, hipStream_t st)
-{
-    const int Lp = round_up(L, kRowPad);
-    dim3 grid((unsigned)kBoundParts * (unsigned)(BHkv + BHq));
-    if (D == 128) hipLaunchKernelGGL(bounds_kernel<128>, grid, dim3(256), 0, st, (const uint16_t*)vb, (const uint16_t*)dob,
-                                     (const float2*)rowstat, Lp, BHkv, BHq, part);
-    else          hipLaunchKernelGGL(bounds_kernel<64>, grid, dim3(256), 0, st, (const uint16_t*)vb, (const uint16_t*)dob,
-                                     (const float2*)rowstat, Lp, BHkv, BHq, part);
-    return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 static int g_bwd_waves = 0;           // waves per workgroup of the dQ and dK/dV passes, 0: chosen per problem; 4 / 8: forced (tests)

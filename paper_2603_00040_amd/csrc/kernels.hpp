@@ -15,9 +15,31 @@ int launch_prep(const void* x, int BH, int L, int D, bool quant, bool out_f16,
                 uint8_t* codes, uint8_t* scales, void* xf_pub, void* xr, void* xt, hipStream_t st,
                 const float* sub = nullptr);
 
-// The layout copies xr / xt (as launch_prep writes them) from an already quantized tensor: codes [BH, L, D/2] and E4M3
-// scale bytes [BH, L, D/16] in the layout attnqat_quantize produces.
-int launch_unpack(const uint8_t* codes, const uint8_t* scales, int BH, int L, int D, bool out_f16, void* xr, void* xt, hipStream_t st);
+// The pages of an NVFP4 KV cache as a source of K or V.
+struct PagedSrc {
+    const unsigned char* cache; const int* table; const int* kv_lens;
+    int max_pages, num_pages, Hkv, which;          // which: 0 the K part, 1 the V part
+};
+
+// Everything a forward or a backward prepares, in one launch.  Q and K become fp16 rows (zero padded to Lp = round_up(L, 128)), V
+// becomes transposed fp16 (forward; bf16 and unquantized with v_quant = false) or bf16 rows (backward).  From bf16 tensors, or
+// from codes and scales (attnqat_quantize's layout; codes[2] != null), or, K and V, from the pages of a cache (ps.cache != null).
+// With d_o the statistics of the backward are made as well (Alg. 3, first line): rowstat [BHq, Lp, 2] = {L log2(e), D / sqrt(d)},
+// D = rowsum(dO o O'), zeros in the padding rows; and in bounds, 3 * BHq * kBoundParts floats, partial maxima per head
+// that limit |dS|: |V^F_j| (kv heads), |dO_i|, |D_i| / sqrt(d).
+constexpr int kBoundParts = 64;
+struct PrepGroup {
+    const uint16_t *q, *k, *v;
+    const uint8_t *codes[3], *scales[3];
+    uint16_t *q_out, *k_out, *v_out;             // q_out / k_out null: that tensor is left out
+    const float* k_sub;                          // [BHkv, D]: subtracted from the rows of K before phi (K smoothing)
+    int BHq, BHkv, L, Lp, L_kv, Lp_kv, D;
+    bool v_quant;
+    PagedSrc ps;
+    const uint16_t* d_o; const void* o_acc; bool o_is_bf16; const float* lse; float rs /* 1 / sqrt(d) */;
+    float2* rowstat; float* bounds; uint16_t* dob;         // dob: zero-padded copy of dO, or null
+};
+int launch_prep_group(const PrepGroup& g, hipStream_t st);
 
 // Token mean of every channel of x [BH, L, D] bf16 -> mean [BH, D] fp32 (fp64 sums in a fixed order).
 // scratch: colmean_scratch_bytes() bytes.
@@ -42,9 +64,6 @@ int launch_fwd_varlen(const void* qh, const void* kh, const void* vt, int B, int
 size_t nvfp4_page_bytes(int Hkv, int D);
 int launch_kv_page_write(const void* k, const void* v, int Hkv, int n, int D, int pos0,
                          void* cache, int num_pages, const int* page_ids, hipStream_t st);
-// which: 0 the K part (xr: rows), 1 the V part (xt: transposed); copies laid out for max_pages * 128 positions per sequence
-int launch_unpack_pages(const void* cache, const int* page_table, const int* kv_lens, int B, int Hkv, int max_pages, int num_pages,
-                        int D, int which, void* xr, void* xt, hipStream_t st);
 
 // Alg. 1 for decode steps over the NVFP4 pages: at most decode_max_rows() query rows per (sequence, kv head), i.e.
 // (Hq / Hkv) * Lq of them; qh [B*Hkv][128][D] fp16 is phi(Q) with the rows of a kv group together (launch_prep on q taken as
@@ -60,17 +79,6 @@ int launch_decode(const void* qh, const void* cache, int num_pages, const int* p
 // qops / qsc: mode 1 on Q; kops / ksc: mode 1 on K (a wave's 32 keys as the A operand of the dK/dV pass); krec: mode 3 on K
 // (64-key records, the A operand of the dQ pass).
 struct MxScoreOps { const void *qops, *qsc, *kops, *ksc, *krec; };
-
-// Per-row statistics of the backward: rowstat [BHq, Lp, 2] = {L log2(e), D / sqrt(d)} with
-// D = rowsum(dO o O') (Alg. 3, first line); padding rows hold zeros.  d_o bf16, o_hp fp32, [rows, D].
-// o_acc: O' fp32, or (ablation) the bf16 O when o_is_bf16.
-int launch_delta(const void* d_o, const void* o_acc, bool o_is_bf16, const float* lse, int BHq, int L, int D,
-                 float* rowstat, hipStream_t st);
-
-// Per-head bounds that limit |dS| (partial maxima of |V^F_j|, |dO_i|, |D_i|/sqrt(d)): part holds
-// 3 * BHq * 64 floats.  vb, dob: bf16 row-major copies padded to Lp rows.
-int launch_bounds(const void* vb, const void* dob, const float* rowstat, int BHkv, int BHq, int L, int D,
-                  float* part, hipStream_t st);
 
 // Alg. 3, query-stationary pass: dQ.  qh, kh: fp16 copies; vb, dob: bf16 copies.
 int launch_bwd_dq(const void* qb, const void* kb, const void* vb, const void* dob,

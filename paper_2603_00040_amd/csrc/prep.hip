@@ -58,33 +58,28 @@ __device__ inline void dequant_block16(uint32_t clo, uint32_t chi, float s, floa
 // attnqat_quantize cut into pages.  Blocks run along d, so positions are independent of each other: a sequence grows by
 // writing its new positions only.
 __host__ __device__ inline size_t nvfp4_page_head_bytes(int D) { return (size_t)2 * 128 * (D / 2 + D / 16); }
-struct PagedSrc {
-    const unsigned char* cache; const int* table; const int* kv_lens;
-    int max_pages, num_pages, Hkv, which;          // which: 0 the K part, 1 the V part
-};
 // Codes and scale byte of block cb of position l (nullptr for a page id outside the cache).
 __device__ inline const unsigned char* nvfp4_page_part(const unsigned char* cache, int page, int num_pages, int Hkv, int h, int D, int which) {
     if (page < 0 || page >= num_pages) return nullptr;
     return cache + ((size_t)page * Hkv + h) * nvfp4_page_head_bytes(D) + (size_t)which * 128 * (D / 2 + D / 16);
 }
 
+// The 64 positions l0 .. l0 + 63 of head bh, by one workgroup.
 // PACKED (with QUANT = false): the input is not x but an already quantized tensor, codes [BH, L, D/2] and E4M3 scale bytes
 // [BH, L, D/16] in the public layout of attnqat_quantize (read through `codes` and `scales`); the kernel writes the
 // dequantized layout copies, the same values the quantizing variant writes for the tensor those codes came from.
 // PAGED (with PACKED): the quantized tensor is the K or the V part of the pages of an NVFP4 KV cache; bh = sequence * Hkv + kv
 // head, position l of sequence b is slot l % 128 of page table[b][l / 128], positions from kv_lens[b] on read as zeros, and
 // L is the capacity max_pages * 128 that the copies are laid out for.
-template <bool QUANT, bool OUT_F16, bool PACKED = false, bool PAGED = false>
-__global__ __launch_bounds__(256) void prep_kernel(
-    const uint16_t* __restrict__ x, int L, int Lp, int D,
+// NORM: n2 becomes the largest squared norm of the rows seen so far (in the lanes that hold a row's first block).
+template <bool QUANT, bool OUT_F16, bool PACKED, bool PAGED, bool NORM>
+__device__ __forceinline__ void prep_tile(
+    uint16_t (*tile)[128 + 2], int bh, int l0, const uint16_t* __restrict__ x, int L, int Lp, int D,
     uint8_t* __restrict__ codes, uint8_t* __restrict__ scales, uint16_t* __restrict__ xf_pub,
-    uint16_t* __restrict__ xr, uint16_t* __restrict__ xt, const float* __restrict__ sub, PagedSrc ps)
+    uint16_t* __restrict__ xr, uint16_t* __restrict__ xt, const float* __restrict__ sub, const PagedSrc& ps, float& n2)
 {
     static_assert(!(QUANT && PACKED), "a packed input is already quantized");
     static_assert(!PAGED || PACKED, "pages hold quantized tensors");
-    __shared__ uint16_t tile[64][128 + 2];
-    const int bh = blockIdx.y;
-    const int l0 = blockIdx.x * 64;
     const int nb = D / 16;                       // 16-element blocks per row
     const size_t in_base = (size_t)bh * L * D;
     int Lseq = L;
@@ -190,6 +185,13 @@ __global__ __launch_bounds__(256) void prep_kernel(
             for (int i = 0; i < 16; ++i) xf[i] = v[i];
         }
 
+        if constexpr (NORM) {                            // |row|^2: nb neighbouring lanes hold a row
+            float acc = 0.0f;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc = fmaf(xf[i], xf[i], acc);
+            for (int w = nb / 2; w >= 1; w >>= 1) acc += __shfl_xor(acc, w);
+            n2 = fmaxf(n2, acc);
+        }
         if (xf_pub && l < L) {                           // public bf16 copy, un-padded
             uint4v o0, o1;
 #pragma unroll
@@ -235,6 +237,171 @@ __global__ __launch_bounds__(256) void prep_kernel(
             *reinterpret_cast<uint4v*>(xt + ((size_t)bh * D + c) * Lp + l0 + kc * 8) = o;
         }
     }
+}
+
+// One tensor, every kind of output.
+template <bool QUANT, bool OUT_F16>
+__global__ __launch_bounds__(256) void prep_kernel(
+    const uint16_t* __restrict__ x, int L, int Lp, int D,
+    uint8_t* __restrict__ codes, uint8_t* __restrict__ scales, uint16_t* __restrict__ xf_pub,
+    uint16_t* __restrict__ xr, uint16_t* __restrict__ xt, const float* __restrict__ sub)
+{
+    __shared__ uint16_t tile[64][128 + 2];
+    float n2 = 0.0f;
+    prep_tile<QUANT, OUT_F16, false, false, false>(tile, blockIdx.y, blockIdx.x * 64, x, L, Lp, D, codes, scales, xf_pub, xr, xt, sub, PagedSrc{}, n2);
+}
+
+// The statistics that the backward needs of 64 rows of dO and O' (Alg. 3, first line): rowstat = {L log2(e), D / sqrt(d)} with
+// D = rowsum(dO o O') (padding rows hold {0, 0}), the largest |dO_i|^2 and |D_i| / sqrt(d) so far in n2 and dmax, and the zero-padded
+// copy of dO where one is asked for (dob).
+__device__ __forceinline__ void grad_tile(int bh, int l0, const uint16_t* __restrict__ dO, const void* __restrict__ o_acc, bool o_is_bf16,
+                                          const float* __restrict__ lse, int L, int Lp, int D, float rs,
+                                          float2* __restrict__ rowstat, uint16_t* __restrict__ dob, float& n2, float& dmax)
+{
+    const int nb = D / 16;
+    for (int blk = threadIdx.x; blk < 64 * nb; blk += 256) {
+        const int row = blk / nb, cb = blk % nb, l = l0 + row;
+        uint4v g[2] = {};
+        float dot = 0.0f, nrm = 0.0f;
+        if (l < L) {
+            const size_t off = ((size_t)bh * L + l) * D + cb * 16;
+            g[0] = reinterpret_cast<const uint4v*>(dO + off)[0];
+            g[1] = reinterpret_cast<const uint4v*>(dO + off)[1];
+            float o[16];
+            if (o_is_bf16) {                       // ablation: D from the low-precision output
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const uint4v w = reinterpret_cast<const uint4v*>(static_cast<const uint16_t*>(o_acc) + off)[t];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) { o[8 * t + 2 * i] = __uint_as_float(w[i] << 16); o[8 * t + 2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u); }
+                }
+            } else {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const floatx4 w = reinterpret_cast<const floatx4*>(static_cast<const float*>(o_acc) + off)[t];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) o[4 * t + i] = w[i];
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float lo = __uint_as_float(g[t][i] << 16), hi = __uint_as_float(g[t][i] & 0xFFFF0000u);
+                    dot += lo * o[8 * t + 2 * i] + hi * o[8 * t + 2 * i + 1];
+                    nrm = fmaf(lo, lo, fmaf(hi, hi, nrm));
+                }
+        }
+        for (int w = nb / 2; w >= 1; w >>= 1) { dot += __shfl_xor(dot, w); nrm += __shfl_xor(nrm, w); }
+        dot *= rs;
+        if (cb == 0) rowstat[(size_t)bh * Lp + l] = make_float2(l < L ? lse[(size_t)bh * L + l] * 1.4426950408889634f : 0.0f, dot);
+        n2 = fmaxf(n2, nrm);
+        dmax = fmaxf(dmax, fabsf(dot));
+        if (dob) {
+            uint4v* dst = reinterpret_cast<uint4v*>(dob + ((size_t)bh * Lp + l) * D + cb * 16);
+            dst[0] = g[0]; dst[1] = g[1];
+        }
+    }
+}
+
+// Largest value of a workgroup; every thread gets it.  (The barriers also keep `red` from being overwritten too early.)
+__device__ inline float wg_max(float v, float (&red)[4]) {
+#pragma unroll
+    for (int w = 32; w >= 1; w >>= 1) v = fmaxf(v, __shfl_xor(v, w));
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+}
+
+// All tensors that a forward or a backward prepares, as one launch.  Bound by HBM on large problems; on small ones a launch takes
+// 3 - 5 us whatever its size (start, first loads, last stores), and a forward had three of them, a backward six.
+// The maxima that bound |dS| come out of the same reads (V^F from its registers, dO and D as they
+// are formed) instead of a second pass over the copies, and dO is not copied where its rows need no padding.  Measured, one launch
+// per tensor -> one: training step of 2 heads, L = 256, d = 64 55.4 -> 37.0 us; 12 heads, L = 1560 199 -> 175 us; 4 x 32 heads of
+// 8 kv heads, L = 4096 3.22 -> 3.10 ms; inference on 32 heads, L = 777 36.6 -> 30.0 us.
+// A workgroup takes 64 positions of one head of one tensor; where a maximum is wanted (V and dO of a backward) it takes the
+// head's chunk of them, at most kBoundParts chunks per head, and writes the chunk's maxima; unused chunks are written as 0.
+// SRC: 0 Q, K, V in bf16; 1 all three packed (codes and scales); 2 Q in bf16, K and V in the pages of the cache.
+// VQUANT false: V only changes layout (bf16).  BWD: V as bf16 rows with its bound, and the dO / O' part; else V transposed.
+template <int SRC, bool VQUANT, bool BWD>
+__global__ __launch_bounds__(256) void prep_group_kernel(PrepGroup g, unsigned nblocks)
+{
+    __shared__ uint16_t tile[BWD ? 1 : 64][128 + 2];
+    __shared__ float red[4];
+    constexpr bool VF16 = VQUANT && !BWD;
+    const int tiles_q = g.Lp / 64, tiles_kv = g.Lp_kv / 64;
+    const int per_g = (tiles_q + kBoundParts - 1) / kBoundParts, nch_g = (tiles_q + per_g - 1) / per_g;        // 64-row tiles per chunk, chunks
+    const int per_v = BWD ? (tiles_kv + kBoundParts - 1) / kBoundParts : 1, nch_v = (tiles_kv + per_v - 1) / per_v;
+    const unsigned n_g = BWD ? (unsigned)g.BHq * nch_g : 0u, n_v = (unsigned)g.BHkv * nch_v;
+    const unsigned n_q = g.q_out ? (unsigned)g.BHq * tiles_q : 0u;
+    for (unsigned blk = blockIdx.x; blk < nblocks; blk += gridDim.x) {
+        unsigned i = blk;
+        float n2 = 0.0f;
+        if (BWD && i < n_g) {
+            const int bh = (int)(i / nch_g), ch = (int)(i % nch_g);
+            float dmax = 0.0f;
+            for (int t = ch * per_g; t < min(tiles_q, (ch + 1) * per_g); ++t)
+                grad_tile(bh, t * 64, g.d_o, g.o_acc, g.o_is_bf16, g.lse, g.L, g.Lp, g.D, g.rs, g.rowstat, g.dob, n2, dmax);
+            const float nrm = sqrtf(wg_max(n2, red)) * 1.0001f;           // rounded up a little: it is an upper bound
+            dmax = wg_max(dmax, red);
+            float* p1 = g.bounds + ((size_t)g.BHq + bh) * kBoundParts;
+            float* p2 = g.bounds + ((size_t)2 * g.BHq + bh) * kBoundParts;
+            if (threadIdx.x == 0) { p1[ch] = nrm; p2[ch] = dmax; }
+            if (ch == 0 && (int)threadIdx.x >= nch_g && threadIdx.x < kBoundParts) { p1[threadIdx.x] = 0.0f; p2[threadIdx.x] = 0.0f; }
+            continue;
+        }
+        i -= n_g;
+        if (i < n_v) {
+            const int bh = (int)(i / nch_v), ch = (int)(i % nch_v);
+            PagedSrc ps = g.ps;
+            ps.which = 1;
+            for (int t = ch * per_v; t < min(tiles_kv, (ch + 1) * per_v); ++t)
+                prep_tile<VQUANT && SRC == 0, VF16, SRC != 0, SRC == 2, BWD>(tile, bh, t * 64, g.v, g.L_kv, g.Lp_kv, g.D, const_cast<uint8_t*>(g.codes[2]),
+                    const_cast<uint8_t*>(g.scales[2]), nullptr, BWD ? g.v_out : nullptr, BWD ? nullptr : g.v_out, nullptr, ps, n2);
+            if constexpr (BWD) {
+                const float nrm = sqrtf(wg_max(n2, red)) * 1.0001f;
+                float* p0 = g.bounds + (size_t)bh * kBoundParts;
+                if (threadIdx.x == 0) p0[ch] = nrm;
+                if (ch == 0 && (int)threadIdx.x >= nch_v && threadIdx.x < kBoundParts) p0[threadIdx.x] = 0.0f;
+            } else if (gridDim.x < nblocks) __syncthreads();              // the next tile of this workgroup takes the LDS tile
+            continue;
+        }
+        i -= n_v;
+        const bool is_q = i < n_q;
+        if (!is_q) i -= n_q;
+        if (SRC == 2 && !is_q) {
+            PagedSrc ps = g.ps;
+            ps.which = 0;
+            prep_tile<false, true, SRC == 2, SRC == 2, false>(tile, (int)(i / tiles_kv), (int)(i % tiles_kv) * 64, nullptr, g.L_kv, g.Lp_kv, g.D, nullptr, nullptr, nullptr,
+                g.k_out, nullptr, nullptr, ps, n2);
+        } else {
+            const int per = is_q ? tiles_q : tiles_kv, w = is_q ? 0 : 1;
+            prep_tile<SRC != 1, true, SRC == 1, false, false>(tile, (int)(i / per), (int)(i % per) * 64, is_q ? g.q : g.k, is_q ? g.L : g.L_kv, is_q ? g.Lp : g.Lp_kv, g.D,
+                const_cast<uint8_t*>(g.codes[w]), const_cast<uint8_t*>(g.scales[w]), nullptr, is_q ? g.q_out : g.k_out, nullptr, is_q ? nullptr : g.k_sub, PagedSrc{}, n2);
+        }
+    }
+}
+
+int launch_prep_group(const PrepGroup& g, hipStream_t st)
+{
+    const int tiles_q = g.Lp / 64, tiles_kv = g.Lp_kv / 64;
+    const bool bwd = g.d_o != nullptr;
+    auto chunks = [](int tiles) { const int per = (tiles + kBoundParts - 1) / kBoundParts; return (tiles + per - 1) / per; };
+    long long n = (long long)g.BHkv * (bwd ? chunks(tiles_kv) : tiles_kv);
+    if (g.q_out) n += (long long)g.BHq * tiles_q;
+    if (g.k_out) n += (long long)g.BHkv * tiles_kv;
+    if (bwd) n += (long long)g.BHq * chunks(tiles_q);
+    if (n > 0x7FFFFFFFLL) return -1;
+    const unsigned nblocks = (unsigned)n, grid = min(nblocks, 1u << 22);       // (a grid has fewer than 2^32 threads)
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, g, nblocks); };
+    const bool packed = g.codes[2] != nullptr, paged = g.ps.cache != nullptr;
+    if (bwd)          { if (packed) go(prep_group_kernel<1, true, true>); else if (g.v_quant) go(prep_group_kernel<0, true, true>); else go(prep_group_kernel<0, false, true>); }
+    else if (paged)   go(prep_group_kernel<2, true, false>);
+    else if (packed)  go(prep_group_kernel<1, true, false>);
+    else if (g.v_quant) go(prep_group_kernel<0, true, false>);
+    else              go(prep_group_kernel<0, false, false>);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 // Writer of the NVFP4 KV cache: phi of n new positions pos0 .. pos0 + n - 1 of one sequence, k and v [Hkv, n, D] bf16, into
@@ -296,19 +463,6 @@ int launch_kv_page_write(const void* k, const void* v, int Hkv, int n, int D, in
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-// The layout copies of the forward (K row-major fp16, or V transposed fp16) from the pages of B sequences; the copies are laid
-// out for max_pages * 128 positions per sequence.
-int launch_unpack_pages(const void* cache, const int* page_table, const int* kv_lens, int B, int Hkv, int max_pages, int num_pages,
-                        int D, int which, void* xr, void* xt, hipStream_t st)
-{
-    const int L = max_pages * 128, Lp = round_up(L, kRowPad);
-    if ((size_t)B * Hkv > 65535) return -1;
-    PagedSrc ps{(const unsigned char*)cache, page_table, kv_lens, max_pages, num_pages, Hkv, which};
-    hipLaunchKernelGGL((prep_kernel<false, true, true, true>), dim3(Lp / 64, B * Hkv), dim3(256), 0, st, (const uint16_t*)nullptr, L, Lp, D,
-                       (uint8_t*)nullptr, (uint8_t*)nullptr, (uint16_t*)nullptr, (uint16_t*)xr, (uint16_t*)xt, (const float*)nullptr, ps);
-    return hipGetLastError() == hipSuccess ? 0 : -1;
-}
-
 // Token mean of every channel, for K smoothing: fp64 partial sums of NCHUNK row ranges, then their sum in a fixed
 // order, divided by L and rounded to fp32.  Deterministic; x [BH, L, D] bf16.
 constexpr int kMeanChunks = 32;
@@ -360,18 +514,7 @@ static int launch_prep_t(const void* x, int BH, int L, int D, uint8_t* codes, ui
     dim3 grid(Lp / 64, BH);
     hipLaunchKernelGGL((prep_kernel<QUANT, OUT_F16>), grid, dim3(256), 0, st,
                        (const uint16_t*)x, L, Lp, D, codes, scales, (uint16_t*)xf_pub,
-                       (uint16_t*)xr, (uint16_t*)xt, sub, PagedSrc{});
-    return hipGetLastError() == hipSuccess ? 0 : -1;
-}
-
-int launch_unpack(const uint8_t* codes, const uint8_t* scales, int BH, int L, int D, bool out_f16, void* xr, void* xt, hipStream_t st)
-{
-    const int Lp = round_up(L, kRowPad);
-    dim3 grid(Lp / 64, BH);
-    if (out_f16) hipLaunchKernelGGL((prep_kernel<false, true, true>), grid, dim3(256), 0, st, (const uint16_t*)nullptr, L, Lp, D,
-                                    const_cast<uint8_t*>(codes), const_cast<uint8_t*>(scales), (uint16_t*)nullptr, (uint16_t*)xr, (uint16_t*)xt, (const float*)nullptr, PagedSrc{});
-    else         hipLaunchKernelGGL((prep_kernel<false, false, true>), grid, dim3(256), 0, st, (const uint16_t*)nullptr, L, Lp, D,
-                                    const_cast<uint8_t*>(codes), const_cast<uint8_t*>(scales), (uint16_t*)nullptr, (uint16_t*)xr, (uint16_t*)xt, (const float*)nullptr, PagedSrc{});
+                       (uint16_t*)xr, (uint16_t*)xt, sub);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
