@@ -177,7 +177,9 @@ int attnqat_bwd_ablation(const void* q, const void* k, const void* v, const void
                          void* dq, void* dk, void* dv,
                          void* workspace, size_t workspace_bytes, void* stream);
 
-/* Bytes of workspace the call named by `which` (ATTNQAT_WS_*) needs; 0 for bad arguments. */
+/* Bytes of workspace the call named by `which` (ATTNQAT_WS_*) needs; 0 for bad arguments.  For the backward this includes room
+ * for the partial sums of problems that do not fill the chip; a smaller workspace that lacks only those is accepted, and the
+ * sums are then formed in one piece (slower; equal up to the rounding of the fp32 sums). */
 size_t attnqat_workspace_bytes(int which, int B, int Hq, int Hkv, int L, int d);
 
 /* The key tile size B_k of Alg. 1/2 that the forward kernels implement. */
@@ -441,11 +443,11 @@ int attnqat_debug_fwd_p_mx(const void* q, const void* k, const void* v,
  * on it adds to counts[0] the number of tiles the pass visited and to counts[1] the number with a non-zero P^F.
  * NULL switches it off (the default).
  *
- * attnqat_debug_bwd_waves: the dQ and dK/dV passes run workgroups of 4 waves (128 query rows / 128 keys), and workgroups
- * of 8 waves (256) for the passes (NVFP4, with or without the options, and MX) of a problem large enough to keep two of
- * them per compute unit, under a causal mask only from 16384 positions on; both compute the same sums over the same tiles
- * in the same order.  waves = 4 or 8 forces one shape (8 only where that variant exists), 0 returns to
- * the automatic choice.  Process-wide, for tests that compare the two shapes at small sizes.  ATTNQAT_EINVAL for any
+ * attnqat_debug_bwd_waves: problems whose workgroups fill the compute units evenly run the dQ and the dK/dV pass one after
+ * another, with workgroups of 4 waves (128 query rows / 128 keys) or, where that leaves enough of them, 8 waves (256); both
+ * compute the same sums over the same tiles in the same order.  All others run both passes in one launch of 4-wave workgroups,
+ * in which several workgroups may share the sum over the queries of a key tile (fp32 partial sums, added in a fixed order).
+ * waves = 4 or 8 forces separate passes of one shape (8 only where that variant exists), 0 returns to the automatic choice.  Process-wide, for tests that compare the two shapes at small sizes.  ATTNQAT_EINVAL for any
  * other value.
  */
 int attnqat_profile_enable(void* stream, int on);

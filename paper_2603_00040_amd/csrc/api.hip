@@ -138,7 +138,8 @@ FwdWs carve_fwd(void* ws, int B, int Hq, int Hkv, int L, int d, bool mx = false)
 // Workspace of the backward: row-major copies (Q^F, K^F fp16; V^F and dO bf16: dO is not exactly
 // representable in fp16), the per-row {L, D} pairs and the partial maxima that bound |dS|.
 struct BwdWs { void *qb, *kb, *vb, *dob; float* rowstat; float* bounds; void* tmp; double* kpart; float* kmean; size_t bytes;
-               void *qops, *qsc, *kops, *ksc, *krec; };
+               void *qops, *qsc, *kops, *ksc, *krec;
+               size_t bytes_min; float* part; };
 BwdWs carve_bwd(void* ws, int B, int Hq, int Hkv, int L, int d, bool mx = false)
 {
     const size_t Lp = round_up(L, kRowPad);
@@ -157,6 +158,10 @@ BwdWs carve_bwd(void* ws, int B, int Hq, int Hkv, int L, int d, bool mx = false)
     w.kops = mx ? c.take(mx_qops_bytes(B * Hkv, L, d)) : nullptr;
     w.ksc  = mx ? c.take(mx_qsc_bytes(B * Hkv, L)) : nullptr;
     w.krec = mx ? c.take(mx_ktrain_bytes(B * Hkv, L, d)) : nullptr;
+    // partial sums of dK and dV (the mask is not known here); without them (bytes_min) such a problem runs unsplit
+    w.bytes_min = c.off;
+    const size_t part = max(bwd_plan(B * Hq, B * Hkv, L, d, false).part_bytes, bwd_plan(B * Hq, B * Hkv, L, d, true).part_bytes);
+    w.part = part ? (float*)c.take(part) : nullptr;
     w.bytes = c.off;
     return w;
 }
@@ -719,7 +724,7 @@ static int bwd_common(const void* q, const void* k, const void* v, const void* d
     if (rc) return rc;
     const bool mx = p_quant == 2;
     BwdWs w = carve_bwd(workspace, B, Hq, Hkv, L, d, mx);
-    if (!workspace || workspace_bytes < w.bytes) return ATTNQAT_EWORKSPACE;
+    if (!workspace || workspace_bytes < w.bytes_min) return ATTNQAT_EWORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     prof_begin(st);
     // Q^F, K^F, V^F again (bit-identical to the forward's), D, the bounds of |dS|, and dO: the attention passes read it as it is
@@ -757,6 +762,15 @@ static int bwd_common(const void* q, const void* k, const void* v, const void* d
     }
     if (launch_prep_group(g, st)) return ATTNQAT_ELAUNCH;
     prof_mark("prep_qkvdo", st);
+    BwdPlan plan = bwd_plan(B * Hq, B * Hkv, L, d, causal != 0);
+    if (plan.joint && p_quant != 0) {
+        if (workspace_bytes < w.bytes && plan.splits > 1) { plan.splits = 1; plan.iters = (L + 31) / 32 * (Hq / Hkv); }
+        if (launch_bwd_joint(w.qb, w.kb, w.vb, dob, w.rowstat, w.bounds, B, Hq, Hkv, L, d, causal != 0, dq, dk, dv, p_quant, plan, w.part,
+                             dkdv_counts_of(st), st, p_dump, dump_row0, mx ? &mxo : nullptr))
+            return ATTNQAT_ELAUNCH;
+        prof_mark("bwd_joint", st);
+        return ATTNQAT_OK;
+    }
     if (launch_bwd_dq(w.qb, w.kb, w.vb, dob, w.rowstat, w.bounds, B, Hq, Hkv, L, d, causal != 0, dq, st, mx ? &mxo : nullptr))
         return ATTNQAT_ELAUNCH;
     prof_mark("bwd_dq", st);

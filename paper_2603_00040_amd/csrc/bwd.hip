@@ -89,23 +89,28 @@ __device__ inline int8v_t fp4_opnd(const uint4v& x) {
 // accumulator layout is that of the 16-bit products, and dP, dS and dQ are computed as before (dO, dS are 16-bit values).
 // NW waves of 32 query rows each share the K / V tiles: 4, or 8 for the passes of a large problem (half the
 // tile copies per query row).
-template <int D, bool CAUSAL, bool MXS, int NW = 4>
-__global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void bwd_dq_kernel(
-    const uint16_t* __restrict__ Qb, const uint16_t* __restrict__ Kb, const uint16_t* __restrict__ Vb,
-    const uint16_t* __restrict__ dOb,
-    const float2* __restrict__ rowstat, const float* __restrict__ bound_part, uint16_t* __restrict__ dQ,
-    int L, int Lp, int Hq, int G, int NHq, float c /* log2e/sqrt(d) */, float rs /* 1/sqrt(d) */,
-    const unsigned char* __restrict__ Qops, const uint32_t* __restrict__ Qsc, const unsigned char* __restrict__ Krec)
+struct DqArgs {
+    const uint16_t *Qb, *Kb, *Vb, *dOb;
+    const float2* rowstat; const float* bound_part; uint16_t* dQ;
+    int L, Lp, Hq, G, NHq; float c /* log2e/sqrt(d) */, rs /* 1/sqrt(d) */;
+    const unsigned char* Qops; const uint32_t* Qsc; const unsigned char* Krec;
+};
+template <int D, bool CAUSAL, bool MXS, int NW>
+__device__ __forceinline__ void bwd_dq_body(const DqArgs& A, int bh, int qt)
 {
     constexpr int DS = D / 16, MB = D / 32, KCH = D / 8, KLD = KCH / NW, QT = 32 * NW /* query rows of a workgroup */;
     constexpr int KSM = D / 64, KREC = mx_ktrain_rec_bytes(D);
     extern __shared__ __align__(256) unsigned char smem_raw[];
     DqSmem<D, MXS>& sm = *reinterpret_cast<DqSmem<D, MXS>*>(smem_raw);
+    const uint16_t *__restrict__ Qb = A.Qb, *__restrict__ Kb = A.Kb, *__restrict__ Vb = A.Vb, *__restrict__ dOb = A.dOb;
+    const float2* __restrict__ rowstat = A.rowstat;
+    const float* __restrict__ bound_part = A.bound_part;
+    uint16_t* __restrict__ dQ = A.dQ;
+    const unsigned char *__restrict__ Qops = A.Qops, *__restrict__ Krec = A.Krec;
+    const uint32_t* __restrict__ Qsc = A.Qsc;
+    const int L = A.L, Lp = A.Lp, Hq = A.Hq, G = A.G, NHq = A.NHq;
+    const float c = A.c, rs = A.rs;
 
-    const int nqt = (Lp + QT - 1) / QT;              // (Lp is a multiple of 128: with 8 waves the last workgroup may own only 128 rows)
-    int bh, qt;
-    head_tile_of_block(blockIdx.x, gridDim.x / nqt, nqt, bh, qt);
-    if (CAUSAL) qt = nqt - 1 - qt;
     const int b = bh / Hq, h = bh % Hq;
     const int bhkv = b * (Hq / G) + h / G;
     const int tid = threadIdx.x, lane = tid & 63, ln = lane & 31, hf = lane >> 5;
@@ -347,23 +352,36 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void bwd_dq_kernel(
     }
 }
 
+template <int D, bool CAUSAL, bool MXS, int NW = 4>
+__global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void bwd_dq_kernel(DqArgs A)
+{
+    const int nqt = (A.Lp + 32 * NW - 1) / (32 * NW);      // (Lp is a multiple of 128: with 8 waves the last workgroup may own only 128 rows)
+    int bh, qt;
+    head_tile_of_block(blockIdx.x, A.NHq, nqt, bh, qt);
+    bwd_dq_body<D, CAUSAL, MXS, NW>(A, bh, CAUSAL ? nqt - 1 - qt : qt);
+}
+
+static DqArgs dq_args(const void* qb, const void* kb, const void* vb, const void* dob, const float* rowstat, const float* bound_part,
+                      int B, int Hq, int Hkv, int L, int D, void* dq, const MxScoreOps* mx)
+{
+    const float rs = 1.0f / sqrtf((float)D);
+    return DqArgs{(const uint16_t*)qb, (const uint16_t*)kb, (const uint16_t*)vb, (const uint16_t*)dob, (const float2*)rowstat, bound_part,
+                  (uint16_t*)dq, L, round_up(L, kRowPad), Hq, Hq / Hkv, B * Hq, 1.4426950408889634f * rs, rs,
+                  (const unsigned char*)(mx ? mx->qops : nullptr), (const uint32_t*)(mx ? mx->qsc : nullptr),
+                  (const unsigned char*)(mx ? mx->krec : nullptr)};
+}
+
 template <int D, bool CAUSAL, bool MXS, int NW>
 static int launch_dq_v(const void* qb, const void* kb, const void* vb, const void* dob,
                        const float* rowstat, const float* bound_part, int B, int Hq, int Hkv, int L, void* dq, hipStream_t st,
                        const MxScoreOps* mx)
 {
-    const int Lp = round_up(L, kRowPad);
     const size_t smem = sizeof(DqSmem<D, MXS>);
     auto kern = bwd_dq_kernel<D, CAUSAL, MXS, NW>;
     static unsigned long long lds_set = 0;          // one per instantiation
     if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)smem, lds_set)) return -1;
-    const float rs = 1.0f / sqrtf((float)D);
-    hipLaunchKernelGGL(kern, dim3((unsigned)(B * Hq * ((Lp + 32 * NW - 1) / (32 * NW)))), dim3(64 * NW), smem, st,
-                       (const uint16_t*)qb, (const uint16_t*)kb, (const uint16_t*)vb,
-                       (const uint16_t*)dob, (const float2*)rowstat, bound_part, (uint16_t*)dq, L, Lp, Hq, Hq / Hkv, B * Hq,
-                       1.4426950408889634f * rs, rs,
-                       (const unsigned char*)(mx ? mx->qops : nullptr), (const uint32_t*)(mx ? mx->qsc : nullptr),
-                       (const unsigned char*)(mx ? mx->krec : nullptr));
+    const DqArgs A = dq_args(qb, kb, vb, dob, rowstat, bound_part, B, Hq, Hkv, L, D, dq, mx);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(B * Hq * ((A.Lp + 32 * NW - 1) / (32 * NW)))), dim3(64 * NW), smem, st, A);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -426,17 +444,22 @@ struct DkvSmem {
     unsigned char qrec[MXS ? 2 : 1][MXS ? (D / 64) * 1024 + 256 : 16];      // MX: Q operands of the FP4 instruction of a tile and their scale dwords
 };
 
+struct DkvArgs {
+    const uint16_t *Qb, *Kb, *Vb, *dOb;
+    const float2* rowstat; const float* bound_part;
+    uint16_t *dK, *dV; unsigned long long* tile_counts;
+    int L, Lp, Hq, G, NHq, NHkv; float c, rs;
+    float* pdump /* COUNT only, may be null: P^F of query rows [dump_row0, dump_row0 + 128), [B*Hq][128][L] */; int dump_row0;
+    const unsigned char* Qops; const uint32_t* Qsc;      // PQ == 2 (MX) only: the scores come from the
+    const unsigned char* Kops; const uint32_t* Ksc;      // codes, see bwd_dq_body
+    int splits, split_iters; float* part;                // SPLIT only: see bwd_joint_kernel
+};
+// SPLIT: only the query tiles piece * split_iters .. of the workgroup's key tile; where that is not all of them, the sums go to
+// `part` as fp32 for dkdv_reduce_kernel instead of to dK and dV.
 template <int D, bool CAUSAL, bool COUNT /* measurement / test variant: count tiles, dump P^F */,
           int PQ /* phi(P): 0 none (ablation: dV from the fp32 P), 1 NVFP4, 2 MX, 3 NVFP4 after the two-level row factor */,
-          int NW = 4 /* waves, 32 keys each */>
-__global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void bwd_dkdv_kernel(
-    const uint16_t* __restrict__ Qb, const uint16_t* __restrict__ Kb, const uint16_t* __restrict__ Vb,
-    const uint16_t* __restrict__ dOb, const float2* __restrict__ rowstat, const float* __restrict__ bound_part,
-    uint16_t* __restrict__ dK, uint16_t* __restrict__ dV, unsigned long long* __restrict__ tile_counts,
-    int L, int Lp, int Hq, int G, int NHq, float c, float rs,
-    float* __restrict__ pdump /* COUNT only, may be null: P^F of query rows [dump_row0, dump_row0 + 128), [B*Hq][128][L] */, int dump_row0,
-    const unsigned char* __restrict__ Qops, const uint32_t* __restrict__ Qsc,      // PQ == 2 (MX) only: the scores come from the
-    const unsigned char* __restrict__ Kops, const uint32_t* __restrict__ Ksc)      // codes, see bwd_dq_kernel
+          int NW /* waves, 32 keys each */, bool SPLIT>
+__device__ __forceinline__ void bwd_dkdv_body(const DkvArgs& A, int bhkv, int kt_, int piece)
 {
     constexpr bool MXS = PQ == 2;
     constexpr int KSM = D / 64, QREC = KSM * 1024 + 256;
@@ -446,11 +469,19 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void bwd_dkdv_kernel(
     extern __shared__ __align__(256) unsigned char smem_raw[];   // XORs of address bits 5..7 below commute with adding this base
     DkvSmem<D, MXS, NW>& sm = *reinterpret_cast<DkvSmem<D, MXS, NW>*>(smem_raw);
 
+    const uint16_t *__restrict__ Qb = A.Qb, *__restrict__ Kb = A.Kb, *__restrict__ Vb = A.Vb, *__restrict__ dOb = A.dOb;
+    const float2* __restrict__ rowstat = A.rowstat;
+    const float* __restrict__ bound_part = A.bound_part;
+    uint16_t *__restrict__ dK = A.dK, *__restrict__ dV = A.dV;
+    unsigned long long* __restrict__ tile_counts = A.tile_counts;
+    float* __restrict__ pdump = A.pdump;
+    const unsigned char *__restrict__ Qops = A.Qops, *__restrict__ Kops = A.Kops;
+    const uint32_t *__restrict__ Qsc = A.Qsc, *__restrict__ Ksc = A.Ksc;
+    const int L = A.L, Lp = A.Lp, Hq = A.Hq, G = A.G, NHq = A.NHq, dump_row0 = A.dump_row0;
+    const float c = A.c, rs = A.rs;
+
     constexpr int KT = 32 * NW;                      // keys of a workgroup
-    const int nkt = (Lp + KT - 1) / KT;              // (Lp is a multiple of 128: with 8 waves the last workgroup may own only 128 keys)
-    int bhkv, kt_;
-    head_tile_of_block(blockIdx.x, gridDim.x / nkt, nkt, bhkv, kt_);    // key tiles in increasing order: under a causal
-    const int Hkv = Hq / G;                         // mask the first tiles see the most queries
+    const int Hkv = Hq / G;
     const int b = bhkv / Hkv, hk = bhkv % Hkv;
     const int tid = threadIdx.x, lane = tid & 63, ln = lane & 31, hf = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);        // scalar: LDS destinations and branches use it
@@ -486,7 +517,16 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void bwd_dkdv_kernel(
     const int nq32 = (L + 31) / 32;
     const int qt_first = CAUSAL ? (kt_ * KT) / 32 : 0;
     const int per_head = nq32 - qt_first;
-    const int niter = per_head > 0 ? per_head * G : 0;
+    int niter = per_head > 0 ? per_head * G : 0;
+    int first = 0;                                   // the first of this workgroup's query tiles
+    bool whole = true;
+    if constexpr (SPLIT) {
+        const int pieces = (niter + A.split_iters - 1) / A.split_iters;
+        if (piece >= pieces) return;                 // (workgroup-uniform; no barrier passed yet)
+        whole = pieces == 1;
+        first = piece * niter / pieces;
+        niter = (piece + 1) * niter / pieces - first;
+    }
     const size_t bh0 = (size_t)b * Hq + hk * G;      // first query head of the group
 
     // dS goes to fp16 after multiplication by ds_scale = 2^k, one k for the kv head, from the bound
@@ -511,7 +551,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void bwd_dkdv_kernel(
         slot_off[i] = 2u * (uint32_t)((slot / KCH) * D + 8 * swz<KCH>(slot / KCH, slot % KCH));
     }
     // (head, tile) walk without divisions: state of the NEXT tile to load and of the current tile
-    int ld_g = 0, ld_t = 0;                          // next tile to issue: head index in group, tile in head
+    int ld_g = SPLIT ? first / per_head : 0, ld_t = SPLIT ? first % per_head : 0;      // next tile to issue: head index in group, tile in head
+    int cur_g = ld_g, cur_t = ld_t;
     auto issue_next = [&](int buf) __attribute__((always_inline)) {
         const size_t row0 = (bh0 + ld_g) * Lp + (size_t)(qt_first + ld_t) * 32;
         if (loader) {
@@ -553,7 +594,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void bwd_dkdv_kernel(
 
     // {L_i log2(e), D_i / sqrt(d)} of this lane's query row of the next tile
     float2 st_n = make_float2(0.0f, 0.0f);
-    if (niter > 0) { issue_next(0); st_n = rowstat[bh0 * Lp + (size_t)qt_first * 32 + ln]; }
+    if (niter > 0) { issue_next(0); st_n = rowstat[(bh0 + cur_g) * Lp + (size_t)(qt_first + cur_t) * 32 + ln]; }
     // every load of the prologue must have arrived before the loop (see the dQ pass)
 #pragma unroll
     for (int ds = 0; ds < DS; ++ds) {
@@ -569,7 +610,6 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void bwd_dkdv_kernel(
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
 
-    int cur_g = 0, cur_t = 0;
     unsigned n_tiles = 0, n_pf_tiles = 0;            // measurement only (wave-uniform)
     for (int it = 0; it < niter; ++it) {
         const int buf = it & 1;
@@ -867,6 +907,24 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void bwd_dkdv_kernel(
     }
 
     // accumulators: row = key 8*(i>>2) + 4*hf + (i&3) of the wave, column d = 32*nb + ln
+    if constexpr (SPLIT) {
+        if (!whole) {
+            // four accumulators (keys 8 t4 + 4 hf .. + 3) at a time, as they lie in the lanes: 1 KiB per wave and store
+            floatx4* dst = reinterpret_cast<floatx4*>(A.part) + (((size_t)bhkv * (Lp / KT) + kt_) * A.splits + piece) * (2 * NB * 4 * NW * 64) + wave * 64 + lane;
+            const float un = rs / rs_s;              // 1 / ds_scale, exact: a power of two
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int t4 = 0; t4 < 4; ++t4) {
+                    floatx4 wk, wv;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) { wk[e] = dk[nb][4 * t4 + e] * un; wv[e] = dv[nb][4 * t4 + e]; }
+                    dst[(size_t)(nb * 4 + t4) * (NW * 64)] = wk;
+                    dst[(size_t)((NB + nb) * 4 + t4) * (NW * 64)] = wv;
+                }
+            return;
+        }
+    }
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -880,24 +938,38 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void bwd_dkdv_kernel(
         }
 }
 
+template <int D, bool CAUSAL, bool COUNT, int PQ, int NW = 4>
+__global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void bwd_dkdv_kernel(DkvArgs A)
+{
+    const int nkt = (A.Lp + 32 * NW - 1) / (32 * NW);      // (Lp is a multiple of 128: with 8 waves the last workgroup may own only 128 keys)
+    int bhkv, kt;
+    head_tile_of_block(blockIdx.x, A.NHkv, nkt, bhkv, kt);    // key tiles in increasing order: under a causal mask the first see the most queries
+    bwd_dkdv_body<D, CAUSAL, COUNT, PQ, NW, false>(A, bhkv, kt, 0);
+}
+
+static DkvArgs dkv_args(const void* qb, const void* kb, const void* vb, const void* dob, const float* rowstat, const float* bound_part,
+                        int B, int Hq, int Hkv, int L, int D, void* dk, void* dv, const MxScoreOps* mx)
+{
+    const float rs = 1.0f / sqrtf((float)D);
+    return DkvArgs{(const uint16_t*)qb, (const uint16_t*)kb, (const uint16_t*)vb, (const uint16_t*)dob, (const float2*)rowstat, bound_part,
+                   (uint16_t*)dk, (uint16_t*)dv, nullptr, L, round_up(L, kRowPad), Hq, Hq / Hkv, B * Hq, B * Hkv, 1.4426950408889634f * rs, rs,
+                   nullptr, 0, (const unsigned char*)(mx ? mx->qops : nullptr), (const uint32_t*)(mx ? mx->qsc : nullptr),
+                   (const unsigned char*)(mx ? mx->kops : nullptr), (const uint32_t*)(mx ? mx->ksc : nullptr), 1, 0, nullptr};
+}
+
 template <int D, bool CAUSAL, bool COUNT, int PQ, int NW>
 static int launch_dkdv_v(const void* qb, const void* kb, const void* vb, const void* dob,
                          const float* rowstat, const float* bound_part,
                          int B, int Hq, int Hkv, int L, void* dk, void* dv, unsigned long long* tile_counts,
                          hipStream_t st, float* p_dump, int dump_row0, const MxScoreOps* mx)
 {
-    const int Lp = round_up(L, kRowPad);
     const size_t smem = sizeof(DkvSmem<D, PQ == 2, NW>);
     auto kern = bwd_dkdv_kernel<D, CAUSAL, COUNT, PQ, NW>;
     static unsigned long long lds_set = 0;          // one per instantiation
     if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)smem, lds_set)) return -1;
-    const float rs = 1.0f / sqrtf((float)D);
-    hipLaunchKernelGGL(kern, dim3((unsigned)(B * Hkv * ((Lp + 32 * NW - 1) / (32 * NW)))), dim3(64 * NW), smem, st,
-                       (const uint16_t*)qb, (const uint16_t*)kb, (const uint16_t*)vb,
-                       (const uint16_t*)dob, (const float2*)rowstat, bound_part, (uint16_t*)dk, (uint16_t*)dv, tile_counts,
-                       L, Lp, Hq, Hq / Hkv, B * Hq, 1.4426950408889634f * rs, rs, p_dump, dump_row0,
-                       (const unsigned char*)(mx ? mx->qops : nullptr), (const uint32_t*)(mx ? mx->qsc : nullptr),
-                       (const unsigned char*)(mx ? mx->kops : nullptr), (const uint32_t*)(mx ? mx->ksc : nullptr));
+    DkvArgs A = dkv_args(qb, kb, vb, dob, rowstat, bound_part, B, Hq, Hkv, L, D, dk, dv, mx);
+    A.tile_counts = tile_counts; A.pdump = p_dump; A.dump_row0 = dump_row0;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(B * Hkv * ((A.Lp + 32 * NW - 1) / (32 * NW)))), dim3(64 * NW), smem, st, A);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -929,6 +1001,161 @@ int launch_bwd_dkdv(const void* qb, const void* kb, const void* vb, const void* 
                                 : launch_dkdv_t<128, false>(qb, kb, vb, dob, rowstat, bound_part, B, Hq, Hkv, L, dk, dv, tile_counts, p_quant, st, p_dump, dump_row0, mx);
     if (D == 64)  return causal ? launch_dkdv_t<64, true>(qb, kb, vb, dob, rowstat, bound_part, B, Hq, Hkv, L, dk, dv, tile_counts, p_quant, st, p_dump, dump_row0, mx)
                                 : launch_dkdv_t<64, false>(qb, kb, vb, dob, rowstat, bound_part, B, Hq, Hkv, L, dk, dv, tile_counts, p_quant, st, p_dump, dump_row0, mx);
+    return -1;
+}
+
+// ------------------------------------------------------------------ both passes in one launch
+// A problem that gives the chip few workgroups, or a last round that is mostly empty, runs both passes side by side (four-wave
+// workgroups of either kind), and where even that leaves compute units idle, or a causal mask leaves one with a tile that is
+// several times the average, the query tiles of a key tile are shared by several workgroups ("pieces" of about split_iters query
+// tiles), whose fp32 sums dkdv_reduce_kernel adds in order.  The arithmetic of a tile and the order inside a piece are those of
+// bwd_dkdv_kernel.  The dK/dV pieces come first, the dQ tiles fill in behind them (alternating the two kinds was 0 - 30 % slower),
+// or the other way round where a dQ tile is the longer piece.  Measured, backward call, passes one after another -> joint
+// without pieces -> as planned by bwd_plan: 2 x 16/4 heads, L = 3001 causal 617 -> 518 -> 292 us (MX 683 -> 596 -> 328 us);
+// 8/2 heads, L = 8192 causal 1264 -> 1139 -> 475 us; 12 heads, L = 1560 120 -> 91 -> 82 us; 4 x 32/8 heads, L = 4096 causal
+// 2.09 -> 1.85 ms (no pieces); 12 heads, L = 6240 833 -> 698 us (no pieces).
+template <int D, bool CAUSAL, int PQ, bool COUNT = false /* the measurement variant of bwd_dkdv_body */>
+__global__ __launch_bounds__(256, 2) void bwd_joint_kernel(DqArgs Q, DkvArgs K, int n_dkdv, int n_dq, bool dq_first)
+{
+    const int nt = K.Lp / 128;
+    int block = blockIdx.x;
+    const bool dkdv = dq_first ? block >= n_dq : block < n_dkdv;
+    if (dkdv == dq_first) block -= dq_first ? n_dq : n_dkdv;
+    // Under a causal mask the longest tiles of all heads first (32 heads, L = 4096: 3 - 5 %), but head after head on long sequences,
+    // where the heads an XCD works on would no longer share its L2 (4 x 32/8 heads, L = 8192: 7.0 against 7.4 ms in MX).
+    const bool by_length = CAUSAL && K.Lp < 8192;
+    auto place = [&](int heads, int per_head, int& head, int& rank) __attribute__((always_inline)) {
+        if (by_length) {
+            const bool pinned = (heads & 7) == 0;
+            const int hx = pinned ? heads >> 3 : heads, i = pinned ? block >> 3 : block;
+            head = pinned ? (block & 7) + 8 * (i % hx) : i % hx;
+            rank = i / hx;
+        } else head_tile_of_block(block, heads, per_head, head, rank);
+    };
+    int head, rank;
+    if (dkdv) {
+        if (block >= K.NHkv * nt * K.splits) return;            // (n_dkdv and n_dq are rounded up to whole rounds of the XCDs)
+        place(K.NHkv, nt * K.splits, head, rank);
+        bwd_dkdv_body<D, CAUSAL, COUNT, PQ, 4, true>(K, head, rank / K.splits, rank % K.splits);
+    } else {
+        if (block >= Q.NHq * nt) return;
+        place(Q.NHq, nt, head, rank);
+        bwd_dq_body<D, CAUSAL, PQ == 2, 4>(Q, head, CAUSAL ? nt - 1 - rank : rank);
+    }
+}
+
+// dK and dV of the key tiles whose query tiles several workgroups shared: their fp32 sums added in order.  A workgroup takes 32
+// columns of dK or dV of one key tile.
+template <int D, bool CAUSAL>
+__global__ __launch_bounds__(256) void dkdv_reduce_kernel(const float* __restrict__ part, uint16_t* __restrict__ dK, uint16_t* __restrict__ dV,
+                                                          int L, int Lp, int G, int splits, int split_iters)
+{
+    constexpr int NB = D / 32;
+    const int nt = Lp / 128, tile = blockIdx.x / (2 * NB), col = blockIdx.x % (2 * NB);
+    const int bhkv = tile / nt, kt = tile % nt;
+    const int niter = ((L + 31) / 32 - (CAUSAL ? kt * 4 : 0)) * G, np = (niter + split_iters - 1) / split_iters;
+    if (np < 2) return;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, ln = lane & 31, hf = lane >> 5;
+    const floatx4* src = reinterpret_cast<const floatx4*>(part) + (size_t)tile * splits * (2 * NB * 4 * 256) + (size_t)col * (4 * 256) + threadIdx.x;
+    floatx4 sum[4];
+#pragma unroll
+    for (int t4 = 0; t4 < 4; ++t4) sum[t4] = src[t4 * 256];
+    for (int p = 1; p < np; ++p) {
+        src += 2 * NB * 4 * 256;
+#pragma unroll
+        for (int t4 = 0; t4 < 4; ++t4) {
+            const floatx4 x = src[t4 * 256];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum[t4][e] += x[e];
+        }
+    }
+    uint16_t* out = col < NB ? dK : dV;
+#pragma unroll
+    for (int t4 = 0; t4 < 4; ++t4)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int key = kt * 128 + wave * 32 + 8 * t4 + 4 * hf + e;
+            if (key < L) out[((size_t)bhkv * L + key) * D + 32 * (col % NB) + ln] = f32_to_bf16_rne(sum[t4][e]);
+        }
+}
+
+// Whether a backward runs both passes in one launch, and how many query tiles a dK/dV workgroup takes.
+// Joint: everything except the problems whose eight-wave workgroups (wide_workgroups) fill their rounds of the compute units to
+// 97 % on average, where the halved tile copies win by 2 - 3 % (24 heads, L = 8192: 2.09 against 2.14 ms; 12 x 2 heads, L = 32760:
+// 32.0 against 33.0 ms), while rounds filled to 95, 92 and 73 % lose to the joint launch by 2, 5 and 24 % (40 heads, L = 20000
+// and 12000; 12 heads of 64, L = 12000).  Under a causal mask the two are even at 32768 positions (46.1 ms) and below that
+// joint wins by 1 - 4 %.
+// Pieces: time is counted in query tiles of the dK/dV pass (1.45 us); a 64-key tile of a dQ workgroup takes 1.16 of them.  With W the
+// work per compute unit, pieces of 0.45 W came out best or within 10 % of it over 16 shapes (8 sizes of piece each), as long as
+//   * a piece is not much shorter than the average dQ tile, which it would only have to wait for,
+//   * the pieces (and, if there are few, the dQ tiles) fit the 2 workgroups per compute unit at once: a second round of
+//     pieces costs more than it evens out (12 heads, L = 1560: 312 pieces 83 us, 468 pieces 107 us).
+BwdPlan bwd_plan(int BHq, int BHkv, int L, int D, bool causal)
+{
+    BwdPlan p{false, 1, 0, 0, false};
+    if (__atomic_load_n(&g_bwd_waves, __ATOMIC_RELAXED) != 0) return p;
+    const int Lp = round_up(L, kRowPad), nt = Lp / 128, G = BHq / BHkv, nq32 = (L + 31) / 32;
+    const long long cus = device_cu_count(), n8q = (long long)BHq * ((Lp + 255) / 256), n8kv = (long long)BHkv * ((Lp + 255) / 256);
+    auto fill = [&](long long n) { return (double)n / (double)((n + cus - 1) / cus * cus); };
+    if (causal ? Lp >= 32768 && n8kv >= 2 * cus : n8kv >= 2 * cus && fill(n8q) + fill(n8kv) >= 2 * 0.97) return p;
+    p.joint = true;
+    const long long whole = (long long)nq32 * G;
+    p.iters = (int)(whole < 0x7FFFFFFF ? whole : 0x7FFFFFFF);
+    const double dq_longest = 1.16 * (Lp / 64), dq_mean = causal ? 0.5 * dq_longest : dq_longest;
+    const double dkv_mean = (double)G * (causal ? nq32 - 2.0 * (nt - 1) : (double)nq32);
+    const double W = (double)nt * (BHkv * dkv_mean + BHq * dq_mean) / (double)cus;
+    double T = fmax(fmax(0.45 * W, 0.6 * dq_mean), 4.0);
+    if (T < (double)whole) {
+        const long long ndq = (long long)BHq * nt, room = 2 * cus - (ndq < cus ? ndq : 0);
+        auto pieces = [&](int t) {
+            long long n = 0;
+            for (int kt = 0; kt < nt; ++kt) n += ((long long)(nq32 - (causal ? 4 * kt : 0)) * G + t - 1) / t;
+            return n * BHkv;
+        };
+        while (T < (double)whole && pieces((int)T) > room) T = T * 1.04 + 1.0;
+        if (T < (double)whole) {
+            p.splits = (int)((whole + (int)T - 1) / (int)T);
+            p.iters = (int)T;
+            p.part_bytes = (size_t)BHkv * nt * p.splits * 2 * 128 * D * 4;
+        }
+    }
+    p.dq_first = dq_longest > 1.5 * p.iters;      // (one head, L = 16000 causal, 192 pieces: 348 against 405 us)
+    return p;
+}
+
+template <int D, bool CAUSAL, int PQ, bool COUNT = false>
+static int launch_joint_t(const DqArgs& Q, DkvArgs K, const BwdPlan& plan, float* part, hipStream_t st)
+{
+    const size_t dq_lds = sizeof(DqSmem<D, PQ == 2>), dkv_lds = sizeof(DkvSmem<D, PQ == 2, 4>), smem = dq_lds > dkv_lds ? dq_lds : dkv_lds;
+    auto kern = bwd_joint_kernel<D, CAUSAL, PQ, COUNT>;
+    static unsigned long long lds_set = 0;          // one per instantiation
+    if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)smem, lds_set)) return -1;
+    K.splits = plan.splits; K.split_iters = plan.iters; K.part = part;
+    const int nt = K.Lp / 128, n_dkdv = round_up(K.NHkv * nt * K.splits, 8), n_dq = round_up(Q.NHq * nt, 8);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(n_dkdv + n_dq)), dim3(256), smem, st, Q, K, n_dkdv, n_dq, plan.dq_first);
+    if (hipGetLastError() != hipSuccess) return -1;
+    if (plan.splits > 1)
+        hipLaunchKernelGGL((dkdv_reduce_kernel<D, CAUSAL>), dim3((unsigned)(K.NHkv * nt * 2 * (D / 32))), dim3(256), 0, st,
+                           part, K.dK, K.dV, K.L, K.Lp, K.G, K.splits, K.split_iters);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int launch_bwd_joint(const void* qb, const void* kb, const void* vb, const void* dob, const float* rowstat, const float* bound_part,
+                     int B, int Hq, int Hkv, int L, int D, bool causal, void* dq, void* dk, void* dv, int p_quant,
+                     const BwdPlan& plan, float* part, unsigned long long* tile_counts, hipStream_t st, float* p_dump, int dump_row0,
+                     const MxScoreOps* mx)
+{
+    if (p_quant != 1) { if (p_dump) return -1; tile_counts = nullptr; }
+    if (p_quant < 1 || p_quant > 3 || (p_quant == 2) != (mx != nullptr) || (plan.splits > 1 && !part)) return -1;
+    const DqArgs Q = dq_args(qb, kb, vb, dob, rowstat, bound_part, B, Hq, Hkv, L, D, dq, mx);
+    DkvArgs K = dkv_args(qb, kb, vb, dob, rowstat, bound_part, B, Hq, Hkv, L, D, dk, dv, mx);
+    K.tile_counts = tile_counts; K.pdump = p_dump; K.dump_row0 = dump_row0;
+    const bool count = tile_counts || p_dump;
+#define AQ_J(DD, C) (count ? launch_joint_t<DD, C, 1, true>(Q, K, plan, part, st) : p_quant == 1 ? launch_joint_t<DD, C, 1>(Q, K, plan, part, st) : p_quant == 2 ? launch_joint_t<DD, C, 2>(Q, K, plan, part, st) \
+                                                                                   : launch_joint_t<DD, C, 3>(Q, K, plan, part, st))
+    if (D == 128) return causal ? AQ_J(128, true) : AQ_J(128, false);
+    if (D == 64)  return causal ? AQ_J(64, true) : AQ_J(64, false);
+#undef AQ_J
     return -1;
 }
 

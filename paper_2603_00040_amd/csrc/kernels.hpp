@@ -94,6 +94,15 @@ int launch_bwd_dkdv(const void* qb, const void* kb, const void* vb, const void* 
                     int p_quant /* phi(P): 0 none (ablation), 1 NVFP4, 2 MX, 3 NVFP4 with the two-level row factor */, hipStream_t st,
                     float* p_dump = nullptr /* test hook, p_quant 1 only: P^F of query rows [dump_row0, dump_row0 + 128), [B*Hq][128][L] */,
                     int dump_row0 = 0, const MxScoreOps* mx = nullptr /* p_quant 2: required */);
+// Both passes in one launch (plan.joint: problems that do not fill the chip evenly), the query tiles of a key tile shared by up to
+// plan.splits workgroups of plan.iters query tiles whose sums meet in `part` (plan.part_bytes bytes).  launch_bwd_dq and
+// launch_bwd_dkdv run what is not joint.
+struct BwdPlan { bool joint; int splits, iters; size_t part_bytes; bool dq_first; };
+BwdPlan bwd_plan(int BHq, int BHkv, int L, int D, bool causal);
+int launch_bwd_joint(const void* qb, const void* kb, const void* vb, const void* dob, const float* rowstat, const float* bound_part,
+                     int B, int Hq, int Hkv, int L, int D, bool causal, void* dq, void* dk, void* dv, int p_quant /* 1, 2 or 3 */,
+                     const BwdPlan& plan, float* part, unsigned long long* tile_counts, hipStream_t st, float* p_dump, int dump_row0,
+                     const MxScoreOps* mx);
 // Waves per workgroup of the dQ and dK/dV passes: 0 = chosen per problem (the default), 4 or 8 = forced where that
 // variant exists (8: not the ablation and not the counting variant).  Process-wide; for tests.
 void set_bwd_waves(int waves);

@@ -1,0 +1,46 @@
+"""The backward as one launch of both passes, several workgroups sharing the query tiles of a key tile, against the two passes one
+after another (their parity with the oracle is tested elsewhere)."""
+import pytest
+import torch
+
+from tests.gpu_util import random_inputs, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+# tiles of 32 queries and 128 keys: below, at and above their edges; one head with many keys (dQ tiles first), few kv heads with
+# many query heads (pieces span heads), whole rounds of the compute units' slots and more
+@pytest.mark.parametrize("B,Hq,Hkv,L,d,causal", [(1, 1, 1, 1, 64, True), (1, 2, 1, 33, 128, True), (1, 8, 1, 129, 64, False), (1, 32, 8, 777, 128, True),
+                                                 (1, 12, 12, 1560, 128, False), (1, 1, 1, 4200, 128, True), (2, 16, 2, 1000, 64, True), (1, 40, 40, 1664, 64, True)])
+@pytest.mark.parametrize("mx", [False, True])
+def test_joint_equals_separate_passes(B, Hq, Hkv, L, d, causal, mx):
+    import paper_2603_00040_amd as aq
+    x = random_inputs(B, Hq, Hkv, L, d, seed=L + Hq)
+    q, k, v, do = (to_dev(x[n]) for n in ("q", "k", "v", "do"))
+    fwd, bwd, which = (aq.attnqat_fwd_mx, aq.attnqat_bwd_mx, aq.WS_BWD_MX) if mx else (aq.attnqat_fwd, aq.attnqat_bwd, aq.WS_BWD)
+    _, lse, ohp = fwd(q, k, v, causal)
+    dq, dk, dv = bwd(q, k, v, do, lse, ohp, causal)
+    again = bwd(q, k, v, do, lse, ohp, causal)
+    assert all(torch.equal(a, b) for a, b in zip((dq, dk, dv), again))
+    aq.debug_bwd_waves(4)
+    try:
+        rq, rk, rv = bwd(q, k, v, do, lse, ohp, causal)
+    finally:
+        aq.debug_bwd_waves(0)
+    assert torch.equal(dq, rq)
+    for a, r in ((dk, rk), (dv, rv)):
+        # the same fp32 terms added in another grouping (errors of 2^-24 times the sum of their magnitudes, here at most some
+        # hundred times the largest result), then one rounding to bf16 each: apart by at most one spacing
+        a, r = a.float(), r.float()
+        assert bool(((a - r).abs() <= 2.0 ** -7 * r.abs() + 1e-4 * r.abs().max()).all())
+    # a workspace without room for the partial sums: one workgroup per key tile, the order of the separate passes
+    ws = torch.empty(aq.workspace_bytes(which, B, Hq, Hkv, L, d) - 1, dtype=torch.uint8, device="cuda")
+    big = [torch.empty_like(t) for t in (q, k, v)]
+    s = torch.cuda.current_stream().cuda_stream
+    f = aq.lib().attnqat_bwd_mx if mx else aq.lib().attnqat_bwd
+    rc = f(q.data_ptr(), k.data_ptr(), v.data_ptr(), do.data_ptr(), lse.data_ptr(), ohp.data_ptr(), B, Hq, Hkv, L, d, int(causal), aq.BF16,
+           *(t.data_ptr() for t in big), ws.data_ptr(), ws.numel(), s)
+    if rc == 0:
+        assert all(torch.equal(a, b) for a, b in zip(big, (rq, rk, rv)))
+    else:
+        assert rc == aq.EWORKSPACE and torch.equal(dk, rk)      # no partial sums in this problem
