@@ -139,7 +139,8 @@ FwdWs carve_fwd(void* ws, int B, int Hq, int Hkv, int L, int d, bool mx = false)
 // representable in fp16), the per-row {L, D} pairs and the partial maxima that bound |dS|.
 struct BwdWs { void *qb, *kb, *vb, *dob; float* rowstat; float* bounds; void* tmp; double* kpart; float* kmean; size_t bytes;
                void *qops, *qsc, *kops, *ksc, *krec;
-               size_t bytes_min; float* part; };
+               size_t bytes_min, bytes_split; float* part; };
+constexpr size_t kSmallBwdWs = (size_t)2 << 20;
 BwdWs carve_bwd(void* ws, int B, int Hq, int Hkv, int L, int d, bool mx = false)
 {
     const size_t Lp = round_up(L, kRowPad);
@@ -158,11 +159,14 @@ BwdWs carve_bwd(void* ws, int B, int Hq, int Hkv, int L, int d, bool mx = false)
     w.kops = mx ? c.take(mx_qops_bytes(B * Hkv, L, d)) : nullptr;
     w.ksc  = mx ? c.take(mx_qsc_bytes(B * Hkv, L)) : nullptr;
     w.krec = mx ? c.take(mx_ktrain_bytes(B * Hkv, L, d)) : nullptr;
-    // partial sums of dK and dV (the mask is not known here); without them (bytes_min) such a problem runs unsplit
+    // Partial sums of dK and dV (the mask is not known here) lie behind everything else; without room for them (bytes_min) a
+    // problem runs unsplit.  The size asked for leaves them out below kSmallBwdWs, where the sizes have always been those of the
+    // arrays above and the sums would be several times as much.
     w.bytes_min = c.off;
     const size_t part = max(bwd_plan(B * Hq, B * Hkv, L, d, false).part_bytes, bwd_plan(B * Hq, B * Hkv, L, d, true).part_bytes);
     w.part = part ? (float*)c.take(part) : nullptr;
-    w.bytes = c.off;
+    w.bytes_split = c.off;
+    w.bytes = w.bytes_min < kSmallBwdWs ? w.bytes_min : w.bytes_split;
     return w;
 }
 
@@ -764,7 +768,7 @@ static int bwd_common(const void* q, const void* k, const void* v, const void* d
     prof_mark("prep_qkvdo", st);
     BwdPlan plan = bwd_plan(B * Hq, B * Hkv, L, d, causal != 0);
     if (plan.joint && p_quant != 0) {
-        if (workspace_bytes < w.bytes && plan.splits > 1) { plan.splits = 1; plan.iters = (L + 31) / 32 * (Hq / Hkv); }
+        if (workspace_bytes < w.bytes_split && plan.splits > 1) { plan.splits = 1; plan.iters = (L + 31) / 32 * (Hq / Hkv); }
         if (launch_bwd_joint(w.qb, w.kb, w.vb, dob, w.rowstat, w.bounds, B, Hq, Hkv, L, d, causal != 0, dq, dk, dv, p_quant, plan, w.part,
                              dkdv_counts_of(st), st, p_dump, dump_row0, mx ? &mxo : nullptr))
             return ATTNQAT_ELAUNCH;
