@@ -117,7 +117,7 @@ int check_dims(int B, int Hq, int Hkv, int L, int d, int dtype)
 }
 
 // Workspace of the forward: fp16 Q^F, K^F (row-major) and V^F^T.
-struct FwdWs { void *qh, *kh, *vt, *tmp, *qsc; double* kpart; float* kmean; size_t bytes; };
+struct FwdWs { void *qh, *kh, *vt, *qsc; double* kpart; float* kmean; size_t bytes; };
 FwdWs carve_fwd(void* ws, int B, int Hq, int Hkv, int L, int d, bool mx = false)
 {
     const size_t Lp = round_up(L, kRowPad);
@@ -126,7 +126,7 @@ FwdWs carve_fwd(void* ws, int B, int Hq, int Hkv, int L, int d, bool mx = false)
     w.qh = c.take((size_t)B * Hq * Lp * d * 2);
     w.kh = c.take((size_t)B * Hkv * Lp * d * 2);
     w.vt = c.take((size_t)B * Hkv * Lp * d * 2);
-    w.tmp = mx ? c.take((size_t)B * Hq * L * d * 2) : nullptr;      // MX: the dequantized bf16 tensor before its layout copy
+    if (mx) c.take((size_t)B * Hq * L * d * 2);      // (not used any more: the size asked for stays what it was)
     // MX: qh and kh hold the operands of the FP4 instruction (smaller than the fp16 copies); the Q scale dwords come extra
     w.qsc = mx ? c.take(mx_qsc_bytes(B * Hq, L)) : nullptr;
     w.kpart = (double*)c.take(colmean_scratch_bytes(B * Hkv, d));  // K smoothing: partial sums and the token mean of K
@@ -137,7 +137,7 @@ FwdWs carve_fwd(void* ws, int B, int Hq, int Hkv, int L, int d, bool mx = false)
 
 // Workspace of the backward: row-major copies (Q^F, K^F fp16; V^F and dO bf16: dO is not exactly
 // representable in fp16), the per-row {L, D} pairs and the partial maxima that bound |dS|.
-struct BwdWs { void *qb, *kb, *vb, *dob; float* rowstat; float* bounds; void* tmp; double* kpart; float* kmean; size_t bytes;
+struct BwdWs { void *qb, *kb, *vb, *dob; float* rowstat; float* bounds; double* kpart; float* kmean; size_t bytes;
                void *qops, *qsc, *kops, *ksc, *krec;
                size_t bytes_min, bytes_split; float* part; };
 constexpr size_t kSmallBwdWs = (size_t)2 << 20;
@@ -150,7 +150,6 @@ BwdWs carve_bwd(void* ws, int B, int Hq, int Hkv, int L, int d, bool mx = false)
     w.qb = c.take(nq); w.kb = c.take(nk); w.vb = c.take(nk); w.dob = c.take(nq);
     w.rowstat = (float*)c.take((size_t)B * Hq * Lp * 8);
     w.bounds = (float*)c.take((size_t)3 * B * Hq * 64 * 4);
-    w.tmp = mx ? c.take((size_t)B * Hq * L * d * 2) : nullptr;
     w.kpart = (double*)c.take(colmean_scratch_bytes(B * Hkv, d));
     w.kmean = (float*)c.take((size_t)B * Hkv * d * 4);
     // MX: the operand arrays of the FP4 instruction from which both passes recompute the scores
@@ -183,19 +182,19 @@ MxWs carve_mx(void* ws, int B, int Hq, int Hkv, int L, int d, bool fp8v = false)
     return w;
 }
 
-// The MX phi of one input tensor and its layout copies (xr row-major, xt transposed; either may be null): the fake-quantizer
-// writes the dequantized bf16 tensor to tmp (blocks along d, or along the sequence for V), then the layout copy runs.
-int quant_copy(const void* x, int BH, int L, int d, int mx_axis, bool out_f16, void* xr, void* xt, void* tmp, hipStream_t st)
-{
-    if (launch_mx_quant(x, BH, L, d, mx_axis, 0, false, nullptr, nullptr, tmp, st)) return -1;
-    return launch_prep(tmp, BH, L, d, false, out_f16, nullptr, nullptr, nullptr, xr, xt, st);
-}
-
 // What the forward prepares: phi(Q), phi(K), phi(V) (Alg. 1 line "phi(Q), phi(K), phi(V)" / Alg. 2 line "Q^F, K^F, V^F").
 PrepGroup group_of(int B, int Hq, int Hkv, int L, int d)
 {
     PrepGroup g{};
     g.BHq = B * Hq; g.BHkv = B * Hkv; g.L = g.L_kv = L; g.Lp = g.Lp_kv = round_up(L, kRowPad); g.D = d; g.v_quant = true;
+    return g;
+}
+
+MxGroup mx_group_of(const void* q, const void* k, const void* v, int BHq, int BHkv, int L)
+{
+    MxGroup g{};
+    g.q = (const uint16_t*)q; g.k = (const uint16_t*)k; g.v = (const uint16_t*)v;
+    g.BHq = BHq; g.BHkv = BHkv; g.L = L; g.Lp = round_up(L, kRowPad);
     return g;
 }
 
@@ -215,9 +214,9 @@ int fwd_common(const void* q, const void* k, const void* v, int B, int Hq, int H
     prof_begin(st);
     if (mx) {
         // Q and K as operands of the scaled FP4 instruction (the scores are computed from the codes), V^F^T as the fp16 copy
-        if (launch_mx_quant(q, B * Hq, L, d, 0, 1, false, (unsigned char*)w.qh, (unsigned char*)w.qsc, nullptr, st)) return ATTNQAT_ELAUNCH;
-        if (launch_mx_quant(k, B * Hkv, L, d, 0, 3, false, (unsigned char*)w.kh, nullptr, nullptr, st)) return ATTNQAT_ELAUNCH;
-        if (quant_copy(v, B * Hkv, L, d, 1, true, nullptr, w.vt, w.tmp, st)) return ATTNQAT_ELAUNCH;
+        MxGroup g = mx_group_of(q, k, v, B * Hq, B * Hkv, L);
+        g.qops = (unsigned char*)w.qh; g.qsc = (unsigned char*)w.qsc; g.krec = (unsigned char*)w.kh; g.v_out = (uint16_t*)w.vt;
+        if (launch_mx_group(g, MX_TRAIN, d, st)) return ATTNQAT_ELAUNCH;
         prof_mark("prep_qkv", st);
         if (launch_fwd(w.qh, w.kh, w.vt, B, Hq, Hkv, L, d, causal != 0, train, 1, o, lse, o_hp, dump_row0, p_dump, st, w.qsc))
             return ATTNQAT_ELAUNCH;
@@ -308,7 +307,7 @@ static int quantize_mx_common(const void* x, int B, int H, int L, int d, int dty
     int rc = check_dims(B, H, H, L, d, dtype);
     if (rc) return rc;
     prof_begin((hipStream_t)stream);
-    if (launch_mx_quant(x, B * H, L, d, axis, 0, fp8, codes, scales, xf, (hipStream_t)stream)) return ATTNQAT_ELAUNCH;
+    if (launch_mx_quant(x, B * H, L, d, axis, fp8, codes, scales, xf, (hipStream_t)stream)) return ATTNQAT_ELAUNCH;
     prof_mark("quantize_mx", (hipStream_t)stream);
     return ATTNQAT_OK;
 }
@@ -337,9 +336,9 @@ static int fwd_infer_mx_common(const void* q, const void* k, const void* v,
     hipStream_t st = (hipStream_t)stream;
     prof_begin(st);
     // Alg. 1 first line, in the MX format: phi(Q), phi(K) along d, phi(V) along the keys (E4M3 elements in the mixed recipe)
-    if (launch_mx_quant(q, B * Hq, L, d, 0, 1, false, w.qops, w.qsc, nullptr, st)) return ATTNQAT_ELAUNCH;
-    if (launch_mx_quant(k, B * Hkv, L, d, 0, 2, fp8pv, w.kv, nullptr, nullptr, st)) return ATTNQAT_ELAUNCH;
-    if (launch_mx_quant(v, B * Hkv, L, d, 1, 2, fp8pv, w.kv, nullptr, nullptr, st)) return ATTNQAT_ELAUNCH;
+    MxGroup g = mx_group_of(q, k, v, B * Hq, B * Hkv, L);
+    g.qops = w.qops; g.qsc = w.qsc; g.kv = w.kv;
+    if (launch_mx_group(g, fp8pv ? MX_INFER_FP8V : MX_INFER, d, st)) return ATTNQAT_ELAUNCH;
     prof_mark("prep_qkv_mx", st);
     if (launch_fwd_mx(w.qops, w.qsc, w.kv, B, Hq, Hkv, L, d, causal != 0, fp8pv, o, lse, st)) return ATTNQAT_ELAUNCH;
     prof_mark(fp8pv ? "fwd_infer_mx_fp8pv" : "fwd_infer_mx", st);
@@ -377,11 +376,12 @@ int attnqat_fwd_infer_mx_sparse(const void* q, const void* k, const void* v,
     if (!workspace || workspace_bytes < c.off) return ATTNQAT_EWORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     prof_begin(st);
-    if (launch_mx_quant(q, B * Hq, L, d, 0, 1, false, w.qops, w.qsc, nullptr, st)) return ATTNQAT_ELAUNCH;
-    if (launch_mx_quant(k, B * Hkv, L, d, 0, 2, false, w.kv, nullptr, nullptr, st)) return ATTNQAT_ELAUNCH;
-    if (launch_mx_quant(v, B * Hkv, L, d, 1, 2, false, w.kv, nullptr, nullptr, st)) return ATTNQAT_ELAUNCH;
+    MxGroup g = mx_group_of(q, k, v, B * Hq, B * Hkv, L);
+    g.qops = w.qops; g.qsc = w.qsc; g.kv = w.kv;
+    g.mask = (const unsigned char*)block_mask; g.list = list; g.list_count = cnt;
+    if (launch_mx_group(g, MX_INFER, d, st)) return ATTNQAT_ELAUNCH;
     prof_mark("prep_qkv_mx", st);
-    if (launch_fwd_mx_sparse(w.qops, w.qsc, w.kv, B, Hq, Hkv, L, d, causal != 0, block_mask, list, cnt, o, lse, st)) return ATTNQAT_ELAUNCH;
+    if (launch_fwd_mx_sparse(w.qops, w.qsc, w.kv, B, Hq, Hkv, L, d, causal != 0, list, cnt, o, lse, st)) return ATTNQAT_ELAUNCH;
     prof_mark("fwd_infer_mx_sparse", st);
     return ATTNQAT_OK;
 }
@@ -400,8 +400,9 @@ int attnqat_kv_cache_write_mx(const void* k, const void* v, int Hkv, int L, int 
     if (rc) return rc;
     hipStream_t st = (hipStream_t)stream;
     prof_begin(st);
-    if (launch_mx_quant(k, Hkv, L, d, 0, 2, false, (unsigned char*)cache, nullptr, nullptr, st, page_ids, num_pages)) return ATTNQAT_ELAUNCH;
-    if (launch_mx_quant(v, Hkv, L, d, 1, 2, false, (unsigned char*)cache, nullptr, nullptr, st, page_ids, num_pages)) return ATTNQAT_ELAUNCH;
+    MxGroup g = mx_group_of(nullptr, k, v, 0, Hkv, L);
+    g.kv = (unsigned char*)cache; g.page_ids = page_ids; g.num_pages = num_pages;
+    if (launch_mx_group(g, MX_INFER, d, st)) return ATTNQAT_ELAUNCH;
     prof_mark("kv_cache_write_mx", st);
     return ATTNQAT_OK;
 }
@@ -424,7 +425,9 @@ int attnqat_fwd_infer_mx_paged(const void* q, int B, int Hq, int Hkv, int Lq, in
     if (!workspace || workspace_bytes < c.off) return ATTNQAT_EWORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     prof_begin(st);
-    if (launch_mx_quant(q, B * Hq_k, Lq_k, d, 0, 1, false, qops, qsc, nullptr, st)) return ATTNQAT_ELAUNCH;
+    MxGroup g = mx_group_of(q, nullptr, nullptr, B * Hq_k, 0, Lq_k);
+    g.qops = qops; g.qsc = qsc;
+    if (launch_mx_group(g, MX_INFER, d, st)) return ATTNQAT_ELAUNCH;
     prof_mark("prep_q_mx", st);
     if (launch_fwd_mx_paged(qops, qsc, cache, B, Hq_k, Hkv, Lq_k, d, causal != 0, page_table, kv_lens, max_pages, num_pages, Lq, o, lse, st))
         return ATTNQAT_ELAUNCH;
@@ -733,24 +736,20 @@ static int bwd_common(const void* q, const void* k, const void* v, const void* d
     prof_begin(st);
     // Q^F, K^F, V^F again (bit-identical to the forward's), D, the bounds of |dS|, and dO: the attention passes read it as it is
     // where its rows need no padding (and lie as the 16-byte copies to LDS want them), otherwise from a zero-padded copy
-    PrepGroup g = group_of(B, Hq, Hkv, L, d);
-    g.v_out = (uint16_t*)w.vb;
-    g.d_o = (const uint16_t*)d_o; g.o_acc = o_acc; g.o_is_bf16 = o_is_bf16; g.lse = lse; g.rs = 1.0f / sqrtf((float)d);
-    g.rowstat = (float2*)w.rowstat; g.bounds = w.bounds;
     const bool pad_do = L % kRowPad != 0 || ((uintptr_t)d_o & 15) != 0;
-    g.dob = pad_do ? (uint16_t*)w.dob : nullptr;
     const void* dob = pad_do ? w.dob : d_o;
+    const GradArgs grad{(const uint16_t*)d_o, o_acc, o_is_bf16, lse, 1.0f / sqrtf((float)d), (float2*)w.rowstat, w.bounds, pad_do ? (uint16_t*)w.dob : nullptr};
     MxScoreOps mxo{w.qops, w.qsc, w.kops, w.ksc, w.krec};
     if (mx) {
-        if (quant_copy(q, B * Hq, L, d, 0, true, w.qb, nullptr, w.tmp, st)) return ATTNQAT_ELAUNCH;
-        if (quant_copy(k, B * Hkv, L, d, 0, true, w.kb, nullptr, w.tmp, st)) return ATTNQAT_ELAUNCH;
-        if (launch_mx_quant(v, B * Hkv, L, d, 1, 0, false, nullptr, nullptr, w.tmp, st)) return ATTNQAT_ELAUNCH;
-        if (launch_mx_quant(q, B * Hq, L, d, 0, 1, false, (unsigned char*)w.qops, (unsigned char*)w.qsc, nullptr, st)) return ATTNQAT_ELAUNCH;
-        if (launch_mx_quant(k, B * Hkv, L, d, 0, 1, false, (unsigned char*)w.kops, (unsigned char*)w.ksc, nullptr, st)) return ATTNQAT_ELAUNCH;
-        if (launch_mx_quant(k, B * Hkv, L, d, 0, 3, false, (unsigned char*)w.krec, nullptr, nullptr, st)) return ATTNQAT_ELAUNCH;
-        g.v = (const uint16_t*)w.tmp; g.v_quant = false;
+        MxGroup g = mx_group_of(q, k, v, B * Hq, B * Hkv, L);
+        g.qops = (unsigned char*)w.qops; g.qsc = (unsigned char*)w.qsc; g.kops = (unsigned char*)w.kops; g.ksc = (unsigned char*)w.ksc;
+        g.krec = (unsigned char*)w.krec; g.q_row = (uint16_t*)w.qb; g.k_row = (uint16_t*)w.kb; g.v_out = (uint16_t*)w.vb;
+        g.grad = grad;
+        if (launch_mx_group(g, MX_BWD, d, st)) return ATTNQAT_ELAUNCH;
     } else {
-        g.q_out = (uint16_t*)w.qb; g.k_out = (uint16_t*)w.kb;
+        PrepGroup g = group_of(B, Hq, Hkv, L, d);
+        g.q_out = (uint16_t*)w.qb; g.k_out = (uint16_t*)w.kb; g.v_out = (uint16_t*)w.vb;
+        g.grad = grad;
         if (packed) {
             // the saved quantized tensors of the forward (appendix "Detailed Training Setup": the extra buffers for the
             // fake-quantized Q, K, V): only the layout copies remain to be made
@@ -763,8 +762,8 @@ static int bwd_common(const void* q, const void* k, const void* v, const void* d
                 g.k_sub = w.kmean;
             }
         }
+        if (launch_prep_group(g, st)) return ATTNQAT_ELAUNCH;
     }
-    if (launch_prep_group(g, st)) return ATTNQAT_ELAUNCH;
     prof_mark("prep_qkvdo", st);
     BwdPlan plan = bwd_plan(B * Hq, B * Hkv, L, d, causal != 0);
     if (plan.joint && p_quant != 0) {

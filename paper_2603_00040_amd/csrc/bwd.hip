@@ -85,7 +85,7 @@ __device__ inline int8v_t fp4_opnd(const uint4v& x) {
 }
 
 // MXS (the MX format): S^T = K^F Q^F^T is recomputed from the E2M1 codes and E8M0 scales by v_mfma_scale_f32_32x32x64_f8f6f4
-// (Qops / Qsc: operands and scale dwords of the query rows, launch_mx_quant mode 1; Krec: the K records of mode 3); the
+// (Qops / Qsc: operands and scale dwords of the query rows; Krec: the K records in natural key order; see launch_mx_group); the
 // accumulator layout is that of the 16-bit products, and dP, dS and dQ are computed as before (dO, dS are 16-bit values).
 // NW waves of 32 query rows each share the K / V tiles: 4, or 8 for the passes of a large problem (half the
 // tile copies per query row).

@@ -24,10 +24,14 @@ struct PagedSrc {
 // Everything a forward or a backward prepares, in one launch.  Q and K become fp16 rows (zero padded to Lp = round_up(L, 128)), V
 // becomes transposed fp16 (forward; bf16 and unquantized with v_quant = false) or bf16 rows (backward).  From bf16 tensors, or
 // from codes and scales (attnqat_quantize's layout; codes[2] != null), or, K and V, from the pages of a cache (ps.cache != null).
-// With d_o the statistics of the backward are made as well (Alg. 3, first line): rowstat [BHq, Lp, 2] = {L log2(e), D / sqrt(d)},
+// With grad.d_o the statistics of the backward are made as well (Alg. 3, first line): rowstat [BHq, Lp, 2] = {L log2(e), D / sqrt(d)},
 // D = rowsum(dO o O'), zeros in the padding rows; and in bounds, 3 * BHq * kBoundParts floats, partial maxima per head
 // that limit |dS|: |V^F_j| (kv heads), |dO_i|, |D_i| / sqrt(d).
 constexpr int kBoundParts = 64;
+struct GradArgs {
+    const uint16_t* d_o; const void* o_acc; bool o_is_bf16; const float* lse; float rs /* 1 / sqrt(d) */;
+    float2* rowstat; float* bounds; uint16_t* dob;         // dob: zero-padded copy of dO, or null
+};
 struct PrepGroup {
     const uint16_t *q, *k, *v;
     const uint8_t *codes[3], *scales[3];
@@ -36,8 +40,7 @@ struct PrepGroup {
     int BHq, BHkv, L, Lp, L_kv, Lp_kv, D;
     bool v_quant;
     PagedSrc ps;
-    const uint16_t* d_o; const void* o_acc; bool o_is_bf16; const float* lse; float rs /* 1 / sqrt(d) */;
-    float2* rowstat; float* bounds; uint16_t* dob;         // dob: zero-padded copy of dO, or null
+    GradArgs grad;
 };
 int launch_prep_group(const PrepGroup& g, hipStream_t st);
 
@@ -47,8 +50,8 @@ size_t colmean_scratch_bytes(int BH, int D);
 int launch_colmean(const void* x, int BH, int L, int D, double* scratch, float* mean, hipStream_t st);
 
 // Alg. 1 (train=false) / Alg. 2 (train=true) on fp16 copies made by launch_prep.
-// p_quant 1 (MX): qh and kh are NOT fp16 copies but the operand arrays of the scaled FP4 instruction (launch_mx_quant mode 1
-// for Q, with its scale dwords in qsc, and mode 3 for K): the scores are computed from the codes; vt stays the fp16 copy.
+// p_quant 1 (MX): qh and kh are NOT fp16 copies but the operand arrays of the scaled FP4 instruction (launch_mx_group,
+// MX_TRAIN: qops with its scale dwords in qsc, and krec): the scores are computed from the codes; vt stays the fp16 copy.
 // p_quant: phi(P-tilde) 0 NVFP4; 1 in the MX format (blocks of 32 keys, power-of-two scale); 2 NVFP4 after the
 // two-level row factor (every 64-key tile row divided by a power of two that brings its maximum just below 448 * 6).
 int launch_fwd(const void* qh, const void* kh, const void* vt,
@@ -75,9 +78,8 @@ size_t decode_ws_bytes(int B, int Hkv, int R, int max_pages, int D);
 int launch_decode(const void* qh, const void* cache, int num_pages, const int* page_table, int max_pages, const int* kv_lens,
                   int B, int Hq, int Hkv, int Lq, int D, bool causal, void* ws, int spin_limit, void* o, float* lse, hipStream_t st);
 
-// The MX format's operand arrays of the scaled FP4 instruction, from which the backward recomputes the scores (launch_mx_quant):
-// qops / qsc: mode 1 on Q; kops / ksc: mode 1 on K (a wave's 32 keys as the A operand of the dK/dV pass); krec: mode 3 on K
-// (64-key records, the A operand of the dQ pass).
+// The MX format's operand arrays of the scaled FP4 instruction, from which the backward recomputes the scores (launch_mx_group):
+// kops / ksc: a wave's 32 keys as the A operand of the dK/dV pass; krec: 64-key records, the A operand of the dQ pass.
 struct MxScoreOps { const void *qops, *qsc, *kops, *ksc, *krec; };
 
 // Alg. 3, query-stationary pass: dQ.  qh, kh: fp16 copies; vb, dob: bf16 copies.
@@ -107,23 +109,39 @@ int launch_bwd_joint(const void* qb, const void* kb, const void* vb, const void*
 // variant exists (8: not the ablation and not the counting variant).  Process-wide; for tests.
 void set_bwd_waves(int waves);
 
-// ---- MX variant (E2M1, blocks of 32, E8M0 scale; mx.hip) ----
-// phi with the blocks along d (axis 0) or along the sequence (axis 1).  x [BH, L, D] bf16.
-//   mode 0: public layout (codes, scales, optional bf16 xf, see attnqat.h)
-//   mode 1: Q operands of the scaled MFMA (axis 0 only): codes -> operand array, scales -> scale dwords
-//   mode 2: the K part (axis 0) or the V part (axis 1) of the 64-key kv records at `codes`
-//   mode 3: K records of the training forward (axis 0 only): natural key order, see mx.hip
-// fp8: E4M3 elements instead of E2M1 (axis 1 only); with axis 0 and mode 2 it selects the record layout whose V part is FP8.
-// page_ids (mode 2, FP4 only; device int32, one entry per 128 positions): the records go into the pages of a KV cache
-// laid out [page][kv head][2 records] instead of one after another; BH then is the number of kv heads of ONE sequence.
-// Records whose page id lies outside [0, num_pages) are not written.
-int launch_mx_quant(const void* x, int BH, int L, int D, int axis, int mode, bool fp8,
-                    unsigned char* codes, unsigned char* scales, void* xf, hipStream_t st, const int* page_ids = nullptr, int num_pages = 0);
+// ---- MX variant (E2M1, blocks of 32, E8M0 scale; mx.hip, mxprep.hip) ----
+// The public quantizer: phi with the blocks along d (axis 0) or along the sequence (axis 1).  x [BH, L, D] bf16; codes, scales,
+// optional bf16 xf: see attnqat.h.  fp8: E4M3 elements instead of E2M1 (axis 1 only).
+int launch_mx_quant(const void* x, int BH, int L, int D, int axis, bool fp8, unsigned char* codes, unsigned char* scales, void* xf, hipStream_t st);
+// Everything that an MX forward or backward prepares, in one launch (null outputs are left out):
+//   Q: operands of the scaled MFMA (qops, scale dwords qsc)              [all]; fp16 rows q_row    [MX_BWD]
+//   K: the K part of the 64-key kv records kv                            [MX_INFER, MX_INFER_FP8V]
+//      records in natural key order krec                                 [MX_TRAIN, MX_BWD]
+//      operands kops, ksc as of Q; fp16 rows k_row                       [MX_BWD]
+//   V: the V part of the kv records                                      [MX_INFER, MX_INFER_FP8V (E4M3 elements)]
+//      transposed fp16 v_out (the layout of launch_prep_group)           [MX_TRAIN]
+//      bf16 rows v_out and the bound of |V^F_j| in grad.bounds           [MX_BWD]
+//   dO and O': grad, as in launch_prep_group                             [MX_BWD]
+//   the block lists of a block-sparse forward: list, list_count from mask [BHq * nb, nb] bytes, nb = Lp / 128   [MX_INFER]
+// page_ids (MX_INFER; device int32, one entry per 128 positions): the records go into the pages of a KV cache laid out
+// [page][kv head][2 records] instead of one after another; BHkv then is the number of kv heads of ONE sequence.  Records whose
+// page id lies outside [0, num_pages) are not written.
+enum MxKind { MX_INFER, MX_INFER_FP8V, MX_TRAIN, MX_BWD };
+struct MxGroup {
+    const uint16_t *q, *k, *v;                   // q null: no Q; k and v null: neither
+    unsigned char *qops, *qsc, *kops, *ksc, *krec, *kv;
+    uint16_t *q_row, *k_row, *v_out;
+    int BHq, BHkv, L, Lp;
+    const int* page_ids; int num_pages;
+    const unsigned char* mask; int *list, *list_count;
+    GradArgs grad;
+};
+int launch_mx_group(const MxGroup& g, MxKind kind, int D, hipStream_t st);
 size_t mx_kv_bytes(int BHkv, int L, int D, bool fp8v);
-size_t mx_ktrain_bytes(int BHkv, int L, int D);      // K records of the MX training forward (launch_mx_quant mode 3)
+size_t mx_ktrain_bytes(int BHkv, int L, int D);      // K records of the MX training forward (krec)
 size_t mx_qops_bytes(int BHq, int L, int D);
 size_t mx_qsc_bytes(int BHq, int L);
-// Alg. 1 on the arrays made by launch_mx_quant (modes 1 and 2).  fp8pv: P-tilde and V in MXFP8 (mixed recipe).
+// Alg. 1 on the arrays made by launch_mx_group.  fp8pv: P-tilde and V in MXFP8 (mixed recipe).
 int launch_fwd_mx(const void* qops, const void* qsc, const void* kv, int B, int Hq, int Hkv, int L, int D, bool causal, bool fp8pv,
                   void* o, float* lse, hipStream_t st);
 
@@ -134,9 +152,9 @@ int launch_fwd_mx_paged(const void* qops, const void* qsc, const void* cache, in
                         const int* page_table, const int* kv_lens, int max_pages, int num_pages, int lq_inner,
                         void* o, float* lse, hipStream_t st);
 
-// Block-sparse forward on contiguous kv records: block_mask [B*Hq*nb, nb] bytes with nb = ceil(L/128); list
-// ([B*Hq*nb, nb] int32) and cnt ([B*Hq*nb] int32) are scratch that the call fills.
+// Block-sparse forward on contiguous kv records, over the block lists that launch_mx_group made: list [B*Hq*nb, nb] and
+// cnt [B*Hq*nb], int32, nb = ceil(L/128).
 int launch_fwd_mx_sparse(const void* qops, const void* qsc, const void* kv, int B, int Hq, int Hkv, int L, int D, bool causal,
-                         const unsigned char* block_mask, int* list, int* cnt, void* o, float* lse, hipStream_t st);
+                         const int* list, const int* cnt, void* o, float* lse, hipStream_t st);
 
 }  // namespace aq

@@ -28,6 +28,7 @@
 // B operand of the P.V product.
 #include "common.hpp"
 #include "kernels.hpp"
+#include "mx_quant.hpp"
 
 namespace aq {
 
@@ -37,159 +38,37 @@ namespace aq {
 
 typedef int int8v __attribute__((ext_vector_type(8)));
 
-// 32 values -> 4 registers of E2M1 codes (value i in nibble i), RNE on v / scale, saturating.
-__device__ inline uint4v mx_codes32(const float (&v)[32], float scale) {
-    uint4v c;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        uint32_t r = 0u;
-        r = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(r, v[8 * w + 0], v[8 * w + 1], scale, 0);
-        r = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(r, v[8 * w + 2], v[8 * w + 3], scale, 1);
-        r = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(r, v[8 * w + 4], v[8 * w + 5], scale, 2);
-        r = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(r, v[8 * w + 6], v[8 * w + 7], scale, 3);
-        c[w] = r;
-    }
-    return c;
-}
-
-__device__ inline float e2m1_value_of(uint32_t code) {
-    const uint32_t m = code & 7u;
-    const float v = m < 2u ? 0.5f * (float)m : __uint_as_float(((m >> 1) + 126u) << 23 | (m & 1u) << 22);
-    return (code & 8u) ? -v : v;
-}
-
-// Bytes of one 64-key record of a kv head: K operands, V^T operands, K scales, V scales.
-__host__ __device__ constexpr int mx_rec_bytes(int D, bool fp8v = false) { return 2 * (D / 64) * 1024 + (D / 32) * (fp8v ? 2048 : 1024) + 512; }
-
-// 32 values -> 8 registers of E4M3 bytes (value i in byte i), RNE on v / scale; |v| / scale <= 448 by the scale rule.
-typedef short short2v __attribute__((ext_vector_type(2)));
-__device__ inline void mx_codes32_fp8(const float (&v)[32], float scale, uint32_t (&c)[8]) {
-#pragma unroll
-    for (int w = 0; w < 8; ++w) {
-        short2v r = {0, 0};
-        r = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(r, v[4 * w + 0], v[4 * w + 1], scale, false);
-        r = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(r, v[4 * w + 2], v[4 * w + 3], scale, true);
-        c[w] = __builtin_bit_cast(uint32_t, r);
-    }
-}
-__device__ inline float e4m3_value_of(uint32_t byte) {
-    const uint32_t e = (byte >> 3) & 15u, m = byte & 7u;
-    const float v = e == 0u ? (float)m * 0.001953125f : __uint_as_float((e + 120u) << 23 | m << 20);
-    return (byte & 0x80u) ? -v : v;
-}
-
-// Where the 64-key record `tile` of kv head `head` lives.  Contiguous: records of a head one after another.  Paged (a
-// KV cache): a page holds two records (128 keys) of every kv head, page_ids[tile / 2] names the page of this sequence.
-// A page id outside [0, num_pages) gives null: the writer leaves that record out instead of touching memory outside the cache.
-__device__ inline unsigned char* mx_record_of(unsigned char* base, const int* page_ids, int num_pages, int head, int nheads, int Lp, int tile, int rec_bytes) {
-    if (page_ids) {
-        const int page = page_ids[tile >> 1];
-        if (page < 0 || page >= num_pages) return nullptr;
-        return base + (((size_t)page * nheads + head) * 2 + (tile & 1)) * rec_bytes;
-    }
-    return base + ((size_t)head * (Lp / 64) + tile) * rec_bytes;
-}
-
-// Row of S^T product t (0/1) that holds key kk (0..63) of a tile, and the lane half that ends up owning it:
-// the accumulator register r of a lane in half h is row 8 (r/4) + 4 h + r % 4; key 32 h + 16 t + r goes there.
-__device__ inline int mx_srow_of_key(int kk) { const int w = kk & 15; return 8 * (w >> 2) + 4 * (kk >> 5) + (w & 3); }
-
 // ---------------------------------------------------------------------------------------------
-// phi along d (blocks of 32).  One thread per block.
-//   MODE 0: public layout   codes [rows, D/2], scales [rows, D/32], optional bf16 xf
-//   MODE 1: Q operands      ops [rows/32, D/64, 64 lanes, 16 B], sc [rows/32, 64 lanes] (byte ks)
-//   MODE 2: K part of the kv records
-//   MODE 3: K records of the training forward (16-bit P V, scores on the FP4 instruction): per 64-key tile
-//           mx_ktrain_rec_bytes(D) bytes = ops [2 blocks of 32 keys][D/64][64 lanes][16 B] with the keys of a block in their
-//           natural order as operand rows (so that the score tile has the accumulator layout of the 16-bit kernels), then
-//           per lane one dword of scale bytes (byte = block * D/64 + ks), padded to a whole KiB
-template <int D, int MODE, bool FP8V = false /* MODE 2: records whose V part is FP8 */>
+// The public quantizer along d (blocks of 32), one thread per block: codes [rows, D/2], scales [rows, D/32], optional bf16 xf.
+template <int D>
 __global__ __launch_bounds__(256) void mx_quant_d_kernel(
-    const uint16_t* __restrict__ x, int L, int Lp, unsigned char* __restrict__ codes, unsigned char* __restrict__ scales,
-    uint16_t* __restrict__ xf, const int* __restrict__ page_ids, int num_pages)
+    const uint16_t* __restrict__ x, int L, unsigned char* __restrict__ codes, unsigned char* __restrict__ scales, uint16_t* __restrict__ xf)
 {
-    constexpr int NB = D / 32, KS = D / 64;
+    constexpr int NB = D / 32;
     const int bh = blockIdx.y;
     const int gid = blockIdx.x * 256 + threadIdx.x;
     const int row = gid / NB, blk = gid % NB;
-    const int rows_out = MODE == 0 ? L : Lp;
-    if (row >= rows_out) return;
-    float v[32];
-    if (row < L) {
-        const uint4v* src = reinterpret_cast<const uint4v*>(x + ((size_t)bh * L + row) * D + blk * 32);
+    if (row >= L) return;
+    uint32_t byte;
+    const uint4v c = mx_block_of_row<D>(x, bh, row, blk, L, byte);
+    if (codes) *reinterpret_cast<uint4v*>(codes + ((size_t)bh * L + row) * (D / 2) + blk * 16) = c;
+    if (scales) scales[((size_t)bh * L + row) * NB + blk] = (unsigned char)byte;
+    if (xf) {
+        uint32_t o[16];
+        mx_dequant32(c, e8m0_as_f32(byte), [&](int i, float lo, float hi) { o[i] = pack_bf16x2_rne(lo, hi); });
+        uint4v* dst = reinterpret_cast<uint4v*>(xf + ((size_t)bh * L + row) * D + blk * 32);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint4v a = src[j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                v[8 * j + 2 * i]     = __uint_as_float(a[i] << 16);
-                v[8 * j + 2 * i + 1] = __uint_as_float(a[i] & 0xFFFF0000u);
-            }
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < 32; ++i) v[i] = 0.0f;
-    }
-    float amax = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 32; ++i) amax = fmaxf(amax, fabsf(v[i]));
-    const uint32_t byte = e8m0_of_amax(amax);
-    const float s = e8m0_as_f32(byte);
-    const uint4v c = mx_codes32(v, s);
-    if (MODE == 0) {
-        if (codes) *reinterpret_cast<uint4v*>(codes + ((size_t)bh * L + row) * (D / 2) + blk * 16) = c;
-        if (scales) scales[((size_t)bh * L + row) * NB + blk] = (unsigned char)byte;
-        if (xf) {
-            uint4v o[4];
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const uint32_t w = c[i >> 2] >> (8 * (i & 3));
-                // code * 2^e: at most 2 significant bits, exact in bf16 whenever it is a normal number
-                const uint32_t lo = f32_to_bf16_rne(e2m1_value_of(w & 15u) * s), hi = f32_to_bf16_rne(e2m1_value_of((w >> 4) & 15u) * s);
-                o[i >> 2][i & 3] = lo | (hi << 16);
-            }
-            uint4v* dst = reinterpret_cast<uint4v*>(xf + ((size_t)bh * L + row) * D + blk * 32);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) dst[j] = o[j];
-        }
-    } else if (MODE == 1) {
-        const int g = row >> 5, ks = blk >> 1, lane = (blk & 1) * 32 + (row & 31);
-        const size_t grp = (size_t)bh * (Lp / 32) + g;
-        *reinterpret_cast<uint4v*>(codes + ((grp * KS + ks) * 64 + lane) * 16) = c;
-        scales[(grp * 64 + lane) * 4 + ks] = (unsigned char)byte;
-        if (KS == 1) { scales[(grp * 64 + lane) * 4 + 1] = 1; }
-        if (ks == 0) { scales[(grp * 64 + lane) * 4 + 2] = 1; scales[(grp * 64 + lane) * 4 + 3] = 1; }
-    } else if (MODE == 3) {
-        constexpr int REC = mx_ktrain_rec_bytes(D), KOPS = 2 * KS * 1024;
-        const int tile = row >> 6, kk = row & 63, kb = kk >> 5;
-        const int ks = blk >> 1, lane = (blk & 1) * 32 + (kk & 31);
-        unsigned char* rec = codes + ((size_t)bh * (Lp / 64) + tile) * REC;
-        *reinterpret_cast<uint4v*>(rec + ((kb * KS + ks) * 64 + lane) * 16) = c;
-        rec[KOPS + lane * 4 + kb * KS + ks] = (unsigned char)byte;
-        if (KS == 1 && kb == 0) { rec[KOPS + lane * 4 + 2] = 1; rec[KOPS + lane * 4 + 3] = 1; }
-    } else {
-        constexpr int REC = mx_rec_bytes(D, FP8V), KOPS = 2 * KS * 1024, VOPS = NB * (FP8V ? 2048 : 1024);
-        const int tile = row >> 6, kk = row & 63, t = (kk >> 4) & 1;
-        const int ks = blk >> 1, lane = (blk & 1) * 32 + mx_srow_of_key(kk);
-        unsigned char* rec = mx_record_of(codes, page_ids, num_pages, bh, (int)gridDim.y, Lp, tile, REC);
-        if (!rec) return;
-        *reinterpret_cast<uint4v*>(rec + ((t * KS + ks) * 64 + lane) * 16) = c;
-        rec[KOPS + VOPS + lane * 4 + t * KS + ks] = (unsigned char)byte;
-        if (KS == 1 && t == 0) { rec[KOPS + VOPS + lane * 4 + 2] = 1; rec[KOPS + VOPS + lane * 4 + 3] = 1; }
+        for (int j = 0; j < 4; ++j) { uint4v w; w[0] = o[4 * j]; w[1] = o[4 * j + 1]; w[2] = o[4 * j + 2]; w[3] = o[4 * j + 3]; dst[j] = w; }
     }
 }
 
-// phi along the sequence axis (blocks of 32 positions, zero padded): how V is blocked.
-// One thread per (block of 32 positions, d index); x [BH, L, D].  FP8: E4M3 elements (one byte each) instead of E2M1.
-//   MODE 0: public layout  codes [BH, D, Lc/2] (FP8: [BH, D, Lc]), scales [BH, D, Lc/32] with Lc = round_up(L, 32);
-//           optional bf16 xf [BH, L, D]
-//   MODE 2: V part of the kv records (FP8: two 1 KiB halves per d-block, bytes 0-15 and 16-31 of every lane)
-template <int D, int MODE, bool FP8>
+// The public quantizer along the sequence (blocks of 32 positions, zero padded): how V is blocked.  One thread per (block, d index);
+// FP8: E4M3 elements (one byte each) instead of E2M1.  codes [BH, D, Lc/2] (FP8: [BH, D, Lc]), scales [BH, D, Lc/32] with
+// Lc = round_up(L, 32); optional bf16 xf [BH, L, D].
+template <int D, bool FP8>
 __global__ __launch_bounds__(D) void mx_quant_l_kernel(
-    const uint16_t* __restrict__ x, int L, int Lp, unsigned char* __restrict__ codes, unsigned char* __restrict__ scales,
-    uint16_t* __restrict__ xf, const int* __restrict__ page_ids, int num_pages)
+    const uint16_t* __restrict__ x, int L, unsigned char* __restrict__ codes, unsigned char* __restrict__ scales, uint16_t* __restrict__ xf)
 {
-    constexpr int KS = D / 64, MT = D / 32;
     const int bh = blockIdx.y, kb = blockIdx.x, dd = threadIdx.x;
     const uint16_t* src = x + (size_t)bh * L * D + dd;
     float v[32];
@@ -198,56 +77,24 @@ __global__ __launch_bounds__(D) void mx_quant_l_kernel(
         const int l = kb * 32 + i;
         v[i] = l < L ? bf16_to_f32(src[(size_t)l * D]) : 0.0f;
     }
-    float amax = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 32; ++i) amax = fmaxf(amax, fabsf(v[i]));
-    const uint32_t byte = FP8 ? e8m0_of_amax_fp8(amax) : e8m0_of_amax(amax);
+    uint32_t byte, c[8];
+    mx_block_codes<FP8>(v, byte, c);
     const float s = e8m0_as_f32(byte);
-    uint32_t c[8];
-    if constexpr (FP8) {
-        mx_codes32_fp8(v, s, c);
-    } else {
-        const uint4v c4 = mx_codes32(v, s);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { c[i] = c4[i]; c[4 + i] = 0u; }
-    }
     constexpr int NW = FP8 ? 8 : 4;                 // code registers per block
-    if (MODE == 0) {
-        const int Lc = round_up(L, 32);
-        if (codes) {
-            uint4v* dst = reinterpret_cast<uint4v*>(codes + (((size_t)bh * D + dd) * (Lc / 32) + kb) * (4 * NW));
+    const int Lc = round_up(L, 32);
+    if (codes) {
+        uint4v* dst = reinterpret_cast<uint4v*>(codes + (((size_t)bh * D + dd) * (Lc / 32) + kb) * (4 * NW));
 #pragma unroll
-            for (int i = 0; i < NW / 4; ++i) { uint4v o; o[0] = c[4 * i]; o[1] = c[4 * i + 1]; o[2] = c[4 * i + 2]; o[3] = c[4 * i + 3]; dst[i] = o; }
-        }
-        if (scales) scales[((size_t)bh * D + dd) * (Lc / 32) + kb] = (unsigned char)byte;
-        if (xf) {
+        for (int i = 0; i < NW / 4; ++i) { uint4v o; o[0] = c[4 * i]; o[1] = c[4 * i + 1]; o[2] = c[4 * i + 2]; o[3] = c[4 * i + 3]; dst[i] = o; }
+    }
+    if (scales) scales[((size_t)bh * D + dd) * (Lc / 32) + kb] = (unsigned char)byte;
+    if (xf) {
 #pragma unroll
-            for (int i = 0; i < 32; ++i) {
-                const int l = kb * 32 + i;
-                const float val = FP8 ? e4m3_value_of((c[i >> 2] >> (8 * (i & 3))) & 255u) : e2m1_value_of((c[i >> 3] >> (4 * (i & 7))) & 15u);
-                if (l < L) xf[((size_t)bh * L + l) * D + dd] = f32_to_bf16_rne(val * s);
-            }
+        for (int i = 0; i < 32; ++i) {
+            const int l = kb * 32 + i;
+            const float val = FP8 ? e4m3_value_of((c[i >> 2] >> (8 * (i & 3))) & 255u) : e2m1_value_of((c[i >> 3] >> (4 * (i & 7))) & 15u);
+            if (l < L) xf[((size_t)bh * L + l) * D + dd] = f32_to_bf16_rne(val * s);
         }
-    } else {
-        constexpr int REC = mx_rec_bytes(D, FP8), KOPS = 2 * KS * 1024, VOPS = MT * (FP8 ? 2048 : 1024);
-        const int tile = kb >> 1, lane = (kb & 1) * 32 + (dd & 31), mt = dd >> 5;
-        unsigned char* rec = mx_record_of(codes, page_ids, num_pages, bh, (int)gridDim.y, Lp, tile, REC);
-        if (!rec) return;
-        if constexpr (FP8) {
-            // FP8 operands: registers 0-3 of lane (row, h) are contraction indices 16 h .. + 15, registers 4-7 are
-            // 32 + 16 h .. + 15, and the scale of indices 32 b .. + 31 is taken from lane (row, b): the two halves of
-            // this block of 32 keys go to the two lane halves, in the register group of the block
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                uint4v o; o[0] = c[4 * i]; o[1] = c[4 * i + 1]; o[2] = c[4 * i + 2]; o[3] = c[4 * i + 3];
-                *reinterpret_cast<uint4v*>(rec + KOPS + ((mt * 2 + (kb & 1)) * 64 + i * 32 + (dd & 31)) * 16) = o;
-            }
-        } else {
-            uint4v o; o[0] = c[0]; o[1] = c[1]; o[2] = c[2]; o[3] = c[3];
-            *reinterpret_cast<uint4v*>(rec + KOPS + (mt * 64 + lane) * 16) = o;
-        }
-        rec[KOPS + VOPS + 256 + lane * 4 + mt] = (unsigned char)byte;
-        if (MT == 2 && mt == 0) { rec[KOPS + VOPS + 256 + lane * 4 + 2] = 1; rec[KOPS + VOPS + 256 + lane * 4 + 3] = 1; }
     }
 }
 
@@ -740,39 +587,16 @@ __global__ __launch_bounds__(256 * NP, NP == 1 ? 2 : 1) void fwd_mx_decode_kerne
 }
 
 // ---------------------------------------------------------------------------------------------
-template <int D>
-static int quant_d(const void* x, int BH, int L, int mode, bool fp8v, unsigned char* codes, unsigned char* scales, void* xf,
-                   const int* page_ids, int num_pages, hipStream_t st)
+int launch_mx_quant(const void* x, int BH, int L, int D, int axis, bool fp8, unsigned char* codes, unsigned char* scales, void* xf, hipStream_t st)
 {
-    const int Lp = round_up(L, kRowPad);
-    const int rows = mode == 0 ? L : Lp;
-    const dim3 grid((unsigned)(((size_t)rows * (D / 32) + 255) / 256), (unsigned)BH);
-    if (mode == 0)      hipLaunchKernelGGL((mx_quant_d_kernel<D, 0>), grid, dim3(256), 0, st, (const uint16_t*)x, L, Lp, codes, scales, (uint16_t*)xf, page_ids, num_pages);
-    else if (mode == 3) hipLaunchKernelGGL((mx_quant_d_kernel<D, 3>), grid, dim3(256), 0, st, (const uint16_t*)x, L, Lp, codes, scales, (uint16_t*)xf, page_ids, num_pages);
-    else if (mode == 1) hipLaunchKernelGGL((mx_quant_d_kernel<D, 1>), grid, dim3(256), 0, st, (const uint16_t*)x, L, Lp, codes, scales, (uint16_t*)xf, page_ids, num_pages);
-    else if (fp8v)      hipLaunchKernelGGL((mx_quant_d_kernel<D, 2, true>), grid, dim3(256), 0, st, (const uint16_t*)x, L, Lp, codes, scales, (uint16_t*)xf, page_ids, num_pages);
-    else                hipLaunchKernelGGL((mx_quant_d_kernel<D, 2>), grid, dim3(256), 0, st, (const uint16_t*)x, L, Lp, codes, scales, (uint16_t*)xf, page_ids, num_pages);
+    if (BH > 65535 || (axis == 0 && fp8) || (D != 64 && D != 128)) return -1;
+    const dim3 grid_d((unsigned)(((size_t)L * (D / 32) + 255) / 256), (unsigned)BH), grid_l((unsigned)((L + 31) / 32), (unsigned)BH);
+#define AQ_Q(KERN, GRID, BLOCK) hipLaunchKernelGGL((KERN), GRID, dim3(BLOCK), 0, st, (const uint16_t*)x, L, codes, scales, (uint16_t*)xf)
+    if (axis == 0) { if (D == 128) AQ_Q(mx_quant_d_kernel<128>, grid_d, 256); else AQ_Q(mx_quant_d_kernel<64>, grid_d, 256); }
+    else if (fp8)  { if (D == 128) AQ_Q((mx_quant_l_kernel<128, true>), grid_l, 128); else AQ_Q((mx_quant_l_kernel<64, true>), grid_l, 64); }
+    else           { if (D == 128) AQ_Q((mx_quant_l_kernel<128, false>), grid_l, 128); else AQ_Q((mx_quant_l_kernel<64, false>), grid_l, 64); }
+#undef AQ_Q
     return hipGetLastError() == hipSuccess ? 0 : -1;
-}
-template <int D, bool FP8>
-static int quant_l(const void* x, int BH, int L, int mode, unsigned char* codes, unsigned char* scales, void* xf,
-                   const int* page_ids, int num_pages, hipStream_t st)
-{
-    const int Lp = round_up(L, kRowPad);
-    const int nblk = mode == 0 ? (L + 31) / 32 : Lp / 32;
-    const dim3 grid((unsigned)nblk, (unsigned)BH);
-    if (mode == 0) hipLaunchKernelGGL((mx_quant_l_kernel<D, 0, FP8>), grid, dim3(D), 0, st, (const uint16_t*)x, L, Lp, codes, scales, (uint16_t*)xf, page_ids, num_pages);
-    else           hipLaunchKernelGGL((mx_quant_l_kernel<D, 2, FP8>), grid, dim3(D), 0, st, (const uint16_t*)x, L, Lp, codes, scales, (uint16_t*)xf, page_ids, num_pages);
-    return hipGetLastError() == hipSuccess ? 0 : -1;
-}
-
-int launch_mx_quant(const void* x, int BH, int L, int D, int axis, int mode, bool fp8,
-                    unsigned char* codes, unsigned char* scales, void* xf, hipStream_t st, const int* page_ids, int num_pages)
-{
-    if (BH > 65535 || (axis == 0 && fp8 && mode != 2) || (page_ids && (mode != 2 || fp8)) || (mode == 3 && axis != 0)) return -1;
-    if (axis == 0) return D == 128 ? quant_d<128>(x, BH, L, mode, fp8, codes, scales, xf, page_ids, num_pages, st) : quant_d<64>(x, BH, L, mode, fp8, codes, scales, xf, page_ids, num_pages, st);
-    if (fp8) return D == 128 ? quant_l<128, true>(x, BH, L, mode, codes, scales, xf, page_ids, num_pages, st) : quant_l<64, true>(x, BH, L, mode, codes, scales, xf, page_ids, num_pages, st);
-    return D == 128 ? quant_l<128, false>(x, BH, L, mode, codes, scales, xf, page_ids, num_pages, st) : quant_l<64, false>(x, BH, L, mode, codes, scales, xf, page_ids, num_pages, st);
 }
 
 size_t mx_kv_bytes(int BHkv, int L, int D, bool fp8v) { return (size_t)BHkv * (round_up(L, kRowPad) / 64) * mx_rec_bytes(D, fp8v); }
@@ -843,24 +667,10 @@ int launch_fwd_mx_paged(const void* qops, const void* qsc, const void* cache, in
     return -1;
 }
 
-// Block lists of the block-sparse forward: row r = (b * Hq + h) * nqb + query block of mask [rows, nkb] (bytes, zero =
-// the block is left out) -> the indices of its non-zero key blocks in increasing order, and their number.
-__global__ void mx_block_list_kernel(const unsigned char* __restrict__ mask, int nrows, int nkb, int* __restrict__ list, int* __restrict__ cnt)
-{
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= nrows) return;
-    int n = 0;
-    for (int kb = 0; kb < nkb; ++kb)
-        if (mask[(size_t)r * nkb + kb]) list[(size_t)r * nkb + n++] = kb;
-    cnt[r] = n;
-}
-
 int launch_fwd_mx_sparse(const void* qops, const void* qsc, const void* kv, int B, int Hq, int Hkv, int L, int D, bool causal,
-                         const unsigned char* block_mask, int* list, int* cnt, void* o, float* lse, hipStream_t st)
+                         const int* list, const int* cnt, void* o, float* lse, hipStream_t st)
 {
-    const int nb = round_up(L, kRowPad) / 128, nrows = B * Hq * nb;
-    hipLaunchKernelGGL(mx_block_list_kernel, dim3((unsigned)((nrows + 127) / 128)), dim3(128), 0, st, block_mask, nrows, nb, list, cnt);
-    if (hipGetLastError() != hipSuccess) return -1;
+    const int nb = round_up(L, kRowPad) / 128;
 #define AQ_SPARSE(DD, CC) launch_fwd_mx_t<DD, CC, false, 2>(qops, qsc, kv, B, Hq, Hkv, L, o, lse, list, cnt, nb, 0, L, st)
     if (D == 128) return causal ? AQ_SPARSE(128, true) : AQ_SPARSE(128, false);
     if (D == 64)  return causal ? AQ_SPARSE(64, true) : AQ_SPARSE(64, false);

@@ -7,6 +7,7 @@
 // both the row-major and the transposed stores are 16-byte vectors.
 #include "common.hpp"
 #include "kernels.hpp"
+#include "prep.hpp"
 
 namespace aq {
 
@@ -251,69 +252,6 @@ __global__ __launch_bounds__(256) void prep_kernel(
     prep_tile<QUANT, OUT_F16, false, false, false>(tile, blockIdx.y, blockIdx.x * 64, x, L, Lp, D, codes, scales, xf_pub, xr, xt, sub, PagedSrc{}, n2);
 }
 
-// The statistics that the backward needs of 64 rows of dO and O' (Alg. 3, first line): rowstat = {L log2(e), D / sqrt(d)} with
-// D = rowsum(dO o O') (padding rows hold {0, 0}), the largest |dO_i|^2 and |D_i| / sqrt(d) so far in n2 and dmax, and the zero-padded
-// copy of dO where one is asked for (dob).
-__device__ __forceinline__ void grad_tile(int bh, int l0, const uint16_t* __restrict__ dO, const void* __restrict__ o_acc, bool o_is_bf16,
-                                          const float* __restrict__ lse, int L, int Lp, int D, float rs,
-                                          float2* __restrict__ rowstat, uint16_t* __restrict__ dob, float& n2, float& dmax)
-{
-    const int nb = D / 16;
-    for (int blk = threadIdx.x; blk < 64 * nb; blk += 256) {
-        const int row = blk / nb, cb = blk % nb, l = l0 + row;
-        uint4v g[2] = {};
-        float dot = 0.0f, nrm = 0.0f;
-        if (l < L) {
-            const size_t off = ((size_t)bh * L + l) * D + cb * 16;
-            g[0] = reinterpret_cast<const uint4v*>(dO + off)[0];
-            g[1] = reinterpret_cast<const uint4v*>(dO + off)[1];
-            float o[16];
-            if (o_is_bf16) {                       // ablation: D from the low-precision output
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    const uint4v w = reinterpret_cast<const uint4v*>(static_cast<const uint16_t*>(o_acc) + off)[t];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) { o[8 * t + 2 * i] = __uint_as_float(w[i] << 16); o[8 * t + 2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u); }
-                }
-            } else {
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const floatx4 w = reinterpret_cast<const floatx4*>(static_cast<const float*>(o_acc) + off)[t];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) o[4 * t + i] = w[i];
-                }
-            }
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float lo = __uint_as_float(g[t][i] << 16), hi = __uint_as_float(g[t][i] & 0xFFFF0000u);
-                    dot += lo * o[8 * t + 2 * i] + hi * o[8 * t + 2 * i + 1];
-                    nrm = fmaf(lo, lo, fmaf(hi, hi, nrm));
-                }
-        }
-        for (int w = nb / 2; w >= 1; w >>= 1) { dot += __shfl_xor(dot, w); nrm += __shfl_xor(nrm, w); }
-        dot *= rs;
-        if (cb == 0) rowstat[(size_t)bh * Lp + l] = make_float2(l < L ? lse[(size_t)bh * L + l] * 1.4426950408889634f : 0.0f, dot);
-        n2 = fmaxf(n2, nrm);
-        dmax = fmaxf(dmax, fabsf(dot));
-        if (dob) {
-            uint4v* dst = reinterpret_cast<uint4v*>(dob + ((size_t)bh * Lp + l) * D + cb * 16);
-            dst[0] = g[0]; dst[1] = g[1];
-        }
-    }
-}
-
-// Largest value of a workgroup; every thread gets it.  (The barriers also keep `red` from being overwritten too early.)
-__device__ inline float wg_max(float v, float (&red)[4]) {
-#pragma unroll
-    for (int w = 32; w >= 1; w >>= 1) v = fmaxf(v, __shfl_xor(v, w));
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    return fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-}
-
 // All tensors that a forward or a backward prepares, as one launch.  Bound by HBM on large problems; on small ones a launch takes
 // 3 - 5 us whatever its size (start, first loads, last stores), and a forward had three of them, a backward six.
 // The maxima that bound |dS| come out of the same reads (V^F from its registers, dO and D as they
@@ -331,24 +269,15 @@ __global__ __launch_bounds__(256) void prep_group_kernel(PrepGroup g, unsigned n
     __shared__ float red[4];
     constexpr bool VF16 = VQUANT && !BWD;
     const int tiles_q = g.Lp / 64, tiles_kv = g.Lp_kv / 64;
-    const int per_g = (tiles_q + kBoundParts - 1) / kBoundParts, nch_g = (tiles_q + per_g - 1) / per_g;        // 64-row tiles per chunk, chunks
-    const int per_v = BWD ? (tiles_kv + kBoundParts - 1) / kBoundParts : 1, nch_v = (tiles_kv + per_v - 1) / per_v;
+    const int per_g = bound_chunk_tiles(tiles_q), nch_g = (tiles_q + per_g - 1) / per_g;        // 64-row tiles per chunk, chunks
+    const int per_v = BWD ? bound_chunk_tiles(tiles_kv) : 1, nch_v = (tiles_kv + per_v - 1) / per_v;
     const unsigned n_g = BWD ? (unsigned)g.BHq * nch_g : 0u, n_v = (unsigned)g.BHkv * nch_v;
     const unsigned n_q = g.q_out ? (unsigned)g.BHq * tiles_q : 0u;
     for (unsigned blk = blockIdx.x; blk < nblocks; blk += gridDim.x) {
         unsigned i = blk;
         float n2 = 0.0f;
         if (BWD && i < n_g) {
-            const int bh = (int)(i / nch_g), ch = (int)(i % nch_g);
-            float dmax = 0.0f;
-            for (int t = ch * per_g; t < min(tiles_q, (ch + 1) * per_g); ++t)
-                grad_tile(bh, t * 64, g.d_o, g.o_acc, g.o_is_bf16, g.lse, g.L, g.Lp, g.D, g.rs, g.rowstat, g.dob, n2, dmax);
-            const float nrm = sqrtf(wg_max(n2, red)) * 1.0001f;           // rounded up a little: it is an upper bound
-            dmax = wg_max(dmax, red);
-            float* p1 = g.bounds + ((size_t)g.BHq + bh) * kBoundParts;
-            float* p2 = g.bounds + ((size_t)2 * g.BHq + bh) * kBoundParts;
-            if (threadIdx.x == 0) { p1[ch] = nrm; p2[ch] = dmax; }
-            if (ch == 0 && (int)threadIdx.x >= nch_g && threadIdx.x < kBoundParts) { p1[threadIdx.x] = 0.0f; p2[threadIdx.x] = 0.0f; }
+            grad_chunk(g.grad, (int)(i / nch_g), (int)(i % nch_g), per_g, nch_g, g.BHq, g.L, g.Lp, g.D, red);
             continue;
         }
         i -= n_g;
@@ -359,12 +288,8 @@ __global__ __launch_bounds__(256) void prep_group_kernel(PrepGroup g, unsigned n
             for (int t = ch * per_v; t < min(tiles_kv, (ch + 1) * per_v); ++t)
                 prep_tile<VQUANT && SRC == 0, VF16, SRC != 0, SRC == 2, BWD>(tile, bh, t * 64, g.v, g.L_kv, g.Lp_kv, g.D, const_cast<uint8_t*>(g.codes[2]),
                     const_cast<uint8_t*>(g.scales[2]), nullptr, BWD ? g.v_out : nullptr, BWD ? nullptr : g.v_out, nullptr, ps, n2);
-            if constexpr (BWD) {
-                const float nrm = sqrtf(wg_max(n2, red)) * 1.0001f;
-                float* p0 = g.bounds + (size_t)bh * kBoundParts;
-                if (threadIdx.x == 0) p0[ch] = nrm;
-                if (ch == 0 && (int)threadIdx.x >= nch_v && threadIdx.x < kBoundParts) p0[threadIdx.x] = 0.0f;
-            } else if (gridDim.x < nblocks) __syncthreads();              // the next tile of this workgroup takes the LDS tile
+            if constexpr (BWD) write_bound(g.grad.bounds + (size_t)bh * kBoundParts, ch, nch_v, sqrtf(wg_max(n2, red)) * 1.0001f);
+            else if (gridDim.x < nblocks) __syncthreads();              // the next tile of this workgroup takes the LDS tile
             continue;
         }
         i -= n_v;
@@ -386,8 +311,8 @@ __global__ __launch_bounds__(256) void prep_group_kernel(PrepGroup g, unsigned n
 int launch_prep_group(const PrepGroup& g, hipStream_t st)
 {
     const int tiles_q = g.Lp / 64, tiles_kv = g.Lp_kv / 64;
-    const bool bwd = g.d_o != nullptr;
-    auto chunks = [](int tiles) { const int per = (tiles + kBoundParts - 1) / kBoundParts; return (tiles + per - 1) / per; };
+    const bool bwd = g.grad.d_o != nullptr;
+    auto chunks = [](int tiles) { const int per = bound_chunk_tiles(tiles); return (tiles + per - 1) / per; };
     long long n = (long long)g.BHkv * (bwd ? chunks(tiles_kv) : tiles_kv);
     if (g.q_out) n += (long long)g.BHq * tiles_q;
     if (g.k_out) n += (long long)g.BHkv * tiles_kv;
@@ -396,7 +321,7 @@ int launch_prep_group(const PrepGroup& g, hipStream_t st)
     const unsigned nblocks = (unsigned)n, grid = min(nblocks, 1u << 22);       // (a grid has fewer than 2^32 threads)
     auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, g, nblocks); };
     const bool packed = g.codes[2] != nullptr, paged = g.ps.cache != nullptr;
-    if (bwd)          { if (packed) go(prep_group_kernel<1, true, true>); else if (g.v_quant) go(prep_group_kernel<0, true, true>); else go(prep_group_kernel<0, false, true>); }
+    if (bwd)          { if (packed) go(prep_group_kernel<1, true, true>); else go(prep_group_kernel<0, true, true>); }
     else if (paged)   go(prep_group_kernel<2, true, false>);
     else if (packed)  go(prep_group_kernel<1, true, false>);
     else if (g.v_quant) go(prep_group_kernel<0, true, false>);

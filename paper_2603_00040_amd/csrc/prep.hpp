@@ -1,0 +1,90 @@
+// The part of the backward's preparation that does not depend on the format of Q, K and V (device code shared by prep.hip and
+// mxprep.hip).
+#pragma once
+#include "common.hpp"
+#include "kernels.hpp"
+
+namespace aq {
+
+// 64-row tiles per chunk of the partial maxima: at most kBoundParts chunks per head.
+__host__ __device__ inline int bound_chunk_tiles(int tiles) { return (tiles + kBoundParts - 1) / kBoundParts; }
+
+// The statistics that the backward needs of 64 rows of dO and O' (Alg. 3, first line): rowstat = {L log2(e), D / sqrt(d)} with
+// D = rowsum(dO o O') (padding rows hold {0, 0}), the largest |dO_i|^2 and |D_i| / sqrt(d) so far in n2 and dmax, and the zero-padded
+// copy of dO where one is asked for (dob).
+__device__ __forceinline__ void grad_tile(int bh, int l0, const uint16_t* __restrict__ dO, const void* __restrict__ o_acc, bool o_is_bf16,
+                                          const float* __restrict__ lse, int L, int Lp, int D, float rs,
+                                          float2* __restrict__ rowstat, uint16_t* __restrict__ dob, float& n2, float& dmax)
+{
+    const int nb = D / 16;
+    for (int blk = threadIdx.x; blk < 64 * nb; blk += 256) {
+        const int row = blk / nb, cb = blk % nb, l = l0 + row;
+        uint4v g[2] = {};
+        float dot = 0.0f, nrm = 0.0f;
+        if (l < L) {
+            const size_t off = ((size_t)bh * L + l) * D + cb * 16;
+            g[0] = reinterpret_cast<const uint4v*>(dO + off)[0];
+            g[1] = reinterpret_cast<const uint4v*>(dO + off)[1];
+            float o[16];
+            if (o_is_bf16) {                       // ablation: D from the low-precision output
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const uint4v w = reinterpret_cast<const uint4v*>(static_cast<const uint16_t*>(o_acc) + off)[t];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) { o[8 * t + 2 * i] = __uint_as_float(w[i] << 16); o[8 * t + 2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u); }
+                }
+            } else {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const floatx4 w = reinterpret_cast<const floatx4*>(static_cast<const float*>(o_acc) + off)[t];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) o[4 * t + i] = w[i];
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float lo = __uint_as_float(g[t][i] << 16), hi = __uint_as_float(g[t][i] & 0xFFFF0000u);
+                    dot += lo * o[8 * t + 2 * i] + hi * o[8 * t + 2 * i + 1];
+                    nrm = fmaf(lo, lo, fmaf(hi, hi, nrm));
+                }
+        }
+        for (int w = nb / 2; w >= 1; w >>= 1) { dot += __shfl_xor(dot, w); nrm += __shfl_xor(nrm, w); }
+        dot *= rs;
+        if (cb == 0) rowstat[(size_t)bh * Lp + l] = make_float2(l < L ? lse[(size_t)bh * L + l] * 1.4426950408889634f : 0.0f, dot);
+        n2 = fmaxf(n2, nrm);
+        dmax = fmaxf(dmax, fabsf(dot));
+        if (dob) {
+            uint4v* dst = reinterpret_cast<uint4v*>(dob + ((size_t)bh * Lp + l) * D + cb * 16);
+            dst[0] = g[0]; dst[1] = g[1];
+        }
+    }
+}
+
+// Largest value of a workgroup; every thread gets it.  (The barriers also keep `red` from being overwritten too early.)
+__device__ inline float wg_max(float v, float (&red)[4]) {
+#pragma unroll
+    for (int w = 32; w >= 1; w >>= 1) v = fmaxf(v, __shfl_xor(v, w));
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+}
+
+// Partial maximum `ch` of a head (nch of them); the unused ones are written as 0.  All threads hold the value.
+__device__ inline void write_bound(float* part, int ch, int nch, float value) {
+    if (threadIdx.x == 0) part[ch] = value;
+    if (ch == 0 && (int)threadIdx.x >= nch && threadIdx.x < kBoundParts) part[threadIdx.x] = 0.0f;
+}
+
+// Chunk ch (of nch, `per` tiles of 64 rows each) of query head bh.
+__device__ __forceinline__ void grad_chunk(const GradArgs& a, int bh, int ch, int per, int nch, int BHq, int L, int Lp, int D, float (&red)[4]) {
+    float n2 = 0.0f, dmax = 0.0f;
+    for (int t = ch * per; t < min(Lp / 64, (ch + 1) * per); ++t)
+        grad_tile(bh, t * 64, a.d_o, a.o_acc, a.o_is_bf16, a.lse, L, Lp, D, a.rs, a.rowstat, a.dob, n2, dmax);
+    write_bound(a.bounds + ((size_t)BHq + bh) * kBoundParts, ch, nch, sqrtf(wg_max(n2, red)) * 1.0001f);      // rounded up a little: it is an upper bound
+    write_bound(a.bounds + ((size_t)2 * BHq + bh) * kBoundParts, ch, nch, wg_max(dmax, red));
+}
+
+}  // namespace aq

@@ -88,3 +88,20 @@ def test_sparse_argument_errors():
         aq.attnqat_fwd_infer_mx_sparse(q, k, v, False, torch.ones((1, 2, 2, 3), dtype=torch.uint8, device="cuda"))
     with pytest.raises(aq.AttnQatError):
         aq.attnqat_fwd_infer_mx_sparse(q, k, v, False, torch.ones((1, 2, 2, 2), dtype=torch.int32, device="cuda"))
+
+
+@pytest.mark.parametrize("nb,first", [(64, 60), (65, 60), (65, 64), (130, 3)])
+def test_more_blocks_than_a_wave_lists_at_once(nb, first):
+    """Keeping the key blocks from `first` on is attention to those keys, bit for bit (records and tiles are the same)."""
+    import paper_2603_00040_amd as aq
+    B, Hq, Hkv, d = 1, 2, 1, 64
+    L = nb * 128 - 5
+    x = random_inputs(B, Hq, Hkv, L, d, seed=nb)
+    q, k, v = (to_dev(x[n]) for n in ("q", "k", "v"))
+    mask = torch.zeros((B, Hq, nb, nb), dtype=torch.uint8, device="cuda")
+    mask[..., first:] = 1
+    o, lse = aq.attnqat_fwd_infer_mx_sparse(q, k, v, False, mask)
+    rows = min(L - 128 * first, 128)          # as many queries as there are keys
+    qs = q[:, :, :L - 128 * first].contiguous()
+    ro, rl = aq.attnqat_fwd_infer_mx(qs, k[:, :, 128 * first:].contiguous(), v[:, :, 128 * first:].contiguous(), False)
+    assert torch.equal(o[:, :, :rows], ro[:, :, :rows]) and torch.equal(lse[:, :, :rows], rl[:, :, :rows])
