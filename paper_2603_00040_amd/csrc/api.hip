@@ -294,7 +294,7 @@ int attnqat_quantize(const void* x, int B, int H, int L, int d, int dtype,
     int rc = check_dims(B, H, H, L, d, dtype);
     if (rc) return rc;
     prof_begin((hipStream_t)stream);
-    if (launch_prep(x, B * H, L, d, true, false, codes, scales, xf, nullptr, nullptr, (hipStream_t)stream))
+    if (launch_quantize(x, B * H, L, d, codes, scales, xf, (hipStream_t)stream))
         return ATTNQAT_ELAUNCH;
     prof_mark("quantize", (hipStream_t)stream);
     return ATTNQAT_OK;
@@ -493,10 +493,7 @@ int paged_common(const void* q, int B, int Hq, int Hkv, int Lq, int d, int causa
     hipStream_t st = (hipStream_t)stream;
     prof_begin(st);
     if (w.dec) {
-        // q [B,Hq,Lq,d] is [B*Hkv, G*Lq, d] in memory: the rows of a kv group form one tile
-        if (launch_prep(q, B * Hkv, (Hq / Hkv) * Lq, d, true, true, nullptr, nullptr, nullptr, w.qh, nullptr, st)) return ATTNQAT_ELAUNCH;
-        prof_mark("prep_q", st);
-        if (launch_decode(w.qh, cache, num_pages, page_table, max_pages, kv_lens, B, Hq, Hkv, Lq, d, causal != 0, w.dec, spin_limit, o, lse, st))
+        if (launch_decode(q, w.qh, cache, num_pages, page_table, max_pages, kv_lens, B, Hq, Hkv, Lq, d, causal != 0, w.dec, spin_limit, o, lse, st))
             return ATTNQAT_ELAUNCH;
         prof_mark("decode_paged", st);
         if (dec_ws) *dec_ws = w.dec;

@@ -14,7 +14,7 @@
 //     counter), and whoever holds a ticket is running: the holder of the lowest unfinished ticket never waits, so every
 //     wait ends.  The wait is bounded all the same (spin_limit polls; on expiry an error word is set and the kernel
 //     finishes with that chunk's maxima missing).
-// The queue holds only chunks that exist: a small kernel in front lists them (sequence, kv head, chunk, key count) in
+// The queue holds only chunks that exist: a small kernel in front (which also makes phi(Q)) lists them (sequence, kv head, chunk, key count) in
 // chunk-major order, so that a ticket is one 16-byte read away from everything a workgroup needs to know, and a workgroup
 // knows its next chunk while it works on the current one: the next chunk's first K tiles and its query rows are requested
 // during the second half of the current chunk, and the stream from the cache never stops at a chunk boundary.
@@ -24,6 +24,7 @@
 // LDS read can hand the matrix instruction keys-contiguous operands.
 #include "common.hpp"
 #include "kernels.hpp"
+#include "nvfp4.hpp"
 
 namespace aq {
 
@@ -84,71 +85,110 @@ __device__ inline half8 dequant8(const RawKV<D>& r, half2v sc, int s) {
     return __builtin_bit_cast(half8, v);
 }
 
-// Before every step: clears the queue's counters and the tagged row maxima (ints [0, nz) from ctl on, except ctl[2]), and
-// workgroup 0 lists the chunks that exist, in chunk-major order, as items of kDecItemInts ints {sequence, kv head, chunk,
-// keys of the sequence, the page ids of the chunk's (at most 8) pages, -1 where the sequence has none}, their number going
-// to ctl[2].  A (sequence, kv head) without keys gets its result here: O = 0, L = -inf.
-__global__ __launch_bounds__(256) void decode_plan_kernel(const int* __restrict__ kv_lens, const int* __restrict__ page_table,
-                                                          int B, int Hkv, int R, int D, int CK, int NC,
-                                                          int max_pages, int* __restrict__ ctl, int nz, int* __restrict__ work,
-                                                          uint16_t* __restrict__ O, float* __restrict__ lse)
+// Before every step, three things that do not depend on each other, by different workgroups of one launch:
+//   * workgroups [0, NC): workgroup ch lists the chunks number ch of all sequences, as items of kDecItemInts ints {sequence, kv head,
+//     chunk, keys of the sequence, the page ids of the chunk's (at most 8) pages, -1 where the sequence has none}.  The list is in
+//     chunk-major order, and the chunks in front of number ch are sum_b min(chunks of b, ch), so nobody waits for anybody.
+//     Workgroup 0 also writes their number to ctl[2] and, for a (sequence, kv head) without keys, the result: O = 0, L = -inf.
+//   * the next nq: phi(Q), two (sequence, kv head)s each: [B*Hkv][128][D] fp16, rows R .. 15 zero (the kernel reads 16 rows)
+//   * the rest: the queue's counters and the tagged row maxima (ints [0, nz) from ctl on, except ctl[2]) are cleared
+// (One workgroup that listed everything and a launch of its own for phi(Q): 9.6 + 5.6 us of 124 for 32 sequences of 8 kv heads;
+// together now ANNO.)
+template <int D>
+__global__ __launch_bounds__(256) void decode_prepare_kernel(const int* __restrict__ kv_lens, const int* __restrict__ page_table,
+                                                             int B, int Hkv, int R, int CK, int NC,
+                                                             int max_pages, int* __restrict__ ctl, int nz, int* __restrict__ work,
+                                                             uint16_t* __restrict__ O, float* __restrict__ lse,
+                                                             const uint16_t* __restrict__ q, half_t* __restrict__ qh, int nq)
 {
     const int tid = threadIdx.x;
-    const int gi = blockIdx.x * 256 + tid;
-    if (gi < nz && gi != 2) ctl[gi] = 0;
-    if (blockIdx.x != 0) return;
-    __shared__ int cnt[4];
-    __shared__ int lens_s[2048];
-    const int BH = B * Hkv;
-    const bool staged = B <= 2048;                            // the sequences' key counts, next to the lanes that walk over them
-    if (staged)
-        for (int i = tid; i < B; i += 256) lens_s[i] = min(kv_lens[i], max_pages * 128);
-    __syncthreads();
-    const int P = NC * B;                                     // pair p = chunk * B + sequence; its Hkv heads are neighbours in the list
-    const int per = (P + 255) / 256;                          // (the host has checked that NC * B * Hkv fits an int)
-    const int p0 = min(P, tid * per), p1 = min(P, p0 + per);
-    auto walk = [&](auto&& visit) __attribute__((always_inline)) {
-        if (p0 >= p1) return;
-        int ch = p0 / B, b = p0 % B;
-        for (int q = p0; q < p1; ++q) {
-            const int Lk = staged ? lens_s[b] : min(kv_lens[b], max_pages * 128);
-            if (Lk >= 1 && (long long)ch * CK < Lk) visit(b, ch, Lk);
-            if (++b == B) { b = 0; ++ch; }
-        }
-    };
-    int n = 0;
-    walk([&](int, int, int) { ++n; });
-    // inclusive prefix sums: inside each wave by shuffles, then the four waves' totals
-    int incl = n;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int up = __shfl_up(incl, d);
-        if ((tid & 63) >= d) incl += up;
+    if ((int)blockIdx.x >= NC + nq) {
+        const int gi = ((int)blockIdx.x - NC - nq) * 256 + tid;
+        if (gi < nz && gi != 2) ctl[gi] = 0;
+        return;
     }
-    if ((tid & 63) == 63) cnt[tid >> 6] = incl;
-    __syncthreads();
-    for (int w = 0; w < (tid >> 6); ++w) incl += cnt[w];
-    const int total = cnt[0] + cnt[1] + cnt[2] + cnt[3];
-    size_t pos = (size_t)(incl - n) * Hkv;
-    walk([&](int b, int ch, int Lk) {
-        int pg[8];
+    const int BH = B * Hkv;
+    if ((int)blockIdx.x >= NC) {
+        constexpr int nb = D / 16, PER = 256 / (16 * nb);           // blocks of a row, (sequence, kv head)s per workgroup
+        const int bh = ((int)blockIdx.x - NC) * PER + tid / (16 * nb), row = tid / nb % 16, cb = tid % nb;
+        if (bh >= BH) return;
+        float v[16], xf[16], s = 0.0f;
+        uint32_t clo = 0, chi = 0;
+        if (row < R) {
+            const uint4v* src = reinterpret_cast<const uint4v*>(q + ((size_t)bh * R + row) * D + cb * 16);
+            const uint4v a = src[0], b = src[1];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int pi = ch * (CK / 128) + j;
-            pg[j] = pi < max_pages && pi * 128 < Lk ? page_table[(size_t)b * max_pages + pi] : -1;
+            for (int i = 0; i < 4; ++i) {
+                v[2 * i]         = __uint_as_float(a[i] << 16);
+                v[2 * i + 1]     = __uint_as_float(a[i] & 0xFFFF0000u);
+                v[8 + 2 * i]     = __uint_as_float(b[i] << 16);
+                v[8 + 2 * i + 1] = __uint_as_float(b[i] & 0xFFFF0000u);
+            }
+            phi_block16_bf16(v, s, clo, chi);
         }
-        for (int h = 0; h < Hkv; ++h) {
-            int4* item = reinterpret_cast<int4*>(work + kDecItemInts * pos++);
-            item[0] = make_int4(b, h, ch, Lk);
+        dequant_block16(clo, chi, s, xf);
+        uint4v o[2];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) o[i >> 2][i & 3] = pack_f16x2(xf[2 * i], xf[2 * i + 1]);
+        uint4v* dst = reinterpret_cast<uint4v*>(qh + ((size_t)bh * 128 + row) * D + cb * 16);
+        dst[0] = o[0]; dst[1] = o[1];
+        return;
+    }
+    __shared__ int red[4];
+    __shared__ int rank[256], len_s[256];
+    auto len_of = [&](int b) __attribute__((always_inline)) { return max(0, min(kv_lens[b], max_pages * 128)); };
+    auto wg_sum = [&](int v) __attribute__((always_inline)) {
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d);
+        __syncthreads();
+        if ((tid & 63) == 0) red[tid >> 6] = v;
+        __syncthreads();
+        return red[0] + red[1] + red[2] + red[3];
+    };
+    const int ch = blockIdx.x;
+    int front = 0, all = 0;                                   // (the host has checked that NC * B * Hkv fits an int)
+    for (int b = tid; b < B; b += 256) {
+        const int n = (len_of(b) + CK - 1) / CK;
+        front += min(n, ch);
+        all += n;
+    }
+    front = wg_sum(front);
+    if (ch == 0) {
+        all = wg_sum(all);
+        if (tid == 0) ctl[2] = all * Hkv;
+    }
+    for (int b0 = 0; b0 < B; b0 += 256) {                     // 256 sequences at a time: which of them have a chunk ch, then its items
+        const int b = b0 + tid, Lk = b < B ? len_of(b) : 0;
+        const bool on = (long long)ch * CK < Lk;
+        const unsigned long long m = __builtin_amdgcn_ballot_w64(on);
+        __syncthreads();
+        if ((tid & 63) == 0) red[tid >> 6] = __popcll(m);
+        __syncthreads();
+        int r = __popcll(m & ((1ull << (tid & 63)) - 1ull));
+        for (int w = 0; w < (tid >> 6); ++w) r += red[w];
+        rank[tid] = on ? front + r : -1;
+        len_s[tid] = Lk;
+        front += red[0] + red[1] + red[2] + red[3];
+        __syncthreads();
+        const int nb = min(256, B - b0);
+        for (int i = tid; i < nb * Hkv; i += 256) {
+            const int bl = i / Hkv, h = i % Hkv, pos = rank[bl], len = len_s[bl];
+            if (ch == 0 && len < 1) {
+                const size_t bh = (size_t)(b0 + bl) * Hkv + h;
+                for (int e = 0; e < R * D; ++e) O[bh * R * D + e] = 0;
+                for (int rr = 0; rr < R; ++rr) lse[bh * R + rr] = -INFINITY;
+            }
+            if (pos < 0) continue;
+            int pg[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int pi = ch * (CK / 128) + j;
+                pg[j] = pi < max_pages && pi * 128 < len ? page_table[(size_t)(b0 + bl) * max_pages + pi] : -1;
+            }
+            int4* item = reinterpret_cast<int4*>(work + (size_t)kDecItemInts * ((size_t)pos * Hkv + h));
+            item[0] = make_int4(b0 + bl, h, ch, len);
             item[1] = make_int4(pg[0], pg[1], pg[2], pg[3]);
             item[2] = make_int4(pg[4], pg[5], pg[6], pg[7]);
-        }
-    });
-    if (tid == 0) ctl[2] = total * Hkv;
-    for (int bh = tid; bh < BH; bh += 256) {
-        if ((staged ? lens_s[bh / Hkv] : kv_lens[bh / Hkv]) < 1) {
-            for (int e = 0; e < R * D; ++e) O[(size_t)bh * R * D + e] = 0;
-            for (int r = 0; r < R; ++r) lse[(size_t)bh * R + r] = -INFINITY;
         }
     }
 }
@@ -160,7 +200,7 @@ __global__ __launch_bounds__(256, 2) void decode_kernel(
     const half_t* __restrict__ Qh,           // [B*Hkv][128][D] fp16: phi(Q), row r = (query head of the group) * Lq + position; rows >= R zero
     const unsigned char* __restrict__ cache, int num_pages, int Hkv, int Lq, int R, int CK, int NC, int spin_limit,
     int* ctl /* [0] ticket counter, [1] error word, [2] number of chunks in the list */,
-    const int* __restrict__ work /* the list of chunks, see decode_plan_kernel */,
+    const int* __restrict__ work /* the list of chunks, see decode_prepare_kernel */,
     unsigned long long* cmax /* per chunk and row: {1, row maximum} once known, 0 before */,
     float* part_o, float* part_l, float* part_m,        // shared between workgroups: no __restrict__
     uint16_t* __restrict__ O, float* __restrict__ lse, float c /* log2(e)/sqrt(d) */)
@@ -555,7 +595,7 @@ size_t decode_ws_bytes(int B, int Hkv, int R, int max_pages, int D)
     return n;
 }
 
-int launch_decode(const void* qh, const void* cache, int num_pages, const int* page_table, int max_pages, const int* kv_lens,
+int launch_decode(const void* q, void* qh, const void* cache, int num_pages, const int* page_table, int max_pages, const int* kv_lens,
                   int B, int Hq, int Hkv, int Lq, int D, bool causal, void* ws, int spin_limit, void* o, float* lse, hipStream_t st)
 {
     const int R = (Hq / Hkv) * Lq;
@@ -574,8 +614,11 @@ int launch_decode(const void* qh, const void* cache, int num_pages, const int* p
     const size_t nz64 = ((unsigned char*)cmax - (unsigned char*)ctl) / 4 + units * kDecRows * 2;
     if (nz64 > 0x7FFFFFFFull) return -1;
     const int nz = (int)nz64;
-    hipLaunchKernelGGL(decode_plan_kernel, dim3((nz + 255) / 256), dim3(256), 0, st, kv_lens, page_table, B, Hkv, R, D, CK, NC, max_pages, ctl, nz, work,
-                       (uint16_t*)o, lse);
+    const int per = 256 / D, nq = (B * Hkv + per - 1) / per;                        // see decode_prepare_kernel
+#define AQ_PREP(DD) hipLaunchKernelGGL(decode_prepare_kernel<DD>, dim3((unsigned)(NC + nq + (nz + 255) / 256)), dim3(256), 0, st, kv_lens, page_table, B, Hkv, R, CK, NC, \
+        max_pages, ctl, nz, work, (uint16_t*)o, lse, (const uint16_t*)q, (half_t*)qh, nq)
+    if (D == 128) AQ_PREP(128); else AQ_PREP(64);
+#undef AQ_PREP
     if (hipGetLastError() != hipSuccess) return -1;
     const int cus = device_cu_count();
     const unsigned grid = (unsigned)min((size_t)2 * cus, units);

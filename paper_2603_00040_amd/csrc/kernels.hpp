@@ -5,15 +5,8 @@
 
 namespace aq {
 
-// phi (+ layout copies).  x [BH, L, D] bf16.  Any output may be null.
-//   codes/scales/xf_pub: the public packed NVFP4 tensor and its bf16 dequantized copy
-//   xr [BH, Lp, D]: dequantized rows, zero padded to Lp = round_up(L, 128)
-//   xt [BH, D, Lp]: the same, transposed, sequence positions permuted inside groups of 16
-//   quant=false copies x unchanged (bf16 only).  out_f16 selects fp16 for xr/xt.
-//   sub (optional) [BH, D] fp32: subtracted from every row before phi (K smoothing: the token mean of each channel)
-int launch_prep(const void* x, int BH, int L, int D, bool quant, bool out_f16,
-                uint8_t* codes, uint8_t* scales, void* xf_pub, void* xr, void* xt, hipStream_t st,
-                const float* sub = nullptr);
+// phi of x [BH, L, D] bf16 in the public layout (codes, scales, bf16 dequantized copy xf; any may be null).
+int launch_quantize(const void* x, int BH, int L, int D, uint8_t* codes, uint8_t* scales, void* xf, hipStream_t st);
 
 // The pages of an NVFP4 KV cache as a source of K or V.
 struct PagedSrc {
@@ -49,7 +42,7 @@ int launch_prep_group(const PrepGroup& g, hipStream_t st);
 size_t colmean_scratch_bytes(int BH, int D);
 int launch_colmean(const void* x, int BH, int L, int D, double* scratch, float* mean, hipStream_t st);
 
-// Alg. 1 (train=false) / Alg. 2 (train=true) on fp16 copies made by launch_prep.
+// Alg. 1 (train=false) / Alg. 2 (train=true) on copies made by launch_prep_group.
 // p_quant 1 (MX): qh and kh are NOT fp16 copies but the operand arrays of the scaled FP4 instruction (launch_mx_group,
 // MX_TRAIN: qops with its scale dwords in qsc, and krec): the scores are computed from the codes; vt stays the fp16 copy.
 // p_quant: phi(P-tilde) 0 NVFP4; 1 in the MX format (blocks of 32 keys, power-of-two scale); 2 NVFP4 after the
@@ -69,13 +62,13 @@ int launch_kv_page_write(const void* k, const void* v, int Hkv, int n, int D, in
                          void* cache, int num_pages, const int* page_ids, hipStream_t st);
 
 // Alg. 1 for decode steps over the NVFP4 pages: at most decode_max_rows() query rows per (sequence, kv head), i.e.
-// (Hq / Hkv) * Lq of them; qh [B*Hkv][128][D] fp16 is phi(Q) with the rows of a kv group together (launch_prep on q taken as
-// [B*Hkv, (Hq/Hkv)*Lq, D]).  ws: decode_ws_bytes() bytes.  spin_limit bounds the polls of a chunk waiting for the row maxima
+// (Hq / Hkv) * Lq of them; q [B*Hkv, (Hq/Hkv)*Lq, D] (the rows of a kv group are neighbours in [B,Hq,Lq,d]); qh: scratch for
+// phi(Q), [B*Hkv][128][D] fp16.  ws: decode_ws_bytes() bytes.  spin_limit bounds the polls of a chunk waiting for the row maxima
 // of the chunks before it (see decode.hip); if it runs out the int at ws + 4 is set and that result is wrong.
 int decode_max_rows();
 int decode_chunk_keys(int R);
 size_t decode_ws_bytes(int B, int Hkv, int R, int max_pages, int D);
-int launch_decode(const void* qh, const void* cache, int num_pages, const int* page_table, int max_pages, const int* kv_lens,
+int launch_decode(const void* q, void* qh, const void* cache, int num_pages, const int* page_table, int max_pages, const int* kv_lens,
                   int B, int Hq, int Hkv, int Lq, int D, bool causal, void* ws, int spin_limit, void* o, float* lse, hipStream_t st);
 
 // The MX format's operand arrays of the scaled FP4 instruction, from which the backward recomputes the scores (launch_mx_group):

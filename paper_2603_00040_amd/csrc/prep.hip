@@ -8,6 +8,7 @@
 #include "common.hpp"
 #include "kernels.hpp"
 #include "prep.hpp"
+#include "nvfp4.hpp"
 
 namespace aq {
 
@@ -17,42 +18,6 @@ namespace aq {
 // 32-63) of such a group, so with this order its 8 values pair with one contiguous
 // 16-byte run of the transposed operand.
 __host__ __device__ inline int perm16(int p) { return (p & ~12) | ((p & 4) << 1) | ((p & 8) >> 1); }
-
-// phi of one block of 16 values that are bf16 numbers (Eq. 1): the E4M3 scale s and the 16 E2M1 codes, element 2k in the low
-// nibble of byte k of {clo, chi}.
-// RNE of the real quotient x / s without a division per element (ten vector instructions each, which bound the streaming
-// kernels).  |x| has 8 significant bits and s has 4, so a quotient that is not on a rounding boundary of the E2M1 grid is at
-// least 2^-9 (relative) away from it, and one that is on a boundary (a tie) has at most 3 significant bits.  x * (1/s) with the
-// approximate reciprocal is within 2^-21 of the quotient; rounding that product to 12 significant bits puts a tie back on its
-// boundary exactly and moves nothing else across one (it moves a value by at most 2^-12).  The rounding to E2M1 itself
-// (nearest, ties to even, saturating at 6, sign kept) then is the hardware conversion, two elements per instruction, which
-// leaves the codes packed as the public layout wants them.
-__device__ inline void phi_block16_bf16(const float (&v)[16], float& s, uint32_t& clo, uint32_t& chi)
-{
-    float amax = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) amax = fmaxf(amax, fabsf(v[i]));
-    s = block_scale_exact(amax);
-    const float inv_s = s > 0.0f ? __builtin_amdgcn_rcpf(s) : 0.0f;      // s = 0: every quotient 0, every code 0
-    auto snap = [](float r) __attribute__((always_inline)) {
-        return __uint_as_float((__float_as_uint(r) + 0x800u) & 0xFFFFF000u);
-    };
-    clo = 0; chi = 0;
-#define AQ_PAIR(W, PR, SEL) W = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(W, snap(v[2 * (PR)] * inv_s), snap(v[2 * (PR) + 1] * inv_s), 1.0f, SEL)
-    AQ_PAIR(clo, 0, 0); AQ_PAIR(clo, 1, 1); AQ_PAIR(clo, 2, 2); AQ_PAIR(clo, 3, 3);
-    AQ_PAIR(chi, 4, 0); AQ_PAIR(chi, 5, 1); AQ_PAIR(chi, 6, 2); AQ_PAIR(chi, 7, 3);
-#undef AQ_PAIR
-}
-
-// The 16 values of a block from its codes and its scale (exact: <= 6 significant bits).
-__device__ inline void dequant_block16(uint32_t clo, uint32_t chi, float s, float (&xf)[16])
-{
-    typedef float float2v __attribute__((ext_vector_type(2)));
-#define AQ_BACK(W, PR, SEL) { const float2v cv = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(W, 1.0f, SEL); xf[2 * (PR)] = cv[0] * s; xf[2 * (PR) + 1] = cv[1] * s; }
-    AQ_BACK(clo, 0, 0) AQ_BACK(clo, 1, 1) AQ_BACK(clo, 2, 2) AQ_BACK(clo, 3, 3)
-    AQ_BACK(chi, 4, 0) AQ_BACK(chi, 5, 1) AQ_BACK(chi, 6, 2) AQ_BACK(chi, 7, 3)
-#undef AQ_BACK
-}
 
 // The NVFP4 KV cache: a page holds 128 consecutive positions of one sequence for all kv heads; per kv head, in this order,
 // K codes [128][D/2], K scale bytes [128][D/16], V codes [128][D/2], V scale bytes [128][D/16]: the public layout of
@@ -217,39 +182,40 @@ __device__ __forceinline__ void prep_tile(
         }
         if (xt) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                tile[row][cb * 16 + 2 * i]     = (uint16_t)(w[i] & 0xFFFFu);
-                tile[row][cb * 16 + 2 * i + 1] = (uint16_t)(w[i] >> 16);
-            }
+            for (int i = 0; i < 8; ++i) reinterpret_cast<uint32_t*>(&tile[row][cb * 16])[i] = w[i];      // (rows are 4-byte aligned)
         }
     }
     if (xt) {
         __syncthreads();
-        // transposed copy [bh][c][Lp]: 8 positions (16 bytes) per store
-        for (int ch = threadIdx.x; ch < D * 8; ch += 256) {
-            const int c = ch >> 3, kc = ch & 7;
-            uint4v o;
+        // transposed copy [bh][c][Lp]: 8 positions (16 bytes) per store; a thread takes them of two neighbouring columns, which
+        // lie in one LDS word
+        for (int ch = threadIdx.x; ch < D * 4; ch += 256) {
+            const int c = 2 * (ch >> 3), kc = ch & 7;
+            uint32_t x[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int p = kc * 8 + j;
+                x[j] = *reinterpret_cast<const uint32_t*>(&tile[(p & ~15) | perm16(p & 15)][c]);
+            }
+            uint4v lo, hi;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const int p0 = kc * 8 + 2 * j, p1 = p0 + 1;
-                const int r0 = (p0 & ~15) | perm16(p0 & 15), r1 = (p1 & ~15) | perm16(p1 & 15);
-                o[j] = (uint32_t)tile[r0][c] | ((uint32_t)tile[r1][c] << 16);
+                lo[j] = __builtin_amdgcn_perm(x[2 * j + 1], x[2 * j], 0x05040100u);
+                hi[j] = __builtin_amdgcn_perm(x[2 * j + 1], x[2 * j], 0x07060302u);
             }
-            *reinterpret_cast<uint4v*>(xt + ((size_t)bh * D + c) * Lp + l0 + kc * 8) = o;
+            uint16_t* dst = xt + ((size_t)bh * D + c) * Lp + l0 + kc * 8;
+            *reinterpret_cast<uint4v*>(dst) = lo;
+            *reinterpret_cast<uint4v*>(dst + Lp) = hi;
         }
     }
 }
 
-// One tensor, every kind of output.
-template <bool QUANT, bool OUT_F16>
-__global__ __launch_bounds__(256) void prep_kernel(
-    const uint16_t* __restrict__ x, int L, int Lp, int D,
-    uint8_t* __restrict__ codes, uint8_t* __restrict__ scales, uint16_t* __restrict__ xf_pub,
-    uint16_t* __restrict__ xr, uint16_t* __restrict__ xt, const float* __restrict__ sub)
+// The public quantizer: codes, scales and dequantized values of one tensor.
+__global__ __launch_bounds__(256) void quantize_kernel(const uint16_t* __restrict__ x, int L, int Lp, int D,
+                                                       uint8_t* __restrict__ codes, uint8_t* __restrict__ scales, uint16_t* __restrict__ xf)
 {
-    __shared__ uint16_t tile[64][128 + 2];
     float n2 = 0.0f;
-    prep_tile<QUANT, OUT_F16, false, false, false>(tile, blockIdx.y, blockIdx.x * 64, x, L, Lp, D, codes, scales, xf_pub, xr, xt, sub, PagedSrc{}, n2);
+    prep_tile<true, false, false, false, false>(nullptr, blockIdx.y, blockIdx.x * 64, x, L, Lp, D, codes, scales, xf, nullptr, nullptr, nullptr, PagedSrc{}, n2);
 }
 
 // All tensors that a forward or a backward prepares, as one launch.  Bound by HBM on large problems; on small ones a launch takes
@@ -332,7 +298,8 @@ int launch_prep_group(const PrepGroup& g, hipStream_t st)
 // Writer of the NVFP4 KV cache: phi of n new positions pos0 .. pos0 + n - 1 of one sequence, k and v [Hkv, n, D] bf16, into
 // the pages page_ids[pos / 128] (the sequence's page list).  The slots between the last new position and the end of its page
 // are cleared (codes and scales 0: they read as zeros until the sequence grows into them).  A page id outside [0, num_pages)
-// is left out.  One thread per block of 16 elements; grid (64-row groups, Hkv, 2: K then V).
+// is left out.  One thread per block of 16 elements, in one pass (a call is as long as its chain of loads); grid (groups of
+// 256 blocks, Hkv, 2: K then V).
 template <int D>
 __global__ __launch_bounds__(256) void kv_page_write_kernel(
     const uint16_t* __restrict__ k, const uint16_t* __restrict__ v, int n, int pos0, int Hkv,
@@ -342,35 +309,33 @@ __global__ __launch_bounds__(256) void kv_page_write_kernel(
     const int h = blockIdx.y, which = blockIdx.z;
     const uint16_t* x = (which ? v : k) + (size_t)h * n * D;
     const int rows_total = ((pos0 + n + 127) & ~127) - pos0;
-    for (int blk = threadIdx.x; blk < 64 * nb; blk += 256) {
-        const int row = blockIdx.x * 64 + blk / nb, cb = blk % nb;
-        float s = 0.0f;
-        uint32_t clo = 0, chi = 0;
-        if (row < n) {
-            const uint4v* src = reinterpret_cast<const uint4v*>(x + (size_t)row * D + cb * 16);
-            const uint4v a = src[0], b = src[1];
-            float val[16];
+    const int row = blockIdx.x * (256 / nb) + threadIdx.x / nb, cb = threadIdx.x % nb;
+    const int pos = pos0 + min(row, rows_total - 1);
+    const int page = page_ids[pos >> 7];
+    float s = 0.0f;
+    uint32_t clo = 0, chi = 0;
+    if (row < n) {
+        const uint4v* src = reinterpret_cast<const uint4v*>(x + (size_t)row * D + cb * 16);
+        const uint4v a = src[0], b = src[1];
+        float val[16];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                val[2 * i]         = __uint_as_float(a[i] << 16);
-                val[2 * i + 1]     = __uint_as_float(a[i] & 0xFFFF0000u);
-                val[8 + 2 * i]     = __uint_as_float(b[i] << 16);
-                val[8 + 2 * i + 1] = __uint_as_float(b[i] & 0xFFFF0000u);
-            }
-            phi_block16_bf16(val, s, clo, chi);
+        for (int i = 0; i < 4; ++i) {
+            val[2 * i]         = __uint_as_float(a[i] << 16);
+            val[2 * i + 1]     = __uint_as_float(a[i] & 0xFFFF0000u);
+            val[8 + 2 * i]     = __uint_as_float(b[i] << 16);
+            val[8 + 2 * i + 1] = __uint_as_float(b[i] & 0xFFFF0000u);
         }
-        // the scale bytes of four neighbouring blocks of a row as one dword (rows beyond the page end take part and write nothing)
-        uint32_t sb = e4m3_byte_of(s);
-        sb |= (uint32_t)__shfl_down((int)sb, 1) << 8;
-        sb |= (uint32_t)__shfl_down((int)sb, 2) << 16;
-        if (row >= rows_total) continue;
-        const int pos = pos0 + row;
-        unsigned char* part = const_cast<unsigned char*>(nvfp4_page_part(cache, page_ids[pos >> 7], num_pages, Hkv, h, D, which));
-        if (!part) continue;
-        uint2v c2; c2[0] = clo; c2[1] = chi;
-        *reinterpret_cast<uint2v*>(part + (size_t)(pos & 127) * (D / 2) + cb * 8) = c2;
-        if ((cb & 3) == 0) *reinterpret_cast<uint32_t*>(part + (size_t)128 * (D / 2) + (size_t)(pos & 127) * nb + cb) = sb;
+        phi_block16_bf16(val, s, clo, chi);
     }
+    // the scale bytes of four neighbouring blocks of a row as one dword (rows beyond the page end take part and write nothing)
+    uint32_t sb = e4m3_byte_of(s);
+    sb |= (uint32_t)__shfl_down((int)sb, 1) << 8;
+    sb |= (uint32_t)__shfl_down((int)sb, 2) << 16;
+    unsigned char* part = const_cast<unsigned char*>(nvfp4_page_part(cache, page, num_pages, Hkv, h, D, which));
+    if (row >= rows_total || !part) return;
+    uint2v c2; c2[0] = clo; c2[1] = chi;
+    *reinterpret_cast<uint2v*>(part + (size_t)(pos & 127) * (D / 2) + cb * 8) = c2;
+    if ((cb & 3) == 0) *reinterpret_cast<uint32_t*>(part + (size_t)128 * (D / 2) + (size_t)(pos & 127) * nb + cb) = sb;
 }
 
 size_t nvfp4_page_bytes(int Hkv, int D) { return (size_t)Hkv * nvfp4_page_head_bytes(D); }
@@ -380,7 +345,8 @@ int launch_kv_page_write(const void* k, const void* v, int Hkv, int n, int D, in
 {
     if (Hkv > 65535 || (D != 64 && D != 128) || n < 1 || pos0 < 0) return -1;
     const int rows_total = ((pos0 + n + 127) & ~127) - pos0;
-    dim3 grid((rows_total + 63) / 64, Hkv, 2);
+    const int per = 256 / (D / 16);
+    dim3 grid((rows_total + per - 1) / per, Hkv, 2);
     if (D == 128) hipLaunchKernelGGL((kv_page_write_kernel<128>), grid, dim3(256), 0, st, (const uint16_t*)k, (const uint16_t*)v, n, pos0, Hkv,
                                      (unsigned char*)cache, num_pages, page_ids);
     else          hipLaunchKernelGGL((kv_page_write_kernel<64>), grid, dim3(256), 0, st, (const uint16_t*)k, (const uint16_t*)v, n, pos0, Hkv,
@@ -431,25 +397,11 @@ int launch_colmean(const void* x, int BH, int L, int D, double* scratch, float* 
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-template <bool QUANT, bool OUT_F16>
-static int launch_prep_t(const void* x, int BH, int L, int D, uint8_t* codes, uint8_t* scales,
-                         void* xf_pub, void* xr, void* xt, const float* sub, hipStream_t st)
+int launch_quantize(const void* x, int BH, int L, int D, uint8_t* codes, uint8_t* scales, void* xf, hipStream_t st)
 {
     const int Lp = round_up(L, kRowPad);
-    dim3 grid(Lp / 64, BH);
-    hipLaunchKernelGGL((prep_kernel<QUANT, OUT_F16>), grid, dim3(256), 0, st,
-                       (const uint16_t*)x, L, Lp, D, codes, scales, (uint16_t*)xf_pub,
-                       (uint16_t*)xr, (uint16_t*)xt, sub);
+    hipLaunchKernelGGL(quantize_kernel, dim3(Lp / 64, BH), dim3(256), 0, st, (const uint16_t*)x, L, Lp, D, codes, scales, (uint16_t*)xf);
     return hipGetLastError() == hipSuccess ? 0 : -1;
-}
-
-int launch_prep(const void* x, int BH, int L, int D, bool quant, bool out_f16,
-                uint8_t* codes, uint8_t* scales, void* xf_pub, void* xr, void* xt, hipStream_t st, const float* sub)
-{
-    if (quant) return out_f16 ? launch_prep_t<true, true>(x, BH, L, D, codes, scales, xf_pub, xr, xt, sub, st)
-                              : launch_prep_t<true, false>(x, BH, L, D, codes, scales, xf_pub, xr, xt, sub, st);
-    return out_f16 ? launch_prep_t<false, true>(x, BH, L, D, codes, scales, xf_pub, xr, xt, sub, st)
-                   : launch_prep_t<false, false>(x, BH, L, D, codes, scales, xf_pub, xr, xt, sub, st);
 }
 
 }  // namespace aq
