@@ -92,8 +92,8 @@ __device__ inline half8 dequant8(const RawKV<D>& r, half2v sc, int s) {
 //     Workgroup 0 also writes their number to ctl[2] and, for a (sequence, kv head) without keys, the result: O = 0, L = -inf.
 //   * the next nq: phi(Q), two (sequence, kv head)s each: [B*Hkv][128][D] fp16, rows R .. 15 zero (the kernel reads 16 rows)
 //   * the rest: the queue's counters and the tagged row maxima (ints [0, nz) from ctl on, except ctl[2]) are cleared
-// (One workgroup that listed everything and a launch of its own for phi(Q): 9.6 + 5.6 us of 124 for 32 sequences of 8 kv heads;
-// together now ANNO.)
+// (One workgroup that listed everything and a launch of its own for phi(Q) took 9.6 + 5.6 us for 32 sequences of 8 kv heads, all
+// of it together now 5.1 us.)
 template <int D>
 __global__ __launch_bounds__(256) void decode_prepare_kernel(const int* __restrict__ kv_lens, const int* __restrict__ page_table,
                                                              int B, int Hkv, int R, int CK, int NC,
@@ -543,50 +543,64 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(
     const float* __restrict__ part_o, const float* __restrict__ part_l, const float* __restrict__ part_m,
     uint16_t* __restrict__ O, float* __restrict__ lse, float c)
 {
-    const int bh = blockIdx.x, tid = threadIdx.x;
+    const int per = (R * D + 255) / 256;             // workgroups per (sequence, kv head): a thread has one element
+    const int bh = blockIdx.x / per, e = (blockIdx.x % per) * 256 + threadIdx.x;
     const int Lk = min(kv_lens[bh / Hkv], max_pages * 128);
     const int nch = (Lk + CK - 1) / CK;
-    if (nch < 2) return;
+    if (nch < 2 || e >= R * D) return;
     const size_t u0 = (size_t)bh * NC;
-    // (eight chunks per round, their loads issued together: one trip to memory per round instead of one per chunk)
-    for (int e = tid; e < R * D; e += 256) {
-        const int r = e / D;
-        float M = -INFINITY, v = 0.0f, l = 0.0f;
-        for (int i0 = 0; i0 < nch; i0 += 8) {
-            float pm[8], po[8], pl[8];
+    const int r = e / D;
+    float M = -INFINITY, v = 0.0f, l = 0.0f;
+    // (sixteen chunks per round, their loads issued together: one trip to memory per round instead of one per chunk)
+    for (int i0 = 0; i0 < nch; i0 += 16) {
+        float pm[16], po[16], pl[16];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const size_t u = u0 + min(i0 + k, nch - 1);
-                pm[k] = i0 + k < nch ? part_m[u * kDecRows + r] : -INFINITY;
-                po[k] = part_o[u * R * D + e];
-                pl[k] = part_l[u * kDecRows + r];
-            }
-            float Mn = M;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) Mn = fmaxf(Mn, pm[k]);
-            const float a = __builtin_amdgcn_exp2f((M - Mn) * c);      // first round: exp2(-inf) = 0 on sums that are 0
-            v *= a; l *= a; M = Mn;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const float w = __builtin_amdgcn_exp2f((pm[k] - M) * c);      // a chunk that does not exist: weight 0
-                v = fmaf(po[k], w, v);
-                l = fmaf(pl[k], w, l);
-            }
+        for (int k = 0; k < 16; ++k) {
+            const size_t u = u0 + min(i0 + k, nch - 1);
+            pm[k] = i0 + k < nch ? part_m[u * kDecRows + r] : -INFINITY;
+            po[k] = part_o[u * R * D + e];
+            pl[k] = part_l[u * kDecRows + r];
         }
-        O[(size_t)bh * R * D + e] = f32_to_bf16_rne(v / l);
-        if (e % D == 0) lse[(size_t)bh * R + r] = M * (c * 0.6931471805599453f) + logf(l);
+        float Mn = M;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) Mn = fmaxf(Mn, pm[k]);
+        const float a = __builtin_amdgcn_exp2f((M - Mn) * c);      // first round: exp2(-inf) = 0 on sums that are 0
+        v *= a; l *= a; M = Mn;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const float w = __builtin_amdgcn_exp2f((pm[k] - M) * c);      // a chunk that does not exist: weight 0
+            v = fmaf(po[k], w, v);
+            l = fmaf(pl[k], w, l);
+        }
     }
+    O[(size_t)bh * R * D + e] = f32_to_bf16_rne(v / l);
+    if (e % D == 0) lse[(size_t)bh * R + r] = M * (c * 0.6931471805599453f) + logf(l);
 }
 
 }  // namespace
 
-// Keys per chunk for R rows per (sequence, kv head): the chunk's scores [R][CK] fp32 fit the LDS set aside for them.
-int decode_chunk_keys(int R) { return max(256, min(1024, (kDecSFloats / R) / 128 * 128)); }
+// Keys per chunk for R rows per (sequence, kv head): the chunk's scores [R][CK] fp32 fit the LDS set aside for them.  A step that would
+// give most compute units nothing to do takes shorter chunks, down to one tile per wave: halved (`halvings`) while the chunks stay
+// within one per compute unit.  A workgroup needs 13 us for one tile per wave and 3 - 4 us for each further one, in a chain
+// that nothing overlaps, so more and shorter chunks are faster there (kernel at 8 kv heads, one sequence: 3000 keys 25.9 -> 16.2 us
+// with chunks of 256 instead of 1024, 8000 keys 26.5 -> 20.1 us); with all units busy they only cost (32 sequences of 4k - 16k
+// keys: 108 us, 146 us with chunks of 512).
+static int chunk_keys(int R, int halvings) {
+    int ck = max(256, min(1024, (kDecSFloats / R) / 128 * 128));
+    for (int i = 0; i < halvings; ++i) ck = max(256, ck / 2 / 128 * 128);
+    return ck;
+}
+int decode_halvings(int B, int Hkv, int R, int max_pages) {
+    auto units = [&](int h) { const long long ck = chunk_keys(R, h); return (long long)B * Hkv * (((long long)max_pages * 128 + ck - 1) / ck); };
+    int h = 0;
+    while (chunk_keys(R, h + 1) < chunk_keys(R, h) && units(h + 1) <= device_cu_count()) ++h;
+    return h;
+}
 int decode_max_rows() { return kDecRows; }
 
-size_t decode_ws_bytes(int B, int Hkv, int R, int max_pages, int D)
+size_t decode_ws_bytes(int B, int Hkv, int R, int max_pages, int D, int halvings)
 {
-    const size_t CK = decode_chunk_keys(R), NC = ((size_t)max_pages * 128 + CK - 1) / CK, units = (size_t)B * Hkv * NC;
+    const size_t CK = chunk_keys(R, halvings), NC = ((size_t)max_pages * 128 + CK - 1) / CK, units = (size_t)B * Hkv * NC;
     size_t n = 256;                                                   // ticket counter, error word, number of chunks
     n += units * kDecRows * 8;                                         // row maxima with their tags
     n += units * kDecRows * 4 * 2;                                     // l and m of the partial sums
@@ -596,11 +610,11 @@ size_t decode_ws_bytes(int B, int Hkv, int R, int max_pages, int D)
 }
 
 int launch_decode(const void* q, void* qh, const void* cache, int num_pages, const int* page_table, int max_pages, const int* kv_lens,
-                  int B, int Hq, int Hkv, int Lq, int D, bool causal, void* ws, int spin_limit, void* o, float* lse, hipStream_t st)
+                  int B, int Hq, int Hkv, int Lq, int D, bool causal, void* ws, int halvings, int spin_limit, void* o, float* lse, hipStream_t st)
 {
     const int R = (Hq / Hkv) * Lq;
     if (R < 1 || R > kDecRows || (D != 64 && D != 128)) return -1;
-    const int CK = decode_chunk_keys(R), NC = (max_pages * 128 + CK - 1) / CK;
+    const int CK = chunk_keys(R, halvings), NC = (max_pages * 128 + CK - 1) / CK;
     const size_t units = (size_t)B * Hkv * NC;
     if (units > 0x7FFFFFFFull) return -1;
     unsigned char* p = (unsigned char*)ws;
@@ -631,9 +645,9 @@ int launch_decode(const void* q, void* qh, const void* cache, int num_pages, con
 #undef AQ_DEC
     if (hipGetLastError() != hipSuccess) return -1;
     if (NC > 1) {
-        if (D == 128) hipLaunchKernelGGL((decode_merge_kernel<128>), dim3(B * Hkv), dim3(256), 0, st, kv_lens, Hkv, R, CK, NC, max_pages,
+        if (D == 128) hipLaunchKernelGGL((decode_merge_kernel<128>), dim3((unsigned)(B * Hkv * ((R * D + 255) / 256))), dim3(256), 0, st, kv_lens, Hkv, R, CK, NC, max_pages,
                                          part_o, part_l, part_m, (uint16_t*)o, lse, c);
-        else          hipLaunchKernelGGL((decode_merge_kernel<64>), dim3(B * Hkv), dim3(256), 0, st, kv_lens, Hkv, R, CK, NC, max_pages,
+        else          hipLaunchKernelGGL((decode_merge_kernel<64>), dim3((unsigned)(B * Hkv * ((R * D + 255) / 256))), dim3(256), 0, st, kv_lens, Hkv, R, CK, NC, max_pages,
                                          part_o, part_l, part_m, (uint16_t*)o, lse, c);
     }
     return hipGetLastError() == hipSuccess ? 0 : -1;

@@ -66,10 +66,10 @@ int launch_kv_page_write(const void* k, const void* v, int Hkv, int n, int D, in
 // phi(Q), [B*Hkv][128][D] fp16.  ws: decode_ws_bytes() bytes.  spin_limit bounds the polls of a chunk waiting for the row maxima
 // of the chunks before it (see decode.hip); if it runs out the int at ws + 4 is set and that result is wrong.
 int decode_max_rows();
-int decode_chunk_keys(int R);
-size_t decode_ws_bytes(int B, int Hkv, int R, int max_pages, int D);
+int decode_halvings(int B, int Hkv, int R, int max_pages);        // how often the chunks of keys are halved at best; any smaller number works
+size_t decode_ws_bytes(int B, int Hkv, int R, int max_pages, int D, int halvings);
 int launch_decode(const void* q, void* qh, const void* cache, int num_pages, const int* page_table, int max_pages, const int* kv_lens,
-                  int B, int Hq, int Hkv, int Lq, int D, bool causal, void* ws, int spin_limit, void* o, float* lse, hipStream_t st);
+                  int B, int Hq, int Hkv, int Lq, int D, bool causal, void* ws, int halvings, int spin_limit, void* o, float* lse, hipStream_t st);
 
 // The MX format's operand arrays of the scaled FP4 instruction, from which the backward recomputes the scores (launch_mx_group):
 // kops / ksc: a wave's 32 keys as the A operand of the dK/dV pass; krec: 64-key records, the A operand of the dQ pass.

@@ -209,3 +209,31 @@ def test_argument_errors_and_bad_page_ids():
     wr = lambda **kw: L_.attnqat_kv_cache_write(k.data_ptr(), v.data_ptr(), Hkv, 256, kw.get("d", d), 0, kw.get("pos0", 0),
                                                 cache2.data_ptr(), kw.get("np", 2), table.data_ptr(), None)
     assert wr(pos0=-1) == aq.EINVAL and wr(np=0) == aq.EINVAL and wr(d=96) == aq.ESHAPE
+
+
+@pytest.mark.parametrize("Hq,Hkv,Lq,d,lens", [(8, 2, 1, 128, (255, 256, 257, 3000)), (4, 4, 4, 64, (512, 1023, 1025, 1)), (4, 1, 1, 128, (4097,)), (6, 1, 1, 64, (2000, 2304))])
+def test_decode_chunks_of_any_length_agree(Hq, Hkv, Lq, d, lens):
+    """Short chunks spread a small step over the chip; a workspace without room for them gets longer ones.  The same P^F and the
+    same fp32 terms, added in another grouping."""
+    import paper_2603_00040_amd as aq
+    lens = [max(n, Lq) for n in lens]
+    B, pages = len(lens), [(max(n, Lq) + 127) // 128 for n in lens]
+    cache = torch.zeros(sum(pages) * aq.kv_cache_page_bytes_nvfp4(Hkv, d), dtype=torch.uint8, device="cuda")
+    table, at = torch.zeros((B, max(pages)), dtype=torch.int32, device="cuda"), 0
+    for b, n in enumerate(lens):
+        ids = torch.arange(at, at + pages[b], dtype=torch.int32, device="cuda")
+        at += pages[b]
+        table[b, :pages[b]] = ids
+        x = random_inputs(1, Hkv, Hkv, n, d, seed=n + b)
+        aq.attnqat_kv_cache_write(to_dev(x["k"]), to_dev(x["v"]), cache, ids, 0, sum(pages))
+    q = to_dev(random_inputs(B, Hq, Hkv, Lq, d, seed=1)["q"])
+    kl = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    need = aq.lib().attnqat_paged_workspace_bytes(B, Hq, Hkv, Lq, max(pages), d)
+    run = lambda nbytes: aq.attnqat_fwd_infer_paged(q, cache, sum(pages), table, kl, Hkv, True,  # noqa: E731
+                                                    workspace=torch.empty(nbytes, dtype=torch.uint8, device="cuda"))
+    o, lse = run(need)
+    o2, lse2 = run(need - 1)
+    # fp32 sums of the same terms (errors of 2^-24 times the sum of their magnitudes), one rounding to bf16 each
+    a, r = o.float(), o2.float()
+    assert bool(((a - r).abs() <= 2.0 ** -7 * r.abs() + 1e-5 * r.abs().max()).all())
+    assert float((lse - lse2).abs().max()) <= 2e-5 * float(lse2.abs().max())
