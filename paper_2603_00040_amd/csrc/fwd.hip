@@ -30,36 +30,6 @@ struct FwdSmem {
     half_t v[2][D * 64];      // V^T tile [d][key], likewise
 };
 
-// Work item of a four-wave workgroup when every sequence has its own number of keys (serving).  A unit is a (sequence, kv head):
-// its G query heads x nqt tiles read the same K and V^T and stay on one XCD.  Units are dealt to the XCDs row by row, the longest
-// sequences first and every other row backwards, so that each XCD gets its share of long ones; inside an XCD the second round of
-// its 32 compute units runs backwards too (see longest_first).  The order of the sequences comes from their lengths here, on the
-// device (up to 64 of them; beyond that the order they have).  The grid is rounded up to whole rows of units: false for an item
-// that does not exist.  (8 sequences of 2k - 16k keys, 512-position chunks: 884 us on paired 256-row workgroups, head after head -> 629 us.)
-__device__ inline bool varlen_item(int block, const int* __restrict__ kv_lens, int B, int Hq, int G, int nqt, int& bh, int& tile)
-{
-    const int x = block & 7, Hkv = Hq / G, per_unit = G * nqt, units = B * Hkv;
-    int s = block >> 3;
-    if ((s >> 5) == 1 && 64 <= (units >> 3) * per_unit) s = 95 - s;
-    const int row = s / per_unit, t = s % per_unit;
-    const int unit = row * 8 + ((row & 1) ? 7 - x : x);
-    if (unit >= units) return false;
-    int b = unit / Hkv;
-    if (B > 1 && B <= 64) {
-        const int lane = (int)(threadIdx.x & 63);
-        const int len = lane < B ? kv_lens[lane] : -1;
-        int rank = lane < B ? 0 : 64;
-        for (int j = 0; j < B; ++j) {
-            const int lj = __builtin_amdgcn_readlane(len, j);
-            rank += (lj > len || (lj == len && j < lane)) ? 1 : 0;
-        }
-        b = (int)__builtin_ctzll(__builtin_amdgcn_ballot_w64(rank == b));
-    }
-    bh = b * Hq + (unit % Hkv) * G + t % G;
-    tile = t / G;
-    return true;
-}
-
 // PQ, the format of P-tilde in the P V product: 0 NVFP4, 1 MX, 2 NVFP4 with the two-level row factor,
 // 3 bf16 with V left in bf16 as well (the mixed recipe "NVFP4 Q K^T, BF16 P V" of Sec. 2.5; the tile buffer of V^T then
 // holds bf16 bit patterns and the P V products are bf16 MFMAs; inference only).

@@ -131,3 +131,26 @@ def test_paged_argument_errors_and_bad_page_ids():
     g = guard.cpu()
     assert bool((g[:2 * page] == 0xAB).all()) and bool((g[3 * page:] == 0xAB).all())      # guards and page 0 untouched
     assert not bool((g[2 * page:3 * page] == 0xAB).all())                                   # page 1 was written
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,Lq,d,causal", [(5, 32, 8, 300, 64, True), (3, 12, 3, 1000, 128, False), (66, 4, 2, 129, 64, True)])
+def test_mx_sequences_together_equal_sequences_alone(B, Hq, Hkv, Lq, d, causal):
+    """With more workgroups than compute units the sequences are taken in order of their lengths (up to 64 of them)."""
+    import paper_2603_00040_amd as aq
+    g = torch.Generator().manual_seed(B)
+    lens = torch.randint(Lq, Lq + 1200, (B,), generator=g).tolist()
+    lens[B // 2] = lens[0]                                         # a tie
+    pages = [(n + 127) // 128 for n in lens]
+    cache = torch.zeros(sum(pages) * aq.kv_cache_page_bytes(Hkv, d), dtype=torch.uint8, device="cuda")
+    table, at = torch.zeros((B, max(pages)), dtype=torch.int32, device="cuda"), 0
+    for b, n in enumerate(lens):
+        table[b, :pages[b]] = torch.arange(at, at + pages[b], dtype=torch.int32, device="cuda")
+        at += pages[b]
+        x = random_inputs(1, Hkv, Hkv, n, d, seed=11 + b)
+        aq.attnqat_kv_cache_write_mx(to_dev(x["k"]), to_dev(x["v"]), cache, table[b, :pages[b]].contiguous(), sum(pages))
+    q = to_dev(random_inputs(B, Hq, Hkv, Lq, d, seed=7)["q"])
+    kl = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    o, lse = aq.attnqat_fwd_infer_mx_paged(q, cache, sum(pages), table, kl, Hkv, causal)
+    for b in sorted({0, 1, B // 2, B - 1}):
+        o1, l1 = aq.attnqat_fwd_infer_mx_paged(q[b:b + 1].contiguous(), cache, sum(pages), table[b:b + 1].contiguous(), kl[b:b + 1].contiguous(), Hkv, causal)
+        assert torch.equal(o[b:b + 1], o1) and torch.equal(lse[b:b + 1], l1), b
