@@ -103,7 +103,9 @@ def _ptr(t):
 
 
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    # (the handle itself: torch.cuda.current_stream() builds a Stream object around it on every call, a few microseconds of a step
+    #  whose kernels take twenty)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _dev_bf16(t, name):
@@ -120,9 +122,8 @@ def workspace_bytes(which: int, B: int, Hq: int, Hkv: int, L: int, d: int) -> in
 
 
 def _workspace(which, B, Hq, Hkv, L, d, workspace):
-    need = workspace_bytes(which, B, Hq, Hkv, L, d)
     if workspace is None:
-        workspace = torch.empty(max(need, 1), dtype=torch.uint8, device="cuda")
+        workspace = torch.empty(max(workspace_bytes(which, B, Hq, Hkv, L, d), 1), dtype=torch.uint8, device="cuda")
     return workspace, workspace.numel()
 
 
@@ -237,8 +238,8 @@ def attnqat_fwd_infer_paged(q, cache, num_pages, page_table, kv_lens, Hkv, causa
     else:
         o, lse = out
     max_pages = page_table.shape[1]
-    need = lib().attnqat_paged_workspace_bytes(B, Hq, Hkv, Lq, max_pages, d)
     if workspace is None:
+        need = lib().attnqat_paged_workspace_bytes(B, Hq, Hkv, Lq, max_pages, d)
         workspace = torch.empty(max(need, 1), dtype=torch.uint8, device="cuda")
     if spin_limit is not None:
         expired = ctypes.c_int(0)
