@@ -78,10 +78,17 @@ __device__ __forceinline__ void mx_v_tile(uint16_t (*tile)[D + 2], const MxGroup
 {
     constexpr int CH = D / 8;                       // 16-byte pieces per row
     const int l0 = t * 64, L = g.L, Lp = g.Lp;
+    const bool aligned = ((uintptr_t)g.v & 15) == 0;          // (V may lie at any address of a 16-bit value)
     for (int i = threadIdx.x; i < 64 * CH; i += 256) {
         const int row = i / CH, c = i % CH;
         uint4v a = {0u, 0u, 0u, 0u};
-        if (l0 + row < L) a = *reinterpret_cast<const uint4v*>(g.v + ((size_t)bh * L + l0 + row) * D + 8 * c);
+        if (l0 + row < L) {
+            const uint16_t* src = g.v + ((size_t)bh * L + l0 + row) * D + 8 * c;
+            if (aligned) a = *reinterpret_cast<const uint4v*>(src);
+            else
+#pragma unroll
+                for (int j = 0; j < 4; ++j) a[j] = (uint32_t)src[2 * j] | ((uint32_t)src[2 * j + 1] << 16);
+        }
         uint32_t* dst = reinterpret_cast<uint32_t*>(&tile[row][8 * c]);       // (rows are 4-byte aligned: D + 2 values)
 #pragma unroll
         for (int j = 0; j < 4; ++j) dst[j] = a[j];

@@ -277,3 +277,18 @@ def test_fp8pv_ragged_lengths_d128_gqa(L, causal):
 @pytest.mark.parametrize("causal", [False, True])
 def test_fp8pv_d64_heavy_tails(causal):
     _run_fp8pv(1, 3, 1, 333, 64, causal, seed=7, dist="t3", scale=0.5, tok_mod=50)
+
+
+@pytest.mark.parametrize("L,d", [(65, 64), (200, 128)])
+def test_v_at_any_address(L, d):
+    """V is read in 16-byte pieces where it lies on 16 bytes and value by value elsewhere: the results are the same."""
+    import paper_2603_00040_amd as aq
+    x = random_inputs(1, 2, 1, L, d, seed=L)
+    q, k, v, do = (to_dev(x[n]) for n in ("q", "k", "v", "do"))
+    odd = torch.empty(v.numel() + 1, dtype=v.dtype, device="cuda")[1:].view(v.shape)
+    odd.copy_(v)
+    assert odd.data_ptr() % 4 == 2
+    for f in (aq.attnqat_fwd_infer_mx, aq.attnqat_fwd_infer_mx_fp8pv, aq.attnqat_fwd_mx):
+        assert all(torch.equal(a, b) for a, b in zip(f(q, k, v, True), f(q, k, odd, True)))
+    _, lse, ohp = aq.attnqat_fwd_mx(q, k, v, True)
+    assert all(torch.equal(a, b) for a, b in zip(aq.attnqat_bwd_mx(q, k, v, do, lse, ohp, True), aq.attnqat_bwd_mx(q, k, odd, do, lse, ohp, True)))
