@@ -11,7 +11,9 @@ __host__ __device__ inline int bound_chunk_tiles(int tiles) { return (tiles + kB
 
 // The statistics that the backward needs of 64 rows of dO and O' (Alg. 3, first line): rowstat = {L log2(e), D / sqrt(d)} with
 // D = rowsum(dO o O') (padding rows hold {0, 0}), the largest |dO_i|^2 and |D_i| / sqrt(d) so far in n2 and dmax, and the zero-padded
-// copy of dO where one is asked for (dob).
+// copy of dO where one is asked for (dob).  D is added up eight elements at a time (pairs 0, 2, 1, 3 of them), then over the groups of
+// eight in a tree whose last level joins neighbours: which order the sum has is part of the result's bits, so the two groups of a
+// thread stay apart until the end.
 __device__ __forceinline__ void grad_tile(int bh, int l0, const uint16_t* __restrict__ dO, const void* __restrict__ o_acc, bool o_is_bf16,
                                           const float* __restrict__ lse, int L, int Lp, int D, float rs,
                                           float2* __restrict__ rowstat, uint16_t* __restrict__ dob, float& n2, float& dmax)
@@ -20,7 +22,7 @@ __device__ __forceinline__ void grad_tile(int bh, int l0, const uint16_t* __rest
     for (int blk = threadIdx.x; blk < 64 * nb; blk += 256) {
         const int row = blk / nb, cb = blk % nb, l = l0 + row;
         uint4v g[2] = {};
-        float dot = 0.0f, nrm = 0.0f;
+        float dot8[2] = {0.0f, 0.0f}, nrm = 0.0f;
         if (l < L) {
             const size_t off = ((size_t)bh * L + l) * D + cb * 16;
             g[0] = reinterpret_cast<const uint4v*>(dO + off)[0];
@@ -42,16 +44,22 @@ __device__ __forceinline__ void grad_tile(int bh, int l0, const uint16_t* __rest
                 }
             }
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
+            for (int t = 0; t < 2; ++t) {
+                float lo[4], hi[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const float lo = __uint_as_float(g[t][i] << 16), hi = __uint_as_float(g[t][i] & 0xFFFF0000u);
-                    dot += lo * o[8 * t + 2 * i] + hi * o[8 * t + 2 * i + 1];
-                    nrm = fmaf(lo, lo, fmaf(hi, hi, nrm));
+                    lo[i] = __uint_as_float(g[t][i] << 16); hi[i] = __uint_as_float(g[t][i] & 0xFFFF0000u);
+                    nrm = fmaf(lo[i], lo[i], fmaf(hi[i], hi[i], nrm));
                 }
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    dot8[t] += lo[i] * o[8 * t + 2 * i] + hi[i] * o[8 * t + 2 * i + 1];
+                    dot8[t] += lo[2 + i] * o[8 * t + 4 + 2 * i] + hi[2 + i] * o[8 * t + 5 + 2 * i];
+                }
+            }
         }
-        for (int w = nb / 2; w >= 1; w >>= 1) { dot += __shfl_xor(dot, w); nrm += __shfl_xor(nrm, w); }
-        dot *= rs;
+        for (int w = nb / 2; w >= 1; w >>= 1) { dot8[0] += __shfl_xor(dot8[0], w); dot8[1] += __shfl_xor(dot8[1], w); nrm += __shfl_xor(nrm, w); }
+        const float dot = (dot8[0] + dot8[1]) * rs;
         if (cb == 0) rowstat[(size_t)bh * Lp + l] = make_float2(l < L ? lse[(size_t)bh * L + l] * 1.4426950408889634f : 0.0f, dot);
         n2 = fmaxf(n2, nrm);
         dmax = fmaxf(dmax, fabsf(dot));
