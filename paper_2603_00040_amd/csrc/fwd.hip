@@ -260,7 +260,13 @@ __device__ __forceinline__ void fwd_body(
     __syncthreads();
     if (has_rows) scores(0);
     if (late) __builtin_amdgcn_s_barrier();              // one phase behind from here on
-    if constexpr (!PHASES) __builtin_amdgcn_s_barrier(); // everyone is past the scores of tile 0: K(2) may take its buffer
+    if constexpr (!PHASES) {
+        // everyone is past the scores of tile 0: K(2) may take its buffer.  The barrier alone orders nothing: up to six LDS reads of
+        // the products behind it were still on their way, and another wave's copy of K(2) could have overtaken them.
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0);
+        __builtin_amdgcn_s_barrier();
+    }
 
     // Two phases per key tile, separated by barriers; waves 0-3 are in the vector phase while waves
     // 4-7 are in the matrix phase and vice versa, so every SIMD holds one wave of each kind:

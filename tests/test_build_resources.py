@@ -122,3 +122,36 @@ def test_mx_forward_kernels_do_not_spill():
     _check(k, r"fwd_mx_kernelILi(64|128)ELb[01]ELb[01]ELi[012]E", 16)
     # fwd_mx_decode_kernel<D, CAUSAL, NP = 1>: two workgroups per CU
     _check(k, r"fwd_mx_decode_kernelILi(64|128)ELb[01]ELi1E", 4)
+
+
+def test_no_lds_read_is_in_flight_at_a_barrier_of_the_forward():
+    """The forward's barriers are bare ones (no fence): behind a barrier another wave copies the next tile over the one that was just
+    read, so every LDS read has to have arrived before it (listing read from top to bottom, reads minus what the waits leave).  In
+    the four-wave kernels the second barrier is the one behind the scores of tile 0: all of their products stand in front of it."""
+    with tempfile.TemporaryDirectory() as tmp:
+        out = os.path.join(tmp, "x.s")
+        r = subprocess.run(["hipcc", *B.FLAGS, "-S", "--cuda-device-only", os.path.join(B.CSRC, "fwd.hip"), "-o", out], capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr[-2000:]
+        text = open(out).read().splitlines()
+    seen, cur = {}, None
+    for line in (l.strip() for l in text):
+        m = re.match(r"^_ZN2aq\d+(fwd_(?:narrow_)?kernel)ILi(64|128)E\S*?(?:ELi|ELb[01]ELi)([0-3])ELb[01]E\S*:", line)
+        if m:
+            cur, reads, products = line, 0, 0
+            seen[cur] = (m.group(1), int(m.group(2)), int(m.group(3)), [])
+        elif line.startswith(".Lfunc_end"):
+            cur = None
+        elif cur and line.startswith("ds_read"):
+            reads += 1
+        elif cur and line.startswith("v_mfma"):
+            products += 1
+        elif cur and line.startswith("s_waitcnt") and "lgkmcnt" in line:
+            reads = min(reads, int(re.search(r"lgkmcnt\((\d+)\)", line).group(1)))
+        elif cur and line.startswith("s_barrier"):
+            seen[cur][3].append((reads, products))
+            products = 0
+    assert len([k for k in seen if "narrow" in k]) == 32 and len(seen) > 64
+    for name, (kind, d, pq, barriers) in seen.items():
+        assert barriers and all(b[0] == 0 for b in barriers), (name, barriers)
+        if kind == "fwd_narrow_kernel":
+            assert barriers[1][1] == (2 * d // 64 if pq == 1 else 2 * d // 16), (name, barriers)      # (MX: the FP4 instruction)
