@@ -707,6 +707,8 @@ int attnqat_debug_fwd_p_mx(const void* q, const void* k, const void* v,
                       workspace, workspace_bytes, stream);
 }
 
+static bool overlap(const void* a, size_t na, const void* b, size_t nb) { return (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na; }
+
 // The six arrays of an already quantized Q, K, V (attnqat_quantize's layout); null = quantize q, k, v here.
 struct PackedQKV { const uint8_t *qc, *qs, *kc, *ks, *vc, *vs; };
 
@@ -735,8 +737,10 @@ static int bwd_common(const void* q, const void* k, const void* v, const void* d
     hipStream_t st = (hipStream_t)stream;
     prof_begin(st);
     // Q^F, K^F, V^F again (bit-identical to the forward's), D, the bounds of |dS|, and dO: the attention passes read it as it is
-    // where its rows need no padding (and lie as the 16-byte copies to LDS want them), otherwise from a zero-padded copy
-    const bool pad_do = L % kRowPad != 0 || ((uintptr_t)d_o & 15) != 0;
+    // where its rows need no padding (and lie as the 16-byte copies to LDS want them) and no result is written over it, otherwise
+    // from a zero-padded copy
+    const size_t nq = (size_t)B * Hq * L * d * 2, nkv = (size_t)B * Hkv * L * d * 2;
+    const bool pad_do = L % kRowPad != 0 || ((uintptr_t)d_o & 15) != 0 || overlap(d_o, nq, dq, nq) || overlap(d_o, nq, dk, nkv) || overlap(d_o, nq, dv, nkv);
     const void* dob = pad_do ? w.dob : d_o;
     const GradArgs grad{(const uint16_t*)d_o, o_acc, o_is_bf16, lse, 1.0f / sqrtf((float)d), (float2*)w.rowstat, w.bounds, pad_do ? (uint16_t*)w.dob : nullptr};
     MxScoreOps mxo{w.qops, w.qsc, w.kops, w.ksc, w.krec};

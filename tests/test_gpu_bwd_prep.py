@@ -1,5 +1,5 @@
 """dO is read by the backward's attention passes as it is where its rows need no padding and its address suits the 16-byte copies
-to LDS, and from a copy otherwise: the results do not depend on which."""
+to LDS and no result is written over it, and from a copy otherwise: the results do not depend on which."""
 import numpy as np
 import pytest
 import torch
@@ -21,6 +21,31 @@ def test_address_of_do_does_not_matter(B, Hq, Hkv, L, d, causal):
         _, lse, ohp = fwd(q, k, v, causal)
         a, b = bwd(q, k, v, do, lse, ohp, causal), bwd(q, k, v, odd, lse, ohp, causal)
         assert all(torch.equal(s, t) for s, t in zip(a, b))
+
+
+@pytest.mark.parametrize("Hq,Hkv,L,d,causal", [(2, 2, 256, 64, False), (4, 2, 257, 128, True), (4, 4, 256, 128, True), (8, 8, 4096, 64, True)])
+@pytest.mark.parametrize("mx", [False, True])
+@pytest.mark.parametrize("waves", [0, 4, 8])
+def test_results_written_over_do(Hq, Hkv, L, d, causal, mx, waves):
+    """dQ (and with as many kv heads dK, dV) has the shape and type of dO and may take its place, whole or in part."""
+    import paper_2603_00040_amd as aq
+    x = random_inputs(1, Hq, Hkv, L, d, seed=L)
+    q, k, v, do = (to_dev(x[n]) for n in ("q", "k", "v", "do"))
+    fwd, bwd = (aq.attnqat_fwd_mx, aq.attnqat_bwd_mx) if mx else (aq.attnqat_fwd, aq.attnqat_bwd)
+    _, lse, ohp = fwd(q, k, v, causal)
+    aq.debug_bwd_waves(waves)
+    try:
+        want = bwd(q, k, v, do, lse, ohp, causal)
+        for which in range(3 if Hq == Hkv else 1):
+            for shift in (0, 8 * d):                    # the result in dO's place, or eight rows behind it
+                room = torch.empty(do.numel() + shift, dtype=do.dtype, device="cuda")
+                buf, res = room[:do.numel()].view(do.shape).copy_(do), room[shift:].view(do.shape)
+                out = [torch.empty_like(t) for t in (q, k, v)]
+                out[which] = res
+                got = bwd(q, k, v, buf, lse, ohp, causal, out=tuple(out))
+                assert all(torch.equal(a, b) for a, b in zip(got, want)), (which, shift)
+    finally:
+        aq.debug_bwd_waves(0)
 
 
 def _sum_in_order(x):
