@@ -162,8 +162,8 @@ BwdWs carve_bwd(void* ws, int B, int Hq, int Hkv, int L, int d, bool mx = false)
     // problem runs unsplit.  The size asked for leaves them out below kSmallBwdWs, where the sizes have always been those of the
     // arrays above and the sums would be several times as much.
     w.bytes_min = c.off;
-    const size_t part = max(bwd_plan(B * Hq, B * Hkv, L, d, false).part_bytes, bwd_plan(B * Hq, B * Hkv, L, d, true).part_bytes);
-    w.part = part ? (float*)c.take(part) : nullptr;
+    const size_t part = max(bwd_plan(B * Hq, B * Hkv, L, d, false, kChipCus).part_bytes, bwd_plan(B * Hq, B * Hkv, L, d, true, kChipCus).part_bytes);
+    w.part = (float*)c.take(part);
     w.bytes_split = c.off;
     w.bytes = w.bytes_min < kSmallBwdWs ? w.bytes_min : w.bytes_split;
     return w;
@@ -459,7 +459,7 @@ namespace {
 // Few rows per (sequence, kv head): the decode kernel reads the pages itself (dec != null); otherwise the pages are unpacked
 // into the K / V^T copies of the general forward.
 struct PagedWs { void *qh, *kh, *vt, *dec; size_t bytes; int Lkp, halvings; };
-PagedWs carve_paged(void* ws, size_t given, int B, int Hq, int Hkv, int Lq, int max_pages, int d)
+PagedWs carve_paged(void* ws, size_t given, int cus, int B, int Hq, int Hkv, int Lq, int max_pages, int d)
 {
     Carver c{(unsigned char*)ws, 0};
     PagedWs w{};
@@ -467,7 +467,7 @@ PagedWs carve_paged(void* ws, size_t given, int B, int Hq, int Hkv, int Lq, int 
     if (R <= decode_max_rows()) {
         w.qh = c.take((size_t)B * Hkv * kRowPad * d * 2);
         // (shorter chunks need more room: a workspace that lacks it gets longer ones)
-        w.halvings = decode_halvings(B, Hkv, R, max_pages);
+        w.halvings = decode_halvings(B, Hkv, R, max_pages, cus);
         while (w.halvings > 0 && c.off + align_up(decode_ws_bytes(B, Hkv, R, max_pages, d, w.halvings)) > given) --w.halvings;
         w.dec = c.take(decode_ws_bytes(B, Hkv, R, max_pages, d, w.halvings));
     } else {
@@ -491,7 +491,7 @@ int paged_common(const void* q, int B, int Hq, int Hkv, int Lq, int d, int causa
     int rc = check_dims(B, Hq, Hkv, Lq, d, dtype);
     if (rc) return rc;
     if (max_pages > (1 << 13) || (long long)B * Hkv > 65535) return ATTNQAT_ESHAPE;          // 2^20 keys per sequence
-    PagedWs w = carve_paged(workspace, workspace_bytes, B, Hq, Hkv, Lq, max_pages, d);
+    PagedWs w = carve_paged(workspace, workspace_bytes, device_cu_count(), B, Hq, Hkv, Lq, max_pages, d);
     if (!workspace || workspace_bytes < w.bytes) return ATTNQAT_EWORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     prof_begin(st);
@@ -520,7 +520,7 @@ int paged_common(const void* q, int B, int Hq, int Hkv, int Lq, int d, int causa
 size_t attnqat_paged_workspace_bytes(int B, int Hq, int Hkv, int Lq, int max_pages, int d)
 {
     if (check_dims(B, Hq, Hkv, Lq, d, ATTNQAT_BF16) || max_pages < 1 || max_pages > (1 << 13)) return 0;
-    return carve_paged(nullptr, SIZE_MAX, B, Hq, Hkv, Lq, max_pages, d).bytes;
+    return carve_paged(nullptr, SIZE_MAX, kChipCus, B, Hq, Hkv, Lq, max_pages, d).bytes;
 }
 
 int attnqat_fwd_infer_paged(const void* q, int B, int Hq, int Hkv, int Lq, int d, int causal, int dtype,
@@ -769,9 +769,9 @@ static int bwd_common(const void* q, const void* k, const void* v, const void* d
         if (launch_prep_group(g, st)) return ATTNQAT_ELAUNCH;
     }
     prof_mark("prep_qkvdo", st);
-    BwdPlan plan = bwd_plan(B * Hq, B * Hkv, L, d, causal != 0);
+    BwdPlan plan = bwd_plan(B * Hq, B * Hkv, L, d, causal != 0, device_cu_count());
     if (plan.joint && p_quant != 0) {
-        if (workspace_bytes < w.bytes_split && plan.splits > 1) { plan.splits = 1; plan.iters = (L + 31) / 32 * (Hq / Hkv); }
+        if (plan.splits > 1 && workspace_bytes < max(w.bytes_split, w.bytes_min + plan.part_bytes)) { plan.splits = 1; plan.iters = (L + 31) / 32 * (Hq / Hkv); }
         if (launch_bwd_joint(w.qb, w.kb, w.vb, dob, w.rowstat, w.bounds, B, Hq, Hkv, L, d, causal != 0, dq, dk, dv, p_quant, plan, w.part,
                              dkdv_counts_of(st), st, p_dump, dump_row0, mx ? &mxo : nullptr))
             return ATTNQAT_ELAUNCH;

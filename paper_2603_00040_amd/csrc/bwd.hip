@@ -1090,12 +1090,12 @@ __global__ __launch_bounds__(256) void dkdv_reduce_kernel(const float* __restric
 //   * a piece is not much shorter than the average dQ tile, which it would only have to wait for,
 //   * the pieces (and, if there are few, the dQ tiles) fit the 2 workgroups per compute unit at once: a second round of
 //     pieces costs more than it evens out (12 heads, L = 1560: 312 pieces 83 us, 468 pieces 107 us).
-BwdPlan bwd_plan(int BHq, int BHkv, int L, int D, bool causal)
+BwdPlan bwd_plan(int BHq, int BHkv, int L, int D, bool causal, int cus_)
 {
     BwdPlan p{false, 1, 0, 0, false};
     if (__atomic_load_n(&g_bwd_waves, __ATOMIC_RELAXED) != 0) return p;
     const int Lp = round_up(L, kRowPad), nt = Lp / 128, G = BHq / BHkv, nq32 = (L + 31) / 32;
-    const long long cus = device_cu_count(), n8q = (long long)BHq * ((Lp + 255) / 256), n8kv = (long long)BHkv * ((Lp + 255) / 256);
+    const long long cus = cus_, n8q = (long long)BHq * ((Lp + 255) / 256), n8kv = (long long)BHkv * ((Lp + 255) / 256);
     auto fill = [&](long long n) { return (double)n / (double)((n + cus - 1) / cus * cus); };
     if (causal ? Lp >= 32768 && n8kv >= 2 * cus : n8kv >= 2 * cus && fill(n8q) + fill(n8kv) >= 2 * 0.97) return p;
     p.joint = true;

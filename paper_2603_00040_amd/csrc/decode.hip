@@ -590,10 +590,10 @@ static int chunk_keys(int R, int halvings) {
     for (int i = 0; i < halvings; ++i) ck = max(256, ck / 2 / 128 * 128);
     return ck;
 }
-int decode_halvings(int B, int Hkv, int R, int max_pages) {
+int decode_halvings(int B, int Hkv, int R, int max_pages, int cus) {
     auto units = [&](int h) { const long long ck = chunk_keys(R, h); return (long long)B * Hkv * (((long long)max_pages * 128 + ck - 1) / ck); };
     int h = 0;
-    while (chunk_keys(R, h + 1) < chunk_keys(R, h) && units(h + 1) <= device_cu_count()) ++h;
+    while (chunk_keys(R, h + 1) < chunk_keys(R, h) && units(h + 1) <= cus) ++h;
     return h;
 }
 int decode_max_rows() { return kDecRows; }

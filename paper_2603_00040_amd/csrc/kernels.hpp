@@ -5,6 +5,10 @@
 
 namespace aq {
 
+// Compute units of a whole MI355X: what the size queries plan for.  They ask no device (they have to work on a machine without one,
+// and a process that asked for a size may still fork); a call plans for the device it runs on and does with the room it is given.
+constexpr int kChipCus = 256;
+
 // phi of x [BH, L, D] bf16 in the public layout (codes, scales, bf16 dequantized copy xf; any may be null).
 int launch_quantize(const void* x, int BH, int L, int D, uint8_t* codes, uint8_t* scales, void* xf, hipStream_t st);
 
@@ -66,7 +70,7 @@ int launch_kv_page_write(const void* k, const void* v, int Hkv, int n, int D, in
 // phi(Q), [B*Hkv][128][D] fp16.  ws: decode_ws_bytes() bytes.  spin_limit bounds the polls of a chunk waiting for the row maxima
 // of the chunks before it (see decode.hip); if it runs out the int at ws + 4 is set and that result is wrong.
 int decode_max_rows();
-int decode_halvings(int B, int Hkv, int R, int max_pages);        // how often the chunks of keys are halved at best; any smaller number works
+int decode_halvings(int B, int Hkv, int R, int max_pages, int cus);        // how often the chunks of keys are halved at best; any smaller number works
 size_t decode_ws_bytes(int B, int Hkv, int R, int max_pages, int D, int halvings);
 int launch_decode(const void* q, void* qh, const void* cache, int num_pages, const int* page_table, int max_pages, const int* kv_lens,
                   int B, int Hq, int Hkv, int Lq, int D, bool causal, void* ws, int halvings, int spin_limit, void* o, float* lse, hipStream_t st);
@@ -93,7 +97,7 @@ int launch_bwd_dkdv(const void* qb, const void* kb, const void* vb, const void* 
 // plan.splits workgroups of plan.iters query tiles whose sums meet in `part` (plan.part_bytes bytes).  launch_bwd_dq and
 // launch_bwd_dkdv run what is not joint.
 struct BwdPlan { bool joint; int splits, iters; size_t part_bytes; bool dq_first; };
-BwdPlan bwd_plan(int BHq, int BHkv, int L, int D, bool causal);
+BwdPlan bwd_plan(int BHq, int BHkv, int L, int D, bool causal, int cus);
 int launch_bwd_joint(const void* qb, const void* kb, const void* vb, const void* dob, const float* rowstat, const float* bound_part,
                      int B, int Hq, int Hkv, int L, int D, bool causal, void* dq, void* dk, void* dv, int p_quant /* 1, 2 or 3 */,
                      const BwdPlan& plan, float* part, unsigned long long* tile_counts, hipStream_t st, float* p_dump, int dump_row0,

@@ -2,6 +2,10 @@
 import ctypes
 import os
 import re
+import subprocess
+import sys
+
+import pytest
 
 import paper_2603_00040_amd as aq
 
@@ -55,3 +59,23 @@ def test_argument_validation_happens_before_any_gpu_call():
     assert L.attnqat_profile_enable(None, 0) == aq.OK and L.attnqat_debug_dkdv_tile_counts(None, None) == aq.OK
     assert L.attnqat_profile_read(None, 0, None, None) == aq.EINVAL
 
+
+
+@pytest.mark.gpu
+def test_size_queries_do_not_open_the_gpu():
+    """A process that has only asked for sizes has not started the GPU runtime (it may still fork)."""
+    code = """
+import ctypes, os, sys
+L = ctypes.CDLL(sys.argv[1])
+L.attnqat_workspace_bytes.restype = L.attnqat_paged_workspace_bytes.restype = ctypes.c_size_t
+opened = lambda: any(os.readlink('/proc/self/fd/' + f) == '/dev/kfd' for f in os.listdir('/proc/self/fd') if os.path.islink('/proc/self/fd/' + f))
+for which in range(9):
+    assert L.attnqat_workspace_bytes(which, 1, 4, 2, 3000, 128) > 0
+for lq in (1, 300):
+    assert L.attnqat_paged_workspace_bytes(2, 8, 2, lq, 30, 128) > 0
+assert not opened()
+n = ctypes.c_int(0)
+assert L.hipGetDeviceCount(ctypes.byref(n)) == 0 and n.value > 0 and opened()
+"""
+    r = subprocess.run([sys.executable, "-c", code, aq.LIB_PATH], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, r.stderr
