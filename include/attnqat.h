@@ -178,8 +178,9 @@ int attnqat_bwd_ablation(const void* q, const void* k, const void* v, const void
                          void* workspace, size_t workspace_bytes, void* stream);
 
 /* Bytes of workspace the call named by `which` (ATTNQAT_WS_*) needs; 0 for bad arguments.  For the backward this includes room
- * for the partial sums of problems that do not fill the chip (above 2 MiB); a smaller workspace that lacks only those is
- * accepted, and the sums are then formed in one piece (slower; equal up to the rounding of the fp32 sums). */
+ * for the partial sums of problems that do not fill the chip (of those whose other arrays take 2 MiB and more; smaller ones run
+ * without).  A workspace that lacks only that room is accepted: the sums are then formed in one piece (slower; equal up to the
+ * rounding of the fp32 sums).  Any size from the one asked for on gives the same bits. */
 size_t attnqat_workspace_bytes(int which, int B, int Hq, int Hkv, int L, int d);
 
 /* The key tile size B_k of Alg. 1/2 that the forward kernels implement. */

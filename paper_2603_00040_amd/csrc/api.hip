@@ -139,7 +139,7 @@ FwdWs carve_fwd(void* ws, int B, int Hq, int Hkv, int L, int d, bool mx = false)
 // representable in fp16), the per-row {L, D} pairs and the partial maxima that bound |dS|.
 struct BwdWs { void *qb, *kb, *vb, *dob; float* rowstat; float* bounds; double* kpart; float* kmean; size_t bytes;
                void *qops, *qsc, *kops, *ksc, *krec;
-               size_t bytes_min, bytes_split; float* part; };
+               size_t bytes_min; bool may_split; float* part; };
 constexpr size_t kSmallBwdWs = (size_t)2 << 20;
 BwdWs carve_bwd(void* ws, int B, int Hq, int Hkv, int L, int d, bool mx = false)
 {
@@ -159,13 +159,14 @@ BwdWs carve_bwd(void* ws, int B, int Hq, int Hkv, int L, int d, bool mx = false)
     w.ksc  = mx ? c.take(mx_qsc_bytes(B * Hkv, L)) : nullptr;
     w.krec = mx ? c.take(mx_ktrain_bytes(B * Hkv, L, d)) : nullptr;
     // Partial sums of dK and dV (the mask is not known here) lie behind everything else; without room for them (bytes_min) a
-    // problem runs unsplit.  The size asked for leaves them out below kSmallBwdWs, where the sizes have always been those of the
-    // arrays above and the sums would be several times as much.
+    // problem runs unsplit.  Below kSmallBwdWs, where they would be several times the arrays above, the size asked for leaves them
+    // out, and such a problem runs unsplit in a larger workspace too: the bits of dK and dV follow from the shape, not from the room
+    // that a caller happens to give (2 heads, L = 256, d = 64: 2 of 30 us).
     w.bytes_min = c.off;
-    const size_t part = max(bwd_plan(B * Hq, B * Hkv, L, d, false, kChipCus).part_bytes, bwd_plan(B * Hq, B * Hkv, L, d, true, kChipCus).part_bytes);
+    w.may_split = w.bytes_min >= kSmallBwdWs;
+    const size_t part = !w.may_split ? 0 : max(bwd_plan(B * Hq, B * Hkv, L, d, false, kChipCus).part_bytes, bwd_plan(B * Hq, B * Hkv, L, d, true, kChipCus).part_bytes);
     w.part = (float*)c.take(part);
-    w.bytes_split = c.off;
-    w.bytes = w.bytes_min < kSmallBwdWs ? w.bytes_min : w.bytes_split;
+    w.bytes = c.off;
     return w;
 }
 
@@ -771,7 +772,9 @@ static int bwd_common(const void* q, const void* k, const void* v, const void* d
     prof_mark("prep_qkvdo", st);
     BwdPlan plan = bwd_plan(B * Hq, B * Hkv, L, d, causal != 0, device_cu_count());
     if (plan.joint && p_quant != 0) {
-        if (plan.splits > 1 && workspace_bytes < max(w.bytes_split, w.bytes_min + plan.part_bytes)) { plan.splits = 1; plan.iters = (L + 31) / 32 * (Hq / Hkv); }
+        if (plan.splits > 1 && (!w.may_split || workspace_bytes < max(w.bytes, w.bytes_min + plan.part_bytes))) {
+            plan.splits = 1; plan.iters = (L + 31) / 32 * (Hq / Hkv); plan.dq_first = false;
+        }
         if (launch_bwd_joint(w.qb, w.kb, w.vb, dob, w.rowstat, w.bounds, B, Hq, Hkv, L, d, causal != 0, dq, dk, dv, p_quant, plan, w.part,
                              dkdv_counts_of(st), st, p_dump, dump_row0, mx ? &mxo : nullptr))
             return ATTNQAT_ELAUNCH;

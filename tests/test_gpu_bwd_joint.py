@@ -20,7 +20,7 @@ def test_joint_equals_separate_passes(B, Hq, Hkv, L, d, causal, mx):
     fwd, bwd, which = (aq.attnqat_fwd_mx, aq.attnqat_bwd_mx, aq.WS_BWD_MX) if mx else (aq.attnqat_fwd, aq.attnqat_bwd, aq.WS_BWD)
     _, lse, ohp = fwd(q, k, v, causal)
     size = aq.workspace_bytes(which, B, Hq, Hkv, L, d)
-    large = torch.empty(size + (256 << 20), dtype=torch.uint8, device="cuda")      # room for partial sums in small problems too
+    large = torch.empty(size + (256 << 20), dtype=torch.uint8, device="cuda")
     dq, dk, dv = bwd(q, k, v, do, lse, ohp, causal, workspace=large)
     again = bwd(q, k, v, do, lse, ohp, causal, workspace=large)
     assert all(torch.equal(a, b) for a, b in zip((dq, dk, dv), again))
@@ -44,3 +44,19 @@ def test_joint_equals_separate_passes(B, Hq, Hkv, L, d, causal, mx):
                         dtype=torch.uint8, device="cuda")
     got = bwd(q, k, v, do, lse, ohp, causal, workspace=small)
     assert all(torch.equal(a, b) for a, b in zip(got, (rq, rk, rv)))
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,L,d,causal", [(1, 2, 2, 256, 64, False), (1, 4, 4, 384, 64, False), (1, 2, 1, 512, 64, True), (1, 1, 1, 600, 128, False),
+                                                 (1, 4, 2, 1100, 128, True)])
+def test_bits_do_not_depend_on_spare_room(B, Hq, Hkv, L, d, causal):
+    """Whether a key tile's query tiles are shared follows from the shape: every workspace from the size asked for on gives the same bits
+    (the first four ask for no partial sums, the last one does)."""
+    import paper_2603_00040_amd as aq
+    x = random_inputs(B, Hq, Hkv, L, d, seed=L)
+    q, k, v, do = (to_dev(x[n]) for n in ("q", "k", "v", "do"))
+    lse, ohp = torch.full((B, Hq, L), float(torch.tensor(L).log()), device="cuda"), torch.zeros((B, Hq, L, d), device="cuda")
+    size = aq.workspace_bytes(aq.WS_BWD, B, Hq, Hkv, L, d)
+    run = lambda n: aq.attnqat_bwd(q, k, v, do, lse, ohp, causal, workspace=torch.empty(n, dtype=torch.uint8, device="cuda"))  # noqa: E731
+    want = run(size)
+    for spare in (256, 64 << 20):
+        assert all(torch.equal(a, b) for a, b in zip(run(size + spare), want))
