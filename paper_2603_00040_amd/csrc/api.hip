@@ -137,7 +137,7 @@ FwdWs carve_fwd(void* ws, int B, int Hq, int Hkv, int L, int d, bool mx = false)
 
 // Workspace of the backward: row-major copies (Q^F, K^F fp16; V^F and dO bf16: dO is not exactly
 // representable in fp16), the per-row {L, D} pairs and the partial maxima that bound |dS|.
-struct BwdWs { void *qb, *kb, *vb, *dob; float* rowstat; float* bounds; double* kpart; float* kmean; size_t bytes;
+struct BwdWs { void *qb, *kb, *vb, *dob; float* rowstat; float* bounds; double* kpart; float* kmean;
                void *qops, *qsc, *kops, *ksc, *krec;
                size_t bytes_min; bool may_split; float* part; };
 constexpr size_t kSmallBwdWs = (size_t)2 << 20;
@@ -158,16 +158,24 @@ BwdWs carve_bwd(void* ws, int B, int Hq, int Hkv, int L, int d, bool mx = false)
     w.kops = mx ? c.take(mx_qops_bytes(B * Hkv, L, d)) : nullptr;
     w.ksc  = mx ? c.take(mx_qsc_bytes(B * Hkv, L)) : nullptr;
     w.krec = mx ? c.take(mx_ktrain_bytes(B * Hkv, L, d)) : nullptr;
-    // Partial sums of dK and dV (the mask is not known here) lie behind everything else; without room for them (bytes_min) a
+    // Partial sums of dK and dV lie behind everything else; without room for them (bytes_min) a
     // problem runs unsplit.  Below kSmallBwdWs, where they would be several times the arrays above, the size asked for leaves them
     // out, and such a problem runs unsplit in a larger workspace too: the bits of dK and dV follow from the shape, not from the room
     // that a caller happens to give (2 heads, L = 256, d = 64: 2 of 30 us).
     w.bytes_min = c.off;
     w.may_split = w.bytes_min >= kSmallBwdWs;
-    const size_t part = !w.may_split ? 0 : max(bwd_plan(B * Hq, B * Hkv, L, d, false, kChipCus).part_bytes, bwd_plan(B * Hq, B * Hkv, L, d, true, kChipCus).part_bytes);
-    w.part = (float*)c.take(part);
-    w.bytes = c.off;
+    w.part = (float*)(w.may_split ? c.take(0) : nullptr);
     return w;
+}
+// The size asked for: with room for the partial sums of either mask.
+size_t bwd_ws_bytes(int B, int Hq, int Hkv, int L, int d, bool mx = false)
+{
+    const BwdWs w = carve_bwd(nullptr, B, Hq, Hkv, L, d, mx);
+    Carver c{nullptr, w.bytes_min};
+    if (!w.may_split) return w.bytes_min;
+    const size_t part = max(bwd_plan(B * Hq, B * Hkv, L, d, false, kChipCus).part_bytes, bwd_plan(B * Hq, B * Hkv, L, d, true, kChipCus).part_bytes);
+    c.take(part);
+    return c.off;
 }
 
 // Workspace of the MX forward: Q operand codes and scale dwords, and the 64-key kv records.
@@ -267,7 +275,7 @@ size_t attnqat_workspace_bytes(int which, int B, int Hq, int Hkv, int L, int d)
     switch (which) {
     case ATTNQAT_WS_FWD:
     case ATTNQAT_WS_FWD_INFER: return carve_fwd(nullptr, B, Hq, Hkv, L, d).bytes;
-    case ATTNQAT_WS_BWD:       return carve_bwd(nullptr, B, Hq, Hkv, L, d).bytes;
+    case ATTNQAT_WS_BWD:       return bwd_ws_bytes(B, Hq, Hkv, L, d);
     case ATTNQAT_WS_FWD_INFER_MX: return carve_mx(nullptr, B, Hq, Hkv, L, d).bytes;
     case ATTNQAT_WS_FWD_INFER_MX_FP8PV: return carve_mx(nullptr, B, Hq, Hkv, L, d, true).bytes;
     case ATTNQAT_WS_FWD_INFER_MX_PAGED: {          // L = the number of query positions per sequence
@@ -282,7 +290,7 @@ size_t attnqat_workspace_bytes(int which, int B, int Hq, int Hkv, int L, int d)
         return c.off;
     }
     case ATTNQAT_WS_FWD_MX:    return carve_fwd(nullptr, B, Hq, Hkv, L, d, true).bytes;
-    case ATTNQAT_WS_BWD_MX:    return carve_bwd(nullptr, B, Hq, Hkv, L, d, true).bytes;
+    case ATTNQAT_WS_BWD_MX:    return bwd_ws_bytes(B, Hq, Hkv, L, d, true);
     default:                   return 0;
     }
 }
@@ -772,7 +780,7 @@ static int bwd_common(const void* q, const void* k, const void* v, const void* d
     prof_mark("prep_qkvdo", st);
     BwdPlan plan = bwd_plan(B * Hq, B * Hkv, L, d, causal != 0, device_cu_count());
     if (plan.joint && p_quant != 0) {
-        if (plan.splits > 1 && (!w.may_split || workspace_bytes < max(w.bytes, w.bytes_min + plan.part_bytes))) {
+        if (plan.splits > 1 && (!w.may_split || workspace_bytes < w.bytes_min + plan.part_bytes)) {
             plan.splits = 1; plan.iters = (L + 31) / 32 * (Hq / Hkv); plan.dq_first = false;
         }
         if (launch_bwd_joint(w.qb, w.kb, w.vb, dob, w.rowstat, w.bounds, B, Hq, Hkv, L, d, causal != 0, dq, dk, dv, p_quant, plan, w.part,

@@ -1079,48 +1079,10 @@ __global__ __launch_bounds__(256) void dkdv_reduce_kernel(const float* __restric
         }
 }
 
-// Whether a backward runs both passes in one launch, and how many query tiles a dK/dV workgroup takes.
-// Joint: everything except the problems whose eight-wave workgroups (wide_workgroups) fill their rounds of the compute units to
-// 97 % on average, where the halved tile copies win by 2 - 3 % (24 heads, L = 8192: 2.09 against 2.14 ms; 12 x 2 heads, L = 32760:
-// 32.0 against 33.0 ms), while rounds filled to 95, 92 and 73 % lose to the joint launch by 2, 5 and 24 % (40 heads, L = 20000
-// and 12000; 12 heads of 64, L = 12000).  Under a causal mask the two are even at 32768 positions (46.1 ms) and below that
-// joint wins by 1 - 4 %.
-// Pieces: time is counted in query tiles of the dK/dV pass (1.45 us); a 64-key tile of a dQ workgroup takes 1.16 of them.  With W the
-// work per compute unit, pieces of 0.45 W came out best or within 10 % of it over 16 shapes (8 sizes of piece each), as long as
-//   * a piece is not much shorter than the average dQ tile, which it would only have to wait for,
-//   * the pieces (and, if there are few, the dQ tiles) fit the 2 workgroups per compute unit at once: a second round of
-//     pieces costs more than it evens out (12 heads, L = 1560: 312 pieces 83 us, 468 pieces 107 us).
-BwdPlan bwd_plan(int BHq, int BHkv, int L, int D, bool causal, int cus_)
+BwdPlan bwd_plan(int BHq, int BHkv, int L, int D, bool causal, int cus)
 {
-    BwdPlan p{false, 1, 0, 0, false};
-    if (__atomic_load_n(&g_bwd_waves, __ATOMIC_RELAXED) != 0) return p;
-    const int Lp = round_up(L, kRowPad), nt = Lp / 128, G = BHq / BHkv, nq32 = (L + 31) / 32;
-    const long long cus = cus_, n8q = (long long)BHq * ((Lp + 255) / 256), n8kv = (long long)BHkv * ((Lp + 255) / 256);
-    auto fill = [&](long long n) { return (double)n / (double)((n + cus - 1) / cus * cus); };
-    if (causal ? Lp >= 32768 && n8kv >= 2 * cus : n8kv >= 2 * cus && fill(n8q) + fill(n8kv) >= 2 * 0.97) return p;
-    p.joint = true;
-    const long long whole = (long long)nq32 * G;
-    p.iters = (int)(whole < 0x7FFFFFFF ? whole : 0x7FFFFFFF);
-    const double dq_longest = 1.16 * (Lp / 64), dq_mean = causal ? 0.5 * dq_longest : dq_longest;
-    const double dkv_mean = (double)G * (causal ? nq32 - 2.0 * (nt - 1) : (double)nq32);
-    const double W = (double)nt * (BHkv * dkv_mean + BHq * dq_mean) / (double)cus;
-    double T = fmax(fmax(0.45 * W, 0.6 * dq_mean), 4.0);
-    if (T < (double)whole) {
-        const long long ndq = (long long)BHq * nt, room = 2 * cus - (ndq < cus ? ndq : 0);
-        auto pieces = [&](int t) {
-            long long n = 0;
-            for (int kt = 0; kt < nt; ++kt) n += ((long long)(nq32 - (causal ? 4 * kt : 0)) * G + t - 1) / t;
-            return n * BHkv;
-        };
-        while (T < (double)whole && pieces((int)T) > room) T = T * 1.04 + 1.0;
-        if (T < (double)whole) {
-            p.splits = (int)((whole + (int)T - 1) / (int)T);
-            p.iters = (int)T;
-            p.part_bytes = (size_t)BHkv * nt * p.splits * 2 * 128 * D * 4;
-        }
-    }
-    p.dq_first = dq_longest > 1.5 * p.iters;      // (one head, L = 16000 causal, 192 pieces: 348 against 405 us)
-    return p;
+    if (__atomic_load_n(&g_bwd_waves, __ATOMIC_RELAXED) != 0) return BwdPlan{false, 1, 0, 0, false};      // (a test forces separate passes)
+    return plan_backward(BHq, BHkv, L, D, causal, cus);
 }
 
 template <int D, bool CAUSAL, int PQ, bool COUNT = false>

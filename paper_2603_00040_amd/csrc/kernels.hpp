@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "plan.hpp"
+
 namespace aq {
 
 // Compute units of a whole MI355X: what the size queries plan for.  They ask no device (they have to work on a machine without one,
@@ -93,10 +95,8 @@ int launch_bwd_dkdv(const void* qb, const void* kb, const void* vb, const void* 
                     int p_quant /* phi(P): 0 none (ablation), 1 NVFP4, 2 MX, 3 NVFP4 with the two-level row factor */, hipStream_t st,
                     float* p_dump = nullptr /* test hook, p_quant 1 only: P^F of query rows [dump_row0, dump_row0 + 128), [B*Hq][128][L] */,
                     int dump_row0 = 0, const MxScoreOps* mx = nullptr /* p_quant 2: required */);
-// Both passes in one launch (plan.joint: problems that do not fill the chip evenly), the query tiles of a key tile shared by up to
-// plan.splits workgroups of plan.iters query tiles whose sums meet in `part` (plan.part_bytes bytes).  launch_bwd_dq and
-// launch_bwd_dkdv run what is not joint.
-struct BwdPlan { bool joint; int splits, iters; size_t part_bytes; bool dq_first; };
+// Both passes in one launch (plan.joint: problems that do not fill the chip evenly), as planned (plan.hpp); partial sums meet in `part`.
+// launch_bwd_dq and launch_bwd_dkdv run what is not joint.
 BwdPlan bwd_plan(int BHq, int BHkv, int L, int D, bool causal, int cus);
 int launch_bwd_joint(const void* qb, const void* kb, const void* vb, const void* dob, const float* rowstat, const float* bound_part,
                      int B, int Hq, int Hkv, int L, int D, bool causal, void* dq, void* dk, void* dv, int p_quant /* 1, 2 or 3 */,
