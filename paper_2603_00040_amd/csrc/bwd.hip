@@ -690,9 +690,16 @@ __device__ __forceinline__ void bwd_dkdv_body(const DkvArgs& A, int bhkv, int kt
             const bool need_mask = (key0_w + 32 > L) || (CAUSAL && key0_w + 31 > q0);
             if (__builtin_expect(need_mask, 0)) {
                 const int klim = CAUSAL ? min(L - 1, q0 + ln) : L - 1;
+// (SPLIT: half of the wave taken afresh, as in the epilogue: no register holds it from one masked tile to the next)
+                int hf_m = hf;
+                if constexpr (SPLIT) {
+                    uint32_t lane_m = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+                    asm volatile("" : "+v"(lane_m));
+                    hf_m = (int)lane_m >> 5;
+                }
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
-                    const int key = key0_w + 8 * (i >> 2) + 4 * hf + (i & 3);
+                    const int key = key0_w + 8 * (i >> 2) + 4 * hf_m + (i & 3);
                     if (key > klim) s[i] = -INFINITY;
                 }
             }
@@ -907,10 +914,17 @@ __device__ __forceinline__ void bwd_dkdv_body(const DkvArgs& A, int bhkv, int kt
     }
 
     // accumulators: row = key 8*(i>>2) + 4*hf + (i&3) of the wave, column d = 32*nb + ln
+    // (SPLIT: the lane number is taken afresh; what the second kind of store needs of it would otherwise lie in scratch during the loop)
+    uint32_t lane_o = (uint32_t)lane;
+    if constexpr (SPLIT) {
+        lane_o = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+        asm volatile("" : "+v"(lane_o));
+    }
+    const int ln_o = (int)lane_o & 31, hf_o = (int)lane_o >> 5;
     if constexpr (SPLIT) {
         if (!whole) {
             // four accumulators (keys 8 t4 + 4 hf .. + 3) at a time, as they lie in the lanes: 1 KiB per wave and store
-            floatx4* dst = reinterpret_cast<floatx4*>(A.part) + (((size_t)bhkv * (Lp / KT) + kt_) * A.splits + piece) * (2 * NB * 4 * NW * 64) + wave * 64 + lane;
+            floatx4* dst = reinterpret_cast<floatx4*>(A.part) + (((size_t)bhkv * (Lp / KT) + kt_) * A.splits + piece) * (2 * NB * 4 * NW * 64) + wave * 64 + lane_o;
             const float un = rs / rs_s;              // 1 / ds_scale, exact: a power of two
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
@@ -929,9 +943,9 @@ __device__ __forceinline__ void bwd_dkdv_body(const DkvArgs& A, int bhkv, int kt
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            const int key = key0_w + 8 * (i >> 2) + 4 * hf + (i & 3);
+            const int key = key0_w + 8 * (i >> 2) + 4 * hf_o + (i & 3);
             if (key < L) {
-                const size_t o = ((size_t)bhkv * L + key) * D + 32 * nb + ln;
+                const size_t o = ((size_t)bhkv * L + key) * D + 32 * nb + ln_o;
                 dK[o] = f32_to_bf16_rne(dk[nb][i] * (rs / rs_s));            // / ds_scale, exact: a power of two
                 dV[o] = f32_to_bf16_rne(dv[nb][i]);
             }

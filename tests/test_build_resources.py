@@ -2,6 +2,7 @@
 a hot loop costs a scratch round trip per tile (and, because vector-memory loads return in order, a
 wait for the tile prefetch in flight).  This test compiles the kernels with the compiler's resource
 remarks and fails if a production kernel spills or loses its occupancy.  CPU only: hipcc cross-compiles."""
+import functools
 import os
 import re
 import shutil
@@ -15,6 +16,7 @@ from paper_2603_00040_amd import build as B
 pytestmark = pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not on PATH")
 
 
+@functools.lru_cache(maxsize=None)
 def _resources(src):
     with tempfile.TemporaryDirectory() as tmp:
         r = subprocess.run(["hipcc", *B.FLAGS, "-Rpass-analysis=kernel-resource-usage", "-c",
@@ -122,6 +124,32 @@ def test_mx_forward_kernels_do_not_spill():
     _check(k, r"fwd_mx_kernelILi(64|128)ELb[01]ELb[01]ELi[012]E", 16)
     # fwd_mx_decode_kernel<D, CAUSAL, NP = 1>: two workgroups per CU
     _check(k, r"fwd_mx_decode_kernelILi(64|128)ELb[01]ELi1E", 4)
+
+
+def test_four_wave_forward_kernels_do_not_spill():
+    # fwd_narrow_kernel<D, TRAIN, CAUSAL, PQ, VARLEN>: the forward of every problem that does not fill the chip with eight-wave workgroups
+    k = _resources("fwd.hip")
+    _check(k, r"fwd_narrow_kernelILi(64|128)ELb[01]ELb[01]ELi[012]ELb0E", 24)
+    _check(k, r"fwd_narrow_kernelILi(64|128)ELb0ELb[01]ELi3ELb0E", 4)
+    _check(k, r"fwd_narrow_kernelILi(64|128)ELb0ELb[01]ELi0ELb1E", 4)
+    assert len([n for n in k if "fwd_narrow_kernel" in n]) == 32
+
+
+def test_joint_backward_kernels_do_not_spill():
+    # bwd_joint_kernel<D, CAUSAL, PQ, COUNT>: the backward of all but the largest problems; the measurement variants (COUNT) are exempt
+    k = _resources("bwd.hip")
+    _check(k, r"bwd_joint_kernelILi(64|128)ELb[01]ELi[123]ELb0E", 12)
+    _check(k, r"dkdv_reduce_kernelILi(64|128)ELb[01]E", 4)
+
+
+def test_preparing_kernels_keep_off_scratch_memory():
+    # scalar registers parked in lanes of a vector register cost no memory access: the backward's group carries the addresses of
+    # nine arrays beside its loop bounds
+    for src, pattern, n in (("prep.hip", r"(prep_group_kernelI|quantize_kernelE|kv_page_write_kernelI)", 9),
+                            ("mxprep.hip", r"(mx_group_kernelI|mx_q_kernelI)", 10), ("decode.hip", r"decode_(prepare|merge)_kernelI", 4)):
+        hit = _check(_resources(src), pattern, n, spill_free=False)
+        assert all(v["VGPRs Spill"] == 0 and v["ScratchSize [bytes/lane]"] == 0 and v["SGPRs Spill"] <= 48 for v in hit.values()), hit
+        assert all(v["Occupancy [waves/SIMD]"] >= 5 for v in hit.values()), hit
 
 
 def test_no_lds_read_is_in_flight_at_a_barrier_of_the_forward():
