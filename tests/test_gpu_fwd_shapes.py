@@ -53,3 +53,26 @@ def test_sequences_together_equal_sequences_alone(B, Hq, Hkv, Lq, d, causal):
     for b in sorted({0, 1, B // 2, B - 1}):
         o1, l1 = aq.attnqat_fwd_infer_paged(q[b:b + 1].contiguous(), cache, num_pages, table[b:b + 1].contiguous(), lens[b:b + 1].contiguous(), Hkv, causal)
         assert torch.equal(o[b:b + 1], o1) and torch.equal(lse[b:b + 1], l1), b
+
+
+def test_long_prefill_chunk_equals_its_parts():
+    """A chunk of 4096 positions under the causal mask runs on eight waves (2 sequences x 16 heads x 8 pairs of tiles are a whole round of
+    the compute units), its parts of 1000 - 2048 positions on four: rows do not depend on each other.  Lengths with and without keys in
+    front of the chunk."""
+    import paper_2603_00040_amd as aq
+    Hq, Hkv, d, Lq, lens = 16, 4, 128, 4096, (5000, 4096)
+    pages = [(n + 127) // 128 for n in lens]
+    num_pages, max_pages = sum(pages), max(pages)
+    cache = torch.zeros(num_pages * aq.kv_cache_page_bytes_nvfp4(Hkv, d), dtype=torch.uint8, device="cuda")
+    table, at = torch.zeros((len(lens), max_pages), dtype=torch.int32, device="cuda"), 0
+    for b, n in enumerate(lens):
+        table[b, :pages[b]] = torch.arange(at, at + pages[b], dtype=torch.int32, device="cuda").flip(0)
+        at += pages[b]
+        x = random_inputs(1, Hkv, Hkv, n, d, seed=5 + b)
+        aq.attnqat_kv_cache_write(to_dev(x["k"]), to_dev(x["v"]), cache, table[b, :pages[b]].contiguous(), 0, num_pages)
+    q = to_dev(random_inputs(len(lens), Hq, Hkv, Lq, d, seed=7)["q"])
+    kl = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    o, lse = aq.attnqat_fwd_infer_paged(q, cache, num_pages, table, kl, Hkv, True)
+    for lo, hi in ((0, 1000), (1000, 2048), (2048, 4096)):
+        part, pl = aq.attnqat_fwd_infer_paged(q[:, :, lo:hi].contiguous(), cache, num_pages, table, kl - (Lq - hi), Hkv, True)
+        assert torch.equal(o[:, :, lo:hi], part) and torch.equal(lse[:, :, lo:hi], pl), (lo, hi)
