@@ -114,14 +114,14 @@ __global__ __launch_bounds__(D) void mx_quant_l_kernel(
 // KVM == 2, block-sparse attention on contiguous kv records: the workgroup visits only the 128-key blocks listed for its
 // 128 query rows (page_table then is the list [B*Hq*ceil(L/128), max_pages] of block indices in increasing order and
 // kv_lens the number of entries per row of that list); a row that ends up without any key gets O = 0 and L = -inf.
-template <int D, bool CAUSAL, bool FP8PV, int KVM /* 0 contiguous, 1 paged KV cache, 2 block-sparse */>
+template <int D, bool CAUSAL, bool FP8PV, int KVM /* 0 contiguous, 1 paged KV cache, 2 block-sparse, 3 paged, by sequence length */>
 __global__ __launch_bounds__(256, 2) void fwd_mx_kernel(
     const unsigned char* __restrict__ qops, const uint32_t* __restrict__ qsc, const unsigned char* __restrict__ kv,
     uint16_t* __restrict__ O, float* __restrict__ lse, int L, int Lp, int Hq, int G, float c /* log2(e)/sqrt(d) */,
     const int* __restrict__ page_table, const int* __restrict__ kv_lens, int max_pages, int num_pages, int lq_inner, int B)
 {
     constexpr int KS = D / 64, MT = D / 32;
-    constexpr bool PAGED = KVM == 1, SPARSE = KVM == 2;
+    constexpr bool PAGED = KVM == 1 || KVM == 3, SPARSE = KVM == 2;
     constexpr int KOPS = 2 * KS * 1024, VOPS = MT * (FP8PV ? 2048 : 1024), REC = mx_rec_bytes(D, FP8PV), STAGE = 2 * REC, NCH = STAGE / 1024;
     static_assert(STAGE % 1024 == 0, "a stage is a whole number of 1 KiB wave copies");
     extern __shared__ __align__(16) unsigned char smem[];          // 3 stage buffers
@@ -131,14 +131,9 @@ __global__ __launch_bounds__(256, 2) void fwd_mx_kernel(
     // In order of length: measured against head after head, 2 x 16/4 heads, L = 3001 causal 87 -> 66 us, 4 x 32/8 heads, L = 4096
     // 416 -> 374 us, L = 8192 364 -> 323 us, 64/8 heads, L = 32768 8.84 ms either way; block-sparse 32/8 heads, L = 8192 148 -> 130 us.
     // (sequences of 2k - 16k keys, 512-position chunks of 8 of them: 392 -> 317 us)
-    if constexpr (PAGED) {
-        if (gridDim.x > 256) {
-            if (!varlen_item(blockIdx.x, kv_lens, B, Hq, G, nqt, bh, qt)) return;
-        } else {                            // every workgroup has a compute unit of its own: no order to look up first (1 - 2 us)
-            head_tile_of_block(blockIdx.x, B * Hq, nqt, bh, qt);
-            if (bh >= B * Hq) return;       // (the grid is rounded up to whole rows of units)
-        }
-    } else if (CAUSAL) longest_first(blockIdx.x, B * Hq, nqt, bh, qt);
+    if constexpr (KVM == 3) {
+        if (!varlen_item(blockIdx.x, kv_lens, B, Hq, G, nqt, bh, qt)) return;
+    } else if (CAUSAL && !PAGED) longest_first(blockIdx.x, B * Hq, nqt, bh, qt);
     else head_tile_of_block(blockIdx.x, B * Hq, nqt, bh, qt);
     if (CAUSAL) qt = nqt - 1 - qt;
     const int b = bh / Hq, h = bh % Hq;
@@ -627,7 +622,7 @@ static int launch_fwd_mx_t(const void* qops, const void* qsc, const void* kv, in
     static unsigned long long lds_set = 0;          // one per instantiation
     if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)smem, lds_set)) return -1;
     const float c = 1.4426950408889634f / sqrtf((float)D);
-    const int groups = KVM == 1 ? round_up(B * Hkv, 8) : B * Hkv;       // (see varlen_item)
+    const int groups = KVM == 3 ? round_up(B * Hkv, 8) : B * Hkv;       // (see varlen_item)
     hipLaunchKernelGGL(kern, dim3((unsigned)(groups * (Hq / Hkv) * (Lp / 128))), dim3(256), smem, st,
                        (const unsigned char*)qops, (const uint32_t*)qsc, (const unsigned char*)kv,
                        (uint16_t*)o, lse, L, Lp, Hq, Hq / Hkv, c, page_table, kv_lens, max_pages, num_pages, lq_inner, B);
@@ -672,10 +667,16 @@ int launch_fwd_mx_paged(const void* qops, const void* qsc, const void* cache, in
 #undef AQ_DECODE
         return -1;
     }
-#define AQ_PAGED(DD, CC) launch_fwd_mx_t<DD, CC, false, 1>(qops, qsc, cache, B, Hq, Hkv, Lq, o, lse, page_table, kv_lens, max_pages, num_pages, lq_inner, st)
+    // With no more workgroups than compute units each has one of its own, and no order is worth looking up.  A kernel of its own: with
+    // both in one the key loop came out 1.5 - 2 % slower, of the same instructions in other registers (16/2 heads, 500 positions over
+    // 15k keys: 112.2 -> 114.4 us; 8 sequences of 16/4 heads, 98 positions over 2k - 7k keys: 87.4 -> 88.8 us).
+    const bool by_length = (long long)B * Hq * (round_up(Lq, kRowPad) / 128) > device_cu_count();
+#define AQ_PAGED_K(DD, CC, KK) launch_fwd_mx_t<DD, CC, false, KK>(qops, qsc, cache, B, Hq, Hkv, Lq, o, lse, page_table, kv_lens, max_pages, num_pages, lq_inner, st)
+#define AQ_PAGED(DD, CC) (by_length ? AQ_PAGED_K(DD, CC, 3) : AQ_PAGED_K(DD, CC, 1))
     if (D == 128) return causal ? AQ_PAGED(128, true) : AQ_PAGED(128, false);
     if (D == 64)  return causal ? AQ_PAGED(64, true) : AQ_PAGED(64, false);
 #undef AQ_PAGED
+#undef AQ_PAGED_K
     return -1;
 }
 
