@@ -67,13 +67,13 @@ __device__ __forceinline__ void fwd_body(
     // the same amount of work (no tail of long tiles at the end of a head) and there are half as many workgroups, each of
     // which costs the CU a fixed 20 - 30 us of start-up and wind-down that nothing overlaps at one workgroup per CU.
     // Four waves (128 rows): one tile per workgroup, the longest first under a causal mask.
-    const int nqt = (Lp + QT - 1) / QT, nheads = B * Hq;
+    const int nqt = (Lp + QT - 1) / QT;
     const int per_head = PAIRED ? (nqt + 1) / 2 : nqt;
     int bh, qt0;
     if constexpr (VARLEN && NW == 4) {
         if (!varlen_item(blockIdx.x, kv_lens, B, Hq, G, nqt, bh, qt0)) return;
-    } else if (CAUSAL && NW == 4) longest_first(blockIdx.x, nheads, per_head, bh, qt0);
-    else head_tile_of_block(blockIdx.x, nheads, per_head, bh, qt0);
+    } else if (CAUSAL && NW == 4) longest_first(blockIdx.x, B * Hq, per_head, bh, qt0);
+    else head_tile_of_block(blockIdx.x, gridDim.x / per_head, per_head, bh, qt0);      // (the heads from the grid: see fwd_mx_kernel)
     const int nitems = (PAIRED && nqt - 1 - qt0 != qt0) ? 2 : 1;
     const int b = bh / Hq, h = bh % Hq;
     const int bhkv = b * (Hq / G) + h / G;
