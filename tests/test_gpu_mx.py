@@ -292,3 +292,24 @@ def test_v_at_any_address(L, d):
         assert all(torch.equal(a, b) for a, b in zip(f(q, k, v, True), f(q, k, odd, True)))
     _, lse, ohp = aq.attnqat_fwd_mx(q, k, v, True)
     assert all(torch.equal(a, b) for a, b in zip(aq.attnqat_bwd_mx(q, k, v, do, lse, ohp, True), aq.attnqat_bwd_mx(q, k, odd, do, lse, ohp, True)))
+
+
+@pytest.mark.parametrize("H,L,d", [(1, 1, 64), (3, 3, 64), (2, 129, 64), (2, 127, 128), (1, 2, 128)])
+def test_dequantized_copy_of_blocks_along_d(H, L, d):
+    """The copy that attnqat_quantize_mx writes beside codes and scales is their product, element by element, and nothing behind it is
+    touched (four blocks are stored together: their ends, rows of two blocks, and odd numbers of rows)."""
+    import paper_2603_00040_amd as aq
+    x = to_dev(random_inputs(1, H, H, L, d, seed=L + d)["q"])
+    codes, scales, _ = aq.attnqat_quantize_mx(x, 0, want_xf=False)
+    room = torch.full((x.numel() + 64,), 7.0, dtype=x.dtype, device="cuda")
+    for with_codes in (True, False):
+        xf = room[:x.numel()]
+        aq._check(aq.lib().attnqat_quantize_mx(x.data_ptr(), 1, H, L, d, aq.BF16, 0, codes.data_ptr() if with_codes else None, None, xf.data_ptr(), None))
+        torch.cuda.synchronize()
+        c = codes.cpu().numpy()
+        code = np.stack([c & 15, c >> 4], axis=-1).reshape(1, H, L, d)
+        grid = np.array([0.0, 0.5, 1.0, 1.5, 2.0, 3.0, 4.0, 6.0])
+        want = np.where(code & 8, -1.0, 1.0) * grid[code & 7] * np.repeat(np.exp2(scales.cpu().numpy().astype(np.float64) - 127.0), 32, axis=-1)
+        assert (xf.view(x.shape).double().cpu().numpy() == want).all()
+        assert bool((room[x.numel():] == 7.0).all())
+        room.fill_(7.0)
