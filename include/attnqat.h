@@ -150,7 +150,13 @@ int attnqat_fwd_infer_static(const void* q, const void* k, const void* v,
  * q,k,v are the un-quantized inputs of the forward (they are fake-quantized
  * again here, which is bit-identical); d_o [B,Hq,L,d] bf16; lse and o_hp are
  * the forward's outputs.  dq [B,Hq,L,d], dk,dv [B,Hkv,L,d] bf16 (written; dk and
- * dv are summed over the Hq/Hkv query heads of a group).
+ * dv are summed over the Hq/Hkv query heads of a group).  They may lie over the
+ * inputs, d_o included (d_o is then copied to the workspace first).
+ * Results are deterministic.  Where the heads of a call leave compute units idle,
+ * several workgroups share the sum over the queries of a key tile: how the fp32
+ * sums of dk and dv are grouped follows from B, Hq, Hkv, L, d, causal and the
+ * device's compute units, so a head's last bits may differ between calls with
+ * other heads beside it (dq is not affected).
  */
 int attnqat_bwd(const void* q, const void* k, const void* v, const void* d_o,
                 const float* lse, const float* o_hp,
@@ -371,7 +377,11 @@ int attnqat_fwd_infer_mx_paged(const void* q, int B, int Hq, int Hkv, int Lq, in
  *     in chunk order, so a predecessor is always running or finished when someone waits for it and the wait ends; it is
  *     bounded nevertheless (2^22 polls), and a wait that expired leaves a wrong result for that sequence.  The partial
  *     sums of the chunks of a sequence are added by a third kernel.  The result is not bit-identical to
- *     attnqat_fwd_infer (the sums are grouped differently) but holds the same parity bars against the oracle.
+ *     attnqat_fwd_infer (the sums are grouped differently) but holds the same parity bars against the oracle.  It is
+ *     deterministic; the grouping (the length of the chunks) follows from B, Hkv, the rows, max_pages and the device's compute
+ *     units, so a sequence's last bits may differ between steps with other sequences beside it or a wider page table.  A
+ *     workspace that lacks only the room for the shortest chunks is accepted and gets longer ones (slower where few
+ *     sequences are served); any size from the one asked for on gives the same bits.
  * attnqat_debug_fwd_infer_paged is the same call with the poll limit as an argument (tests force the expiry path with
  * 0); it synchronizes the stream and sets *wait_expired (host) to 1 if any wait of the decode path ran out.
  */

@@ -385,10 +385,10 @@ static int launch_dq_v(const void* qb, const void* kb, const void* vb, const voi
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-// Eight waves per workgroup for a pass whose problem still leaves every compute unit two such workgroups to balance
-// with, and, under a causal mask, whose sequences are long enough for the 256 rows at the diagonal, where part of the
-// workgroup idles, not to matter (llm32k_gqa: 1.5 % faster with eight; llm4k_gqa: 2 - 8 % slower); or when a test
-// forces them; four otherwise.
+// Eight waves per workgroup for a separate pass (plan.hpp says which problems run those) whose problem still leaves every compute
+// unit two such workgroups to balance with, and, under a causal mask, whose sequences are long enough for the 256 rows at the diagonal,
+// where part of the workgroup idles, not to matter (llm32k_gqa: 1.5 % faster with eight; llm4k_gqa: 2 - 8 % slower; the plan leaves
+// no shorter causal problem here but the ablation with the unquantized P); or when a test forces them; four otherwise.
 static bool wide_workgroups(bool causal, long long groups_of_256, int Lp)
 {
     const int forced = __atomic_load_n(&g_bwd_waves, __ATOMIC_RELAXED);
@@ -1025,7 +1025,7 @@ int launch_bwd_dkdv(const void* qb, const void* kb, const void* vb, const void* 
 // tiles), whose fp32 sums dkdv_reduce_kernel adds in order.  The arithmetic of a tile and the order inside a piece are those of
 // bwd_dkdv_kernel.  The dK/dV pieces come first, the dQ tiles fill in behind them (alternating the two kinds was 0 - 30 % slower),
 // or the other way round where a dQ tile is the longer piece.  Measured, backward call, passes one after another -> joint
-// without pieces -> as planned by bwd_plan: 2 x 16/4 heads, L = 3001 causal 617 -> 518 -> 292 us (MX 683 -> 596 -> 328 us);
+// without pieces -> as planned (plan.hpp): 2 x 16/4 heads, L = 3001 causal 617 -> 518 -> 292 us (MX 683 -> 596 -> 328 us);
 // 8/2 heads, L = 8192 causal 1264 -> 1139 -> 475 us; 12 heads, L = 1560 120 -> 91 -> 82 us; 4 x 32/8 heads, L = 4096 causal
 // 2.09 -> 1.85 ms (no pieces); 12 heads, L = 6240 833 -> 698 us (no pieces).
 template <int D, bool CAUSAL, int PQ, bool COUNT = false /* the measurement variant of bwd_dkdv_body */>

@@ -95,7 +95,7 @@ def test_decode_sequences_cut_into_chunks(d, causal):
 
 
 def test_decode_many_short_sequences():
-    """More sequences than the chunk list's builder stages next to its lanes (2048): the list is built from the lengths in
+    """More sequences than the chunk list's builder takes at a time (256): the list is built from the lengths in
     memory, and every sequence is a single chunk."""
     rng = np.random.default_rng(9)
     lens = [int(n) for n in rng.integers(1, 41, size=2100)]
