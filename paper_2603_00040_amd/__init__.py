@@ -102,10 +102,15 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+# (the handle itself where this torch has a way to it, which is not part of its public interface: torch.cuda.current_stream() builds a
+#  Stream object around it on every call, a few microseconds of a step whose kernels take twenty)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
-    # (the handle itself: torch.cuda.current_stream() builds a Stream object around it on every call, a few microseconds of a step
-    #  whose kernels take twenty)
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _dev_bf16(t, name):

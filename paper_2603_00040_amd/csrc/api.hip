@@ -160,7 +160,7 @@ BwdWs carve_bwd(void* ws, int B, int Hq, int Hkv, int L, int d, bool mx = false)
     w.krec = mx ? c.take(mx_ktrain_bytes(B * Hkv, L, d)) : nullptr;
     // Partial sums of dK and dV lie behind everything else; without room for them (bytes_min) a
     // problem runs unsplit.  Below kSmallBwdWs, where they would be several times the arrays above, the size asked for leaves them
-    // out, and such a problem runs unsplit in a larger workspace too: the bits of dK and dV follow from the shape, not from the room
+    // out (it stays what callers have computed for such problems), and such a problem runs unsplit in a larger workspace too: the bits of dK and dV follow from the shape, not from the room
     // that a caller happens to give (2 heads, L = 256, d = 64: 2 of 30 us).
     w.bytes_min = c.off;
     w.may_split = w.bytes_min >= kSmallBwdWs;

@@ -255,6 +255,7 @@ __device__ inline void head_tile_of_block(int block, int nheads, int per_head, i
 // compute unit from the start, the first round of an XCD's 32 compute units and the second: in order of length the second
 // round would put the longest tiles on the units that already have the longest (with a multiple of 32 tiles per head it
 // did so exactly), so it runs backwards.  From the third round on the units take what comes as they get free.
+// (Eight XCDs of 32 compute units, a whole MI355X: on a part of one the order is another and only time depends on it.)
 // Heads stay on their XCD as in head_tile_of_block where their number allows it.  Measured on the causal forward
 // (four-wave workgroups, d = 128), head after head -> longest first, second round backwards: 2 x 16 heads, L = 3001
 // 165 -> 127 us; 4 x 32 heads, L = 4096 852 -> 799 us; 12 heads, L = 24000 2657 -> 2322 us.

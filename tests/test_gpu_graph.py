@@ -160,3 +160,14 @@ def test_graph_replay_of_the_paged_nvfp4_forward():
             assert torch.equal(t, w), (rep, seed)
         assert not torch.isnan(l1).any() and not torch.isnan(l64).any()
     print("paged NVFP4 forward: graph replays bit-identical to eager", flush=True)
+
+
+def test_calls_go_to_the_current_stream(monkeypatch):
+    """The binding launches on torch's current stream, with and without torch's shortcut to its handle."""
+    import paper_2603_00040_amd as aq
+    side = torch.cuda.Stream()
+    for short in (aq._raw_stream, None):
+        monkeypatch.setattr(aq, "_raw_stream", short)
+        assert (aq._stream() or 0) == torch.cuda.current_stream().cuda_stream
+        with torch.cuda.stream(side):
+            assert aq._stream() == side.cuda_stream
