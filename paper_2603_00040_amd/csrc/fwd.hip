@@ -73,8 +73,10 @@ __device__ __forceinline__ void fwd_body(
     if constexpr (VARLEN && NW == 4) {
         if (!varlen_item(blockIdx.x, kv_lens, B, Hq, G, nqt, bh, qt0)) return;
     } else if (CAUSAL && NW == 4) longest_first(blockIdx.x, B * Hq, per_head, bh, qt0);
-    else if (NW == 4) head_tile_of_block(blockIdx.x, B * Hq, per_head, bh, qt0);          // (the division costs the smallest calls 0.3 us)
-    else head_tile_of_block(blockIdx.x, gridDim.x / per_head, per_head, bh, qt0);      // (the heads from the grid: see fwd_mx_kernel)
+    // (The heads from the arguments, or from the grid: the same number, but the longer entry moves the key loop, see fwd_mx_kernel.
+    //  Training, eight waves: 4 x 64/8 heads, L = 4096, d = 64 1903 -> 1884 us from the grid, d = 128 even; inference and four waves
+    //  are better off without the division: 2 x 12 heads, L = 32760, d = 128 11.31 -> 11.24 ms, 2 heads, L = 256 training step 30.6 -> 30.3 us.)
+    else head_tile_of_block(blockIdx.x, TRAIN && NW == 8 ? gridDim.x / per_head : B * Hq, per_head, bh, qt0);
     const int nitems = (PAIRED && nqt - 1 - qt0 != qt0) ? 2 : 1;
     const int b = bh / Hq, h = bh % Hq;
     const int bhkv = b * (Hq / G) + h / G;
