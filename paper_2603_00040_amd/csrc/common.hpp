@@ -233,6 +233,19 @@ __device__ inline void async_copy16(const void* gbase, uint32_t voff, void* lds_
                  :: "v"(voff), "s"(gbase), "s"(lds) : "memory");
 }
 
+// ---- the forward's copies of K and V^T -----------------------------------------
+// Where the forward's workspace keeps 8 values of one lane's matrix operand (16 bytes), as an offset in values from the start of the
+// copy of a head.  Tiles of 64 keys, 64 D values each; in a tile one KiB per operand, in the order in which the products take them:
+// K: (16 d, 32 keys); lane (key, half) holds d 16 ds + 8 half .. + 7 of its key.
+// V^T: (16 keys, 32 d); lane (d, half) holds of the group's 16 keys those that a lane of that half owns in the accumulator of S^T:
+// keys {0-3, 8-11} (half 0) or {4-7, 12-15} (half 1) of the group, position p of the group being key perm16(p).
+__host__ __device__ inline size_t k_operand_offset(int l, int ds, int half, int D) {
+    return (size_t)(l >> 6) * 64 * D + (size_t)((2 * ds + ((l >> 5) & 1)) * 64 + 32 * half + (l & 31)) * 8;
+}
+__host__ __device__ inline size_t v_operand_offset(int group /* of 16 keys */, int c /* d */, int half, int D) {
+    return (size_t)(group >> 2) * 64 * D + (size_t)(((group & 3) * (D / 32) + (c >> 5)) * 64 + 32 * half + (c & 31)) * 8;
+}
+
 // ---- workgroup -> (head, tile) with heads pinned to XCDs ----------------------
 // The dispatcher hands workgroup i to XCD i % 8, and every XCD has its own L2.  All workgroups of a head stream the
 // same K/V (or Q/dO) tiles, so a head is kept on one XCD: XCD x works through heads x, x + 8, ... one after another

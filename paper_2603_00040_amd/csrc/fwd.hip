@@ -2,11 +2,12 @@
 //
 // Work split: a workgroup of 8 waves owns 256 query rows of one head; each wave owns 32
 // of them.  Key tiles of B_k = 64 keys are visited in increasing order; K and V^T tiles
-// are copied global->LDS directly (global_load_lds, double buffered, XOR-swizzled rows)
-// and shared by the eight waves.  Waves 0-3 and waves 4-7 run half an iteration apart
+// are copied global->LDS directly (global_load_lds, double buffered, in the order of the
+// matrix instruction's operands) and shared by the eight waves.  Waves 0-3 and waves 4-7 run half an iteration apart
 // (vector phase / matrix phase, separated by barriers).  Problems that do not fill the chip with
 // such workgroups run four waves and 128 rows (fwd_narrow_kernel, chosen by narrow_workgroups):
-// the same arithmetic in the same order, one barrier per tile, two workgroups per compute unit.
+// the same arithmetic in the same order, one barrier per tile, two workgroups per compute unit;
+// and the smallest four waves that share 32 rows (fwd_split_kernel, chosen by split_key_tiles).
 //
 // MFMA shapes (v_mfma_f32_32x32x16_f16, fp32 accumulate).  All operands are the
 // dequantized NVFP4 values s*c, which fp16 represents exactly, so the products are those
@@ -18,7 +19,9 @@
 // keys: the row max, the row sum and the 16-key block max of phi(P-tilde) are register
 // reductions plus one exchange between the two 32-lane halves, and the accumulator
 // layout of S^T already is the B-operand layout of the P.V products (V^T is stored with
-// the matching key permutation, see prep.hip).
+// the matching key permutation, see v_operand_offset).
+#include <type_traits>
+
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -26,8 +29,8 @@ namespace aq {
 
 template <int D>
 struct FwdSmem {
-    half_t k[2][64 * D];      // K tile [key][d], 16-byte chunks XOR-swizzled inside a row
-    half_t v[2][D * 64];      // V^T tile [d][key], likewise
+    half_t k[2][64 * D];      // K tile in the order of the S products' operands (k_operand_offset)
+    half_t v[2][D * 64];      // V^T tile, in the order of the P V products' (v_operand_offset)
 };
 
 // PQ, the format of P-tilde in the P V product: 0 NVFP4, 1 MX, 2 NVFP4 with the two-level row factor,
@@ -36,15 +39,17 @@ struct FwdSmem {
 // VARLEN (serving): every sequence b has its own number of keys kv_lens[b] (read here, on the device), the copies of K and V^T
 // are laid out for Lkp positions per head, and the L query rows are the LAST L positions of their sequence: under the causal
 // mask query i sees keys 0 .. kv_lens[b] - L + i (a chunk of a prefill; needs kv_lens[b] >= L).
-template <int D, bool TRAIN, bool CAUSAL, bool DUMP, int PQ, bool VARLEN, int NW>
+// SPLIT (fwd_split_kernel): the four waves share 32 query rows and take four key tiles at a time; see there.
+template <int D, bool TRAIN, bool CAUSAL, bool DUMP, int PQ, bool VARLEN, int NW, bool SPLIT = false>
 __device__ __forceinline__ void fwd_body(
     const half_t* __restrict__ Qh, const half_t* __restrict__ Kh, const half_t* __restrict__ Vt,
     uint16_t* __restrict__ O, float* __restrict__ lse, float* __restrict__ Ohp,
     int L, int Lp, int Hq, int G, float c /* log2(e)/sqrt(d) */, int dump_row0, float* __restrict__ pdump,
     int Lkp_arg, const int* __restrict__ kv_lens, const uint32_t* __restrict__ Qsc, int B /* batch (VARLEN: sequences) */)
 {
-    constexpr int QT = 32 * NW;     // query rows of a workgroup
-    constexpr bool PHASES = NW == 8, PAIRED = CAUSAL && NW == 8;
+    constexpr int KS = SPLIT ? NW : 1;
+    constexpr int QT = 32 * NW / KS;       // query rows of a workgroup
+    constexpr bool PHASES = NW == 8 && !SPLIT, PAIRED = CAUSAL && PHASES;
     // PQ == 1 (MX): S = Q^F K^F^T comes from the E2M1 codes and E8M0 scales by v_mfma_scale_f32_32x32x64_f8f6f4 (a quarter of
     // the matrix time of the 16-bit products, a quarter of the K bytes through LDS).  Qh then holds the Q operands of that
     // instruction (64 d per step: lane (row, half) has d-slots 64 ks + 32 half .. + 31 of its row) with one dword of scale
@@ -56,8 +61,9 @@ __device__ __forceinline__ void fwd_body(
     typedef int int8v __attribute__((ext_vector_type(8)));
     constexpr int DS = D / 16;      // contraction steps of S
     constexpr int MB = D / 32;      // 32-row blocks of O^T
-    constexpr int KCH = D / 8;      // 16-byte chunks per K row
-    constexpr int KLD = KCH / NW;   // 1 KiB wave-loads per wave for the K tile
+    constexpr int OB = MB >= KS ? MB / KS : 1;      // those of a wave
+    constexpr bool BOTH = MB >= KS;                 // a wave has its blocks of O and of O' (else: of either, or of nothing)
+    constexpr int KLD = D / 8 / NW; // 1 KiB wave-loads per wave for the K tile
     constexpr int VLD = D / 8 / NW; // ... for the V^T tile
     extern __shared__ __align__(256) unsigned char smem_raw[];   // the XORs of address bits 5..7 commute with adding this base
     FwdSmem<D>& sm = *reinterpret_cast<FwdSmem<D>*>(smem_raw);
@@ -67,16 +73,16 @@ __device__ __forceinline__ void fwd_body(
     // the same amount of work (no tail of long tiles at the end of a head) and there are half as many workgroups, each of
     // which costs the CU a fixed 20 - 30 us of start-up and wind-down that nothing overlaps at one workgroup per CU.
     // Four waves (128 rows): one tile per workgroup, the longest first under a causal mask.
-    const int nqt = (Lp + QT - 1) / QT;
+    const int nqt = SPLIT ? (L + QT - 1) / QT : (Lp + QT - 1) / QT;
     const int per_head = PAIRED ? (nqt + 1) / 2 : nqt;
     int bh, qt0;
-    if constexpr (VARLEN && NW == 4) {
+    if constexpr (VARLEN && !PHASES) {
         if (!varlen_item(blockIdx.x, kv_lens, B, Hq, G, nqt, bh, qt0)) return;
-    } else if (CAUSAL && NW == 4) longest_first(blockIdx.x, B * Hq, per_head, bh, qt0);
+    } else if (CAUSAL && !PHASES) longest_first(blockIdx.x, B * Hq, per_head, bh, qt0);
     // (The heads from the arguments, or from the grid: the same number, but the longer entry moves the key loop, see fwd_mx_kernel.
     //  Training, eight waves: 4 x 64/8 heads, L = 4096, d = 64 1903 -> 1884 us from the grid, d = 128 even; inference and four waves
     //  are better off without the division: 2 x 12 heads, L = 32760, d = 128 11.31 -> 11.24 ms, 2 heads, L = 256 training step 30.6 -> 30.3 us.)
-    else head_tile_of_block(blockIdx.x, TRAIN && NW == 8 ? gridDim.x / per_head : B * Hq, per_head, bh, qt0);
+    else head_tile_of_block(blockIdx.x, TRAIN && PHASES ? gridDim.x / per_head : B * Hq, per_head, bh, qt0);
     const int nitems = (PAIRED && nqt - 1 - qt0 != qt0) ? 2 : 1;
     const int b = bh / Hq, h = bh % Hq;
     const int bhkv = b * (Hq / G) + h / G;
@@ -95,31 +101,15 @@ __device__ __forceinline__ void fwd_body(
     asm volatile("" : "+v"(lane_i));
     const int lane = (int)lane_i, ln = lane & 31, hf = lane >> 5;
 
-    // Chunk c of row r sits at chunk c ^ key(r), so an operand's byte offset is (per-lane constant) XOR
-    // (compile-time constant): K rows  k_rd ^ (ds << 5),  V^T rows  v_rd ^ (ks << 5); 32 more rows and
-    // the other buffer are constant distances.
-    const int k_rd = 2 * swz_elem<KCH>(ln, 8 * hf);
-    const int v_rd = 2 * swz_elem<8>(ln, 8 * hf);
+    // The copies lie in memory, and so in LDS, in the order of the operands: operand i of a tile is the KiB at 1024 i, of which a
+    // lane takes the 16 bytes at 16 lane.  Copies and reads are then one lane offset plus constants (an LDS read's own offset
+    // field): rows in LDS, their chunks swizzled against bank conflicts, cost an XOR per read and two offset registers, and the
+    // vector pipe is what bounds these kernels.
     const unsigned char* kbase = reinterpret_cast<const unsigned char*>(&sm.k[0][0]);
     const unsigned char* vbase = reinterpret_cast<const unsigned char*>(&sm.v[0][0]);
 
-    // direct-to-LDS tile loads: wave-uniform tile base + this lane's byte offset inside the tile
-    // (four waves: a wave's copies of a tile differ by whole 1 KiB steps in the row and by one swizzle bit pair, so one offset
-    //  register each for K and V^T serves all of them: the training kernel has none to spare)
-    constexpr bool ONE_OFF = NW == 4;
-    uint32_t k_ld[ONE_OFF ? 1 : KLD], v_ld[ONE_OFF ? 1 : VLD];
-#pragma unroll
-    for (int i = 0; i < (ONE_OFF ? 1 : KLD); ++i) {
-        const int slot = 64 * (wave * KLD + i) + lane, r = slot / KCH, pc = slot % KCH;
-        k_ld[i] = 2u * (uint32_t)(r * D + 8 * swz<KCH>(r, pc));
-    }
-#pragma unroll
-    for (int i = 0; i < (ONE_OFF ? 1 : VLD); ++i) {
-        const int slot = 64 * (wave * VLD + i) + lane, r = slot / 8, pc = slot % 8;
-        v_ld[i] = 2u * ((uint32_t)r * (uint32_t)Lkp + 8u * (uint32_t)swz<8>(r, pc));
-    }
-    const half_t* k_head = Kh + (size_t)bhkv * Lkp * D;      // [key][d]
-    const half_t* v_head = Vt + (size_t)bhkv * D * Lkp;      // [d][key]
+    const half_t* k_head = Kh + (size_t)bhkv * Lkp * D;      // tiles of 64 keys, 64 D values each
+    const half_t* v_head = Vt + (size_t)bhkv * D * Lkp;
     const unsigned char* k_recs = reinterpret_cast<const unsigned char*>(Kh) + (size_t)bhkv * (Lkp / 64) * KREC;
     auto issue_k = [&](int buf, int jt) __attribute__((always_inline)) {
         if constexpr (MXS) {      // a record is KREC / 1024 wave copies of 1 KiB
@@ -129,38 +119,27 @@ __device__ __forceinline__ void fwd_body(
                 if (ch < KREC / 1024)
                     async_copy16(k_recs + (size_t)jt * KREC, (uint32_t)(ch * 1024 + lane * 16), reinterpret_cast<unsigned char*>(&sm.k[buf][0]) + ch * 1024);
             }
-        } else if constexpr (ONE_OFF) {
-            // the next 1 KiB of the tile is 4 (D = 128) or 8 (D = 64) rows further: swizzle key bits 0-1 or bit 2 of the chunk
-            uint32_t off0 = k_ld[0];
-            asm volatile("" : "+v"(off0));
-#pragma unroll
-            for (int i = 0; i < KLD; ++i)
-                async_copy16(k_head + (size_t)jt * (64 * D) + i * 512, off0 ^ (uint32_t)(KCH == 16 ? (i << 4) : ((i & 1) << 6)), &sm.k[buf][512 * (wave * KLD + i)]);
         } else {
 #pragma unroll
-            for (int i = 0; i < KLD; ++i) async_copy16(k_head + (size_t)jt * (64 * D), k_ld[i], &sm.k[buf][512 * (wave * KLD + i)]);
+            for (int i = 0; i < KLD; ++i)
+                async_copy16(k_head + (size_t)jt * (64 * D) + 512 * (wave * KLD + i), 16u * (uint32_t)lane, &sm.k[buf][512 * (wave * KLD + i)]);
         }
     };
     auto issue_v = [&](int buf, int jt) __attribute__((always_inline)) {
-        if constexpr (ONE_OFF) {
-            uint32_t off0 = v_ld[0];
-            asm volatile("" : "+v"(off0));
 #pragma unroll
-            for (int i = 0; i < VLD; ++i)
-                async_copy16(v_head + (size_t)jt * 64 + (size_t)(8 * i) * Lkp, off0 ^ (uint32_t)((i & 1) << 6), &sm.v[buf][512 * (wave * VLD + i)]);
-            return;
-        }
-#pragma unroll
-        for (int i = 0; i < VLD; ++i) async_copy16(v_head + (size_t)jt * 64, v_ld[i], &sm.v[buf][512 * (wave * VLD + i)]);
+        for (int i = 0; i < VLD; ++i)
+            async_copy16(v_head + (size_t)jt * (64 * D) + 512 * (wave * VLD + i), 16u * (uint32_t)lane, &sm.v[buf][512 * (wave * VLD + i)]);
     };
 
     const int qt = CAUSAL ? (item == 0 ? nqt - 1 - qt0 : qt0) : qt0;      // (four waves: item is 0)
-    const int row0_w = qt * QT + wave * 32;
+    const int row0_w = qt * QT + (SPLIT ? 0 : wave * 32);
     const bool has_rows = !PHASES || row0_w < Lp;        // false only in the last tile of a head (Lp is a multiple of 128)
     const int q_row = row0_w + ln;
 
     // Q^F operand: this lane's query row, d-slots 16*ds + 8*hf .. +7
-    half8 qreg[MXS ? 1 : DS];
+    // (Q_LDS, the split training kernel at d = 128: it has no registers for them)
+    constexpr bool Q_LDS = SPLIT && TRAIN && D == 128 && !MXS;
+    half8 qreg[MXS || Q_LDS ? 1 : DS];
     uint4v qop[MXS ? KSM : 1];
     uint32_t qs = 0u;
     if constexpr (MXS) {
@@ -169,7 +148,7 @@ __device__ __forceinline__ void fwd_body(
 #pragma unroll
         for (int ks = 0; ks < KSM; ++ks) qop[ks] = *reinterpret_cast<const uint4v*>(qo + ((grp * KSM + ks) * 64 + lane) * 16);
         qs = Qsc[grp * 64 + lane];
-    } else {
+    } else if constexpr (!Q_LDS) {
         const half_t* qp = Qh + ((size_t)bh * Lp + (has_rows ? q_row : 0)) * D + 8 * hf;
 #pragma unroll
         for (int ds = 0; ds < DS; ++ds) qreg[ds] = *reinterpret_cast<const half8*>(qp + 16 * ds);
@@ -177,11 +156,11 @@ __device__ __forceinline__ void fwd_body(
     const int nkt = CAUSAL ? min((qt * QT + QT - 1 + off) / 64 + 1, nkt_all) : nkt_all;     // key tiles this item visits
     const int wave_qmax = row0_w + 31 + off;             // the last key that a row of this wave sees
 
-    floatx16 o[MB], op[TRAIN ? MB : 1];
+    floatx16 o[OB], op[TRAIN && BOTH ? OB : 1];
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
+    for (int mb = 0; mb < OB; ++mb) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) { o[mb][i] = 0.0f; if constexpr (TRAIN) op[mb][i] = 0.0f; }
+        for (int i = 0; i < 16; ++i) { o[mb][i] = 0.0f; if constexpr (TRAIN && BOTH) op[mb][i] = 0.0f; }
     }
     float m = -INFINITY, lsum = 0.0f;     // lsum: this half-wave's part of l (same alpha in both halves)
     float s1_prev = 1.0f, s1_cur = 1.0f;  // two-level P-tilde: the row factor O is currently expressed in, and this tile's
@@ -216,13 +195,8 @@ __device__ __forceinline__ void fwd_body(
             mfma_scale_settle(s[0], s[1]);
             return;
         }
-        // per-lane offset of this tile, opaque to the compiler: it would otherwise hoist every
-        // (offset ^ constant) out of the loop and pay for it with registers
-        int k_it = k_rd + buf * (int)sizeof(sm.k[0]) + (int)lds_addr_of(kbase);
-        asm volatile("" : "+v"(k_it));
-        auto k_opnd = [&](int i) __attribute__((always_inline)) -> half8 {
-            return __builtin_bit_cast(half8, lds_read16_at((uint32_t)((k_it ^ ((i >> 1) << 5)) + (i & 1) * (32 * D * 2))));
-        };
+        const uint32_t k_it = 16u * (uint32_t)lane + (uint32_t)(buf * (int)sizeof(sm.k[0])) + lds_addr_of(kbase);
+        auto k_opnd = [&](int i) __attribute__((always_inline)) -> half8 { return __builtin_bit_cast(half8, lds_read16_at(k_it + 1024u * i)); };
         constexpr int NS = 2 * DS, RING = 6;
         half8 ring[RING];
 #pragma unroll
@@ -245,25 +219,62 @@ __device__ __forceinline__ void fwd_body(
         }
     };
 
+    // ---- SPLIT: LDS holds P-tilde^F and (training) P-tilde of the four tiles as operands of the P V products, 4 KiB each; then per
+    // tile the row maxima, alpha, and l's terms.
+    constexpr int PT = KS * 4096;                       // bytes of one kind of P
+    const uint32_t p_lds = lds_addr_of(smem_raw);
+    float* x_max = reinterpret_cast<float*>(smem_raw + (TRAIN ? 2 : 1) * PT);      // [KS][32]
+    float* x_alpha = x_max + KS * 32;                   // [KS][32]
+    float* x_sum = x_alpha + KS * 32;                   // [KS][64]
+    const uint32_t q_lds = lds_addr_of(x_sum + KS * 64) + 16u * (uint32_t)lane;      // Q_LDS: [d / 16] operands of 1 KiB
+    float m_next = 0.0f;                                // the running maximum after the four tiles
+    int nt = 0;                                         // how many of them there are for these rows
+    // K operands of this wave's next tile and V^T operands of its blocks of O for the next four tiles: straight to registers, no
+    // other wave reads them
+    half8 kr[SPLIT && !MXS ? 2 * DS : 1], vr[SPLIT ? KS : 1][4][OB];
+    uint4v kr_mx[SPLIT && MXS ? 2 * KSM : 1];
+    uint32_t ksc_mx = 0u;
+    auto load_k = [&](int jt) __attribute__((always_inline)) {
+        if constexpr (MXS) {
+            const unsigned char* rec = k_recs + (size_t)jt * KREC;
+#pragma unroll
+            for (int i = 0; i < 2 * KSM; ++i) kr_mx[i] = *reinterpret_cast<const uint4v*>(rec + 1024 * i + 16 * lane);
+            ksc_mx = *reinterpret_cast<const uint32_t*>(rec + 2 * KSM * 1024 + 4 * lane);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 2 * DS; ++i) kr[i] = *reinterpret_cast<const half8*>(k_head + (size_t)jt * (64 * D) + 512 * i + 8 * lane);
+        }
+    };
     // ---- prologue: K(0), V(0), K(1) land, then every wave computes its S of tile 0
-    issue_k(0, 0);
-    issue_v(0, 0);
-    if (nkt > 1) issue_k(1, 1);
+    if constexpr (!SPLIT) {
+        issue_k(0, 0);
+        issue_v(0, 0);
+        if (nkt > 1) issue_k(1, 1);
+    }
     // The Q registers must have arrived BEFORE the loop: a load still pending at loop entry makes the
     // compiler wait for all vector-memory traffic at the first product of every iteration.
     if constexpr (MXS) {
 #pragma unroll
         for (int ks = 0; ks < KSM; ++ks) asm volatile("" : "+v"(qop[ks]));
         asm volatile("" : "+v"(qs));
+    } else if constexpr (Q_LDS) {
+#pragma unroll
+        for (int i = 0; i < DS / NW; ++i) {
+            const int ds = wave * (DS / NW) + i;
+            lds_write16_at(q_lds + 1024u * ds, *reinterpret_cast<const uint4v*>(Qh + ((size_t)bh * Lp + q_row) * D + 8 * hf + 16 * ds));
+        }
+        __syncthreads();
     } else {
 #pragma unroll
         for (int ds = 0; ds < DS; ++ds) asm volatile("" : "+v"(qreg[ds]));
     }
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    if (has_rows) scores(0);
+    if constexpr (!SPLIT) {
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        if (has_rows) scores(0);
+    }
     if (late) __builtin_amdgcn_s_barrier();              // one phase behind from here on
-    if constexpr (!PHASES) {
+    if constexpr (!PHASES && !SPLIT) {
         // everyone is past the scores of tile 0: K(2) may take its buffer.  The barrier alone orders nothing: up to six LDS reads of
         // the products behind it were still on their way, and another wave's copy of K(2) could have overtaken them.
         __builtin_amdgcn_sched_barrier(0);
@@ -280,6 +291,13 @@ __device__ __forceinline__ void fwd_body(
     // runs at raised priority against a pure vector stream and that a tile copy serves 256 rows.)
     // Tile traffic: K(j+2) and V(j+1) are requested at the start of matrix phase j into the buffers
     // whose last readers (matrix phase j-1 of either group) are two barriers back.
+    // SPLIT: what this wave has written to LDS is there, what it has read has arrived, and the other waves have got here too
+    auto lds_barrier = [&]() __attribute__((always_inline)) {
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0xC07F);              // lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+    };
     // ---- vector phase of one key tile: mask, online softmax, block scales of phi(P-tilde)  (no MFMA, no LDS)
     auto vector_phase = [&](int j, float (&bsc)[4], float (&binv)[4]) __attribute__((always_inline)) {
         const int k0 = j * 64;
@@ -321,6 +339,20 @@ __device__ __forceinline__ void fwd_body(
             for (int ks = 0; ks < 4; ++ks) gmax[ks] = xhalf_max(gmax[ks]);
             mt = max_nc(max_nc(gmax[0], gmax[1]), max_nc(gmax[2], gmax[3]));
         }
+        if constexpr (SPLIT) {
+            // the tile's row maxima to the waves that have the other tiles; the running maximum before this tile from theirs
+            if (hf == 0) x_max[wave * 32 + ln] = mt;
+            lds_barrier();
+            float xm[KS];
+#pragma unroll
+            for (int t = 0; t < KS; ++t) xm[t] = x_max[t * 32 + ln];
+            m_next = m;
+#pragma unroll
+            for (int t = 0; t < KS; ++t) {
+                if (t < wave) m = max_nc(m, xm[t]);
+                if (t < nt) m_next = max_nc(m_next, xm[t]);
+            }
+        }
         const float mnew = max_nc(m, mt);
         const float alpha = __builtin_amdgcn_exp2f((m - mnew) * c);
         const float ms = mnew * c;
@@ -334,13 +366,19 @@ __device__ __forceinline__ void fwd_body(
                 if (kb == 0 && i < 4) rp[i] = s[kb][i];
                 else                  rp[i & 3] += s[kb][i];
             }
+        if constexpr (SPLIT) {
+            x_sum[wave * 64 + lane] = (rp[0] + rp[1]) + (rp[2] + rp[3]);
+            if (hf == 0) x_alpha[wave * 32 + ln] = alpha;
+        } else
         lsum = lsum * alpha + ((rp[0] + rp[1]) + (rp[2] + rp[3]));          // un-quantized P-tilde
         // (pinned: the compiler otherwise sinks the additions to the end of the tile and keeps P-tilde alive beside the next S)
-        if constexpr (!PHASES) asm volatile("" : "+v"(lsum));
+        if constexpr (!PHASES && !SPLIT) asm volatile("" : "+v"(lsum));
         // rescale: exact no-op unless some row of this wave moved its maximum (rare after the
         // first tiles), so it lives on the cold path
         float inv1 = 1.0f;
-        if constexpr (PQ == 2) {
+        if constexpr (SPLIT) {
+            // (O and O' are rescaled by the waves that hold them)
+        } else if constexpr (PQ == 2) {
             // Two-level quantization of P-tilde (Sec. 2.1): the row of this tile is divided by s1, the smallest power
             // of two with 2688 s1 >= max(row maximum, 2^-24), before the NVFP4 blocks.  The row maximum is exp2 of the
             // tile's largest score, the same instructions on the same inputs as that element's P-tilde.
@@ -419,8 +457,7 @@ __device__ __forceinline__ void fwd_body(
         (void)k0;
         // per 16 keys: phi^-1(phi(P-tilde)), then O^T += V^F^T P-tilde^F^T and O'^T += V^F^T P-tilde^T
         // (an LDS address as an integer: pointer arithmetic on the dynamic LDS symbol costs an add per read)
-        int v_it = v_rd + (j & 1) * (int)sizeof(sm.v[0]) + (int)lds_addr_of(vbase);
-        asm volatile("" : "+v"(v_it));
+        const uint32_t v_it = 16u * (uint32_t)lane + (uint32_t)((j & 1) * (int)sizeof(sm.v[0])) + lds_addr_of(vbase);
         struct QState { uint32_t c01, c23; };
         float pfv[DUMP ? 8 : 1];
         // the FP4 round trip of one group of 16 keys, cut into four parts of a few instructions
@@ -487,12 +524,26 @@ __device__ __forceinline__ void fwd_body(
         // vector ALU idle while the MFMAs queue up.  So the parts of step ks+1 follow the products of
         // step ks one by one (scheduling fences keep the compiler from regrouping them); a V^T operand
         // register is reloaded for step ks+1 as soon as its last product of step ks has issued.
+        if constexpr (SPLIT) {
+            // the whole tile as operands of the P V products, to the waves that have the blocks of O
+            const uint32_t dst = p_lds + (uint32_t)(wave * 4096 + 16 * lane);
+            QState st;
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                uint4v bq, bu;
+#pragma unroll
+                for (int part = 0; part < 4; ++part) q_part(ks, part, st, bq, bu);
+                lds_write16_at(dst + 1024u * ks, bq);
+                if constexpr (TRAIN) lds_write16_at(dst + PT + 1024u * ks, bu);
+            }
+            return;
+        }
         half8 av[MB];
         uint4v bq[2], bu[2];
         QState st;
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
-            av[mb] = __builtin_bit_cast(half8, lds_read16_at((uint32_t)(v_it + mb * (32 * 64 * 2))));
+            av[mb] = __builtin_bit_cast(half8, lds_read16_at(v_it + 1024u * mb));
 #pragma unroll
         for (int part = 0; part < 4; ++part) q_part(0, part, st, bq[0], bu[0]);
 #pragma unroll
@@ -514,7 +565,7 @@ __device__ __forceinline__ void fwd_body(
                 if (ks < 3) {
 #pragma unroll
                     for (int part = (4 * mb) / MB; part < (4 * (mb + 1)) / MB; ++part) q_part(ks + 1, part, st, bq[nxt], bu[nxt]);
-                    av[mb] = __builtin_bit_cast(half8, lds_read16_at((uint32_t)((v_it ^ ((ks + 1) << 5)) + mb * (32 * 64 * 2))));
+                    av[mb] = __builtin_bit_cast(half8, lds_read16_at(v_it + 1024u * ((ks + 1) * MB + mb)));
                 }
             }
         }
@@ -530,7 +581,131 @@ __device__ __forceinline__ void fwd_body(
     // starts at the workgroup's first row included; rows inside it are masked in the vector phase), and only the last
     // three have waves that skip.  The two kinds of tile get loops of their own: the form with the skipping branch
     // schedules markedly worse (17 % slower on tiles where nobody skips), so it only runs where somebody does.
-    if constexpr (PHASES) {
+    // which blocks of O (and O') this wave has: OB of them from ob0 on; fewer blocks than waves: one block of O, or of O', or none
+    const int ob0 = !SPLIT ? 0 : BOTH ? wave * OB : wave % MB;
+    const bool second = !BOTH && wave >= MB, has_o = BOTH || wave < (TRAIN ? 2 : 1) * MB;
+    if constexpr (SPLIT) {
+        const half_t* v_lane = v_head + 512 * ob0 + 8 * lane;
+        const uint32_t p_src = p_lds + 16u * (uint32_t)lane + (TRAIN && second ? (uint32_t)PT : 0u);
+        // V^T operand of this wave's block ob, keys 16 ks .. of tile t of the four from j0 on (beyond the last tile: the last one again,
+        // not used)
+        auto v_opnd = [&](int j0, int t, int ks, int ob) __attribute__((always_inline)) -> half8 {
+            return *reinterpret_cast<const half8*>(v_lane + (size_t)min(j0 + t, nkt - 1) * (64 * D) + 512 * (ks * MB + ob));
+        };
+        // Four key tiles.  MORE: not the last ones; an operand register is reloaded for the next four right behind its last product
+        // (asked for all at once, the 16 KiB of each wave held it up for the time they take to get through the compute unit's
+        // cache at 64 bytes per clock).
+        auto four_tiles = [&](auto more, int j0) __attribute__((always_inline)) {
+            constexpr bool MORE = decltype(more)::value;
+            const int j = j0 + wave, k_next = min(j + KS, nkt - 1);
+            const bool active = MORE || j < nkt;
+            nt = MORE ? KS : nkt - j0;
+            if (active) {
+                if constexpr (MXS) {
+                    auto as8 = [](const uint4v& x) __attribute__((always_inline)) -> int8v {
+                        int8v r = {(int)x[0], (int)x[1], (int)x[2], (int)x[3], 0, 0, 0, 0};
+                        return r;
+                    };
+                    const floatx16 zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+                    s[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr_mx[0]), as8(qop[0]), zero, 4, 4, 0, ksc_mx, 0, qs);
+                    s[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr_mx[KSM]), as8(qop[0]), zero, 4, 4, KSM, ksc_mx, 0, qs);
+                    if constexpr (KSM == 2) {
+                        s[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr_mx[1]), as8(qop[1]), s[0], 4, 4, 1, ksc_mx, 1, qs);
+                        s[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr_mx[3]), as8(qop[1]), s[1], 4, 4, 3, ksc_mx, 1, qs);
+                    }
+                    mfma_scale_settle(s[0], s[1]);
+                    if constexpr (MORE) load_k(k_next);
+                } else {
+#pragma unroll
+                    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) s[kb][i] = 0.0f;
+                    constexpr int RQ = 4;
+                    half8 qr[Q_LDS ? RQ : 1];
+                    auto q_opnd = [&](int ds) __attribute__((always_inline)) { return __builtin_bit_cast(half8, lds_read16_at(q_lds + 1024u * ds)); };
+                    if constexpr (Q_LDS) {
+#pragma unroll
+                        for (int ds = 0; ds < RQ; ++ds) qr[ds] = q_opnd(ds);
+                    }
+#pragma unroll
+                    for (int i = 0; i < 2 * DS; ++i) {
+                        const int ds = i >> 1;
+                        s[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kr[i], Q_LDS ? qr[Q_LDS ? ds % RQ : 0] : qreg[Q_LDS ? 0 : ds], s[i & 1], 0, 0, 0);
+                        if constexpr (Q_LDS) { if ((i & 1) && ds + RQ < DS) qr[ds % RQ] = q_opnd(ds + RQ); }
+                        if constexpr (MORE) kr[i] = *reinterpret_cast<const half8*>(k_head + (size_t)k_next * (64 * D) + 512 * i + 8 * lane);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+                float bsc[4], binv[4];
+                vector_phase(j, bsc, binv);
+                matrix_phase(j, bsc, binv);
+            } else {
+                lds_barrier();
+                m_next = m;
+#pragma unroll
+                for (int t = 0; t < KS; ++t) if (t < nt) m_next = max_nc(m_next, x_max[t * 32 + ln]);
+            }
+            m = m_next;
+            lds_barrier();                               // P, alpha and the sums are in LDS
+            float al[KS], sm_[KS];
+#pragma unroll
+            for (int t = 0; t < KS; ++t) { al[t] = x_alpha[t * 32 + ln]; sm_[t] = x_sum[t * 64 + lane]; }
+            // operands are read R steps of 16 keys ahead of their products
+            constexpr int R = 4;
+            uint4v rq[R], ru[TRAIN && BOTH ? R : 1];
+            auto fetch = [&](int i) __attribute__((always_inline)) {
+                rq[i % R] = lds_read16_at(p_src + 1024u * i);
+                if constexpr (TRAIN && BOTH) ru[i % R] = lds_read16_at(p_src + (uint32_t)PT + 1024u * i);
+            };
+            if (has_o) {
+#pragma unroll
+                for (int i = 0; i < R; ++i) fetch(i);
+            }
+#pragma unroll
+            for (int t = 0; t < KS; ++t) {
+                if (MORE || t < nt) {
+                    const float alpha = al[t];
+                    lsum = lsum * alpha + sm_[t];        // l in tile order
+                    if (has_o) {
+                        if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
+#pragma unroll
+                            for (int ob = 0; ob < OB; ++ob)
+#pragma unroll
+                                for (int i = 0; i < 16; ++i) { o[ob][i] *= alpha; if constexpr (TRAIN && BOTH) op[ob][i] *= alpha; }
+                        }
+#pragma unroll
+                        for (int ks = 0; ks < 4; ++ks) {
+                            const int i = 4 * t + ks;
+                            const half8 pf = __builtin_bit_cast(half8, rq[i % R]), pu = __builtin_bit_cast(half8, ru[TRAIN && BOTH ? i % R : 0]);
+#pragma unroll
+                            for (int ob = 0; ob < OB; ++ob) {
+                                if constexpr (PQ == 3)
+                                    o[ob] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vr[t][ks][ob]), __builtin_bit_cast(bf16x8, pf), o[ob], 0, 0, 0);
+                                else
+                                    o[ob] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vr[t][ks][ob], pf, o[ob], 0, 0, 0);
+                                if constexpr (TRAIN && BOTH) op[ob] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vr[t][ks][ob], pu, op[ob], 0, 0, 0);
+                                if constexpr (MORE) vr[t][ks][ob] = v_opnd(j0 + KS, t, ks, ob);
+                            }
+                            if (i + R < 4 * KS) fetch(i + R);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    }
+                }
+            }
+        };
+        load_k(min(wave, nkt - 1));
+        if (has_o) {
+#pragma unroll
+            for (int t = 0; t < KS; ++t)
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                    for (int ob = 0; ob < OB; ++ob) vr[t][ks][ob] = v_opnd(0, t, ks, ob);
+        }
+        int j0 = 0;
+        for (; j0 + KS < nkt; j0 += KS) four_tiles(std::true_type{}, j0);
+        four_tiles(std::false_type{}, j0);
+    } else if constexpr (PHASES) {
     const int j_all = CAUSAL ? min(nkt, (qt * QT + 31 + off) / 64 + 1) : nkt;
     for (int j = 0; j < j_all; ++j) {
         const int k0 = j * 64;
@@ -601,25 +776,28 @@ __device__ __forceinline__ void fwd_body(
     const float l = xhalf_sum(lsum);
     const float inv_l = 1.0f / l;
     const float inv_lo = PQ == 2 ? s1_prev * inv_l : inv_l;      // O leaves the units of the last row factor
-    if (q_row < L) {
+    if (q_row < L && has_o) {
         const size_t row = (size_t)bh * L + q_row;
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+        for (int mb = 0; mb < OB; ++mb)
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
-                const int d0 = 32 * mb + 8 * t + 4 * hf;
-                uint2v w;
-                w[0] = pack_bf16x2_rne(o[mb][4 * t] * inv_lo, o[mb][4 * t + 1] * inv_lo);
-                w[1] = pack_bf16x2_rne(o[mb][4 * t + 2] * inv_lo, o[mb][4 * t + 3] * inv_lo);
-                *reinterpret_cast<uint2v*>(O + row * D + d0) = w;
-                if constexpr (TRAIN) {
+                const int d0 = 32 * (ob0 + mb) + 8 * t + 4 * hf;
+                if (!second) {
+                    uint2v w;
+                    w[0] = pack_bf16x2_rne(o[mb][4 * t] * inv_lo, o[mb][4 * t + 1] * inv_lo);
+                    w[1] = pack_bf16x2_rne(o[mb][4 * t + 2] * inv_lo, o[mb][4 * t + 3] * inv_lo);
+                    *reinterpret_cast<uint2v*>(O + row * D + d0) = w;
+                }
+                if (TRAIN && (BOTH || second)) {
+                    const floatx16& acc = BOTH ? op[BOTH && TRAIN ? mb : 0] : o[mb];
                     floatx4 f;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) f[e] = op[mb][4 * t + e] * inv_l;
+                    for (int e = 0; e < 4; ++e) f[e] = acc[4 * t + e] * inv_l;
                     *reinterpret_cast<floatx4*>(Ohp + row * D + d0) = f;
                 }
             }
-        if (hf == 0) lse[row] = m * (c * 0.6931471805599453f) + logf(l);   // m is in raw q.k units
+        if (hf == 0 && (!SPLIT || wave == 0)) lse[row] = m * (c * 0.6931471805599453f) + logf(l);   // m is in raw q.k units
     }
     // (a second item may overwrite the tile buffers at once: every wave's last read of them lies before a barrier that
     //  all eight waves have passed by now)
@@ -640,6 +818,24 @@ template <int D, bool TRAIN, bool CAUSAL, int PQ, bool VARLEN = false>
 __global__ __launch_bounds__(256, 2) void fwd_narrow_kernel(AQ_FWD_ARGS)
 {
     fwd_body<D, TRAIN, CAUSAL, false, PQ, VARLEN, 4>(Qh, Kh, Vt, O, lse, Ohp, L, Lp, Hq, G, c, dump_row0, pdump, Lkp, kv_lens, Qsc, B);
+}
+// Alg. 1 / Alg. 2 where there are too few query rows to fill the chip: a workgroup owns 32 rows, and its four waves take four key
+// tiles at a time, wave w tile 4 n + w for S, the softmax and phi(P-tilde), and block w of O (and O') for the P V products of all four.
+// What bounds a problem of this size is not a rate but the chain of one wave: 13 tiles in sequence at 1.6 us (infer) or 2.1 us
+// (train), half of it waiting, while the other SIMDs idle.  Here a chain is a quarter as long, and its steps shorter: O's rescaling and
+// its registers are shared out too.  Nothing of Alg. 1 changes: the running maximum before a tile is the largest of the tiles' row
+// maxima, exchanged through LDS between the scores and the softmax, so every P-tilde^F has the bits it has in sequence; P goes
+// through LDS as operands of the products (4 KiB per tile); each element of O is added up by one wave in tile order and l from
+// the tiles' sums in tile order: all results have the bits of fwd_kernel.
+// K and V^T operands go straight to registers: each is read by one wave only (a version with 64 rows per workgroup and tiles in
+// LDS spent its time on the LDS ports: 8700 cycles per four tiles and 64 rows, this one 3600 where two workgroups share a compute unit).
+// Two barriers per four tiles.  Two workgroups per compute unit.  Measured, four-wave tiles of 128 rows -> this, with the preparing launch:
+// d = 128, training: 2 heads, L = 1000 40.3 -> 19.6 us; 8 heads, L = 2000 75.6 -> 48.9 us; 12 heads, L = 2300 causal 84 -> 53 us;
+// inference, 32 heads, L = 777 causal 32.8 -> 28.8 us; d = 64, training: 2 heads, L = 256 13.2 -> 10.3 us.
+template <int D, bool TRAIN, bool CAUSAL, int PQ, bool VARLEN = false>
+__global__ __launch_bounds__(256, 2) void fwd_split_kernel(AQ_FWD_ARGS)
+{
+    fwd_body<D, TRAIN, CAUSAL, false, PQ, VARLEN, 4, true>(Qh, Kh, Vt, O, lse, Ohp, L, Lp, Hq, G, c, dump_row0, pdump, Lkp, kv_lens, Qsc, B);
 }
 #undef AQ_FWD_ARGS
 
@@ -665,6 +861,21 @@ static bool narrow_workgroups(int heads, int Lp, int D, bool causal)
     return n4 / (2 * cus) * 102 + (rest == 0 ? 0 : rest <= cus ? 80 : 102) < rounds8 * 100;
 }
 
+// Whether the key tiles are shared (fwd_split_kernel), for heads x n32 groups of 32 rows.  All rows of the same length (no mask, or chunks
+// of sequences that are mostly longer than they): two such workgroups share a compute unit, a round of 2 per unit costs 40 where narrow_workgroups
+// counts 102 for its own, one more per unit 23, against 80 for the 128-row tiles that leave units idle: up to three per unit.  Measured (training,
+// d = 128): 588 groups 61.7 -> 55.7 us, 752 groups 103.6 -> 87.6 us; 800 groups 46.4 -> 46.6 us, 864 groups (inference) 69.6 -> 71.5 us.
+// Causal: the 128-row tiles wait for their longest chain, these only for a quarter of it: six per unit (24 heads, L = 2000, 1512 groups
+// 82.9 -> 72.4 us; L = 2700, 2040 groups 110 -> 114 us), fewer for short rows, where the start of a workgroup is most of it (64 heads,
+// L = 500, 1024 groups, inference 29.1 -> 29.8 us; 160 heads, L = 200, 1120 groups 27.8 -> 30.9 us; 64 heads, L = 256, 512 groups 20.9 -> 18.1 us).
+static bool split_key_tiles(int heads, int n32, bool causal)
+{
+    const long long cus = device_cu_count(), n = (long long)heads * n32;
+    return n <= cus * (causal ? min(6, 2 + n32 / 8) : 3);
+}
+// (P-tilde^F, and P-tilde, of four tiles; row maxima, alpha and two parts of l; Q where it has no registers)
+static size_t split_lds_bytes(int D, bool train, int pq) { return (size_t)(train ? 2 : 1) * 4 * 4096 + 4 * 128 * 4 + (train && D == 128 && pq != 1 ? 8192 : 0); }
+
 template <int D, bool TRAIN, bool CAUSAL, bool DUMP, int PQ, bool VARLEN = false>
 static int launch_t(const void* qh, const void* kh, const void* vt, int B, int Hq, int Hkv, int L,
                     void* o, float* lse, float* o_hp, int dump_row0, float* p_dump, hipStream_t st,
@@ -676,22 +887,30 @@ static int launch_t(const void* qh, const void* kh, const void* vt, int B, int H
     const int per_head = CAUSAL ? (nqt + 1) / 2 : nqt;         // under a causal mask a workgroup takes a long and a short tile
     const size_t smem = sizeof(FwdSmem<D>);
     const float c = 1.4426950408889634f / sqrtf((float)D);
-    auto go = [&](auto kern, unsigned grid, unsigned block, unsigned long long& lds_set) -> int {
+    auto go = [&](auto kern, unsigned grid, unsigned block, size_t smem, unsigned long long& lds_set) -> int {
         if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)smem, lds_set)) return -1;
         hipLaunchKernelGGL(kern, dim3(grid), dim3(block), smem, st,
                            (const half_t*)qh, (const half_t*)kh, (const half_t*)vt, (uint16_t*)o, lse, o_hp,
                            L, Lp, Hq, Hq / Hkv, c, dump_row0, p_dump, Lkp, kv_lens, (const uint32_t*)qsc, B);
         return hipGetLastError() == hipSuccess ? 0 : -1;
     };
+    if constexpr (!DUMP && PQ != 2) {
+        static unsigned long long lds_set_split = 0;       // one per instantiation
+        const int n32 = (L + 31) / 32;
+        if (split_key_tiles(B * Hq, n32, CAUSAL && !VARLEN)) {
+            const int groups = VARLEN ? round_up(B * Hkv, 8) : B * Hkv;       // (see varlen_item)
+            return go(fwd_split_kernel<D, TRAIN, CAUSAL, PQ, VARLEN>, (unsigned)(groups * (Hq / Hkv) * n32), 256, split_lds_bytes(D, TRAIN, PQ), lds_set_split);
+        }
+    }
     if constexpr (!DUMP) {
         static unsigned long long lds_set_narrow = 0;      // one per instantiation
         if (narrow_workgroups(B * Hq, Lp, D, CAUSAL)) {
             const int groups = VARLEN ? round_up(B * Hkv, 8) : B * Hkv;       // (see varlen_item)
-            return go(fwd_narrow_kernel<D, TRAIN, CAUSAL, PQ, VARLEN>, (unsigned)(groups * (Hq / Hkv) * (Lp / 128)), 256, lds_set_narrow);
+            return go(fwd_narrow_kernel<D, TRAIN, CAUSAL, PQ, VARLEN>, (unsigned)(groups * (Hq / Hkv) * (Lp / 128)), 256, smem, lds_set_narrow);
         }
     }
     static unsigned long long lds_set = 0;          // one per instantiation
-    return go(fwd_kernel<D, TRAIN, CAUSAL, DUMP, PQ, VARLEN>, (unsigned)(B * Hq * per_head), 512, lds_set);
+    return go(fwd_kernel<D, TRAIN, CAUSAL, DUMP, PQ, VARLEN>, (unsigned)(B * Hq * per_head), 512, smem, lds_set);
 }
 
 template <int D, int PQ>

@@ -108,16 +108,17 @@ __device__ __forceinline__ void mx_v_tile(uint16_t (*tile)[D + 2], const MxGroup
             const uint4v c4 = {c[0], c[1], c[2], c[3]};
             const float s = e8m0_as_f32(byte);
             if constexpr (KIND == MX_TRAIN) {
-                // transposed, the positions of a group of 16 in the order the forward's accumulators have them: quads 1 and 2 exchanged
+                // transposed, in the order of the forward's operands: quads 1 and 2 of a group of 16 positions exchanged
                 uint32_t o[16];
                 mx_dequant32(c4, s, [&](int i, float lo, float hi) { o[i] = pack_f16x2(lo, hi); });
-                uint4v* dst = reinterpret_cast<uint4v*>(g.v_out + ((size_t)bh * D + dd) * Lp + l0 + kb * 32);
+                uint16_t* dst = g.v_out + (size_t)bh * D * Lp;
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     uint4v a, b;
                     a[0] = o[8 * h]; a[1] = o[8 * h + 1]; a[2] = o[8 * h + 4]; a[3] = o[8 * h + 5];
                     b[0] = o[8 * h + 2]; b[1] = o[8 * h + 3]; b[2] = o[8 * h + 6]; b[3] = o[8 * h + 7];
-                    dst[2 * h] = a; dst[2 * h + 1] = b;
+                    *reinterpret_cast<uint4v*>(dst + v_operand_offset((l0 >> 4) + 2 * kb + h, dd, 0, D)) = a;
+                    *reinterpret_cast<uint4v*>(dst + v_operand_offset((l0 >> 4) + 2 * kb + h, dd, 1, D)) = b;
                 }
             } else {
                 mx_dequant32(c4, s, [&](int i, float lo, float hi) {

@@ -5,6 +5,8 @@
 // One thread owns one block of 16 consecutive d-elements (32 bytes in).  A workgroup
 // covers 64 sequence positions; the optional transposed copy goes through LDS so that
 // both the row-major and the transposed stores are 16-byte vectors.
+#include <type_traits>
+
 #include "common.hpp"
 #include "kernels.hpp"
 #include "prep.hpp"
@@ -38,7 +40,8 @@ __device__ inline const unsigned char* nvfp4_page_part(const unsigned char* cach
 // head, position l of sequence b is slot l % 128 of page table[b][l / 128], positions from kv_lens[b] on read as zeros, and
 // L is the capacity max_pages * 128 that the copies are laid out for.
 // NORM: n2 becomes the largest squared norm of the rows seen so far (in the lanes that hold a row's first block).
-template <bool QUANT, bool OUT_F16, bool PACKED, bool PAGED, bool NORM>
+// KOPS: the rows (xr) are written in the order of the forward's K operands.
+template <bool QUANT, bool OUT_F16, bool PACKED, bool PAGED, bool NORM, bool KOPS = false>
 __device__ __forceinline__ void prep_tile(
     uint16_t (*tile)[128 + 2], int bh, int l0, const uint16_t* __restrict__ x, int L, int Lp, int D,
     uint8_t* __restrict__ codes, uint8_t* __restrict__ scales, uint16_t* __restrict__ xf_pub,
@@ -173,12 +176,13 @@ __device__ __forceinline__ void prep_tile(
 #pragma unroll
         for (int i = 0; i < 8; ++i)
             w[i] = OUT_F16 ? pack_f16x2(xf[2 * i], xf[2 * i + 1]) : pack_bf16x2_rne(xf[2 * i], xf[2 * i + 1]);
-        if (xr) {                                        // row-major, rows padded to Lp with zeros
+        if (xr) {                                        // rows padded to Lp with zeros
             uint4v o0, o1;
 #pragma unroll
             for (int i = 0; i < 4; ++i) { o0[i] = w[i]; o1[i] = w[4 + i]; }
-            uint4v* dst = reinterpret_cast<uint4v*>(xr + ((size_t)bh * Lp + l) * D + cb * 16);
-            dst[0] = o0; dst[1] = o1;
+            uint16_t* dst = xr + (size_t)bh * Lp * D + (KOPS ? k_operand_offset(l, cb, 0, D) : (size_t)l * D + cb * 16);
+            *reinterpret_cast<uint4v*>(dst) = o0;
+            *reinterpret_cast<uint4v*>(dst + (KOPS ? 32 * 8 : 8)) = o1;
         }
         if (xt) {
 #pragma unroll
@@ -187,10 +191,10 @@ __device__ __forceinline__ void prep_tile(
     }
     if (xt) {
         __syncthreads();
-        // transposed copy [bh][c][Lp]: 8 positions (16 bytes) per store; a thread takes them of two neighbouring columns, which
-        // lie in one LDS word
+        // transposed copy: 8 positions (16 bytes) per store; a thread takes them of two neighbouring columns, which lie in one LDS
+        // word and whose operands are neighbours in memory
         for (int ch = threadIdx.x; ch < D * 4; ch += 256) {
-            const int c = 2 * (ch >> 3), kc = ch & 7;
+            const int c = 2 * (ch % (D / 2)), kc = ch / (D / 2);
             uint32_t x[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
@@ -203,9 +207,9 @@ __device__ __forceinline__ void prep_tile(
                 lo[j] = __builtin_amdgcn_perm(x[2 * j + 1], x[2 * j], 0x05040100u);
                 hi[j] = __builtin_amdgcn_perm(x[2 * j + 1], x[2 * j], 0x07060302u);
             }
-            uint16_t* dst = xt + ((size_t)bh * D + c) * Lp + l0 + kc * 8;
+            uint16_t* dst = xt + (size_t)bh * Lp * D + v_operand_offset((l0 >> 4) + (kc >> 1), c, kc & 1, D);
             *reinterpret_cast<uint4v*>(dst) = lo;
-            *reinterpret_cast<uint4v*>(dst + Lp) = hi;
+            *reinterpret_cast<uint4v*>(dst + 8) = hi;
         }
     }
 }
@@ -261,16 +265,18 @@ __global__ __launch_bounds__(256) void prep_group_kernel(PrepGroup g, unsigned n
         i -= n_v;
         const bool is_q = i < n_q;
         if (!is_q) i -= n_q;
-        if (SRC == 2 && !is_q) {
+        auto rows = [&](auto k_ops) __attribute__((always_inline)) {      // Q, or a backward's K: rows
+            const int per = is_q ? tiles_q : tiles_kv, w = is_q ? 0 : 1;
+            prep_tile<SRC != 1, true, SRC == 1, false, false, decltype(k_ops)::value>(tile, (int)(i / per), (int)(i % per) * 64, is_q ? g.q : g.k, is_q ? g.L : g.L_kv, is_q ? g.Lp : g.Lp_kv, g.D,
+                const_cast<uint8_t*>(g.codes[w]), const_cast<uint8_t*>(g.scales[w]), nullptr, is_q ? g.q_out : g.k_out, nullptr, is_q ? nullptr : g.k_sub, PagedSrc{}, n2);
+        };
+        if (BWD || is_q) rows(std::false_type{});
+        else if constexpr (SRC == 2) {
             PagedSrc ps = g.ps;
             ps.which = 0;
-            prep_tile<false, true, SRC == 2, SRC == 2, false>(tile, (int)(i / tiles_kv), (int)(i % tiles_kv) * 64, nullptr, g.L_kv, g.Lp_kv, g.D, nullptr, nullptr, nullptr,
+            prep_tile<false, true, true, true, false, true>(tile, (int)(i / tiles_kv), (int)(i % tiles_kv) * 64, nullptr, g.L_kv, g.Lp_kv, g.D, nullptr, nullptr, nullptr,
                 g.k_out, nullptr, nullptr, ps, n2);
-        } else {
-            const int per = is_q ? tiles_q : tiles_kv, w = is_q ? 0 : 1;
-            prep_tile<SRC != 1, true, SRC == 1, false, false>(tile, (int)(i / per), (int)(i % per) * 64, is_q ? g.q : g.k, is_q ? g.L : g.L_kv, is_q ? g.Lp : g.Lp_kv, g.D,
-                const_cast<uint8_t*>(g.codes[w]), const_cast<uint8_t*>(g.scales[w]), nullptr, is_q ? g.q_out : g.k_out, nullptr, is_q ? nullptr : g.k_sub, PagedSrc{}, n2);
-        }
+        } else rows(std::true_type{});
     }
 }
 

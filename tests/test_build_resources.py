@@ -183,3 +183,11 @@ def test_no_lds_read_is_in_flight_at_a_barrier_of_the_forward():
         assert barriers and all(b[0] == 0 for b in barriers), (name, barriers)
         if kind == "fwd_narrow_kernel":
             assert barriers[1][1] == (2 * d // 64 if pq == 1 else 2 * d // 16), (name, barriers)      # (MX: the FP4 instruction)
+
+
+def test_split_forward_kernels_do_not_spill():
+    # fwd_split_kernel<D, TRAIN, CAUSAL, PQ, VARLEN>: the forward of few query rows (no two-level variant)
+    k = _resources("fwd.hip")
+    _check(k, r"fwd_split_kernelILi(64|128)ELb[01]ELb[01]ELi[01]ELb0E", 16)
+    _check(k, r"fwd_split_kernelILi(64|128)ELb0ELb[01]ELi(3ELb0|0ELb1)E", 8)
+    assert len([n for n in k if "fwd_split_kernel" in n]) == 24
