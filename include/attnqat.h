@@ -376,14 +376,15 @@ int attnqat_fwd_infer_mx_paged(const void* q, int B, int Hq, int Hkv, int Lq, in
  *     in the workspace and waits for those of its predecessors, then does the rest (the V half).  Tickets are handed out
  *     in chunk order, so a predecessor is always running or finished when someone waits for it and the wait ends; it is
  *     bounded nevertheless (2^22 polls), and a wait that expired leaves a wrong result for that sequence.  The partial
- *     sums of the chunks of a sequence are added by a third kernel.  The result is not bit-identical to
+ *     sums of the chunks of a sequence are added by a third kernel.  Steps with few keys do without the queue: one kernel
+ *     computes all scores (kept in the workspace), the next does the rest in chunks of 256 keys.  The result is not bit-identical to
  *     attnqat_fwd_infer (the sums are grouped differently) but holds the same parity bars against the oracle.  It is
  *     deterministic; the grouping (the length of the chunks) follows from B, Hkv, the rows, max_pages and the device's compute
  *     units, so a sequence's last bits may differ between steps with other sequences beside it or a wider page table.  A
- *     workspace that lacks only the room for the shortest chunks is accepted and gets longer ones (slower where few
- *     sequences are served); any size from the one asked for on gives the same bits.
+ *     workspace that lacks only the room for the scores or for the shortest chunks is accepted and gets the queue or longer
+ *     chunks (slower where few sequences are served); any size from the one asked for on gives the same bits.
  * attnqat_debug_fwd_infer_paged is the same call with the poll limit as an argument (tests force the expiry path with
- * 0); it synchronizes the stream and sets *wait_expired (host) to 1 if any wait of the decode path ran out.
+ * 0) and always with the queue; it synchronizes the stream and sets *wait_expired (host) to 1 if any wait of the decode path ran out.
  */
 size_t attnqat_kv_cache_page_bytes_nvfp4(int Hkv, int d);
 int attnqat_kv_cache_write(const void* k, const void* v, int Hkv, int n, int d, int dtype, int pos0,

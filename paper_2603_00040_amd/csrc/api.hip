@@ -467,13 +467,19 @@ int attnqat_kv_cache_write(const void* k, const void* v, int Hkv, int n, int d, 
 namespace {
 // Few rows per (sequence, kv head): the decode kernel reads the pages itself (dec != null); otherwise the pages are unpacked
 // into the K / V^T copies of the general forward.
-struct PagedWs { void *qh, *kh, *vt, *dec; size_t bytes; int Lkp, halvings; };
-PagedWs carve_paged(void* ws, size_t given, int cus, int B, int Hq, int Hkv, int Lq, int max_pages, int d)
+struct PagedWs { void *qh, *kh, *vt, *dec; size_t bytes; int Lkp, halvings; bool direct; };
+PagedWs carve_paged(void* ws, size_t given, bool queue /* not the two launches without one */, int cus, int B, int Hq, int Hkv, int Lq, int max_pages, int d)
 {
     Carver c{(unsigned char*)ws, 0};
     PagedWs w{};
     const int R = (Hq / Hkv) * Lq;
     if (R <= decode_max_rows()) {
+        if (!queue && decode_is_direct(B, Hkv, R, max_pages, cus)) {
+            w.dec = c.take(decode_direct_ws_bytes(B, Hkv, R, max_pages, d));
+            w.direct = c.off <= given;
+            if (w.direct) { w.bytes = c.off; return w; }
+            c.off = 0;                                   // (an older, smaller workspace: the queue)
+        }
         w.qh = c.take((size_t)B * Hkv * kRowPad * d * 2);
         // (shorter chunks need more room: a workspace that lacks it gets longer ones)
         w.halvings = decode_halvings(B, Hkv, R, max_pages, cus);
@@ -500,10 +506,15 @@ int paged_common(const void* q, int B, int Hq, int Hkv, int Lq, int d, int causa
     int rc = check_dims(B, Hq, Hkv, Lq, d, dtype);
     if (rc) return rc;
     if (max_pages > (1 << 13) || (long long)B * Hkv > 65535) return ATTNQAT_ESHAPE;          // 2^20 keys per sequence
-    PagedWs w = carve_paged(workspace, workspace_bytes, device_cu_count(), B, Hq, Hkv, Lq, max_pages, d);
+    PagedWs w = carve_paged(workspace, workspace_bytes, dec_ws != nullptr, device_cu_count(), B, Hq, Hkv, Lq, max_pages, d);
     if (!workspace || workspace_bytes < w.bytes) return ATTNQAT_EWORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     prof_begin(st);
+    if (w.direct) {
+        if (launch_decode_direct(q, cache, num_pages, page_table, max_pages, kv_lens, B, Hq, Hkv, Lq, d, causal != 0, w.dec, o, lse, st)) return ATTNQAT_ELAUNCH;
+        prof_mark("decode_paged", st);
+        return ATTNQAT_OK;
+    }
     if (w.dec) {
         if (launch_decode(q, w.qh, cache, num_pages, page_table, max_pages, kv_lens, B, Hq, Hkv, Lq, d, causal != 0, w.dec, w.halvings, spin_limit, o, lse, st))
             return ATTNQAT_ELAUNCH;
@@ -529,7 +540,9 @@ int paged_common(const void* q, int B, int Hq, int Hkv, int Lq, int d, int causa
 size_t attnqat_paged_workspace_bytes(int B, int Hq, int Hkv, int Lq, int max_pages, int d)
 {
     if (check_dims(B, Hq, Hkv, Lq, d, ATTNQAT_BF16) || max_pages < 1 || max_pages > (1 << 13)) return 0;
-    return carve_paged(nullptr, SIZE_MAX, kChipCus, B, Hq, Hkv, Lq, max_pages, d).bytes;
+    const size_t direct = carve_paged(nullptr, SIZE_MAX, false, kChipCus, B, Hq, Hkv, Lq, max_pages, d).bytes;
+    const size_t queue = carve_paged(nullptr, SIZE_MAX, true, kChipCus, B, Hq, Hkv, Lq, max_pages, d).bytes;
+    return direct > queue ? direct : queue;
 }
 
 int attnqat_fwd_infer_paged(const void* q, int B, int Hq, int Hkv, int Lq, int d, int causal, int dtype,

@@ -1,7 +1,7 @@
 // Alg. 1 for decode steps over the NVFP4 KV cache: a (sequence, kv head) has at most 16 query rows (the G query heads of
 // its group times the few newest positions), so the step is bound by reading the cache once, and the work of a launch is
 // as uneven as the sequences are long.  The keys of a sequence are therefore cut into chunks of CK keys that workgroups
-// take from a queue, and three facts keep the result that of Alg. 1 in key-tile order:
+// take from a queue (steps with few chunks do without it, see decode_scores_kernel), and three facts keep the result that of Alg. 1 in key-tile order:
 //   * P-tilde of key tile j is exp(S - m_j) with m_j the running row maximum after tile j, and phi is applied to that.
 //     m_j needs nothing but the scores: a chunk first computes its scores S = Q^F K^F^T (kept in LDS; only the K half of
 //     its pages is read), publishes its row maxima, and takes the maxima of the chunks before it from memory.  With the
@@ -85,6 +85,48 @@ __device__ inline half8 dequant8(const RawKV<D>& r, half2v sc, int s) {
     return __builtin_bit_cast(half8, v);
 }
 
+// phi^-1(phi(P-tilde)) of four keys of a row as fp16; four neighbouring lanes hold a block of 16.
+__device__ inline uint2v phi_p_quad(const float (&pt)[4]) {
+    float amax = fmaxf(fmaxf(pt[0], pt[1]), fmaxf(pt[2], pt[3]));
+    amax = fmaxf(amax, __shfl_xor(amax, 1));
+    amax = fmaxf(amax, __shfl_xor(amax, 2));
+    // RNE_E4M3(amax / 6) by the hardware conversion and back (P-tilde <= 1: no saturation)
+    typedef short short2v __attribute__((ext_vector_type(2)));
+    short2v pk = {0, 0};
+    pk = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(pk, amax * (1.0f / 6.0f), amax * (1.0f / 6.0f), 1.0f, false);
+    const uint32_t pkw = __builtin_bit_cast(uint32_t, pk);
+    const float bsc = __builtin_amdgcn_cvt_scalef32_f32_fp8(pkw, 1.0f, 0);
+    const half2v sc2 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(pkw, 1.0f, false);      // (bsc, bsc)
+    const float inv = fminf(__builtin_amdgcn_rcpf(bsc), 512.0f);      // a scale of 0: P^F is 0 whatever the codes
+    uint32_t codes = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(pkw, pt[0] * inv, pt[1] * inv, 1.0f, 0);
+    codes = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(codes, pt[2] * inv, pt[3] * inv, 1.0f, 1);
+    uint2v w;
+    w[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(codes, 1.0f, 0) * sc2);
+    w[1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(codes, 1.0f, 1) * sc2);
+    return w;
+}
+
+// A block of 16 values of a query row, quantized and back, as fp16 (zeros for a row that does not exist).
+__device__ inline void phi_q_block(const uint16_t* q, bool exists, uint4v (&o)[2]) {
+    float v[16], xf[16], s = 0.0f;
+    uint32_t clo = 0, chi = 0;
+    if (exists) {
+        const uint4v* src = reinterpret_cast<const uint4v*>(q);
+        const uint4v a = src[0], b = src[1];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            v[2 * i]         = __uint_as_float(a[i] << 16);
+            v[2 * i + 1]     = __uint_as_float(a[i] & 0xFFFF0000u);
+            v[8 + 2 * i]     = __uint_as_float(b[i] << 16);
+            v[8 + 2 * i + 1] = __uint_as_float(b[i] & 0xFFFF0000u);
+        }
+        phi_block16_bf16(v, s, clo, chi);
+    }
+    dequant_block16(clo, chi, s, xf);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) o[i >> 2][i & 3] = pack_f16x2(xf[2 * i], xf[2 * i + 1]);
+}
+
 // Before every step, three things that do not depend on each other, by different workgroups of one launch:
 //   * workgroups [0, NC): workgroup ch lists the chunks number ch of all sequences, as items of kDecItemInts ints {sequence, kv head,
 //     chunk, keys of the sequence, the page ids of the chunk's (at most 8) pages, -1 where the sequence has none}.  The list is in
@@ -112,24 +154,8 @@ __global__ __launch_bounds__(256) void decode_prepare_kernel(const int* __restri
         constexpr int nb = D / 16, PER = 256 / (16 * nb);           // blocks of a row, (sequence, kv head)s per workgroup
         const int bh = ((int)blockIdx.x - NC) * PER + tid / (16 * nb), row = tid / nb % 16, cb = tid % nb;
         if (bh >= BH) return;
-        float v[16], xf[16], s = 0.0f;
-        uint32_t clo = 0, chi = 0;
-        if (row < R) {
-            const uint4v* src = reinterpret_cast<const uint4v*>(q + ((size_t)bh * R + row) * D + cb * 16);
-            const uint4v a = src[0], b = src[1];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                v[2 * i]         = __uint_as_float(a[i] << 16);
-                v[2 * i + 1]     = __uint_as_float(a[i] & 0xFFFF0000u);
-                v[8 + 2 * i]     = __uint_as_float(b[i] << 16);
-                v[8 + 2 * i + 1] = __uint_as_float(b[i] & 0xFFFF0000u);
-            }
-            phi_block16_bf16(v, s, clo, chi);
-        }
-        dequant_block16(clo, chi, s, xf);
         uint4v o[2];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) o[i >> 2][i & 3] = pack_f16x2(xf[2 * i], xf[2 * i + 1]);
+        phi_q_block(q + ((size_t)bh * R + row) * D + cb * 16, row < R, o);
         uint4v* dst = reinterpret_cast<uint4v*>(qh + ((size_t)bh * 128 + row) * D + cb * 16);
         dst[0] = o[0]; dst[1] = o[1];
         return;
@@ -427,22 +453,7 @@ __global__ __launch_bounds__(256, 2) void decode_kernel(
                     for (int i = 0; i < 4; ++i) pt[i] = __builtin_amdgcn_exp2f(fmaf(sv[i], c, -ms));
                     lacc[ps] = fmaf(lacc[ps], __builtin_amdgcn_exp2f((mp_prev[ps] - mrow) * c), (pt[0] + pt[1]) + (pt[2] + pt[3]));
                     mp_prev[ps] = mrow;
-                    float amax = fmaxf(fmaxf(pt[0], pt[1]), fmaxf(pt[2], pt[3]));
-                    amax = fmaxf(amax, __shfl_xor(amax, 1));
-                    amax = fmaxf(amax, __shfl_xor(amax, 2));
-                    // RNE_E4M3(amax / 6) by the hardware conversion and back (P-tilde <= 1: no saturation)
-                    typedef short short2v __attribute__((ext_vector_type(2)));
-                    short2v pk = {0, 0};
-                    pk = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(pk, amax * (1.0f / 6.0f), amax * (1.0f / 6.0f), 1.0f, false);
-                    const uint32_t pkw = __builtin_bit_cast(uint32_t, pk);
-                    const float bsc = __builtin_amdgcn_cvt_scalef32_f32_fp8(pkw, 1.0f, 0);
-                    const half2v sc2 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(pkw, 1.0f, false);      // (bsc, bsc)
-                    const float inv = fminf(__builtin_amdgcn_rcpf(bsc), 512.0f);      // a scale of 0: P^F is 0 whatever the codes
-                    uint32_t codes = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(pkw, pt[0] * inv, pt[1] * inv, 1.0f, 0);
-                    codes = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(codes, pt[2] * inv, pt[3] * inv, 1.0f, 1);
-                    uint2v w;
-                    w[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(codes, 1.0f, 0) * sc2);
-                    w[1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(codes, 1.0f, 1) * sc2);
+                    const uint2v w = phi_p_quad(pt);
                     *reinterpret_cast<uint2v*>(pfw + (4 * ps + pq) * PS + 8 * pj) = w;
                 }
             }
@@ -577,6 +588,231 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(
     if (e % D == 0) lse[(size_t)bh * R + r] = M * (c * 0.6931471805599453f) + logf(l);
 }
 
+// ---- Few chunks: two launches without a queue -------------------------------------------------------------------
+// What a small step waits for is its chain of trips to memory, not work: the list, the ticket, the item, K, the maxima of other
+// chunks (17 us of a step for one tile per wave).  Where the chunks of 256 keys (a tile per wave) are few, every chunk has its own
+// workgroup (blockIdx: chunk, (sequence, kv head)), and the end of the first launch is what hands the row maxima over:
+//   decode_scores_kernel: phi(Q), the scores and every tile's row maxima to memory.
+//   decode_values_kernel: the maxima in front of the chunk, softmax, phi(P-tilde), P V, the chunk's sums, which decode_merge_kernel
+//   adds up.  (Adding them in the chunk that finishes last, device-scope atomics instead of a launch: 14.2 us for one sequence of
+//   3000 keys, as with it, but 24 to 30 us with 16 rows of 40 chunks, which one workgroup then adds up alone.)
+// One sequence of 3000 keys, 8 kv heads, 4 rows: 4.1 + 6.3 + 3 us.  The price is the scores' way through memory, 8 bytes per row and key.
+// The arithmetic and its grouping are those of decode_kernel with chunks of 256 keys.
+constexpr int kDirTiles = 4;                     // 64-key tiles per chunk: one per wave
+
+// What a wave of either kernel knows of its tile.
+struct DirTile { int b, h, bh, ch, Lk, nch, NT, k_t; bool live; const unsigned char* src; };
+template <int D>
+__device__ inline DirTile dir_tile(const unsigned char* cache, int num_pages, const int* __restrict__ page_table, const int* __restrict__ kv_lens, int Hkv, int max_pages) {
+    constexpr size_t HB = (size_t)2 * 128 * (D / 2 + D / 16);
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    DirTile x;
+    x.bh = blockIdx.y; x.ch = blockIdx.x; x.b = x.bh / Hkv; x.h = x.bh % Hkv;
+    const int pi = 2 * x.ch + (wave >> 1);
+    int page = page_table[(size_t)x.b * max_pages + min(pi, max_pages - 1)];      // (beside the length, not behind it)
+    x.Lk = max(0, min(kv_lens[x.b], max_pages * 128));
+    x.nch = (x.Lk + 64 * kDirTiles - 1) / (64 * kDirTiles);
+    x.NT = min(kDirTiles, (x.Lk - 64 * kDirTiles * x.ch + 63) / 64);
+    x.k_t = 64 * (kDirTiles * x.ch + wave);
+    x.live = x.k_t < x.Lk && page >= 0 && page < num_pages;                        // (a page outside the cache reads as zeros)
+    x.src = cache + ((size_t)(x.live ? page : 0) * Hkv + x.h) * HB;
+    return x;
+}
+
+template <int D, bool CAUSAL>
+__global__ __launch_bounds__(256) void decode_scores_kernel(
+    const uint16_t* __restrict__ q, const unsigned char* __restrict__ cache, int num_pages, const int* __restrict__ page_table, const int* __restrict__ kv_lens,
+    int Hkv, int Lq, int R, int NC, int max_pages, float* __restrict__ S /* [unit][tile][R][64] */, float* __restrict__ tmax /* [unit][tile][16] */,
+    uint16_t* __restrict__ O, float* __restrict__ lse)
+{
+    constexpr int NS = D / 32, QS = 2 * D + 16;          // bytes per row of phi(Q) (padded: 16 rows are read side by side)
+    __shared__ __align__(16) unsigned char qs[kDecRows * QS];
+    const int tid = threadIdx.x, lane = tid & 63, cc = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const DirTile x = dir_tile<D>(cache, num_pages, page_table, kv_lens, Hkv, max_pages);
+    if (x.ch == 0 && x.Lk < 1) {                         // no keys: O = 0, L = -inf
+        for (int e = tid; e < R * D; e += 256) O[(size_t)x.bh * R * D + e] = 0;
+        if (tid < R) lse[(size_t)x.bh * R + tid] = -INFINITY;
+    }
+    if (x.ch >= x.nch) return;
+    RawKV<D> raw[4];
+    const bool exists = x.k_t < x.Lk;                    // wave-uniform
+    if (exists) {
+#pragma unroll
+        for (int blk = 0; blk < 4; ++blk)
+            raw[blk] = load_raw<D>(x.src, (uint32_t)(cc * (D / 2) + (D / 8) * g) + (uint32_t)(x.k_t & 64) * (D / 2),
+                                   (uint32_t)(128 * (D / 2) + cc * (D / 16) + (D / 64) * g) + (uint32_t)(x.k_t & 64) * (D / 16), blk);
+    }
+    if (tid < kDecRows * (D / 16)) {
+        const int row = tid / (D / 16), cb = tid % (D / 16);
+        uint4v o[2];
+        phi_q_block(q + ((size_t)x.bh * R + row) * D + cb * 16, row < R, o);
+        *reinterpret_cast<uint4v*>(qs + row * QS + cb * 32) = o[0];
+        *reinterpret_cast<uint4v*>(qs + row * QS + cb * 32 + 16) = o[1];
+    }
+    __syncthreads();
+    if (!exists) return;
+    half8 qreg[NS];                                      // row cc, d = (D/4) g + 8 s .. + 7
+#pragma unroll
+    for (int s = 0; s < NS; ++s) qreg[s] = *reinterpret_cast<const half8*>(qs + cc * QS + (D / 2) * g + 16 * s);
+    const int row = cc < R ? cc : 0;
+    const int klim = CAUSAL ? x.Lk - Lq + (row % Lq) : x.Lk - 1, klim_min = CAUSAL ? x.Lk - Lq : x.Lk - 1;
+    const bool need_mask = x.k_t + 63 > klim_min;
+    const size_t tile = ((size_t)x.bh * NC + x.ch) * kDirTiles + wave;
+    float mx = -INFINITY;
+#pragma unroll
+    for (int blk = 0; blk < 4; ++blk) {
+        floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+        const half2v sc = scales_of<D>(raw[blk], x.live);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(dequant8<D>(raw[blk], sc, s), qreg[s], acc, 0, 0, 0);
+        if (need_mask) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (x.k_t + 16 * blk + 4 * g + i > klim) acc[i] = -INFINITY;
+        }
+        mx = max_nc(max_nc(mx, max_nc(acc[0], acc[1])), max_nc(acc[2], acc[3]));
+        if (cc < R) *reinterpret_cast<floatx4*>(S + tile * (R * 64) + cc * 64 + 16 * blk + 4 * g) = acc;
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 16));
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    if (g == 0) tmax[tile * kDecRows + cc] = mx;
+}
+
+template <int D>
+__global__ __launch_bounds__(256) void decode_values_kernel(
+    const unsigned char* __restrict__ cache, int num_pages, const int* __restrict__ page_table, const int* __restrict__ kv_lens,
+    int Hkv, int R, int NC, int max_pages, const float* __restrict__ S, const float* __restrict__ tmax,
+    float* __restrict__ part_o, float* __restrict__ part_l, float* __restrict__ part_m, uint16_t* __restrict__ O, float* __restrict__ lse, float c /* log2(e)/sqrt(d) */)
+{
+    constexpr int NS = D / 32, NDT = D / 16, RS = 2 * D + 16, PS = 144;
+    constexpr size_t VOFF = (size_t)128 * (D / 2 + D / 16);
+    __shared__ __align__(16) unsigned char stage[4 * 32 * RS];     // per wave: V^F of 32 keys [key][d] fp16; later the waves' sums [4][R][D]
+    __shared__ __align__(16) unsigned char pfb[4 * kDecRows * PS]; // per wave: P^F of its tile [row][key] fp16
+    __shared__ __align__(16) float front[4][kDecRows];             // per wave: largest score of the tiles in front that it has looked at
+    __shared__ float lsum_w[4][kDecRows];
+    const int tid = threadIdx.x, lane = tid & 63, cc = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const DirTile x = dir_tile<D>(cache, num_pages, page_table, kv_lens, Hkv, max_pages);
+    if (x.ch >= x.nch) return;
+    const bool exists = wave < x.NT;
+    const size_t unit = (size_t)x.bh * NC + x.ch;
+    const int row = cc < R ? cc : 0, pq = lane >> 4, pj = lane & 15;
+    // everything this wave needs from memory, at once
+    RawKV<D> raw[4];
+    floatx4 sv[4];
+    float tm_c[kDirTiles], tm_p[4][kDirTiles];           // the chunk's tile maxima of row cc and of the rows of the passes below
+    if (exists) {
+#pragma unroll
+        for (int blk = 0; blk < 4; ++blk)
+            raw[blk] = load_raw<D>(x.src + VOFF, (uint32_t)(cc * (D / 2) + (D / 8) * g) + (uint32_t)(x.k_t & 64) * (D / 2),
+                                   (uint32_t)(128 * (D / 2) + cc * (D / 16) + (D / 64) * g) + (uint32_t)(x.k_t & 64) * (D / 16), blk);
+#pragma unroll
+        for (int ps = 0; ps < 4; ++ps)
+            if (4 * ps < R) sv[ps] = *reinterpret_cast<const floatx4*>(S + (unit * kDirTiles + wave) * (R * 64) + min(4 * ps + pq, R - 1) * 64 + 4 * pj);
+    }
+#pragma unroll
+    for (int t = 0; t < kDirTiles; ++t) {
+        const float* tm = tmax + (unit * kDirTiles + min(t, x.NT - 1)) * kDecRows;
+        tm_c[t] = tm[row];
+#pragma unroll
+        for (int ps = 0; ps < 4; ++ps) tm_p[ps][t] = 4 * ps < R ? tm[min(4 * ps + pq, R - 1)] : 0.0f;
+    }
+    // the running maximum in front of the chunk: the tiles before it, 64 at a time; a thread has four rows of a tile
+    floatx4 fm = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    for (int i = tid >> 2; i < kDirTiles * x.ch; i += 64) {
+        const floatx4 v = *reinterpret_cast<const floatx4*>(tmax + ((size_t)x.bh * NC * kDirTiles + i) * kDecRows + 4 * (tid & 3));
+#pragma unroll
+        for (int k = 0; k < 4; ++k) fm[k] = fmaxf(fm[k], v[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+#pragma unroll
+        for (int dd = 4; dd < 64; dd <<= 1) fm[k] = fmaxf(fm[k], __shfl_xor(fm[k], dd));
+    }
+    if (lane < 4) *reinterpret_cast<floatx4*>(&front[wave][4 * lane]) = fm;
+    __syncthreads();
+    auto in_front = [&](int r) __attribute__((always_inline)) { return fmaxf(fmaxf(front[0][r], front[1][r]), fmaxf(front[2][r], front[3][r])); };
+    // running maximum after this wave's tile, and after the chunk's last, of a row with the tile maxima tm
+    auto running = [&](float m, const float (&tm)[kDirTiles], int upto) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < kDirTiles; ++t) if (t <= upto) m = fmaxf(m, tm[t]);
+        return m;
+    };
+    const float m0 = in_front(row), m = running(m0, tm_c, wave), m_end = running(m0, tm_c, x.NT - 1);
+    floatx4 o[NDT];
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt) o[dt] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+    unsigned char* stg = stage + wave * (32 * RS);
+    unsigned char* pfw = pfb + wave * (kDecRows * PS);
+    const uint32_t tr_base = lds_addr_of(stg) + (uint32_t)((8 * g + (cc >> 2)) * RS + 8 * (cc & 3));
+#pragma unroll
+    for (int ps = 0; ps < 4; ++ps) {
+        if (4 * ps < R) {
+            const int prow = min(4 * ps + pq, R - 1);
+            const float mp0 = in_front(prow), mrow = running(mp0, tm_p[ps], wave), mrow_end = running(mp0, tm_p[ps], x.NT - 1);
+            float lacc = 0.0f;
+            if (exists) {
+                const float ms = mrow * c;
+                float pt[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) pt[i] = __builtin_amdgcn_exp2f(fmaf(sv[ps][i], c, -ms));
+                lacc = (pt[0] + pt[1]) + (pt[2] + pt[3]);
+                const uint2v w = phi_p_quad(pt);
+                *reinterpret_cast<uint2v*>(pfw + (4 * ps + pq) * PS + 8 * pj) = w;
+            }
+            float l = lacc * __builtin_amdgcn_exp2f((mrow - mrow_end) * c);
+            l += __shfl_xor(l, 1); l += __shfl_xor(l, 2); l += __shfl_xor(l, 4); l += __shfl_xor(l, 8);
+            if (pj == 0 && 4 * ps + pq < R) lsum_w[wave][4 * ps + pq] = l;
+        }
+    }
+    if (exists) {
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh) {
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int sub = 0; sub < 2; ++sub) {
+                unsigned char* dst = stg + (16 * sub + cc) * RS + (D / 2) * g;
+                const half2v sc = scales_of<D>(raw[2 * hh + sub], x.live && x.k_t + 32 * hh + 16 * sub + cc < x.Lk);
+#pragma unroll
+                for (int s = 0; s < NS; ++s) *reinterpret_cast<half8*>(dst + 16 * s) = dequant8<D>(raw[2 * hh + sub], sc, s);
+            }
+            __builtin_amdgcn_wave_barrier();
+            const half8 bp = *reinterpret_cast<const half8*>(pfw + cc * PS + 64 * hh + 16 * g);
+#pragma unroll
+            for (int dt = 0; dt < NDT; ++dt) {
+                const uint2v lo = lds_read_tr16_at(tr_base + 32 * dt), hi = lds_read_tr16_at(tr_base + 32 * dt + 4 * RS);
+                uint4v av; av[0] = lo[0]; av[1] = lo[1]; av[2] = hi[0]; av[3] = hi[1];
+                o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, av), bp, o[dt], 0, 0, 0);
+            }
+        }
+    }
+    // ---- the four waves' sums, re-based to the chunk's last maximum
+    const float f = exists ? __builtin_amdgcn_exp2f((m - m_end) * c) : 0.0f;
+    float* mbuf = reinterpret_cast<float*>(stage);                 // [4][R][D]
+    __syncthreads();                                               // every wave is done with its V tile
+    if (cc < R) {
+#pragma unroll
+        for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) mbuf[(wave * R + cc) * D + 16 * dt + 4 * g + i] = o[dt][i] * f;
+    }
+    __syncthreads();
+    const float ln2c = c * 0.6931471805599453f;
+    auto l_of = [&](int r) __attribute__((always_inline)) { return (lsum_w[0][r] + lsum_w[1][r]) + (lsum_w[2][r] + lsum_w[3][r]); };
+    auto o_of = [&](int e) __attribute__((always_inline)) { return (mbuf[e] + mbuf[R * D + e]) + (mbuf[2 * R * D + e] + mbuf[3 * R * D + e]); };
+    if (x.nch == 1) {
+        for (int e = tid; e < R * D; e += 256) O[(size_t)x.bh * R * D + e] = f32_to_bf16_rne(o_of(e) / l_of(e / D));
+        if (wave == 0 && g == 0 && cc < R) lse[(size_t)x.bh * R + cc] = m_end * ln2c + logf(l_of(cc));
+        return;
+    }
+    for (int e = tid; e < R * D; e += 256) part_o[unit * R * D + e] = o_of(e);
+    if (wave == 0 && g == 0 && cc < R) {
+        part_l[unit * kDecRows + cc] = l_of(cc);
+        part_m[unit * kDecRows + cc] = m_end;
+    }
+}
+
 }  // namespace
 
 // Keys per chunk for R rows per (sequence, kv head): the chunk's scores [R][CK] fp32 fit the LDS set aside for them.  A step that would
@@ -607,6 +843,56 @@ size_t decode_ws_bytes(int B, int Hkv, int R, int max_pages, int D, int halvings
     n += units * R * D * 4;                                            // O of the partial sums (R rows each)
     n += units * kDecItemInts * 4;                                     // the list of chunks
     return n;
+}
+
+// ---- the two launches without a queue
+struct DirectWs { int NC; size_t units, tmax, scores, part_l, part_m, part_o, bytes; };
+static DirectWs direct_ws(int B, int Hkv, int R, int max_pages, int D)
+{
+    DirectWs w{};
+    w.NC = (max_pages * 128 + 64 * kDirTiles - 1) / (64 * kDirTiles);
+    w.units = (size_t)B * Hkv * w.NC;
+    auto take = [&](size_t n) { const size_t at = w.bytes; w.bytes += (n + 255) / 256 * 256; return at; };
+    w.tmax = take(w.units * kDirTiles * kDecRows * 4);
+    w.scores = take(w.units * kDirTiles * R * 64 * 4);
+    w.part_l = take(w.units * kDecRows * 4);
+    w.part_m = take(w.units * kDecRows * 4);
+    w.part_o = take(w.units * R * D * 4);
+    return w;
+}
+// Up to twelve chunks of 256 keys per compute unit, counted by the page table's width, or 24 where the queue's chunks are no longer than
+// that either (more than ten rows).  Queue -> direct, whole step, d = 128, 8 kv heads: 4 rows: 1 sequence of 3000 keys (96 chunks) 20.4 -> 14.1 us,
+// of 16000 (504) 28.8 -> 20.3; 8 of 500 - 3000 (768) 27.2 -> 17.5; 16 of 4000 (2048) 41.9 -> 35.2; 12 of 8000 (3072) 50.7 -> 47.7; 16 of
+// 2000 - 8000 (4096) 49.9 -> 52.4; 32 of 4k - 16k (16384) 104 -> about 190: the queue reads no scores back and keeps loads in flight across
+// chunks.  16 rows: 8 of 4000 (1024) 50.5 -> 33.9; 16 of 2000 - 8000 (4096) 89.9 -> 79.0; 40 of 2000 - 16000, 4 kv heads (10080) 163 -> 139, but
+// the scores alone then take 160 MB.
+bool decode_is_direct(int B, int Hkv, int R, int max_pages, int cus)
+{
+    return (long long)B * Hkv * ((max_pages + 1) / 2) <= (long long)cus * (chunk_keys(R, 0) == 64 * kDirTiles ? 24 : 12);
+}
+size_t decode_direct_ws_bytes(int B, int Hkv, int R, int max_pages, int D) { return direct_ws(B, Hkv, R, max_pages, D).bytes; }
+
+int launch_decode_direct(const void* q, const void* cache, int num_pages, const int* page_table, int max_pages, const int* kv_lens,
+                         int B, int Hq, int Hkv, int Lq, int D, bool causal, void* ws, void* o, float* lse, hipStream_t st)
+{
+    const int R = (Hq / Hkv) * Lq;
+    if (R < 1 || R > kDecRows || (D != 64 && D != 128) || B * Hkv > 65535) return -1;
+    const DirectWs w = direct_ws(B, Hkv, R, max_pages, D);
+    unsigned char* p = (unsigned char*)ws;
+    const dim3 grid((unsigned)w.NC, (unsigned)(B * Hkv));
+    const float c = 1.4426950408889634f / sqrtf((float)D);
+#define AQ_DIR(DD, C) do { \
+        hipLaunchKernelGGL((decode_scores_kernel<DD, C>), grid, dim3(256), 0, st, (const uint16_t*)q, (const unsigned char*)cache, num_pages, page_table, kv_lens, \
+                           Hkv, Lq, R, w.NC, max_pages, (float*)(p + w.scores), (float*)(p + w.tmax), (uint16_t*)o, lse); \
+        hipLaunchKernelGGL((decode_values_kernel<DD>), grid, dim3(256), 0, st, (const unsigned char*)cache, num_pages, page_table, kv_lens, \
+                           Hkv, R, w.NC, max_pages, (const float*)(p + w.scores), (const float*)(p + w.tmax), \
+                           (float*)(p + w.part_o), (float*)(p + w.part_l), (float*)(p + w.part_m), (uint16_t*)o, lse, c); \
+        if (w.NC > 1) hipLaunchKernelGGL((decode_merge_kernel<DD>), dim3((unsigned)(B * Hkv * ((R * DD + 255) / 256))), dim3(256), 0, st, kv_lens, Hkv, R, 64 * kDirTiles, w.NC, \
+                           max_pages, (const float*)(p + w.part_o), (const float*)(p + w.part_l), (const float*)(p + w.part_m), (uint16_t*)o, lse, c); } while (0)
+    if (D == 128) { if (causal) AQ_DIR(128, true); else AQ_DIR(128, false); }
+    else          { if (causal) AQ_DIR(64, true); else AQ_DIR(64, false); }
+#undef AQ_DIR
+    return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 int launch_decode(const void* q, void* qh, const void* cache, int num_pages, const int* page_table, int max_pages, const int* kv_lens,

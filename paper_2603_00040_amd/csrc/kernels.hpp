@@ -77,6 +77,12 @@ size_t decode_ws_bytes(int B, int Hkv, int R, int max_pages, int D, int halvings
 int launch_decode(const void* q, void* qh, const void* cache, int num_pages, const int* page_table, int max_pages, const int* kv_lens,
                   int B, int Hq, int Hkv, int Lq, int D, bool causal, void* ws, int halvings, int spin_limit, void* o, float* lse, hipStream_t st);
 
+// The same for a step with few chunks: two launches without a queue (see decode.hip).  ws: decode_direct_ws_bytes() bytes.
+bool decode_is_direct(int B, int Hkv, int R, int max_pages, int cus);
+size_t decode_direct_ws_bytes(int B, int Hkv, int R, int max_pages, int D);
+int launch_decode_direct(const void* q, const void* cache, int num_pages, const int* page_table, int max_pages, const int* kv_lens,
+                         int B, int Hq, int Hkv, int Lq, int D, bool causal, void* ws, void* o, float* lse, hipStream_t st);
+
 // The MX format's operand arrays of the scaled FP4 instruction, from which the backward recomputes the scores (launch_mx_group):
 // kops / ksc: a wave's 32 keys as the A operand of the dK/dV pass; krec: 64-key records, the A operand of the dQ pass.
 struct MxScoreOps { const void *qops, *qsc, *kops, *ksc, *krec; };

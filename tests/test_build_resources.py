@@ -191,3 +191,7 @@ def test_split_forward_kernels_do_not_spill():
     _check(k, r"fwd_split_kernelILi(64|128)ELb[01]ELb[01]ELi[01]ELb0E", 16)
     _check(k, r"fwd_split_kernelILi(64|128)ELb0ELb[01]ELi(3ELb0|0ELb1)E", 8)
     assert len([n for n in k if "fwd_split_kernel" in n]) == 24
+
+
+def test_decode_kernels_without_a_queue_keep_off_scratch_memory():
+    _check(_resources("decode.hip"), r"decode_(scores_kernelILi(64|128)ELb[01]|values_kernelILi(64|128))E", 6)

@@ -237,3 +237,29 @@ def test_decode_chunks_of_any_length_agree(Hq, Hkv, Lq, d, lens):
     a, r = o.float(), o2.float()
     assert bool(((a - r).abs() <= 2.0 ** -7 * r.abs() + 1e-5 * r.abs().max()).all())
     assert float((lse - lse2).abs().max()) <= 2e-5 * float(lse2.abs().max())
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("Hq,Hkv,Lq,d,lens", [(8, 2, 1, 128, (1, 63, 64, 65, 255, 256, 257, 3000)), (4, 4, 4, 64, (5, 512, 1023, 1025)), (16, 1, 1, 128, (4700, 300)),
+                                              (5, 1, 3, 64, (17, 2304)), (9, 1, 1, 128, (640, 129)), (2, 2, 16, 64, (16, 100, 1500))])
+def test_decode_without_the_queue_equals_the_queue(Hq, Hkv, Lq, d, lens, causal):
+    """Few chunks: two launches without a queue, one chunk of 256 keys per workgroup.  The debug entry point always takes the queue, whose
+    chunks are as short here: the same bits.  A page id outside the cache reads as zeros on either."""
+    import paper_2603_00040_amd as aq
+    B, pages = len(lens), [(n + 127) // 128 for n in lens]
+    cache = torch.randint(0, 256, (sum(pages) * aq.kv_cache_page_bytes_nvfp4(Hkv, d),), dtype=torch.uint8, device="cuda")
+    table, at = torch.full((B, max(pages)), -7, dtype=torch.int32, device="cuda"), 0
+    for b, n in enumerate(lens):
+        ids = torch.arange(at, at + pages[b], dtype=torch.int32, device="cuda").flip(0).contiguous()
+        at += pages[b]
+        table[b, :pages[b]] = ids
+        x = random_inputs(1, Hkv, Hkv, n, d, seed=n + b, k_chan=2)
+        aq.attnqat_kv_cache_write(to_dev(x["k"]), to_dev(x["v"]), cache, ids, 0, sum(pages))
+    q = to_dev(random_inputs(B, Hq, Hkv, Lq, d, seed=1)["q"])
+    kl = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    for outside in (None, -1, sum(pages)):
+        if outside is not None:
+            table[B - 1, pages[B - 1] // 2] = outside
+        o, lse = aq.attnqat_fwd_infer_paged(q, cache, sum(pages), table, kl, Hkv, causal)
+        oq, lq, expired = aq.attnqat_fwd_infer_paged(q, cache, sum(pages), table, kl, Hkv, causal, spin_limit=1 << 22)
+        assert not expired and torch.isfinite(o.float()).all() and torch.equal(o, oq) and torch.equal(lse, lq), outside
