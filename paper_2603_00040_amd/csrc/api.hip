@@ -269,6 +269,17 @@ const char* attnqat_strerror(int code)
     }
 }
 
+namespace {
+// The paged MX forward's heads.  Grouped-query heads with few positions: q [B,Hq,Lq,d] is [B*Hkv, G*Lq, d] in memory, so the G query
+// heads of a kv group are treated as one head with G*Lq rows: one tile and one pass over the pages instead of G.
+struct MxPacked { int Hq, Lq; };
+MxPacked mx_packed(int Hq, int Hkv, int Lq)
+{
+    const int G = Hq / Hkv;
+    return G > 1 && G * Lq <= 128 ? MxPacked{Hkv, G * Lq} : MxPacked{Hq, Lq};
+}
+}  // namespace
+
 size_t attnqat_workspace_bytes(int which, int B, int Hq, int Hkv, int L, int d)
 {
     if (check_dims(B, Hq, Hkv, L, d, ATTNQAT_BF16)) return 0;
@@ -281,6 +292,8 @@ size_t attnqat_workspace_bytes(int which, int B, int Hq, int Hkv, int L, int d)
     case ATTNQAT_WS_FWD_INFER_MX_PAGED: {          // L = the number of query positions per sequence
         Carver c{nullptr, 0};
         c.take(mx_qops_bytes(B * Hq, L, d)); c.take(mx_qsc_bytes(B * Hq, L));
+        const MxPacked p = mx_packed(Hq, Hkv, L);
+        c.take(mx_decode_part_bytes(B * p.Hq, p.Lq, d));
         return c.off;
     }
     case ATTNQAT_WS_FWD_INFER_MX_SPARSE: {
@@ -423,22 +436,22 @@ int attnqat_fwd_infer_mx_paged(const void* q, int B, int Hq, int Hkv, int Lq, in
     if (!q || !cache || !page_table || !kv_lens || !o || !lse || num_pages < 1 || max_pages < 1) return ATTNQAT_EINVAL;
     int rc = check_dims(B, Hq, Hkv, Lq, d, dtype);
     if (rc) return rc;
-    // Grouped-query heads with few positions: q [B,Hq,Lq,d] is [B*Hkv, G*Lq, d] in memory, so the G query heads of a kv
-    // group are treated as one head with G*Lq rows: one tile and one pass over the pages instead of G.
-    const int G = Hq / Hkv;
-    const bool pack = G > 1 && G * Lq <= 128;
-    const int Hq_k = pack ? Hkv : Hq, Lq_k = pack ? G * Lq : Lq;
+    const int Hq_k = mx_packed(Hq, Hkv, Lq).Hq, Lq_k = mx_packed(Hq, Hkv, Lq).Lq;
     Carver c{(unsigned char*)workspace, 0};
     unsigned char* qops = (unsigned char*)c.take(mx_qops_bytes(B * Hq, Lq, d));      // sized for the unpacked case (the larger)
     unsigned char* qsc = (unsigned char*)c.take(mx_qsc_bytes(B * Hq, Lq));
     if (!workspace || workspace_bytes < c.off) return ATTNQAT_EWORKSPACE;
+    // (the sums of a decode step's chunks: a workspace without the room for them gets one workgroup per head)
+    const size_t part_bytes = mx_decode_part_bytes(B * Hq_k, Lq_k, d);
+    float* part = part_bytes ? (float*)c.take(part_bytes) : nullptr;
+    if (workspace_bytes < c.off) part = nullptr;
     hipStream_t st = (hipStream_t)stream;
     prof_begin(st);
     MxGroup g = mx_group_of(q, nullptr, nullptr, B * Hq_k, 0, Lq_k);
     g.qops = qops; g.qsc = qsc;
     if (launch_mx_group(g, MX_INFER, d, st)) return ATTNQAT_ELAUNCH;
     prof_mark("prep_q_mx", st);
-    if (launch_fwd_mx_paged(qops, qsc, cache, B, Hq_k, Hkv, Lq_k, d, causal != 0, page_table, kv_lens, max_pages, num_pages, Lq, o, lse, st))
+    if (launch_fwd_mx_paged(qops, qsc, cache, B, Hq_k, Hkv, Lq_k, d, causal != 0, page_table, kv_lens, max_pages, num_pages, Lq, part, o, lse, st))
         return ATTNQAT_ELAUNCH;
     prof_mark("fwd_infer_mx_paged", st);
     return ATTNQAT_OK;

@@ -860,7 +860,7 @@ static DirectWs direct_ws(int B, int Hkv, int R, int max_pages, int D)
     w.part_o = take(w.units * R * D * 4);
     return w;
 }
-// Up to twelve chunks of 256 keys per compute unit, counted by the page table's width, or 24 where the queue's chunks are no longer than
+// Up to twelve chunks of 256 keys per compute unit, counted by the page table's width, or 40 where the queue's chunks are no longer than
 // that either (more than ten rows).  Queue -> direct, whole step, d = 128, 8 kv heads: 4 rows: 1 sequence of 3000 keys (96 chunks) 20.4 -> 14.1 us,
 // of 16000 (504) 28.8 -> 20.3; 8 of 500 - 3000 (768) 27.2 -> 17.5; 16 of 4000 (2048) 41.9 -> 35.2; 12 of 8000 (3072) 50.7 -> 47.7; 16 of
 // 2000 - 8000 (4096) 49.9 -> 52.4; 32 of 4k - 16k (16384) 104 -> about 190: the queue reads no scores back and keeps loads in flight across
@@ -868,7 +868,7 @@ static DirectWs direct_ws(int B, int Hkv, int R, int max_pages, int D)
 // the scores alone then take 160 MB.
 bool decode_is_direct(int B, int Hkv, int R, int max_pages, int cus)
 {
-    return (long long)B * Hkv * ((max_pages + 1) / 2) <= (long long)cus * (chunk_keys(R, 0) == 64 * kDirTiles ? 24 : 12);
+    return (long long)B * Hkv * ((max_pages + 1) / 2) <= (long long)cus * (chunk_keys(R, 0) == 64 * kDirTiles ? 40 : 12);
 }
 size_t decode_direct_ws_bytes(int B, int Hkv, int R, int max_pages, int D) { return direct_ws(B, Hkv, R, max_pages, D).bytes; }
 

@@ -379,11 +379,14 @@ __global__ __launch_bounds__(256, 2) void fwd_mx_kernel(
 // waves of a block derive the same scale).  Each wave then quantizes its 16 keys per row against the maximum after ITS
 // tile, exactly as the tile order of Alg. 1 prescribes, and accumulates its own O and l against its own reference
 // maximum; the partial results are brought to the final maximum and added at the end.
-template <int D, bool CAUSAL, int NP /* pages per iteration: 4 NP waves */>
-__global__ __launch_bounds__(256 * NP, NP == 1 ? 2 : 1) void fwd_mx_decode_kernel(
+// PART (fwd_mx_decode_part_kernel): the pages of one chunk only, blockIdx.y; see there.
+struct MxChunks { int per /* pages of a chunk */, n /* chunks of a sequence */; const float* cmax; float *part_o, *part_l, *part_m; };
+constexpr int kMxDecRows = 32;                       // most rows of a head
+template <int D, bool CAUSAL, int NP /* pages per iteration: 4 NP waves */, bool PART>
+__device__ __forceinline__ void mx_decode_body(
     const unsigned char* __restrict__ qops, const uint32_t* __restrict__ qsc, const unsigned char* __restrict__ kv,
     uint16_t* __restrict__ O, float* __restrict__ lse, int L /* rows, <= 32 */, int Hq, int G, float c /* log2(e)/sqrt(d) */,
-    const int* __restrict__ page_table, const int* __restrict__ kv_lens, int max_pages, int num_pages, int lq_inner)
+    const int* __restrict__ page_table, const int* __restrict__ kv_lens, int max_pages, int num_pages, int lq_inner, MxChunks ck)
 {
     constexpr int KS = D / 64, MT = D / 32, NW = 4 * NP;
     constexpr int NIT = NP == 1 ? 4 : NP == 2 ? 3 : 2;   // iterations whose pages the LDS ring holds (NIT - 1 of them in flight)
@@ -412,7 +415,10 @@ __global__ __launch_bounds__(256 * NP, NP == 1 ? 2 : 1) void fwd_mx_decode_kerne
     const int Lk = __builtin_amdgcn_readfirstlane(kv_lens[b]);
     const int koff = Lk - lq_inner;
     const bool packed = lq_inner != L;
-    const int nst = min((Lk + 127) / 128, max_pages);              // pages of this sequence
+    const int nst_all = min((Lk + 127) / 128, max_pages);          // pages of this sequence
+    const int ch = PART ? (int)blockIdx.y : 0, p0 = PART ? ch * ck.per : 0;
+    if (PART && p0 >= max(nst_all, 1)) return;
+    const int nst = PART ? min(nst_all - p0, ck.per) : nst_all;    // pages of this chunk
     const int nit = (nst + NP - 1) / NP;
     const int klim = CAUSAL ? min(Lk - 1, koff + (packed ? q_row % lq_inner : q_row)) : Lk - 1;
 
@@ -422,7 +428,7 @@ __global__ __launch_bounds__(256 * NP, NP == 1 ? 2 : 1) void fwd_mx_decode_kerne
         for (int pp = 0; pp < NP; ++pp) {
             const int st = it * NP + pp;
             if (st < nst) {
-                int page = __builtin_amdgcn_readfirstlane(page_table[(size_t)b * max_pages + st]);
+                int page = __builtin_amdgcn_readfirstlane(page_table[(size_t)b * max_pages + p0 + st]);
                 page = min(max(page, 0), num_pages - 1);           // a bad table entry reads a wrong page, never outside the cache
                 const unsigned char* src = kv + ((size_t)page * Hkv + (h / G)) * STAGE;
                 unsigned char* dst = smem + (st % NR) * STAGE;
@@ -455,6 +461,10 @@ __global__ __launch_bounds__(256 * NP, NP == 1 ? 2 : 1) void fwd_mx_decode_kerne
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[mt][i] = 0.0f;
     float m_run = -INFINITY;         // maximum after the last iteration (the same in every wave)
+    if constexpr (PART) {            // ... which for a later chunk is that of the chunks in front; the halves of the wave take every other one
+        for (int i = hf; i < ch; i += 2) m_run = fmaxf(m_run, ck.cmax[((size_t)bh * ck.n + i) * kMxDecRows + ln]);
+        m_run = xhalf_max(m_run);
+    }
     float mref = -INFINITY;          // maximum this wave's O and l refer to (after its tile of its last iteration)
     float lsum = 0.0f;
 
@@ -476,7 +486,7 @@ __global__ __launch_bounds__(256 * NP, NP == 1 ? 2 : 1) void fwd_mx_decode_kerne
         const int st = it * NP + pi;                                          // this wave's page
         const bool valid = st < nst;                                          // (the last iteration may be short of pages)
         const unsigned char* rec = smem + (st % NR) * STAGE + T * REC;
-        const int k0 = st * 128 + T * 64;
+        const int k0 = (p0 + st) * 128 + T * 64;
         // S^T of this wave's 32 keys
         floatx16 sv;
 #pragma unroll
@@ -598,7 +608,18 @@ __global__ __launch_bounds__(256 * NP, NP == 1 ? 2 : 1) void fwd_mx_decode_kerne
         }
         __syncthreads();
     }
-    if (wave == 0) {
+    if (PART && wave == 0 && nst_all > ck.per) {                              // several chunks: the sums go to memory
+        if (q_row < L) {
+            const size_t unit = (size_t)bh * ck.n + ch;
+            float* dst = ck.part_o + (unit * L + q_row) * D;
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int tt = 0; tt < 4; ++tt)
+                    *reinterpret_cast<floatx4*>(dst + 32 * mt + 8 * tt + 4 * hf) = floatx4{o[mt][4 * tt], o[mt][4 * tt + 1], o[mt][4 * tt + 2], o[mt][4 * tt + 3]};
+            if (hf == 0) { ck.part_l[unit * kMxDecRows + ln] = l; ck.part_m[unit * kMxDecRows + ln] = m_run; }
+        }
+    } else if (wave == 0) {
         const float inv_l = l > 0.0f ? 1.0f / l : 0.0f;                       // a sequence without keys: O = 0, L = -inf
         if (q_row < L) {
             const size_t row = (size_t)bh * L + q_row;
@@ -616,6 +637,135 @@ __global__ __launch_bounds__(256 * NP, NP == 1 ? 2 : 1) void fwd_mx_decode_kerne
         }
     }
 }
+
+#define AQ_DEC_ARGS \
+    const unsigned char* __restrict__ qops, const uint32_t* __restrict__ qsc, const unsigned char* __restrict__ kv, \
+    uint16_t* __restrict__ O, float* __restrict__ lse, int L, int Hq, int G, float c, \
+    const int* __restrict__ page_table, const int* __restrict__ kv_lens, int max_pages, int num_pages, int lq_inner
+template <int D, bool CAUSAL, int NP>
+__global__ __launch_bounds__(256 * NP, NP == 1 ? 2 : 1) void fwd_mx_decode_kernel(AQ_DEC_ARGS)
+{
+    mx_decode_body<D, CAUSAL, NP, false>(qops, qsc, kv, O, lse, L, Hq, G, c, page_table, kv_lens, max_pages, num_pages, lq_inner, MxChunks{});
+}
+
+// Few sequences: one workgroup per (sequence, kv head) walks all pages, a microsecond each, while most compute units idle.  The pages are
+// then cut into chunks with a workgroup each.  What a chunk has to know of those in front of it is their row maxima (P-tilde
+// is quantized against the running maximum), and on the FP4 instruction scores are cheap: a launch of its own computes
+// all scores for their maxima alone (mx_decode_max_kernel reads the K half of the records), this one takes them as its starting
+// maximum and does what fwd_mx_decode_kernel does, and mx_decode_merge_kernel adds the chunks' sums, re-based to the last maximum.
+template <int D, bool CAUSAL>
+__global__ __launch_bounds__(256, 2) void fwd_mx_decode_part_kernel(AQ_DEC_ARGS, MxChunks ck)
+{
+    mx_decode_body<D, CAUSAL, 1, true>(qops, qsc, kv, O, lse, L, Hq, G, c, page_table, kv_lens, max_pages, num_pages, lq_inner, ck);
+}
+#undef AQ_DEC_ARGS
+
+// Row maxima of the scores of every chunk but a sequence's last (nobody asks for that one's): blockIdx = (head, chunk).  Operands straight
+// to registers, a page ahead; waves as in mx_decode_body: wave w has product w % 2 of tile w / 2 of each page.
+template <int D, bool CAUSAL>
+__global__ __launch_bounds__(256) void mx_decode_max_kernel(
+    const unsigned char* __restrict__ qops, const uint32_t* __restrict__ qsc, const unsigned char* __restrict__ kv, int L, int Hq, int G,
+    const int* __restrict__ page_table, const int* __restrict__ kv_lens, int max_pages, int num_pages, int lq_inner, int per, int n, float* __restrict__ cmax)
+{
+    constexpr int KS = D / 64, MT = D / 32, KOPS = 2 * KS * 1024, VOPS = MT * 1024, REC = mx_rec_bytes(D, false), STAGE = 2 * REC;
+    __shared__ float red[4][64];
+    const int bh = blockIdx.x, ch = blockIdx.y, b = bh / Hq, h = bh % Hq, Hkv = Hq / G;
+    const int lane = threadIdx.x & 63, ln = lane & 31, hf = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), T = wave >> 1, t = wave & 1;
+    const int Lk = __builtin_amdgcn_readfirstlane(kv_lens[b]);
+    const int nst = min((Lk + 127) / 128, max_pages), p0 = ch * per;
+    if (p0 + per >= nst) return;                                              // the last chunk, or none
+    const int koff = Lk - lq_inner;
+    const int klim = CAUSAL ? min(Lk - 1, koff + (lq_inner != L ? ln % lq_inner : ln)) : Lk - 1;
+    uint4v qop[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) qop[ks] = *reinterpret_cast<const uint4v*>(qops + (((size_t)bh * 4 * KS + ks) * 64 + lane) * 16);
+    const uint32_t qs = qsc[(size_t)bh * 4 * 64 + lane];
+    auto as8 = [](const uint4v& x) __attribute__((always_inline)) -> int8v {
+        int8v r = {(int)x[0], (int)x[1], (int)x[2], (int)x[3], 0, 0, 0, 0};
+        return r;
+    };
+    uint4v a[KS];
+    uint32_t ksc;
+    auto load = [&](int p) __attribute__((always_inline)) {
+        const int page = min(max(__builtin_amdgcn_readfirstlane(page_table[(size_t)b * max_pages + p]), 0), num_pages - 1);
+        const unsigned char* rec = kv + ((size_t)page * Hkv + h / G) * STAGE + T * REC;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) a[ks] = *reinterpret_cast<const uint4v*>(rec + ((t * KS + ks) * 64 + lane) * 16);
+        ksc = *reinterpret_cast<const uint32_t*>(rec + KOPS + VOPS + lane * 4) >> (8 * t * KS);
+    };
+    float mx = -INFINITY;
+    load(p0);
+    for (int p = p0; p < p0 + per; ++p) {
+        floatx16 sv;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sv[i] = 0.0f;
+        sv = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[0]), as8(qop[0]), sv, 4, 4, 0, ksc, 0, qs);
+        if constexpr (KS == 2) sv = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[1]), as8(qop[1]), sv, 4, 4, 1, ksc, 1, qs);
+        mfma_scale_settle(sv);
+        if (p + 1 < p0 + per) load(p + 1);
+        const int k0 = p * 128 + T * 64;
+        if ((k0 + 64 > Lk) || (CAUSAL && k0 + 63 > koff)) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                if (k0 + 32 * hf + 16 * t + i > klim) sv[i] = -INFINITY;
+        }
+        float pm[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) pm[i] = max_nc(max_nc(sv[i], sv[4 + i]), max_raw(sv[8 + i], sv[12 + i]));
+        mx = max_nc(mx, max_nc(max_nc(pm[0], pm[1]), max_nc(pm[2], pm[3])));
+    }
+    red[wave][lane] = xhalf_max(mx);
+    __syncthreads();
+    if (wave == 0 && hf == 0) cmax[((size_t)bh * n + ch) * kMxDecRows + ln] = fmaxf(fmaxf(red[0][lane], red[1][lane]), fmaxf(red[2][lane], red[3][lane]));
+}
+
+// O and L of the sequences with several chunks; a thread has one element.
+template <int D>
+__global__ __launch_bounds__(256) void mx_decode_merge_kernel(
+    const int* __restrict__ kv_lens, int Hq, int L, int max_pages, MxChunks ck, uint16_t* __restrict__ O, float* __restrict__ lse, float c)
+{
+    const int bh = blockIdx.y, e = blockIdx.x * 256 + threadIdx.x;
+    const int nst = min((kv_lens[bh / Hq] + 127) / 128, max_pages), nch = (nst + ck.per - 1) / ck.per;
+    if (nch < 2 || e >= L * D) return;
+    const size_t u0 = (size_t)bh * ck.n;
+    const int r = e / D;
+    const float M = ck.part_m[(u0 + nch - 1) * kMxDecRows + r];               // (running maxima: the last is the largest)
+    float v = 0.0f, l = 0.0f;
+    for (int i0 = 0; i0 < nch; i0 += 16) {                                    // (sixteen chunks' loads in flight at a time)
+        float pm[16], po[16], pl[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const size_t u = u0 + min(i0 + k, nch - 1);
+            pm[k] = i0 + k < nch ? ck.part_m[u * kMxDecRows + r] : -INFINITY;
+            po[k] = ck.part_o[u * L * D + e];
+            pl[k] = ck.part_l[u * kMxDecRows + r];
+        }
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const float w = __builtin_amdgcn_exp2f((pm[k] - M) * c);          // a chunk that does not exist: weight 0
+            v = fmaf(po[k], w, v);
+            l = fmaf(pl[k], w, l);
+        }
+    }
+    O[(size_t)bh * L * D + e] = f32_to_bf16_rne(v * (1.0f / l));
+    if (e % D == 0) lse[(size_t)bh * L + r] = M * (c * 0.6931471805599453f) + logf(l);
+}
+
+// How many chunks a sequence of max_pages pages is cut into for `heads` (sequence, kv head)s, 1: not at all.  Two workgroups per compute unit
+// at most, of two pages at least; more chunks than sqrt(8 pages) cost more in maxima to read and sums to add than their shorter
+// walk saves (8 heads, 128 pages: 16 / 32 / 64 chunks 22.9 / 19.4 / 21.0 us).  The two more launches cost what 12 pages take.  Whole step,
+// d = 128, one workgroup per head -> chunks: 8 kv heads of one sequence of 16000 keys 110 -> 19.4 us, of 3000 26.8 -> 16.5 us; 8 sequences of
+// 2000 - 8000 56 -> 26 us, 16 of them (4 chunks) 60 -> 41 us; but 16 of 256 - 2000 20.8 -> 18.8 us, 3 x 40 heads of 500 - 1500 14.9 -> 17.2 us
+// and two chunks for 256 heads of 4k - 16k 116.6 -> 118.6 us.
+static int mx_decode_chunks(int heads, int max_pages) {
+    int n = min(max_pages / 2, kMxDecUnits / heads);
+    while ((long long)n * n > 8ll * max_pages) --n;
+    if (n < 3 || (long long)max_pages * (n - 1) < 12ll * n) return 1;
+    const int per = (max_pages + n - 1) / n;
+    return (max_pages + per - 1) / per;
+}
+size_t mx_decode_part_bytes(int heads, int L, int D) { return L > kMxDecRows || 3 * heads > kMxDecUnits ? 0 : (size_t)kMxDecUnits * (3 * kMxDecRows + (size_t)L * D) * 4; }
 
 // ---------------------------------------------------------------------------------------------
 int launch_mx_quant(const void* x, int BH, int L, int D, int axis, bool fp8, unsigned char* codes, unsigned char* scales, void* xf, hipStream_t st)
@@ -673,11 +823,36 @@ int launch_fwd_mx(const void* qops, const void* qsc, const void* kv, int B, int 
 
 int launch_fwd_mx_paged(const void* qops, const void* qsc, const void* cache, int B, int Hq, int Hkv, int Lq, int D, bool causal,
                         const int* page_table, const int* kv_lens, int max_pages, int num_pages, int lq_inner,
-                        void* o, float* lse, hipStream_t st)
+                        float* part, void* o, float* lse, hipStream_t st)
 {
-    if (Lq <= 32) {
+    if (Lq <= kMxDecRows) {
         // a step of decoding: the four waves of a workgroup share the keys of a page
         const float c = 1.4426950408889634f / sqrtf((float)D);
+        const int n = part ? mx_decode_chunks(B * Hq, max_pages) : 1;
+        if (n > 1) {
+            const size_t units = (size_t)B * Hq * n;
+            float* cmax = part; part += units * kMxDecRows;
+            MxChunks ck{(max_pages + n - 1) / n, n, cmax, nullptr, nullptr, nullptr};
+            ck.part_l = part; part += units * kMxDecRows;
+            ck.part_m = part; part += units * kMxDecRows;
+            ck.part_o = part;
+            const dim3 grid((unsigned)(B * Hq), (unsigned)n);
+#define AQ_PARTS(DD, CC) do { \
+            constexpr size_t smem = 4 * 2 * (size_t)mx_rec_bytes(DD, false) + 4 * 256; \
+            auto kern = fwd_mx_decode_part_kernel<DD, CC>; \
+            static unsigned long long lds_set = 0; \
+            if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)smem, lds_set)) return -1; \
+            hipLaunchKernelGGL((mx_decode_max_kernel<DD, CC>), dim3(grid.x, grid.y - 1), dim3(256), 0, st, (const unsigned char*)qops, (const uint32_t*)qsc, (const unsigned char*)cache, \
+                               Lq, Hq, Hq / Hkv, page_table, kv_lens, max_pages, num_pages, lq_inner, ck.per, n, cmax); \
+            hipLaunchKernelGGL(kern, grid, dim3(256), smem, st, (const unsigned char*)qops, (const uint32_t*)qsc, (const unsigned char*)cache, \
+                               (uint16_t*)o, lse, Lq, Hq, Hq / Hkv, c, page_table, kv_lens, max_pages, num_pages, lq_inner, ck); \
+            hipLaunchKernelGGL((mx_decode_merge_kernel<DD>), dim3((unsigned)((Lq * DD + 255) / 256), grid.x), dim3(256), 0, st, kv_lens, Hq, Lq, max_pages, ck, (uint16_t*)o, lse, c); \
+            return hipGetLastError() == hipSuccess ? 0 : -1; } while (0)
+            if (D == 128) { if (causal) AQ_PARTS(128, true); else AQ_PARTS(128, false); }
+            if (D == 64)  { if (causal) AQ_PARTS(64, true); else AQ_PARTS(64, false); }
+#undef AQ_PARTS
+            return -1;
+        }
 #define AQ_DECODE(DD, CC) do { \
         constexpr int NP = AQ_DECODE_NP; \
         constexpr size_t smem = (NP == 1 ? 4 : NP == 2 ? 3 : 2) * NP * 2 * (size_t)mx_rec_bytes(DD, false) + 4 * NP * 256; \

@@ -195,3 +195,8 @@ def test_split_forward_kernels_do_not_spill():
 
 def test_decode_kernels_without_a_queue_keep_off_scratch_memory():
     _check(_resources("decode.hip"), r"decode_(scores_kernelILi(64|128)ELb[01]|values_kernelILi(64|128))E", 6)
+
+
+def test_mx_decode_kernels_in_chunks_do_not_spill():
+    _check(_resources("mx.hip"), r"(fwd_mx_decode_part_kernel|mx_decode_max_kernel)ILi(64|128)ELb[01]E", 8)
+    _check(_resources("mx.hip"), r"mx_decode_merge_kernelILi(64|128)E", 2)

@@ -154,3 +154,31 @@ def test_mx_sequences_together_equal_sequences_alone(B, Hq, Hkv, Lq, d, causal):
     for b in sorted({0, 1, B // 2, B - 1}):
         o1, l1 = aq.attnqat_fwd_infer_mx_paged(q[b:b + 1].contiguous(), cache, sum(pages), table[b:b + 1].contiguous(), kl[b:b + 1].contiguous(), Hkv, causal)
         assert torch.equal(o[b:b + 1], o1) and torch.equal(lse[b:b + 1], l1), b
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("Hq,Hkv,Lq,d,lens", [(8, 2, 1, 128, (4100, 2048, 2049, 513, 64, 1)), (4, 4, 7, 64, (3000, 2431, 7)), (32, 1, 1, 128, (9000,)), (16, 2, 4, 64, (5000, 129))])
+def test_mx_decode_in_chunks_equals_one_workgroup_per_head(Hq, Hkv, Lq, d, lens, causal):
+    """Few sequences: the pages are cut into chunks whose sums are added at the end; a workspace without the room for them gets one
+    workgroup per head.  The same P^F and the same fp32 terms, added in another grouping.  A sequence without keys among them."""
+    import paper_2603_00040_amd as aq
+    B, pages = len(lens), [(n + 127) // 128 for n in lens]
+    cache = torch.randint(0, 256, (sum(pages) * aq.kv_cache_page_bytes(Hkv, d),), dtype=torch.uint8, device="cuda")
+    table, at = torch.zeros((B + 1, max(pages)), dtype=torch.int32, device="cuda"), 0
+    for b, n in enumerate(lens):
+        ids = torch.arange(at, at + pages[b], dtype=torch.int32, device="cuda").flip(0).contiguous()
+        at += pages[b]
+        table[b, :pages[b]] = ids
+        x = random_inputs(1, Hkv, Hkv, n, d, seed=n + b, k_chan=2)
+        aq.attnqat_kv_cache_write_mx(to_dev(x["k"]), to_dev(x["v"]), cache, ids, sum(pages))
+    q = to_dev(random_inputs(B + 1, Hq, Hkv, Lq, d, seed=1)["q"])
+    kl = torch.tensor(list(lens) + [0], dtype=torch.int32, device="cuda")
+    need = aq.workspace_bytes(aq.WS_FWD_INFER_MX_PAGED, B + 1, Hq, Hkv, Lq, d)
+    run = lambda nbytes: aq.attnqat_fwd_infer_mx_paged(q, cache, sum(pages), table, kl, Hkv, causal,  # noqa: E731
+                                                       workspace=torch.empty(nbytes, dtype=torch.uint8, device="cuda"))
+    (o, lse), (o2, lse2) = run(need), run(need - 1)
+    assert bool((o[B] == 0).all()) and bool(torch.isneginf(lse[B]).all())
+    # fp32 sums of the same terms (errors of 2^-24 times the sum of their magnitudes), one rounding to bf16 each
+    a, r = o.float(), o2.float()
+    assert bool(((a - r).abs() <= 2.0 ** -7 * r.abs() + 1e-5 * r.abs().max()).all())
+    assert float((lse[:B] - lse2[:B]).abs().max()) <= 2e-5 * float(lse2[:B].abs().max())
