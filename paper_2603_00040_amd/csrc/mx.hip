@@ -367,6 +367,227 @@ __global__ __launch_bounds__(256, 2) void fwd_mx_kernel(
     }
 }
 
+// The same where there are too few query rows to fill the chip (see fwd_split_kernel in fwd.hip): a workgroup owns 32 rows, its four waves take
+// four key tiles at a time, wave w tile 4 n + w for the scores, the softmax and phi(P-tilde), and block w of 32 d of O for the products of
+// all four.  P crosses LDS as the codes and scale bytes that the instruction takes (1.25 KiB per tile), K and V operands go straight to
+// registers.  All sums keep their order: the bits of fwd_mx_kernel.  KVM: 0 contiguous, 1 paged, 2 block-sparse, as there.
+template <int D, bool CAUSAL, bool FP8PV, int KVM>
+__global__ __launch_bounds__(256, 2) void fwd_mx_split_kernel(
+    const unsigned char* __restrict__ qops, const uint32_t* __restrict__ qsc, const unsigned char* __restrict__ kv,
+    uint16_t* __restrict__ O, float* __restrict__ lse, int L, int Lp, int Hq, int G, float c /* log2(e)/sqrt(d) */,
+    const int* __restrict__ page_table, const int* __restrict__ kv_lens, int max_pages, int num_pages, int lq_inner, int B)
+{
+    constexpr int KS = D / 64, MT = D / 32, NT = 4, VW = FP8PV ? 2 : 1;     // VW: 16-byte pieces of a lane's V operand and of its codes of P
+    constexpr bool PAGED = KVM == 1, SPARSE = KVM == 2;
+    constexpr int KOPS = 2 * KS * 1024, VOPS = MT * VW * 1024, REC = mx_rec_bytes(D, FP8PV);
+    __shared__ __align__(16) uint4v p_codes[NT][VW][64];
+    __shared__ uint32_t p_byte[NT][64];
+    __shared__ float x_max[NT][32], x_alpha[NT][32], x_sum[NT][64];
+
+    const int n32 = (L + 31) / 32, nqt = Lp / 128;
+    int bh, qt;
+    if (CAUSAL && !PAGED) { longest_first(blockIdx.x, B * Hq, n32, bh, qt); qt = n32 - 1 - qt; }
+    else head_tile_of_block(blockIdx.x, B * Hq, n32, bh, qt);
+    const int b = bh / Hq, h = bh % Hq, bhkv = b * (Hq / G) + h / G, Hkv = Hq / G;
+    const int lane = threadIdx.x & 63, ln = lane & 31, hf = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int row0 = qt * 32, q_row = row0 + ln;
+    uint4v qop[KS];
+    const size_t grp = (size_t)bh * (Lp / 32) + qt;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) qop[ks] = *reinterpret_cast<const uint4v*>(qops + ((grp * KS + ks) * 64 + lane) * 16);
+    const uint32_t qs = qsc[grp * 64 + lane];
+
+    const int Lk = PAGED ? __builtin_amdgcn_readfirstlane(kv_lens[b]) : L;
+    const int koff = PAGED ? Lk - lq_inner : 0;
+    const bool packed = PAGED && lq_inner != L;
+    const int nkt_all = PAGED ? min((Lk + 63) / 64, 2 * max_pages) : (Lk + 63) / 64;
+    // block-sparse: the list of this row block, and how many of its blocks these rows see at least in part (they are in increasing order)
+    const int* blk_row = SPARSE ? page_table + ((size_t)bh * nqt + (qt >> 2)) * max_pages : nullptr;
+    int nkt;
+    if constexpr (SPARSE) {
+        const int listed = min(max(__builtin_amdgcn_readfirstlane(kv_lens[(size_t)bh * nqt + (qt >> 2)]), 0), max_pages);
+        int seen = 0;
+        for (int i = 0; i < listed; i += 64)
+            seen += __popcll(__builtin_amdgcn_ballot_w64(i + lane < listed && (!CAUSAL || blk_row[min(i + lane, listed - 1)] * 128 <= row0 + 31)));
+        nkt = 2 * seen;
+    } else nkt = CAUSAL && !packed ? min((koff + row0 + 31) / 64 + 1, nkt_all) : nkt_all;
+    auto blk_of = [&](int s) __attribute__((always_inline)) -> int {
+        return min(max(__builtin_amdgcn_readfirstlane(blk_row[s]), 0), Lp / 128 - 1);      // a bad entry reads a wrong block, never outside
+    };
+    auto k0_of = [&](int j) __attribute__((always_inline)) -> int { return SPARSE ? blk_of(j >> 1) * 128 + (j & 1) * 64 : j * 64; };
+    if (SPARSE && CAUSAL && nkt > 0 && k0_of(nkt - 1) > row0 + 31) --nkt;                   // (the last block's second half)
+    const unsigned char* kv_head = kv + (size_t)bhkv * (Lp / 64) * REC;
+    auto rec_of = [&](int j_) __attribute__((always_inline)) -> const unsigned char* {      // (beyond the last tile: the last one)
+        const int j = min(j_, nkt - 1);
+        if constexpr (PAGED) {
+            int page = __builtin_amdgcn_readfirstlane(page_table[(size_t)b * max_pages + (j >> 1)]);
+            page = min(max(page, 0), num_pages - 1);               // a bad table entry reads a wrong page, never outside the cache
+            return kv + (((size_t)page * Hkv + (h / G)) * 2 + (j & 1)) * REC;
+        }
+        return kv_head + (size_t)(SPARSE ? 2 * blk_of(j >> 1) + (j & 1) : j) * REC;
+    };
+    auto as8 = [](const uint4v& x) __attribute__((always_inline)) -> int8v {
+        int8v r = {(int)x[0], (int)x[1], (int)x[2], (int)x[3], 0, 0, 0, 0};
+        return r;
+    };
+    const bool has_o = wave < MT;
+    const int mt = has_o ? wave : 0;
+    uint4v kr[2 * KS], vr[NT][VW];
+    uint32_t ksc = 0u, vsc[NT];
+    auto load_k = [&](const unsigned char* rec) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 2 * KS; ++i) kr[i] = *reinterpret_cast<const uint4v*>(rec + 1024 * i + 16 * lane);
+        ksc = *reinterpret_cast<const uint32_t*>(rec + KOPS + VOPS + 4 * lane);
+    };
+    auto load_v = [&](int t, const unsigned char* rec) __attribute__((always_inline)) {
+#pragma unroll
+        for (int w = 0; w < VW; ++w) vr[t][w] = *reinterpret_cast<const uint4v*>(rec + KOPS + ((mt * VW + w) * 64 + lane) * 16);
+        vsc[t] = *reinterpret_cast<const uint32_t*>(rec + KOPS + VOPS + 256 + 4 * lane) >> (8 * mt);
+    };
+    auto lds_barrier = [&]() __attribute__((always_inline)) {       // what was written to LDS is there, what was read has arrived
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0xC07F);                         // lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    floatx16 o;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) o[i] = 0.0f;
+    float m = -INFINITY, lsum = 0.0f;
+    if (nkt > 0) {
+        load_k(rec_of(wave));
+#pragma unroll
+        for (int t = 0; t < NT; ++t) load_v(t, rec_of(t));
+    }
+    for (int j0 = 0; j0 < nkt; j0 += NT) {
+        const int j = j0 + wave, nt = min(nkt - j0, NT);
+        const bool active = wave < nt;
+        floatx16 s[2];
+        if (active) {
+            const floatx16 zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+            s[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr[0]), as8(qop[0]), zero, 4, 4, 0, ksc, 0, qs);
+            s[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr[KS]), as8(qop[0]), zero, 4, 4, KS, ksc, 0, qs);
+            if constexpr (KS == 2) {
+                s[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr[1]), as8(qop[1]), s[0], 4, 4, 1, ksc, 1, qs);
+                s[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr[3]), as8(qop[1]), s[1], 4, 4, 3, ksc, 1, qs);
+            }
+            mfma_scale_settle(s[0], s[1]);
+        }
+        const bool more = j0 + NT < nkt;
+        if (more) load_k(rec_of(j + NT));
+        float mown = -INFINITY;
+        if (active) {
+            const int k0 = k0_of(j);
+            if ((k0 + 64 > Lk) || (CAUSAL && k0 + 63 > koff + (packed ? 0 : row0))) {
+                const int klim = CAUSAL ? min(Lk - 1, koff + (packed ? q_row % lq_inner : q_row)) : Lk - 1;
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i)
+                        if (k0 + 32 * hf + 16 * t + i > klim) s[t][i] = -INFINITY;
+            }
+            float mp[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) mp[t] = max_raw(s[0][t], s[1][t]);
+#pragma unroll
+            for (int i = 4; i < 16; ++i) mp[i & 3] = max_nc(max_nc(mp[i & 3], s[0][i]), s[1][i]);
+            mown = max_nc(max_nc(mp[0], mp[1]), max_nc(mp[2], mp[3]));              // maximum of this lane's block
+            const float mt_ = xhalf_max(mown);
+            if (hf == 0) x_max[wave][ln] = mt_;
+        }
+        lds_barrier();
+        float m_next = m, m_prev = m, mnew = m;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const float x = x_max[t][ln];
+            if (t < wave) m_prev = max_nc(m_prev, x);
+            if (t <= wave) mnew = max_nc(mnew, x);
+            if (t < nt) m_next = max_nc(m_next, x);
+        }
+        m = m_next;
+        if (active) {
+            // (block-sparse: see fwd_mx_kernel)
+            const float mref = (SPARSE && mnew == -INFINITY) ? 0.0f : mnew;
+            const float alpha = __builtin_amdgcn_exp2f((m_prev - mref) * c);
+            const float ms = mref * c;
+            float p[32];
+            float rp[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    p[16 * t + i] = __builtin_amdgcn_exp2f(fmaf(s[t][i], c, -ms));
+                    rp[i & 3] += p[16 * t + i];
+                }
+            x_sum[wave][lane] = (rp[0] + rp[1]) + (rp[2] + rp[3]);                      // un-quantized P-tilde
+            if (hf == 0) x_alpha[wave][ln] = alpha;
+            const float amax = __builtin_amdgcn_exp2f(fmaf(mown, c, -ms));
+            const uint32_t pbyte = FP8PV ? e8m0_of_amax_fp8(amax) : e8m0_of_amax(amax);
+            if constexpr (FP8PV) {
+                uint32_t own[8];
+                mx_codes32_fp8(p, e8m0_as_f32(pbyte), own);
+                uint4v lo, hi;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    auto r = __builtin_amdgcn_permlane32_swap(own[i], own[4 + i], false, false);
+                    lo[i] = r[0]; hi[i] = r[1];
+                }
+                p_codes[wave][0][lane] = lo;
+                p_codes[wave][VW - 1][lane] = hi;
+            } else p_codes[wave][0][lane] = mx_codes32(p, e8m0_as_f32(pbyte));
+            p_byte[wave][lane] = pbyte;
+        }
+        lds_barrier();                                              // P, alpha and the sums are in LDS
+        uint4v pc[NT][VW];
+        uint32_t pb[NT];
+        float al[NT], sm[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            al[t] = x_alpha[t][ln]; sm[t] = x_sum[t][lane]; pb[t] = p_byte[t][lane];
+#pragma unroll
+            for (int w = 0; w < VW; ++w) pc[t][w] = p_codes[t][w][lane];
+        }
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            if (t < nt) {
+                lsum = lsum * al[t] + sm[t];                        // l in tile order
+                if (has_o) {
+                    if (__builtin_amdgcn_ballot_w64(al[t] != 1.0f) != 0) {
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) o[i] *= al[t];
+                    }
+                    if constexpr (FP8PV) {
+                        const int8v va = {(int)vr[t][0][0], (int)vr[t][0][1], (int)vr[t][0][2], (int)vr[t][0][3],
+                                          (int)vr[t][VW - 1][0], (int)vr[t][VW - 1][1], (int)vr[t][VW - 1][2], (int)vr[t][VW - 1][3]};
+                        const int8v pv = {(int)pc[t][0][0], (int)pc[t][0][1], (int)pc[t][0][2], (int)pc[t][0][3],
+                                          (int)pc[t][VW - 1][0], (int)pc[t][VW - 1][1], (int)pc[t][VW - 1][2], (int)pc[t][VW - 1][3]};
+                        o = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(va, pv, o, 0, 0, 0, vsc[t], 0, pb[t]);
+                    } else o = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(vr[t][0]), as8(pc[t][0]), o, 4, 4, 0, vsc[t], 0, pb[t]);
+                }
+            }
+        }
+        mfma_scale_settle(o);
+        if (more && has_o) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t) load_v(t, rec_of(j0 + NT + t));
+        }
+    }
+    const float l = xhalf_sum(lsum);
+    const float inv_l = ((PAGED || SPARSE) && !(l > 0.0f)) ? 0.0f : 1.0f / l;         // a row without keys: O = 0, L = -inf
+    if (q_row < L && has_o) {
+        const size_t row = (size_t)bh * L + q_row;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            uint2v w;
+            w[0] = pack_bf16x2_rne(o[4 * t] * inv_l, o[4 * t + 1] * inv_l);
+            w[1] = pack_bf16x2_rne(o[4 * t + 2] * inv_l, o[4 * t + 3] * inv_l);
+            *reinterpret_cast<uint2v*>(O + row * D + 32 * mt + 8 * t + 4 * hf) = w;
+        }
+        if (hf == 0 && wave == 0) lse[row] = m * (c * 0.6931471805599453f) + logf(l);
+    }
+}
+
 // ---------------------------------------------------------------------------------------------
 // Decode form of the paged forward: at most 32 query rows per (sequence, kv head) — one position, or a few, of the G
 // query heads of a group — against a long sequence.  fwd_mx_kernel would leave three of its four waves without rows
@@ -786,6 +1007,18 @@ size_t mx_qops_bytes(int BHq, int L, int D) { return (size_t)BHq * round_up(L, k
 size_t mx_qsc_bytes(int BHq, int L) { return (size_t)BHq * (round_up(L, kRowPad) / 32) * 64 * 4; }
 size_t mx_page_bytes(int D) { return 2 * (size_t)mx_rec_bytes(D, false); }
 
+// Whether the key tiles are shared (fwd_mx_split_kernel): by the number of 32-row groups per compute unit, as split_key_tiles in fwd.hip.  Rows of
+// one length: three, as many as share a unit (two in the mixed recipe): d = 128, 8 heads, L = 2000 (504 groups) 34.8 -> 25.3 us, L = 3000 (752)
+// 47.6 -> 41.1 us, 32 heads, L = 777 (800) 22.7 -> 26.5 us; mixed recipe 37.0 -> 27.9 us, 51 -> 59 us; chunks of a prefill, 8 sequences of
+// 2000 - 8000 (512) 101 -> 70 us.  Causal: five, fewer for short rows: 12 heads, L = 2300 (864) 41.7 -> 30.2 us, 8 heads, L = 5000 (1256)
+// 76 -> 56 us, 64 heads, L = 256 (512) 12.8 -> 11.4 us, L = 500 (1024) 18.7 -> 19.2 us, 32 heads, L = 2500 (2528) 54 -> 63 us.  Block-sparse under it
+// (0.3 of the blocks): six: 32 heads, L = 1500 (1504) 30.5 -> 27.0 us, L = 2500 (2528) 42.4 -> 44.9 us.
+static bool mx_split_key_tiles(int heads, int L, bool causal, bool fp8pv, bool sparse)
+{
+    const long long cus = device_cu_count(), n32 = (L + 31) / 32, per = causal ? min((long long)(sparse ? 6 : 5), 1 + n32 / 8) : fp8pv ? 2 : 3;
+    return heads * n32 <= per * cus;
+}
+
 template <int D, bool CAUSAL, bool FP8PV, int KVM>
 static int launch_fwd_mx_t(const void* qops, const void* qsc, const void* kv, int B, int Hq, int Hkv, int L,
                            void* o, float* lse, const int* page_table, const int* kv_lens, int max_pages, int num_pages, int lq_inner,
@@ -793,10 +1026,18 @@ static int launch_fwd_mx_t(const void* qops, const void* qsc, const void* kv, in
 {
     const int Lp = round_up(L, kRowPad);
     const size_t smem = 3 * 2 * (size_t)mx_rec_bytes(D, FP8PV);
+    const float c = 1.4426950408889634f / sqrtf((float)D);
+    if constexpr (KVM != 3) {
+        if (mx_split_key_tiles(B * Hq, L, CAUSAL && KVM != 1, FP8PV, KVM == 2)) {
+            hipLaunchKernelGGL((fwd_mx_split_kernel<D, CAUSAL, FP8PV, KVM>), dim3((unsigned)(B * Hq * ((L + 31) / 32))), dim3(256), 0, st,
+                               (const unsigned char*)qops, (const uint32_t*)qsc, (const unsigned char*)kv,
+                               (uint16_t*)o, lse, L, Lp, Hq, Hq / Hkv, c, page_table, kv_lens, max_pages, num_pages, lq_inner, B);
+            return hipGetLastError() == hipSuccess ? 0 : -1;
+        }
+    }
     auto kern = fwd_mx_kernel<D, CAUSAL, FP8PV, KVM>;
     static unsigned long long lds_set = 0;          // one per instantiation
     if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)smem, lds_set)) return -1;
-    const float c = 1.4426950408889634f / sqrtf((float)D);
     const int groups = KVM == 3 ? round_up(B * Hkv, 8) : B * Hkv;       // (see varlen_item)
     hipLaunchKernelGGL(kern, dim3((unsigned)(groups * (Hq / Hkv) * (Lp / 128))), dim3(256), smem, st,
                        (const unsigned char*)qops, (const uint32_t*)qsc, (const unsigned char*)kv,
@@ -870,7 +1111,8 @@ int launch_fwd_mx_paged(const void* qops, const void* qsc, const void* cache, in
     // With no more workgroups than compute units each has one of its own, and no order is worth looking up.  A kernel of its own: with
     // both in one the key loop came out 1.5 - 2 % slower, of the same instructions in other registers (16/2 heads, 500 positions over
     // 15k keys: 112.2 -> 114.4 us; 8 sequences of 16/4 heads, 98 positions over 2k - 7k keys: 87.4 -> 88.8 us).
-    const bool by_length = (long long)B * Hq * (round_up(Lq, kRowPad) / 128) > device_cu_count();
+    // (few query rows: the kernel in which four waves share the key tiles takes the plain order, too)
+    const bool by_length = (long long)B * Hq * (round_up(Lq, kRowPad) / 128) > device_cu_count() && !mx_split_key_tiles(B * Hq, Lq, false, false, false);
 #define AQ_PAGED_K(DD, CC, KK) launch_fwd_mx_t<DD, CC, false, KK>(qops, qsc, cache, B, Hq, Hkv, Lq, o, lse, page_table, kv_lens, max_pages, num_pages, lq_inner, st)
 #define AQ_PAGED(DD, CC) (by_length ? AQ_PAGED_K(DD, CC, 3) : AQ_PAGED_K(DD, CC, 1))
     if (D == 128) return causal ? AQ_PAGED(128, true) : AQ_PAGED(128, false);
