@@ -136,9 +136,13 @@ __device__ __forceinline__ void bwd_dq_body(const DqArgs& A, int bh, int qt)
         }
     }
     const float2 st_ = rowstat[(size_t)bh * Lp + q_ld];
-    const float Ls = st_.x;                                          // L_i log2(e)
     // dS of this row goes to fp16 after multiplication by ds_scale = 2^k, k from the bound
-    // (|dO_i| max_j |V^F_j| + |D_i|) / sqrt(d) >= |dS_ij|; rs_s and Dq_s carry the factor.
+    // (|dO_i| max_j |V^F_j| + |D_i|) / sqrt(d) >= |dS_ij|.  FOLD: 2^k and 1 / sqrt(d) go into the exponent of P and -D_i is what the
+    // accumulators of dP start from, so that dS is one multiplication (32 of 112 vector instructions of a tile, which add to the time of
+    // its 48 products: the same tree otherwise, in turn, 4 x 32/8 heads, L = 4096 causal 2922 -> 2884 us, 40 heads, L = 75600 418.7 ->
+    // 416.3 ms, MX 4 x 8/2 heads, L = 3124 759 -> 749 us; MX of d = 128 under a causal mask lost, 2 x 16/4 heads, L = 3001 428.0 -> 429.7 us;
+    // d = 64 265.8 -> 260.0 us).
+    constexpr bool FOLD = !(MXS && CAUSAL && D == 128);
     float ds_scale;
     {
         float n2 = 0.0f;
@@ -153,7 +157,12 @@ __device__ __forceinline__ void bwd_dq_body(const DqArgs& A, int bh, int qt)
         const float vmax = bound_of(bound_part, NHq, 0, bhkv);
         ds_scale = ds_scale_for((sqrtf(n2) * 1.0001f * vmax) * rs + fabsf(st_.y));
     }
-    const float rs_s = rs * ds_scale, Dq_s = st_.y * ds_scale;        // D_i / sqrt(d), scaled
+    // L_i log2(e) - k - log2(1 / sqrt(d))  (3.5 and 3 are exact)
+    const float Ls = st_.x - (FOLD ? (float)((int)(__float_as_uint(ds_scale) >> 23) - 127) - (D == 128 ? 3.5f : 3.0f) : 0.0f);
+    const float rs_s = rs * ds_scale, Dq_s = st_.y * ds_scale;        // (not FOLD) D_i / sqrt(d), scaled
+    floatx16 dp0;                                                    // what dP starts from: -D_i in every register
+#pragma unroll
+    for (int i = 0; i < 16; ++i) dp0[i] = FOLD ? -st_.y / rs : 0.0f;
 
     const int nkt_all = (L + 63) / 64;
     const int nkt = CAUSAL ? min((qt + 1) * (QT / 64), nkt_all) : nkt_all;
@@ -198,6 +207,9 @@ __device__ __forceinline__ void bwd_dq_body(const DqArgs& A, int bh, int qt)
 #pragma unroll
         for (int v = 0; v < 2; ++v)
             toff[mb][v] = k0_ad + 2u * (uint32_t)swz_elem<KCH>(4 * hf + (tr_r >> 2) + 8 * v, 32 * mb + 16 * tr_grp + 4 * (tr_r & 3));
+    // (opaque: the addition of the base of LDS, which is zero, is otherwise left for every tile, eight instructions)
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) asm volatile("" : "+v"(toff[mb][0]), "+v"(toff[mb][1]));
     constexpr uint32_t kTileB = 64 * D * 2, kVfromK = 2 * kTileB;      // bytes of a tile buffer; sm.v[b] lies kVfromK after sm.k[b]
 
     floatx16 acc[MB];
@@ -220,7 +232,12 @@ __device__ __forceinline__ void bwd_dq_body(const DqArgs& A, int bh, int qt)
         for (int ks = 0; ks < KSM; ++ks) asm volatile("" : "+v"(qop[ks]));
         asm volatile("" : "+v"(qs));
     }
-    asm volatile("" :: "v"(Ls), "v"(rs_s), "v"(Dq_s));
+    asm volatile("" :: "v"(Ls));
+    // (opaque: sixteen equal values would otherwise be one register, copied sixteen times in front of every chain of products)
+    if constexpr (FOLD) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) asm volatile("" : "+v"(dp0[i]));
+    } else asm volatile("" :: "v"(rs_s), "v"(Dq_s));
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
 
@@ -257,18 +274,14 @@ __device__ __forceinline__ void bwd_dq_body(const DqArgs& A, int bh, int qt)
 #pragma unroll
                 for (int i = 0; i < RING; ++i) ring[i] = opnd(i);
 #pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) dp[kb][i] = 0.0f;
-#pragma unroll
                 for (int i = 0; i < NST; ++i) {
                     const uint4v av = ring[i % RING];
                     if (i + RING < NST) ring[i % RING] = opnd(i + RING);
-                    dp[i & 1] = mfma_bf16(av, doreg[i >> 1], dp[i & 1]);
+                    dp[i & 1] = mfma_bf16(av, doreg[i >> 1], i < 2 ? dp0 : dp[i & 1]);
                 }
             } else
             {   // S^T = K^F Q^F^T and dP^T = V^F dO^T: 4*DS steps, step i: ds = i/4, kb = (i/2)%2, K or V = i%2
-                constexpr int NST = 4 * DS, RING = 6;
+                constexpr int NST = 4 * DS, RING = D == 128 ? 5 : 6;      // (six operands of d = 128 do not fit beside dp0)
                 auto opnd = [&](int i) __attribute__((always_inline)) -> uint4v {
                     return lds_read16_at(koff[i >> 2] + (uint32_t)(BUF * kTileB + (i & 1) * kVfromK + ((i >> 1) & 1) * (32 * D * 2)));
                 };
@@ -278,13 +291,13 @@ __device__ __forceinline__ void bwd_dq_body(const DqArgs& A, int bh, int qt)
 #pragma unroll
                 for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) { s[kb][i] = 0.0f; dp[kb][i] = 0.0f; }
+                    for (int i = 0; i < 16; ++i) s[kb][i] = 0.0f;
 #pragma unroll
                 for (int i = 0; i < NST; ++i) {
                     const uint4v a = ring[i % RING];
                     if (i + RING < NST) ring[i % RING] = opnd(i + RING);
                     const int kb = (i >> 1) & 1, ds = i >> 2;
-                    if (i & 1) dp[kb] = mfma_bf16(a, doreg[ds], dp[kb]);
+                    if (i & 1) dp[kb] = mfma_bf16(a, doreg[ds], ds == 0 ? dp0 : dp[kb]);
                     else       s[kb] = mfma_f16(a, qreg[ds], s[kb]);
                 }
                 __builtin_amdgcn_sched_group_barrier(0x100, RING, 0);
@@ -320,10 +333,11 @@ __device__ __forceinline__ void bwd_dq_body(const DqArgs& A, int bh, int qt)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int r0 = 8 * g + 2 * i;
-                    const float p0 = __builtin_amdgcn_exp2f(fmaf(s[kb][r0], c, -Ls));           // P = exp(S - L_i)
+                    const float p0 = __builtin_amdgcn_exp2f(fmaf(s[kb][r0], c, -Ls));           // P = exp(S - L_i) (FOLD: times 2^k / sqrt(d))
                     const float p1 = __builtin_amdgcn_exp2f(fmaf(s[kb][r0 + 1], c, -Ls));
-                    // dS = P (dP - D_i)/sqrt(d), times ds_scale, to fp16
-                    bds[i] = pack_f16x2(p0 * fmaf(dp[kb][r0], rs_s, -Dq_s), p1 * fmaf(dp[kb][r0 + 1], rs_s, -Dq_s));
+                    // dS = P (dP - D_i)/sqrt(d), times 2^k, to fp16
+                    if constexpr (FOLD) bds[i] = pack_f16x2(p0 * dp[kb][r0], p1 * dp[kb][r0 + 1]);
+                    else bds[i] = pack_f16x2(p0 * fmaf(dp[kb][r0], rs_s, -Dq_s), p1 * fmaf(dp[kb][r0 + 1], rs_s, -Dq_s));
                 }
 #pragma unroll
                 for (int mb = 0; mb < MB; ++mb) acc[mb] = mfma_f16(at[mb], bds, acc[mb]);
@@ -339,7 +353,7 @@ __device__ __forceinline__ void bwd_dq_body(const DqArgs& A, int bh, int qt)
 
     if (q_row < L && wave_live) {
         const size_t row = (size_t)bh * L + q_row;
-        const float un = rs / rs_s;                                  // 1 / ds_scale, exact: a power of two
+        const float un = 1.0f / ds_scale;                            // exact: a power of two
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
