@@ -176,7 +176,7 @@ __device__ inline void mx_block_list(const unsigned char* __restrict__ mask, int
 // A workgroup takes 64 positions of V (in a backward the chunk of a head's 64-row tiles that one partial maximum covers), 256 blocks
 // of 32 values of Q or K, four rows of the mask, or a chunk of dO.
 template <int D, MxKind KIND>
-__global__ __launch_bounds__(256) void mx_group_kernel(MxGroup g, unsigned nblocks)
+__global__ __launch_bounds__(256, 5) void mx_group_kernel(MxGroup g, unsigned nblocks)
 {
     constexpr int NB = D / 32, RW = 256 / NB;       // blocks per row, rows of Q or K per workgroup
     __shared__ uint16_t tile[64][D + 2];

@@ -14,34 +14,58 @@ __host__ __device__ inline int bound_chunk_tiles(int tiles) { return (tiles + kB
 // copy of dO where one is asked for (dob).  D is added up eight elements at a time (pairs 0, 2, 1, 3 of them), then over the groups of
 // eight in a tree whose last level joins neighbours: which order the sum has is part of the result's bits, so the two groups of a
 // thread stay apart until the end.
+template <int D>
 __device__ __forceinline__ void grad_tile(int bh, int l0, const uint16_t* __restrict__ dO, const void* __restrict__ o_acc, bool o_is_bf16,
-                                          const float* __restrict__ lse, int L, int Lp, int D, float rs,
+                                          const float* __restrict__ lse, int L, int Lp, float rs,
                                           float2* __restrict__ rowstat, uint16_t* __restrict__ dob, float& n2, float& dmax)
 {
-    const int nb = D / 16;
-    for (int blk = threadIdx.x; blk < 64 * nb; blk += 256) {
-        const int row = blk / nb, cb = blk % nb, l = l0 + row;
-        uint4v g[2] = {};
-        float dot8[2] = {0.0f, 0.0f}, nrm = 0.0f;
+    constexpr int nb = D / 16, NI = nb / 4;        // blocks of 16 elements per row, and of the 64 rows per thread
+    // (opaque: the addresses of every variant would otherwise be formed in front of the loop over tiles and held in registers)
+    uint32_t tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int cb = (int)(tid % nb), row0 = (int)(tid / nb);
+    // the loads of all blocks of a thread first: one trip to memory instead of one per block
+    uint4v g_[NI][2] = {};
+    floatx4 w_[NI][4] = {};
+    float lse_[NI] = {};
+#pragma unroll
+    for (int it = 0; it < NI; ++it) {
+        const int l = l0 + row0 + it * (256 / nb);
         if (l < L) {
             const size_t off = ((size_t)bh * L + l) * D + cb * 16;
-            g[0] = reinterpret_cast<const uint4v*>(dO + off)[0];
-            g[1] = reinterpret_cast<const uint4v*>(dO + off)[1];
-            float o[16];
+            g_[it][0] = reinterpret_cast<const uint4v*>(dO + off)[0];
+            g_[it][1] = reinterpret_cast<const uint4v*>(dO + off)[1];
             if (o_is_bf16) {                       // ablation: D from the low-precision output
 #pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    const uint4v w = reinterpret_cast<const uint4v*>(static_cast<const uint16_t*>(o_acc) + off)[t];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) { o[8 * t + 2 * i] = __uint_as_float(w[i] << 16); o[8 * t + 2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u); }
-                }
+                for (int t = 0; t < 2; ++t) w_[it][t] = reinterpret_cast<const floatx4*>(static_cast<const uint16_t*>(o_acc) + off)[t];
             } else {
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const floatx4 w = reinterpret_cast<const floatx4*>(static_cast<const float*>(o_acc) + off)[t];
+                for (int t = 0; t < 4; ++t) w_[it][t] = reinterpret_cast<const floatx4*>(static_cast<const float*>(o_acc) + off)[t];
+            }
+            if (cb == 0) lse_[it] = lse[(size_t)bh * L + l];
+        }
+    }
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) o[4 * t + i] = w[i];
-                }
+    for (int it = 0; it < NI; ++it) {
+        __builtin_amdgcn_sched_barrier(0);         // (one block after the other: the registers of two at once would cost wavefronts)
+        const int l = l0 + row0 + it * (256 / nb);
+        const uint4v (&g)[2] = g_[it];
+        float dot8[2] = {0.0f, 0.0f}, nrm = 0.0f;
+        if (l < L) {
+            float o[16];
+            if (o_is_bf16) {
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const uint32_t w = __float_as_uint(w_[it][t][i]);
+                        o[8 * t + 2 * i] = __uint_as_float(w << 16); o[8 * t + 2 * i + 1] = __uint_as_float(w & 0xFFFF0000u);
+                    }
+            } else {
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) o[4 * t + i] = w_[it][t][i];
             }
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
@@ -58,9 +82,10 @@ __device__ __forceinline__ void grad_tile(int bh, int l0, const uint16_t* __rest
                 }
             }
         }
+#pragma unroll
         for (int w = nb / 2; w >= 1; w >>= 1) { dot8[0] += __shfl_xor(dot8[0], w); dot8[1] += __shfl_xor(dot8[1], w); nrm += __shfl_xor(nrm, w); }
         const float dot = (dot8[0] + dot8[1]) * rs;
-        if (cb == 0) rowstat[(size_t)bh * Lp + l] = make_float2(l < L ? lse[(size_t)bh * L + l] * 1.4426950408889634f : 0.0f, dot);
+        if (cb == 0) rowstat[(size_t)bh * Lp + l] = make_float2(l < L ? lse_[it] * 1.4426950408889634f : 0.0f, dot);
         n2 = fmaxf(n2, nrm);
         dmax = fmaxf(dmax, fabsf(dot));
         if (dob) {
@@ -90,7 +115,8 @@ __device__ inline void write_bound(float* part, int ch, int nch, float value) {
 __device__ __forceinline__ void grad_chunk(const GradArgs& a, int bh, int ch, int per, int nch, int BHq, int L, int Lp, int D, float (&red)[4]) {
     float n2 = 0.0f, dmax = 0.0f;
     for (int t = ch * per; t < min(Lp / 64, (ch + 1) * per); ++t)
-        grad_tile(bh, t * 64, a.d_o, a.o_acc, a.o_is_bf16, a.lse, L, Lp, D, a.rs, a.rowstat, a.dob, n2, dmax);
+        if (D == 128) grad_tile<128>(bh, t * 64, a.d_o, a.o_acc, a.o_is_bf16, a.lse, L, Lp, a.rs, a.rowstat, a.dob, n2, dmax);
+        else          grad_tile<64>(bh, t * 64, a.d_o, a.o_acc, a.o_is_bf16, a.lse, L, Lp, a.rs, a.rowstat, a.dob, n2, dmax);
     write_bound(a.bounds + ((size_t)BHq + bh) * kBoundParts, ch, nch, sqrtf(wg_max(n2, red)) * 1.0001f);      // rounded up a little: it is an upper bound
     write_bound(a.bounds + ((size_t)2 * BHq + bh) * kBoundParts, ch, nch, wg_max(dmax, red));
 }
