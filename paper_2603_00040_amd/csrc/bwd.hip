@@ -547,12 +547,22 @@ __device__ __forceinline__ void bwd_dkdv_body(const DkvArgs& A, int bhkv, int kt
     // (max_i |dO_i| max_j |V^F_j| + max_i |D_i|) / sqrt(d) >= |dS_ij| over the query heads of the group
     float ds_scale;
     {
-        float domax = 0.0f, dmax = 0.0f;
-        for (int g = 0; g < G; ++g) {
-            domax = fmaxf(domax, bound_of(bound_part, NHq, 1, (int)bh0 + g));
-            dmax = fmaxf(dmax, bound_of(bound_part, NHq, 2, (int)bh0 + g));
+        // (the heads are joined lane by lane, four loads on their way at a time, and the lanes once for all of them)
+        const float* p = bound_part + (size_t)bhkv * kBoundParts + (tid & 63);
+        const float *p1 = bound_part + ((size_t)NHq + bh0) * kBoundParts + (tid & 63), *p2 = p1 + (size_t)NHq * kBoundParts;
+        float vmax = *p, domax = 0.0f, dmax = 0.0f;
+        for (int g0 = 0; g0 < G; g0 += 4) {
+            float a[4], e[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) { const size_t o = (size_t)min(g0 + i, G - 1) * kBoundParts; a[i] = p1[o]; e[i] = p2[o]; }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) { domax = fmaxf(domax, a[i]); dmax = fmaxf(dmax, e[i]); }
         }
-        ds_scale = ds_scale_for(domax * bound_of(bound_part, NHq, 0, bhkv) * rs + dmax);
+#pragma unroll
+        for (int w = 32; w >= 1; w >>= 1) {
+            vmax = fmaxf(vmax, __shfl_xor(vmax, w)); domax = fmaxf(domax, __shfl_xor(domax, w)); dmax = fmaxf(dmax, __shfl_xor(dmax, w));
+        }
+        ds_scale = ds_scale_for(domax * vmax * rs + dmax);
     }
     const float rs_s = rs * ds_scale;
 
