@@ -458,7 +458,7 @@ int attnqat_debug_fwd_p_mx(const void* q, const void* k, const void* v,
  * on it adds to counts[0] the number of tiles the pass visited and to counts[1] the number with a non-zero P^F.
  * NULL switches it off (the default).
  *
- * attnqat_debug_bwd_waves: problems whose workgroups fill the compute units evenly run the dQ and the dK/dV pass one after
+ * attnqat_debug_bwd_waves: problems of d = 128 whose workgroups fill the compute units evenly run the dQ and the dK/dV pass one after
  * another, with workgroups of 4 waves (128 query rows / 128 keys) or, where that leaves enough of them, 8 waves (256); both
  * compute the same sums over the same tiles in the same order.  All others run both passes in one launch of 4-wave workgroups,
  * in which several workgroups may share the sum over the queries of a key tile (fp32 partial sums, added in a fixed order).

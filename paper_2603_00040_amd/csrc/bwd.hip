@@ -100,6 +100,11 @@ __device__ __forceinline__ void bwd_dq_body(const DqArgs& A, int bh, int qt)
 {
     constexpr int DS = D / 16, MB = D / 32, KCH = D / 8, KLD = KCH / NW, QT = 32 * NW /* query rows of a workgroup */;
     constexpr int KSM = D / 64, KREC = mx_ktrain_rec_bytes(D);
+    // 32-key blocks of a tile whose S and dP are computed at a time.  One, where that brings the registers down to those of three
+    // wavefronts per SIMD (d = 64; both blocks of d = 64 in MX fit as they are): with two, every wavefront waits for its own chains
+    // of products and exponentials.  2 x 16/4 heads, L = 3001, d = 64 causal, training step 312 -> 290 us, MX 266.6 -> 263.5 us; 12 heads,
+    // L = 2000, where there are no three workgroups per compute unit, 127 us as before.
+    constexpr int KH = D == 64 && !MXS ? 1 : 2;
     extern __shared__ __align__(256) unsigned char smem_raw[];
     DqSmem<D, MXS>& sm = *reinterpret_cast<DqSmem<D, MXS>*>(smem_raw);
     const uint16_t *__restrict__ Qb = A.Qb, *__restrict__ Kb = A.Kb, *__restrict__ Vb = A.Vb, *__restrict__ dOb = A.dOb;
@@ -141,7 +146,7 @@ __device__ __forceinline__ void bwd_dq_body(const DqArgs& A, int bh, int qt)
     // accumulators of dP start from, so that dS is one multiplication (32 of 112 vector instructions of a tile, which add to the time of
     // its 48 products: the same tree otherwise, in turn, 4 x 32/8 heads, L = 4096 causal 2922 -> 2884 us, 40 heads, L = 75600 418.7 ->
     // 416.3 ms, MX 4 x 8/2 heads, L = 3124 759 -> 749 us; MX of d = 128 under a causal mask lost, 2 x 16/4 heads, L = 3001 428.0 -> 429.7 us;
-    // d = 64 265.8 -> 260.0 us).
+    // d = 64 gains there, 265.8 -> 260.0 us, and without a mask, 2 x 24 heads, L = 3000 633 -> 618 us).
     constexpr bool FOLD = !(MXS && CAUSAL && D == 128);
     float ds_scale;
     {
@@ -248,7 +253,9 @@ __device__ __forceinline__ void bwd_dq_body(const DqArgs& A, int bh, int qt)
         if (j + 1 < nkt) issue_tile(BUF ^ 1, j + 1);
         const bool active = (!CAUSAL || k0 <= wave_qmax) && wave_live;
         if (active) {
-            floatx16 s[2], dp[2];
+#pragma unroll
+            for (int h0 = 0; h0 < 2; h0 += KH) {
+            floatx16 s[KH], dp[KH];
             if constexpr (MXS) {
                 // S^T from the codes (2 * D/64 products), then dP^T = V^F dO^T: 2*DS steps, step i: ds = i/2, kb = i%2
                 const uint32_t rec = lds_addr_of(&sm.krec[BUF][0]);
@@ -280,23 +287,23 @@ __device__ __forceinline__ void bwd_dq_body(const DqArgs& A, int bh, int qt)
                     dp[i & 1] = mfma_bf16(av, doreg[i >> 1], i < 2 ? dp0 : dp[i & 1]);
                 }
             } else
-            {   // S^T = K^F Q^F^T and dP^T = V^F dO^T: 4*DS steps, step i: ds = i/4, kb = (i/2)%2, K or V = i%2
-                constexpr int NST = 4 * DS, RING = D == 128 ? 5 : 6;      // (six operands of d = 128 do not fit beside dp0)
+            {   // S^T = K^F Q^F^T and dP^T = V^F dO^T: 2*KH*DS steps, step i: ds = i/(2*KH), kb = (i/2)%KH, K or V = i%2
+                constexpr int NST = 2 * KH * DS, RING = D == 128 ? 5 : 6;      // (six operands of d = 128 do not fit beside dp0)
                 auto opnd = [&](int i) __attribute__((always_inline)) -> uint4v {
-                    return lds_read16_at(koff[i >> 2] + (uint32_t)(BUF * kTileB + (i & 1) * kVfromK + ((i >> 1) & 1) * (32 * D * 2)));
+                    return lds_read16_at(koff[i / (2 * KH)] + (uint32_t)(BUF * kTileB + (i & 1) * kVfromK + (h0 + (i >> 1) % KH) * (32 * D * 2)));
                 };
                 uint4v ring[RING];
 #pragma unroll
                 for (int i = 0; i < RING; ++i) ring[i] = opnd(i);
 #pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
+                for (int kb = 0; kb < KH; ++kb)
 #pragma unroll
                     for (int i = 0; i < 16; ++i) s[kb][i] = 0.0f;
 #pragma unroll
                 for (int i = 0; i < NST; ++i) {
                     const uint4v a = ring[i % RING];
                     if (i + RING < NST) ring[i % RING] = opnd(i + RING);
-                    const int kb = (i >> 1) & 1, ds = i >> 2;
+                    const int kb = (i >> 1) % KH, ds = i / (2 * KH);
                     if (i & 1) dp[kb] = mfma_bf16(a, doreg[ds], ds == 0 ? dp0 : dp[kb]);
                     else       s[kb] = mfma_f16(a, qreg[ds], s[kb]);
                 }
@@ -312,18 +319,18 @@ __device__ __forceinline__ void bwd_dq_body(const DqArgs& A, int bh, int qt)
             if (__builtin_expect(need_mask, 0)) {
                 const int klim = CAUSAL ? min(L - 1, q_row) : L - 1;
 #pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
+                for (int kb = 0; kb < KH; ++kb)
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
-                        const int key = k0 + 32 * kb + 8 * (i >> 2) + 4 * hf + (i & 3);
+                        const int key = k0 + 32 * (h0 + kb) + 8 * (i >> 2) + 4 * hf + (i & 3);
                         if (key > klim) s[kb][i] = -INFINITY;
                     }
             }
             // dQ^T += K^F^T dS^T, 16 keys per step; the K^T operands of a step are read (transposed)
             // before that step's dS is computed, so their latency hides behind the VALU work
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                const int kb = ks >> 1, g = ks & 1;
+            for (int ks = 2 * h0; ks < 2 * (h0 + KH); ++ks) {
+                const int kb = (ks >> 1) - h0, g = ks & 1;
                 uint4v at[MB];
 #pragma unroll
                 for (int mb = 0; mb < MB; ++mb)
@@ -341,6 +348,7 @@ __device__ __forceinline__ void bwd_dq_body(const DqArgs& A, int bh, int qt)
                 }
 #pragma unroll
                 for (int mb = 0; mb < MB; ++mb) acc[mb] = mfma_f16(at[mb], bds, acc[mb]);
+            }
             }
         }
         __builtin_amdgcn_s_waitcnt(0);
@@ -367,7 +375,7 @@ __device__ __forceinline__ void bwd_dq_body(const DqArgs& A, int bh, int qt)
 }
 
 template <int D, bool CAUSAL, bool MXS, int NW = 4>
-__global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void bwd_dq_kernel(DqArgs A)
+__global__ __launch_bounds__(64 * NW, NW == 4 ? (D == 64 ? 3 : 2) : 1) void bwd_dq_kernel(DqArgs A)
 {
     const int nqt = (A.Lp + 32 * NW - 1) / (32 * NW);      // (Lp is a multiple of 128: with 8 waves the last workgroup may own only 128 rows)
     int bh, qt;
@@ -402,12 +410,13 @@ static int launch_dq_v(const void* qb, const void* kb, const void* vb, const voi
 // Eight waves per workgroup for a separate pass (plan.hpp says which problems run those) whose problem still leaves every compute
 // unit two such workgroups to balance with, and, under a causal mask, whose sequences are long enough for the 256 rows at the diagonal,
 // where part of the workgroup idles, not to matter (llm32k_gqa: 1.5 % faster with eight; llm4k_gqa: 2 - 8 % slower; the plan leaves
-// no shorter causal problem here but the ablation with the unquantized P); or when a test forces them; four otherwise.
-static bool wide_workgroups(bool causal, long long groups_of_256, int Lp)
+// no shorter causal problem here but the ablation with the unquantized P); or when a test forces them; four otherwise.  d = 64: four, of
+// which three share a compute unit (bwd_plan).
+static bool wide_workgroups(int D, bool causal, long long groups_of_256, int Lp)
 {
     const int forced = __atomic_load_n(&g_bwd_waves, __ATOMIC_RELAXED);
     if (forced != 0) return forced == 8;
-    return groups_of_256 >= 2LL * device_cu_count() && (!causal || Lp >= 16384);
+    return D == 128 && groups_of_256 >= 2LL * device_cu_count() && (!causal || Lp >= 16384);
 }
 
 template <int D, bool CAUSAL, bool MXS>
@@ -415,7 +424,7 @@ static int launch_dq_t(const void* qb, const void* kb, const void* vb, const voi
                        const float* rowstat, const float* bound_part, int B, int Hq, int Hkv, int L, void* dq, hipStream_t st,
                        const MxScoreOps* mx)
 {
-    if (wide_workgroups(CAUSAL, (long long)B * Hq * ((round_up(L, kRowPad) + 255) / 256), round_up(L, kRowPad)))
+    if (wide_workgroups(D, CAUSAL, (long long)B * Hq * ((round_up(L, kRowPad) + 255) / 256), round_up(L, kRowPad)))
         return launch_dq_v<D, CAUSAL, MXS, 8>(qb, kb, vb, dob, rowstat, bound_part, B, Hq, Hkv, L, dq, st, mx);
     return launch_dq_v<D, CAUSAL, MXS, 4>(qb, kb, vb, dob, rowstat, bound_part, B, Hq, Hkv, L, dq, st, mx);
 }
@@ -1024,7 +1033,7 @@ static int launch_dkdv_t(const void* qb, const void* kb, const void* vb, const v
                                                                        tile_counts, st, p_dump, dump_row0, mx)
     if (tile_counts || p_dump) return AQ_DKV(true, 1, 4);       // the counting / dumping variant
     if (p_quant == 0) return AQ_DKV(false, 0, 4);               // the ablation
-    if (wide_workgroups(CAUSAL, (long long)B * Hkv * ((round_up(L, kRowPad) + 255) / 256), round_up(L, kRowPad)))
+    if (wide_workgroups(D, CAUSAL, (long long)B * Hkv * ((round_up(L, kRowPad) + 255) / 256), round_up(L, kRowPad)))
         return p_quant == 1 ? AQ_DKV(false, 1, 8) : p_quant == 2 ? AQ_DKV(false, 2, 8) : AQ_DKV(false, 3, 8);
     return p_quant == 1 ? AQ_DKV(false, 1, 4) : p_quant == 2 ? AQ_DKV(false, 2, 4) : AQ_DKV(false, 3, 4);
 #undef AQ_DKV
@@ -1053,7 +1062,7 @@ int launch_bwd_dkdv(const void* qb, const void* kb, const void* vb, const void* 
 // 8/2 heads, L = 8192 causal 1264 -> 1139 -> 475 us; 12 heads, L = 1560 120 -> 91 -> 82 us; 4 x 32/8 heads, L = 4096 causal
 // 2.09 -> 1.85 ms (no pieces); 12 heads, L = 6240 833 -> 698 us (no pieces).
 template <int D, bool CAUSAL, int PQ, bool COUNT = false /* the measurement variant of bwd_dkdv_body */>
-__global__ __launch_bounds__(256, 2) void bwd_joint_kernel(DqArgs Q, DkvArgs K, int n_dkdv, int n_dq, bool dq_first)
+__global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_joint_kernel(DqArgs Q, DkvArgs K, int n_dkdv, int n_dq, bool dq_first)
 {
     const int nt = K.Lp / 128;
     int block = blockIdx.x;
@@ -1120,7 +1129,12 @@ __global__ __launch_bounds__(256) void dkdv_reduce_kernel(const float* __restric
 BwdPlan bwd_plan(int BHq, int BHkv, int L, int D, bool causal, int cus)
 {
     if (__atomic_load_n(&g_bwd_waves, __ATOMIC_RELAXED) != 0) return BwdPlan{false, 1, 0, 0, false};      // (a test forces separate passes)
-    return plan_backward(BHq, BHkv, L, D, causal, cus);
+    const BwdPlan p = plan_backward(BHq, BHkv, L, D, causal, cus);
+    // d = 64: three four-wave workgroups of the joint launch share a compute unit, where an eight-wave one has it to itself (its registers
+    // would have to halve).  Training step, separate passes of eight -> joint: 24 heads, L = 8192 2270 -> 1993 us, MX 16 heads 1476 -> 1304 us;
+    // 16 heads, L = 32768 causal 11.80 -> 9.50 ms, MX 11.96 -> 9.80 ms.  (Separate passes of four: 1 % behind the joint launch.)
+    if (p.joint || D != 64) return p;
+    return BwdPlan{true, 1, (L + 31) / 32 * (BHq / BHkv), 0, false};
 }
 
 template <int D, bool CAUSAL, int PQ, bool COUNT = false>

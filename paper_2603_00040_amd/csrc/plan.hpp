@@ -13,7 +13,7 @@ struct BwdPlan { bool joint; int splits, iters; size_t part_bytes; bool dq_first
 // 97 % on average, where the halved tile copies win by 2 - 3 % (24 heads, L = 8192: 2.09 against 2.14 ms; 12 x 2 heads, L = 32760:
 // 32.0 against 33.0 ms), while rounds filled to 95, 92 and 73 % lose to the joint launch by 2, 5 and 24 % (40 heads, L = 20000
 // and 12000; 12 heads of 64, L = 12000).  Under a causal mask the two are even at 32768 positions (46.1 ms) and below that
-// joint wins by 1 - 4 %.
+// joint wins by 1 - 4 %.  (All of that at d = 128; at d = 64 bwd_plan makes the rest joint as well.)
 // Pieces: time is counted in query tiles of the dK/dV pass (1.45 us); a 64-key tile of a dQ workgroup takes 1.16 of them.  With W the
 // work per compute unit, pieces of 0.45 W came out best or within 10 % of it over 16 shapes (8 sizes of piece each), as long as
 //   * a piece is not much shorter than the average dQ tile, which it would only have to wait for,

@@ -142,6 +142,12 @@ def test_joint_backward_kernels_do_not_spill():
     _check(k, r"dkdv_reduce_kernelILi(64|128)ELb[01]E", 4)
 
 
+def test_backward_of_d64_leaves_room_for_three_wavefronts():
+    # (a SIMD has 512 registers; with more than 168 each, two)
+    hit = _check(_resources("bwd.hip"), r"bwd_joint_kernelILi64ELb[01]ELi[123]ELb0E", 6)
+    assert all(v["Occupancy [waves/SIMD]"] >= 3 for v in hit.values()), hit
+
+
 def test_preparing_kernels_keep_off_scratch_memory():
     # scalar registers parked in lanes of a vector register cost no memory access: the backward's group carries the addresses of
     # nine arrays beside its loop bounds

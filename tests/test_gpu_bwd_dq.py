@@ -64,3 +64,22 @@ def test_factor_of_ds_covers_every_head_of_a_group(head):
                          ohp[:, head:head + 1].contiguous(), False)[1].double()
     # the other heads add 2^-24 of it (their own size, 1, against 2^24; seven of them, their dS rounded to steps of 2^-39 of the bound)
     assert bool(torch.isfinite(dk).all()) and float((dk - one).norm()) <= 2.0 ** -7 * float(one.norm())
+
+
+@pytest.mark.parametrize("H,L,causal", [(32, 4096, False), (4, 32700, True)])
+@pytest.mark.parametrize("mx", [False, True])
+def test_large_problems_of_d64_run_both_passes_in_one_launch(H, L, causal, mx):
+    """Shapes whose eight-wave workgroups fill the chip evenly: at d = 64 one launch of four-wave workgroups, the bits of the separate passes."""
+    import paper_2603_00040_amd as aq
+    g = torch.Generator(device="cuda").manual_seed(L)
+    q, k, v, do = (torch.randn(1, H, L, 64, generator=g, device="cuda").to(torch.bfloat16) for _ in range(4))
+    fwd, bwd = (aq.attnqat_fwd_mx, aq.attnqat_bwd_mx) if mx else (aq.attnqat_fwd, aq.attnqat_bwd)
+    _, lse, ohp = fwd(q, k, v, causal)
+    got = bwd(q, k, v, do, lse, ohp, causal)
+    for waves in (4, 8):
+        aq.debug_bwd_waves(waves)
+        try:
+            want = bwd(q, k, v, do, lse, ohp, causal)
+        finally:
+            aq.debug_bwd_waves(0)
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
