@@ -175,6 +175,7 @@ __device__ inline void mx_block_list(const unsigned char* __restrict__ mask, int
 
 // A workgroup takes 64 positions of V (in a backward the chunk of a head's 64-row tiles that one partial maximum covers), 256 blocks
 // of 32 values of Q or K, four rows of the mask, or a chunk of dO.
+// (five wavefronts per SIMD: the loads of a backward's dO and O' together would otherwise take 101 registers, one wavefront less)
 template <int D, MxKind KIND>
 __global__ __launch_bounds__(256, 5) void mx_group_kernel(MxGroup g, unsigned nblocks)
 {
