@@ -106,6 +106,9 @@ __host__ __device__ constexpr int mx_ktrain_rec_bytes(int D) { return 2 * (D / 6
 // that uses the instruction on the 16-bit path.
 __device__ inline void mfma_scale_settle(floatx16& a) { asm volatile("s_nop 15\n\ts_nop 15" : "+v"(a)); }
 __device__ inline void mfma_scale_settle(floatx16& a, floatx16& b) { asm volatile("s_nop 15\n\ts_nop 15" : "+v"(a), "+v"(b)); }
+// The same behind v_mfma_f32_32x32x16 (eight passes: 11 wait states) where inline assembly, whose operands the compiler's count does not
+// look at, may be the first to read the product.
+__device__ inline void mfma_settle(floatx16& a, floatx16& b) { asm volatile("s_nop 11" : "+v"(a), "+v"(b)); }
 
 // max(a, b) written as median(a, b, +inf): fmaxf() on values the compiler cannot prove quiet (MFMA
 // results) costs a canonicalizing v_max per operand, the median has no such requirement and the

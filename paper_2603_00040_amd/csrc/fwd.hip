@@ -635,6 +635,7 @@ __device__ __forceinline__ void fwd_body(
                         if constexpr (MORE) kr[i] = *reinterpret_cast<const half8*>(k_head + (size_t)k_next * (64 * D) + 512 * i + 8 * lane);
                         __builtin_amdgcn_sched_barrier(0);
                     }
+                    mfma_settle(s[0], s[1]);             // (no barrier stands between the products and max_raw here)
                 }
                 float bsc[4], binv[4];
                 vector_phase(j, bsc, binv);

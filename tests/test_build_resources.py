@@ -211,3 +211,54 @@ def test_mx_decode_kernels_in_chunks_do_not_spill():
 def test_split_mx_forward_kernels_do_not_spill():
     # fwd_mx_split_kernel<D, CAUSAL, FP8PV, KVM>: contiguous in both recipes, paged and block-sparse
     _check(_resources("mx.hip"), r"fwd_mx_split_kernelILi(64|128)ELb[01]E(Lb0ELi[012]|Lb1ELi0)E", 16)
+
+
+def _registers(operand):
+    m = re.match(r"[-|]*v(?:\[(\d+):(\d+)\]|(\d+))\|?$", operand)
+    return range(0) if not m else range(int(m.group(1)), int(m.group(2)) + 1) if m.group(1) else range(int(m.group(3)), int(m.group(3)) + 1)
+
+
+def _reads_without_settling(src, pattern, suspect):
+    """For every kernel whose mangled name matches: its vector instructions that read the result of a product although no wait written in
+    the source (s_nop in inline assembly) stands in between, out of those that suspect(product, in another block, in inline assembly)
+    picks.  The listing is read from top to bottom; after 20 instructions every product has arrived."""
+    with tempfile.TemporaryDirectory() as tmp:
+        out = os.path.join(tmp, "x.s")
+        r = subprocess.run(["hipcc", *B.FLAGS, "-S", "--cuda-device-only", os.path.join(B.CSRC, src), "-o", out], capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr[-2000:]
+        text = open(out).read().splitlines()
+    found, cur, written, at, block, in_asm, settled = {}, None, {}, 0, 0, False, 0
+    for line in (l.strip() for l in text):
+        m = re.match(r"^(_Z\w+):", line)
+        if m:
+            cur = m.group(1) if re.search(pattern, m.group(1)) else None
+            written, at, block, settled = {}, 0, 0, 0
+            if cur:
+                found[cur] = []
+        elif line.startswith((".LBB", "; %bb")):
+            block += 1
+        elif "ASMSTART" in line or "ASMEND" in line:
+            in_asm = "ASMSTART" in line
+        elif cur and line and line[0] not in ";.":
+            op, _, rest = line.partition(" ")
+            operands = [t.strip().split(" ")[0] for t in rest.split(",")]
+            at += int(operands[0]) + 1 if op == "s_nop" else 1
+            if op == "s_nop" and in_asm:
+                settled = at
+            elif op.startswith("v_mfma"):
+                written.update({reg: (at, block, op) for reg in _registers(operands[0])})
+            elif op.startswith("v_"):
+                for reg in (reg for t in operands[1:] for reg in _registers(t) if reg in written):
+                    when, where, product = written[reg]
+                    if settled < when and at - when < 20 and suspect(product, block != where, in_asm):
+                        found[cur].append((at - when, line))
+                for reg in _registers(operands[0]):
+                    written.pop(reg, None)
+    return found
+
+
+def test_inline_assembly_of_the_split_forward_reads_settled_products():
+    """The compiler counts the wait states between a product and its readers, but does not look into inline assembly (max_raw): in the kernel
+    that has no barrier between the scores and the softmax the wait stands in the source."""
+    found = _reads_without_settling("fwd.hip", r"fwd_split_kernel", lambda product, other_block, in_asm: in_asm)
+    assert len(found) == 24 and not any(found.values()), {k: v[:3] for k, v in found.items() if v}
