@@ -262,3 +262,9 @@ def test_inline_assembly_of_the_split_forward_reads_settled_products():
     that has no barrier between the scores and the softmax the wait stands in the source."""
     found = _reads_without_settling("fwd.hip", r"fwd_split_kernel", lambda product, other_block, in_asm: in_asm)
     assert len(found) == 24 and not any(found.values()), {k: v[:3] for k, v in found.items() if v}
+
+
+def test_split_mx_forward_settles_products_that_another_block_reads():
+    """No wait states are relied on that the compiler would have to count across blocks for the scaled product (see mfma_scale_settle)."""
+    found = _reads_without_settling("mx.hip", r"fwd_mx_split_kernel", lambda product, other_block, in_asm: "scale" in product and (other_block or in_asm))
+    assert len(found) == 16 and not any(found.values()), {k: v[:3] for k, v in found.items() if v}
