@@ -142,13 +142,13 @@ __device__ __forceinline__ void bwd_dq_body(const DqArgs& A, int bh, int qt)
     }
     const float2 st_ = rowstat[(size_t)bh * Lp + q_ld];
     // dS of this row goes to fp16 after multiplication by ds_scale = 2^k, k from the bound
-    // (|dO_i| max_j |V^F_j| + |D_i|) / sqrt(d) >= |dS_ij|.  FOLD: 2^k and 1 / sqrt(d) go into the exponent of P and -D_i is what the
-    // accumulators of dP start from, so that dS is one multiplication (32 of 112 vector instructions of a tile, which add to the time of
+    // (|dO_i| max_j |V^F_j| + |D_i|) / sqrt(d) >= |dS_ij|.  FOLD: the dO operand is multiplied by 2^k, -2^k D_i is what the accumulators of
+    // dP start from, and 1 / sqrt(d) goes into the exponent of P, so that dS is one multiplication (32 of 112 vector instructions of a tile, which add to the time of
     // its 48 products: the same tree otherwise, in turn, 4 x 32/8 heads, L = 4096 causal 2922 -> 2884 us, 40 heads, L = 75600 418.7 ->
     // 416.3 ms, MX 4 x 8/2 heads, L = 3124 759 -> 749 us; MX of d = 128 under a causal mask lost, 2 x 16/4 heads, L = 3001 428.0 -> 429.7 us;
     // d = 64 gains there, 265.8 -> 260.0 us, and without a mask, 2 x 24 heads, L = 3000 633 -> 618 us).
     constexpr bool FOLD = !(MXS && CAUSAL && D == 128);
-    float ds_scale;
+    float ds_scale, do_scale = 1.0f;
     {
         float n2 = 0.0f;
 #pragma unroll
@@ -160,14 +160,25 @@ __device__ __forceinline__ void bwd_dq_body(const DqArgs& A, int bh, int qt)
             }
         n2 = xhalf_sum(n2);
         const float vmax = bound_of(bound_part, NHq, 0, bhkv);
-        ds_scale = ds_scale_for((sqrtf(n2) * 1.0001f * vmax) * rs + fabsf(st_.y));
-    }
-    // L_i log2(e) - k - log2(1 / sqrt(d))  (3.5 and 3 are exact)
-    const float Ls = st_.x - (FOLD ? (float)((int)(__float_as_uint(ds_scale) >> 23) - 127) - (D == 128 ? 3.5f : 3.0f) : 0.0f);
-    const float rs_s = rs * ds_scale, Dq_s = st_.y * ds_scale;        // (not FOLD) D_i / sqrt(d), scaled
-    floatx16 dp0;                                                    // what dP starts from: -D_i in every register
+        ds_scale = ds_scale_for((sqrtf(n2) * 1.0001f * vmax) * rs + fabsf(st_.y * rs));
+        if constexpr (FOLD) {
+            // 2^k on dO, exactly, so that no rounding depends on the scale of the gradients (in the exponent of P it cost up to 1 % of dQ's
+            // error at |dO| = 2^-40).  Where that would leave the range of bf16 (V^F next to zero, |dO| beyond 2^40), it does go into
+            // the exponent.
+            if (sqrtf(n2) * ds_scale < 1e30f) do_scale = ds_scale;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) dp0[i] = FOLD ? -st_.y / rs : 0.0f;
+            for (int ds = 0; ds < DS; ++ds)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    doreg[ds][i] = __builtin_amdgcn_perm(__float_as_uint(bf16_hi_f32(doreg[ds][i]) * do_scale), __float_as_uint(bf16_lo_f32(doreg[ds][i]) * do_scale), 0x07060302u);
+        }
+    }
+    // L_i log2(e) - log2(1 / sqrt(d))  (3.5 and 3 are exact), and the part of k that dO does not carry
+    const float Ls = st_.x - (FOLD ? (float)((int)(__float_as_uint(ds_scale / do_scale) >> 23) - 127) - (D == 128 ? 3.5f : 3.0f) : 0.0f);
+    const float rs_s = rs * ds_scale, Dq_s = st_.y * rs_s;            // (not FOLD) D_i / sqrt(d), scaled
+    floatx16 dp0;                                                    // what dP starts from: -2^k D_i in every register
+#pragma unroll
+    for (int i = 0; i < 16; ++i) dp0[i] = FOLD ? -st_.y * do_scale : 0.0f;
 
     const int nkt_all = (L + 63) / 64;
     const int nkt = CAUSAL ? min((qt + 1) * (QT / 64), nkt_all) : nkt_all;
@@ -340,7 +351,7 @@ __device__ __forceinline__ void bwd_dq_body(const DqArgs& A, int bh, int qt)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int r0 = 8 * g + 2 * i;
-                    const float p0 = __builtin_amdgcn_exp2f(fmaf(s[kb][r0], c, -Ls));           // P = exp(S - L_i) (FOLD: times 2^k / sqrt(d))
+                    const float p0 = __builtin_amdgcn_exp2f(fmaf(s[kb][r0], c, -Ls));           // P = exp(S - L_i) (FOLD: / sqrt(d))
                     const float p1 = __builtin_amdgcn_exp2f(fmaf(s[kb][r0 + 1], c, -Ls));
                     // dS = P (dP - D_i)/sqrt(d), times 2^k, to fp16
                     if constexpr (FOLD) bds[i] = pack_f16x2(p0 * dp[kb][r0], p1 * dp[kb][r0 + 1]);
@@ -647,7 +658,7 @@ __device__ __forceinline__ void bwd_dkdv_body(const DkvArgs& A, int bhkv, int kt
     for (int it = 0; it < niter; ++it) {
         const int buf = it & 1;
         const int q0 = (qt_first + cur_t) * 32;
-        const float Ls = st_n.x, Dq_s = st_n.y * (rs_s / rs);
+        const float Ls = st_n.x, Dq_s = st_n.y * rs_s;
         // next tile: start its copy and fetch its row scalars now, they are needed one iteration later
         int nx_g = cur_g, nx_t = cur_t + 1;
         if (nx_t == per_head) { nx_t = 0; ++nx_g; }

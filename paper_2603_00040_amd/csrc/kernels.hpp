@@ -23,7 +23,7 @@ struct PagedSrc {
 // Everything a forward or a backward prepares, in one launch.  Q and K become fp16 rows (zero padded to Lp = round_up(L, 128)), V
 // becomes transposed fp16 (forward; bf16 and unquantized with v_quant = false) or bf16 rows (backward).  From bf16 tensors, or
 // from codes and scales (attnqat_quantize's layout; codes[2] != null), or, K and V, from the pages of a cache (ps.cache != null).
-// With grad.d_o the statistics of the backward are made as well (Alg. 3, first line): rowstat [BHq, Lp, 2] = {L log2(e), D / sqrt(d)},
+// With grad.d_o the statistics of the backward are made as well (Alg. 3, first line): rowstat [BHq, Lp, 2] = {L log2(e), D},
 // D = rowsum(dO o O'), zeros in the padding rows; and in bounds, 3 * BHq * kBoundParts floats, partial maxima per head
 // that limit |dS|: |V^F_j| (kv heads), |dO_i|, |D_i| / sqrt(d).
 constexpr int kBoundParts = 64;

@@ -9,7 +9,7 @@ namespace aq {
 // 64-row tiles per chunk of the partial maxima: at most kBoundParts chunks per head.
 __host__ __device__ inline int bound_chunk_tiles(int tiles) { return (tiles + kBoundParts - 1) / kBoundParts; }
 
-// The statistics that the backward needs of 64 rows of dO and O' (Alg. 3, first line): rowstat = {L log2(e), D / sqrt(d)} with
+// The statistics that the backward needs of 64 rows of dO and O' (Alg. 3, first line): rowstat = {L log2(e), D} with
 // D = rowsum(dO o O') (padding rows hold {0, 0}), the largest |dO_i|^2 and |D_i| / sqrt(d) so far in n2 and dmax, and the zero-padded
 // copy of dO where one is asked for (dob).  D is added up eight elements at a time (pairs 0, 2, 1, 3 of them), then over the groups of
 // eight in a tree whose last level joins neighbours: which order the sum has is part of the result's bits, so the two groups of a
@@ -84,10 +84,10 @@ __device__ __forceinline__ void grad_tile(int bh, int l0, const uint16_t* __rest
         }
 #pragma unroll
         for (int w = nb / 2; w >= 1; w >>= 1) { dot8[0] += __shfl_xor(dot8[0], w); dot8[1] += __shfl_xor(dot8[1], w); nrm += __shfl_xor(nrm, w); }
-        const float dot = (dot8[0] + dot8[1]) * rs;
+        const float dot = dot8[0] + dot8[1];
         if (cb == 0) rowstat[(size_t)bh * Lp + l] = make_float2(l < L ? lse_[it] * 1.4426950408889634f : 0.0f, dot);
         n2 = fmaxf(n2, nrm);
-        dmax = fmaxf(dmax, fabsf(dot));
+        dmax = fmaxf(dmax, fabsf(dot * rs));
         if (dob) {
             uint4v* dst = reinterpret_cast<uint4v*>(dob + ((size_t)bh * Lp + l) * D + cb * 16);
             dst[0] = g[0]; dst[1] = g[1];

@@ -52,6 +52,34 @@ def test_dq_within_its_roundings(Hq, Hkv, L, d, causal, offset, spread, waves):
     assert bool(((dq - want).abs() <= 1.01 * tol + 2.0 ** -8 * want.abs() + 1e-37).all())
 
 
+@pytest.mark.parametrize("mx", [False, True])
+@pytest.mark.parametrize("Hq,Hkv,L,d,causal", [(4, 1, 513, 128, True), (2, 2, 300, 128, False), (2, 1, 640, 64, True), (2, 2, 97, 64, False)])
+def test_gradients_scale_exactly_with_dO(Hq, Hkv, L, d, causal, mx):
+    """Everything between dO and the gradients is linear in dO and rounds relative to its size: dO times a power of two gives the same
+    gradients times that power, bit for bit, as long as nothing leaves the normal range (the gradients of 2^-40 dO lie above 2^-100)."""
+    import paper_2603_00040_amd as aq
+    q, k, v, do = _inputs(Hq, Hkv, L, d, 0.0, 0.0, seed=L)
+    fwd, bwd = (aq.attnqat_fwd_mx, aq.attnqat_bwd_mx) if mx else (aq.attnqat_fwd, aq.attnqat_bwd)
+    _, lse, ohp = fwd(q, k, v, causal)
+    one = bwd(q, k, v, do, lse, ohp, causal)
+    for e in (-40, -17, 20):
+        got = bwd(q, k, v, do * 2.0 ** e, lse, ohp, causal)
+        for name, a, b in zip(("dQ", "dK", "dV"), got, one):
+            assert torch.equal(a, b * 2.0 ** e), (name, e, float((a.double() - b.double() * 2.0 ** e).norm() / (b.double() * 2.0 ** e).norm()))
+
+
+def test_dq_where_the_factor_of_ds_would_overflow_dO():
+    """V^F all but zero and dO large: dS is tiny, its factor 2^60 and dO beyond the range that dO times that has in bf16."""
+    import paper_2603_00040_amd as aq
+    for d, causal in ((64, True), (128, False)):
+        q, k, v, do = _inputs(2, 1, 130, d, 0.0, 0.0, seed=d)
+        v.zero_()
+        do *= 2.0 ** 90
+        _, lse, ohp = aq.attnqat_fwd(q, k, v, causal)
+        dq, dk, dv = aq.attnqat_bwd(q, k, v, do, lse, ohp, causal)
+        assert not bool(dq.any()) and not bool(dk.any()) and bool(torch.isfinite(dv.float()).all())
+
+
 @pytest.mark.parametrize("head", [0, 4, 7])
 def test_factor_of_ds_covers_every_head_of_a_group(head):
     """dS of a kv head is scaled by the largest of its eight query heads, whichever that is: fp16 would overflow otherwise."""
