@@ -337,9 +337,9 @@ int attnqat_fwd_infer_mx_fp8pv(const void* q, const void* k, const void* v,
  * max_pages >= ceil(max kv_len / 128)).  causal != 0: query i sees keys 0 .. kv_lens[b] - Lq + i (chunked prefill;
  * Lq = 1 is a decode step).  o [B,Hq,Lq,d] bf16, lse [B,Hq,Lq] fp32.  Page ids outside [0, num_pages) are clamped
  * (wrong result, no out-of-bounds access); a sequence with kv_lens[b] = 0 gets o = 0.
- * With at most 32 query rows per (sequence, kv head) and few of those, the pages are cut into chunks whose sums meet in the
- * workspace: the last bits of o and lse then depend on B, Hkv, the rows and max_pages.  A workspace that lacks only the room for the
- * sums is accepted (one workgroup per head, slower).
+ * With at most 32 query rows per (sequence, kv head), and at most 170 of those, the workspace includes room (up to 17 MB, and 2.3 KB per row of
+ * q) in which the launches of a decode step hand over P; a smaller one is accepted (one workgroup per head, slower).  The bits of o and
+ * lse do not depend on that, nor on the other sequences or on max_pages.
  */
 size_t attnqat_kv_cache_page_bytes(int Hkv, int d);
 int attnqat_kv_cache_write_mx(const void* k, const void* v, int Hkv, int L, int d, int dtype,

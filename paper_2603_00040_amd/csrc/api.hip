@@ -441,9 +441,9 @@ int attnqat_fwd_infer_mx_paged(const void* q, int B, int Hq, int Hkv, int Lq, in
     unsigned char* qops = (unsigned char*)c.take(mx_qops_bytes(B * Hq, Lq, d));      // sized for the unpacked case (the larger)
     unsigned char* qsc = (unsigned char*)c.take(mx_qsc_bytes(B * Hq, Lq));
     if (!workspace || workspace_bytes < c.off) return ATTNQAT_EWORKSPACE;
-    // (the sums of a decode step's chunks: a workspace without the room for them gets one workgroup per head)
+    // (what the launches of a decode step hand over: a workspace without the room for it gets one workgroup per head)
     const size_t part_bytes = mx_decode_part_bytes(B * Hq_k, Lq_k, d);
-    float* part = part_bytes ? (float*)c.take(part_bytes) : nullptr;
+    unsigned char* part = part_bytes ? (unsigned char*)c.take(part_bytes) : nullptr;
     if (workspace_bytes < c.off) part = nullptr;
     hipStream_t st = (hipStream_t)stream;
     prof_begin(st);

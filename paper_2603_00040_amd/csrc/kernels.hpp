@@ -153,8 +153,9 @@ int launch_fwd_mx(const void* qops, const void* qsc, const void* kv, int B, int 
 size_t mx_page_bytes(int D);
 int launch_fwd_mx_paged(const void* qops, const void* qsc, const void* cache, int B, int Hq, int Hkv, int Lq, int D, bool causal,
                         const int* page_table, const int* kv_lens, int max_pages, int num_pages, int lq_inner,
-                        float* part /* mx_decode_part_bytes() bytes, or null: one workgroup per head */, void* o, float* lse, hipStream_t st);
-constexpr int kMxDecUnits = 512;                    // most chunks of pages of a decode step
+                        unsigned char* part /* mx_decode_part_bytes() bytes, or null: one workgroup per head */, void* o, float* lse, hipStream_t st);
+constexpr int kMxDecUnits = 2048;                   // most chunks of pages, times heads, of a decode step
+constexpr int kMxDecPageHeads = 8192;               // most pages, times heads, whose P the workspace of a decode step has room for
 size_t mx_decode_part_bytes(int heads /* B * Hq */, int Lq, int D);      // 0: such a step is not cut into chunks
 
 // Block-sparse forward on contiguous kv records, over the block lists that launch_mx_group made: list [B*Hq*nb, nb] and

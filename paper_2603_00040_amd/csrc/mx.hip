@@ -601,14 +601,12 @@ __global__ __launch_bounds__(256, 2) void fwd_mx_split_kernel(
 // waves of a block derive the same scale).  Each wave then quantizes its 16 keys per row against the maximum after ITS
 // tile, exactly as the tile order of Alg. 1 prescribes, and accumulates its own O and l against its own reference
 // maximum; the partial results are brought to the final maximum and added at the end.
-// PART (fwd_mx_decode_part_kernel): the pages of one chunk only, blockIdx.y; see there.
-struct MxChunks { int per /* pages of a chunk */, n /* chunks of a sequence */; const float* cmax; float *part_o, *part_l, *part_m; };
 constexpr int kMxDecRows = 32;                       // most rows of a head
-template <int D, bool CAUSAL, int NP /* pages per iteration: 4 NP waves */, bool PART>
-__device__ __forceinline__ void mx_decode_body(
+template <int D, bool CAUSAL, int NP /* pages per iteration: 4 NP waves */>
+__global__ __launch_bounds__(256 * NP, NP == 1 ? 2 : 1) void fwd_mx_decode_kernel(
     const unsigned char* __restrict__ qops, const uint32_t* __restrict__ qsc, const unsigned char* __restrict__ kv,
     uint16_t* __restrict__ O, float* __restrict__ lse, int L /* rows, <= 32 */, int Hq, int G, float c /* log2(e)/sqrt(d) */,
-    const int* __restrict__ page_table, const int* __restrict__ kv_lens, int max_pages, int num_pages, int lq_inner, MxChunks ck)
+    const int* __restrict__ page_table, const int* __restrict__ kv_lens, int max_pages, int num_pages, int lq_inner)
 {
     constexpr int KS = D / 64, MT = D / 32, NW = 4 * NP;
     constexpr int NIT = NP == 1 ? 4 : NP == 2 ? 3 : 2;   // iterations whose pages the LDS ring holds (NIT - 1 of them in flight)
@@ -637,10 +635,7 @@ __device__ __forceinline__ void mx_decode_body(
     const int Lk = __builtin_amdgcn_readfirstlane(kv_lens[b]);
     const int koff = Lk - lq_inner;
     const bool packed = lq_inner != L;
-    const int nst_all = min((Lk + 127) / 128, max_pages);          // pages of this sequence
-    const int ch = PART ? (int)blockIdx.y : 0, p0 = PART ? ch * ck.per : 0;
-    if (PART && p0 >= max(nst_all, 1)) return;
-    const int nst = PART ? min(nst_all - p0, ck.per) : nst_all;    // pages of this chunk
+    const int nst = min((Lk + 127) / 128, max_pages);              // pages of this sequence
     const int nit = (nst + NP - 1) / NP;
     const int klim = CAUSAL ? min(Lk - 1, koff + (packed ? q_row % lq_inner : q_row)) : Lk - 1;
 
@@ -650,7 +645,7 @@ __device__ __forceinline__ void mx_decode_body(
         for (int pp = 0; pp < NP; ++pp) {
             const int st = it * NP + pp;
             if (st < nst) {
-                int page = __builtin_amdgcn_readfirstlane(page_table[(size_t)b * max_pages + p0 + st]);
+                int page = __builtin_amdgcn_readfirstlane(page_table[(size_t)b * max_pages + st]);
                 page = min(max(page, 0), num_pages - 1);           // a bad table entry reads a wrong page, never outside the cache
                 const unsigned char* src = kv + ((size_t)page * Hkv + (h / G)) * STAGE;
                 unsigned char* dst = smem + (st % NR) * STAGE;
@@ -683,10 +678,6 @@ __device__ __forceinline__ void mx_decode_body(
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[mt][i] = 0.0f;
     float m_run = -INFINITY;         // maximum after the last iteration (the same in every wave)
-    if constexpr (PART) {            // ... which for a later chunk is that of the chunks in front; the halves of the wave take every other one
-        for (int i = hf; i < ch; i += 2) m_run = fmaxf(m_run, ck.cmax[((size_t)bh * ck.n + i) * kMxDecRows + ln]);
-        m_run = xhalf_max(m_run);
-    }
     float mref = -INFINITY;          // maximum this wave's O and l refer to (after its tile of its last iteration)
     float lsum = 0.0f;
 
@@ -708,7 +699,7 @@ __device__ __forceinline__ void mx_decode_body(
         const int st = it * NP + pi;                                          // this wave's page
         const bool valid = st < nst;                                          // (the last iteration may be short of pages)
         const unsigned char* rec = smem + (st % NR) * STAGE + T * REC;
-        const int k0 = (p0 + st) * 128 + T * 64;
+        const int k0 = st * 128 + T * 64;
         // S^T of this wave's 32 keys
         floatx16 sv;
 #pragma unroll
@@ -830,18 +821,7 @@ __device__ __forceinline__ void mx_decode_body(
         }
         __syncthreads();
     }
-    if (PART && wave == 0 && nst_all > ck.per) {                              // several chunks: the sums go to memory
-        if (q_row < L) {
-            const size_t unit = (size_t)bh * ck.n + ch;
-            float* dst = ck.part_o + (unit * L + q_row) * D;
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int tt = 0; tt < 4; ++tt)
-                    *reinterpret_cast<floatx4*>(dst + 32 * mt + 8 * tt + 4 * hf) = floatx4{o[mt][4 * tt], o[mt][4 * tt + 1], o[mt][4 * tt + 2], o[mt][4 * tt + 3]};
-            if (hf == 0) { ck.part_l[unit * kMxDecRows + ln] = l; ck.part_m[unit * kMxDecRows + ln] = m_run; }
-        }
-    } else if (wave == 0) {
+    if (wave == 0) {
         const float inv_l = l > 0.0f ? 1.0f / l : 0.0f;                       // a sequence without keys: O = 0, L = -inf
         if (q_row < L) {
             const size_t row = (size_t)bh * L + q_row;
@@ -860,30 +840,28 @@ __device__ __forceinline__ void mx_decode_body(
     }
 }
 
-#define AQ_DEC_ARGS \
-    const unsigned char* __restrict__ qops, const uint32_t* __restrict__ qsc, const unsigned char* __restrict__ kv, \
-    uint16_t* __restrict__ O, float* __restrict__ lse, int L, int Hq, int G, float c, \
-    const int* __restrict__ page_table, const int* __restrict__ kv_lens, int max_pages, int num_pages, int lq_inner
-template <int D, bool CAUSAL, int NP>
-__global__ __launch_bounds__(256 * NP, NP == 1 ? 2 : 1) void fwd_mx_decode_kernel(AQ_DEC_ARGS)
-{
-    mx_decode_body<D, CAUSAL, NP, false>(qops, qsc, kv, O, lse, L, Hq, G, c, page_table, kv_lens, max_pages, num_pages, lq_inner, MxChunks{});
+// Few sequences: one workgroup per (sequence, kv head) walks all pages, a microsecond each, while most compute units idle.  The walk is then
+// taken apart; every sum keeps its terms and their order, so the results have the bits of fwd_mx_decode_kernel, whatever runs beside a sequence:
+//   mx_decode_max_kernel   the scores of a chunk of pages for their row maxima alone (P-tilde is quantized against the running maximum; on
+//                          the FP4 instruction scores are cheap, and this reads the K half of the records only);
+//   mx_decode_p_kernel     a workgroup per chunk, from the maximum in front of it: scores, softmax, phi(P-tilde).  Codes, scale byte, running
+//                          maximum and the two parts of l that the walk's waves add go to memory, 36 bytes per row and 32 keys;
+//   mx_decode_pv_kernel    a workgroup per (sequence, kv head) and block of 32 d: what is sequential about the walk, P V and l of each of
+//                          its four waves page by page, with the loads of sixteen pages on their way: 0.12 us a page (10 KiB through
+//                          the cache of one compute unit), 15.4 us for 16000 keys.
+// The records of P have room for kMxDecPageHeads pages; longer sequences take the last two launches in several segments.
+// A record of a page: 32 bytes per (tile, half of its keys, row), {codes, sum of P-tilde, maximum} of keys 0-15 and of keys 16-31 of the block
+// of 32; then a dword each, the block's scale byte.
+constexpr int kMxDecSlot = 32;
+constexpr int kMxDecAhead = 16;                      // pages whose loads mx_decode_pv_kernel has on their way
+struct MxDecSplit { int per /* pages of a chunk */, n /* chunks of a sequence */, seg /* pages of a segment */; float* cmax; float* state; unsigned char* rec; };
+__host__ __device__ constexpr size_t mx_dec_rec_bytes(int L) { return (size_t)4 * L * (kMxDecSlot + 4); }
+__device__ inline unsigned char* mx_dec_rec(const MxDecSplit& sp, int L, int bh, int page /* of the segment */) {
+    return sp.rec + ((size_t)bh * sp.seg + page) * mx_dec_rec_bytes(L);
 }
-
-// Few sequences: one workgroup per (sequence, kv head) walks all pages, a microsecond each, while most compute units idle.  The pages are
-// then cut into chunks with a workgroup each.  What a chunk has to know of those in front of it is their row maxima (P-tilde
-// is quantized against the running maximum), and on the FP4 instruction scores are cheap: a launch of its own computes
-// all scores for their maxima alone (mx_decode_max_kernel reads the K half of the records), this one takes them as its starting
-// maximum and does what fwd_mx_decode_kernel does, and mx_decode_merge_kernel adds the chunks' sums, re-based to the last maximum.
-template <int D, bool CAUSAL>
-__global__ __launch_bounds__(256, 2) void fwd_mx_decode_part_kernel(AQ_DEC_ARGS, MxChunks ck)
-{
-    mx_decode_body<D, CAUSAL, 1, true>(qops, qsc, kv, O, lse, L, Hq, G, c, page_table, kv_lens, max_pages, num_pages, lq_inner, ck);
-}
-#undef AQ_DEC_ARGS
 
 // Row maxima of the scores of every chunk but a sequence's last (nobody asks for that one's): blockIdx = (head, chunk).  Operands straight
-// to registers, a page ahead; waves as in mx_decode_body: wave w has product w % 2 of tile w / 2 of each page.
+// to registers, a page ahead; waves as in fwd_mx_decode_kernel: wave w has product w % 2 of tile w / 2 of each page.
 template <int D, bool CAUSAL>
 __global__ __launch_bounds__(256) void mx_decode_max_kernel(
     const unsigned char* __restrict__ qops, const uint32_t* __restrict__ qsc, const unsigned char* __restrict__ kv, int L, int Hq, int G,
@@ -942,52 +920,277 @@ __global__ __launch_bounds__(256) void mx_decode_max_kernel(
     if (wave == 0 && hf == 0) cmax[((size_t)bh * n + ch) * kMxDecRows + ln] = fmaxf(fmaxf(red[0][lane], red[1][lane]), fmaxf(red[2][lane], red[3][lane]));
 }
 
-// O and L of the sequences with several chunks; a thread has one element.
-template <int D>
-__global__ __launch_bounds__(256) void mx_decode_merge_kernel(
-    const int* __restrict__ kv_lens, int Hq, int L, int max_pages, MxChunks ck, uint16_t* __restrict__ O, float* __restrict__ lse, float c)
+template <int D, bool CAUSAL>
+__global__ __launch_bounds__(256) void mx_decode_p_kernel(
+    const unsigned char* __restrict__ qops, const uint32_t* __restrict__ qsc, const unsigned char* __restrict__ kv, int L, int Hq, int G, float c,
+    const int* __restrict__ page_table, const int* __restrict__ kv_lens, int max_pages, int num_pages, int lq_inner, MxDecSplit sp, int seg0 /* first page of the segment */)
 {
-    const int bh = blockIdx.y, e = blockIdx.x * 256 + threadIdx.x;
-    const int nst = min((kv_lens[bh / Hq] + 127) / 128, max_pages), nch = (nst + ck.per - 1) / ck.per;
-    if (nch < 2 || e >= L * D) return;
-    const size_t u0 = (size_t)bh * ck.n;
-    const int r = e / D;
-    const float M = ck.part_m[(u0 + nch - 1) * kMxDecRows + r];               // (running maxima: the last is the largest)
-    float v = 0.0f, l = 0.0f;
-    for (int i0 = 0; i0 < nch; i0 += 16) {                                    // (sixteen chunks' loads in flight at a time)
-        float pm[16], po[16], pl[16];
+    constexpr int KS = D / 64, MT = D / 32, KOPS = 2 * KS * 1024, VOPS = MT * 1024, REC = mx_rec_bytes(D, false), NT = 4;
+    __shared__ float front[8][32], x_max[2][NT][32];
+    const int bh = blockIdx.x, ch = seg0 / sp.per + (int)blockIdx.y, b = bh / Hq, h = bh % Hq, Hkv = Hq / G;
+    const int lane = threadIdx.x & 63, ln = lane & 31, hf = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int Lk = __builtin_amdgcn_readfirstlane(kv_lens[b]);
+    const int p0 = ch * sp.per, nt_all = 2 * min(min((Lk + 127) / 128, max_pages) - p0, sp.per);      // tiles of this chunk
+    if (nt_all <= 0) return;
+    const int koff = Lk - lq_inner;
+    const int klim = CAUSAL ? min(Lk - 1, koff + (lq_inner != L ? ln % lq_inner : ln)) : Lk - 1;
+    uint4v kr[2 * KS], qop[KS];
+    uint32_t ksc;
+    // tile j of the chunk (beyond the last one: the last one)
+    auto page_of = [&](int j) __attribute__((always_inline)) { return page_table[(size_t)b * max_pages + p0 + (min(j, nt_all - 1) >> 1)]; };
+    auto load_k = [&](int j, int id) __attribute__((always_inline)) {
+        const int page = min(max(__builtin_amdgcn_readfirstlane(id), 0), num_pages - 1);           // a bad table entry reads a wrong page, never outside the cache
+        const unsigned char* rec = kv + (((size_t)page * Hkv + h / G) * 2 + (min(j, nt_all - 1) & 1)) * REC;
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const size_t u = u0 + min(i0 + k, nch - 1);
-            pm[k] = i0 + k < nch ? ck.part_m[u * kMxDecRows + r] : -INFINITY;
-            po[k] = ck.part_o[u * L * D + e];
-            pl[k] = ck.part_l[u * kMxDecRows + r];
+        for (int i = 0; i < 2 * KS; ++i) kr[i] = *reinterpret_cast<const uint4v*>(rec + 1024 * i + 16 * lane);
+        ksc = *reinterpret_cast<const uint32_t*>(rec + KOPS + VOPS + 4 * lane);
+    };
+    load_k(wave, page_of(wave));
+    int id_next = page_of(wave + NT);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) qop[ks] = *reinterpret_cast<const uint4v*>(qops + (((size_t)bh * 4 * KS + ks) * 64 + lane) * 16);
+    const uint32_t qs = qsc[(size_t)bh * 4 * 64 + lane];
+    auto as8 = [](const uint4v& x) __attribute__((always_inline)) -> int8v {
+        int8v r = {(int)x[0], (int)x[1], (int)x[2], (int)x[3], 0, 0, 0, 0};
+        return r;
+    };
+    auto lds_barrier = [&]() __attribute__((always_inline)) {       // (fences, not __syncthreads(): the loads of the next tile stay on their way)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    };
+    // the maximum in front of the chunk: the half-waves take every eighth chunk
+    float m = -INFINITY;
+    for (int i = 2 * wave + hf; i < ch; i += 8) m = fmaxf(m, sp.cmax[((size_t)bh * sp.n + i) * kMxDecRows + ln]);
+    front[2 * wave + hf][ln] = m;
+    lds_barrier();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) m = fmaxf(m, front[i][ln]);
+    for (int j0 = 0, buf = 0; j0 < nt_all; j0 += NT, buf ^= 1) {
+        const int j = j0 + wave;
+        const bool active = j < nt_all;
+        const floatx16 zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+        floatx16 s[2];
+        s[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr[0]), as8(qop[0]), zero, 4, 4, 0, ksc, 0, qs);
+        s[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr[KS]), as8(qop[0]), zero, 4, 4, KS, ksc, 0, qs);
+        if constexpr (KS == 2) {
+            s[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr[1]), as8(qop[1]), s[0], 4, 4, 1, ksc, 1, qs);
+            s[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr[3]), as8(qop[1]), s[1], 4, 4, 3, ksc, 1, qs);
         }
+        mfma_scale_settle(s[0], s[1]);
+        if (j0 + NT < nt_all) {
+            load_k(j + NT, id_next);
+            id_next = page_of(j + 2 * NT);
+        }
+        const int k0 = p0 * 128 + j * 64;
+        if (active && ((k0 + 64 > Lk) || (CAUSAL && k0 + 63 > koff))) {
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const float w = __builtin_amdgcn_exp2f((pm[k] - M) * c);          // a chunk that does not exist: weight 0
-            v = fmaf(po[k], w, v);
-            l = fmaf(pl[k], w, l);
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    if (k0 + 32 * hf + 16 * t + i > klim) s[t][i] = -INFINITY;
+        }
+        float pm[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) pm[i] = max_raw(s[0][i], s[1][i]);
+#pragma unroll
+        for (int i = 4; i < 16; ++i) pm[i & 3] = max_nc(max_nc(pm[i & 3], s[0][i]), s[1][i]);
+        const float bm = max_nc(max_nc(pm[0], pm[1]), max_nc(pm[2], pm[3]));      // maximum of this lane's block of 32 keys
+        const float tm = xhalf_max(bm);
+        if (hf == 0) x_max[buf][wave][ln] = tm;
+        lds_barrier();
+        float mT = m;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const float x = x_max[buf][t][ln];
+            if (t <= wave) mT = max_nc(mT, x);
+            if (j0 + t < nt_all) m = max_nc(m, x);
+        }
+        if (active) {
+            const float ms = mT * c;
+            float p[32], sum[2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                float rp[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    p[16 * t + i] = __builtin_amdgcn_exp2f(fmaf(s[t][i], c, -ms));
+                    rp[i & 3] += p[16 * t + i];
+                }
+                sum[t] = (rp[0] + rp[1]) + (rp[2] + rp[3]);                       // un-quantized P-tilde
+            }
+            const uint32_t pbyte = e8m0_of_amax(__builtin_amdgcn_exp2f(fmaf(bm, c, -ms)));
+            const uint4v codes = mx_codes32(p, e8m0_as_f32(pbyte));
+            if (ln < L) {
+                unsigned char* rec = mx_dec_rec(sp, L, bh, p0 - seg0 + (j >> 1));
+                const int slot = (2 * (j & 1) + hf) * L + ln;
+                uint4v* dst = reinterpret_cast<uint4v*>(rec + (size_t)slot * kMxDecSlot);
+                dst[0] = uint4v{codes[0], codes[1], __float_as_uint(sum[0]), __float_as_uint(mT)};
+                dst[1] = uint4v{codes[2], codes[3], __float_as_uint(sum[1]), __float_as_uint(mT)};
+                *reinterpret_cast<uint32_t*>(rec + (size_t)4 * L * kMxDecSlot + 4 * slot) = pbyte;
+            }
         }
     }
-    O[(size_t)bh * L * D + e] = f32_to_bf16_rne(v * (1.0f / l));
-    if (e % D == 0) lse[(size_t)bh * L + r] = M * (c * 0.6931471805599453f) + logf(l);
 }
 
-// How many chunks a sequence of max_pages pages is cut into for `heads` (sequence, kv head)s, 1: not at all.  Two workgroups per compute unit
-// at most, of two pages at least; more chunks than sqrt(8 pages) cost more in maxima to read and sums to add than their shorter
-// walk saves (8 heads, 128 pages: 16 / 32 / 64 chunks 22.9 / 19.4 / 21.0 us).  The two more launches cost what 12 pages take.  Whole step,
-// d = 128, one workgroup per head -> chunks: 8 kv heads of one sequence of 16000 keys 110 -> 19.4 us, of 3000 26.8 -> 16.5 us; 8 sequences of
-// 2000 - 8000 56 -> 26 us, 16 of them (4 chunks) 60 -> 41 us; but 16 of 256 - 2000 20.8 -> 18.8 us, 3 x 40 heads of 500 - 1500 14.9 -> 17.2 us
-// and two chunks for 256 heads of 4k - 16k 116.6 -> 118.6 us.
-static int mx_decode_chunks(int heads, int max_pages) {
-    int n = min(max_pages / 2, kMxDecUnits / heads);
-    while ((long long)n * n > 8ll * max_pages) --n;
-    if (n < 3 || (long long)max_pages * (n - 1) < 12ll * n) return 1;
-    const int per = (max_pages + n - 1) / n;
-    return (max_pages + per - 1) / per;
+// Waves as in fwd_mx_decode_kernel: wave w has the keys {32 hf + 16 t .. + 15} of tile T of every page, t = w % 2, T = w / 2.
+template <int D>
+__global__ __launch_bounds__(256, 2) void mx_decode_pv_kernel(
+    const unsigned char* __restrict__ kv, uint16_t* __restrict__ O, float* __restrict__ lse, int L, int Hq, int G, float c,
+    const int* __restrict__ page_table, const int* __restrict__ kv_lens, int max_pages, int num_pages, MxDecSplit sp, int seg0)
+{
+    constexpr int KS = D / 64, MT = D / 32, KOPS = 2 * KS * 1024, VOPS = MT * 1024, REC = mx_rec_bytes(D, false), PF = kMxDecAhead, NV = 17;
+    __shared__ float red[2][NV][64];
+    __shared__ __align__(16) uint32_t ids[kMxDecPageHeads + 2 * PF];
+    const int bh = blockIdx.x, mt = blockIdx.y, b = bh / Hq, h = bh % Hq, Hkv = Hq / G;
+    const int lane = threadIdx.x & 63, ln = lane & 31, hf = lane >> 5, row = min(ln, L - 1);
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), T = wave >> 1, t = wave & 1;
+    const int nst = min((__builtin_amdgcn_readfirstlane(kv_lens[b]) + 127) / 128, max_pages);
+    if (seg0 > 0 && nst <= seg0) return;                           // finished in a segment in front
+    const int n = max(min(nst - seg0, sp.seg), 0);                 // its pages in this segment
+    // the ids of the segment's pages, in LDS (scalar loads of them would be waited for page by page, all at once each time); behind the last
+    // page: that one again
+    if (n > 0) {
+        for (int i = threadIdx.x; i < n + 2 * PF; i += 256)
+            ids[i] = min(max(page_table[(size_t)b * max_pages + seg0 + min(i, n - 1)], 0), num_pages - 1);      // a bad table entry reads a wrong page, never outside the cache
+    }
+    __syncthreads();
+    const unsigned char* v_head = kv + ((size_t)(h / G) * 2 + T) * REC;
+    const uint32_t page_stride = (uint32_t)Hkv * 2 * REC, rec_stride = (uint32_t)mx_dec_rec_bytes(L);
+    uint4v va[PF], pc[PF];                                         // V; codes, sum, maximum
+    uint32_t vsc[PF], psc[PF];
+    const int slot = (2 * T + hf) * L + row;
+    const uint32_t v_lane = (uint32_t)(KOPS + (mt * 64 + lane) * 16), s_lane = (uint32_t)(KOPS + VOPS + 256 + 4 * lane);
+    const uint32_t p_lane = (uint32_t)(slot * kMxDecSlot + 16 * t), b_lane = (uint32_t)(4 * L * kMxDecSlot + 4 * slot);
+    const unsigned char* p_at = mx_dec_rec(sp, L, bh, 0);           // of the page that is loaded next
+    auto load = [&](int u, uint32_t id) __attribute__((always_inline)) {
+        va[u] = *reinterpret_cast<const uint4v*>(v_head + v_lane + (uint64_t)id * page_stride);
+        vsc[u] = *reinterpret_cast<const uint32_t*>(v_head + s_lane + (uint64_t)id * page_stride);
+        pc[u] = *reinterpret_cast<const uint4v*>(p_at + p_lane);
+        psc[u] = *reinterpret_cast<const uint32_t*>(p_at + b_lane);
+        p_at += rec_stride;
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    floatx16 o;
+    float mref, lsum;
+    float* state = sp.state + ((((size_t)bh * MT + mt) * 4 + wave) * 18 * 2 + hf) * L + row;       // [18][2][L]
+    if (seg0 > 0) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[i] = state[i * 2 * L];
+        mref = state[16 * 2 * L]; lsum = state[17 * 2 * L];
+        asm volatile("" : "+v"(o), "+v"(mref), "+v"(lsum));        // (arrived: they would otherwise be waited for in the loop, every time)
+    } else {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[i] = 0.0f;
+        mref = -INFINITY; lsum = 0.0f;
+    }
+    const int keep_lo = t ? 0 : -1;
+    auto page = [&](int u) __attribute__((always_inline)) {
+        // (pinned copies and results: whatever of a page's registers lived on behind its next load would be copied, all of them at the end of
+        //  the loop, where those loads would then be waited for)
+        float mT;
+        uint32_t vs;
+        asm volatile("v_mov_b32 %0, %1" : "=v"(mT) : "v"(pc[u][3]));
+        asm volatile("v_lshrrev_b32 %0, %1, %2" : "=v"(vs) : "s"(8 * mt), "v"(vsc[u]));
+        const float alpha = __builtin_amdgcn_exp2f((mref - mT) * c);
+        mref = mT;
+        lsum = fmaf(lsum, alpha, __uint_as_float(pc[u][2]));
+        asm volatile("" : "+v"(lsum));
+        if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
+            mfma_scale_settle(o);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) o[i] *= alpha;
+        }
+        const int c0 = (int)pc[u][0], c1 = (int)pc[u][1];
+        const int8v pb = {c0 & keep_lo, c1 & keep_lo, c0 & ~keep_lo, c1 & ~keep_lo, 0, 0, 0, 0};
+        const int8v av = {(int)va[u][0], (int)va[u][1], (int)va[u][2], (int)va[u][3], 0, 0, 0, 0};
+        o = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, pb, o, 4, 4, 0, vs, 0, psc[u]);
+    };
+    // the next PF pages
+    auto load_all = [&](int i, auto between) __attribute__((always_inline)) {
+        uint4v id[PF / 4];
+#pragma unroll
+        for (int u = 0; u < PF / 4; ++u) id[u] = *reinterpret_cast<const uint4v*>(&ids[i + 4 * u]);
+#pragma unroll
+        for (int u = 0; u < PF; ++u) { between(u); load(u, id[u / 4][u % 4]); }
+    };
+    if (n > 0) load_all(0, [](int) {});
+    int i0 = 0;
+    for (; i0 + PF <= n; i0 += PF) load_all(i0 + PF, page);
+#pragma unroll
+    for (int u = 0; u < PF; ++u)
+        if (i0 + u < n) page(u);
+    mfma_scale_settle(o);
+    if (nst > seg0 + sp.seg) {                                      // the sequence goes on in the next segment
+        if (ln < L) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) state[i * 2 * L] = o[i];
+            state[16 * 2 * L] = mref; state[17 * 2 * L] = lsum;
+        }
+        return;
+    }
+    // the waves' sums brought to the last maximum and added, as in fwd_mx_decode_kernel
+    const float m_run = n > 0 ? *reinterpret_cast<const float*>(mx_dec_rec(sp, L, bh, n - 1) + ((2 + hf) * L + row) * kMxDecSlot + 12) : -INFINITY;
+    const float f = (mref == m_run) ? 1.0f : __builtin_amdgcn_exp2f((mref - m_run) * c);
+    float l = xhalf_sum(lsum) * f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) o[i] *= f;
+#pragma unroll
+    for (int step = 2; step >= 1; step >>= 1) {
+        if (wave >= step && wave < 2 * step) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) red[wave - step][i][lane] = o[i];
+            red[wave - step][16][lane] = l;
+        }
+        __syncthreads();
+        if (wave < step) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) o[i] += red[wave][i][lane];
+            l += red[wave][16][lane];
+        }
+        __syncthreads();
+    }
+    if (wave == 0 && ln < L) {
+        const float inv_l = l > 0.0f ? 1.0f / l : 0.0f;                       // a sequence without keys: O = 0, L = -inf
+        const size_t at = (size_t)bh * L + ln;
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) {
+            uint2v w;
+            w[0] = pack_bf16x2_rne(o[4 * tt] * inv_l, o[4 * tt + 1] * inv_l);
+            w[1] = pack_bf16x2_rne(o[4 * tt + 2] * inv_l, o[4 * tt + 3] * inv_l);
+            *reinterpret_cast<uint2v*>(O + at * D + 32 * mt + 8 * tt + 4 * hf) = w;
+        }
+        if (hf == 0 && mt == 0) lse[at] = m_run * (c * 0.6931471805599453f) + logf(l);
+    }
 }
-size_t mx_decode_part_bytes(int heads, int L, int D) { return L > kMxDecRows || 3 * heads > kMxDecUnits ? 0 : (size_t)kMxDecUnits * (3 * kMxDecRows + (size_t)L * D) * 4; }
+
+// How the pages are cut for `heads` (sequence, kv head)s; n = 1: not at all.  Up to four workgroups per compute unit, of two pages at least.  The
+// walk takes 0.85 us a page, two more launches what 12 pages take.  Whole step, d = 128, 8 kv heads, walk -> in parts: one sequence of 3000
+// keys 26.9 -> 15.5 us, of 16000 111 -> 25.0, of 64000 429 -> 67; 8 of 500 - 1700 18.5 -> 14.4, of 2000 - 8000 60 -> 27.2; 16 of 256 - 2000 20.5 ->
+// 19.2, of 2000 - 8000 60 -> 40.7.  In several segments: 14 of 4000 - 16000 (112 heads) 113 -> 79, but 20 of them 113 -> 130 and 20 of
+// 2000 - 8000 61 -> 68: up to 128 heads.  (Chunks added up each by itself, whose bits then depend on how many there are: one sequence 13.6,
+// 19.0 and 38 us, the others the same.)
+static int mx_decode_room(int L) { return min(kMxDecPageHeads, (int)((16u << 20) / mx_dec_rec_bytes(L))); }      // pages times heads
+static MxDecSplit mx_decode_split(int heads, int L, int max_pages)
+{
+    MxDecSplit sp{};
+    sp.n = 1;
+    const int room = mx_decode_room(L) / heads / 2 * 2, want = min((max_pages + 1) / 2, 1024 / heads);
+    if (room < 2 || want < 3 || (long long)max_pages * (want - 1) < 12ll * want) return sp;
+    const int n = max(want, (max_pages + room - 1) / room);
+    if ((long long)n * heads > kMxDecUnits || (max_pages > room && heads > 128)) return sp;
+    sp.per = ((max_pages + n - 1) / n + 1) / 2 * 2;                           // (the kernel of P takes two pages at a time)
+    sp.n = (max_pages + sp.per - 1) / sp.per;
+    sp.seg = min(room, sp.n * sp.per) / sp.per * sp.per;
+    return sp;
+}
+static size_t mx_decode_state_bytes(int heads, int L, int D) { return (size_t)heads * (D / 32) * 4 * 18 * 2 * L * 4; }
+size_t mx_decode_part_bytes(int heads, int L, int D)
+{
+    if (L > kMxDecRows || heads > 170) return 0;
+    return (size_t)kMxDecUnits * kMxDecRows * 4 + mx_decode_state_bytes(heads, L, D) + (size_t)(mx_decode_room(L) + kMxDecAhead) * mx_dec_rec_bytes(L);
+}
 
 // ---------------------------------------------------------------------------------------------
 int launch_mx_quant(const void* x, int BH, int L, int D, int axis, bool fp8, unsigned char* codes, unsigned char* scales, void* xf, hipStream_t st)
@@ -1065,34 +1268,30 @@ int launch_fwd_mx(const void* qops, const void* qsc, const void* kv, int B, int 
 
 int launch_fwd_mx_paged(const void* qops, const void* qsc, const void* cache, int B, int Hq, int Hkv, int Lq, int D, bool causal,
                         const int* page_table, const int* kv_lens, int max_pages, int num_pages, int lq_inner,
-                        float* part, void* o, float* lse, hipStream_t st)
+                        unsigned char* part, void* o, float* lse, hipStream_t st)
 {
     if (Lq <= kMxDecRows) {
         // a step of decoding: the four waves of a workgroup share the keys of a page
         const float c = 1.4426950408889634f / sqrtf((float)D);
-        const int n = part ? mx_decode_chunks(B * Hq, max_pages) : 1;
-        if (n > 1) {
-            const size_t units = (size_t)B * Hq * n;
-            float* cmax = part; part += units * kMxDecRows;
-            MxChunks ck{(max_pages + n - 1) / n, n, cmax, nullptr, nullptr, nullptr};
-            ck.part_l = part; part += units * kMxDecRows;
-            ck.part_m = part; part += units * kMxDecRows;
-            ck.part_o = part;
-            const dim3 grid((unsigned)(B * Hq), (unsigned)n);
-#define AQ_PARTS(DD, CC) do { \
-            constexpr size_t smem = 4 * 2 * (size_t)mx_rec_bytes(DD, false) + 4 * 256; \
-            auto kern = fwd_mx_decode_part_kernel<DD, CC>; \
-            static unsigned long long lds_set = 0; \
-            if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)smem, lds_set)) return -1; \
-            hipLaunchKernelGGL((mx_decode_max_kernel<DD, CC>), dim3(grid.x, grid.y - 1), dim3(256), 0, st, (const unsigned char*)qops, (const uint32_t*)qsc, (const unsigned char*)cache, \
-                               Lq, Hq, Hq / Hkv, page_table, kv_lens, max_pages, num_pages, lq_inner, ck.per, n, cmax); \
-            hipLaunchKernelGGL(kern, grid, dim3(256), smem, st, (const unsigned char*)qops, (const uint32_t*)qsc, (const unsigned char*)cache, \
-                               (uint16_t*)o, lse, Lq, Hq, Hq / Hkv, c, page_table, kv_lens, max_pages, num_pages, lq_inner, ck); \
-            hipLaunchKernelGGL((mx_decode_merge_kernel<DD>), dim3((unsigned)((Lq * DD + 255) / 256), grid.x), dim3(256), 0, st, kv_lens, Hq, Lq, max_pages, ck, (uint16_t*)o, lse, c); \
+        MxDecSplit sp{};
+        if (part) sp = mx_decode_split(B * Hq, Lq, max_pages);
+        if (sp.n > 1) {
+            sp.cmax = reinterpret_cast<float*>(part);
+            sp.rec = part + (size_t)kMxDecUnits * kMxDecRows * 4;
+            sp.state = reinterpret_cast<float*>(sp.rec + (size_t)(mx_decode_room(Lq) + kMxDecAhead) * mx_dec_rec_bytes(Lq));
+#define AQ_SPLIT(DD, CC) do { \
+            hipLaunchKernelGGL((mx_decode_max_kernel<DD, CC>), dim3((unsigned)(B * Hq), (unsigned)(sp.n - 1)), dim3(256), 0, st, (const unsigned char*)qops, (const uint32_t*)qsc, \
+                               (const unsigned char*)cache, Lq, Hq, Hq / Hkv, page_table, kv_lens, max_pages, num_pages, lq_inner, sp.per, sp.n, sp.cmax); \
+            for (int seg0 = 0; seg0 < max_pages; seg0 += sp.seg) { \
+                hipLaunchKernelGGL((mx_decode_p_kernel<DD, CC>), dim3((unsigned)(B * Hq), (unsigned)(min(sp.seg, max_pages - seg0) + sp.per - 1) / sp.per), dim3(256), 0, st, \
+                                   (const unsigned char*)qops, (const uint32_t*)qsc, (const unsigned char*)cache, Lq, Hq, Hq / Hkv, c, page_table, kv_lens, max_pages, num_pages, lq_inner, sp, seg0); \
+                hipLaunchKernelGGL((mx_decode_pv_kernel<DD>), dim3((unsigned)(B * Hq), DD / 32), dim3(256), 0, st, (const unsigned char*)cache, (uint16_t*)o, lse, \
+                                   Lq, Hq, Hq / Hkv, c, page_table, kv_lens, max_pages, num_pages, sp, seg0); \
+            } \
             return hipGetLastError() == hipSuccess ? 0 : -1; } while (0)
-            if (D == 128) { if (causal) AQ_PARTS(128, true); else AQ_PARTS(128, false); }
-            if (D == 64)  { if (causal) AQ_PARTS(64, true); else AQ_PARTS(64, false); }
-#undef AQ_PARTS
+            if (D == 128) { if (causal) AQ_SPLIT(128, true); else AQ_SPLIT(128, false); }
+            if (D == 64)  { if (causal) AQ_SPLIT(64, true); else AQ_SPLIT(64, false); }
+#undef AQ_SPLIT
             return -1;
         }
 #define AQ_DECODE(DD, CC) do { \

@@ -204,8 +204,8 @@ def test_decode_kernels_without_a_queue_keep_off_scratch_memory():
 
 
 def test_mx_decode_kernels_in_chunks_do_not_spill():
-    _check(_resources("mx.hip"), r"(fwd_mx_decode_part_kernel|mx_decode_max_kernel)ILi(64|128)ELb[01]E", 8)
-    _check(_resources("mx.hip"), r"mx_decode_merge_kernelILi(64|128)E", 2)
+    _check(_resources("mx.hip"), r"mx_decode_(p|max)_kernelILi(64|128)ELb[01]E", 8)
+    _check(_resources("mx.hip"), r"mx_decode_pv_kernelILi(64|128)E", 2)
 
 
 def test_split_mx_forward_kernels_do_not_spill():
