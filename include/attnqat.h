@@ -380,7 +380,8 @@ int attnqat_fwd_infer_mx_paged(const void* q, int B, int Hq, int Hkv, int Lq, in
  *     in chunk order, so a predecessor is always running or finished when someone waits for it and the wait ends; it is
  *     bounded nevertheless (2^22 polls), and a wait that expired leaves a wrong result for that sequence.  The partial
  *     sums of the chunks of a sequence are added by a third kernel.  Steps with few keys do without the queue: one kernel
- *     computes all scores (kept in the workspace), the next does the rest in chunks of 256 keys.  The result is not bit-identical to
+ *     computes all scores (kept in the workspace: 384 + 1024 bytes per row for every 256 positions of the page table, sequence and
+ *     kv head, at most 128 MiB), the next does the rest in chunks of 256 keys.  The result is not bit-identical to
  *     attnqat_fwd_infer (the sums are grouped differently) but holds the same parity bars against the oracle.  It is
  *     deterministic; the grouping (the length of the chunks) follows from B, Hkv, the rows, max_pages and the device's compute
  *     units, so a sequence's last bits may differ between steps with other sequences beside it or a wider page table.  A

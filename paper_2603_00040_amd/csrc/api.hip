@@ -488,7 +488,7 @@ PagedWs carve_paged(void* ws, size_t given, bool queue /* not the two launches w
     const int R = (Hq / Hkv) * Lq;
     if (R <= decode_max_rows()) {
         if (!queue && decode_is_direct(B, Hkv, R, max_pages, cus)) {
-            w.dec = c.take(decode_direct_ws_bytes(B, Hkv, R, max_pages, d));
+            w.dec = c.take(decode_direct_ws_bytes(B, Hkv, R, max_pages));
             w.direct = c.off <= given;
             if (w.direct) { w.bytes = c.off; return w; }
             c.off = 0;                                   // (an older, smaller workspace: the queue)

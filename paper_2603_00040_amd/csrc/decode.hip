@@ -551,7 +551,7 @@ __global__ __launch_bounds__(256, 2) void decode_kernel(
 template <int D>
 __global__ __launch_bounds__(256) void decode_merge_kernel(
     const int* __restrict__ kv_lens, int Hkv, int R, int CK, int NC, int max_pages,
-    const float* __restrict__ part_o, const float* __restrict__ part_l, const float* __restrict__ part_m,
+    const float* __restrict__ part_o, int o_stride /* floats per chunk */, const float* __restrict__ part_l, const float* __restrict__ part_m,
     uint16_t* __restrict__ O, float* __restrict__ lse, float c)
 {
     const int per = (R * D + 255) / 256;             // workgroups per (sequence, kv head): a thread has one element
@@ -569,7 +569,7 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(
         for (int k = 0; k < 16; ++k) {
             const size_t u = u0 + min(i0 + k, nch - 1);
             pm[k] = i0 + k < nch ? part_m[u * kDecRows + r] : -INFINITY;
-            po[k] = part_o[u * R * D + e];
+            po[k] = part_o[u * o_stride + e];
             pl[k] = part_l[u * kDecRows + r];
         }
         float Mn = M;
@@ -682,8 +682,8 @@ __global__ __launch_bounds__(256) void decode_scores_kernel(
 template <int D>
 __global__ __launch_bounds__(256) void decode_values_kernel(
     const unsigned char* __restrict__ cache, int num_pages, const int* __restrict__ page_table, const int* __restrict__ kv_lens,
-    int Hkv, int R, int NC, int max_pages, const float* __restrict__ S, const float* __restrict__ tmax,
-    float* __restrict__ part_o, float* __restrict__ part_l, float* __restrict__ part_m, uint16_t* __restrict__ O, float* __restrict__ lse, float c /* log2(e)/sqrt(d) */)
+    int Hkv, int R, int NC, int max_pages, float* S /* scores; later, in their place, the chunk's O [R][D] */, const float* __restrict__ tmax,
+    float* __restrict__ part_l, float* __restrict__ part_m, uint16_t* __restrict__ O, float* __restrict__ lse, float c /* log2(e)/sqrt(d) */)
 {
     constexpr int NS = D / 32, NDT = D / 16, RS = 2 * D + 16, PS = 144;
     constexpr size_t VOFF = (size_t)128 * (D / 2 + D / 16);
@@ -806,7 +806,7 @@ __global__ __launch_bounds__(256) void decode_values_kernel(
         if (wave == 0 && g == 0 && cc < R) lse[(size_t)x.bh * R + cc] = m_end * ln2c + logf(l_of(cc));
         return;
     }
-    for (int e = tid; e < R * D; e += 256) part_o[unit * R * D + e] = o_of(e);
+    for (int e = tid; e < R * D; e += 256) S[unit * kDirTiles * (R * 64) + e] = o_of(e);      // (every wave took its scores in front of the last two barriers)
     if (wave == 0 && g == 0 && cc < R) {
         part_l[unit * kDecRows + cc] = l_of(cc);
         part_m[unit * kDecRows + cc] = m_end;
@@ -820,7 +820,8 @@ __global__ __launch_bounds__(256) void decode_values_kernel(
 // within one per compute unit.  A workgroup needs 13 us for one tile per wave and 3 - 4 us for each further one, in a chain
 // that nothing overlaps, so more and shorter chunks are faster there (kernel at 8 kv heads, one sequence: 3000 keys 25.9 -> 16.2 us
 // with chunks of 256 instead of 1024, 8000 keys 26.5 -> 20.1 us); with all units busy they only cost (32 sequences of 4k - 16k
-// keys: 108 us, 146 us with chunks of 512).
+// keys: 108 us, 146 us with chunks of 512).  (Steps as small as that do without the queue, see decode_is_direct, unless they come through the
+// debug entry point or with a workspace that has no room for the scores.)
 static int chunk_keys(int R, int halvings) {
     int ck = max(256, min(1024, (kDecSFloats / R) / 128 * 128));
     for (int i = 0; i < halvings; ++i) ck = max(256, ck / 2 / 128 * 128);
@@ -846,8 +847,8 @@ size_t decode_ws_bytes(int B, int Hkv, int R, int max_pages, int D, int halvings
 }
 
 // ---- the two launches without a queue
-struct DirectWs { int NC; size_t units, tmax, scores, part_l, part_m, part_o, bytes; };
-static DirectWs direct_ws(int B, int Hkv, int R, int max_pages, int D)
+struct DirectWs { int NC; size_t units, tmax, scores, part_l, part_m, bytes; };
+static DirectWs direct_ws(int B, int Hkv, int R, int max_pages)
 {
     DirectWs w{};
     w.NC = (max_pages * 128 + 64 * kDirTiles - 1) / (64 * kDirTiles);
@@ -857,27 +858,28 @@ static DirectWs direct_ws(int B, int Hkv, int R, int max_pages, int D)
     w.scores = take(w.units * kDirTiles * R * 64 * 4);
     w.part_l = take(w.units * kDecRows * 4);
     w.part_m = take(w.units * kDecRows * 4);
-    w.part_o = take(w.units * R * D * 4);
     return w;
 }
 // Up to twelve chunks of 256 keys per compute unit, counted by the page table's width, or 40 where the queue's chunks are no longer than
 // that either (more than ten rows).  Queue -> direct, whole step, d = 128, 8 kv heads: 4 rows: 1 sequence of 3000 keys (96 chunks) 20.4 -> 14.1 us,
 // of 16000 (504) 28.8 -> 20.3; 8 of 500 - 3000 (768) 27.2 -> 17.5; 16 of 4000 (2048) 41.9 -> 35.2; 12 of 8000 (3072) 50.7 -> 47.7; 16 of
 // 2000 - 8000 (4096) 49.9 -> 52.4; 32 of 4k - 16k (16384) 104 -> about 190: the queue reads no scores back and keeps loads in flight across
-// chunks.  16 rows: 8 of 4000 (1024) 50.5 -> 33.9; 16 of 2000 - 8000 (4096) 89.9 -> 79.0; 40 of 2000 - 16000, 4 kv heads (10080) 163 -> 139, but
-// the scores alone then take 160 MB.
+// chunks.  16 rows: 8 of 4000 (1024) 50.5 -> 33.9; 16 of 2000 - 8000 (4096) 89.9 -> 79.0; 40 of 2000 - 16000, 4 kv heads (10080) 163 -> 139.
+// And no more than 128 MiB of scores and maxima (384 + 1024 R bytes per chunk), 7990 chunks of 16 rows: the last of these would take 169 MB
+// where the queue takes 86.
 bool decode_is_direct(int B, int Hkv, int R, int max_pages, int cus)
 {
-    return (long long)B * Hkv * ((max_pages + 1) / 2) <= (long long)cus * (chunk_keys(R, 0) == 64 * kDirTiles ? 40 : 12);
+    return (long long)B * Hkv * ((max_pages + 1) / 2) <= (long long)cus * (chunk_keys(R, 0) == 64 * kDirTiles ? 40 : 12)
+        && direct_ws(B, Hkv, R, max_pages).bytes <= ((size_t)128 << 20);
 }
-size_t decode_direct_ws_bytes(int B, int Hkv, int R, int max_pages, int D) { return direct_ws(B, Hkv, R, max_pages, D).bytes; }
+size_t decode_direct_ws_bytes(int B, int Hkv, int R, int max_pages) { return direct_ws(B, Hkv, R, max_pages).bytes; }
 
 int launch_decode_direct(const void* q, const void* cache, int num_pages, const int* page_table, int max_pages, const int* kv_lens,
                          int B, int Hq, int Hkv, int Lq, int D, bool causal, void* ws, void* o, float* lse, hipStream_t st)
 {
     const int R = (Hq / Hkv) * Lq;
     if (R < 1 || R > kDecRows || (D != 64 && D != 128) || B * Hkv > 65535) return -1;
-    const DirectWs w = direct_ws(B, Hkv, R, max_pages, D);
+    const DirectWs w = direct_ws(B, Hkv, R, max_pages);
     unsigned char* p = (unsigned char*)ws;
     const dim3 grid((unsigned)w.NC, (unsigned)(B * Hkv));
     const float c = 1.4426950408889634f / sqrtf((float)D);
@@ -885,10 +887,10 @@ int launch_decode_direct(const void* q, const void* cache, int num_pages, const 
         hipLaunchKernelGGL((decode_scores_kernel<DD, C>), grid, dim3(256), 0, st, (const uint16_t*)q, (const unsigned char*)cache, num_pages, page_table, kv_lens, \
                            Hkv, Lq, R, w.NC, max_pages, (float*)(p + w.scores), (float*)(p + w.tmax), (uint16_t*)o, lse); \
         hipLaunchKernelGGL((decode_values_kernel<DD>), grid, dim3(256), 0, st, (const unsigned char*)cache, num_pages, page_table, kv_lens, \
-                           Hkv, R, w.NC, max_pages, (const float*)(p + w.scores), (const float*)(p + w.tmax), \
-                           (float*)(p + w.part_o), (float*)(p + w.part_l), (float*)(p + w.part_m), (uint16_t*)o, lse, c); \
+                           Hkv, R, w.NC, max_pages, (float*)(p + w.scores), (const float*)(p + w.tmax), \
+                           (float*)(p + w.part_l), (float*)(p + w.part_m), (uint16_t*)o, lse, c); \
         if (w.NC > 1) hipLaunchKernelGGL((decode_merge_kernel<DD>), dim3((unsigned)(B * Hkv * ((R * DD + 255) / 256))), dim3(256), 0, st, kv_lens, Hkv, R, 64 * kDirTiles, w.NC, \
-                           max_pages, (const float*)(p + w.part_o), (const float*)(p + w.part_l), (const float*)(p + w.part_m), (uint16_t*)o, lse, c); } while (0)
+                           max_pages, (const float*)(p + w.scores), kDirTiles * R * 64, (const float*)(p + w.part_l), (const float*)(p + w.part_m), (uint16_t*)o, lse, c); } while (0)
     if (D == 128) { if (causal) AQ_DIR(128, true); else AQ_DIR(128, false); }
     else          { if (causal) AQ_DIR(64, true); else AQ_DIR(64, false); }
 #undef AQ_DIR
@@ -932,9 +934,9 @@ int launch_decode(const void* q, void* qh, const void* cache, int num_pages, con
     if (hipGetLastError() != hipSuccess) return -1;
     if (NC > 1) {
         if (D == 128) hipLaunchKernelGGL((decode_merge_kernel<128>), dim3((unsigned)(B * Hkv * ((R * D + 255) / 256))), dim3(256), 0, st, kv_lens, Hkv, R, CK, NC, max_pages,
-                                         part_o, part_l, part_m, (uint16_t*)o, lse, c);
+                                         part_o, R * D, part_l, part_m, (uint16_t*)o, lse, c);
         else          hipLaunchKernelGGL((decode_merge_kernel<64>), dim3((unsigned)(B * Hkv * ((R * D + 255) / 256))), dim3(256), 0, st, kv_lens, Hkv, R, CK, NC, max_pages,
-                                         part_o, part_l, part_m, (uint16_t*)o, lse, c);
+                                         part_o, R * D, part_l, part_m, (uint16_t*)o, lse, c);
     }
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }

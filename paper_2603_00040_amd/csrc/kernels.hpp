@@ -79,7 +79,7 @@ int launch_decode(const void* q, void* qh, const void* cache, int num_pages, con
 
 // The same for a step with few chunks: two launches without a queue (see decode.hip).  ws: decode_direct_ws_bytes() bytes.
 bool decode_is_direct(int B, int Hkv, int R, int max_pages, int cus);
-size_t decode_direct_ws_bytes(int B, int Hkv, int R, int max_pages, int D);
+size_t decode_direct_ws_bytes(int B, int Hkv, int R, int max_pages);
 int launch_decode_direct(const void* q, const void* cache, int num_pages, const int* page_table, int max_pages, const int* kv_lens,
                          int B, int Hq, int Hkv, int Lq, int D, bool causal, void* ws, void* o, float* lse, hipStream_t st);
 

@@ -46,6 +46,16 @@ def test_host_side_queries_need_no_gpu():
     assert aq.workspace_bytes(99, B, Hq, Hkv, L, d) == 0
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,Lq,pages,d", [(40, 16, 4, 4, 125, 128), (12, 32, 8, 1, 63, 128), (30, 16, 4, 4, 131, 64), (32, 32, 8, 1, 128, 128), (1, 16, 1, 1, 8192, 64),
+                                                 (64, 16, 8, 8, 32, 128), (50, 12, 4, 4, 100, 128)])
+def test_decode_workspace_is_bounded(B, Hq, Hkv, Lq, pages, d):
+    """NVFP4 decode steps without the queue keep all scores in the workspace: up to 128 MiB of them, beyond that the queue's size (chunks of
+    256 keys at the shortest: items, tagged maxima, l and m of 16 rows, O)."""
+    R, chunks = Hq // Hkv * Lq, B * Hkv * ((pages + 1) // 2)
+    direct, queue = chunks * (384 + 1024 * R) + 4 * 256, 256 + chunks * (64 + 16 * 8 + 16 * 8 + R * d * 4) + B * Hkv * 128 * d * 2 + 4 * 256
+    assert 0 < aq.lib().attnqat_paged_workspace_bytes(B, Hq, Hkv, Lq, pages, d) <= max(queue, min(direct, 128 << 20))
+
+
 def test_argument_validation_happens_before_any_gpu_call():
     f = aq.lib().attnqat_fwd_infer
     assert f(None, None, None, 1, 2, 2, 64, 128, 0, 0, None, None, None, 0, None) == aq.EINVAL
