@@ -41,6 +41,19 @@ def _fill_cache(aq, x, Hkv, d, kv_lens, seed, pieces=1):
     return cache, num_pages, table
 
 
+def _longest_chunk(R):
+    """Keys of the queue's longest chunks: the scores of R rows fit 4096 floats of LDS."""
+    return max(256, min(1024, 4096 // R // 128 * 128))
+
+
+def _queue_bytes(B, Hkv, R, pages, d, keys):
+    """Workspace of a decode step through the queue with chunks of that many keys: phi(Q), then counters and, per chunk, tagged maxima, l and m
+    of 16 rows, O and an item of the list."""
+    up = lambda n: (n + 255) // 256 * 256  # noqa: E731
+    chunks = B * Hkv * ((pages * 128 + keys - 1) // keys)
+    return up(B * Hkv * 128 * d * 2) + up(256 + chunks * (16 * 8 + 2 * 16 * 4 + R * d * 4 + 64))
+
+
 def _run(Hq, Hkv, d, kv_lens, Lq, causal, seed, pieces=1, tol=TOL, **kw):
     import paper_2603_00040_amd as aq
     B = len(kv_lens)
@@ -48,8 +61,18 @@ def _run(Hq, Hkv, d, kv_lens, Lq, causal, seed, pieces=1, tol=TOL, **kw):
     cache, num_pages, table = _fill_cache(aq, x, Hkv, d, kv_lens, seed, pieces)
     qb = np.stack([x["q"][b, :, n - Lq:n] for b, n in enumerate(kv_lens)])      # the last Lq positions of every sequence
     q = to_dev(np.ascontiguousarray(qb))
-    o, lse = aq.attnqat_fwd_infer_paged(q, cache, num_pages, torch.from_numpy(table).cuda(),
-                                        torch.tensor(kv_lens, dtype=torch.int32, device="cuda"), Hkv, causal)
+    args = (q, cache, num_pages, torch.from_numpy(table).cuda(), torch.tensor(kv_lens, dtype=torch.int32, device="cuda"), Hkv, causal)
+    o, lse = aq.attnqat_fwd_infer_paged(*args)
+    outs = [(o, lse)]
+    if Hq // Hkv * Lq <= 16:      # a decode step: steps as small as these do without the queue of chunks, the debug entry point always takes it
+        oq, lq, expired = aq.attnqat_fwd_infer_paged(*args, spin_limit=1 << 22)
+        assert not expired
+        outs.append((oq, lq))
+        # ... and with a workspace that only has room for its longest chunks
+        oq, lq, expired = aq.attnqat_fwd_infer_paged(*args, spin_limit=1 << 22, workspace=torch.empty(
+            _queue_bytes(B, Hkv, Hq // Hkv * Lq, table.shape[1], d, _longest_chunk(Hq // Hkv * Lq)), dtype=torch.uint8, device="cuda"))
+        assert not expired
+        outs.append((oq, lq))
     torch.cuda.synchronize()
     worst = 0.0
     for b, n in enumerate(kv_lens):
@@ -57,10 +80,11 @@ def _run(Hq, Hkv, d, kv_lens, Lq, causal, seed, pieces=1, tol=TOL, **kw):
         qf[0, :, n - Lq:] = f32(qb[b])
         rows = oracle.flat_rows(1, Hq, n, [(0, h, i) for h in range(Hq) for i in range(n - Lq, n)])
         ref = oracle.fwd(qf, f32(x["k"][b:b + 1, :, :n]), f32(x["v"][b:b + 1, :, :n]), causal, aq.block_k(), rows=rows)
-        check_bf16_output("O", host(o[b]).reshape(-1, d), ref["O"], tol, label=f"sequence {b} ({n} keys)")
-        eL = max_abs(host(lse[b]).reshape(-1), ref["L"])
-        worst = max(worst, eL)
-        assert eL <= 2e-5 * max(1.0, np.abs(ref["L"]).max()), (b, n, eL)
+        for i, (oi, li) in enumerate(outs):
+            check_bf16_output("O", host(oi[b]).reshape(-1, d), ref["O"], tol, label=f"sequence {b} ({n} keys), call {i}")
+            eL = max_abs(host(li[b]).reshape(-1), ref["L"])
+            worst = max(worst, eL)
+            assert eL <= 2e-5 * max(1.0, np.abs(ref["L"]).max()), (b, n, i, eL)
     print(f"paged nvfp4 Hq{Hq} Hkv{Hkv} d{d} kv_lens{kv_lens} Lq{Lq} causal{int(causal)} pieces{pieces}: worst L {worst:.2e}", flush=True)
     return x, q, cache, num_pages, table, o, lse
 
@@ -85,8 +109,8 @@ def test_few_positions_grouped_heads(d, causal):
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("d", [64, 128])
 def test_decode_sequences_cut_into_chunks(d, causal):
-    # 4 rows per (sequence, kv head): chunks of 1024 keys, up to 5 of them; 12 rows: chunks of 256 keys, up to 12; 16 rows (the
-    # most the decode kernel takes); lengths at chunk and tile edges; more (sequence, head, chunk) units than workgroups wait for
+    # without the queue (chunks of 256 keys), through it with the same chunks, and with its longest: 4 rows per (sequence, kv head): 1024
+    # keys, up to 5 of them; 12 rows: 256 keys, up to 12; 16 rows (the most the decode kernels take); lengths at chunk and tile edges
     _run(8, 2, d, [5000, 1030, 1024, 3, 2049], 1, causal, seed=50 + d, k_chan=4)
     _run(8, 2, d, [3000, 700, 257], 3, causal, seed=51 + d)
     _run(16, 1, d, [1500, 256], 1, causal, seed=52 + d, dist="t3", scale=0.5)
@@ -95,7 +119,7 @@ def test_decode_sequences_cut_into_chunks(d, causal):
 
 
 def test_decode_many_short_sequences():
-    """More sequences than the chunk list's builder takes at a time (256): the list is built from the lengths in
+    """More sequences than the builder of the queue's list takes at a time (256): the list is built from the lengths in
     memory, and every sequence is a single chunk."""
     rng = np.random.default_rng(9)
     lens = [int(n) for n in rng.integers(1, 41, size=2100)]
@@ -106,7 +130,7 @@ def test_decode_many_short_sequences():
 
 def test_decode_wait_limit_is_honoured_and_leaves_no_state():
     """The bounded wait of a chunk for the maxima of the chunks before it: with no polls allowed the kernel still finishes
-    (waits that found nothing are reported), and the next ordinary call is unaffected."""
+    (waits that found nothing are reported), and the next calls, through the queue and without it, are unaffected."""
     import paper_2603_00040_amd as aq
     Hq, Hkv, d, lens = 8, 2, 128, [6000, 4100, 5000, 2100]
     x = random_inputs(len(lens), Hq, Hkv, max(lens), d, 77)
@@ -119,13 +143,19 @@ def test_decode_wait_limit_is_honoured_and_leaves_no_state():
     torch.cuda.synchronize()
     print(f"decode wait limit 0: expired={expired0}; limit 2^22: expired={expired1}", flush=True)
     assert expired1 is False
-    assert torch.equal(l1, l2)          # lse depends on the scores and the row sums of P-tilde only: the same in any order of arrival
+    assert torch.equal(l1, l2) and torch.equal(o1, o2)          # (chunks of 256 keys either way)
+    # an ordinary call through the queue, on the workspace that the expired one has left: chunks of 1024 keys
+    ws = torch.empty(_queue_bytes(len(lens), Hkv, Hq // Hkv, tab.shape[1], d, 1024), dtype=torch.uint8, device="cuda")
+    aq.attnqat_fwd_infer_paged(q, cache, num_pages, tab, kl, Hkv, True, spin_limit=0, workspace=ws)
+    o3, l3 = aq.attnqat_fwd_infer_paged(q, cache, num_pages, tab, kl, Hkv, True, workspace=ws)
     for b, n in enumerate(lens):
         qf = np.zeros((1, Hq, n, d), np.float32)
         qf[0, :, n - 1:] = f32(host_bits(q[b]))
         rows = oracle.flat_rows(1, Hq, n, [(0, h, n - 1) for h in range(Hq)])
         ref = oracle.fwd(qf, f32(x["k"][b:b + 1, :, :n]), f32(x["v"][b:b + 1, :, :n]), True, aq.block_k(), rows=rows)
-        check_bf16_output("O", host(o2[b]).reshape(-1, d), ref["O"], TOL, label=f"sequence {b}")
+        for o, lse in ((o1, l1), (o2, l2), (o3, l3)):
+            check_bf16_output("O", host(o[b]).reshape(-1, d), ref["O"], TOL, label=f"sequence {b}")
+            assert max_abs(host(lse[b]).reshape(-1), ref["L"]) <= 2e-5 * max(1.0, np.abs(ref["L"]).max())
 
 
 def test_whole_sequences_d64_gqa():
@@ -213,8 +243,8 @@ def test_argument_errors_and_bad_page_ids():
 
 @pytest.mark.parametrize("Hq,Hkv,Lq,d,lens", [(8, 2, 1, 128, (255, 256, 257, 3000)), (4, 4, 4, 64, (512, 1023, 1025, 1)), (4, 1, 1, 128, (4097,)), (6, 1, 1, 64, (2000, 2304))])
 def test_decode_chunks_of_any_length_agree(Hq, Hkv, Lq, d, lens):
-    """Short chunks spread a small step over the chip; a workspace without room for them gets longer ones.  The same P^F and the
-    same fp32 terms, added in another grouping."""
+    """The queue's chunks are as long as the step allows; a workspace without room for short ones gets longer ones, and one without room for
+    the scores of the launches without a queue gets the queue.  The same P^F and the same fp32 terms, added in another grouping."""
     import paper_2603_00040_amd as aq
     lens = [max(n, Lq) for n in lens]
     B, pages = len(lens), [(max(n, Lq) + 127) // 128 for n in lens]
@@ -229,10 +259,16 @@ def test_decode_chunks_of_any_length_agree(Hq, Hkv, Lq, d, lens):
     q = to_dev(random_inputs(B, Hq, Hkv, Lq, d, seed=1)["q"])
     kl = torch.tensor(lens, dtype=torch.int32, device="cuda")
     need = aq.lib().attnqat_paged_workspace_bytes(B, Hq, Hkv, Lq, max(pages), d)
-    run = lambda nbytes: aq.attnqat_fwd_infer_paged(q, cache, sum(pages), table, kl, Hkv, True,  # noqa: E731
-                                                    workspace=torch.empty(nbytes, dtype=torch.uint8, device="cuda"))
+    R = Hq // Hkv * Lq
+    short, long = (_queue_bytes(B, Hkv, R, max(pages), d, keys) for keys in (256, _longest_chunk(R)))
+    assert long < short and long < need - 256
+    run = lambda nbytes, **kw: aq.attnqat_fwd_infer_paged(q, cache, sum(pages), table, kl, Hkv, True,  # noqa: E731
+                                                          workspace=torch.empty(nbytes, dtype=torch.uint8, device="cuda"), **kw)
     o, lse = run(need)
-    o2, lse2 = run(need - 1)
+    os, ls, _ = run(short, spin_limit=1 << 22)
+    o2, lse2, _ = run(long, spin_limit=1 << 22)
+    o3, lse3 = run(long)
+    assert torch.equal(o, os) and torch.equal(lse, ls) and torch.equal(o2, o3) and torch.equal(lse2, lse3)
     # fp32 sums of the same terms (errors of 2^-24 times the sum of their magnitudes), one rounding to bf16 each
     a, r = o.float(), o2.float()
     assert bool(((a - r).abs() <= 2.0 ** -7 * r.abs() + 1e-5 * r.abs().max()).all())
