@@ -100,22 +100,22 @@ __device__ inline float e8m0_inverse_as_f32(uint32_t byte) { return __uint_as_fl
 __host__ __device__ constexpr int mx_ktrain_rec_bytes(int D) { return 2 * (D / 64) * 1024 + 1024; }
 
 // The result of v_mfma_scale_f32_32x32x64_f8f6f4 must not be read by a vector instruction before the wait states of the matrix
-// pipeline have passed; the compiler counts them inside a basic block, but when the product is the last instruction of a
-// block it inserts nothing at the start of the next one (seen: the first score register read too early, NaN).  These
+// pipeline have passed (11 with FP4 operands, 19 with FP8).  The compiler counts them for its own instructions, over the ends of basic blocks
+// too (the rescaling of O in fwd_mx_split_kernel and mx_decode_pv_kernel, in a block of its own, has them in the listing, which a test reads), but
+// not for the operands of inline assembly, such as max_raw below: there the first score register was once read too early, NaN.  These
 // no-ops, tied to the accumulators by a data dependence, stand behind the last score product of a tile in every kernel
 // that uses the instruction on the 16-bit path.
 __device__ inline void mfma_scale_settle(floatx16& a) { asm volatile("s_nop 15\n\ts_nop 15" : "+v"(a)); }
 __device__ inline void mfma_scale_settle(floatx16& a, floatx16& b) { asm volatile("s_nop 15\n\ts_nop 15" : "+v"(a), "+v"(b)); }
-// The same behind v_mfma_f32_32x32x16 (eight passes: 11 wait states) where inline assembly, whose operands the compiler's count does not
-// look at, may be the first to read the product.
-__device__ inline void mfma_settle(floatx16& a, floatx16& b) { asm volatile("s_nop 11" : "+v"(a), "+v"(b)); }
 
 // max(a, b) written as median(a, b, +inf): fmaxf() on values the compiler cannot prove quiet (MFMA
 // results) costs a canonicalizing v_max per operand, the median has no such requirement and the
 // compiler folds chains of it into v_max3.  No NaN reaches these reductions.
 __device__ inline float max_nc(float a, float b) { return __builtin_amdgcn_fmed3f(a, b, __builtin_inff()); }
 // A lone two-input maximum still gets its operands canonicalized (v_max x, x, x twice) when they come out of an MFMA or a
-// cross-lane move; this one is the bare instruction.  Same precondition: no NaN.
+// cross-lane move; this one is the bare instruction.  Same precondition: no NaN.  The compiler does not count wait states for the operands of
+// inline assembly: a matrix product may be read here only behind a barrier or a settling wait, or beside an operand that an ordinary
+// instruction has made from the same product.
 __device__ inline float max_raw(float a, float b) {
     float r;
     asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));

@@ -333,7 +333,9 @@ __device__ __forceinline__ void fwd_body(
                 const int b0 = 8 * (ks & 1);
                 const float a0 = max_nc(max_nc(sv[b0], sv[b0 + 1]), sv[b0 + 2]);
                 const float a1 = max_nc(max_nc(sv[b0 + 3], sv[b0 + 4]), sv[b0 + 5]);
-                gmax[ks] = max_nc(max_nc(a0, a1), max_raw(sv[b0 + 6], sv[b0 + 7]));
+                // (SPLIT has no barrier between the products and here: max_raw only beside what was made from the same product)
+                if constexpr (SPLIT) gmax[ks] = max_raw(max_nc(max_nc(a0, a1), sv[b0 + 6]), sv[b0 + 7]);
+                else gmax[ks] = max_nc(max_nc(a0, a1), max_raw(sv[b0 + 6], sv[b0 + 7]));
             }
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) gmax[ks] = xhalf_max(gmax[ks]);
@@ -635,7 +637,6 @@ __device__ __forceinline__ void fwd_body(
                         if constexpr (MORE) kr[i] = *reinterpret_cast<const half8*>(k_head + (size_t)k_next * (64 * D) + 512 * i + 8 * lane);
                         __builtin_amdgcn_sched_barrier(0);
                     }
-                    mfma_settle(s[0], s[1]);             // (no barrier stands between the products and max_raw here)
                 }
                 float bsc[4], binv[4];
                 vector_phase(j, bsc, binv);

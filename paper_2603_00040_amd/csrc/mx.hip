@@ -554,7 +554,6 @@ __global__ __launch_bounds__(256, 2) void fwd_mx_split_kernel(
                 lsum = lsum * al[t] + sm[t];                        // l in tile order
                 if (has_o) {
                     if (__builtin_amdgcn_ballot_w64(al[t] != 1.0f) != 0) {
-                        mfma_scale_settle(o);                       // (the product of the tile in front stands in another block)
 #pragma unroll
                         for (int i = 0; i < 16; ++i) o[i] *= al[t];
                     }
@@ -1098,7 +1097,6 @@ __global__ __launch_bounds__(256, 2) void mx_decode_pv_kernel(
         lsum = fmaf(lsum, alpha, __uint_as_float(pc[u][2]));
         asm volatile("" : "+v"(lsum));
         if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
-            mfma_scale_settle(o);
 #pragma unroll
             for (int i = 0; i < 16; ++i) o[i] *= alpha;
         }

@@ -158,18 +158,21 @@ def test_preparing_kernels_keep_off_scratch_memory():
         assert all(v["Occupancy [waves/SIMD]"] >= 5 for v in hit.values()), hit
 
 
-def test_no_lds_read_is_in_flight_at_a_barrier_of_the_forward():
+@pytest.mark.parametrize("src", ["fwd.hip", "mx.hip"])
+def test_no_lds_read_is_in_flight_at_a_barrier_of_the_forward(src):
     """The forward's barriers are bare ones (no fence): behind a barrier another wave copies the next tile over the one that was just
-    read, so every LDS read has to have arrived before it (listing read from top to bottom, reads minus what the waits leave).  In
-    the four-wave kernels the second barrier is the one behind the scores of tile 0: all of their products stand in front of it."""
+    read, or, where waves share key tiles, writes its P and row maxima over them, so every LDS read has to have arrived before it (listing
+    read from top to bottom, reads minus what the waits leave).  In the four-wave kernels the second barrier is the one behind the scores of
+    tile 0: all of their products stand in front of it."""
     with tempfile.TemporaryDirectory() as tmp:
         out = os.path.join(tmp, "x.s")
-        r = subprocess.run(["hipcc", *B.FLAGS, "-S", "--cuda-device-only", os.path.join(B.CSRC, "fwd.hip"), "-o", out], capture_output=True, text=True)
+        r = subprocess.run(["hipcc", *B.FLAGS, "-S", "--cuda-device-only", os.path.join(B.CSRC, src), "-o", out], capture_output=True, text=True)
         assert r.returncode == 0, r.stderr[-2000:]
         text = open(out).read().splitlines()
     seen, cur = {}, None
     for line in (l.strip() for l in text):
-        m = re.match(r"^_ZN2aq\d+(fwd_(?:narrow_)?kernel)ILi(64|128)E\S*?(?:ELi|ELb[01]ELi)([0-3])ELb[01]E\S*:", line)
+        m = (re.match(r"^_ZN2aq\d+(fwd_(?:narrow_|split_)?kernel)ILi(64|128)E\S*?(?:ELi|ELb[01]ELi)([0-3])ELb[01]E\S*:", line)
+             or re.match(r"^_ZN2aq\d+(fwd_mx_split_kernel)ILi(64|128)E\S*?ELi([0-2])E\S*:", line))
         if m:
             cur, reads, products = line, 0, 0
             seen[cur] = (m.group(1), int(m.group(2)), int(m.group(3)), [])
@@ -184,7 +187,10 @@ def test_no_lds_read_is_in_flight_at_a_barrier_of_the_forward():
         elif cur and line.startswith("s_barrier"):
             seen[cur][3].append((reads, products))
             products = 0
-    assert len([k for k in seen if "narrow" in k]) == 32 and len(seen) > 64
+    if src == "mx.hip":
+        assert len(seen) == 16
+    else:
+        assert len([k for k in seen if "narrow" in k]) == 32 and len([k for k in seen if "split" in k]) == 24 and len(seen) > 88
     for name, (kind, d, pq, barriers) in seen.items():
         assert barriers and all(b[0] == 0 for b in barriers), (name, barriers)
         if kind == "fwd_narrow_kernel":
@@ -221,18 +227,19 @@ def _registers(operand):
 def _reads_without_settling(src, pattern, suspect):
     """For every kernel whose mangled name matches: its vector instructions that read the result of a product although no wait written in
     the source (s_nop in inline assembly) stands in between, out of those that suspect(product, in another block, in inline assembly)
-    picks.  The listing is read from top to bottom; after 20 instructions every product has arrived."""
+    picks, unless another of their operands has been made from the same product by instructions that the compiler counts for.  The
+    listing is read from top to bottom; after 20 instructions every product has arrived."""
     with tempfile.TemporaryDirectory() as tmp:
         out = os.path.join(tmp, "x.s")
         r = subprocess.run(["hipcc", *B.FLAGS, "-S", "--cuda-device-only", os.path.join(B.CSRC, src), "-o", out], capture_output=True, text=True)
         assert r.returncode == 0, r.stderr[-2000:]
         text = open(out).read().splitlines()
-    found, cur, written, at, block, in_asm, settled = {}, None, {}, 0, 0, False, 0
+    found, cur, written, made, at, block, in_asm, settled = {}, None, {}, {}, 0, 0, False, 0
     for line in (l.strip() for l in text):
         m = re.match(r"^(_Z\w+):", line)
         if m:
             cur = m.group(1) if re.search(pattern, m.group(1)) else None
-            written, at, block, settled = {}, 0, 0, 0
+            written, made, at, block, settled = {}, {}, 0, 0, 0
             if cur:
                 found[cur] = []
         elif line.startswith((".LBB", "; %bb")):
@@ -248,23 +255,31 @@ def _reads_without_settling(src, pattern, suspect):
             elif op.startswith("v_mfma"):
                 written.update({reg: (at, block, op) for reg in _registers(operands[0])})
             elif op.startswith("v_"):
-                for reg in (reg for t in operands[1:] for reg in _registers(t) if reg in written):
+                sources = [reg for t in operands[1:] for reg in _registers(t)]
+                beside = set().union(*(made.get(reg, set()) for reg in sources if reg not in written)) if sources else set()
+                for reg in (reg for reg in sources if reg in written):
                     when, where, product = written[reg]
-                    if settled < when and at - when < 20 and suspect(product, block != where, in_asm):
+                    if settled < when and at - when < 20 and when not in beside and suspect(product, block != where, in_asm):
                         found[cur].append((at - when, line))
+                result = beside | {written[reg][0] for reg in sources if reg in written}
                 for reg in _registers(operands[0]):
                     written.pop(reg, None)
+                    made[reg] = result
     return found
 
 
 def test_inline_assembly_of_the_split_forward_reads_settled_products():
     """The compiler counts the wait states between a product and its readers, but does not look into inline assembly (max_raw): in the kernel
-    that has no barrier between the scores and the softmax the wait stands in the source."""
+    that has no barrier between the scores and the softmax, such a read has to wait in the source or depend on a counted one."""
     found = _reads_without_settling("fwd.hip", r"fwd_split_kernel", lambda product, other_block, in_asm: in_asm)
     assert len(found) == 24 and not any(found.values()), {k: v[:3] for k, v in found.items() if v}
 
 
-def test_split_mx_forward_settles_products_that_another_block_reads():
-    """No wait states are relied on that the compiler would have to count across blocks for the scaled product (see mfma_scale_settle)."""
-    found = _reads_without_settling("mx.hip", r"fwd_mx_split_kernel", lambda product, other_block, in_asm: "scale" in product and (other_block or in_asm))
-    assert len(found) == 16 and not any(found.values()), {k: v[:3] for k, v in found.items() if v}
+@pytest.mark.parametrize("pattern,n", [(r"fwd_mx_split_kernelILi(64|128)ELb[01]ELb0E", 12), (r"fwd_mx_split_kernelILi(64|128)ELb[01]ELb1E", 4), (r"mx_decode_pv_kernel", 2)])
+def test_products_that_another_block_reads_have_settled(pattern, n):
+    """The rescaling of O reads the product of the tile in front in a block of its own: the wait states (FP4 operands 11, FP8 19) that
+    the compiler puts there are in the listing.  Inline assembly reads no product that has not settled in the source."""
+    found = _reads_without_settling("mx.hip", pattern, lambda product, other_block, in_asm: "scale" in product and (other_block or in_asm))
+    need = 19 if "ELb1E" in pattern[-6:] else 11
+    assert len(found) == n and all(when > need for reads in found.values() for when, _ in reads), {k: v[:3] for k, v in found.items() if v}
+    assert not any("v_max_f32" in line for reads in found.values() for _, line in reads)
