@@ -65,7 +65,7 @@ __device__ __forceinline__ void fwd_body(
     constexpr bool BOTH = MB >= KS;                 // a wave has its blocks of O and of O' (else: of either, or of nothing)
     constexpr int KLD = D / 8 / NW; // 1 KiB wave-loads per wave for the K tile
     constexpr int VLD = D / 8 / NW; // ... for the V^T tile
-    extern __shared__ __align__(256) unsigned char smem_raw[];   // the XORs of address bits 5..7 commute with adding this base
+    extern __shared__ __align__(256) unsigned char smem_raw[];
     FwdSmem<D>& sm = *reinterpret_cast<FwdSmem<D>*>(smem_raw);
 
     // Work items: a tile of 256 query rows of one head.  Without a mask a workgroup takes one.  Under a causal mask tile qt
@@ -298,7 +298,7 @@ __device__ __forceinline__ void fwd_body(
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
     };
-    // ---- vector phase of one key tile: mask, online softmax, block scales of phi(P-tilde)  (no MFMA, no LDS)
+    // ---- vector phase of one key tile: mask, online softmax, block scales of phi(P-tilde)  (no MFMA; LDS only for SPLIT, the tiles' row maxima)
     auto vector_phase = [&](int j, float (&bsc)[4], float (&binv)[4]) __attribute__((always_inline)) {
         const int k0 = j * 64;
         // mask: keys beyond L, and keys after the query when causal
@@ -863,17 +863,37 @@ static bool narrow_workgroups(int heads, int Lp, int D, bool causal)
     return n4 / (2 * cus) * 102 + (rest == 0 ? 0 : rest <= cus ? 80 : 102) < rounds8 * 100;
 }
 
-// Whether the key tiles are shared (fwd_split_kernel), for heads x n32 groups of 32 rows.  All rows of the same length (no mask, or chunks
-// of sequences that are mostly longer than they): two such workgroups share a compute unit, a round of 2 per unit costs 40 where narrow_workgroups
-// counts 102 for its own, one more per unit 23, against 80 for the 128-row tiles that leave units idle: up to three per unit.  Measured (training,
-// d = 128): 588 groups 61.7 -> 55.7 us, 752 groups 103.6 -> 87.6 us; 800 groups 46.4 -> 46.6 us, 864 groups (inference) 69.6 -> 71.5 us.
-// Causal: the 128-row tiles wait for their longest chain, these only for a quarter of it: six per unit (24 heads, L = 2000, 1512 groups
-// 82.9 -> 72.4 us; L = 2700, 2040 groups 110 -> 114 us), fewer for short rows, where the start of a workgroup is most of it (64 heads,
-// L = 500, 1024 groups, inference 29.1 -> 29.8 us; 160 heads, L = 200, 1120 groups 27.8 -> 30.9 us; 64 heads, L = 256, 512 groups 20.9 -> 18.1 us).
-static bool split_key_tiles(int heads, int n32, bool causal)
+// Whether the key tiles are shared (fwd_split_kernel), for heads x n32 groups of 32 rows: up to a number of groups per compute unit, which was
+// measured over 420 shapes (L = 33 - 9000, 1 - 384 heads, 0.9 - 6 groups per unit), each on both kernels.
+// All rows of the same length (no mask, or chunks of sequences that are mostly longer than they): two such workgroups share a compute unit, a
+// round of 2 per unit costs 40 where narrow_workgroups counts 102 for its own, one more per unit 23, against 80 for the 128-row tiles that leave
+// units idle: up to three per unit (training, d = 128: 588 groups 61.7 -> 55.7 us, 752 groups 103.6 -> 87.6 us; 800 groups 46.4 -> 46.6 us; chunks
+// of a prefill gain 5 - 120 % up to there), two or less for short rows, where the start of a workgroup is most of it (inference, 144 heads,
+// L = 100 21.0 -> 23.6 us; 64 heads, L = 320 25.9 -> 28.0 us).
+// Causal: the 128-row tiles wait for their longest chain, these only for a quarter of it: up to six per unit (training, 24 heads, L = 2000 82.9 ->
+// 72.4 us; inference, 40 heads, L = 777 37.8 -> 33.8 us, 6 heads, L = 6000 1.5 times), fewer for short rows (inference, 64 heads, L = 256 21.4 -> 18.1 us,
+// 96 heads 22.3 -> 23.7 us).
+// A group reads K and V for 32 rows instead of 128.  Where the number of heads does not let every head stay on one XCD (spread: a head's groups lie
+// on two, four or all eight), the L2s see the K and V of many heads, and with many heads the kernel waits for them: fewer groups (inference, causal,
+// 35 heads, L = 1250 53.8 -> 87.8 us, L = 777 36.6 -> 43.7 us; 46 heads, L = 1000 48.8 -> 65.9 us; 44 heads, L = 1000 47.1 -> 49.9 us; but 21 heads, L = 1600 even, 9 heads,
+// L = 4000 1.3 times).  Training does twice the work per byte of K and V and loses later (35 heads, L = 1250 64.0 -> 89.7 us, L = 777 43.8 -> 46.6 us).
+static bool split_key_tiles(int heads, int n32, bool causal, bool varlen, bool train, bool mx)
 {
-    const long long cus = device_cu_count(), n = (long long)heads * n32;
-    return n <= cus * (causal ? min(6, 2 + n32 / 8) : 3);
+    const int spread = heads % 8 == 0 ? 0 : heads % 4 == 0 ? 1 : heads % 2 == 0 ? 2 : 3;
+    int quarters;                                      // of a group per compute unit
+    if (varlen) quarters = n32 < 40 ? 12 : 10;         // (heads stay on their XCD, see varlen_item)
+    else if (!causal) {
+        if (train) quarters = n32 < 4 ? (mx ? 4 : 12) : n32 == 4 || (n32 > 8 && n32 < 12) ? 8 : 12;
+        else quarters = n32 < 4 ? 4 : n32 < 8 ? 8 : n32 < 12 ? (spread ? 4 : 8) : n32 < 16 ? (spread ? 8 : 10) : n32 < 20 ? (spread ? 10 : 12) : n32 < 32 ? (spread ? 8 : 9) : 12;
+    } else {
+        if (train) quarters = mx && n32 < 4 ? 4 : 4 * min(6, 2 + n32 / 8);
+        else quarters = n32 < 4 ? 4 : n32 < 10 ? 8 : n32 < 16 ? 10 : n32 < 32 ? 16 : n32 < 63 ? 20 : 24;
+        if (heads > (spread == 0 ? 65535 : spread == 1 ? 28 : spread == 2 ? 22 : 13)) {
+            if (train) quarters = min(quarters, spread == 1 ? 24 : mx ? 19 : heads <= (spread == 2 ? 30 : 19) ? 16 : 13);
+            else quarters = min(quarters, n32 < 16 ? 8 : n32 < 25 ? 10 : spread == 1 ? (n32 < 32 ? 14 : 18) : spread == 2 && n32 >= 32 && heads <= 30 ? 16 : spread == 2 ? 12 : 13);
+        }
+    }
+    return (long long)heads * n32 * 4 <= (long long)device_cu_count() * quarters;
 }
 // (P-tilde^F, and P-tilde, of four tiles; row maxima, alpha and two parts of l; Q where it has no registers)
 static size_t split_lds_bytes(int D, bool train, int pq) { return (size_t)(train ? 2 : 1) * 4 * 4096 + 4 * 128 * 4 + (train && D == 128 && pq != 1 ? 8192 : 0); }
@@ -899,7 +919,7 @@ static int launch_t(const void* qh, const void* kh, const void* vt, int B, int H
     if constexpr (!DUMP && PQ != 2) {
         static unsigned long long lds_set_split = 0;       // one per instantiation
         const int n32 = (L + 31) / 32;
-        if (split_key_tiles(B * Hq, n32, CAUSAL && !VARLEN)) {
+        if (split_key_tiles(B * Hq, n32, CAUSAL, VARLEN, TRAIN, PQ == 1)) {
             const int groups = VARLEN ? round_up(B * Hkv, 8) : B * Hkv;       // (see varlen_item)
             return go(fwd_split_kernel<D, TRAIN, CAUSAL, PQ, VARLEN>, (unsigned)(groups * (Hq / Hkv) * n32), 256, split_lds_bytes(D, TRAIN, PQ), lds_set_split);
         }

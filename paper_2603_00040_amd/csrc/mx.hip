@@ -1213,12 +1213,19 @@ size_t mx_page_bytes(int D) { return 2 * (size_t)mx_rec_bytes(D, false); }
 // one length: three, as many as share a unit (two in the mixed recipe): d = 128, 8 heads, L = 2000 (504 groups) 34.8 -> 25.3 us, L = 3000 (752)
 // 47.6 -> 41.1 us, 32 heads, L = 777 (800) 22.7 -> 26.5 us; mixed recipe 37.0 -> 27.9 us, 51 -> 59 us; chunks of a prefill, 8 sequences of
 // 2000 - 8000 (512) 101 -> 70 us.  Causal: five, fewer for short rows: 12 heads, L = 2300 (864) 41.7 -> 30.2 us, 8 heads, L = 5000 (1256)
-// 76 -> 56 us, 64 heads, L = 256 (512) 12.8 -> 11.4 us, L = 500 (1024) 18.7 -> 19.2 us, 32 heads, L = 2500 (2528) 54 -> 63 us.  Block-sparse under it
-// (0.3 of the blocks): six: 32 heads, L = 1500 (1504) 30.5 -> 27.0 us, L = 2500 (2528) 42.4 -> 44.9 us.
-static bool mx_split_key_tiles(int heads, int L, bool causal, bool fp8pv, bool sparse)
+// 76 -> 56 us, 64 heads, L = 256 (512) 12.8 -> 11.4 us, L = 500 (1024) 18.7 -> 19.2 us, 32 heads, L = 2500 (2528) 54 -> 63 us; four in the mixed recipe
+// (40 heads, L = 1000 (1280) 29.3 -> 32.3 us; 9 heads, L = 4000 (1125) 1.14 times).  Block-sparse under it (0.3 of the blocks): six: 32 heads,
+// L = 1500 (1504) 30.5 -> 27.0 us, L = 2500 (2528) 42.4 -> 44.9 us.  Contiguous heads whose number does not let them stay on one XCD: fewer for short rows
+// without a mask (60 heads, L = 320 (600) 16.1 -> 17.8 us, 52 heads, L = 256 (416), mixed 14.2 -> 15.5 us) and in the mixed recipe (46 heads, L = 500 (736)
+// causal 21.1 -> 23.5 us).
+static bool mx_split_key_tiles(int heads, int L, bool causal, bool fp8pv, bool sparse, bool paged)
 {
-    const long long cus = device_cu_count(), n32 = (L + 31) / 32, per = causal ? min((long long)(sparse ? 6 : 5), 1 + n32 / 8) : fp8pv ? 2 : 3;
-    return heads * n32 <= per * cus;
+    const int n32 = (L + 31) / 32;
+    const bool spread = heads % 8 != 0 && !sparse && !paged;
+    int quarters = 4 * (causal ? min(sparse ? 6 : 5, 1 + n32 / 8) : fp8pv ? 2 : 3);      // of a group per compute unit
+    if (causal && fp8pv && n32 < 100) quarters = min(quarters, !spread || n32 >= 32 ? 16 : n32 < 20 ? 8 : 12);
+    if (!causal && spread && n32 < 16) quarters = fp8pv ? 5 : 7;
+    return (long long)heads * n32 * 4 <= (long long)device_cu_count() * quarters;
 }
 
 template <int D, bool CAUSAL, bool FP8PV, int KVM>
@@ -1230,7 +1237,7 @@ static int launch_fwd_mx_t(const void* qops, const void* qsc, const void* kv, in
     const size_t smem = 3 * 2 * (size_t)mx_rec_bytes(D, FP8PV);
     const float c = 1.4426950408889634f / sqrtf((float)D);
     if constexpr (KVM != 3) {
-        if (mx_split_key_tiles(B * Hq, L, CAUSAL && KVM != 1, FP8PV, KVM == 2)) {
+        if (mx_split_key_tiles(B * Hq, L, CAUSAL && KVM != 1, FP8PV, KVM == 2, KVM == 1)) {
             hipLaunchKernelGGL((fwd_mx_split_kernel<D, CAUSAL, FP8PV, KVM>), dim3((unsigned)(B * Hq * ((L + 31) / 32))), dim3(256), 0, st,
                                (const unsigned char*)qops, (const uint32_t*)qsc, (const unsigned char*)kv,
                                (uint16_t*)o, lse, L, Lp, Hq, Hq / Hkv, c, page_table, kv_lens, max_pages, num_pages, lq_inner, B);
@@ -1310,7 +1317,7 @@ int launch_fwd_mx_paged(const void* qops, const void* qsc, const void* cache, in
     // both in one the key loop came out 1.5 - 2 % slower, of the same instructions in other registers (16/2 heads, 500 positions over
     // 15k keys: 112.2 -> 114.4 us; 8 sequences of 16/4 heads, 98 positions over 2k - 7k keys: 87.4 -> 88.8 us).
     // (few query rows: the kernel in which four waves share the key tiles takes the plain order, too)
-    const bool by_length = (long long)B * Hq * (round_up(Lq, kRowPad) / 128) > device_cu_count() && !mx_split_key_tiles(B * Hq, Lq, false, false, false);
+    const bool by_length = (long long)B * Hq * (round_up(Lq, kRowPad) / 128) > device_cu_count() && !mx_split_key_tiles(B * Hq, Lq, false, false, false, true);
 #define AQ_PAGED_K(DD, CC, KK) launch_fwd_mx_t<DD, CC, false, KK>(qops, qsc, cache, B, Hq, Hkv, Lq, o, lse, page_table, kv_lens, max_pages, num_pages, lq_inner, st)
 #define AQ_PAGED(DD, CC) (by_length ? AQ_PAGED_K(DD, CC, 3) : AQ_PAGED_K(DD, CC, 1))
     if (D == 128) return causal ? AQ_PAGED(128, true) : AQ_PAGED(128, false);
