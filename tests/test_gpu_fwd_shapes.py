@@ -1,6 +1,6 @@
-"""The two workgroup shapes of the forward (eight waves = 256 query rows, four waves = 128) and the order in which the four-wave
-workgroups take their tiles: the dispatch picks by the size of the whole problem, rows do not depend on each other, so heads and
-sequences computed together and alone have to agree bit for bit (the parity of either with the oracle is tested elsewhere)."""
+"""The workgroup shapes of the forward (eight waves = 256 query rows, four waves = 128, four waves that share 32 rows) and the order in
+which the four-wave workgroups take their tiles: the dispatch picks by the size of the whole problem, rows do not depend on each other,
+so heads and sequences computed together and alone have to agree bit for bit (the parity of either with the oracle is tested elsewhere)."""
 import pytest
 import torch
 
@@ -9,10 +9,11 @@ from tests.gpu_util import random_inputs, to_dev
 pytestmark = pytest.mark.gpu
 
 
-# Without a mask 257 - 512 tiles of 128 rows run on eight waves, few tiles on four; under a causal mask eight waves are taken from
-# 4096 positions on when the pairs of tiles fill whole rounds of the compute units (8 heads x 32 pairs).
-@pytest.mark.parametrize("H,L,d,causal", [(130, 256, 64, False), (130, 129, 128, False), (260, 1, 128, False), (88, 300, 64, False),
-                                          (8, 16384, 128, True), (9, 511, 128, True), (24, 1025, 64, True)])
+# One head alone always shares its key tiles (at most three groups of 32 rows per compute unit).  Together: without a mask 257 - 512 tiles of
+# 128 rows run on eight waves, one row per head and tiles that would leave a small second round on four; under a causal mask eight waves
+# are taken from 4096 positions on when the pairs of tiles fill whole rounds of the compute units (8 heads x 32 pairs), four otherwise.
+@pytest.mark.parametrize("H,L,d,causal", [(130, 256, 64, False), (160, 129, 128, False), (150, 255, 128, False), (88, 300, 64, False), (8, 16384, 128, True),
+                                          (800, 1, 128, False), (200, 257, 128, False), (72, 511, 128, True), (50, 1025, 64, True)])
 def test_heads_together_equal_heads_alone(H, L, d, causal):
     import paper_2603_00040_amd as aq
     x = random_inputs(1, H, H, L, d, seed=H + L, k_chan=2)
@@ -28,10 +29,10 @@ def test_heads_together_equal_heads_alone(H, L, d, causal):
 
 
 @pytest.mark.parametrize("causal", [False, True])
-@pytest.mark.parametrize("B,Hq,Hkv,Lq,d", [(5, 6, 3, 200, 64), (11, 8, 8, 130, 128), (70, 4, 2, 40, 64), (3, 32, 8, 300, 128)])
+@pytest.mark.parametrize("B,Hq,Hkv,Lq,d", [(20, 6, 3, 200, 64), (22, 8, 8, 130, 128), (100, 4, 2, 40, 64), (3, 32, 8, 300, 128)])
 def test_sequences_together_equal_sequences_alone(B, Hq, Hkv, Lq, d, causal):
     """Prefill chunks of sequences of very different lengths over the paged NVFP4 cache (sorted by length on the device up to 64
-    sequences, in their own order beyond)."""
+    sequences, in their own order beyond).  Together on 128 rows per workgroup, alone with shared key tiles."""
     import paper_2603_00040_amd as aq
     g = torch.Generator().manual_seed(B)
     lens = torch.randint(Lq, 1500 if B < 20 else 500, (B,), generator=g)
