@@ -463,7 +463,8 @@ int attnqat_debug_fwd_p_mx(const void* q, const void* k, const void* v,
  * another, with workgroups of 4 waves (128 query rows / 128 keys) or, where that leaves enough of them, 8 waves (256); both
  * compute the same sums over the same tiles in the same order.  All others run both passes in one launch of 4-wave workgroups,
  * in which several workgroups may share the sum over the queries of a key tile (fp32 partial sums, added in a fixed order).
- * waves = 4 or 8 forces separate passes of one shape (8 only where that variant exists), 0 returns to the automatic choice.  Process-wide, for tests that compare the two shapes at small sizes.  ATTNQAT_EINVAL for any
+ * waves = 4 or 8 forces separate passes of one shape (8 only where that variant exists; at d = 64, the ablation with unquantized P aside, they
+ * run only when forced), 0 returns to the automatic choice.  Process-wide, for tests that compare the shapes at small sizes.  ATTNQAT_EINVAL for any
  * other value.
  */
 int attnqat_profile_enable(void* stream, int on);
