@@ -1144,6 +1144,7 @@ BwdPlan bwd_plan(int BHq, int BHkv, int L, int D, bool causal, int cus)
     // d = 64: three four-wave workgroups of the joint launch share a compute unit, where an eight-wave one has it to itself (its registers
     // would have to halve).  Training step, separate passes of eight -> joint: 24 heads, L = 8192 2270 -> 1993 us, MX 16 heads 1476 -> 1304 us;
     // 16 heads, L = 32768 causal 11.80 -> 9.50 ms, MX 11.96 -> 9.80 ms.  (Separate passes of four: 1 % behind the joint launch.)
+    // Where three lose against two, the launch asks for two (joint_in_pairs).
     if (p.joint || D != 64) return p;
     return BwdPlan{true, 1, (L + 31) / 32 * (BHq / BHkv), 0, false};
 }
@@ -1151,10 +1152,13 @@ BwdPlan bwd_plan(int BHq, int BHkv, int L, int D, bool causal, int cus)
 template <int D, bool CAUSAL, int PQ, bool COUNT = false>
 static int launch_joint_t(const DqArgs& Q, DkvArgs K, const BwdPlan& plan, float* part, hipStream_t st)
 {
-    const size_t dq_lds = sizeof(DqSmem<D, PQ == 2>), dkv_lds = sizeof(DkvSmem<D, PQ == 2, 4>), smem = dq_lds > dkv_lds ? dq_lds : dkv_lds;
+    const size_t dq_lds = sizeof(DqSmem<D, PQ == 2>), dkv_lds = sizeof(DkvSmem<D, PQ == 2, 4>), need = dq_lds > dkv_lds ? dq_lds : dkv_lds;
+    constexpr size_t kPairLds = (size_t)64 << 10;   // two fit into the 160 KiB of a compute unit, three do not
+    static_assert(D != 64 || (sizeof(DqSmem<D, PQ == 2>) <= kPairLds && sizeof(DkvSmem<D, PQ == 2, 4>) <= kPairLds), "LDS of the joint kernel");
+    const size_t smem = joint_in_pairs(plan, Q.NHq, K.NHkv, K.L, D, CAUSAL, device_cu_count()) ? kPairLds : need;
     auto kern = bwd_joint_kernel<D, CAUSAL, PQ, COUNT>;
     static unsigned long long lds_set = 0;          // one per instantiation
-    if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)smem, lds_set)) return -1;
+    if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)(D == 64 ? kPairLds : need), lds_set)) return -1;
     K.splits = plan.splits; K.split_iters = plan.iters; K.part = part;
     const int nt = K.Lp / 128, n_dkdv = round_up(K.NHkv * nt * K.splits, 8), n_dq = round_up(Q.NHq * nt, 8);
     hipLaunchKernelGGL(kern, dim3((unsigned)(n_dkdv + n_dq)), dim3(256), smem, st, Q, K, n_dkdv, n_dq, plan.dq_first);

@@ -66,4 +66,19 @@ inline BwdPlan plan_backward(int BHq, int BHkv, int L, int D, bool causal, int c
     return p;
 }
 
+// Whether the joint launch of d = 64 keeps to two workgroups per compute unit, although three fit.  Key tiles that are not cut into pieces
+// are long chains, and a third workgroup beside them slows them down; where they are one to a little over two rounds of the compute
+// units, they end last and the call waits for them.  Backward with two / with three, measured over 90 shapes with 170 - 700 whole key tiles:
+// without a mask, grouped heads, 257 - 384 tiles 2 - 9 % shorter (2 x 32/4 heads, L = 5000, 320 tiles 1442 / 1556 us; 16/4 heads, L = 9637,
+// 304 tiles 1305 / 1432 us; 8 x 16/2 heads, L = 3000, 384 tiles even), 16/8 heads, L = 3300 x 2, 416 tiles 346 / 324 us; heads of their own up to 15 %
+// longer where they are few (2 x 2 heads, L = 10205, 320 tiles).  Causal, up to 2.3 tiles per unit 0 - 9 % shorter (8 heads of 32, L = 8456, 536 tiles
+// 1080 / 1162 us; 552 tiles of 12 heads, L = 5781 214 / 225 us), from 2.5 on even or longer, and so below 2048 positions (4 x 24 heads, L = 668 57 / 55 us).
+inline bool joint_in_pairs(const BwdPlan& p, int BHq, int BHkv, int L, int D, bool causal, int cus)
+{
+    if (D != 64 || !p.joint || p.splits > 1) return false;
+    const long long tiles = (long long)BHkv * ((L + 127) / 128);
+    if (tiles <= cus) return false;
+    return causal ? L >= 2048 && tiles * 10 <= (long long)cus * 23 : BHq > BHkv && tiles * 2 <= (long long)cus * 3;
+}
+
 }  // namespace aq

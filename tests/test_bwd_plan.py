@@ -24,6 +24,9 @@ def planner(tmp_path_factory):
                 'extern "C" void plan(int q, int kv, int L, int d, int causal, int cus, long long* o) {\n'
                 '    const aq::BwdPlan p = aq::plan_backward(q, kv, L, d, causal != 0, cus);\n'
                 '    o[0] = p.joint; o[1] = p.splits; o[2] = p.iters; o[3] = (long long)p.part_bytes; o[4] = p.dq_first;\n'
+                '}\n'
+                'extern "C" int in_pairs(int q, int kv, int L, int d, int causal, int cus) {\n'
+                '    return aq::joint_in_pairs(aq::plan_backward(q, kv, L, d, causal != 0, cus), q, kv, L, d, causal != 0, cus);\n'
                 '}\n')
     subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-I", B.CSRC, src, "-o", lib], check=True)
     L = ctypes.CDLL(lib)
@@ -32,6 +35,7 @@ def planner(tmp_path_factory):
     def plan(*a):
         L.plan(*a, out)
         return tuple(out)
+    plan.in_pairs = lambda *a: bool(L.in_pairs(*a))
     return plan
 
 
@@ -87,3 +91,13 @@ def test_size_query_includes_the_plan():
         part = max(_step_by_step(B_ * Hq, B_ * Hkv, L, d, c, 256)[3] for c in (0, 1))
         Lp = -(-L // 128) * 128
         assert size >= part + 2 * (Hq + Hkv) * B_ * Lp * d * 2
+
+
+def test_whole_key_tiles_of_d64_keep_to_two_workgroups(planner):
+    """Long chains that end last (whole key tiles, a few more than compute units) have no third workgroup beside them; pieces, single heads
+    without a mask, short rows under one, fewer tiles and whole rounds of them do."""
+    for s in ((64, 8, 5518, 64, 0), (64, 8, 5000, 64, 0), (16, 4, 9637, 64, 0), (32, 8, 8456, 64, 1), (12, 12, 5781, 64, 1), (48, 12, 5673, 64, 1)):
+        assert planner(*s, 256)[1] == 1 and planner.in_pairs(*s, 256), s
+    for s in ((64, 16, 4096, 64, 0), (32, 16, 3300, 64, 0), (4, 4, 10205, 64, 0), (48, 48, 8700, 64, 0), (64, 8, 5518, 64, 1), (96, 96, 668, 64, 1), (48, 12, 16255, 64, 1),
+              (2, 2, 256, 64, 0), (64, 8, 5518, 128, 0), (16, 2, 12000, 64, 0)):
+        assert not planner.in_pairs(*s, 256), s

@@ -60,3 +60,22 @@ def test_bits_do_not_depend_on_spare_room(B, Hq, Hkv, L, d, causal):
     want = run(size)
     for spare in (256, 64 << 20):
         assert all(torch.equal(a, b) for a, b in zip(run(size + spare), want))
+
+
+# whole key tiles, a few more than compute units: two workgroups per unit instead of three (257 - 384 tiles; causal from 2048 positions on);
+# and next to both limits
+@pytest.mark.parametrize("mx", [False, True])
+@pytest.mark.parametrize("B,Hq,Hkv,L,causal", [(4, 48, 12, 700, False), (2, 32, 16, 1025, False), (4, 48, 12, 1025, False), (2, 34, 17, 2050, True), (2, 36, 18, 2050, True)])
+def test_whole_key_tiles_equal_separate_passes(B, Hq, Hkv, L, causal, mx):
+    import paper_2603_00040_amd as aq
+    x = random_inputs(B, Hq, Hkv, L, 64, seed=L + Hq)
+    q, k, v, do = (to_dev(x[n]) for n in ("q", "k", "v", "do"))
+    fwd, bwd = (aq.attnqat_fwd_mx, aq.attnqat_bwd_mx) if mx else (aq.attnqat_fwd, aq.attnqat_bwd)
+    _, lse, ohp = fwd(q, k, v, causal)
+    got = bwd(q, k, v, do, lse, ohp, causal)
+    aq.debug_bwd_waves(4)
+    try:
+        want = bwd(q, k, v, do, lse, ohp, causal)
+    finally:
+        aq.debug_bwd_waves(0)
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
