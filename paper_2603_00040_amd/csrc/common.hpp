@@ -129,11 +129,24 @@ __device__ inline float xhalf_max(float x) {
     auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return max_raw(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
+// Two such maxima by one exchange: lanes 0-31 get that of a, lanes 32-63 that of b (the swap of a and b pairs the halves of each).
+__device__ inline float xhalf_max_pair(float a, float b) {
+    auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return max_raw(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
 __device__ inline float xhalf_sum(float x) {
     auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+
+// Whatever a free register holds: the first operand of a conversion that replaces part of a register whose rest is never read, or is
+// replaced by the conversions that follow.  A zero, or a register that is still needed, costs a move.
+__device__ inline uint32_t any_register() {
+    uint32_t r;
+    asm volatile("" : "=v"(r));      // (volatile: two of them are two registers)
+    return r;
+}
 
 // ---- phi^-1(phi(.)) of two P values with the hardware FP4 converts ------------
 // v_cvt_scalef32_pk_fp4_f32 rounds to E2M1 with ties-to-even and saturates at 6 (checked

@@ -299,7 +299,8 @@ __device__ __forceinline__ void fwd_body(
         __builtin_amdgcn_sched_barrier(0);
     };
     // ---- vector phase of one key tile: mask, online softmax, block scales of phi(P-tilde)  (no MFMA; LDS only for SPLIT, the tiles' row maxima)
-    auto vector_phase = [&](int j, float (&bsc)[4], float (&binv)[4]) __attribute__((always_inline)) {
+    // (the scale of group ks in element ks / 2 of bsc[ks % 2])
+    auto vector_phase = [&](int j, half2v (&bsc)[2], float (&binv)[4]) __attribute__((always_inline)) {
         const int k0 = j * 64;
         // mask: keys beyond L, and keys after the query when causal
         const bool need_mask = (k0 + 64 > Lk) || (CAUSAL && k0 + 63 > row0_w + off);
@@ -318,7 +319,7 @@ __device__ __forceinline__ void fwd_body(
         // The maxima are taken on S: one per group of 16 keys (registers 8g..8g+7 of both halves), the tile's row
         // maximum from those four.  exp2 of a group's largest score, by the same instructions on the same inputs as
         // that element's P-tilde, then is the group's largest P-tilde, which the block scale of phi needs below.
-        float mt, gmax[4];
+        float mt, gmax[4], gpair[2];
         if constexpr (PQ == 1 || PQ == 3) {
             float mp[4];
 #pragma unroll
@@ -337,9 +338,16 @@ __device__ __forceinline__ void fwd_body(
                 if constexpr (SPLIT) gmax[ks] = max_raw(max_nc(max_nc(a0, a1), sv[b0 + 6]), sv[b0 + 7]);
                 else gmax[ks] = max_nc(max_nc(a0, a1), max_raw(sv[b0 + 6], sv[b0 + 7]));
             }
+            if constexpr (PQ == 0) {
+                // groups 0 and 2 in lanes 0-31, groups 1 and 3 in lanes 32-63: one exchange for two groups
+                gpair[0] = xhalf_max_pair(gmax[0], gmax[1]);
+                gpair[1] = xhalf_max_pair(gmax[2], gmax[3]);
+                mt = xhalf_max(max_raw(gpair[0], gpair[1]));
+            } else {
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) gmax[ks] = xhalf_max(gmax[ks]);
-            mt = max_nc(max_nc(gmax[0], gmax[1]), max_nc(gmax[2], gmax[3]));
+                for (int ks = 0; ks < 4; ++ks) gmax[ks] = xhalf_max(gmax[ks]);
+                mt = max_nc(max_nc(gmax[0], gmax[1]), max_nc(gmax[2], gmax[3]));
+            }
         }
         if constexpr (SPLIT) {
             // the tile's row maxima to the waves that have the other tiles; the running maximum before this tile from theirs
@@ -355,7 +363,7 @@ __device__ __forceinline__ void fwd_body(
                 if (t < nt) m_next = max_nc(m_next, xm[t]);
             }
         }
-        const float mnew = max_nc(m, mt);
+        const float mnew = max_raw(m, mt);                  // (both come out of vector instructions)
         const float alpha = __builtin_amdgcn_exp2f((m - mnew) * c);
         const float ms = mnew * c;
         m = mnew;
@@ -421,40 +429,49 @@ __device__ __forceinline__ void fwd_body(
 #pragma unroll
                 for (int t = 0; t < 4; ++t) a4[t] = fmaxf(fmaxf(sv[t], sv[4 + t]), fmaxf(sv[8 + t], sv[12 + t]));
                 const uint32_t byte = e8m0_of_amax(xhalf_max(fmaxf(fmaxf(a4[0], a4[1]), fmaxf(a4[2], a4[3]))));
-                bsc[2 * kb] = bsc[2 * kb + 1] = e8m0_as_f32(byte);
+                bsc[0][kb] = bsc[1][kb] = (half_t)e8m0_as_f32(byte);
                 binv[2 * kb] = binv[2 * kb + 1] = e8m0_inverse_as_f32(byte);
             }
             return;
         }
         // block scales of phi(P-tilde) for the four 16-key groups of the tile (keys of a group =
-        // registers 8g..8g+7 of both halves), as four independent chains
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) bsc[ks] = __builtin_amdgcn_exp2f(fmaf(gmax[ks], c, -ms));
-        // (two-level: the block maxima of P-tilde / s1 are at most 2688 (1 + 2^-23), whose sixth rounds to 448, the largest scale)
+        // registers 8g..8g+7 of both halves)
         if constexpr (PQ == 0) {
+            // A lane forms the scales of two groups, its half's (gpair), and hands them to the other half: two instructions of a kind
+            // instead of four, and the exchange of the two scale bytes is one.
+            float bm[2], inv[2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) bm[t] = __builtin_amdgcn_exp2f(fmaf(gpair[t], c, -ms)) * (1.0f / 6.0f);
             // RNE_E4M3(amax / 6) by the hardware conversion (OCP E4M3, round to nearest even, subnormals kept; two values
             // per instruction) and back: the same values as rne_e4m3_grid in a quarter of the instructions.
             // P-tilde <= 1: no saturation
             typedef short short2v __attribute__((ext_vector_type(2)));
-            short2v pk = {0, 0};
-            pk = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(pk, bsc[0] * (1.0f / 6.0f), bsc[1] * (1.0f / 6.0f), 1.0f, false);
-            pk = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(pk, bsc[2] * (1.0f / 6.0f), bsc[3] * (1.0f / 6.0f), 1.0f, true);
-            const uint32_t w = __builtin_bit_cast(uint32_t, pk);
-            bsc[0] = __builtin_amdgcn_cvt_scalef32_f32_fp8(w, 1.0f, 0);
-            bsc[1] = __builtin_amdgcn_cvt_scalef32_f32_fp8(w, 1.0f, 1);
-            bsc[2] = __builtin_amdgcn_cvt_scalef32_f32_fp8(w, 1.0f, 2);
-            bsc[3] = __builtin_amdgcn_cvt_scalef32_f32_fp8(w, 1.0f, 3);
+            const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(__builtin_bit_cast(short2v, any_register()), bm[0], bm[1], 1.0f, false));
+            // reciprocals.  A scale of 0: P^F is 0 whatever the codes are (the dequantization multiplies by the scale), so
+            // any finite factor serves; 512 = 1 / (smallest non-zero scale) keeps the quotients finite.
+            inv[0] = fminf(__builtin_amdgcn_rcpf(__builtin_amdgcn_cvt_scalef32_f32_fp8(w, 1.0f, 0)), 512.0f);
+            inv[1] = fminf(__builtin_amdgcn_rcpf(__builtin_amdgcn_cvt_scalef32_f32_fp8(w, 1.0f, 1)), 512.0f);
+            const auto wb = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+#pragma unroll
+            for (int g = 0; g < 2; ++g)                  // (g: which half formed them)
+                bsc[g] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(wb[g], 1.0f, false);      // (an E4M3 scale is an fp16 number)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const auto ib = __builtin_amdgcn_permlane32_swap(__float_as_uint(inv[t]), __float_as_uint(inv[t]), false, false);
+                binv[2 * t] = __uint_as_float(ib[0]); binv[2 * t + 1] = __uint_as_float(ib[1]);
+            }
         } else {
+            // (two-level: the block maxima of P-tilde / s1 are at most 2688 (1 + 2^-23), whose sixth rounds to 448, the largest scale)
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) bsc[ks] = rne_e4m3_grid((bsc[ks] * inv1) * (1.0f / 6.0f));
+            for (int ks = 0; ks < 4; ++ks) {
+                const float sc = rne_e4m3_grid((__builtin_amdgcn_exp2f(fmaf(gmax[ks], c, -ms)) * inv1) * (1.0f / 6.0f));
+                bsc[ks & 1][ks >> 1] = (half_t)sc;
+                binv[ks] = fminf(__builtin_amdgcn_rcpf(sc), 512.0f) * inv1;
+            }
         }
-        // reciprocals.  A scale of 0: P^F is 0 whatever the codes are (the dequantization multiplies by the scale), so
-        // any finite factor serves; 512 = 1 / (smallest non-zero scale) keeps the quotients finite.
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) binv[ks] = fminf(__builtin_amdgcn_rcpf(bsc[ks]), 512.0f) * inv1;
     };
     // ---- matrix phase of one key tile: O, O' += V^F^T P with the FP4 round trip of P-tilde in between
-    auto matrix_phase = [&](int j, const float (&bsc)[4], const float (&binv)[4]) __attribute__((always_inline)) {
+    auto matrix_phase = [&](int j, const half2v (&bsc)[2], const float (&binv)[4]) __attribute__((always_inline)) {
         const int k0 = j * 64;
         (void)k0;
         // per 16 keys: phi^-1(phi(P-tilde)), then O^T += V^F^T P-tilde^F^T and O'^T += V^F^T P-tilde^T
@@ -487,15 +504,15 @@ __device__ __forceinline__ void fwd_body(
             }
             const float inv = binv[ks];
             if (part == 0) {
-                // (the conversion replaces one byte of its first operand; bytes 2 and 3 of the code registers are never
-                //  read, so any register that is live anyway serves and none has to be cleared)
-                st.c01 = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(__float_as_uint(inv), sv[b0] * inv, sv[b0 + 1] * inv, 1.0f, 0);
-                st.c23 = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(__float_as_uint(inv), sv[b0 + 4] * inv, sv[b0 + 5] * inv, 1.0f, 0);
+                // (the conversion replaces one byte of its first operand; bytes 2 and 3 of the code registers are never read)
+                st.c01 = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(any_register(), sv[b0] * inv, sv[b0 + 1] * inv, 1.0f, 0);
+                st.c23 = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(any_register(), sv[b0 + 4] * inv, sv[b0 + 5] * inv, 1.0f, 0);
             } else if (part == 1) {
                 st.c01 = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(st.c01, sv[b0 + 2] * inv, sv[b0 + 3] * inv, 1.0f, 1);
                 st.c23 = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(st.c23, sv[b0 + 6] * inv, sv[b0 + 7] * inv, 1.0f, 1);
             } else if (part == 2) {
-                const half2v sc2 = __builtin_bit_cast(half2v, pack_f16x2(bsc[ks], bsc[ks]));
+                const half_t sc = bsc[ks & 1][ks >> 1];
+                const half2v sc2 = {sc, sc};
                 uint32_t w[4];
                 w[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(st.c01, 1.0f, 0) * sc2);
                 w[1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(st.c01, 1.0f, 1) * sc2);
@@ -638,7 +655,7 @@ __device__ __forceinline__ void fwd_body(
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 }
-                float bsc[4], binv[4];
+                half2v bsc[2]; float binv[4];
                 vector_phase(j, bsc, binv);
                 matrix_phase(j, bsc, binv);
             } else {
@@ -711,7 +728,7 @@ __device__ __forceinline__ void fwd_body(
     const int j_all = CAUSAL ? min(nkt, (qt * QT + 31 + off) / 64 + 1) : nkt;
     for (int j = 0; j < j_all; ++j) {
         const int k0 = j * 64;
-        float bsc[4], binv[4];
+        half2v bsc[2]; float binv[4];
         if (has_rows) vector_phase(j, bsc, binv);
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_s_setprio(1);    // the MFMA stream is the scarce one: it wins issue conflicts
@@ -731,7 +748,7 @@ __device__ __forceinline__ void fwd_body(
             // either path: written as two branches around a common barrier, the softmax state looks live to
             // the compiler on the skipping path and the kernel spills.
             if (active) {
-                float bsc[4], binv[4];
+                half2v bsc[2]; float binv[4];
                 vector_phase(j, bsc, binv);
                 __builtin_amdgcn_s_barrier();
                 __builtin_amdgcn_s_setprio(1);
@@ -755,7 +772,7 @@ __device__ __forceinline__ void fwd_body(
         auto step = [&](int j, bool active, bool next_active) __attribute__((always_inline)) {
             request_tiles(j);
             if (active) {
-                float bsc[4], binv[4];
+                half2v bsc[2]; float binv[4];
                 vector_phase(j, bsc, binv);
                 __builtin_amdgcn_sched_barrier(0);
                 __builtin_amdgcn_s_setprio(1);
