@@ -148,38 +148,6 @@ __device__ inline uint32_t any_register() {
     return r;
 }
 
-// ---- phi^-1(phi(.)) of two P values with the hardware FP4 converts ------------
-// v_cvt_scalef32_pk_fp4_f32 rounds to E2M1 with ties-to-even and saturates at 6 (checked
-// against the threshold definition on the device, including +-3 ulp around every tie).
-// r0, r1 = p * (1/s);  returns the fp16 pair (s*c0, s*c1), exact in fp16.
-__device__ inline uint32_t fq_pair_f16(float r0, float r1, uint32_t s_f16x2) {
-    const uint32_t codes = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, r0, r1, 1.0f, 0);
-    const half2v c = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(codes, 1.0f, 0);
-    const half2v s = __builtin_bit_cast(half2v, s_f16x2);
-    return __builtin_bit_cast(uint32_t, c * s);
-}
-// Eight values at once: the four converts fill one register of codes byte by byte (one
-// zero-initialisation instead of four).  r[i] = p[i] * (1/s); out[j] = fp16 pair (s*c[2j], s*c[2j+1]).
-__device__ inline void fq_oct_f16(const float (&r)[8], uint32_t s_f16x2, uint32_t (&out)[4]) {
-    uint32_t codes = 0u;
-    codes = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(codes, r[0], r[1], 1.0f, 0);
-    codes = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(codes, r[2], r[3], 1.0f, 1);
-    codes = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(codes, r[4], r[5], 1.0f, 2);
-    codes = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(codes, r[6], r[7], 1.0f, 3);
-    const half2v s = __builtin_bit_cast(half2v, s_f16x2);
-    out[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(codes, 1.0f, 0) * s);
-    out[1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(codes, 1.0f, 1) * s);
-    out[2] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(codes, 1.0f, 2) * s);
-    out[3] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(codes, 1.0f, 3) * s);
-}
-// The same, returning the two dequantized values as fp32 (for bf16 consumers).
-__device__ inline void fq_pair_f32(float r0, float r1, float s, float& o0, float& o1) {
-    typedef float float2v __attribute__((ext_vector_type(2)));
-    const uint32_t codes = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, r0, r1, 1.0f, 0);
-    const float2v c = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(codes, 1.0f, 0);
-    o0 = c[0] * s; o1 = c[1] * s;
-}
-
 // ---- LDS tiles filled by direct global->LDS loads ------------------------------
 // global_load_lds_dwordx4 writes lane i's 16 bytes to (wave-uniform LDS base) + 16*i, so a
 // tile row cannot be padded; bank conflicts are avoided by an XOR swizzle of the 16-byte

@@ -299,8 +299,8 @@ __device__ __forceinline__ void fwd_body(
         __builtin_amdgcn_sched_barrier(0);
     };
     // ---- vector phase of one key tile: mask, online softmax, block scales of phi(P-tilde)  (no MFMA; LDS only for SPLIT, the tiles' row maxima)
-    // (the scale of group ks in element ks / 2 of bsc[ks % 2])
-    auto vector_phase = [&](int j, half2v (&bsc)[2], float (&binv)[4]) __attribute__((always_inline)) {
+    // (psc[ks]: reciprocal of the scale of group ks, with the scale in element ks / 2 of bsc[ks % 2]; MX: the scale, a power of two)
+    auto vector_phase = [&](int j, half2v (&bsc)[2], float (&psc)[4]) __attribute__((always_inline)) {
         const int k0 = j * 64;
         // mask: keys beyond L, and keys after the query when causal
         const bool need_mask = (k0 + 64 > Lk) || (CAUSAL && k0 + 63 > row0_w + off);
@@ -320,7 +320,20 @@ __device__ __forceinline__ void fwd_body(
         // maximum from those four.  exp2 of a group's largest score, by the same instructions on the same inputs as
         // that element's P-tilde, then is the group's largest P-tilde, which the block scale of phi needs below.
         float mt, gmax[4], gpair[2];
-        if constexpr (PQ == 1 || PQ == 3) {
+        if constexpr (PQ == 1) {
+            // MX: the blocks are the tile's two halves of 32 keys; block 0's maximum in lanes 0-31, block 1's in lanes 32-63
+            float bmax[2];
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) {
+                const floatx16& sv = s[kb];
+                const float a0 = max_nc(max_nc(sv[0], sv[1]), sv[2]), a1 = max_nc(max_nc(sv[3], sv[4]), sv[5]);
+                const float a2 = max_nc(max_nc(sv[6], sv[7]), sv[8]), a3 = max_nc(max_nc(sv[9], sv[10]), sv[11]);
+                const float a4 = max_nc(max_nc(sv[12], sv[13]), sv[14]);
+                bmax[kb] = max_nc(max_nc(max_nc(max_nc(a0, a1), a2), max_nc(a3, a4)), sv[15]);
+            }
+            gpair[0] = xhalf_max_pair(bmax[0], bmax[1]);
+            mt = xhalf_max(gpair[0]);
+        } else if constexpr (PQ == 3) {
             float mp[4];
 #pragma unroll
             for (int t = 0; t < 4; ++t) mp[t] = max_nc(s[0][t], s[1][t]);
@@ -420,18 +433,11 @@ __device__ __forceinline__ void fwd_body(
         }
         if constexpr (PQ == 3) return;      // bf16 P-tilde has no block scales
         if constexpr (PQ == 1) {
-            // MX format: one power-of-two scale per 32 keys = all 16 registers of s[kb] in both halves;
-            // the two 16-key groups of a block share it
+            // MX format: one power-of-two scale per 32 keys = all 16 registers of s[kb] in both halves, formed by one of them
+            const uint32_t byte = e8m0_of_amax(__builtin_amdgcn_exp2f(fmaf(gpair[0], c, -ms)));
+            const auto sb = __builtin_amdgcn_permlane32_swap(byte << 23, byte << 23, false, false);
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
-                const floatx16& sv = s[kb];
-                float a4[4];
-#pragma unroll
-                for (int t = 0; t < 4; ++t) a4[t] = fmaxf(fmaxf(sv[t], sv[4 + t]), fmaxf(sv[8 + t], sv[12 + t]));
-                const uint32_t byte = e8m0_of_amax(xhalf_max(fmaxf(fmaxf(a4[0], a4[1]), fmaxf(a4[2], a4[3]))));
-                bsc[0][kb] = bsc[1][kb] = (half_t)e8m0_as_f32(byte);
-                binv[2 * kb] = binv[2 * kb + 1] = e8m0_inverse_as_f32(byte);
-            }
+            for (int kb = 0; kb < 2; ++kb) psc[2 * kb] = psc[2 * kb + 1] = __uint_as_float(sb[kb]);
             return;
         }
         // block scales of phi(P-tilde) for the four 16-key groups of the tile (keys of a group =
@@ -458,7 +464,7 @@ __device__ __forceinline__ void fwd_body(
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
                 const auto ib = __builtin_amdgcn_permlane32_swap(__float_as_uint(inv[t]), __float_as_uint(inv[t]), false, false);
-                binv[2 * t] = __uint_as_float(ib[0]); binv[2 * t + 1] = __uint_as_float(ib[1]);
+                psc[2 * t] = __uint_as_float(ib[0]); psc[2 * t + 1] = __uint_as_float(ib[1]);
             }
         } else {
             // (two-level: the block maxima of P-tilde / s1 are at most 2688 (1 + 2^-23), whose sixth rounds to 448, the largest scale)
@@ -466,12 +472,12 @@ __device__ __forceinline__ void fwd_body(
             for (int ks = 0; ks < 4; ++ks) {
                 const float sc = rne_e4m3_grid((__builtin_amdgcn_exp2f(fmaf(gmax[ks], c, -ms)) * inv1) * (1.0f / 6.0f));
                 bsc[ks & 1][ks >> 1] = (half_t)sc;
-                binv[ks] = fminf(__builtin_amdgcn_rcpf(sc), 512.0f) * inv1;
+                psc[ks] = fminf(__builtin_amdgcn_rcpf(sc), 512.0f) * inv1;
             }
         }
     };
     // ---- matrix phase of one key tile: O, O' += V^F^T P with the FP4 round trip of P-tilde in between
-    auto matrix_phase = [&](int j, const half2v (&bsc)[2], const float (&binv)[4]) __attribute__((always_inline)) {
+    auto matrix_phase = [&](int j, const half2v (&bsc)[2], const float (&psc)[4]) __attribute__((always_inline)) {
         const int k0 = j * 64;
         (void)k0;
         // per 16 keys: phi^-1(phi(P-tilde)), then O^T += V^F^T P-tilde^F^T and O'^T += V^F^T P-tilde^T
@@ -502,22 +508,32 @@ __device__ __forceinline__ void fwd_body(
                 }
                 return;
             }
-            const float inv = binv[ks];
+            // (MX: the conversions themselves divide and multiply by a power of two.  With the blocks' maxima taken on S, about 100 vector instructions
+            //  less per tile; with the backward's share 2 x 16/4 heads, L = 3001 causal, training step 426 -> 404 us)
+            const float inv = MXS ? 1.0f : psc[ks], cs = MXS ? psc[ks] : 1.0f;
+            auto quo = [&](int e) __attribute__((always_inline)) { return MXS ? sv[b0 + e] : sv[b0 + e] * inv; };
             if (part == 0) {
                 // (the conversion replaces one byte of its first operand; bytes 2 and 3 of the code registers are never read)
-                st.c01 = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(any_register(), sv[b0] * inv, sv[b0 + 1] * inv, 1.0f, 0);
-                st.c23 = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(any_register(), sv[b0 + 4] * inv, sv[b0 + 5] * inv, 1.0f, 0);
+                st.c01 = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(any_register(), quo(0), quo(1), cs, 0);
+                st.c23 = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(any_register(), quo(4), quo(5), cs, 0);
             } else if (part == 1) {
-                st.c01 = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(st.c01, sv[b0 + 2] * inv, sv[b0 + 3] * inv, 1.0f, 1);
-                st.c23 = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(st.c23, sv[b0 + 6] * inv, sv[b0 + 7] * inv, 1.0f, 1);
+                st.c01 = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(st.c01, quo(2), quo(3), cs, 1);
+                st.c23 = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(st.c23, quo(6), quo(7), cs, 1);
             } else if (part == 2) {
-                const half_t sc = bsc[ks & 1][ks >> 1];
-                const half2v sc2 = {sc, sc};
+                half2v f[4];
+                f[0] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(st.c01, cs, 0);
+                f[1] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(st.c01, cs, 1);
+                f[2] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(st.c23, cs, 0);
+                f[3] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(st.c23, cs, 1);
                 uint32_t w[4];
-                w[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(st.c01, 1.0f, 0) * sc2);
-                w[1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(st.c01, 1.0f, 1) * sc2);
-                w[2] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(st.c23, 1.0f, 0) * sc2);
-                w[3] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(st.c23, 1.0f, 1) * sc2);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if constexpr (!MXS) {
+                        const half_t sc = bsc[ks & 1][ks >> 1];
+                        f[i] *= half2v{sc, sc};
+                    }
+                    w[i] = __builtin_bit_cast(uint32_t, f[i]);
+                }
                 bq[0] = w[0]; bq[1] = w[1]; bq[2] = w[2]; bq[3] = w[3];
                 if constexpr (DUMP) {
 #pragma unroll
@@ -655,9 +671,9 @@ __device__ __forceinline__ void fwd_body(
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 }
-                half2v bsc[2]; float binv[4];
-                vector_phase(j, bsc, binv);
-                matrix_phase(j, bsc, binv);
+                half2v bsc[2]; float psc[4];
+                vector_phase(j, bsc, psc);
+                matrix_phase(j, bsc, psc);
             } else {
                 lds_barrier();
                 m_next = m;
@@ -728,12 +744,12 @@ __device__ __forceinline__ void fwd_body(
     const int j_all = CAUSAL ? min(nkt, (qt * QT + 31 + off) / 64 + 1) : nkt;
     for (int j = 0; j < j_all; ++j) {
         const int k0 = j * 64;
-        half2v bsc[2]; float binv[4];
-        if (has_rows) vector_phase(j, bsc, binv);
+        half2v bsc[2]; float psc[4];
+        if (has_rows) vector_phase(j, bsc, psc);
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_s_setprio(1);    // the MFMA stream is the scarce one: it wins issue conflicts
         request_tiles(j);
-        if (has_rows) matrix_phase(j, bsc, binv);
+        if (has_rows) matrix_phase(j, bsc, psc);
         // S of the next tile (its P-tilde predecessor in the same registers has been consumed above)
         if (has_rows && j + 1 < nkt && (!CAUSAL || k0 + 64 <= wave_qmax)) scores((j + 1) & 1);
         __builtin_amdgcn_s_setprio(0);
@@ -748,12 +764,12 @@ __device__ __forceinline__ void fwd_body(
             // either path: written as two branches around a common barrier, the softmax state looks live to
             // the compiler on the skipping path and the kernel spills.
             if (active) {
-                half2v bsc[2]; float binv[4];
-                vector_phase(j, bsc, binv);
+                half2v bsc[2]; float psc[4];
+                vector_phase(j, bsc, psc);
                 __builtin_amdgcn_s_barrier();
                 __builtin_amdgcn_s_setprio(1);
                 request_tiles(j);
-                matrix_phase(j, bsc, binv);
+                matrix_phase(j, bsc, psc);
             } else {
                 __builtin_amdgcn_s_barrier();
                 request_tiles(j);
@@ -772,11 +788,11 @@ __device__ __forceinline__ void fwd_body(
         auto step = [&](int j, bool active, bool next_active) __attribute__((always_inline)) {
             request_tiles(j);
             if (active) {
-                half2v bsc[2]; float binv[4];
-                vector_phase(j, bsc, binv);
+                half2v bsc[2]; float psc[4];
+                vector_phase(j, bsc, psc);
                 __builtin_amdgcn_sched_barrier(0);
                 __builtin_amdgcn_s_setprio(1);
-                matrix_phase(j, bsc, binv);
+                matrix_phase(j, bsc, psc);
             }
             if (next_active) scores((j + 1) & 1);
             __builtin_amdgcn_sched_barrier(0);
