@@ -33,6 +33,14 @@ void* static_scratch_of_current_device()
     return p;
 }
 
+bool overlap(const void* a, size_t na, const void* b, size_t nb) { return (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na; }
+// Whether an attention kernel may read Q itself: no workgroup writes a result over rows that another has yet to read.
+bool q_unwritten(const void* q, int B, int Hq, int L, int d, const void* o, const float* lse, const float* o_hp)
+{
+    const size_t rows = (size_t)B * Hq * L, nq = rows * d * 2;
+    return !overlap(q, nq, o, nq) && !overlap(q, nq, lse, rows * 4) && !(o_hp && overlap(q, nq, o_hp, 2 * nq));
+}
+
 constexpr size_t kAlign = 256;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
@@ -223,11 +231,12 @@ int fwd_common(const void* q, const void* k, const void* v, int B, int Hq, int H
     prof_begin(st);
     if (mx) {
         // Q and K as operands of the scaled FP4 instruction (the scores are computed from the codes), V^F^T as the fp16 copy
-        MxGroup g = mx_group_of(q, k, v, B * Hq, B * Hkv, L);
+        const bool direct = q_unwritten(q, B, Hq, L, d, o, lse, train ? o_hp : nullptr);       // the attention kernel quantizes Q
+        MxGroup g = mx_group_of(direct ? nullptr : q, k, v, B * Hq, B * Hkv, L);
         g.qops = (unsigned char*)w.qh; g.qsc = (unsigned char*)w.qsc; g.krec = (unsigned char*)w.kh; g.v_out = (uint16_t*)w.vt;
         if (launch_mx_group(g, MX_TRAIN, d, st)) return ATTNQAT_ELAUNCH;
         prof_mark("prep_qkv", st);
-        if (launch_fwd(w.qh, w.kh, w.vt, B, Hq, Hkv, L, d, causal != 0, train, 1, o, lse, o_hp, dump_row0, p_dump, st, w.qsc))
+        if (launch_fwd(direct ? q : w.qh, w.kh, w.vt, B, Hq, Hkv, L, d, causal != 0, train, 1, o, lse, o_hp, dump_row0, p_dump, st, direct ? nullptr : w.qsc))
             return ATTNQAT_ELAUNCH;
         prof_mark(train ? "fwd_train" : "fwd_infer", st);
         return ATTNQAT_OK;
@@ -358,11 +367,13 @@ static int fwd_infer_mx_common(const void* q, const void* k, const void* v,
     hipStream_t st = (hipStream_t)stream;
     prof_begin(st);
     // Alg. 1 first line, in the MX format: phi(Q), phi(K) along d, phi(V) along the keys (E4M3 elements in the mixed recipe)
-    MxGroup g = mx_group_of(q, k, v, B * Hq, B * Hkv, L);
+    // (phi(Q) in the attention kernel)
+    const bool direct = q_unwritten(q, B, Hq, L, d, o, lse, nullptr);
+    MxGroup g = mx_group_of(direct ? nullptr : q, k, v, B * Hq, B * Hkv, L);
     g.qops = w.qops; g.qsc = w.qsc; g.kv = w.kv;
     if (launch_mx_group(g, fp8pv ? MX_INFER_FP8V : MX_INFER, d, st)) return ATTNQAT_ELAUNCH;
     prof_mark("prep_qkv_mx", st);
-    if (launch_fwd_mx(w.qops, w.qsc, w.kv, B, Hq, Hkv, L, d, causal != 0, fp8pv, o, lse, st)) return ATTNQAT_ELAUNCH;
+    if (launch_fwd_mx(direct ? q : w.qops, direct ? nullptr : w.qsc, w.kv, B, Hq, Hkv, L, d, causal != 0, fp8pv, o, lse, st)) return ATTNQAT_ELAUNCH;
     prof_mark(fp8pv ? "fwd_infer_mx_fp8pv" : "fwd_infer_mx", st);
     return ATTNQAT_OK;
 }
@@ -398,12 +409,13 @@ int attnqat_fwd_infer_mx_sparse(const void* q, const void* k, const void* v,
     if (!workspace || workspace_bytes < c.off) return ATTNQAT_EWORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     prof_begin(st);
-    MxGroup g = mx_group_of(q, k, v, B * Hq, B * Hkv, L);
+    const bool direct = q_unwritten(q, B, Hq, L, d, o, lse, nullptr);
+    MxGroup g = mx_group_of(direct ? nullptr : q, k, v, B * Hq, B * Hkv, L);
     g.qops = w.qops; g.qsc = w.qsc; g.kv = w.kv;
     g.mask = (const unsigned char*)block_mask; g.list = list; g.list_count = cnt;
     if (launch_mx_group(g, MX_INFER, d, st)) return ATTNQAT_ELAUNCH;
     prof_mark("prep_qkv_mx", st);
-    if (launch_fwd_mx_sparse(w.qops, w.qsc, w.kv, B, Hq, Hkv, L, d, causal != 0, list, cnt, o, lse, st)) return ATTNQAT_ELAUNCH;
+    if (launch_fwd_mx_sparse(direct ? q : w.qops, direct ? nullptr : w.qsc, w.kv, B, Hq, Hkv, L, d, causal != 0, list, cnt, o, lse, st)) return ATTNQAT_ELAUNCH;
     prof_mark("fwd_infer_mx_sparse", st);
     return ATTNQAT_OK;
 }
@@ -447,11 +459,14 @@ int attnqat_fwd_infer_mx_paged(const void* q, int B, int Hq, int Hkv, int Lq, in
     if (workspace_bytes < c.off) part = nullptr;
     hipStream_t st = (hipStream_t)stream;
     prof_begin(st);
-    MxGroup g = mx_group_of(q, nullptr, nullptr, B * Hq_k, 0, Lq_k);
-    g.qops = qops; g.qsc = qsc;
-    if (launch_mx_group(g, MX_INFER, d, st)) return ATTNQAT_ELAUNCH;
+    const bool direct = q_unwritten(q, B, Hq, Lq, d, o, lse, nullptr);
+    if (!direct) {
+        MxGroup g = mx_group_of(q, nullptr, nullptr, B * Hq_k, 0, Lq_k);
+        g.qops = qops; g.qsc = qsc;
+        if (launch_mx_group(g, MX_INFER, d, st)) return ATTNQAT_ELAUNCH;
+    }
     prof_mark("prep_q_mx", st);
-    if (launch_fwd_mx_paged(qops, qsc, cache, B, Hq_k, Hkv, Lq_k, d, causal != 0, page_table, kv_lens, max_pages, num_pages, Lq, part, o, lse, st))
+    if (launch_fwd_mx_paged(direct ? q : qops, direct ? nullptr : qsc, cache, B, Hq_k, Hkv, Lq_k, d, causal != 0, page_table, kv_lens, max_pages, num_pages, Lq, part, o, lse, st))
         return ATTNQAT_ELAUNCH;
     prof_mark("fwd_infer_mx_paged", st);
     return ATTNQAT_OK;
@@ -742,7 +757,6 @@ int attnqat_debug_fwd_p_mx(const void* q, const void* k, const void* v,
                       workspace, workspace_bytes, stream);
 }
 
-static bool overlap(const void* a, size_t na, const void* b, size_t nb) { return (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na; }
 
 // The six arrays of an already quantized Q, K, V (attnqat_quantize's layout); null = quantize q, k, v here.
 struct PackedQKV { const uint8_t *qc, *qs, *kc, *ks, *vc, *vs; };

@@ -24,6 +24,7 @@
 
 #include "common.hpp"
 #include "kernels.hpp"
+#include "mx_quant.hpp"
 
 namespace aq {
 
@@ -53,7 +54,7 @@ __device__ __forceinline__ void fwd_body(
     // PQ == 1 (MX): S = Q^F K^F^T comes from the E2M1 codes and E8M0 scales by v_mfma_scale_f32_32x32x64_f8f6f4 (a quarter of
     // the matrix time of the 16-bit products, a quarter of the K bytes through LDS).  Qh then holds the Q operands of that
     // instruction (64 d per step: lane (row, half) has d-slots 64 ks + 32 half .. + 31 of its row) with one dword of scale
-    // bytes per lane in Qsc, and Kh the K records of mx_ktrain_rec_bytes(D) bytes per key tile.  The accumulator layout is
+    // bytes per lane in Qsc, or Q itself in bf16 (Qsc null, MxQ), and Kh the K records of mx_ktrain_rec_bytes(D) bytes per key tile.  The accumulator layout is
     // that of the 16-bit products, so everything after the scores is unchanged (O and O' stay 16-bit products: O' needs the
     // un-quantized P-tilde, which is no operand of that instruction).
     constexpr bool MXS = PQ == 1;
@@ -139,15 +140,12 @@ __device__ __forceinline__ void fwd_body(
     // Q^F operand: this lane's query row, d-slots 16*ds + 8*hf .. +7
     // (Q_LDS, the split training kernel at d = 128: it has no registers for them)
     constexpr bool Q_LDS = SPLIT && TRAIN && D == 128 && !MXS;
+    const size_t grp = (size_t)bh * (Lp / 32) + ((has_rows ? row0_w : 0) >> 5);      // (MXS) group of 32 rows
+    const int q_tid = SPLIT ? (int)threadIdx.x : lane;
     half8 qreg[MXS || Q_LDS ? 1 : DS];
-    uint4v qop[MXS ? KSM : 1];
-    uint32_t qs = 0u;
+    MxQ<D, SPLIT ? 64 * NW : 64> Q;      // (SPLIT: the four waves share the rows)
     if constexpr (MXS) {
-        const size_t grp = (size_t)bh * (Lp / 32) + ((has_rows ? row0_w : 0) >> 5);
-        const unsigned char* qo = reinterpret_cast<const unsigned char*>(Qh);
-#pragma unroll
-        for (int ks = 0; ks < KSM; ++ks) qop[ks] = *reinterpret_cast<const uint4v*>(qo + ((grp * KSM + ks) * 64 + lane) * 16);
-        qs = Qsc[grp * 64 + lane];
+        Q.fetch(Qh, Qsc, bh, has_rows ? row0_w : 0, grp, q_tid, L);
     } else if constexpr (!Q_LDS) {
         const half_t* qp = Qh + ((size_t)bh * Lp + (has_rows ? q_row : 0)) * D + 8 * hf;
 #pragma unroll
@@ -186,11 +184,11 @@ __device__ __forceinline__ void fwd_body(
             };
             const floatx16 zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
             // (format codes 4, 4: both operands E2M1; the scale operands are a dword of four bytes and the index of the byte)
-            s[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[0][0]), as8(qop[0]), zero, 4, 4, 0, ksc, 0, qs);
-            s[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[1][0]), as8(qop[0]), zero, 4, 4, KSM, ksc, 0, qs);
+            s[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[0][0]), as8(Q.op[0]), zero, 4, 4, 0, ksc, 0, Q.sc);
+            s[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[1][0]), as8(Q.op[0]), zero, 4, 4, KSM, ksc, 0, Q.sc);
             if constexpr (KSM == 2) {
-                s[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[0][1]), as8(qop[1]), s[0], 4, 4, 1, ksc, 1, qs);
-                s[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[1][1]), as8(qop[1]), s[1], 4, 4, 3, ksc, 1, qs);
+                s[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[0][1]), as8(Q.op[1]), s[0], 4, 4, 1, ksc, 1, Q.sc);
+                s[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[1][1]), as8(Q.op[1]), s[1], 4, 4, 3, ksc, 1, Q.sc);
             }
             mfma_scale_settle(s[0], s[1]);
             return;
@@ -254,9 +252,14 @@ __device__ __forceinline__ void fwd_body(
     // The Q registers must have arrived BEFORE the loop: a load still pending at loop entry makes the
     // compiler wait for all vector-memory traffic at the first product of every iteration.
     if constexpr (MXS) {
-#pragma unroll
-        for (int ks = 0; ks < KSM; ++ks) asm volatile("" : "+v"(qop[ks]));
-        asm volatile("" : "+v"(qs));
+        if constexpr (!SPLIT) {
+            // (phi(Q) through the second V^T buffer and what the K record leaves of the first K buffer: neither has been asked for yet)
+            static_assert(NW * kMxQOps<D> <= sizeof(sm.v[1]) && KREC + NW * 256 <= (int)sizeof(sm.k[0]));
+            const uint32_t ops = lds_addr_of(vbase) + (uint32_t)sizeof(sm.v[0]) + (uint32_t)(wave * kMxQOps<D>), scs = lds_addr_of(kbase) + (uint32_t)(KREC + wave * 256);
+            Q.quantize(Qsc, ops, scs, q_tid);
+            mx_q_wave_fence();
+            Q.read(Qh, Qsc, grp, lane, ops, scs);
+        }
     } else if constexpr (Q_LDS) {
 #pragma unroll
         for (int i = 0; i < DS / NW; ++i) {
@@ -642,11 +645,11 @@ __device__ __forceinline__ void fwd_body(
                         return r;
                     };
                     const floatx16 zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-                    s[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr_mx[0]), as8(qop[0]), zero, 4, 4, 0, ksc_mx, 0, qs);
-                    s[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr_mx[KSM]), as8(qop[0]), zero, 4, 4, KSM, ksc_mx, 0, qs);
+                    s[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr_mx[0]), as8(Q.op[0]), zero, 4, 4, 0, ksc_mx, 0, Q.sc);
+                    s[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr_mx[KSM]), as8(Q.op[0]), zero, 4, 4, KSM, ksc_mx, 0, Q.sc);
                     if constexpr (KSM == 2) {
-                        s[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr_mx[1]), as8(qop[1]), s[0], 4, 4, 1, ksc_mx, 1, qs);
-                        s[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr_mx[3]), as8(qop[1]), s[1], 4, 4, 3, ksc_mx, 1, qs);
+                        s[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr_mx[1]), as8(Q.op[1]), s[0], 4, 4, 1, ksc_mx, 1, Q.sc);
+                        s[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr_mx[3]), as8(Q.op[1]), s[1], 4, 4, 3, ksc_mx, 1, Q.sc);
                     }
                     mfma_scale_settle(s[0], s[1]);
                     if constexpr (MORE) load_k(k_next);
@@ -736,6 +739,12 @@ __device__ __forceinline__ void fwd_body(
                 for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
                     for (int ob = 0; ob < OB; ++ob) vr[t][ks][ob] = v_opnd(0, t, ks, ob);
+        }
+        if constexpr (MXS) {
+            // (phi(Q) through the room of P, which is first written behind the barrier of the maxima)
+            Q.quantize(Qsc, p_lds, p_lds + kMxQOps<D>, q_tid);
+            lds_barrier();
+            Q.read(Qh, Qsc, grp, lane, p_lds, p_lds + kMxQOps<D>);
         }
         int j0 = 0;
         for (; j0 + KS < nkt; j0 += KS) four_tiles(std::true_type{}, j0);
@@ -936,7 +945,6 @@ static int launch_t(const void* qh, const void* kh, const void* vt, int B, int H
                     void* o, float* lse, float* o_hp, int dump_row0, float* p_dump, hipStream_t st,
                     int Lkp = 0, const int* kv_lens = nullptr, const void* qsc = nullptr)
 {
-    if (PQ == 1 && !qsc) return -1;
     const int Lp = round_up(L, kRowPad);
     const int nqt = (Lp + 255) / 256;
     const int per_head = CAUSAL ? (nqt + 1) / 2 : nqt;         // under a causal mask a workgroup takes a long and a short tile

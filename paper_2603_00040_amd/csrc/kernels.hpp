@@ -50,7 +50,7 @@ int launch_colmean(const void* x, int BH, int L, int D, double* scratch, float* 
 
 // Alg. 1 (train=false) / Alg. 2 (train=true) on copies made by launch_prep_group.
 // p_quant 1 (MX): qh and kh are NOT fp16 copies but the operand arrays of the scaled FP4 instruction (launch_mx_group,
-// MX_TRAIN: qops with its scale dwords in qsc, and krec): the scores are computed from the codes; vt stays the fp16 copy.
+// MX_TRAIN: qops with its scale dwords in qsc, or Q itself with qsc null; and krec): the scores are computed from the codes; vt stays the fp16 copy.
 // p_quant: phi(P-tilde) 0 NVFP4; 1 in the MX format (blocks of 32 keys, power-of-two scale); 2 NVFP4 after the
 // two-level row factor (every 64-key tile row divided by a power of two that brings its maximum just below 448 * 6).
 int launch_fwd(const void* qh, const void* kh, const void* vt,
@@ -144,7 +144,7 @@ size_t mx_kv_bytes(int BHkv, int L, int D, bool fp8v);
 size_t mx_ktrain_bytes(int BHkv, int L, int D);      // K records of the MX training forward (krec)
 size_t mx_qops_bytes(int BHq, int L, int D);
 size_t mx_qsc_bytes(int BHq, int L);
-// Alg. 1 on the arrays made by launch_mx_group.  fp8pv: P-tilde and V in MXFP8 (mixed recipe).
+// Alg. 1 on the arrays made by launch_mx_group, here and below with Q itself in the place of qops where qsc is null.  fp8pv: P-tilde and V in MXFP8 (mixed recipe).
 int launch_fwd_mx(const void* qops, const void* qsc, const void* kv, int B, int Hq, int Hkv, int L, int D, bool causal, bool fp8pv,
                   void* o, float* lse, hipStream_t st);
 

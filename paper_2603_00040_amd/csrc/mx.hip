@@ -139,7 +139,7 @@ __global__ __launch_bounds__(D) void mx_quant_l_kernel(
 // kv_lens the number of entries per row of that list); a row that ends up without any key gets O = 0 and L = -inf.
 template <int D, bool CAUSAL, bool FP8PV, int KVM /* 0 contiguous, 1 paged KV cache, 2 block-sparse, 3 paged, by sequence length */>
 __global__ __launch_bounds__(256, 2) void fwd_mx_kernel(
-    const unsigned char* __restrict__ qops, const uint32_t* __restrict__ qsc, const unsigned char* __restrict__ kv,
+    const void* __restrict__ qops, const uint32_t* __restrict__ qsc, const unsigned char* __restrict__ kv,
     uint16_t* __restrict__ O, float* __restrict__ lse, int L, int Lp, int Hq, int G, float c /* log2(e)/sqrt(d) */,
     const int* __restrict__ page_table, const int* __restrict__ kv_lens, int max_pages, int num_pages, int lq_inner, int B)
 {
@@ -170,11 +170,9 @@ __global__ __launch_bounds__(256, 2) void fwd_mx_kernel(
     const int wave_qmax = row0_w + 31;
 
     // Q operands of this lane: codes of its row for d-slots 64 ks + 32 hf .. + 31, scale bytes by ks
-    uint4v qop[KS];
+    MxQ<D, 64> Q;
     const size_t grp = (size_t)bh * (Lp / 32) + (row0_w >> 5);
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qop[ks] = *reinterpret_cast<const uint4v*>(qops + ((grp * KS + ks) * 64 + lane) * 16);
-    uint32_t qs = qsc[grp * 64 + lane];
+    Q.fetch(qops, qsc, bh, row0_w, grp, lane, L);
 
     const int Lk = PAGED ? __builtin_amdgcn_readfirstlane(kv_lens[b]) : L;      // keys of this sequence
     const int koff = PAGED ? Lk - lq_inner : 0;                    // key index of position 0's diagonal
@@ -227,11 +225,11 @@ __global__ __launch_bounds__(256, 2) void fwd_mx_kernel(
             for (int ks = 0; ks < KS; ++ks) a[t][ks] = lds_read16(rec + ((t * KS + ks) * 64 + lane) * 16);
         // (a constant zero accumulator is encoded in the instruction: no registers to clear)
         const floatx16 zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-        s[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[0][0]), as8(qop[0]), zero, 4, 4, 0, ksc, 0, qs);
-        s[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[1][0]), as8(qop[0]), zero, 4, 4, KS, ksc, 0, qs);
+        s[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[0][0]), as8(Q.op[0]), zero, 4, 4, 0, ksc, 0, Q.sc);
+        s[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[1][0]), as8(Q.op[0]), zero, 4, 4, KS, ksc, 0, Q.sc);
         if constexpr (KS == 2) {
-            s[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[0][1]), as8(qop[1]), s[0], 4, 4, 1, ksc, 1, qs);
-            s[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[1][1]), as8(qop[1]), s[1], 4, 4, 3, ksc, 1, qs);
+            s[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[0][1]), as8(Q.op[1]), s[0], 4, 4, 1, ksc, 1, Q.sc);
+            s[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[1][1]), as8(Q.op[1]), s[1], 4, 4, 3, ksc, 1, Q.sc);
         }
     };
     // online softmax of one tile (Alg. 1 inner loop), phi of this lane's P-tilde block, O += V^F^T P-tilde^F
@@ -336,9 +334,12 @@ __global__ __launch_bounds__(256, 2) void fwd_mx_kernel(
 
     issue_stage(0);
     if (nst > 1) issue_stage(1);
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qop[ks]));
-    asm volatile("" : "+v"(qs));
+    // (phi(Q) through the third stage buffer, which is not asked for yet)
+    const uint32_t q_ops = lds_addr_of(smem) + (uint32_t)(2 * STAGE + wave * (kMxQOps<D> + 256));
+    static_assert(4 * (kMxQOps<D> + 256) <= STAGE);
+    Q.quantize(qsc, q_ops, q_ops + kMxQOps<D>, lane);
+    mx_q_wave_fence();
+    Q.read(qops, qsc, grp, lane, q_ops, q_ops + kMxQOps<D>);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     floatx16 sa[2], sb[2];
@@ -373,7 +374,7 @@ __global__ __launch_bounds__(256, 2) void fwd_mx_kernel(
 // registers.  All sums keep their order: the bits of fwd_mx_kernel.  KVM: 0 contiguous, 1 paged, 2 block-sparse, as there.
 template <int D, bool CAUSAL, bool FP8PV, int KVM>
 __global__ __launch_bounds__(256, 2) void fwd_mx_split_kernel(
-    const unsigned char* __restrict__ qops, const uint32_t* __restrict__ qsc, const unsigned char* __restrict__ kv,
+    const void* __restrict__ qops, const uint32_t* __restrict__ qsc, const unsigned char* __restrict__ kv,
     uint16_t* __restrict__ O, float* __restrict__ lse, int L, int Lp, int Hq, int G, float c /* log2(e)/sqrt(d) */,
     const int* __restrict__ page_table, const int* __restrict__ kv_lens, int max_pages, int num_pages, int lq_inner, int B)
 {
@@ -392,11 +393,9 @@ __global__ __launch_bounds__(256, 2) void fwd_mx_split_kernel(
     const int lane = threadIdx.x & 63, ln = lane & 31, hf = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int row0 = qt * 32, q_row = row0 + ln;
-    uint4v qop[KS];
+    MxQ<D, 256> Q;
     const size_t grp = (size_t)bh * (Lp / 32) + qt;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qop[ks] = *reinterpret_cast<const uint4v*>(qops + ((grp * KS + ks) * 64 + lane) * 16);
-    const uint32_t qs = qsc[grp * 64 + lane];
+    Q.fetch(qops, qsc, bh, row0, grp, (int)threadIdx.x, L);
 
     const int Lk = PAGED ? __builtin_amdgcn_readfirstlane(kv_lens[b]) : L;
     const int koff = PAGED ? Lk - lq_inner : 0;
@@ -460,17 +459,22 @@ __global__ __launch_bounds__(256, 2) void fwd_mx_split_kernel(
 #pragma unroll
         for (int t = 0; t < NT; ++t) load_v(t, rec_of(t));
     }
+    // (phi(Q) through the room of P, which is first written behind the barrier in the loop)
+    static_assert(kMxQOps<D> <= sizeof(p_codes) && 256 <= sizeof(p_byte));
+    Q.quantize(qsc, lds_addr_of(&p_codes[0][0][0]), lds_addr_of(&p_byte[0][0]), (int)threadIdx.x);
+    lds_barrier();
+    Q.read(qops, qsc, grp, lane, lds_addr_of(&p_codes[0][0][0]), lds_addr_of(&p_byte[0][0]));
     for (int j0 = 0; j0 < nkt; j0 += NT) {
         const int j = j0 + wave, nt = min(nkt - j0, NT);
         const bool active = wave < nt;
         floatx16 s[2];
         if (active) {
             const floatx16 zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-            s[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr[0]), as8(qop[0]), zero, 4, 4, 0, ksc, 0, qs);
-            s[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr[KS]), as8(qop[0]), zero, 4, 4, KS, ksc, 0, qs);
+            s[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr[0]), as8(Q.op[0]), zero, 4, 4, 0, ksc, 0, Q.sc);
+            s[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr[KS]), as8(Q.op[0]), zero, 4, 4, KS, ksc, 0, Q.sc);
             if constexpr (KS == 2) {
-                s[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr[1]), as8(qop[1]), s[0], 4, 4, 1, ksc, 1, qs);
-                s[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr[3]), as8(qop[1]), s[1], 4, 4, 3, ksc, 1, qs);
+                s[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr[1]), as8(Q.op[1]), s[0], 4, 4, 1, ksc, 1, Q.sc);
+                s[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr[3]), as8(Q.op[1]), s[1], 4, 4, 3, ksc, 1, Q.sc);
             }
             mfma_scale_settle(s[0], s[1]);
         }
@@ -603,7 +607,7 @@ __global__ __launch_bounds__(256, 2) void fwd_mx_split_kernel(
 constexpr int kMxDecRows = 32;                       // most rows of a head
 template <int D, bool CAUSAL, int NP /* pages per iteration: 4 NP waves */>
 __global__ __launch_bounds__(256 * NP, NP == 1 ? 2 : 1) void fwd_mx_decode_kernel(
-    const unsigned char* __restrict__ qops, const uint32_t* __restrict__ qsc, const unsigned char* __restrict__ kv,
+    const void* __restrict__ qops, const uint32_t* __restrict__ qsc, const unsigned char* __restrict__ kv,
     uint16_t* __restrict__ O, float* __restrict__ lse, int L /* rows, <= 32 */, int Hq, int G, float c /* log2(e)/sqrt(d) */,
     const int* __restrict__ page_table, const int* __restrict__ kv_lens, int max_pages, int num_pages, int lq_inner)
 {
@@ -625,11 +629,8 @@ __global__ __launch_bounds__(256 * NP, NP == 1 ? 2 : 1) void fwd_mx_decode_kerne
     const int Hkv = Hq / G;
 
     // Q operands of row block 0 (rows 0..31 of this head's only tile; rows >= L are zero)
-    uint4v qop[KS];
-    const size_t grp = (size_t)bh * 4;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qop[ks] = *reinterpret_cast<const uint4v*>(qops + ((grp * KS + ks) * 64 + lane) * 16);
-    uint32_t qs = qsc[grp * 64 + lane];
+    MxQ<D, 64 * NW> Q;
+    Q.fetch(qops, qsc, bh, 0, (size_t)bh * 4, tid, L);
 
     const int Lk = __builtin_amdgcn_readfirstlane(kv_lens[b]);
     const int koff = Lk - lq_inner;
@@ -681,13 +682,18 @@ __global__ __launch_bounds__(256 * NP, NP == 1 ? 2 : 1) void fwd_mx_decode_kerne
     float lsum = 0.0f;
 
     // Q must have arrived before the copies start: the wait for an ordinary load issued after them would wait for them too
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qop[ks]));
-    asm volatile("" : "+v"(qs));
+    Q.arrived();
     __builtin_amdgcn_s_waitcnt(0);
 #pragma unroll
     for (int i = 0; i < NIT - 1; ++i)
         if (i < nit) issue_iter(i);
+    // (phi(Q) through the buffers of iteration NIT - 1, which is asked for behind the first barrier of the loop)
+    const uint32_t q_ops = lds_addr_of(smem) + (uint32_t)((NIT - 1) * NP * STAGE);
+    Q.quantize(qsc, q_ops, q_ops + kMxQOps<D>, tid);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    Q.read(qops, qsc, (size_t)bh * 4, lane, q_ops, q_ops + kMxQOps<D>);
 
     for (int it = 0; it < nit; ++it) {
         // iteration it's pages are in LDS (the newer ones may be in flight if they are whole), everyone is past iteration it - 1
@@ -711,11 +717,11 @@ __global__ __launch_bounds__(256 * NP, NP == 1 ? 2 : 1) void fwd_mx_decode_kerne
 #pragma unroll
             for (int i = 0; i < 16; ++i) sv[i] = 0.0f;
             if (t == 0) {
-                sv = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[0]), as8(qop[0]), sv, 4, 4, 0, ksc, 0, qs);
-                if constexpr (KS == 2) sv = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[1]), as8(qop[1]), sv, 4, 4, 1, ksc, 1, qs);
+                sv = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[0]), as8(Q.op[0]), sv, 4, 4, 0, ksc, 0, Q.sc);
+                if constexpr (KS == 2) sv = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[1]), as8(Q.op[1]), sv, 4, 4, 1, ksc, 1, Q.sc);
             } else {
-                sv = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[0]), as8(qop[0]), sv, 4, 4, KS, ksc, 0, qs);
-                if constexpr (KS == 2) sv = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[1]), as8(qop[1]), sv, 4, 4, 3, ksc, 1, qs);
+                sv = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[0]), as8(Q.op[0]), sv, 4, 4, KS, ksc, 0, Q.sc);
+                if constexpr (KS == 2) sv = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[1]), as8(Q.op[1]), sv, 4, 4, 3, ksc, 1, Q.sc);
             }
             const bool need_mask = (k0 + 64 > Lk) || (CAUSAL && k0 + 63 > koff);
             if (need_mask) {
@@ -863,7 +869,7 @@ __device__ inline unsigned char* mx_dec_rec(const MxDecSplit& sp, int L, int bh,
 // to registers, a page ahead; waves as in fwd_mx_decode_kernel: wave w has product w % 2 of tile w / 2 of each page.
 template <int D, bool CAUSAL>
 __global__ __launch_bounds__(256) void mx_decode_max_kernel(
-    const unsigned char* __restrict__ qops, const uint32_t* __restrict__ qsc, const unsigned char* __restrict__ kv, int L, int Hq, int G,
+    const void* __restrict__ qops, const uint32_t* __restrict__ qsc, const unsigned char* __restrict__ kv, int L, int Hq, int G,
     const int* __restrict__ page_table, const int* __restrict__ kv_lens, int max_pages, int num_pages, int lq_inner, int per, int n, float* __restrict__ cmax)
 {
     constexpr int KS = D / 64, MT = D / 32, KOPS = 2 * KS * 1024, VOPS = MT * 1024, REC = mx_rec_bytes(D, false), STAGE = 2 * REC;
@@ -876,10 +882,8 @@ __global__ __launch_bounds__(256) void mx_decode_max_kernel(
     if (p0 + per >= nst) return;                                              // the last chunk, or none
     const int koff = Lk - lq_inner;
     const int klim = CAUSAL ? min(Lk - 1, koff + (lq_inner != L ? ln % lq_inner : ln)) : Lk - 1;
-    uint4v qop[KS];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qop[ks] = *reinterpret_cast<const uint4v*>(qops + (((size_t)bh * 4 * KS + ks) * 64 + lane) * 16);
-    const uint32_t qs = qsc[(size_t)bh * 4 * 64 + lane];
+    MxQ<D, 256> Q;
+    Q.fetch(qops, qsc, bh, 0, (size_t)bh * 4, (int)threadIdx.x, L);
     auto as8 = [](const uint4v& x) __attribute__((always_inline)) -> int8v {
         int8v r = {(int)x[0], (int)x[1], (int)x[2], (int)x[3], 0, 0, 0, 0};
         return r;
@@ -895,12 +899,16 @@ __global__ __launch_bounds__(256) void mx_decode_max_kernel(
     };
     float mx = -INFINITY;
     load(p0);
+    __shared__ __align__(16) unsigned char q_lds[kMxQOps<D> + 256];
+    Q.quantize(qsc, lds_addr_of(q_lds), lds_addr_of(q_lds) + kMxQOps<D>, (int)threadIdx.x);
+    __syncthreads();
+    Q.read(qops, qsc, (size_t)bh * 4, lane, lds_addr_of(q_lds), lds_addr_of(q_lds) + kMxQOps<D>);
     for (int p = p0; p < p0 + per; ++p) {
         floatx16 sv;
 #pragma unroll
         for (int i = 0; i < 16; ++i) sv[i] = 0.0f;
-        sv = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[0]), as8(qop[0]), sv, 4, 4, 0, ksc, 0, qs);
-        if constexpr (KS == 2) sv = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[1]), as8(qop[1]), sv, 4, 4, 1, ksc, 1, qs);
+        sv = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[0]), as8(Q.op[0]), sv, 4, 4, 0, ksc, 0, Q.sc);
+        if constexpr (KS == 2) sv = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(a[1]), as8(Q.op[1]), sv, 4, 4, 1, ksc, 1, Q.sc);
         mfma_scale_settle(sv);
         if (p + 1 < p0 + per) load(p + 1);
         const int k0 = p * 128 + T * 64;
@@ -921,7 +929,7 @@ __global__ __launch_bounds__(256) void mx_decode_max_kernel(
 
 template <int D, bool CAUSAL>
 __global__ __launch_bounds__(256) void mx_decode_p_kernel(
-    const unsigned char* __restrict__ qops, const uint32_t* __restrict__ qsc, const unsigned char* __restrict__ kv, int L, int Hq, int G, float c,
+    const void* __restrict__ qops, const uint32_t* __restrict__ qsc, const unsigned char* __restrict__ kv, int L, int Hq, int G, float c,
     const int* __restrict__ page_table, const int* __restrict__ kv_lens, int max_pages, int num_pages, int lq_inner, MxDecSplit sp, int seg0 /* first page of the segment */)
 {
     constexpr int KS = D / 64, MT = D / 32, KOPS = 2 * KS * 1024, VOPS = MT * 1024, REC = mx_rec_bytes(D, false), NT = 4;
@@ -934,7 +942,8 @@ __global__ __launch_bounds__(256) void mx_decode_p_kernel(
     if (nt_all <= 0) return;
     const int koff = Lk - lq_inner;
     const int klim = CAUSAL ? min(Lk - 1, koff + (lq_inner != L ? ln % lq_inner : ln)) : Lk - 1;
-    uint4v kr[2 * KS], qop[KS];
+    uint4v kr[2 * KS];
+    MxQ<D, 256> Q;
     uint32_t ksc;
     // tile j of the chunk (beyond the last one: the last one)
     auto page_of = [&](int j) __attribute__((always_inline)) { return page_table[(size_t)b * max_pages + p0 + (min(j, nt_all - 1) >> 1)]; };
@@ -945,11 +954,9 @@ __global__ __launch_bounds__(256) void mx_decode_p_kernel(
         for (int i = 0; i < 2 * KS; ++i) kr[i] = *reinterpret_cast<const uint4v*>(rec + 1024 * i + 16 * lane);
         ksc = *reinterpret_cast<const uint32_t*>(rec + KOPS + VOPS + 4 * lane);
     };
+    Q.fetch(qops, qsc, bh, 0, (size_t)bh * 4, (int)threadIdx.x, L);
     load_k(wave, page_of(wave));
     int id_next = page_of(wave + NT);
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qop[ks] = *reinterpret_cast<const uint4v*>(qops + (((size_t)bh * 4 * KS + ks) * 64 + lane) * 16);
-    const uint32_t qs = qsc[(size_t)bh * 4 * 64 + lane];
     auto as8 = [](const uint4v& x) __attribute__((always_inline)) -> int8v {
         int8v r = {(int)x[0], (int)x[1], (int)x[2], (int)x[3], 0, 0, 0, 0};
         return r;
@@ -963,19 +970,22 @@ __global__ __launch_bounds__(256) void mx_decode_p_kernel(
     float m = -INFINITY;
     for (int i = 2 * wave + hf; i < ch; i += 8) m = fmaxf(m, sp.cmax[((size_t)bh * sp.n + i) * kMxDecRows + ln]);
     front[2 * wave + hf][ln] = m;
+    __shared__ __align__(16) unsigned char q_lds[kMxQOps<D> + 256];
+    Q.quantize(qsc, lds_addr_of(q_lds), lds_addr_of(q_lds) + kMxQOps<D>, (int)threadIdx.x);
     lds_barrier();
 #pragma unroll
     for (int i = 0; i < 8; ++i) m = fmaxf(m, front[i][ln]);
+    Q.read(qops, qsc, (size_t)bh * 4, lane, lds_addr_of(q_lds), lds_addr_of(q_lds) + kMxQOps<D>);
     for (int j0 = 0, buf = 0; j0 < nt_all; j0 += NT, buf ^= 1) {
         const int j = j0 + wave;
         const bool active = j < nt_all;
         const floatx16 zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
         floatx16 s[2];
-        s[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr[0]), as8(qop[0]), zero, 4, 4, 0, ksc, 0, qs);
-        s[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr[KS]), as8(qop[0]), zero, 4, 4, KS, ksc, 0, qs);
+        s[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr[0]), as8(Q.op[0]), zero, 4, 4, 0, ksc, 0, Q.sc);
+        s[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr[KS]), as8(Q.op[0]), zero, 4, 4, KS, ksc, 0, Q.sc);
         if constexpr (KS == 2) {
-            s[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr[1]), as8(qop[1]), s[0], 4, 4, 1, ksc, 1, qs);
-            s[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr[3]), as8(qop[1]), s[1], 4, 4, 3, ksc, 1, qs);
+            s[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr[1]), as8(Q.op[1]), s[0], 4, 4, 1, ksc, 1, Q.sc);
+            s[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as8(kr[3]), as8(Q.op[1]), s[1], 4, 4, 3, ksc, 1, Q.sc);
         }
         mfma_scale_settle(s[0], s[1]);
         if (j0 + NT < nt_all) {
@@ -1239,7 +1249,7 @@ static int launch_fwd_mx_t(const void* qops, const void* qsc, const void* kv, in
     if constexpr (KVM != 3) {
         if (mx_split_key_tiles(B * Hq, L, CAUSAL && KVM != 1, FP8PV, KVM == 2, KVM == 1)) {
             hipLaunchKernelGGL((fwd_mx_split_kernel<D, CAUSAL, FP8PV, KVM>), dim3((unsigned)(B * Hq * ((L + 31) / 32))), dim3(256), 0, st,
-                               (const unsigned char*)qops, (const uint32_t*)qsc, (const unsigned char*)kv,
+                               qops, (const uint32_t*)qsc, (const unsigned char*)kv,
                                (uint16_t*)o, lse, L, Lp, Hq, Hq / Hkv, c, page_table, kv_lens, max_pages, num_pages, lq_inner, B);
             return hipGetLastError() == hipSuccess ? 0 : -1;
         }
@@ -1249,7 +1259,7 @@ static int launch_fwd_mx_t(const void* qops, const void* qsc, const void* kv, in
     if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)smem, lds_set)) return -1;
     const int groups = KVM == 3 ? round_up(B * Hkv, 8) : B * Hkv;       // (see varlen_item)
     hipLaunchKernelGGL(kern, dim3((unsigned)(groups * (Hq / Hkv) * (Lp / 128))), dim3(256), smem, st,
-                       (const unsigned char*)qops, (const uint32_t*)qsc, (const unsigned char*)kv,
+                       qops, (const uint32_t*)qsc, (const unsigned char*)kv,
                        (uint16_t*)o, lse, L, Lp, Hq, Hq / Hkv, c, page_table, kv_lens, max_pages, num_pages, lq_inner, B);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
@@ -1285,11 +1295,11 @@ int launch_fwd_mx_paged(const void* qops, const void* qsc, const void* cache, in
             sp.rec = part + (size_t)kMxDecUnits * kMxDecRows * 4;
             sp.state = reinterpret_cast<float*>(sp.rec + (size_t)(mx_decode_room(Lq) + kMxDecAhead) * mx_dec_rec_bytes(Lq));
 #define AQ_SPLIT(DD, CC) do { \
-            hipLaunchKernelGGL((mx_decode_max_kernel<DD, CC>), dim3((unsigned)(B * Hq), (unsigned)(sp.n - 1)), dim3(256), 0, st, (const unsigned char*)qops, (const uint32_t*)qsc, \
+            hipLaunchKernelGGL((mx_decode_max_kernel<DD, CC>), dim3((unsigned)(B * Hq), (unsigned)(sp.n - 1)), dim3(256), 0, st, qops, (const uint32_t*)qsc, \
                                (const unsigned char*)cache, Lq, Hq, Hq / Hkv, page_table, kv_lens, max_pages, num_pages, lq_inner, sp.per, sp.n, sp.cmax); \
             for (int seg0 = 0; seg0 < max_pages; seg0 += sp.seg) { \
                 hipLaunchKernelGGL((mx_decode_p_kernel<DD, CC>), dim3((unsigned)(B * Hq), (unsigned)(min(sp.seg, max_pages - seg0) + sp.per - 1) / sp.per), dim3(256), 0, st, \
-                                   (const unsigned char*)qops, (const uint32_t*)qsc, (const unsigned char*)cache, Lq, Hq, Hq / Hkv, c, page_table, kv_lens, max_pages, num_pages, lq_inner, sp, seg0); \
+                                   qops, (const uint32_t*)qsc, (const unsigned char*)cache, Lq, Hq, Hq / Hkv, c, page_table, kv_lens, max_pages, num_pages, lq_inner, sp, seg0); \
                 hipLaunchKernelGGL((mx_decode_pv_kernel<DD>), dim3((unsigned)(B * Hq), DD / 32), dim3(256), 0, st, (const unsigned char*)cache, (uint16_t*)o, lse, \
                                    Lq, Hq, Hq / Hkv, c, page_table, kv_lens, max_pages, num_pages, sp, seg0); \
             } \
@@ -1305,7 +1315,7 @@ int launch_fwd_mx_paged(const void* qops, const void* qsc, const void* cache, in
         auto kern = fwd_mx_decode_kernel<DD, CC, NP>; \
         static unsigned long long lds_set = 0; \
         if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)smem, lds_set)) return -1; \
-        hipLaunchKernelGGL(kern, dim3((unsigned)(B * Hq)), dim3(256 * NP), smem, st, (const unsigned char*)qops, (const uint32_t*)qsc, \
+        hipLaunchKernelGGL(kern, dim3((unsigned)(B * Hq)), dim3(256 * NP), smem, st, qops, (const uint32_t*)qsc, \
                            (const unsigned char*)cache, (uint16_t*)o, lse, Lq, Hq, Hq / Hkv, c, page_table, kv_lens, max_pages, num_pages, lq_inner); \
         return hipGetLastError() == hipSuccess ? 0 : -1; } while (0)
         if (D == 128) { if (causal) AQ_DECODE(128, true); else AQ_DECODE(128, false); }
