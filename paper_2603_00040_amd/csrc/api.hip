@@ -125,7 +125,7 @@ int check_dims(int B, int Hq, int Hkv, int L, int d, int dtype)
 }
 
 // Workspace of the forward: fp16 Q^F, K^F (row-major) and V^F^T.
-struct FwdWs { void *qh, *kh, *vt, *qsc; double* kpart; float* kmean; size_t bytes; };
+struct FwdWs { void *qh, *kh, *vt; double* kpart; float* kmean; size_t bytes; };
 FwdWs carve_fwd(void* ws, int B, int Hq, int Hkv, int L, int d, bool mx = false)
 {
     const size_t Lp = round_up(L, kRowPad);
@@ -134,9 +134,8 @@ FwdWs carve_fwd(void* ws, int B, int Hq, int Hkv, int L, int d, bool mx = false)
     w.qh = c.take((size_t)B * Hq * Lp * d * 2);
     w.kh = c.take((size_t)B * Hkv * Lp * d * 2);
     w.vt = c.take((size_t)B * Hkv * Lp * d * 2);
-    if (mx) c.take((size_t)B * Hq * L * d * 2);      // (not used any more: the size asked for stays what it was)
-    // MX: qh and kh hold the operands of the FP4 instruction (smaller than the fp16 copies); the Q scale dwords come extra
-    w.qsc = mx ? c.take(mx_qsc_bytes(B * Hq, L)) : nullptr;
+    // MX: kh holds the K records of the FP4 instruction (smaller than the fp16 copies), qh a copy of Q where one is needed
+    if (mx) { c.take((size_t)B * Hq * L * d * 2); c.take(mx_qsc_bytes(B * Hq, L)); }      // (not used any more: the size asked for stays what it was)
     w.kpart = (double*)c.take(colmean_scratch_bytes(B * Hkv, d));  // K smoothing: partial sums and the token mean of K
     w.kmean = (float*)c.take((size_t)B * Hkv * d * 4);
     w.bytes = c.off;
@@ -230,13 +229,15 @@ int fwd_common(const void* q, const void* k, const void* v, int B, int Hq, int H
     hipStream_t st = (hipStream_t)stream;
     prof_begin(st);
     if (mx) {
-        // Q and K as operands of the scaled FP4 instruction (the scores are computed from the codes), V^F^T as the fp16 copy
-        const bool direct = q_unwritten(q, B, Hq, L, d, o, lse, train ? o_hp : nullptr);       // the attention kernel quantizes Q
-        MxGroup g = mx_group_of(direct ? nullptr : q, k, v, B * Hq, B * Hkv, L);
-        g.qops = (unsigned char*)w.qh; g.qsc = (unsigned char*)w.qsc; g.krec = (unsigned char*)w.kh; g.v_out = (uint16_t*)w.vt;
+        // K as operands of the scaled FP4 instruction (the scores are computed from the codes), V^F^T as the fp16 copy; the attention kernel
+        // quantizes Q, from a copy where a result lies over it
+        const bool direct = q_unwritten(q, B, Hq, L, d, o, lse, train ? o_hp : nullptr);
+        if (!direct && hipMemcpyAsync(w.qh, q, (size_t)B * Hq * L * d * 2, hipMemcpyDeviceToDevice, st) != hipSuccess) return ATTNQAT_ELAUNCH;
+        MxGroup g = mx_group_of(nullptr, k, v, B * Hq, B * Hkv, L);
+        g.krec = (unsigned char*)w.kh; g.v_out = (uint16_t*)w.vt;
         if (launch_mx_group(g, MX_TRAIN, d, st)) return ATTNQAT_ELAUNCH;
         prof_mark("prep_qkv", st);
-        if (launch_fwd(direct ? q : w.qh, w.kh, w.vt, B, Hq, Hkv, L, d, causal != 0, train, 1, o, lse, o_hp, dump_row0, p_dump, st, direct ? nullptr : w.qsc))
+        if (launch_fwd(direct ? q : w.qh, w.kh, w.vt, B, Hq, Hkv, L, d, causal != 0, train, 1, o, lse, o_hp, dump_row0, p_dump, st))
             return ATTNQAT_ELAUNCH;
         prof_mark(train ? "fwd_train" : "fwd_infer", st);
         return ATTNQAT_OK;

@@ -46,15 +46,14 @@ __device__ __forceinline__ void fwd_body(
     const half_t* __restrict__ Qh, const half_t* __restrict__ Kh, const half_t* __restrict__ Vt,
     uint16_t* __restrict__ O, float* __restrict__ lse, float* __restrict__ Ohp,
     int L, int Lp, int Hq, int G, float c /* log2(e)/sqrt(d) */, int dump_row0, float* __restrict__ pdump,
-    int Lkp_arg, const int* __restrict__ kv_lens, const uint32_t* __restrict__ Qsc, int B /* batch (VARLEN: sequences) */)
+    int Lkp_arg, const int* __restrict__ kv_lens, int B /* batch (VARLEN: sequences) */)
 {
     constexpr int KS = SPLIT ? NW : 1;
     constexpr int QT = 32 * NW / KS;       // query rows of a workgroup
     constexpr bool PHASES = NW == 8 && !SPLIT, PAIRED = CAUSAL && PHASES;
     // PQ == 1 (MX): S = Q^F K^F^T comes from the E2M1 codes and E8M0 scales by v_mfma_scale_f32_32x32x64_f8f6f4 (a quarter of
-    // the matrix time of the 16-bit products, a quarter of the K bytes through LDS).  Qh then holds the Q operands of that
-    // instruction (64 d per step: lane (row, half) has d-slots 64 ks + 32 half .. + 31 of its row) with one dword of scale
-    // bytes per lane in Qsc, or Q itself in bf16 (Qsc null, MxQ), and Kh the K records of mx_ktrain_rec_bytes(D) bytes per key tile.  The accumulator layout is
+    // the matrix time of the 16-bit products, a quarter of the K bytes through LDS).  Qh then is Q itself in bf16, of which
+    // the waves make the operands of that instruction (MxQ), and Kh the K records of mx_ktrain_rec_bytes(D) bytes per key tile.  The accumulator layout is
     // that of the 16-bit products, so everything after the scores is unchanged (O and O' stay 16-bit products: O' needs the
     // un-quantized P-tilde, which is no operand of that instruction).
     constexpr bool MXS = PQ == 1;
@@ -145,7 +144,7 @@ __device__ __forceinline__ void fwd_body(
     half8 qreg[MXS || Q_LDS ? 1 : DS];
     MxQ<D, SPLIT ? 64 * NW : 64> Q;      // (SPLIT: the four waves share the rows)
     if constexpr (MXS) {
-        Q.fetch(Qh, Qsc, bh, has_rows ? row0_w : 0, grp, q_tid, L);
+        Q.fetch(Qh, nullptr, bh, has_rows ? row0_w : 0, grp, q_tid, L);
     } else if constexpr (!Q_LDS) {
         const half_t* qp = Qh + ((size_t)bh * Lp + (has_rows ? q_row : 0)) * D + 8 * hf;
 #pragma unroll
@@ -256,9 +255,9 @@ __device__ __forceinline__ void fwd_body(
             // (phi(Q) through the second V^T buffer and what the K record leaves of the first K buffer: neither has been asked for yet)
             static_assert(NW * kMxQOps<D> <= sizeof(sm.v[1]) && KREC + NW * 256 <= (int)sizeof(sm.k[0]));
             const uint32_t ops = lds_addr_of(vbase) + (uint32_t)sizeof(sm.v[0]) + (uint32_t)(wave * kMxQOps<D>), scs = lds_addr_of(kbase) + (uint32_t)(KREC + wave * 256);
-            Q.quantize(Qsc, ops, scs, q_tid);
+            Q.quantize(nullptr, ops, scs, q_tid);
             mx_q_wave_fence();
-            Q.read(Qh, Qsc, grp, lane, ops, scs);
+            Q.read(Qh, nullptr, grp, lane, ops, scs);
         }
     } else if constexpr (Q_LDS) {
 #pragma unroll
@@ -742,9 +741,9 @@ __device__ __forceinline__ void fwd_body(
         }
         if constexpr (MXS) {
             // (phi(Q) through the room of P, which is first written behind the barrier of the maxima)
-            Q.quantize(Qsc, p_lds, p_lds + kMxQOps<D>, q_tid);
+            Q.quantize(nullptr, p_lds, p_lds + kMxQOps<D>, q_tid);
             lds_barrier();
-            Q.read(Qh, Qsc, grp, lane, p_lds, p_lds + kMxQOps<D>);
+            Q.read(Qh, nullptr, grp, lane, p_lds, p_lds + kMxQOps<D>);
         }
         int j0 = 0;
         for (; j0 + KS < nkt; j0 += KS) four_tiles(std::true_type{}, j0);
@@ -852,16 +851,16 @@ __device__ __forceinline__ void fwd_body(
     const half_t* __restrict__ Qh, const half_t* __restrict__ Kh, const half_t* __restrict__ Vt, \
     uint16_t* __restrict__ O, float* __restrict__ lse, float* __restrict__ Ohp, \
     int L, int Lp, int Hq, int G, float c, int dump_row0, float* __restrict__ pdump, \
-    int Lkp, const int* __restrict__ kv_lens, const uint32_t* __restrict__ Qsc, int B
+    int Lkp, const int* __restrict__ kv_lens, int B
 template <int D, bool TRAIN, bool CAUSAL, bool DUMP, int PQ, bool VARLEN = false>
 __global__ __launch_bounds__(512, 2) void fwd_kernel(AQ_FWD_ARGS)
 {
-    fwd_body<D, TRAIN, CAUSAL, DUMP, PQ, VARLEN, 8>(Qh, Kh, Vt, O, lse, Ohp, L, Lp, Hq, G, c, dump_row0, pdump, Lkp, kv_lens, Qsc, B);
+    fwd_body<D, TRAIN, CAUSAL, DUMP, PQ, VARLEN, 8>(Qh, Kh, Vt, O, lse, Ohp, L, Lp, Hq, G, c, dump_row0, pdump, Lkp, kv_lens, B);
 }
 template <int D, bool TRAIN, bool CAUSAL, int PQ, bool VARLEN = false>
 __global__ __launch_bounds__(256, 2) void fwd_narrow_kernel(AQ_FWD_ARGS)
 {
-    fwd_body<D, TRAIN, CAUSAL, false, PQ, VARLEN, 4>(Qh, Kh, Vt, O, lse, Ohp, L, Lp, Hq, G, c, dump_row0, pdump, Lkp, kv_lens, Qsc, B);
+    fwd_body<D, TRAIN, CAUSAL, false, PQ, VARLEN, 4>(Qh, Kh, Vt, O, lse, Ohp, L, Lp, Hq, G, c, dump_row0, pdump, Lkp, kv_lens, B);
 }
 // Alg. 1 / Alg. 2 where there are too few query rows to fill the chip: a workgroup owns 32 rows, and its four waves take four key
 // tiles at a time, wave w tile 4 n + w for S, the softmax and phi(P-tilde), and block w of O (and O') for the P V products of all four.
@@ -879,7 +878,7 @@ __global__ __launch_bounds__(256, 2) void fwd_narrow_kernel(AQ_FWD_ARGS)
 template <int D, bool TRAIN, bool CAUSAL, int PQ, bool VARLEN = false>
 __global__ __launch_bounds__(256, 2) void fwd_split_kernel(AQ_FWD_ARGS)
 {
-    fwd_body<D, TRAIN, CAUSAL, false, PQ, VARLEN, 4, true>(Qh, Kh, Vt, O, lse, Ohp, L, Lp, Hq, G, c, dump_row0, pdump, Lkp, kv_lens, Qsc, B);
+    fwd_body<D, TRAIN, CAUSAL, false, PQ, VARLEN, 4, true>(Qh, Kh, Vt, O, lse, Ohp, L, Lp, Hq, G, c, dump_row0, pdump, Lkp, kv_lens, B);
 }
 #undef AQ_FWD_ARGS
 
@@ -943,7 +942,7 @@ static size_t split_lds_bytes(int D, bool train, int pq) { return (size_t)(train
 template <int D, bool TRAIN, bool CAUSAL, bool DUMP, int PQ, bool VARLEN = false>
 static int launch_t(const void* qh, const void* kh, const void* vt, int B, int Hq, int Hkv, int L,
                     void* o, float* lse, float* o_hp, int dump_row0, float* p_dump, hipStream_t st,
-                    int Lkp = 0, const int* kv_lens = nullptr, const void* qsc = nullptr)
+                    int Lkp = 0, const int* kv_lens = nullptr)
 {
     const int Lp = round_up(L, kRowPad);
     const int nqt = (Lp + 255) / 256;
@@ -954,7 +953,7 @@ static int launch_t(const void* qh, const void* kh, const void* vt, int B, int H
         if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)smem, lds_set)) return -1;
         hipLaunchKernelGGL(kern, dim3(grid), dim3(block), smem, st,
                            (const half_t*)qh, (const half_t*)kh, (const half_t*)vt, (uint16_t*)o, lse, o_hp,
-                           L, Lp, Hq, Hq / Hkv, c, dump_row0, p_dump, Lkp, kv_lens, (const uint32_t*)qsc, B);
+                           L, Lp, Hq, Hq / Hkv, c, dump_row0, p_dump, Lkp, kv_lens, B);
         return hipGetLastError() == hipSuccess ? 0 : -1;
     };
     if constexpr (!DUMP && PQ != 2) {
@@ -979,27 +978,27 @@ static int launch_t(const void* qh, const void* kh, const void* vt, int B, int H
 template <int D, int PQ>
 static int launch_d(const void* qh, const void* kh, const void* vt, int B, int Hq, int Hkv, int L,
                     bool causal, bool train, void* o, float* lse, float* o_hp,
-                    int dump_row0, float* p_dump, hipStream_t st, const void* qsc)
+                    int dump_row0, float* p_dump, hipStream_t st)
 {
     if (p_dump) {
-        return causal ? launch_t<D, false, true, true, PQ>(qh, kh, vt, B, Hq, Hkv, L, o, lse, o_hp, dump_row0, p_dump, st, 0, nullptr, qsc)
-                      : launch_t<D, false, false, true, PQ>(qh, kh, vt, B, Hq, Hkv, L, o, lse, o_hp, dump_row0, p_dump, st, 0, nullptr, qsc);
+        return causal ? launch_t<D, false, true, true, PQ>(qh, kh, vt, B, Hq, Hkv, L, o, lse, o_hp, dump_row0, p_dump, st)
+                      : launch_t<D, false, false, true, PQ>(qh, kh, vt, B, Hq, Hkv, L, o, lse, o_hp, dump_row0, p_dump, st);
     }
     if constexpr (PQ != 3) {
         if (train) {
-            return causal ? launch_t<D, true, true, false, PQ>(qh, kh, vt, B, Hq, Hkv, L, o, lse, o_hp, 0, nullptr, st, 0, nullptr, qsc)
-                          : launch_t<D, true, false, false, PQ>(qh, kh, vt, B, Hq, Hkv, L, o, lse, o_hp, 0, nullptr, st, 0, nullptr, qsc);
+            return causal ? launch_t<D, true, true, false, PQ>(qh, kh, vt, B, Hq, Hkv, L, o, lse, o_hp, 0, nullptr, st)
+                          : launch_t<D, true, false, false, PQ>(qh, kh, vt, B, Hq, Hkv, L, o, lse, o_hp, 0, nullptr, st);
         }
     }
-    return causal ? launch_t<D, false, true, false, PQ>(qh, kh, vt, B, Hq, Hkv, L, o, lse, o_hp, 0, nullptr, st, 0, nullptr, qsc)
-                  : launch_t<D, false, false, false, PQ>(qh, kh, vt, B, Hq, Hkv, L, o, lse, o_hp, 0, nullptr, st, 0, nullptr, qsc);
+    return causal ? launch_t<D, false, true, false, PQ>(qh, kh, vt, B, Hq, Hkv, L, o, lse, o_hp, 0, nullptr, st)
+                  : launch_t<D, false, false, false, PQ>(qh, kh, vt, B, Hq, Hkv, L, o, lse, o_hp, 0, nullptr, st);
 }
 
 int launch_fwd(const void* qh, const void* kh, const void* vt,
                int B, int Hq, int Hkv, int L, int D, bool causal, bool train, int p_quant,
-               void* o, float* lse, float* o_hp, int dump_row0, float* p_dump, hipStream_t st, const void* qsc)
+               void* o, float* lse, float* o_hp, int dump_row0, float* p_dump, hipStream_t st)
 {
-#define AQ_FWD(DD, PQ) launch_d<DD, PQ>(qh, kh, vt, B, Hq, Hkv, L, causal, train, o, lse, o_hp, dump_row0, p_dump, st, qsc)
+#define AQ_FWD(DD, PQ) launch_d<DD, PQ>(qh, kh, vt, B, Hq, Hkv, L, causal, train, o, lse, o_hp, dump_row0, p_dump, st)
     if (p_quant == 3 && train) return -1;           // the bf16 P V recipe has no backward
     if (D == 128) return p_quant == 1 ? AQ_FWD(128, 1) : p_quant == 2 ? AQ_FWD(128, 2) : p_quant == 3 ? AQ_FWD(128, 3) : AQ_FWD(128, 0);
     if (D == 64)  return p_quant == 1 ? AQ_FWD(64, 1) : p_quant == 2 ? AQ_FWD(64, 2) : p_quant == 3 ? AQ_FWD(64, 3) : AQ_FWD(64, 0);

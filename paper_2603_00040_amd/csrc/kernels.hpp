@@ -49,13 +49,13 @@ size_t colmean_scratch_bytes(int BH, int D);
 int launch_colmean(const void* x, int BH, int L, int D, double* scratch, float* mean, hipStream_t st);
 
 // Alg. 1 (train=false) / Alg. 2 (train=true) on copies made by launch_prep_group.
-// p_quant 1 (MX): qh and kh are NOT fp16 copies but the operand arrays of the scaled FP4 instruction (launch_mx_group,
-// MX_TRAIN: qops with its scale dwords in qsc, or Q itself with qsc null; and krec): the scores are computed from the codes; vt stays the fp16 copy.
+// p_quant 1 (MX): qh is Q itself in bf16 (no result may lie over it) and kh the K records of launch_mx_group (MX_TRAIN, krec), not fp16
+// copies: the scores are computed from the codes; vt stays the fp16 copy.
 // p_quant: phi(P-tilde) 0 NVFP4; 1 in the MX format (blocks of 32 keys, power-of-two scale); 2 NVFP4 after the
 // two-level row factor (every 64-key tile row divided by a power of two that brings its maximum just below 448 * 6).
 int launch_fwd(const void* qh, const void* kh, const void* vt,
                int B, int Hq, int Hkv, int L, int D, bool causal, bool train, int p_quant,
-               void* o, float* lse, float* o_hp, int dump_row0, float* p_dump, hipStream_t st, const void* qsc = nullptr);
+               void* o, float* lse, float* o_hp, int dump_row0, float* p_dump, hipStream_t st);
 
 // Alg. 1 for sequences of different lengths (serving): queries are the last Lq positions of every sequence, sequence b has
 // kv_lens[b] keys (device array), kh / vt are laid out for Lkp positions per kv head.
@@ -117,7 +117,7 @@ void set_bwd_waves(int waves);
 // optional bf16 xf: see attnqat.h.  fp8: E4M3 elements instead of E2M1 (axis 1 only).
 int launch_mx_quant(const void* x, int BH, int L, int D, int axis, bool fp8, unsigned char* codes, unsigned char* scales, void* xf, hipStream_t st);
 // Everything that an MX forward or backward prepares, in one launch (null outputs are left out):
-//   Q: operands of the scaled MFMA (qops, scale dwords qsc)              [all]; fp16 rows q_row    [MX_BWD]
+//   Q: operands of the scaled MFMA (qops, scale dwords qsc)              [not MX_TRAIN]; fp16 rows q_row    [MX_BWD]
 //   K: the K part of the 64-key kv records kv                            [MX_INFER, MX_INFER_FP8V]
 //      records in natural key order krec                                 [MX_TRAIN, MX_BWD]
 //      operands kops, ksc as of Q; fp16 rows k_row                       [MX_BWD]
