@@ -62,9 +62,7 @@ __device__ inline uint4v join(uint2v a, uint2v b) { uint4v r; r[0] = a[0]; r[1] 
 // One of the three maxima of a head: every lane gets the maximum of the head's partial values.
 __device__ inline float bound_of(const float* __restrict__ part, int NHq, int which, int head) {
     float v = part[((size_t)which * NHq + head) * kBoundParts + (threadIdx.x & 63)];
-#pragma unroll
-    for (int w = 32; w >= 1; w >>= 1) v = fmaxf(v, __shfl_xor(v, w));
-    return v;
+    return lanes_max<32, 1>(v);
 }
 
 static int g_bwd_waves = 0;           // waves per workgroup of the dQ and dK/dV passes, 0: chosen per problem; 4 / 8: forced (tests)
@@ -578,10 +576,7 @@ __device__ __forceinline__ void bwd_dkdv_body(const DkvArgs& A, int bhkv, int kt
 #pragma unroll
             for (int i = 0; i < 4; ++i) { domax = fmaxf(domax, a[i]); dmax = fmaxf(dmax, e[i]); }
         }
-#pragma unroll
-        for (int w = 32; w >= 1; w >>= 1) {
-            vmax = fmaxf(vmax, __shfl_xor(vmax, w)); domax = fmaxf(domax, __shfl_xor(domax, w)); dmax = fmaxf(dmax, __shfl_xor(dmax, w));
-        }
+        vmax = lanes_max<32, 1>(vmax); domax = lanes_max<32, 1>(domax); dmax = lanes_max<32, 1>(dmax);
         ds_scale = ds_scale_for(domax * vmax * rs + dmax);
     }
     const float rs_s = rs * ds_scale;

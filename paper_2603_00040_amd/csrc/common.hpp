@@ -140,6 +140,44 @@ __device__ inline float xhalf_sum(float x) {
 }
 
 
+// Reductions over neighbouring lanes without LDS: a step of the tree x = op(x, value of lane ^ W), by DPP up to 8 and by the row and
+// half swaps from 16 on (where both lanes of a pair get op(lower, upper): op commutes).  __shfl_xor goes through the LDS, 100 - 130 cycles a step, and
+// these trees are serial: decode steps and the starts and ends of the preparing and backward kernels wait for them.  Through LDS -> here: decode step
+// of 32 sequences of 4k - 16k keys 113.0 -> 110.7 us; training step of 2 heads, L = 256, d = 64 25.3 -> 24.95 us.
+template <int W, class OP>
+__device__ __forceinline__ float xor_step(float x, OP op) {
+    static_assert(W == 1 || W == 2 || W == 4 || W == 8 || W == 16 || W == 32);
+    const uint32_t u = __float_as_uint(x);
+    if constexpr (W == 1) return op(x, __uint_as_float(__builtin_amdgcn_update_dpp(u, u, 0xB1, 0xF, 0xF, false)));        // quad_perm 1,0,3,2
+    else if constexpr (W == 2) return op(x, __uint_as_float(__builtin_amdgcn_update_dpp(u, u, 0x4E, 0xF, 0xF, false)));   // quad_perm 2,3,0,1
+    else if constexpr (W == 4) {
+        const uint32_t a = __builtin_amdgcn_update_dpp(u, u, 0x104, 0xF, 0x5, false);                                     // row_shl 4 into quads 0 and 2
+        return op(x, __uint_as_float(__builtin_amdgcn_update_dpp(a, u, 0x114, 0xF, 0xA, false)));                         // row_shr 4 into quads 1 and 3
+    }
+    else if constexpr (W == 8) return op(x, __uint_as_float(__builtin_amdgcn_update_dpp(u, u, 0x128, 0xF, 0xF, false)));  // row_ror 8
+    else if constexpr (W == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+        return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    } else {
+        const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+        return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    }
+}
+// Steps FROM, ... , TO (each twice or half the one before): the largest value, or the sum, over lanes that differ in those bits.
+template <int FROM, int TO, class OP>
+__device__ __forceinline__ float xor_tree(float x, OP op) {
+    x = xor_step<FROM>(x, op);
+    if constexpr (FROM == TO) return x;
+    else return xor_tree<(FROM < TO ? FROM * 2 : FROM / 2), TO>(x, op);
+}
+struct OpMax { __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); } };
+struct OpAdd { __device__ __forceinline__ float operator()(float a, float b) const { return a + b; } };
+template <int FROM, int TO> __device__ __forceinline__ float lanes_max(float x) { return xor_tree<FROM, TO>(x, OpMax{}); }
+template <int FROM, int TO> __device__ __forceinline__ float lanes_sum(float x) { return xor_tree<FROM, TO>(x, OpAdd{}); }
+// The value of the next lane, of the second next, ... (N = 1 .. 15) of a row of 16 lanes; 0 beyond the row.
+template <int N>
+__device__ __forceinline__ uint32_t lane_down(uint32_t x) { return __builtin_amdgcn_update_dpp(0u, x, 0x100 + N, 0xF, 0xF, true); }
+
 // Whatever a free register holds: the first operand of a conversion that replaces part of a register whose rest is never read, or is
 // replaced by the conversions that follow.  A zero, or a register that is still needed, costs a move.
 __device__ inline uint32_t any_register() {

@@ -88,8 +88,7 @@ __device__ inline half8 dequant8(const RawKV<D>& r, half2v sc, int s) {
 // phi^-1(phi(P-tilde)) of four keys of a row as fp16; four neighbouring lanes hold a block of 16.
 __device__ inline uint2v phi_p_quad(const float (&pt)[4]) {
     float amax = fmaxf(fmaxf(pt[0], pt[1]), fmaxf(pt[2], pt[3]));
-    amax = fmaxf(amax, __shfl_xor(amax, 1));
-    amax = fmaxf(amax, __shfl_xor(amax, 2));
+    amax = lanes_max<1, 2>(amax);
     // RNE_E4M3(amax / 6) by the hardware conversion and back (P-tilde <= 1: no saturation)
     typedef short short2v __attribute__((ext_vector_type(2)));
     short2v pk = {0, 0};
@@ -339,7 +338,7 @@ __global__ __launch_bounds__(256, 2) void decode_kernel(
         const int klim_min = CAUSAL ? Lk - Lq : Lk - 1;            // ... and the least of those over the rows
 
         // exchange map of the maxima: lane (xr, xt) = row xr, tile xt of this chunk / xt-th chunk in front (16 neighbouring lanes
-        // per row: reductions and running maxima are shuffles)
+        // per row: reductions and running maxima stay within a row)
         const int xr = tid >> 4, xt = tid & 15;
         unsigned long long v_early = 0;
 
@@ -369,8 +368,7 @@ __global__ __launch_bounds__(256, 2) void decode_kernel(
                     // (CK is a multiple of 128: the address is a multiple of 16, which the compiler cannot see in an index)
                     if (cc < R) lds_write16_at(sbuf_ad + 4u * (uint32_t)(cc * CK + 64 * t + 16 * blk + 4 * g), __builtin_bit_cast(uint4v, acc));
                 }
-                mx = fmaxf(mx, __shfl_xor(mx, 16));
-                mx = fmaxf(mx, __shfl_xor(mx, 32));
+                mx = lanes_max<16, 32>(mx);
                 if (g == 0 && cc < R) tmax[cc][t] = mx;
             }
             issue(cur, it + 3);                  // (the first V parts travel while the maxima are exchanged)
@@ -389,11 +387,10 @@ __global__ __launch_bounds__(256, 2) void decode_kernel(
         // ---- the chunk's row maxima out, those of the chunks before it in
         const size_t unit = (size_t)bh * NC + ch;
         float pm = xr < R && xt < NT ? tmax[xr][xt] : -INFINITY;      // becomes the row's running maximum over the tiles
-#pragma unroll
-        for (int dd = 1; dd < 16; dd <<= 1) {
-            const float up = __shfl_up(pm, dd, 16);
-            if (xt >= dd) pm = fmaxf(pm, up);
-        }
+        // (row_shr 1, 2, 4, 8: -inf where there is no lane in front)
+#define AQ_UP(CTRL) pm = fmaxf(pm, __uint_as_float(__builtin_amdgcn_update_dpp(0xFF800000u, __float_as_uint(pm), CTRL, 0xF, 0xF, false)))
+        AQ_UP(0x111); AQ_UP(0x112); AQ_UP(0x114); AQ_UP(0x118);
+#undef AQ_UP
         if (nch > 1 && xt == 15 && xr < R)
             __hip_atomic_store(&cmax[unit * kDecRows + xr], (1ull << 32) | (unsigned long long)__float_as_uint(pm),
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -415,8 +412,7 @@ __global__ __launch_bounds__(256, 2) void decode_kernel(
                 else __hip_atomic_store(&ctl[1], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
-#pragma unroll
-        for (int dd = 1; dd < 16; dd <<= 1) m_pred = fmaxf(m_pred, __shfl_xor(m_pred, dd, 16));
+        m_pred = lanes_max<1, 8>(m_pred);
         if (xr < R && xt < NT) run[xr][xt] = fmaxf(m_pred, pm);
         __syncthreads();
 
@@ -511,7 +507,7 @@ __global__ __launch_bounds__(256, 2) void decode_kernel(
             if (4 * ps < R) {
                 const int prow = min(4 * ps + pq, R - 1);
                 float l = lacc[ps] * __builtin_amdgcn_exp2f((mp_prev[ps] - run[prow][NT - 1]) * c);
-                l += __shfl_xor(l, 1); l += __shfl_xor(l, 2); l += __shfl_xor(l, 4); l += __shfl_xor(l, 8);
+                l = lanes_sum<1, 8>(l);
                 if (pj == 0 && 4 * ps + pq < R) lsum_w[wave][4 * ps + pq] = l;
             }
         }
@@ -674,8 +670,7 @@ __global__ __launch_bounds__(256) void decode_scores_kernel(
         mx = max_nc(max_nc(mx, max_nc(acc[0], acc[1])), max_nc(acc[2], acc[3]));
         if (cc < R) *reinterpret_cast<floatx4*>(S + tile * (R * 64) + cc * 64 + 16 * blk + 4 * g) = acc;
     }
-    mx = fmaxf(mx, __shfl_xor(mx, 16));
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    mx = lanes_max<16, 32>(mx);
     if (g == 0) tmax[tile * kDecRows + cc] = mx;
 }
 
@@ -726,10 +721,7 @@ __global__ __launch_bounds__(256) void decode_values_kernel(
         for (int k = 0; k < 4; ++k) fm[k] = fmaxf(fm[k], v[k]);
     }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-#pragma unroll
-        for (int dd = 4; dd < 64; dd <<= 1) fm[k] = fmaxf(fm[k], __shfl_xor(fm[k], dd));
-    }
+    for (int k = 0; k < 4; ++k) fm[k] = lanes_max<4, 32>(fm[k]);
     if (lane < 4) *reinterpret_cast<floatx4*>(&front[wave][4 * lane]) = fm;
     __syncthreads();
     auto in_front = [&](int r) __attribute__((always_inline)) { return fmaxf(fmaxf(front[0][r], front[1][r]), fmaxf(front[2][r], front[3][r])); };
@@ -762,7 +754,7 @@ __global__ __launch_bounds__(256) void decode_values_kernel(
                 *reinterpret_cast<uint2v*>(pfw + (4 * ps + pq) * PS + 8 * pj) = w;
             }
             float l = lacc * __builtin_amdgcn_exp2f((mrow - mrow_end) * c);
-            l += __shfl_xor(l, 1); l += __shfl_xor(l, 2); l += __shfl_xor(l, 4); l += __shfl_xor(l, 8);
+            l = lanes_sum<1, 8>(l);
             if (pj == 0 && 4 * ps + pq < R) lsum_w[wave][4 * ps + pq] = l;
         }
     }

@@ -141,8 +141,7 @@ __device__ __forceinline__ void mx_v_tile(uint16_t (*tile)[D + 2], const MxGroup
                 const float lo = __uint_as_float(a[j] << 16), hi = __uint_as_float(a[j] & 0xFFFF0000u);
                 acc = fmaf(lo, lo, fmaf(hi, hi, acc));
             }
-#pragma unroll
-            for (int w = CH / 2; w >= 1; w >>= 1) acc += __shfl_xor(acc, w);
+            acc = lanes_sum<CH / 2, 1>(acc);
             n2 = fmaxf(n2, acc);
             *reinterpret_cast<uint4v*>(g.v_out + ((size_t)bh * Lp + l0 + row) * D + 8 * c) = a;
         }

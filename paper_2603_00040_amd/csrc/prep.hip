@@ -159,8 +159,8 @@ __device__ __forceinline__ void prep_tile_d(
                 // four neighbouring blocks of a row (four neighbouring lanes: nb is 4 or 8 and a wave starts at a multiple
                 // of 64 blocks) write their scale bytes as one dword; rows beyond L take part in the exchange and write nothing
                 uint32_t sb = e4m3_byte_of(s);
-                sb |= (uint32_t)__shfl_down((int)sb, 1) << 8;
-                sb |= (uint32_t)__shfl_down((int)sb, 2) << 16;
+                sb |= lane_down<1>(sb) << 8;
+                sb |= lane_down<2>(sb) << 16;
                 if (l < L && (cb & 3) == 0) *reinterpret_cast<uint32_t*>(scales + ((size_t)bh * L + l) * nb + cb) = sb;
             }
         } else {
@@ -172,8 +172,7 @@ __device__ __forceinline__ void prep_tile_d(
             float acc = 0.0f;
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc = fmaf(xf[i], xf[i], acc);
-#pragma unroll
-            for (int w = nb / 2; w >= 1; w >>= 1) acc += __shfl_xor(acc, w);
+            acc = lanes_sum<nb / 2, 1>(acc);
             n2 = fmaxf(n2, acc);
         }
         if (xf_pub && l < L) {                           // public bf16 copy, un-padded
@@ -362,8 +361,8 @@ __global__ __launch_bounds__(256) void kv_page_write_kernel(
     }
     // the scale bytes of four neighbouring blocks of a row as one dword (rows beyond the page end take part and write nothing)
     uint32_t sb = e4m3_byte_of(s);
-    sb |= (uint32_t)__shfl_down((int)sb, 1) << 8;
-    sb |= (uint32_t)__shfl_down((int)sb, 2) << 16;
+    sb |= lane_down<1>(sb) << 8;
+    sb |= lane_down<2>(sb) << 16;
     unsigned char* part = const_cast<unsigned char*>(nvfp4_page_part(cache, page, num_pages, Hkv, h, D, which));
     if (row >= rows_total || !part) return;
     uint2v c2; c2[0] = clo; c2[1] = chi;

@@ -82,8 +82,7 @@ __device__ __forceinline__ void grad_tile(int bh, int l0, const uint16_t* __rest
                 }
             }
         }
-#pragma unroll
-        for (int w = nb / 2; w >= 1; w >>= 1) { dot8[0] += __shfl_xor(dot8[0], w); dot8[1] += __shfl_xor(dot8[1], w); nrm += __shfl_xor(nrm, w); }
+        dot8[0] = lanes_sum<nb / 2, 1>(dot8[0]); dot8[1] = lanes_sum<nb / 2, 1>(dot8[1]); nrm = lanes_sum<nb / 2, 1>(nrm);
         const float dot = dot8[0] + dot8[1];
         if (cb == 0) rowstat[(size_t)bh * Lp + l] = make_float2(l < L ? lse_[it] * 1.4426950408889634f : 0.0f, dot);
         n2 = fmaxf(n2, nrm);
@@ -97,8 +96,7 @@ __device__ __forceinline__ void grad_tile(int bh, int l0, const uint16_t* __rest
 
 // Largest value of a workgroup; every thread gets it.  (The barriers also keep `red` from being overwritten too early.)
 __device__ inline float wg_max(float v, float (&red)[4]) {
-#pragma unroll
-    for (int w = 32; w >= 1; w >>= 1) v = fmaxf(v, __shfl_xor(v, w));
+    v = lanes_max<32, 1>(v);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
