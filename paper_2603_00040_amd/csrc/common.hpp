@@ -60,17 +60,6 @@ __device__ inline float rne_e2m1_grid(float r) {
     float c = __uint_as_float(e + 0x0B400000u);            // 1.5 * 2^(e+22)
     return (r + c) - c;
 }
-// E4M3 byte of a value already on the E4M3 grid (0 <= s <= 448).
-__device__ inline uint32_t e4m3_byte_of(float s) {
-    uint32_t u = __float_as_uint(s);
-    if (s < 0.015625f) return (uint32_t)(s * 512.0f);      // subnormal: m * 2^-9
-    return (((u >> 23) - 120u) << 3) | ((u >> 20) & 7u);
-}
-// E2M1 magnitude index (0..7) of a value already on the E2M1 grid.
-__device__ inline uint32_t e2m1_index_of(float q) {
-    return q < 1.0f ? (uint32_t)(q * 2.0f) : (__float_as_uint(q) >> 22) - 252u;
-}
-
 // Block scale of Eq. 1, exact: RNE_E4M3(amax/6) saturating at 448.  amax/6 is an IEEE
 // (correctly rounded) division; for bf16 amax no quotient lies within 2^-13 (relative)
 // of an E4M3 rounding boundary without being on it, so rounding the fp32 quotient

@@ -107,11 +107,11 @@ __device__ inline uint2v phi_p_quad(const float (&pt)[4]) {
 
 // A block of 16 values of a query row, quantized and back, as fp16 (zeros for a row that does not exist).
 __device__ inline void phi_q_block(const uint16_t* q, bool exists, uint4v (&o)[2]) {
-    float v[16], xf[16], s = 0.0f;
-    uint32_t clo = 0, chi = 0;
+    Nv16 blk = nv16_of(0u, 0u, 0u);
     if (exists) {
         const uint4v* src = reinterpret_cast<const uint4v*>(q);
         const uint4v a = src[0], b = src[1];
+        float v[16];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             v[2 * i]         = __uint_as_float(a[i] << 16);
@@ -119,11 +119,12 @@ __device__ inline void phi_q_block(const uint16_t* q, bool exists, uint4v (&o)[2
             v[8 + 2 * i]     = __uint_as_float(b[i] << 16);
             v[8 + 2 * i + 1] = __uint_as_float(b[i] & 0xFFFF0000u);
         }
-        phi_block16_bf16(v, s, clo, chi);
+        blk = phi_block16_bf16(v);
     }
-    dequant_block16(clo, chi, s, xf);
+    uint32_t w[8];
+    dequant_block16_f16(blk, w);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) o[i >> 2][i & 3] = pack_f16x2(xf[2 * i], xf[2 * i + 1]);
+    for (int i = 0; i < 8; ++i) o[i >> 2][i & 3] = w[i];
 }
 
 // Before every step, three things that do not depend on each other, by different workgroups of one launch:

@@ -99,9 +99,9 @@ __device__ __forceinline__ void prep_tile_d(
         __builtin_amdgcn_sched_barrier(0);         // (one block after the other: the registers of two at once would cost wavefronts)
         const int row = row0 + it * (256 / nb), l = l0 + row;
         float v[16];
+        Nv16 q = nv16_of(0u, 0u, 0u);
         if constexpr (PACKED) {
-            // E4M3 byte -> value: the hardware conversion (OCP E4M3, subnormals kept), byte 0 of the operand
-            dequant_block16(cw[it][0], cw[it][1], __builtin_amdgcn_cvt_scalef32_f32_fp8(sw[it], 1.0f, 0), v);
+            q = nv16_of(cw[it][0], cw[it][1], sw[it]);
         } else {
             const uint4v a = xa[it], b = xb[it];
 #pragma unroll
@@ -121,51 +121,48 @@ __device__ __forceinline__ void prep_tile_d(
         }
 
         float xf[16];
-        if (QUANT) {
-            float s;
-            uint32_t clo = 0, chi = 0;
+        bool direct = true;                              // the values are those of q
+        if constexpr (QUANT) {
             if (sub) {
+                direct = false;
                 float amax = 0.0f;
 #pragma unroll
                 for (int i = 0; i < 16; ++i) amax = fmaxf(amax, fabsf(v[i]));
-                s = block_scale_exact(amax);
+                q.s = block_scale_exact(amax);
                 // (inputs with 24 significant bits, after the K smoothing subtraction: IEEE division and the grid rounding
-                //  of common.hpp; the short cut below relies on bf16 inputs)
+                //  of common.hpp; the short cuts of phi_block16_bf16 rely on bf16 inputs)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     const uint32_t sign = __float_as_uint(v[i]) >> 31;
-                    float q = 0.0f;
-                    if (s > 0.0f) {
-                        float r = fabsf(v[i]) / s;
-                        r = r < 6.0f ? r : 6.0f;
-                        q = rne_e2m1_grid(r);
+                    float r = 0.0f;
+                    if (q.s > 0.0f) {
+                        r = fabsf(v[i]) / q.s;
+                        r = rne_e2m1_grid(r < 6.0f ? r : 6.0f);
                     }
-                    const uint32_t code = (sign << 3) | e2m1_index_of(q);
-                    if (i < 8) clo |= code << (4 * i); else chi |= code << (4 * (i - 8));
-                    const float d = q * s;                   // exact: <= 6 significant bits
+                    const float d = r * q.s;                 // exact: <= 6 significant bits
                     xf[i] = sign ? -d : d;
                 }
-            } else {
-                phi_block16_bf16(v, s, clo, chi);
-                dequant_block16(clo, chi, s, xf);
-            }
-            if (l < L) {
-                if (codes) {
-                    uint2v c2; c2[0] = clo; c2[1] = chi;
-                    *reinterpret_cast<uint2v*>(codes + ((size_t)bh * L + l) * (D / 2) + cb * 8) = c2;
-                }
+            } else q = phi_block16_bf16(v);
+            if (l < L && codes) {
+                uint2v c2; c2[0] = q.clo; c2[1] = q.chi;
+                *reinterpret_cast<uint2v*>(codes + ((size_t)bh * L + l) * (D / 2) + cb * 8) = c2;
             }
             if (scales) {
                 // four neighbouring blocks of a row (four neighbouring lanes: nb is 4 or 8 and a wave starts at a multiple
                 // of 64 blocks) write their scale bytes as one dword; rows beyond L take part in the exchange and write nothing
-                uint32_t sb = e4m3_byte_of(s);
+                uint32_t sb = q.sc & 0xFFu;
                 sb |= lane_down<1>(sb) << 8;
                 sb |= lane_down<2>(sb) << 16;
                 if (l < L && (cb & 3) == 0) *reinterpret_cast<uint32_t*>(scales + ((size_t)bh * L + l) * nb + cb) = sb;
             }
-        } else {
+        }
+        // the values as floats where more than the fp16 copy is made of them
+        constexpr bool FLOATS = NORM || !OUT_F16;
+        if constexpr (FLOATS) {
+            if constexpr (QUANT || PACKED) { if (direct) dequant_block16(q, xf); }
+            else
 #pragma unroll
-            for (int i = 0; i < 16; ++i) xf[i] = v[i];
+                for (int i = 0; i < 16; ++i) xf[i] = v[i];
         }
 
         if constexpr (NORM) {                            // |row|^2: nb neighbouring lanes hold a row
@@ -175,21 +172,25 @@ __device__ __forceinline__ void prep_tile_d(
             acc = lanes_sum<nb / 2, 1>(acc);
             n2 = fmaxf(n2, acc);
         }
-        if (xf_pub && l < L) {                           // public bf16 copy, un-padded
-            uint4v o0, o1;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                o0[i] = pack_bf16x2_rne(xf[2 * i], xf[2 * i + 1]);
-                o1[i] = pack_bf16x2_rne(xf[8 + 2 * i], xf[8 + 2 * i + 1]);
-            }
-            uint4v* dst = reinterpret_cast<uint4v*>(xf_pub + in_base + (size_t)l * D + cb * 16);
-            dst[0] = o0; dst[1] = o1;
-        }
-        // workspace copies: fp16 or bf16; both hold s*c exactly
+        // public copy (bf16, un-padded) and workspace copies (fp16 or bf16); both formats hold s*c exactly
         uint32_t w[8];
+        if constexpr (OUT_F16) {
+            static_assert(QUANT || PACKED);
+            if (direct) dequant_block16_f16(q, w);
+            else
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-            w[i] = OUT_F16 ? pack_f16x2(xf[2 * i], xf[2 * i + 1]) : pack_bf16x2_rne(xf[2 * i], xf[2 * i + 1]);
+                for (int i = 0; i < 8; ++i) w[i] = pack_f16x2(xf[2 * i], xf[2 * i + 1]);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) w[i] = pack_bf16x2_cvt(xf[2 * i], xf[2 * i + 1]);
+            if (xf_pub && l < L) {
+                uint4v o0, o1;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) { o0[i] = w[i]; o1[i] = w[4 + i]; }
+                uint4v* dst = reinterpret_cast<uint4v*>(xf_pub + in_base + (size_t)l * D + cb * 16);
+                dst[0] = o0; dst[1] = o1;
+            }
+        }
         if (xr) {                                        // rows padded to Lp with zeros
             uint4v o0, o1;
 #pragma unroll
@@ -344,8 +345,7 @@ __global__ __launch_bounds__(256) void kv_page_write_kernel(
     const int row = blockIdx.x * (256 / nb) + threadIdx.x / nb, cb = threadIdx.x % nb;
     const int pos = pos0 + min(row, rows_total - 1);
     const int page = page_ids[pos >> 7];
-    float s = 0.0f;
-    uint32_t clo = 0, chi = 0;
+    Nv16 q = nv16_of(0u, 0u, 0u);
     if (row < n) {
         const uint4v* src = reinterpret_cast<const uint4v*>(x + (size_t)row * D + cb * 16);
         const uint4v a = src[0], b = src[1];
@@ -357,15 +357,15 @@ __global__ __launch_bounds__(256) void kv_page_write_kernel(
             val[8 + 2 * i]     = __uint_as_float(b[i] << 16);
             val[8 + 2 * i + 1] = __uint_as_float(b[i] & 0xFFFF0000u);
         }
-        phi_block16_bf16(val, s, clo, chi);
+        q = phi_block16_bf16(val);
     }
     // the scale bytes of four neighbouring blocks of a row as one dword (rows beyond the page end take part and write nothing)
-    uint32_t sb = e4m3_byte_of(s);
+    uint32_t sb = q.sc & 0xFFu;
     sb |= lane_down<1>(sb) << 8;
     sb |= lane_down<2>(sb) << 16;
     unsigned char* part = const_cast<unsigned char*>(nvfp4_page_part(cache, page, num_pages, Hkv, h, D, which));
     if (row >= rows_total || !part) return;
-    uint2v c2; c2[0] = clo; c2[1] = chi;
+    uint2v c2; c2[0] = q.clo; c2[1] = q.chi;
     *reinterpret_cast<uint2v*>(part + (size_t)(pos & 127) * (D / 2) + cb * 8) = c2;
     if ((cb & 3) == 0) *reinterpret_cast<uint32_t*>(part + (size_t)128 * (D / 2) + (size_t)(pos & 127) * nb + cb) = sb;
 }
