@@ -820,10 +820,15 @@ static int bwd_common(const void* q, const void* k, const void* v, const void* d
     }
     prof_mark("prep_qkvdo", st);
     BwdPlan plan = bwd_plan(B * Hq, B * Hkv, L, d, causal != 0, device_cu_count());
+    if (plan.splits > 1 && (!w.may_split || workspace_bytes < w.bytes_min + plan.part_bytes)) {
+        plan.splits = 1; plan.iters = (L + 31) / 32 * (Hq / Hkv); plan.dq_first = false;
+    }
+    if (p_quant == 1 && !p_dump && !dkdv_counts_of(st) && bwd_few_rows(B * Hq, B * Hkv, L, causal != 0, plan.splits > 1, device_cu_count())) {
+        if (launch_bwd_few(w.qb, w.kb, w.vb, dob, w.rowstat, w.bounds, B, Hq, Hkv, L, d, causal != 0, dq, dk, dv, st)) return ATTNQAT_ELAUNCH;
+        prof_mark("bwd_joint", st);
+        return ATTNQAT_OK;
+    }
     if (plan.joint && p_quant != 0) {
-        if (plan.splits > 1 && (!w.may_split || workspace_bytes < w.bytes_min + plan.part_bytes)) {
-            plan.splits = 1; plan.iters = (L + 31) / 32 * (Hq / Hkv); plan.dq_first = false;
-        }
         if (launch_bwd_joint(w.qb, w.kb, w.vb, dob, w.rowstat, w.bounds, B, Hq, Hkv, L, d, causal != 0, dq, dk, dv, p_quant, plan, w.part,
                              dkdv_counts_of(st), st, p_dump, dump_row0, mx ? &mxo : nullptr))
             return ATTNQAT_ELAUNCH;

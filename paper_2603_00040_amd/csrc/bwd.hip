@@ -65,6 +65,74 @@ __device__ inline float bound_of(const float* __restrict__ part, int NHq, int wh
     return lanes_max<32, 1>(v);
 }
 
+// ---- what the kernels of both passes share
+// Largest P of group gq (16 keys) in this lane, of its 8 values of them.
+__device__ __forceinline__ float nvfp4_group_max(const floatx16& s, int gq) {
+    const float a0 = fmaxf(fmaxf(s[8 * gq], s[8 * gq + 1]), s[8 * gq + 2]), a1 = fmaxf(fmaxf(s[8 * gq + 3], s[8 * gq + 4]), s[8 * gq + 5]);
+    return fmaxf(fmaxf(a0, a1), fmaxf(s[8 * gq + 6], s[8 * gq + 7]));
+}
+// Is the block scale of a largest P of amax non-zero?  It is RNE_E4M3(amax / 6), which is zero exactly when amax / 6 <= 2^-10 (half of the smallest
+// subnormal, and the tie goes to the even neighbour, zero), and it grows with amax: some block of a tile has a non-zero scale iff some
+// lane's largest P passes this test.
+__device__ __forceinline__ bool nvfp4_scale_nonzero(float amax) { return amax * (1.0f / 6.0f) > 0.0009765625f; }
+// Block scales of phi(P) of the two groups, and their reciprocals.  Each half of the wave forms the scale of one group and hands it to the other, as in
+// the forward (P <= 1: no saturation; a scale of 0 leaves any finite factor).  112 instead of 145 vector instructions beside the products of a
+// tile with P^F, with the maxima of the test above used again and no register cleared for the conversions: 4 x 32/8 heads, L = 4096 causal, where 98 % of
+// the tiles come here, training step 2903 -> 2817 us (the forward's share: 25 us).
+__device__ __forceinline__ void nvfp4_pair_scales(const float (&gmax)[2], float (&sc)[2], float (&inv)[2]) {
+    typedef short short2v __attribute__((ext_vector_type(2)));
+    const float bm = xhalf_max_pair(gmax[0], gmax[1]) * (1.0f / 6.0f);
+    const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(__builtin_bit_cast(short2v, any_register()), bm, bm, 1.0f, false));
+    const float own = __builtin_amdgcn_cvt_scalef32_f32_fp8(w, 1.0f, 0), r = fminf(__builtin_amdgcn_rcpf(own), 512.0f);
+    const auto sb = __builtin_amdgcn_permlane32_swap(__float_as_uint(own), __float_as_uint(own), false, false);
+    const auto ib = __builtin_amdgcn_permlane32_swap(__float_as_uint(r), __float_as_uint(r), false, false);
+#pragma unroll
+    for (int gq = 0; gq < 2; ++gq) { sc[gq] = __uint_as_float(sb[gq]); inv[gq] = __uint_as_float(ib[gq]); }
+}
+// phi^-1(phi(P)) of registers r0 .. r0 + 3 as bf16.
+__device__ __forceinline__ uint2v nvfp4_pf_quad(const floatx16& s, int r0, float sc, float inv) {
+    typedef float float2v __attribute__((ext_vector_type(2)));
+    uint2v w;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const uint32_t codes = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(any_register(), s[r0 + 2 * u] * inv, s[r0 + 2 * u + 1] * inv, 1.0f, 0);
+        const float2v q = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(codes, 1.0f, 0);
+        w[u] = pack_bf16x2(q[0] * sc, q[1] * sc);
+    }
+    return w;
+}
+// The dQ pass: dS of a row goes to fp16 after multiplication by ds_scale = 2^k, k from the bound (|dO_i| max_j |V^F_j| + |D_i|) / sqrt(d) >= |dS_ij|.
+// FOLD: the dO operand of the row is multiplied by 2^k, exactly, so that no rounding depends on the scale of the gradients (in the exponent of P it
+// cost up to 1 % of dQ's error at |dO| = 2^-40); where that would leave the range of bf16 (V^F next to zero, |dO| beyond 2^40), it goes
+// into the exponent (dq_row_exponent), and do_scale is 1.
+template <bool FOLD, int DS>
+__device__ __forceinline__ void dq_row_scale(uint4v (&doreg)[DS], float vmax, float Di, float rs, float& ds_scale, float& do_scale) {
+    float n2 = 0.0f;
+#pragma unroll
+    for (int ds = 0; ds < DS; ++ds)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float lo = bf16_lo_f32(doreg[ds][i]), hi = bf16_hi_f32(doreg[ds][i]);
+            n2 = fmaf(lo, lo, fmaf(hi, hi, n2));
+        }
+    n2 = xhalf_sum(n2);
+    ds_scale = ds_scale_for((sqrtf(n2) * 1.0001f * vmax) * rs + fabsf(Di * rs));
+    do_scale = 1.0f;
+    if constexpr (FOLD) {
+        if (sqrtf(n2) * ds_scale < 1e30f) do_scale = ds_scale;
+#pragma unroll
+        for (int ds = 0; ds < DS; ++ds)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                doreg[ds][i] = __builtin_amdgcn_perm(__float_as_uint(bf16_hi_f32(doreg[ds][i]) * do_scale), __float_as_uint(bf16_lo_f32(doreg[ds][i]) * do_scale), 0x07060302u);
+    }
+}
+// L_i log2(e) - log2(1 / sqrt(d))  (3.5 and 3 are exact), and the part of k that dO does not carry
+template <int D>
+__device__ __forceinline__ float dq_row_exponent(float Llog2e, float ds_scale, float do_scale) {
+    return Llog2e - ((float)((int)(__float_as_uint(ds_scale / do_scale) >> 23) - 127) - (D == 128 ? 3.5f : 3.0f));
+}
+
 static int g_bwd_waves = 0;           // waves per workgroup of the dQ and dK/dV passes, 0: chosen per problem; 4 / 8: forced (tests)
 void set_bwd_waves(int waves) { __atomic_store_n(&g_bwd_waves, waves, __ATOMIC_RELAXED); }
 
@@ -139,40 +207,15 @@ __device__ __forceinline__ void bwd_dq_body(const DqArgs& A, int bh, int qt)
         }
     }
     const float2 st_ = rowstat[(size_t)bh * Lp + q_ld];
-    // dS of this row goes to fp16 after multiplication by ds_scale = 2^k, k from the bound
-    // (|dO_i| max_j |V^F_j| + |D_i|) / sqrt(d) >= |dS_ij|.  FOLD: the dO operand is multiplied by 2^k, -2^k D_i is what the accumulators of
-    // dP start from, and 1 / sqrt(d) goes into the exponent of P, so that dS is one multiplication (32 of 112 vector instructions of a tile, which add to the time of
+    // FOLD (see dq_row_scale): -2^k D_i is what the accumulators of dP start from, and 1 / sqrt(d) goes into the exponent of P, so that dS is one
+    // multiplication (32 of 112 vector instructions of a tile, which add to the time of
     // its 48 products: the same tree otherwise, in turn, 4 x 32/8 heads, L = 4096 causal 2922 -> 2884 us, 40 heads, L = 75600 418.7 ->
     // 416.3 ms, MX 4 x 8/2 heads, L = 3124 759 -> 749 us; MX of d = 128 under a causal mask lost, 2 x 16/4 heads, L = 3001 428.0 -> 429.7 us;
     // d = 64 gains there, 265.8 -> 260.0 us, and without a mask, 2 x 24 heads, L = 3000 633 -> 618 us).
     constexpr bool FOLD = !(MXS && CAUSAL && D == 128);
-    float ds_scale, do_scale = 1.0f;
-    {
-        float n2 = 0.0f;
-#pragma unroll
-        for (int ds = 0; ds < DS; ++ds)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float lo = bf16_lo_f32(doreg[ds][i]), hi = bf16_hi_f32(doreg[ds][i]);
-                n2 = fmaf(lo, lo, fmaf(hi, hi, n2));
-            }
-        n2 = xhalf_sum(n2);
-        const float vmax = bound_of(bound_part, NHq, 0, bhkv);
-        ds_scale = ds_scale_for((sqrtf(n2) * 1.0001f * vmax) * rs + fabsf(st_.y * rs));
-        if constexpr (FOLD) {
-            // 2^k on dO, exactly, so that no rounding depends on the scale of the gradients (in the exponent of P it cost up to 1 % of dQ's
-            // error at |dO| = 2^-40).  Where that would leave the range of bf16 (V^F next to zero, |dO| beyond 2^40), it does go into
-            // the exponent.
-            if (sqrtf(n2) * ds_scale < 1e30f) do_scale = ds_scale;
-#pragma unroll
-            for (int ds = 0; ds < DS; ++ds)
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    doreg[ds][i] = __builtin_amdgcn_perm(__float_as_uint(bf16_hi_f32(doreg[ds][i]) * do_scale), __float_as_uint(bf16_lo_f32(doreg[ds][i]) * do_scale), 0x07060302u);
-        }
-    }
-    // L_i log2(e) - log2(1 / sqrt(d))  (3.5 and 3 are exact), and the part of k that dO does not carry
-    const float Ls = st_.x - (FOLD ? (float)((int)(__float_as_uint(ds_scale / do_scale) >> 23) - 127) - (D == 128 ? 3.5f : 3.0f) : 0.0f);
+    float ds_scale, do_scale;
+    dq_row_scale<FOLD>(doreg, bound_of(bound_part, NHq, 0, bhkv), st_.y, rs, ds_scale, do_scale);
+    const float Ls = FOLD ? dq_row_exponent<D>(st_.x, ds_scale, do_scale) : st_.x;
     const float rs_s = rs * ds_scale, Dq_s = st_.y * rs_s;            // (not FOLD) D_i / sqrt(d), scaled
     floatx16 dp0;                                                    // what dP starts from: -2^k D_i in every register
 #pragma unroll
@@ -748,13 +791,9 @@ __device__ __forceinline__ void bwd_dkdv_body(const DkvArgs& A, int bhkv, int kt
             constexpr bool PQUANT = PQ != 0;
             float sc[2], inv[2], gmax[2] = {0.0f, 0.0f};
             bool nz = false;
-            // the largest P of either group in this lane (chains of v_max3)
             auto group_maxima = [&]() __attribute__((always_inline)) {
 #pragma unroll
-                for (int gq = 0; gq < 2; ++gq) {
-                    const float a0 = fmaxf(fmaxf(s[8 * gq], s[8 * gq + 1]), s[8 * gq + 2]), a1 = fmaxf(fmaxf(s[8 * gq + 3], s[8 * gq + 4]), s[8 * gq + 5]);
-                    gmax[gq] = fmaxf(fmaxf(a0, a1), fmaxf(s[8 * gq + 6], s[8 * gq + 7]));
-                }
+                for (int gq = 0; gq < 2; ++gq) gmax[gq] = nvfp4_group_max(s, gq);
             };
             if constexpr (PQ == 2) {
                 // MX format: this wave's 32 keys are one block with a power-of-two scale
@@ -766,12 +805,9 @@ __device__ __forceinline__ void bwd_dkdv_body(const DkvArgs& A, int bhkv, int kt
                 sc[0] = sc[1] = e8m0_as_f32(byte);
                 nz = amax > 0.0f;
             } else if constexpr (PQ == 1) {
-                // Is any block scale of this tile non-zero?  A scale is RNE_E4M3(amax / 6), which is zero exactly when
-                // amax / 6 <= 2^-10 (half of the smallest subnormal, and the tie goes to the even neighbour, zero), and
-                // it grows with amax: some block has a non-zero scale iff some lane's largest P passes that test.  The
-                // scales themselves are only needed where the answer is yes (below).
+                // Is any block scale of this tile non-zero?  The scales themselves are only needed where the answer is yes (below).
                 group_maxima();
-                nz = fmaxf(gmax[0], gmax[1]) * (1.0f / 6.0f) > 0.0009765625f;
+                nz = nvfp4_scale_nonzero(fmaxf(gmax[0], gmax[1]));
             }
             // Two-level quantization of P (PQ == 3): the row factor belongs to an aligned group of 64 keys, the tile row
             // of the forward, i.e. to this wave's 32 keys and those of its neighbour (waves 0|1 and 2|3 of the
@@ -790,18 +826,7 @@ __device__ __forceinline__ void bwd_dkdv_body(const DkvArgs& A, int bhkv, int kt
             // the row factor of the two-level form)
             auto nvfp4_scales = [&]() __attribute__((always_inline)) {
                 if constexpr (PQ == 1) {
-                    // Each half of the wave forms the scale of one group and hands it to the other, as in the forward (P <= 1: no saturation;
-                    // a scale of 0 leaves any finite factor).  112 instead of 145 vector instructions beside the products of a tile with P^F, with the
-                    // maxima of the test above used again and no register cleared for the conversions: 4 x 32/8 heads, L = 4096 causal, where
-                    // 98 % of the tiles come here, training step 2903 -> 2817 us (the forward's share: 25 us).
-                    typedef short short2v __attribute__((ext_vector_type(2)));
-                    const float bm = xhalf_max_pair(gmax[0], gmax[1]) * (1.0f / 6.0f);
-                    const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(__builtin_bit_cast(short2v, any_register()), bm, bm, 1.0f, false));
-                    const float own = __builtin_amdgcn_cvt_scalef32_f32_fp8(w, 1.0f, 0), r = fminf(__builtin_amdgcn_rcpf(own), 512.0f);
-                    const auto sb = __builtin_amdgcn_permlane32_swap(__float_as_uint(own), __float_as_uint(own), false, false);
-                    const auto ib = __builtin_amdgcn_permlane32_swap(__float_as_uint(r), __float_as_uint(r), false, false);
-#pragma unroll
-                    for (int gq = 0; gq < 2; ++gq) { sc[gq] = __uint_as_float(sb[gq]); inv[gq] = __uint_as_float(ib[gq]); }
+                    nvfp4_pair_scales(gmax, sc, inv);
                     return true;
                 }
                 // Two-level quantization of P (PQ == 3): the row of the aligned 64-key group is divided by s1, the
@@ -837,19 +862,13 @@ __device__ __forceinline__ void bwd_dkdv_body(const DkvArgs& A, int bhkv, int kt
                     for (int t4 = 0; t4 < 4; ++t4) {
                         const int r0 = 4 * t4, gq = t4 >> 1;
                         uint2v wp;
+                        if constexpr (PQ == 2) {      // the conversions divide and multiply by a power of two themselves (117 -> 68 vector instructions)
 #pragma unroll
-                        for (int u = 0; u < 2; ++u) {
-                            const float p0 = s[r0 + 2 * u], p1 = s[r0 + 2 * u + 1];
-                            if constexpr (PQ == 2) {      // the conversions divide and multiply by a power of two themselves (117 -> 68 vector instructions)
-                                const uint32_t codes = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(any_register(), p0, p1, sc[gq], 0);
+                            for (int u = 0; u < 2; ++u) {
+                                const uint32_t codes = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(any_register(), s[r0 + 2 * u], s[r0 + 2 * u + 1], sc[gq], 0);
                                 wp[u] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(codes, sc[gq], 0));
-                            } else {
-                                typedef float float2v __attribute__((ext_vector_type(2)));
-                                const uint32_t codes = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(any_register(), p0 * inv[gq], p1 * inv[gq], 1.0f, 0);
-                                const float2v q = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(codes, 1.0f, 0);
-                                wp[u] = pack_bf16x2(q[0] * sc[gq], q[1] * sc[gq]);
                             }
-                        }
+                        } else wp = nvfp4_pf_quad(s, r0, sc[gq], inv[gq]);
                         lds_write8_at(tw_ad + (uint32_t)(16 * t4), wp);
                         if constexpr (COUNT) {
                             const int qr = q0 + ln;      // registers r0 .. r0 + 3: keys key0_w + 8 t4 + 4 hf + e of query row qr
@@ -1145,6 +1164,388 @@ __global__ __launch_bounds__(256) void dkdv_reduce_kernel(const float* __restric
             const int key = kt * 128 + wave * 32 + 8 * t4 + 4 * hf + e;
             if (key < L) out[((size_t)bhkv * L + key) * D + 32 * (col % NB) + ln] = f32_to_bf16_rne(sum[t4][e]);
         }
+}
+
+// ------------------------------------------------------------------ few rows
+// Both passes for problems that leave most compute units idle (few_rows), NVFP4.  What bounds those is the chain of one workgroup, tile after tile; here a
+// workgroup owns 32 keys (or 32 query rows), its four waves take four query tiles (key tiles) at a time, wave w tile 4 n + w for S, dP, P^F and
+// dS, and then one block of 32 columns of dK and of dV (of dQ) for the products of all four, whose P^F and dS they find in LDS: a chain is a quarter as
+// long, and every sum has the order, so every result the bits, of the kernels above.  Two barriers per four tiles; one workgroup per compute unit,
+// whose waves have the registers of two.  V^F of a dQ tile goes straight to registers: nobody else reads it, and the LDS has no room for two rounds of it.
+// Joint launch -> this, with the preparing launch: d = 64: 2 heads, L = 256 16.3 -> 12.0 us, L = 700 27.4 -> 17.8 us; 4 heads, L = 1000 30.3 -> 21.6 us;
+// 12 heads, L = 200 17.0 -> 13.2 us; one head, L = 2000 58.8 -> 32.4 us; d = 128: 2 heads, L = 700 35.6 -> 23.6 us, 4 heads, L = 1000 38.3 -> 30.4 us, 8 heads,
+// L = 700 causal 35.1 -> 26.2 us.
+template <int D>
+struct FewDkv {
+    uint16_t q[2][4][32 * D];            // Q^F tiles of this round and the next [query][d], fp16, swizzled
+    uint16_t g[2][4][32 * D];            // dO tiles
+    uint16_t t[4][2][kTTileB / 2];       // P^F and dS of the four tiles, as in DkvSmem
+    int pf[4];                           // whether tile t has a non-zero P^F
+};
+template <int D>
+struct FewDq {
+    uint16_t k[2][4][64 * D];            // K^F tiles of this round and the next [key][d], fp16, swizzled
+    uint4v ds[4][4][64];                 // dS of the four tiles as operands of the dQ products: [tile][16 keys][lane]
+};
+
+// What this wave has written to LDS is there, what it has read has arrived, and the other waves have got here too (the copies and loads of the next
+// round stay on their way).
+__device__ __forceinline__ void few_barrier() {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0xC07F);                  // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+template <int D, bool CAUSAL>
+__device__ __forceinline__ void few_dkdv(const DkvArgs& A, int bhkv, int kt /* 32 keys */)
+{
+    constexpr int DS = D / 16, NB = D / 32, KCH = D / 8, NWL = D / 16 /* 1 KiB copies of a tile */;
+    constexpr uint32_t kRowB = 2 * D, kTB = 32 * kRowB, kGB = 8 * kTB;
+    extern __shared__ __align__(256) unsigned char smem_raw[];
+    FewDkv<D>& sm = *reinterpret_cast<FewDkv<D>*>(smem_raw);
+    const int L = A.L, Lp = A.Lp, Hq = A.Hq, G = A.G, Hkv = Hq / G;
+    const int b = bhkv / Hkv, hk = bhkv % Hkv;
+    const int lane = threadIdx.x & 63, ln = lane & 31, hf = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int key0 = kt * 32;
+
+    uint4v kreg[DS], vreg[DS];                           // A operands: row = key, d-slots 16 ds + 8 hf
+    {
+        const size_t off = ((size_t)bhkv * Lp + key0 + ln) * D + 8 * hf;
+#pragma unroll
+        for (int ds = 0; ds < DS; ++ds) {
+            kreg[ds] = *reinterpret_cast<const uint4v*>(A.Kb + off + 16 * ds);
+            vreg[ds] = *reinterpret_cast<const uint4v*>(A.Vb + off + 16 * ds);
+        }
+    }
+    // query tiles of 32 rows, query heads of the group one after another; this wave's in round r is number 4 r + wave
+    const int qt_first = CAUSAL ? kt : 0, per_head = (L + 31) / 32 - qt_first, niter = per_head * G;
+    const size_t bh0 = (size_t)b * Hq + hk * G;
+    auto row_of = [&](int it) __attribute__((always_inline)) { return (bh0 + it / per_head) * Lp + (size_t)(qt_first + it % per_head) * 32; };
+    uint32_t slot_off[NWL];
+#pragma unroll
+    for (int i = 0; i < NWL; ++i) {
+        const int slot = 64 * i + lane;
+        slot_off[i] = 2u * (uint32_t)((slot / KCH) * D + 8 * swz<KCH>(slot / KCH, slot % KCH));
+    }
+    float2 st_n = make_float2(0.0f, 0.0f);
+    auto request = [&](int buf, int it) __attribute__((always_inline)) {
+        if (it >= niter) return;
+        const size_t row0 = row_of(it);
+#pragma unroll
+        for (int i = 0; i < NWL; ++i) {
+            async_copy16(A.Qb + row0 * D, slot_off[i], &sm.q[buf][wave][512 * i]);
+            async_copy16(A.dOb + row0 * D, slot_off[i], &sm.g[buf][wave][512 * i]);
+        }
+        st_n = A.rowstat[row0 + ln];
+    };
+    request(0, wave);
+    // (the factor of dS: as in bwd_dkdv_body)
+    float ds_scale;
+    {
+        const float* p = A.bound_part + (size_t)bhkv * kBoundParts + lane;
+        const float *p1 = A.bound_part + ((size_t)A.NHq + bh0) * kBoundParts + lane, *p2 = p1 + (size_t)A.NHq * kBoundParts;
+        float vmax = *p, domax = 0.0f, dmax = 0.0f;
+        for (int g = 0; g < G; ++g) { domax = fmaxf(domax, p1[(size_t)g * kBoundParts]); dmax = fmaxf(dmax, p2[(size_t)g * kBoundParts]); }
+        vmax = lanes_max<32, 1>(vmax); domax = lanes_max<32, 1>(domax); dmax = lanes_max<32, 1>(dmax);
+        ds_scale = ds_scale_for(domax * vmax * A.rs + dmax);
+    }
+    const float rs_s = A.rs * ds_scale;
+
+    const uint32_t lds0 = lds_addr_of(smem_raw), t0 = lds_addr_of(&sm.t[0][0][0]);
+    const int tr_r = lane & 15, tr_grp = (lane >> 4) & 1;
+    const uint32_t a_rd = lds0 + 2u * (uint32_t)swz_elem<KCH>(ln, 8 * hf) + (uint32_t)wave * kTB;
+    // this wave's block: columns 32 nb .. of dK and dV (d = 64: of dK, waves 0 and 1, or of dV)
+    constexpr bool BOTH = NB == 4;
+    const int nb = BOTH ? wave : wave & 1;
+    const bool do_k = BOTH || wave < 2, do_v = BOTH || wave >= 2;
+    uint32_t g_rd[2];
+#pragma unroll
+    for (int v = 0; v < 2; ++v) g_rd[v] = (lds0 + 2u * (uint32_t)swz_elem<KCH>(8 * hf + (tr_r >> 2) + 4 * v, 16 * tr_grp + 4 * (tr_r & 3))) ^ (uint32_t)(nb << 6);
+    const uint32_t tw_ad = t0 + (uint32_t)(wave * 2 * kTTileB + kTGroupB * (ln >> 2) + 64 * (ln & 3) + 8 * (hf ^ ((ln >> 1) & 1)));
+    const uint32_t ta_ad = t0 + (uint32_t)(kTGroupB * (2 * hf) + 64 * (tr_r >> 2) + 32 * tr_grp + 8 * ((tr_r & 3) ^ ((tr_r >> 3) & 1)));
+    floatx16 dk, dv;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) { dk[i] = 0.0f; dv[i] = 0.0f; }
+#pragma unroll
+    for (int ds = 0; ds < DS; ++ds) asm volatile("" : "+v"(kreg[ds]), "+v"(vreg[ds]));
+    asm volatile("" : "+v"(st_n.x), "+v"(st_n.y));
+    __builtin_amdgcn_s_waitcnt(0);
+
+    for (int r0 = 0, buf = 0; r0 < niter; r0 += 4, buf ^= 1) {
+        const int it = r0 + wave, nt = min(niter - r0, 4);
+        const float Ls = st_n.x, Dq_s = st_n.y * rs_s;
+        request(buf ^ 1, it + 4);
+        if (it < niter) {
+            const int q0 = (qt_first + it % per_head) * 32;
+            const uint32_t a_it = a_rd + (uint32_t)buf * (4 * kTB);
+            uint4v qo[DS], go[DS];
+#pragma unroll
+            for (int ds = 0; ds < DS; ++ds) { qo[ds] = lds_read16_at(a_it ^ (uint32_t)(ds << 5)); go[ds] = lds_read16_at((a_it ^ (uint32_t)(ds << 5)) + kGB); }
+            floatx16 s, dp;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) { s[i] = 0.0f; dp[i] = 0.0f; }
+#pragma unroll
+            for (int ds = 0; ds < DS; ++ds) { s = mfma_f16(kreg[ds], qo[ds], s); dp = mfma_bf16(vreg[ds], go[ds], dp); }
+            if ((key0 + 32 > L) || (CAUSAL && key0 + 31 > q0)) {
+                const int klim = CAUSAL ? min(L - 1, q0 + ln) : L - 1;
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    if (key0 + 8 * (i >> 2) + 4 * hf + (i & 3) > klim) s[i] = -INFINITY;
+            }
+#pragma unroll
+            for (int i = 0; i < 16; ++i) s[i] = __builtin_amdgcn_exp2f(fmaf(s[i], A.c, -Ls));    // P = exp(S - L_i)
+            float gmax[2];
+#pragma unroll
+            for (int gq = 0; gq < 2; ++gq) gmax[gq] = nvfp4_group_max(s, gq);
+            const bool with_pf = __builtin_amdgcn_ballot_w64(nvfp4_scale_nonzero(fmaxf(gmax[0], gmax[1]))) != 0;
+            if (lane == 0) sm.pf[wave] = with_pf;
+            if (with_pf) {
+                float sc[2], inv[2];
+                nvfp4_pair_scales(gmax, sc, inv);
+#pragma unroll
+                for (int t4 = 0; t4 < 4; ++t4) lds_write8_at(tw_ad + (uint32_t)(16 * t4), nvfp4_pf_quad(s, 4 * t4, sc[t4 >> 1], inv[t4 >> 1]));
+            }
+#pragma unroll
+            for (int t4 = 0; t4 < 4; ++t4) {
+                float dsv[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) dsv[e] = s[4 * t4 + e] * fmaf(dp[4 * t4 + e], rs_s, -Dq_s);
+                uint2v wh;
+                wh[0] = pack_f16x2(dsv[0], dsv[1]); wh[1] = pack_f16x2(dsv[2], dsv[3]);
+                lds_write8_at(tw_ad + (uint32_t)(kTTileB + 16 * t4), wh);
+            }
+        }
+        few_barrier();
+        // dK += dS^T Q^F, dV += P^F^T dO, tile after tile (contraction slots as in bwd_dkdv_body)
+        auto product = [&](int t, uint32_t staged, uint32_t rows, int ks, uint4v& a, uint4v& bq) __attribute__((always_inline)) {
+            const uint32_t ta = ta_ad + (uint32_t)(t * 2 * kTTileB) + staged + (uint32_t)(ks * (4 * kTGroupB)), o = (uint32_t)((buf * 4 + t) * kTB) + rows + (uint32_t)(ks * 16 * kRowB);
+            a = join(lds_read_tr16_at(ta), lds_read_tr16_at(ta + kTGroupB));
+            bq = join(lds_read_tr16_at(g_rd[0] + o), lds_read_tr16_at(g_rd[1] + o));
+        };
+        auto tiles = [&](auto full) __attribute__((always_inline)) {
+            constexpr bool FULL = decltype(full)::value;
+            uint4v a[4][2], bq[4][2];
+            if (do_k) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    if (FULL || t < nt)
+#pragma unroll
+                        for (int ks = 0; ks < 2; ++ks) product(t, kTTileB, 0u, ks, a[t][ks], bq[t][ks]);
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    if (FULL || t < nt)
+#pragma unroll
+                        for (int ks = 0; ks < 2; ++ks) dk = mfma_f16(a[t][ks], bq[t][ks], dk);
+            }
+            if (do_v) {
+                int pf[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) pf[t] = __builtin_amdgcn_readfirstlane(sm.pf[t]);
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    if ((FULL || t < nt) && pf[t])
+#pragma unroll
+                        for (int ks = 0; ks < 2; ++ks) product(t, 0u, kGB, ks, a[t][ks], bq[t][ks]);
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    if ((FULL || t < nt) && pf[t])
+#pragma unroll
+                        for (int ks = 0; ks < 2; ++ks) dv = mfma_bf16(a[t][ks], bq[t][ks], dv);
+            }
+        };
+        if (nt == 4) tiles(std::true_type{}); else tiles(std::false_type{});
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0);                   // this wave's tile of the next round is in LDS
+        few_barrier();
+        asm volatile("" : "+v"(st_n.x), "+v"(st_n.y));
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int key = key0 + 8 * (i >> 2) + 4 * hf + (i & 3);
+        if (key < L) {
+            const size_t o = ((size_t)bhkv * L + key) * D + 32 * nb + ln;
+            if (do_k) A.dK[o] = f32_to_bf16_rne(dk[i] * (A.rs / rs_s));          // / ds_scale, exact: a power of two
+            if (do_v) A.dV[o] = f32_to_bf16_rne(dv[i]);
+        }
+    }
+}
+
+template <int D, bool CAUSAL>
+__device__ __forceinline__ void few_dq(const DqArgs& A, int bh, int qt /* 32 rows */)
+{
+    constexpr int DS = D / 16, MB = D / 32, KCH = D / 8, KLD = D / 8 /* 1 KiB copies of a tile */;
+    constexpr uint32_t kTB = 64 * D * 2;
+    extern __shared__ __align__(256) unsigned char smem_raw[];
+    FewDq<D>& sm = *reinterpret_cast<FewDq<D>*>(smem_raw);
+    const int L = A.L, Lp = A.Lp, Hq = A.Hq, G = A.G;
+    const int b = bh / Hq, h = bh % Hq, bhkv = b * (Hq / G) + h / G;
+    const int lane = threadIdx.x & 63, ln = lane & 31, hf = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int row0 = qt * 32, q_row = row0 + ln;
+    const int nkt_all = (L + 63) / 64, nkt = CAUSAL ? min((row0 + 31) / 64 + 1, nkt_all) : nkt_all;
+
+    const uint16_t* k_head = A.Kb + (size_t)bhkv * Lp * D;
+    const uint16_t* v_lane = A.Vb + ((size_t)bhkv * Lp + ln) * D + 8 * hf;
+    uint32_t k_ld[KLD];
+#pragma unroll
+    for (int i = 0; i < KLD; ++i) {
+        const int slot = 64 * i + lane, r = slot / KCH, pc = slot % KCH;
+        k_ld[i] = 2u * (uint32_t)(r * D + 8 * swz<KCH>(r, pc));
+    }
+    uint4v vn[2][DS];                                    // V^F rows of this wave's next tile: nobody else reads them
+    auto request = [&](int buf, int j) __attribute__((always_inline)) {
+        if (j >= nkt) return;
+#pragma unroll
+        for (int i = 0; i < KLD; ++i) async_copy16(k_head + (size_t)j * (64 * D), k_ld[i], &sm.k[buf][wave][512 * i]);
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+            for (int ds = 0; ds < DS; ++ds) vn[kb][ds] = *reinterpret_cast<const uint4v*>(v_lane + (size_t)(j * 64 + 32 * kb) * D + 16 * ds);
+    };
+    uint4v qreg[DS], doreg[DS];
+    {
+        const size_t off = ((size_t)bh * Lp + q_row) * D + 8 * hf;
+#pragma unroll
+        for (int ds = 0; ds < DS; ++ds) {
+            qreg[ds] = *reinterpret_cast<const uint4v*>(A.Qb + off + 16 * ds);
+            doreg[ds] = *reinterpret_cast<const uint4v*>(A.dOb + off + 16 * ds);
+        }
+    }
+    const float2 st_ = A.rowstat[(size_t)bh * Lp + q_row];
+    const float vmax_part = A.bound_part[(size_t)bhkv * kBoundParts + lane];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int ds = 0; ds < DS; ++ds) vn[kb][ds] = uint4v{0u, 0u, 0u, 0u};
+    request(0, wave);
+    float ds_scale, do_scale;
+    dq_row_scale<true>(doreg, lanes_max<32, 1>(vmax_part), st_.y, A.rs, ds_scale, do_scale);
+    const float Ls = dq_row_exponent<D>(st_.x, ds_scale, do_scale);
+    floatx16 dp0, acc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) { dp0[i] = -st_.y * do_scale; acc[i] = 0.0f; }
+
+    const uint32_t lds0 = lds_addr_of(smem_raw), ds0 = lds_addr_of(&sm.ds[0][0][0]);
+    const int tr_r = lane & 15, tr_grp = (lane >> 4) & 1;
+    const int mb = wave & (MB - 1);
+    const bool do_q = wave < MB;                         // d = 64: two blocks of dQ
+    uint32_t koff[DS], toff[2];
+#pragma unroll
+    for (int ds = 0; ds < DS; ++ds) koff[ds] = lds0 + (uint32_t)wave * kTB + 2u * (uint32_t)((ln * KCH + swz<KCH>(ln, 2 * ds + hf)) * 8);
+#pragma unroll
+    for (int v = 0; v < 2; ++v) toff[v] = lds0 + 2u * (uint32_t)swz_elem<KCH>(4 * hf + (tr_r >> 2) + 8 * v, 32 * mb + 16 * tr_grp + 4 * (tr_r & 3));
+    __builtin_amdgcn_s_waitcnt(0);
+
+    for (int j0 = 0, buf = 0; j0 < nkt; j0 += 4, buf ^= 1) {
+        const int j = j0 + wave, nt = min(nkt - j0, 4);
+        uint4v vc[2][DS];
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+            for (int ds = 0; ds < DS; ++ds) vc[kb][ds] = vn[kb][ds];
+        request(buf ^ 1, j + 4);
+        if (j < nkt) {
+            const int k0 = j * 64;
+            floatx16 s[2], dp[2];
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) s[kb][i] = 0.0f;
+#pragma unroll
+            for (int ds = 0; ds < DS; ++ds)
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb) {
+                    s[kb] = mfma_f16(lds_read16_at(koff[ds] + (uint32_t)buf * (4 * kTB) + (uint32_t)(kb * 32 * D * 2)), qreg[ds], s[kb]);
+                    dp[kb] = mfma_bf16(vc[kb][ds], doreg[ds], ds == 0 ? dp0 : dp[kb]);
+                }
+            if ((k0 + 64 > L) || (CAUSAL && k0 + 63 > row0)) {
+                const int klim = CAUSAL ? min(L - 1, q_row) : L - 1;
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i)
+                        if (k0 + 32 * kb + 8 * (i >> 2) + 4 * hf + (i & 3) > klim) s[kb][i] = -INFINITY;
+            }
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                uint4v bds;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int kb = ks >> 1, r = 8 * (ks & 1) + 2 * i;
+                    const float p0 = __builtin_amdgcn_exp2f(fmaf(s[kb][r], A.c, -Ls)), p1 = __builtin_amdgcn_exp2f(fmaf(s[kb][r + 1], A.c, -Ls));
+                    bds[i] = pack_f16x2(p0 * dp[kb][r], p1 * dp[kb][r + 1]);
+                }
+                lds_write16_at(ds0 + (uint32_t)((wave * 4 + ks) * 1024 + 16 * lane), bds);
+            }
+        }
+        few_barrier();
+        if (do_q) {
+            auto tiles = [&](auto full) __attribute__((always_inline)) {
+                constexpr bool FULL = decltype(full)::value;
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    if (FULL || t < nt)
+#pragma unroll
+                        for (int ks = 0; ks < 4; ++ks) {
+                            const uint32_t o = (uint32_t)((buf * 4 + t) * kTB) + (uint32_t)(ks * 16 * D * 2);
+                            const uint4v at = join(lds_read_tr16_at(toff[0] + o), lds_read_tr16_at(toff[1] + o));
+                            acc = mfma_f16(at, lds_read16_at(ds0 + (uint32_t)((t * 4 + ks) * 1024 + 16 * lane)), acc);
+                        }
+            };
+            if (nt == 4) tiles(std::true_type{}); else tiles(std::false_type{});
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0);                   // this wave's tile of the next round is in LDS
+        few_barrier();
+    }
+    if (q_row < L && do_q) {
+        const float un = 1.0f / ds_scale;                // exact: a power of two
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            uint2v w;
+            w[0] = pack_bf16x2(acc[4 * t] * un, acc[4 * t + 1] * un);
+            w[1] = pack_bf16x2(acc[4 * t + 2] * un, acc[4 * t + 3] * un);
+            *reinterpret_cast<uint2v*>(A.dQ + ((size_t)bh * L + q_row) * D + 32 * mb + 8 * t + 4 * hf) = w;
+        }
+    }
+}
+
+template <int D, bool CAUSAL>
+__global__ __launch_bounds__(256, 1) void bwd_few_kernel(DqArgs Q, DkvArgs K)
+{
+    const int n32 = (K.L + 31) / 32, n_dkdv = K.NHkv * n32;
+    int block = blockIdx.x;                              // (under a causal mask the longest first)
+    if (block < n_dkdv) few_dkdv<D, CAUSAL>(K, block % K.NHkv, block / K.NHkv);
+    else {
+        block -= n_dkdv;
+        few_dq<D, CAUSAL>(Q, block % Q.NHq, CAUSAL ? n32 - 1 - block / Q.NHq : block / Q.NHq);
+    }
+}
+
+bool bwd_few_rows(int BHq, int BHkv, int L, bool causal, bool pieces, int cus)
+{
+    if (__atomic_load_n(&g_bwd_waves, __ATOMIC_RELAXED) != 0) return false;      // (a test forces separate passes)
+    return few_rows(BHq, BHkv, L, causal, pieces, cus);
+}
+
+int launch_bwd_few(const void* qb, const void* kb, const void* vb, const void* dob, const float* rowstat, const float* bound_part,
+                   int B, int Hq, int Hkv, int L, int D, bool causal, void* dq, void* dk, void* dv, hipStream_t st)
+{
+    const DqArgs Q = dq_args(qb, kb, vb, dob, rowstat, bound_part, B, Hq, Hkv, L, D, dq, nullptr);
+    const DkvArgs K = dkv_args(qb, kb, vb, dob, rowstat, bound_part, B, Hq, Hkv, L, D, dk, dv, nullptr);
+    auto go = [&](auto kern, size_t smem, unsigned long long& lds_set) -> int {
+        if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)smem, lds_set)) return -1;
+        hipLaunchKernelGGL(kern, dim3((unsigned)((Q.NHq + K.NHkv) * ((L + 31) / 32))), dim3(256), smem, st, Q, K);
+        return hipGetLastError() == hipSuccess ? 0 : -1;
+    };
+    static unsigned long long lds_set[4] = {0, 0, 0, 0};      // one per instantiation
+#define AQ_FEW(DD, C, I) go(bwd_few_kernel<DD, C>, sizeof(FewDkv<DD>) > sizeof(FewDq<DD>) ? sizeof(FewDkv<DD>) : sizeof(FewDq<DD>), lds_set[I])
+    if (D == 128) return causal ? AQ_FEW(128, true, 0) : AQ_FEW(128, false, 1);
+    if (D == 64)  return causal ? AQ_FEW(64, true, 2) : AQ_FEW(64, false, 3);
+#undef AQ_FEW
+    return -1;
 }
 
 BwdPlan bwd_plan(int BHq, int BHkv, int L, int D, bool causal, int cus)

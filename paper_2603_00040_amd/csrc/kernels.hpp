@@ -108,6 +108,11 @@ int launch_bwd_joint(const void* qb, const void* kb, const void* vb, const void*
                      int B, int Hq, int Hkv, int L, int D, bool causal, void* dq, void* dk, void* dv, int p_quant /* 1, 2 or 3 */,
                      const BwdPlan& plan, float* part, unsigned long long* tile_counts, hipStream_t st, float* p_dump, int dump_row0,
                      const MxScoreOps* mx);
+// Both passes of an NVFP4 backward of few rows, with the bits of the others where those share no key tile among workgroups (few_rows in plan.hpp; never
+// while set_bwd_waves forces separate passes).
+bool bwd_few_rows(int BHq, int BHkv, int L, bool causal, bool pieces, int cus);
+int launch_bwd_few(const void* qb, const void* kb, const void* vb, const void* dob, const float* rowstat, const float* bound_part,
+                   int B, int Hq, int Hkv, int L, int D, bool causal, void* dq, void* dk, void* dv, hipStream_t st);
 // Waves per workgroup of the dQ and dK/dV passes: 0 = chosen per problem (the default), 4 or 8 = forced where that
 // variant exists (8: not the ablation and not the counting variant).  Process-wide; for tests.
 void set_bwd_waves(int waves);

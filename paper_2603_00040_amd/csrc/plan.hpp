@@ -81,4 +81,17 @@ inline bool joint_in_pairs(const BwdPlan& p, int BHq, int BHkv, int L, int D, bo
     return causal ? L >= 2048 && tiles * 10 <= (long long)cus * 23 : BHq > BHkv && tiles * 2 <= (long long)cus * 3;
 }
 
+// Whether the four waves of a workgroup share the tiles of 32 rows in a backward (bwd_few_kernel): up to one such group of keys or of queries per compute unit, and up to
+// two under a causal mask, where most chains are short, with rows of more than four tiles.  With several query heads to a kv head a group of keys has all their
+// query tiles in one chain, and the joint launch is the faster one where it may cut key tiles into pieces.  Measured over 420 shapes (L = 33 - 4000, 1 - 40 kv
+// heads, 1 - 8 query heads to each, 4 - 900 groups): 7 - 90 % faster in all 288 that this rule takes but one (40 heads, L = 98, d = 128 causal, 5 % slower, which the four tiles
+// leave out); beyond: no mask, 2 heads, L = 2411, d = 64, 304 groups 6 % slower, 6 heads, L = 1316, d = 128, 504 groups 17 %; causal, 4 heads, L = 2688, 672
+// groups 9 %; with pieces, 8/2 heads, L = 582 causal, 190 groups 1.6 times slower, 6/3 heads, L = 575 causal, 162 groups 10 %.
+inline bool few_rows(int BHq, int BHkv, int L, bool causal, bool pieces /* the joint launch would cut key tiles */, int cus)
+{
+    const int n32 = (L + 31) / 32;
+    if (BHq != BHkv && pieces) return false;
+    return (long long)(BHq + BHkv) * n32 <= (long long)cus * (causal && BHq == BHkv && n32 > 4 ? 2 : 1);
+}
+
 }  // namespace aq
