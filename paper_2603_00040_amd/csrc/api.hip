@@ -228,23 +228,25 @@ int fwd_common(const void* q, const void* k, const void* v, int B, int Hq, int H
     if (!workspace || workspace_bytes < w.bytes) return ATTNQAT_EWORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     prof_begin(st);
+    // (the attention kernel quantizes Q, from a copy where a result lies over it)
+    if (!q_unwritten(q, B, Hq, L, d, o, lse, train ? o_hp : nullptr)) {
+        if (hipMemcpyAsync(w.qh, q, (size_t)B * Hq * L * d * 2, hipMemcpyDeviceToDevice, st) != hipSuccess) return ATTNQAT_ELAUNCH;
+        q = w.qh;
+    }
     if (mx) {
-        // K as operands of the scaled FP4 instruction (the scores are computed from the codes), V^F^T as the fp16 copy; the attention kernel
-        // quantizes Q, from a copy where a result lies over it
-        const bool direct = q_unwritten(q, B, Hq, L, d, o, lse, train ? o_hp : nullptr);
-        if (!direct && hipMemcpyAsync(w.qh, q, (size_t)B * Hq * L * d * 2, hipMemcpyDeviceToDevice, st) != hipSuccess) return ATTNQAT_ELAUNCH;
+        // K as operands of the scaled FP4 instruction (the scores are computed from the codes), V^F^T as the fp16 copy
         MxGroup g = mx_group_of(nullptr, k, v, B * Hq, B * Hkv, L);
         g.krec = (unsigned char*)w.kh; g.v_out = (uint16_t*)w.vt;
         if (launch_mx_group(g, MX_TRAIN, d, st)) return ATTNQAT_ELAUNCH;
         prof_mark("prep_qkv", st);
-        if (launch_fwd(direct ? q : w.qh, w.kh, w.vt, B, Hq, Hkv, L, d, causal != 0, train, 1, o, lse, o_hp, dump_row0, p_dump, st))
+        if (launch_fwd(q, w.kh, w.vt, B, Hq, Hkv, L, d, causal != 0, train, 1, o, lse, o_hp, dump_row0, p_dump, st))
             return ATTNQAT_ELAUNCH;
         prof_mark(train ? "fwd_train" : "fwd_infer", st);
         return ATTNQAT_OK;
     }
     PrepGroup g = group_of(B, Hq, Hkv, L, d);
-    g.q = (const uint16_t*)q; g.k = (const uint16_t*)k; g.v = (const uint16_t*)v;
-    g.q_out = (uint16_t*)w.qh; g.k_out = (uint16_t*)w.kh; g.v_out = (uint16_t*)w.vt;
+    g.k = (const uint16_t*)k; g.v = (const uint16_t*)v;
+    g.k_out = (uint16_t*)w.kh; g.v_out = (uint16_t*)w.vt;
     g.v_quant = !bf16pv;                           // Sec. 2.5, NVFP4 Q K^T with BF16 P V: V only changes layout
     if (options & ATTNQAT_OPT_SMOOTH_K) {          // K minus its token mean (Sec. 2.1), then phi
         if (launch_colmean(k, B * Hkv, L, d, w.kpart, w.kmean, st)) return ATTNQAT_ELAUNCH;
@@ -253,7 +255,7 @@ int fwd_common(const void* q, const void* k, const void* v, int B, int Hq, int H
     if (launch_prep_group(g, st)) return ATTNQAT_ELAUNCH;
     prof_mark("prep_qkv", st);
     const int p_quant = bf16pv ? 3 : (options & ATTNQAT_OPT_TWO_LEVEL_P) ? 2 : 0;
-    if (launch_fwd(w.qh, w.kh, w.vt, B, Hq, Hkv, L, d, causal != 0, train, p_quant, o, lse, o_hp, dump_row0, p_dump, st))
+    if (launch_fwd(q, w.kh, w.vt, B, Hq, Hkv, L, d, causal != 0, train, p_quant, o, lse, o_hp, dump_row0, p_dump, st))
         return ATTNQAT_ELAUNCH;
     prof_mark(train ? "fwd_train" : "fwd_infer", st);
     return ATTNQAT_OK;
@@ -552,15 +554,19 @@ int paged_common(const void* q, int B, int Hq, int Hkv, int Lq, int d, int causa
         return ATTNQAT_OK;
     }
     if (dec_ws) *dec_ws = nullptr;
-    // phi(Q); K^F and V^F are in the cache already and only change layout
+    // (as in fwd_common)
+    if (!q_unwritten(q, B, Hq, Lq, d, o, lse, nullptr)) {
+        if (hipMemcpyAsync(w.qh, q, (size_t)B * Hq * Lq * d * 2, hipMemcpyDeviceToDevice, st) != hipSuccess) return ATTNQAT_ELAUNCH;
+        q = w.qh;
+    }
+    // K^F and V^F are in the cache already and only change layout
     PrepGroup g = group_of(B, Hq, Hkv, Lq, d);
-    g.q = (const uint16_t*)q;
     g.ps = PagedSrc{(const unsigned char*)cache, page_table, kv_lens, max_pages, num_pages, Hkv, 0};
     g.L_kv = max_pages * 128; g.Lp_kv = w.Lkp;
-    g.q_out = (uint16_t*)w.qh; g.k_out = (uint16_t*)w.kh; g.v_out = (uint16_t*)w.vt;
+    g.k_out = (uint16_t*)w.kh; g.v_out = (uint16_t*)w.vt;
     if (launch_prep_group(g, st)) return ATTNQAT_ELAUNCH;
     prof_mark("prep_q_unpack_pages", st);
-    if (launch_fwd_varlen(w.qh, w.kh, w.vt, B, Hq, Hkv, Lq, w.Lkp, d, causal != 0, kv_lens, o, lse, st)) return ATTNQAT_ELAUNCH;
+    if (launch_fwd_varlen(q, w.kh, w.vt, B, Hq, Hkv, Lq, w.Lkp, d, causal != 0, kv_lens, o, lse, st)) return ATTNQAT_ELAUNCH;
     prof_mark("fwd_infer_paged", st);
     return ATTNQAT_OK;
 }
@@ -697,7 +703,7 @@ int attnqat_fwd_infer_packed(const uint8_t* q_codes, const uint8_t* q_scales, co
     g.q_out = (uint16_t*)w.qh; g.k_out = (uint16_t*)w.kh; g.v_out = (uint16_t*)w.vt;
     if (launch_prep_group(g, st)) return ATTNQAT_ELAUNCH;
     prof_mark("unpack_qkv", st);
-    if (launch_fwd(w.qh, w.kh, w.vt, B, Hq, Hkv, L, d, causal != 0, false, 0, o, lse, nullptr, 0, nullptr, st)) return ATTNQAT_ELAUNCH;
+    if (launch_fwd(w.qh, w.kh, w.vt, B, Hq, Hkv, L, d, causal != 0, false, 0, o, lse, nullptr, 0, nullptr, st, true)) return ATTNQAT_ELAUNCH;
     prof_mark("fwd_infer", st);
     return ATTNQAT_OK;
 }

@@ -12,7 +12,7 @@
 // MFMA shapes (v_mfma_f32_32x32x16_f16, fp32 accumulate).  All operands are the
 // dequantized NVFP4 values s*c, which fp16 represents exactly, so the products are those
 // of Eq. 4 (BF16MM on fake-quantized operands == FP4MM of Eq. 3).
-//   S^T[key, query]   = K^F (A, from LDS)   x  Q^F^T (B, registers)
+//   S^T[key, query]   = K^F (A, from LDS)   x  Q^F^T (B, registers, made of Q here)
 //   O^T[d, query]    += V^F^T (A, from LDS) x  P-tilde^F^T (B, registers)
 //   O'^T[d, query]   += V^F^T (same A)      x  P-tilde^T   (B, registers; training only)
 // With S transposed, a lane owns ONE query row and 8+8 keys of every aligned group of 16
@@ -25,6 +25,7 @@
 #include "common.hpp"
 #include "kernels.hpp"
 #include "mx_quant.hpp"
+#include "nvfp4.hpp"
 
 namespace aq {
 
@@ -46,7 +47,7 @@ __device__ __forceinline__ void fwd_body(
     const half_t* __restrict__ Qh, const half_t* __restrict__ Kh, const half_t* __restrict__ Vt,
     uint16_t* __restrict__ O, float* __restrict__ lse, float* __restrict__ Ohp,
     int L, int Lp, int Hq, int G, float c /* log2(e)/sqrt(d) */, int dump_row0, float* __restrict__ pdump,
-    int Lkp_arg, const int* __restrict__ kv_lens, int B /* batch (VARLEN: sequences) */)
+    int Lkp_arg, const int* __restrict__ kv_lens, int B /* batch (VARLEN: sequences) */, int q_copy)
 {
     constexpr int KS = SPLIT ? NW : 1;
     constexpr int QT = 32 * NW / KS;       // query rows of a workgroup
@@ -136,20 +137,31 @@ __device__ __forceinline__ void fwd_body(
     const bool has_rows = !PHASES || row0_w < Lp;        // false only in the last tile of a head (Lp is a multiple of 128)
     const int q_row = row0_w + ln;
 
-    // Q^F operand: this lane's query row, d-slots 16*ds + 8*hf .. +7
-    // (Q_LDS, the split training kernel at d = 128: it has no registers for them)
+    // Q^F operand: this lane's query row, d-slots 16*ds + 8*hf .. +7.  phi(Q) is made here, in registers (about 360 vector instructions for a wave's 32 rows,
+    // while the first tiles are on their way), with the bits of the preparing launch, which read and wrote all of Q once more: 32 heads of 8 kv heads, L = 777 causal,
+    // inference 24.8 -> 21.6 us; 4 x 32/8 heads, L = 4096, training: that launch 66.7 -> 27.9 us, this kernel even.
+    // (q_copy: Qh is Q^F in fp16 instead, rows padded to Lp: packed inputs.  SPLIT: the waves share the work, and the rows through LDS.  Q_LDS, the split training kernel at d = 128: it has no registers for them)
     constexpr bool Q_LDS = SPLIT && TRAIN && D == 128 && !MXS;
     const size_t grp = (size_t)bh * (Lp / 32) + ((has_rows ? row0_w : 0) >> 5);      // (MXS) group of 32 rows
     const int q_tid = SPLIT ? (int)threadIdx.x : lane;
-    half8 qreg[MXS || Q_LDS ? 1 : DS];
+    constexpr int DSW = SPLIT ? DS / NW : DS;      // contraction steps of Q^F that this wave makes
+    const bool q_phi = TRAIN || VARLEN || DUMP || PQ != 0 || !q_copy;
+    uint4v qreg[MXS || Q_LDS ? DSW : DS];
     MxQ<D, SPLIT ? 64 * NW : 64> Q;      // (SPLIT: the four waves share the rows)
     if constexpr (MXS) {
         Q.fetch(Qh, nullptr, bh, has_rows ? row0_w : 0, grp, q_tid, L);
-    } else if constexpr (!Q_LDS) {
-        const half_t* qp = Qh + ((size_t)bh * Lp + (has_rows ? q_row : 0)) * D + 8 * hf;
+    } else {
+        const half_t* qp = Qh + ((size_t)bh * (q_phi ? L : Lp) + min(q_row, L - 1)) * D + 8 * hf + (SPLIT ? 16 * DSW * wave : 0);
 #pragma unroll
-        for (int ds = 0; ds < DS; ++ds) qreg[ds] = *reinterpret_cast<const half8*>(qp + 16 * ds);
+        for (int i = 0; i < DSW; ++i) qreg[i] = *reinterpret_cast<const uint4v*>(qp + 16 * i);
     }
+    auto phi_q = [&]() __attribute__((always_inline)) {
+        if (!q_phi) return;
+        if constexpr (DSW == 1) { uint4v same = qreg[0]; phi_half_blocks(qreg[0], same); }
+        else
+#pragma unroll
+            for (int i = 0; i + 1 < DSW; i += 2) phi_half_blocks(qreg[i], qreg[i + 1]);
+    };
     const int nkt = CAUSAL ? min((qt * QT + QT - 1 + off) / 64 + 1, nkt_all) : nkt_all;     // key tiles this item visits
     const int wave_qmax = row0_w + 31 + off;             // the last key that a row of this wave sees
 
@@ -206,7 +218,7 @@ __device__ __forceinline__ void fwd_body(
         for (int i = 0; i < NS; ++i) {                  // step i: ds = i / 2, kb = i % 2
             const half8 a = ring[i % RING];
             if (i + RING < NS) ring[i % RING] = k_opnd(i + RING);
-            s[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, qreg[i >> 1], s[i & 1], 0, 0, 0);
+            s[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, __builtin_bit_cast(half8, qreg[i >> 1]), s[i & 1], 0, 0, 0);
         }
         __builtin_amdgcn_sched_group_barrier(0x100, RING, 0);
 #pragma unroll
@@ -259,14 +271,8 @@ __device__ __forceinline__ void fwd_body(
             mx_q_wave_fence();
             Q.read(Qh, nullptr, grp, lane, ops, scs);
         }
-    } else if constexpr (Q_LDS) {
-#pragma unroll
-        for (int i = 0; i < DS / NW; ++i) {
-            const int ds = wave * (DS / NW) + i;
-            lds_write16_at(q_lds + 1024u * ds, *reinterpret_cast<const uint4v*>(Qh + ((size_t)bh * Lp + q_row) * D + 8 * hf + 16 * ds));
-        }
-        __syncthreads();
-    } else {
+    } else if constexpr (!SPLIT) {
+        phi_q();
 #pragma unroll
         for (int ds = 0; ds < DS; ++ds) asm volatile("" : "+v"(qreg[ds]));
     }
@@ -667,7 +673,7 @@ __device__ __forceinline__ void fwd_body(
 #pragma unroll
                     for (int i = 0; i < 2 * DS; ++i) {
                         const int ds = i >> 1;
-                        s[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kr[i], Q_LDS ? qr[Q_LDS ? ds % RQ : 0] : qreg[Q_LDS ? 0 : ds], s[i & 1], 0, 0, 0);
+                        s[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kr[i], Q_LDS ? qr[Q_LDS ? ds % RQ : 0] : __builtin_bit_cast(half8, qreg[Q_LDS ? 0 : ds]), s[i & 1], 0, 0, 0);
                         if constexpr (Q_LDS) { if ((i & 1) && ds + RQ < DS) qr[ds % RQ] = q_opnd(ds + RQ); }
                         if constexpr (MORE) kr[i] = *reinterpret_cast<const half8*>(k_head + (size_t)k_next * (64 * D) + 512 * i + 8 * lane);
                         __builtin_amdgcn_sched_barrier(0);
@@ -744,6 +750,17 @@ __device__ __forceinline__ void fwd_body(
             Q.quantize(nullptr, p_lds, p_lds + kMxQOps<D>, q_tid);
             lds_barrier();
             Q.read(Qh, nullptr, grp, lane, p_lds, p_lds + kMxQOps<D>);
+        } else {
+            // (Q_LDS: they stay there.  Else through the room of P, as above)
+            phi_q();
+            const uint32_t q_ops = Q_LDS ? q_lds : p_lds + 16u * (uint32_t)lane;
+#pragma unroll
+            for (int i = 0; i < DSW; ++i) lds_write16_at(q_ops + 1024u * (uint32_t)(wave * DSW + i), qreg[i]);
+            lds_barrier();
+            if constexpr (!Q_LDS) {
+#pragma unroll
+                for (int ds = 0; ds < DS; ++ds) qreg[ds] = lds_read16_at(q_ops + 1024u * ds);
+            }
         }
         int j0 = 0;
         for (; j0 + KS < nkt; j0 += KS) four_tiles(std::true_type{}, j0);
@@ -851,16 +868,16 @@ __device__ __forceinline__ void fwd_body(
     const half_t* __restrict__ Qh, const half_t* __restrict__ Kh, const half_t* __restrict__ Vt, \
     uint16_t* __restrict__ O, float* __restrict__ lse, float* __restrict__ Ohp, \
     int L, int Lp, int Hq, int G, float c, int dump_row0, float* __restrict__ pdump, \
-    int Lkp, const int* __restrict__ kv_lens, int B
+    int Lkp, const int* __restrict__ kv_lens, int B, int q_copy
 template <int D, bool TRAIN, bool CAUSAL, bool DUMP, int PQ, bool VARLEN = false>
 __global__ __launch_bounds__(512, 2) void fwd_kernel(AQ_FWD_ARGS)
 {
-    fwd_body<D, TRAIN, CAUSAL, DUMP, PQ, VARLEN, 8>(Qh, Kh, Vt, O, lse, Ohp, L, Lp, Hq, G, c, dump_row0, pdump, Lkp, kv_lens, B);
+    fwd_body<D, TRAIN, CAUSAL, DUMP, PQ, VARLEN, 8>(Qh, Kh, Vt, O, lse, Ohp, L, Lp, Hq, G, c, dump_row0, pdump, Lkp, kv_lens, B, q_copy);
 }
 template <int D, bool TRAIN, bool CAUSAL, int PQ, bool VARLEN = false>
 __global__ __launch_bounds__(256, 2) void fwd_narrow_kernel(AQ_FWD_ARGS)
 {
-    fwd_body<D, TRAIN, CAUSAL, false, PQ, VARLEN, 4>(Qh, Kh, Vt, O, lse, Ohp, L, Lp, Hq, G, c, dump_row0, pdump, Lkp, kv_lens, B);
+    fwd_body<D, TRAIN, CAUSAL, false, PQ, VARLEN, 4>(Qh, Kh, Vt, O, lse, Ohp, L, Lp, Hq, G, c, dump_row0, pdump, Lkp, kv_lens, B, q_copy);
 }
 // Alg. 1 / Alg. 2 where there are too few query rows to fill the chip: a workgroup owns 32 rows, and its four waves take four key
 // tiles at a time, wave w tile 4 n + w for S, the softmax and phi(P-tilde), and block w of O (and O') for the P V products of all four.
@@ -878,7 +895,7 @@ __global__ __launch_bounds__(256, 2) void fwd_narrow_kernel(AQ_FWD_ARGS)
 template <int D, bool TRAIN, bool CAUSAL, int PQ, bool VARLEN = false>
 __global__ __launch_bounds__(256, 2) void fwd_split_kernel(AQ_FWD_ARGS)
 {
-    fwd_body<D, TRAIN, CAUSAL, false, PQ, VARLEN, 4, true>(Qh, Kh, Vt, O, lse, Ohp, L, Lp, Hq, G, c, dump_row0, pdump, Lkp, kv_lens, B);
+    fwd_body<D, TRAIN, CAUSAL, false, PQ, VARLEN, 4, true>(Qh, Kh, Vt, O, lse, Ohp, L, Lp, Hq, G, c, dump_row0, pdump, Lkp, kv_lens, B, q_copy);
 }
 #undef AQ_FWD_ARGS
 
@@ -942,7 +959,7 @@ static size_t split_lds_bytes(int D, bool train, int pq) { return (size_t)(train
 template <int D, bool TRAIN, bool CAUSAL, bool DUMP, int PQ, bool VARLEN = false>
 static int launch_t(const void* qh, const void* kh, const void* vt, int B, int Hq, int Hkv, int L,
                     void* o, float* lse, float* o_hp, int dump_row0, float* p_dump, hipStream_t st,
-                    int Lkp = 0, const int* kv_lens = nullptr)
+                    int Lkp = 0, const int* kv_lens = nullptr, bool q_copy = false)
 {
     const int Lp = round_up(L, kRowPad);
     const int nqt = (Lp + 255) / 256;
@@ -953,7 +970,7 @@ static int launch_t(const void* qh, const void* kh, const void* vt, int B, int H
         if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)smem, lds_set)) return -1;
         hipLaunchKernelGGL(kern, dim3(grid), dim3(block), smem, st,
                            (const half_t*)qh, (const half_t*)kh, (const half_t*)vt, (uint16_t*)o, lse, o_hp,
-                           L, Lp, Hq, Hq / Hkv, c, dump_row0, p_dump, Lkp, kv_lens, B);
+                           L, Lp, Hq, Hq / Hkv, c, dump_row0, p_dump, Lkp, kv_lens, B, q_copy ? 1 : 0);
         return hipGetLastError() == hipSuccess ? 0 : -1;
     };
     if constexpr (!DUMP && PQ != 2) {
@@ -978,7 +995,7 @@ static int launch_t(const void* qh, const void* kh, const void* vt, int B, int H
 template <int D, int PQ>
 static int launch_d(const void* qh, const void* kh, const void* vt, int B, int Hq, int Hkv, int L,
                     bool causal, bool train, void* o, float* lse, float* o_hp,
-                    int dump_row0, float* p_dump, hipStream_t st)
+                    int dump_row0, float* p_dump, hipStream_t st, bool q_copy)
 {
     if (p_dump) {
         return causal ? launch_t<D, false, true, true, PQ>(qh, kh, vt, B, Hq, Hkv, L, o, lse, o_hp, dump_row0, p_dump, st)
@@ -990,16 +1007,17 @@ static int launch_d(const void* qh, const void* kh, const void* vt, int B, int H
                           : launch_t<D, true, false, false, PQ>(qh, kh, vt, B, Hq, Hkv, L, o, lse, o_hp, 0, nullptr, st);
         }
     }
-    return causal ? launch_t<D, false, true, false, PQ>(qh, kh, vt, B, Hq, Hkv, L, o, lse, o_hp, 0, nullptr, st)
-                  : launch_t<D, false, false, false, PQ>(qh, kh, vt, B, Hq, Hkv, L, o, lse, o_hp, 0, nullptr, st);
+    return causal ? launch_t<D, false, true, false, PQ>(qh, kh, vt, B, Hq, Hkv, L, o, lse, o_hp, 0, nullptr, st, 0, nullptr, q_copy)
+                  : launch_t<D, false, false, false, PQ>(qh, kh, vt, B, Hq, Hkv, L, o, lse, o_hp, 0, nullptr, st, 0, nullptr, q_copy);
 }
 
 int launch_fwd(const void* qh, const void* kh, const void* vt,
                int B, int Hq, int Hkv, int L, int D, bool causal, bool train, int p_quant,
-               void* o, float* lse, float* o_hp, int dump_row0, float* p_dump, hipStream_t st)
+               void* o, float* lse, float* o_hp, int dump_row0, float* p_dump, hipStream_t st, bool q_copy)
 {
-#define AQ_FWD(DD, PQ) launch_d<DD, PQ>(qh, kh, vt, B, Hq, Hkv, L, causal, train, o, lse, o_hp, dump_row0, p_dump, st)
+#define AQ_FWD(DD, PQ) launch_d<DD, PQ>(qh, kh, vt, B, Hq, Hkv, L, causal, train, o, lse, o_hp, dump_row0, p_dump, st, q_copy)
     if (p_quant == 3 && train) return -1;           // the bf16 P V recipe has no backward
+    if (q_copy && (train || p_quant != 0 || p_dump)) return -1;
     if (D == 128) return p_quant == 1 ? AQ_FWD(128, 1) : p_quant == 2 ? AQ_FWD(128, 2) : p_quant == 3 ? AQ_FWD(128, 3) : AQ_FWD(128, 0);
     if (D == 64)  return p_quant == 1 ? AQ_FWD(64, 1) : p_quant == 2 ? AQ_FWD(64, 2) : p_quant == 3 ? AQ_FWD(64, 3) : AQ_FWD(64, 0);
 #undef AQ_FWD

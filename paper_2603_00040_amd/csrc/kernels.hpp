@@ -34,7 +34,7 @@ struct GradArgs {
 struct PrepGroup {
     const uint16_t *q, *k, *v;
     const uint8_t *codes[3], *scales[3];
-    uint16_t *q_out, *k_out, *v_out;             // q_out / k_out null: that tensor is left out
+    uint16_t *q_out, *k_out, *v_out;             // q_out: backward, packed inputs; k_out null: K is left out
     const float* k_sub;                          // [BHkv, D]: subtracted from the rows of K before phi (K smoothing)
     int BHq, BHkv, L, Lp, L_kv, Lp_kv, D;
     bool v_quant;
@@ -48,18 +48,19 @@ int launch_prep_group(const PrepGroup& g, hipStream_t st);
 size_t colmean_scratch_bytes(int BH, int D);
 int launch_colmean(const void* x, int BH, int L, int D, double* scratch, float* mean, hipStream_t st);
 
-// Alg. 1 (train=false) / Alg. 2 (train=true) on copies made by launch_prep_group.
-// p_quant 1 (MX): qh is Q itself in bf16 (no result may lie over it) and kh the K records of launch_mx_group (MX_TRAIN, krec), not fp16
+// Alg. 1 (train=false) / Alg. 2 (train=true): q is Q itself in bf16, of which the kernels make phi(Q) (no result may lie over it), kh and vt are copies made by
+// launch_prep_group.  q_copy (inference, p_quant 0): q is such a copy too.
+// p_quant 1 (MX): kh the K records of launch_mx_group (MX_TRAIN, krec), not fp16
 // copies: the scores are computed from the codes; vt stays the fp16 copy.
 // p_quant: phi(P-tilde) 0 NVFP4; 1 in the MX format (blocks of 32 keys, power-of-two scale); 2 NVFP4 after the
 // two-level row factor (every 64-key tile row divided by a power of two that brings its maximum just below 448 * 6).
-int launch_fwd(const void* qh, const void* kh, const void* vt,
+int launch_fwd(const void* q, const void* kh, const void* vt,
                int B, int Hq, int Hkv, int L, int D, bool causal, bool train, int p_quant,
-               void* o, float* lse, float* o_hp, int dump_row0, float* p_dump, hipStream_t st);
+               void* o, float* lse, float* o_hp, int dump_row0, float* p_dump, hipStream_t st, bool q_copy = false);
 
 // Alg. 1 for sequences of different lengths (serving): queries are the last Lq positions of every sequence, sequence b has
 // kv_lens[b] keys (device array), kh / vt are laid out for Lkp positions per kv head.
-int launch_fwd_varlen(const void* qh, const void* kh, const void* vt, int B, int Hq, int Hkv, int Lq, int Lkp, int D, bool causal,
+int launch_fwd_varlen(const void* q, const void* kh, const void* vt, int B, int Hq, int Hkv, int Lq, int Lkp, int D, bool causal,
                       const int* kv_lens, void* o, float* lse, hipStream_t st);
 
 // The NVFP4 KV cache (pages of 128 positions; per kv head K codes, K scales, V codes, V scales in the public layout).

@@ -21,17 +21,22 @@ struct Nv16 { uint32_t clo, chi, sc; float s; };
 // (About 70 vector instructions a block.  With an IEEE division and the grid rounding of common.hpp for the scale and two integer instructions per element to
 // round the quotient it was 130; these bound the preparing launches of small problems and the cache writes: training step of 2 heads,
 // L = 256, d = 64 24.95 -> 24.55 us, 12 heads, L = 1560 131.0 -> 129.9 us, inference 32 heads, L = 777 24.9 -> 24.7 us.)
-__device__ inline Nv16 phi_block16_bf16(const float (&v)[16])
+__device__ __forceinline__ void nv16_scale(float amax, uint32_t& sc, float& s, float& inv)
 {
     typedef short short2v __attribute__((ext_vector_type(2)));
+    const float q = __uint_as_float((__float_as_uint(amax * (1.0f / 6.0f)) + 0x80u) & 0xFFFFFF00u), qs = fminf(q, 448.0f);
+    sc = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(short2v{0, 0}, qs, qs, 1.0f, false));
+    s = __builtin_amdgcn_cvt_scalef32_f32_fp8(sc, 1.0f, 0);
+    inv = s > 0.0f ? __builtin_amdgcn_rcpf(s) : 0.0f;      // s = 0: every quotient 0, every code 0
+}
+__device__ inline Nv16 phi_block16_bf16(const float (&v)[16])
+{
     float amax = 0.0f;
 #pragma unroll
     for (int i = 0; i < 16; ++i) amax = fmaxf(amax, fabsf(v[i]));
-    const float q = __uint_as_float((__float_as_uint(amax * (1.0f / 6.0f)) + 0x80u) & 0xFFFFFF00u), qs = fminf(q, 448.0f);
     Nv16 b;
-    b.sc = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(short2v{0, 0}, qs, qs, 1.0f, false));
-    b.s = __builtin_amdgcn_cvt_scalef32_f32_fp8(b.sc, 1.0f, 0);
-    const float inv = b.s > 0.0f ? __builtin_amdgcn_rcpf(b.s) : 0.0f;      // s = 0: every quotient 0, every code 0
+    float inv;
+    nv16_scale(amax, b.sc, b.s, inv);
     // (where the scale is saturated a quotient may be beyond fp16: infinity, which becomes 6)
     auto pair = [&](int i) __attribute__((always_inline)) { return half2v{(half_t)(v[2 * i] * inv), (half_t)(v[2 * i + 1] * inv)}; };
     b.clo = any_register(); b.chi = any_register();
@@ -65,6 +70,40 @@ __device__ inline void dequant_block16_f16(const Nv16& b, uint32_t (&w)[8])
     AQ_BACK(b.clo, 0, 0) AQ_BACK(b.clo, 1, 1) AQ_BACK(b.clo, 2, 2) AQ_BACK(b.clo, 3, 3)
     AQ_BACK(b.chi, 4, 0) AQ_BACK(b.chi, 5, 1) AQ_BACK(b.chi, 6, 2) AQ_BACK(b.chi, 7, 3)
 #undef AQ_BACK
+}
+
+// phi, and back to fp16, of two blocks of bf16 values shared by the lanes l and l + 32: a lane has 8 values of block a in a and 8 of block b in b.  The
+// bits of phi_block16_bf16 and dequant_block16_f16.  One half forms the scale of a, the other that of b.
+__device__ __forceinline__ void phi_half_blocks(uint4v& a, uint4v& b)
+{
+    float v[2][8], m[2] = {0.0f, 0.0f};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        v[0][2 * i] = __uint_as_float(a[i] << 16); v[0][2 * i + 1] = __uint_as_float(a[i] & 0xFFFF0000u);
+        v[1][2 * i] = __uint_as_float(b[i] << 16); v[1][2 * i + 1] = __uint_as_float(b[i] & 0xFFFF0000u);
+    }
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) m[g] = fmaxf(m[g], fabsf(v[g][i]));
+    uint32_t sc;
+    float s, inv;
+    nv16_scale(xhalf_max_pair(m[0], m[1]), sc, s, inv);
+    const auto sc2 = __builtin_amdgcn_permlane32_swap(sc, sc, false, false);
+    const auto inv2 = __builtin_amdgcn_permlane32_swap(__float_as_uint(inv), __float_as_uint(inv), false, false);
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+        const float iv = __uint_as_float(inv2[g]);
+        const half2v sh = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(sc2[g], 1.0f, false);
+        uint32_t c = any_register();
+        uint4v& w = g ? b : a;
+#define AQ_PAIR(I) c = __builtin_amdgcn_cvt_scalef32_pk_fp4_f16(c, half2v{(half_t)(v[g][2 * I] * iv), (half_t)(v[g][2 * I + 1] * iv)}, 1.0f, I);
+        AQ_PAIR(0) AQ_PAIR(1) AQ_PAIR(2) AQ_PAIR(3)
+#undef AQ_PAIR
+#define AQ_BACK(I) w[I] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(c, 1.0f, I) * sh);
+        AQ_BACK(0) AQ_BACK(1) AQ_BACK(2) AQ_BACK(3)
+#undef AQ_BACK
+    }
 }
 
 }  // namespace aq

@@ -1,5 +1,5 @@
-"""Where the attention kernels quantize Q themselves: bit for bit what they return on operands that the preparing launch made, which is what
-a call gets whose output lies over its Q."""
+"""Where the attention kernels quantize Q themselves: bit for bit what a call returns whose output lies over its Q, which takes operands that the
+preparing launch made, or a copy of Q."""
 import pytest
 import torch
 
@@ -28,7 +28,7 @@ def _same(a, b):
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("B,Hq,Hkv,L", SHAPES)
-@pytest.mark.parametrize("kind", ["mx", "mx_fp8pv", "mx_sparse", "mx_train"])
+@pytest.mark.parametrize("kind", ["mx", "mx_fp8pv", "mx_sparse", "mx_train", "nvfp4", "nvfp4_train"])
 def test_forward(kind, B, Hq, Hkv, L, d, causal):
     import paper_2603_00040_amd as aq
     x = random_inputs(B, Hq, Hkv, L, d, seed=L + d, k_chan=4)
@@ -36,14 +36,14 @@ def test_forward(kind, B, Hq, Hkv, L, d, causal):
 
     def run(q, o):
         lse = torch.empty((B, Hq, L), dtype=torch.float32, device="cuda")
-        if kind == "mx_train":
-            return aq.attnqat_fwd_mx(q, k, v, causal, out=(o, lse, torch.empty((B, Hq, L, d), dtype=torch.float32, device="cuda")))
+        if kind in ("mx_train", "nvfp4_train"):
+            return (aq.attnqat_fwd_mx if kind == "mx_train" else aq.attnqat_fwd)(q, k, v, causal, out=(o, lse, torch.empty((B, Hq, L, d), dtype=torch.float32, device="cuda")))
         if kind == "mx_sparse":
             nb = (L + 127) // 128
             mask = torch.ones((B, Hq, nb, nb), dtype=torch.uint8, device="cuda")
             mask[..., ::2, 1::3] = 0
             return aq.attnqat_fwd_infer_mx_sparse(q, k, v, causal, mask, out=(o, lse))
-        return {"mx": aq.attnqat_fwd_infer_mx, "mx_fp8pv": aq.attnqat_fwd_infer_mx_fp8pv}[kind](q, k, v, causal, out=(o, lse))
+        return {"nvfp4": aq.attnqat_fwd_infer, "mx": aq.attnqat_fwd_infer_mx, "mx_fp8pv": aq.attnqat_fwd_infer_mx_fp8pv}[kind](q, k, v, causal, out=(o, lse))
     _same(*_both(run, q))
 
 
@@ -65,4 +65,25 @@ def test_paged(B, Hq, Hkv, Lq, n, d):
     def run(q, o):
         lse = torch.empty((B, Hq, Lq), dtype=torch.float32, device="cuda")
         return aq.attnqat_fwd_infer_mx_paged(q, cache, B * pages, table, lens, Hkv, True, out=(o, lse))
+    _same(*_both(run, q))
+
+
+# NVFP4: a prompt's last positions over the pages of a cache, rows of one length and of several
+@pytest.mark.parametrize("B,Hq,Hkv,Lq,n", [(2, 4, 2, 77, 300), (1, 40, 8, 1000, 1000)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_paged_nvfp4(B, Hq, Hkv, Lq, n, d):
+    import paper_2603_00040_amd as aq
+    x = random_inputs(B, Hq, Hkv, n, d, seed=n + d, k_chan=4)
+    pages = (n + 127) // 128
+    cache = torch.zeros(B * pages * aq.kv_cache_page_bytes_nvfp4(Hkv, d), dtype=torch.uint8, device="cuda")
+    table = torch.arange(B * pages, dtype=torch.int32, device="cuda").flip(0).reshape(B, pages).contiguous()
+    k, v = to_dev(x["k"]), to_dev(x["v"])
+    for b in range(B):
+        aq.attnqat_kv_cache_write(k[b:b + 1], v[b:b + 1], cache, table[b])
+    q = to_dev(x["q"])[:, :, n - Lq:].contiguous()
+    lens = torch.tensor([n, n - 60][:B], dtype=torch.int32, device="cuda")
+
+    def run(q, o):
+        lse = torch.empty((B, Hq, Lq), dtype=torch.float32, device="cuda")
+        return aq.attnqat_fwd_infer_paged(q, cache, B * pages, table, lens, Hkv, True, out=(o, lse))
     _same(*_both(run, q))
