@@ -243,6 +243,12 @@ __device__ __forceinline__ void fwd_body(
     half8 kr[SPLIT && !MXS ? 2 * DS : 1], vr[SPLIT ? KS : 1][4][OB];
     uint4v kr_mx[SPLIT && MXS ? 2 * KSM : 1];
     uint32_t ksc_mx = 0u;
+    // AHEAD (training, d = 128): S of the next four tiles is computed between the P V products, whose accumulators' rescaling (a quarter of the vector
+    // instructions: on few keys some row moves its maximum in nearly every tile) then has products beside it instead of waiting for the last ones; its K operands are
+    // asked for while P-tilde is quantized, when its registers are free.  1 - 5 % (12 heads, L = 1560 53.7 -> 52.2 us, 15 heads causal 39.9 -> 38.4 us).  Inference, with half
+    // the products and rescaling: even to 3 % slower; d = 64: 2 % slower.
+    constexpr bool AHEAD = Q_LDS;
+    int k_tile = 0; bool k_more = false;                // AHEAD: the tile of those operands, if there is one
     auto load_k = [&](int jt) __attribute__((always_inline)) {
         if constexpr (MXS) {
             const unsigned char* rec = k_recs + (size_t)jt * KREC;
@@ -578,6 +584,14 @@ __device__ __forceinline__ void fwd_body(
                 for (int part = 0; part < 4; ++part) q_part(ks, part, st, bq, bu);
                 lds_write16_at(dst + 1024u * ks, bq);
                 if constexpr (TRAIN) lds_write16_at(dst + PT + 1024u * ks, bu);
+                if constexpr (AHEAD) {
+                    if (k_more) {
+#pragma unroll
+                        for (int i = ks * (DS / 2); i < (ks + 1) * (DS / 2); ++i)
+                            kr[i] = *reinterpret_cast<const half8*>(k_head + (size_t)k_tile * (64 * D) + 512 * i + 8 * lane);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
             }
             return;
         }
@@ -638,9 +652,35 @@ __device__ __forceinline__ void fwd_body(
         // Four key tiles.  MORE: not the last ones; an operand register is reloaded for the next four right behind its last product
         // (asked for all at once, the 16 KiB of each wave held it up for the time they take to get through the compute unit's
         // cache at 64 bytes per clock).
+        // S of a tile of this wave, in KS parts.  RELOAD: the operand registers take those of tile k_next
+        constexpr int RQ = 4, SP = 2 * DS / KS;
+        half8 qr[Q_LDS ? RQ : 1];
+        auto q_opnd = [&](int ds) __attribute__((always_inline)) { return __builtin_bit_cast(half8, lds_read16_at(q_lds + 1024u * ds)); };
+        auto s_part = [&](auto reload, int part, int k_next) __attribute__((always_inline)) {
+            constexpr bool RELOAD = decltype(reload)::value;
+            if (part == 0) {
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) s[kb][i] = 0.0f;
+                if constexpr (Q_LDS) {
+#pragma unroll
+                    for (int ds = 0; ds < RQ; ++ds) qr[ds] = q_opnd(ds);
+                }
+            }
+#pragma unroll
+            for (int i = part * SP; i < (part + 1) * SP; ++i) {
+                const int ds = i >> 1;
+                s[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kr[MXS ? 0 : i], Q_LDS ? qr[Q_LDS ? ds % RQ : 0] : __builtin_bit_cast(half8, qreg[Q_LDS || MXS ? 0 : ds]), s[i & 1], 0, 0, 0);
+                if constexpr (Q_LDS) { if ((i & 1) && ds + RQ < DS) qr[ds % RQ] = q_opnd(ds + RQ); }
+                if constexpr (RELOAD) kr[MXS ? 0 : i] = *reinterpret_cast<const half8*>(k_head + (size_t)k_next * (64 * D) + 512 * i + 8 * lane);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
         auto four_tiles = [&](auto more, int j0) __attribute__((always_inline)) {
             constexpr bool MORE = decltype(more)::value;
             const int j = j0 + wave, k_next = min(j + KS, nkt - 1);
+            k_tile = k_next; k_more = MORE;
             const bool active = MORE || j < nkt;
             nt = MORE ? KS : nkt - j0;
             if (active) {
@@ -658,26 +698,9 @@ __device__ __forceinline__ void fwd_body(
                     }
                     mfma_scale_settle(s[0], s[1]);
                     if constexpr (MORE) load_k(k_next);
-                } else {
+                } else if constexpr (!AHEAD) {
 #pragma unroll
-                    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) s[kb][i] = 0.0f;
-                    constexpr int RQ = 4;
-                    half8 qr[Q_LDS ? RQ : 1];
-                    auto q_opnd = [&](int ds) __attribute__((always_inline)) { return __builtin_bit_cast(half8, lds_read16_at(q_lds + 1024u * ds)); };
-                    if constexpr (Q_LDS) {
-#pragma unroll
-                        for (int ds = 0; ds < RQ; ++ds) qr[ds] = q_opnd(ds);
-                    }
-#pragma unroll
-                    for (int i = 0; i < 2 * DS; ++i) {
-                        const int ds = i >> 1;
-                        s[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kr[i], Q_LDS ? qr[Q_LDS ? ds % RQ : 0] : __builtin_bit_cast(half8, qreg[Q_LDS ? 0 : ds]), s[i & 1], 0, 0, 0);
-                        if constexpr (Q_LDS) { if ((i & 1) && ds + RQ < DS) qr[ds % RQ] = q_opnd(ds + RQ); }
-                        if constexpr (MORE) kr[i] = *reinterpret_cast<const half8*>(k_head + (size_t)k_next * (64 * D) + 512 * i + 8 * lane);
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
+                    for (int part = 0; part < KS; ++part) s_part(more, part, k_next);
                 }
                 half2v bsc[2]; float psc[4];
                 vector_phase(j, bsc, psc);
@@ -694,7 +717,7 @@ __device__ __forceinline__ void fwd_body(
 #pragma unroll
             for (int t = 0; t < KS; ++t) { al[t] = x_alpha[t * 32 + ln]; sm_[t] = x_sum[t * 64 + lane]; }
             // operands are read R steps of 16 keys ahead of their products
-            constexpr int R = 4;
+            constexpr int R = AHEAD ? 2 : 4;
             uint4v rq[R], ru[TRAIN && BOTH ? R : 1];
             auto fetch = [&](int i) __attribute__((always_inline)) {
                 rq[i % R] = lds_read16_at(p_src + 1024u * i);
@@ -734,6 +757,7 @@ __device__ __forceinline__ void fwd_body(
                         }
                     }
                 }
+                if constexpr (MORE && AHEAD) s_part(std::false_type{}, t, 0);
             }
         };
         load_k(min(wave, nkt - 1));
@@ -761,6 +785,10 @@ __device__ __forceinline__ void fwd_body(
 #pragma unroll
                 for (int ds = 0; ds < DS; ++ds) qreg[ds] = lds_read16_at(q_ops + 1024u * ds);
             }
+        }
+        if constexpr (AHEAD) {
+#pragma unroll
+            for (int part = 0; part < KS; ++part) s_part(std::false_type{}, part, 0);
         }
         int j0 = 0;
         for (; j0 + KS < nkt; j0 += KS) four_tiles(std::true_type{}, j0);
