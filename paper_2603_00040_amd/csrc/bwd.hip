@@ -1101,8 +1101,36 @@ int launch_bwd_dkdv(const void* qb, const void* kb, const void* vb, const void* 
 // without pieces -> as planned (plan.hpp): 2 x 16/4 heads, L = 3001 causal 617 -> 518 -> 292 us (MX 683 -> 596 -> 328 us);
 // 8/2 heads, L = 8192 causal 1264 -> 1139 -> 475 us; 12 heads, L = 1560 120 -> 91 -> 82 us; 4 x 32/8 heads, L = 4096 causal
 // 2.09 -> 1.85 ms (no pieces); 12 heads, L = 6240 833 -> 698 us (no pieces).
+// The pieces of a kv head's key tiles under a causal mask, in the order in which they are handed out: the first piece of every tile, then the second of
+// those that have one (the first tiles), and so on; without a mask all tiles have all pieces.  A lane counts the tiles that have piece number s0 + lane.
+// Workgroups go to the XCDs in turn and, inside an XCD, to its four shader engines (eight compute units each) in turn, and one whose turn it is waits for room in
+// its own engine while others have some.  So every four workgroups in a row of an XCD should take the same time.  Tile after tile with room for the largest number of
+// pieces, four here, the fourth engine got the last pieces, shorter or empty, and stood idle: 384 workgroups at once instead of 512.  With this order,
+// the joint launch: 2 x 16/4 heads, L = 3001 causal 304 -> 251 us (MX 288 -> 236 us); 2 x 32/8 heads 552 -> 474 us; 16/4 heads, L = 6000 520 -> 428 us.
+__device__ __forceinline__ void piece_of_rank(int rank, const DkvArgs& K, int nt, int& kt, int& piece)
+{
+    const int lane = threadIdx.x & 63, nq32 = (K.L + 31) / 32;
+    int base = 0, p = 0;
+    for (int s0 = 0; s0 < K.splits; s0 += 64) {
+        // (tile kt has (nq32 - 4 kt) G query tiles)
+        const int more = nq32 - 1 - (int)((unsigned)(s0 + lane) * (unsigned)K.split_iters / (unsigned)K.G);
+        int sum = more < 0 ? 0 : min(more / 4 + 1, nt);
+#pragma unroll
+        for (int d = 1; d < 64; d *= 2) { const int x = __shfl_up(sum, d); if (lane >= d) sum += x; }
+        const unsigned long long past = __builtin_amdgcn_ballot_w64(rank < base + sum);
+        if (past) {
+            const int f = __builtin_ctzll(past);
+            if (f > 0) base += __builtin_amdgcn_readlane(sum, f - 1);
+            p = s0 + f;
+            break;
+        }
+        base += __builtin_amdgcn_readlane(sum, 63);
+    }
+    kt = rank - base; piece = p;
+}
+
 template <int D, bool CAUSAL, int PQ, bool COUNT = false /* the measurement variant of bwd_dkdv_body */>
-__global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_joint_kernel(DqArgs Q, DkvArgs K, int n_dkdv, int n_dq, bool dq_first)
+__global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_joint_kernel(DqArgs Q, DkvArgs K, int n_dkdv, int n_dq, int pieces /* of a kv head */, bool dq_first)
 {
     const int nt = K.Lp / 128;
     int block = blockIdx.x;
@@ -1121,9 +1149,14 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_joint_kernel(DqArgs 
     };
     int head, rank;
     if (dkdv) {
-        if (block >= K.NHkv * nt * K.splits) return;            // (n_dkdv and n_dq are rounded up to whole rounds of the XCDs)
-        place(K.NHkv, nt * K.splits, head, rank);
-        bwd_dkdv_body<D, CAUSAL, COUNT, PQ, 4, true>(K, head, rank / K.splits, rank % K.splits);
+        if (block >= K.NHkv * pieces) return;                   // (n_dkdv and n_dq are rounded up to whole rounds of the XCDs)
+        place(K.NHkv, pieces, head, rank);
+        int piece = 0;
+        if (K.splits > 1) {
+            if constexpr (CAUSAL) piece_of_rank(rank, K, nt, rank, piece);
+            else { piece = rank / nt; rank %= nt; }
+        }
+        bwd_dkdv_body<D, CAUSAL, COUNT, PQ, 4, true>(K, head, rank, piece);
     } else {
         if (block >= Q.NHq * nt) return;
         place(Q.NHq, nt, head, rank);
@@ -1571,8 +1604,14 @@ static int launch_joint_t(const DqArgs& Q, DkvArgs K, const BwdPlan& plan, float
     static unsigned long long lds_set = 0;          // one per instantiation
     if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)(D == 64 ? kPairLds : need), lds_set)) return -1;
     K.splits = plan.splits; K.split_iters = plan.iters; K.part = part;
-    const int nt = K.Lp / 128, n_dkdv = round_up(K.NHkv * nt * K.splits, 8), n_dq = round_up(Q.NHq * nt, 8);
-    hipLaunchKernelGGL(kern, dim3((unsigned)(n_dkdv + n_dq)), dim3(256), smem, st, Q, K, n_dkdv, n_dq, plan.dq_first);
+    const int nt = K.Lp / 128;
+    int pieces = nt * K.splits;
+    if (CAUSAL && K.splits > 1) {
+        pieces = 0;
+        for (int kt = 0; kt < nt; ++kt) pieces += (int)(((unsigned)((K.L + 31) / 32 - 4 * kt) * (unsigned)K.G + (unsigned)K.split_iters - 1) / (unsigned)K.split_iters);
+    }
+    const int n_dkdv = round_up(K.NHkv * pieces, 8), n_dq = round_up(Q.NHq * nt, 8);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(n_dkdv + n_dq)), dim3(256), smem, st, Q, K, n_dkdv, n_dq, pieces, plan.dq_first);
     if (hipGetLastError() != hipSuccess) return -1;
     if (plan.splits > 1)
         hipLaunchKernelGGL((dkdv_reduce_kernel<D, CAUSAL>), dim3((unsigned)(K.NHkv * nt * 2 * (D / 32))), dim3(256), 0, st,
