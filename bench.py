@@ -48,13 +48,13 @@ HBM_PEAK_GBS = 8000.0              # MI355X HBM3E
 
 def hbm_kernel_report(kern_ms, w, train):
     """Achieved GB/s of the bandwidth-bound kernels against the HBM peak.  Algorithmic bytes per element (d innermost):
-    a quantization pass reads 2 B (bf16) and writes 2 B (the fp16/bf16 workspace copy the attention kernels read);
+    a quantization pass reads 2 B (bf16) and writes 2 B (the fp16/bf16 workspace copy the attention kernels read), a forward's of K and V only;
     the backward's pass also reads dO (2 B) and O' (4 B) and, per row, L (4 B), and writes the {L, D} pair (8 B) and, where
     the rows of dO need padding, a copy of dO (2 B)."""
     nq = float(w.B) * w.Hq * w.L * w.d
     nkv = float(w.B) * w.Hkv * w.L * w.d
     rows = float(w.B) * w.Hq * w.L
-    byts = {"prep_qkv": 4.0 * (nq + 2 * nkv), "prep_qkvdo": 4.0 * (nq + 2 * nkv) + (8.0 if w.L % 128 else 6.0) * nq + 12.0 * rows,
+    byts = {"prep_qkv": 4.0 * 2 * nkv, "prep_qkvdo": 4.0 * (nq + 2 * nkv) + (8.0 if w.L % 128 else 6.0) * nq + 12.0 * rows,
             "quantize": None}
     out = {}
     for name, b in byts.items():
