@@ -71,19 +71,17 @@ __device__ __forceinline__ float nvfp4_group_max(const floatx16& s, int gq) {
     const float a0 = fmaxf(fmaxf(s[8 * gq], s[8 * gq + 1]), s[8 * gq + 2]), a1 = fmaxf(fmaxf(s[8 * gq + 3], s[8 * gq + 4]), s[8 * gq + 5]);
     return fmaxf(fmaxf(a0, a1), fmaxf(s[8 * gq + 6], s[8 * gq + 7]));
 }
-// Is the block scale of a largest P of amax non-zero?  It is RNE_E4M3(amax / 6), which is zero exactly when amax / 6 <= 2^-10 (half of the smallest
+// Does a largest P of amax ask for products with P^F?  RNE_E4M3(amax / 6) is zero exactly when amax / 6 <= 2^-10 (half of the smallest
 // subnormal, and the tie goes to the even neighbour, zero), and it grows with amax: some block of a tile has a non-zero scale iff some
-// lane's largest P passes this test.
+// lane's largest P passes this test.  (The product is rounded to fp32 here and not in nvfp4_pair_scales: at the one P where they differ, 6 * 2^-10 itself, a
+// tile is left out if no larger one is in it.)
 __device__ __forceinline__ bool nvfp4_scale_nonzero(float amax) { return amax * (1.0f / 6.0f) > 0.0009765625f; }
 // Block scales of phi(P) of the two groups, and their reciprocals.  Each half of the wave forms the scale of one group and hands it to the other, as in
-// the forward (P <= 1: no saturation; a scale of 0 leaves any finite factor).  112 instead of 145 vector instructions beside the products of a
-// tile with P^F, with the maxima of the test above used again and no register cleared for the conversions: 4 x 32/8 heads, L = 4096 causal, where 98 % of
-// the tiles come here, training step 2903 -> 2817 us (the forward's share: 25 us).
+// the forward (P <= 1: no saturation; a scale of 0 leaves any finite factor).  A scale is RNE_E4M3 of the unrounded product of the largest P with fp32's 1/6; the forward
+// rounds that product to fp32 first, which differs at ties of the grid only.  (The hardware conversion would round it first here too, in three
+// instructions instead of six: training step of 4 x 32/8 heads, L = 4096 causal 2800 us instead of 2813, but dV moves by 1e-4 of its norm.)
 __device__ __forceinline__ void nvfp4_pair_scales(const float (&gmax)[2], float (&sc)[2], float (&inv)[2]) {
-    typedef short short2v __attribute__((ext_vector_type(2)));
-    const float bm = xhalf_max_pair(gmax[0], gmax[1]) * (1.0f / 6.0f);
-    const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(__builtin_bit_cast(short2v, any_register()), bm, bm, 1.0f, false));
-    const float own = __builtin_amdgcn_cvt_scalef32_f32_fp8(w, 1.0f, 0), r = fminf(__builtin_amdgcn_rcpf(own), 512.0f);
+    const float own = rne_e4m3_grid_of_product(xhalf_max_pair(gmax[0], gmax[1]), 1.0f / 6.0f), r = fminf(__builtin_amdgcn_rcpf(own), 512.0f);
     const auto sb = __builtin_amdgcn_permlane32_swap(__float_as_uint(own), __float_as_uint(own), false, false);
     const auto ib = __builtin_amdgcn_permlane32_swap(__float_as_uint(r), __float_as_uint(r), false, false);
 #pragma unroll
@@ -837,7 +835,7 @@ __device__ __forceinline__ void bwd_dkdv_body(const DkvArgs& A, int bhkv, int kt
                 bool any = false;
 #pragma unroll
                 for (int gq = 0; gq < 2; ++gq) {
-                    const float s2 = rne_e4m3_grid((xhalf_max(gmax[gq]) * inv1) * (1.0f / 6.0f));
+                    const float s2 = rne_e4m3_grid_of_product(xhalf_max(gmax[gq]) * inv1, 1.0f / 6.0f);
                     // P^F = (s1 s2) * code and the code is RNE(P / (s1 s2)): from here on the product of the two levels
                     // stands in for the block scale (a power of two times an E4M3 value: still exact in bf16)
                     sc[gq] = s2 * s1;

@@ -52,6 +52,14 @@ __device__ inline float rne_e4m3_grid(float v) {
     float c = __uint_as_float(e + 0x0A400000u);            // 1.5 * 2^(e+20)
     return (v + c) - c;
 }
+// The same of the product x y >= 0, which is not rounded before: the exact product decides on which side of a tie it lies.  Written as
+// rne_e4m3_grid(x * y) the compiler would be free to contract the two or not.
+__device__ inline float rne_e4m3_grid_of_product(float x, float y) {
+    uint32_t e = __float_as_uint(x * y) & 0x7F800000u;
+    e = e > 0x3C800000u ? e : 0x3C800000u;
+    const float c = __uint_as_float(e + 0x0A400000u);
+    return __builtin_fmaf(x, y, c) - c;
+}
 // Round 0 <= r <= 6 to the E2M1 grid {0,.5,1,1.5,2,3,4,6} (RNE), same trick with
 // 1.5 * 2^(e+22); binades below 1 share the spacing 0.5.
 __device__ inline float rne_e2m1_grid(float r) {

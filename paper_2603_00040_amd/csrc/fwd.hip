@@ -483,7 +483,7 @@ __device__ __forceinline__ void fwd_body(
             // (two-level: the block maxima of P-tilde / s1 are at most 2688 (1 + 2^-23), whose sixth rounds to 448, the largest scale)
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) {
-                const float sc = rne_e4m3_grid((__builtin_amdgcn_exp2f(fmaf(gmax[ks], c, -ms)) * inv1) * (1.0f / 6.0f));
+                const float sc = rne_e4m3_grid_of_product(__builtin_amdgcn_exp2f(fmaf(gmax[ks], c, -ms)) * inv1, 1.0f / 6.0f);
                 bsc[ks & 1][ks >> 1] = (half_t)sc;
                 psc[ks] = fminf(__builtin_amdgcn_rcpf(sc), 512.0f) * inv1;
             }
