@@ -124,7 +124,7 @@ int check_dims(int B, int Hq, int Hkv, int L, int d, int dtype)
     return ATTNQAT_OK;
 }
 
-// Workspace of the forward: fp16 Q^F, K^F (row-major) and V^F^T.
+// Workspace of the forward: K^F and V^F^T in fp16, and, in qh, Q^F in fp16 (packed inputs) or a copy of Q where a result lies over it.
 struct FwdWs { void *qh, *kh, *vt; double* kpart; float* kmean; size_t bytes; };
 FwdWs carve_fwd(void* ws, int B, int Hq, int Hkv, int L, int d, bool mx = false)
 {
@@ -134,7 +134,7 @@ FwdWs carve_fwd(void* ws, int B, int Hq, int Hkv, int L, int d, bool mx = false)
     w.qh = c.take((size_t)B * Hq * Lp * d * 2);
     w.kh = c.take((size_t)B * Hkv * Lp * d * 2);
     w.vt = c.take((size_t)B * Hkv * Lp * d * 2);
-    // MX: kh holds the K records of the FP4 instruction (smaller than the fp16 copies), qh a copy of Q where one is needed
+    // MX: kh holds the K records of the FP4 instruction (smaller than the fp16 copies)
     if (mx) { c.take((size_t)B * Hq * L * d * 2); c.take(mx_qsc_bytes(B * Hq, L)); }      // (not used any more: the size asked for stays what it was)
     w.kpart = (double*)c.take(colmean_scratch_bytes(B * Hkv, d));  // K smoothing: partial sums and the token mean of K
     w.kmean = (float*)c.take((size_t)B * Hkv * d * 4);
@@ -228,25 +228,23 @@ int fwd_common(const void* q, const void* k, const void* v, int B, int Hq, int H
     if (!workspace || workspace_bytes < w.bytes) return ATTNQAT_EWORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     prof_begin(st);
-    // (the attention kernel quantizes Q, from a copy where a result lies over it)
-    if (!q_unwritten(q, B, Hq, L, d, o, lse, train ? o_hp : nullptr)) {
-        if (hipMemcpyAsync(w.qh, q, (size_t)B * Hq * L * d * 2, hipMemcpyDeviceToDevice, st) != hipSuccess) return ATTNQAT_ELAUNCH;
-        q = w.qh;
-    }
+    // (the attention kernel quantizes Q, from a copy that the preparing launch makes where a result lies over it)
+    const bool copy_q = !q_unwritten(q, B, Hq, L, d, o, lse, train ? o_hp : nullptr);
+    const void* q_rd = copy_q ? w.qh : q;
     if (mx) {
         // K as operands of the scaled FP4 instruction (the scores are computed from the codes), V^F^T as the fp16 copy
-        MxGroup g = mx_group_of(nullptr, k, v, B * Hq, B * Hkv, L);
-        g.krec = (unsigned char*)w.kh; g.v_out = (uint16_t*)w.vt;
+        MxGroup g = mx_group_of(copy_q ? q : nullptr, k, v, B * Hq, B * Hkv, L);
+        g.q_row = (uint16_t*)w.qh; g.krec = (unsigned char*)w.kh; g.v_out = (uint16_t*)w.vt;
         if (launch_mx_group(g, MX_TRAIN, d, st)) return ATTNQAT_ELAUNCH;
         prof_mark("prep_qkv", st);
-        if (launch_fwd(q, w.kh, w.vt, B, Hq, Hkv, L, d, causal != 0, train, 1, o, lse, o_hp, dump_row0, p_dump, st))
+        if (launch_fwd(q_rd, w.kh, w.vt, B, Hq, Hkv, L, d, causal != 0, train, 1, o, lse, o_hp, dump_row0, p_dump, st))
             return ATTNQAT_ELAUNCH;
         prof_mark(train ? "fwd_train" : "fwd_infer", st);
         return ATTNQAT_OK;
     }
     PrepGroup g = group_of(B, Hq, Hkv, L, d);
-    g.k = (const uint16_t*)k; g.v = (const uint16_t*)v;
-    g.k_out = (uint16_t*)w.kh; g.v_out = (uint16_t*)w.vt;
+    g.q = (const uint16_t*)q; g.k = (const uint16_t*)k; g.v = (const uint16_t*)v;
+    g.q_out = copy_q ? (uint16_t*)w.qh : nullptr; g.k_out = (uint16_t*)w.kh; g.v_out = (uint16_t*)w.vt;
     g.v_quant = !bf16pv;                           // Sec. 2.5, NVFP4 Q K^T with BF16 P V: V only changes layout
     if (options & ATTNQAT_OPT_SMOOTH_K) {          // K minus its token mean (Sec. 2.1), then phi
         if (launch_colmean(k, B * Hkv, L, d, w.kpart, w.kmean, st)) return ATTNQAT_ELAUNCH;
@@ -255,7 +253,7 @@ int fwd_common(const void* q, const void* k, const void* v, int B, int Hq, int H
     if (launch_prep_group(g, st)) return ATTNQAT_ELAUNCH;
     prof_mark("prep_qkv", st);
     const int p_quant = bf16pv ? 3 : (options & ATTNQAT_OPT_TWO_LEVEL_P) ? 2 : 0;
-    if (launch_fwd(q, w.kh, w.vt, B, Hq, Hkv, L, d, causal != 0, train, p_quant, o, lse, o_hp, dump_row0, p_dump, st))
+    if (launch_fwd(q_rd, w.kh, w.vt, B, Hq, Hkv, L, d, causal != 0, train, p_quant, o, lse, o_hp, dump_row0, p_dump, st))
         return ATTNQAT_ELAUNCH;
     prof_mark(train ? "fwd_train" : "fwd_infer", st);
     return ATTNQAT_OK;
@@ -554,19 +552,16 @@ int paged_common(const void* q, int B, int Hq, int Hkv, int Lq, int d, int causa
         return ATTNQAT_OK;
     }
     if (dec_ws) *dec_ws = nullptr;
-    // (as in fwd_common)
-    if (!q_unwritten(q, B, Hq, Lq, d, o, lse, nullptr)) {
-        if (hipMemcpyAsync(w.qh, q, (size_t)B * Hq * Lq * d * 2, hipMemcpyDeviceToDevice, st) != hipSuccess) return ATTNQAT_ELAUNCH;
-        q = w.qh;
-    }
-    // K^F and V^F are in the cache already and only change layout
+    // (Q as in fwd_common)  K^F and V^F are in the cache already and only change layout
+    const bool copy_q = !q_unwritten(q, B, Hq, Lq, d, o, lse, nullptr);
     PrepGroup g = group_of(B, Hq, Hkv, Lq, d);
+    g.q = (const uint16_t*)q; g.q_out = copy_q ? (uint16_t*)w.qh : nullptr;
     g.ps = PagedSrc{(const unsigned char*)cache, page_table, kv_lens, max_pages, num_pages, Hkv, 0};
     g.L_kv = max_pages * 128; g.Lp_kv = w.Lkp;
     g.k_out = (uint16_t*)w.kh; g.v_out = (uint16_t*)w.vt;
     if (launch_prep_group(g, st)) return ATTNQAT_ELAUNCH;
     prof_mark("prep_q_unpack_pages", st);
-    if (launch_fwd_varlen(q, w.kh, w.vt, B, Hq, Hkv, Lq, w.Lkp, d, causal != 0, kv_lens, o, lse, st)) return ATTNQAT_ELAUNCH;
+    if (launch_fwd_varlen(copy_q ? w.qh : q, w.kh, w.vt, B, Hq, Hkv, Lq, w.Lkp, d, causal != 0, kv_lens, o, lse, st)) return ATTNQAT_ELAUNCH;
     prof_mark("fwd_infer_paged", st);
     return ATTNQAT_OK;
 }

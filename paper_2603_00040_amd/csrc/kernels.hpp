@@ -34,7 +34,7 @@ struct GradArgs {
 struct PrepGroup {
     const uint16_t *q, *k, *v;
     const uint8_t *codes[3], *scales[3];
-    uint16_t *q_out, *k_out, *v_out;             // q_out: backward, packed inputs; k_out null: K is left out
+    uint16_t *q_out, *k_out, *v_out;             // q_out: Q^F (backward, packed inputs) or a copy of Q [BHq, L, D] (forward of bf16 Q), null: none; k_out null: K is left out
     const float* k_sub;                          // [BHkv, D]: subtracted from the rows of K before phi (K smoothing)
     int BHq, BHkv, L, Lp, L_kv, Lp_kv, D;
     bool v_quant;
@@ -123,7 +123,7 @@ void set_bwd_waves(int waves);
 // optional bf16 xf: see attnqat.h.  fp8: E4M3 elements instead of E2M1 (axis 1 only).
 int launch_mx_quant(const void* x, int BH, int L, int D, int axis, bool fp8, unsigned char* codes, unsigned char* scales, void* xf, hipStream_t st);
 // Everything that an MX forward or backward prepares, in one launch (null outputs are left out):
-//   Q: operands of the scaled MFMA (qops, scale dwords qsc)              [not MX_TRAIN]; fp16 rows q_row    [MX_BWD]
+//   Q: operands of the scaled MFMA (qops, scale dwords qsc)              [not MX_TRAIN]; fp16 rows q_row    [MX_BWD]; a copy of Q in q_row    [MX_TRAIN]
 //   K: the K part of the 64-key kv records kv                            [MX_INFER, MX_INFER_FP8V]
 //      records in natural key order krec                                 [MX_TRAIN, MX_BWD]
 //      operands kops, ksc as of Q; fp16 rows k_row                       [MX_BWD]

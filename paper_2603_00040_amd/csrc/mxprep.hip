@@ -173,7 +173,7 @@ __device__ inline void mx_block_list(const unsigned char* __restrict__ mask, int
 }
 
 // A workgroup takes 64 positions of V (in a backward the chunk of a head's 64-row tiles that one partial maximum covers), 256 blocks
-// of 32 values of Q or K, four rows of the mask, or a chunk of dO.
+// of 32 values of Q or K, 64 rows of Q to copy (training forward), four rows of the mask, or a chunk of dO.
 // (five wavefronts per SIMD: the loads of a backward's dO and O' together would otherwise take 101 registers, one wavefront less)
 template <int D, MxKind KIND>
 __global__ __launch_bounds__(256, 5) void mx_group_kernel(MxGroup g, unsigned nblocks)
@@ -183,7 +183,8 @@ __global__ __launch_bounds__(256, 5) void mx_group_kernel(MxGroup g, unsigned nb
     __shared__ float red[4];
     const int tiles = g.Lp / 64, per = KIND == MX_BWD ? bound_chunk_tiles(tiles) : 1, nch = (tiles + per - 1) / per;
     const unsigned n_g = KIND == MX_BWD ? (unsigned)g.BHq * nch : 0u, n_v = g.v ? (unsigned)g.BHkv * nch : 0u;
-    const unsigned per_qk = (unsigned)(g.Lp / RW), n_q = g.q ? (unsigned)g.BHq * per_qk : 0u, n_k = g.k ? (unsigned)g.BHkv * per_qk : 0u;
+    const unsigned per_qk = (unsigned)(g.Lp / RW), n_k = g.k ? (unsigned)g.BHkv * per_qk : 0u;
+    const unsigned n_q = !g.q ? 0u : KIND == MX_TRAIN ? (unsigned)(((size_t)g.BHq * g.L + 63) / 64) : (unsigned)g.BHq * per_qk;
     for (unsigned b = blockIdx.x; b < nblocks; b += gridDim.x) {
         unsigned i = b;
         if (KIND == MX_BWD && i < n_g) {
@@ -201,11 +202,17 @@ __global__ __launch_bounds__(256, 5) void mx_group_kernel(MxGroup g, unsigned nb
         i -= n_v;
         if (i < n_q + n_k) {
             const bool is_q = i < n_q;
+            if constexpr (KIND == MX_TRAIN) {
+                if (is_q) {
+                    copy_rows64<D>(g.q, g.q_row, (size_t)g.BHq * g.L, i);
+                    continue;
+                }
+            }
             if (!is_q) i -= n_q;
             const int bh = (int)(i / per_qk), row = (int)(i % per_qk) * RW + threadIdx.x / NB, blk = threadIdx.x % NB;
             uint32_t byte;
             const uint4v c = mx_block_of_row<D>(is_q ? g.q : g.k, bh, row, blk, g.L, byte);
-            if (is_q) mx_put_operand<D>(g.qops, g.qsc, bh, row, blk, g.Lp, c, byte);
+            if (KIND != MX_TRAIN && is_q) mx_put_operand<D>(g.qops, g.qsc, bh, row, blk, g.Lp, c, byte);
             else if (KIND == MX_TRAIN || KIND == MX_BWD) mx_put_krec<D>(g.krec, bh, row, blk, g.Lp, c, byte);
             else mx_put_kv_k<D, KIND == MX_INFER_FP8V>(g.kv, g.page_ids, g.num_pages, bh, g.BHkv, row, blk, g.Lp, c, byte);
             if constexpr (KIND == MX_BWD) {
@@ -247,7 +254,7 @@ int launch_mx_group(const MxGroup& g, MxKind kind, int D, hipStream_t st)
         return hipGetLastError() == hipSuccess ? 0 : -1;
     }
     const int tiles = g.Lp / 64, per = kind == MX_BWD ? bound_chunk_tiles(tiles) : 1, nch = (tiles + per - 1) / per, per_qk = g.Lp / (256 / (D / 32));
-    long long n = (kind == MX_BWD ? (long long)g.BHq * nch : 0) + (g.v ? (long long)g.BHkv * nch : 0) + (g.q ? (long long)g.BHq * per_qk : 0) + (g.k ? (long long)g.BHkv * per_qk : 0);
+    long long n = (kind == MX_BWD ? (long long)g.BHq * nch : 0) + (g.v ? (long long)g.BHkv * nch : 0) + (!g.q ? 0 : kind == MX_TRAIN ? ((long long)g.BHq * g.L + 63) / 64 : (long long)g.BHq * per_qk) + (g.k ? (long long)g.BHkv * per_qk : 0);
     if (g.mask) n += ((long long)g.BHq * (g.Lp / 128) + 3) / 4;
     if (n < 1 || n > 0x7FFFFFFFLL || (g.mask && kind != MX_INFER) || (g.page_ids && kind != MX_INFER)) return -1;
     const unsigned nblocks = (unsigned)n, grid = min(nblocks, 1u << 22);       // (a grid has fewer than 2^32 threads)

@@ -257,7 +257,9 @@ __global__ __launch_bounds__(256) void quantize_kernel(const uint16_t* __restric
 // 8 kv heads, L = 4096 3.22 -> 3.10 ms; inference on 32 heads, L = 777 36.6 -> 30.0 us.
 // A workgroup takes 64 positions of one head of one tensor; where a maximum is wanted (V and dO of a backward) it takes the
 // head's chunk of them, at most kBoundParts chunks per head, and writes the chunk's maxima; unused chunks are written as 0.
-// SRC: 0 Q (backward only: a forward's attention kernel quantizes Q), K, V in bf16; 1 all three packed (codes and scales); 2 K and V in the pages of the cache.
+// SRC: 0 Q, K, V in bf16; 1 all three packed (codes and scales); 2 K and V in the pages of the cache.  A forward's attention kernel quantizes Q
+// itself: with bf16 Q a forward's launch does no more than copy it, where a result lies over it (32/8 heads, L = 777 causal, inference with O over Q 25.6 us, with the copy as a
+// command of its own 28.0; O elsewhere 22.4).
 // VQUANT false: V only changes layout (bf16).  BWD: V as bf16 rows with its bound, and the dO / O' part; else V transposed.
 template <int SRC, bool VQUANT, bool BWD>
 __global__ __launch_bounds__(256) void prep_group_kernel(PrepGroup g, unsigned nblocks)
@@ -269,7 +271,8 @@ __global__ __launch_bounds__(256) void prep_group_kernel(PrepGroup g, unsigned n
     const int per_g = bound_chunk_tiles(tiles_q), nch_g = (tiles_q + per_g - 1) / per_g;        // 64-row tiles per chunk, chunks
     const int per_v = BWD ? bound_chunk_tiles(tiles_kv) : 1, nch_v = (tiles_kv + per_v - 1) / per_v;
     const unsigned n_g = BWD ? (unsigned)g.BHq * nch_g : 0u, n_v = (unsigned)g.BHkv * nch_v;
-    const unsigned n_q = BWD || SRC == 1 ? (unsigned)g.BHq * tiles_q : 0u;
+    constexpr bool QPHI = BWD || SRC == 1;               // phi(Q); else at most a copy of Q
+    const unsigned n_q = QPHI ? (unsigned)g.BHq * tiles_q : g.q_out ? (unsigned)(((size_t)g.BHq * g.L + 63) / 64) : 0u;
     for (unsigned blk = blockIdx.x; blk < nblocks; blk += gridDim.x) {
         unsigned i = blk;
         float n2 = 0.0f;
@@ -297,6 +300,13 @@ __global__ __launch_bounds__(256) void prep_group_kernel(PrepGroup g, unsigned n
             prep_tile<SRC != 1, true, SRC == 1, false, false, decltype(k_ops)::value>(tile, (int)(i / per), (int)(i % per) * 64, is_q ? g.q : g.k, is_q ? g.L : g.L_kv, is_q ? g.Lp : g.Lp_kv, g.D,
                 const_cast<uint8_t*>(g.codes[w]), const_cast<uint8_t*>(g.scales[w]), nullptr, is_q ? g.q_out : g.k_out, nullptr, is_q ? nullptr : g.k_sub, PagedSrc{}, n2);
         };
+        if constexpr (!QPHI) {
+            if (is_q) {
+                if (g.D == 128) copy_rows64<128>(g.q, g.q_out, (size_t)g.BHq * g.L, i);
+                else            copy_rows64<64>(g.q, g.q_out, (size_t)g.BHq * g.L, i);
+                continue;
+            }
+        }
         if (BWD || (SRC == 1 && is_q)) rows(std::false_type{});
         else if constexpr (SRC == 2) {
             PagedSrc ps = g.ps;
@@ -315,6 +325,7 @@ int launch_prep_group(const PrepGroup& g, hipStream_t st)
     long long n = (long long)g.BHkv * (bwd ? chunks(tiles_kv) : tiles_kv);
     const bool packed = g.codes[2] != nullptr, paged = g.ps.cache != nullptr;
     if (bwd || packed) n += (long long)g.BHq * tiles_q;
+    else if (g.q_out) n += ((long long)g.BHq * g.L + 63) / 64;
     if (g.k_out) n += (long long)g.BHkv * tiles_kv;
     if (bwd) n += (long long)g.BHq * chunks(tiles_q);
     if (n > 0x7FFFFFFFLL) return -1;

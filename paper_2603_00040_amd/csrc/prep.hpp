@@ -94,6 +94,18 @@ __device__ __forceinline__ void grad_tile(int bh, int l0, const uint16_t* __rest
     }
 }
 
+// Copies rows 64 i .. of Q [rows, D] as they are: a forward whose results lie over Q reads this copy.
+template <int D>
+__device__ __forceinline__ void copy_rows64(const uint16_t* __restrict__ src, uint16_t* __restrict__ dst, size_t rows, size_t i)
+{
+    const uint4v* s = reinterpret_cast<const uint4v*>(src) + i * (64 * D / 8);
+    uint4v* d = reinterpret_cast<uint4v*>(dst) + i * (64 * D / 8);
+    const uint32_t n = (uint32_t)min((size_t)64, rows - 64 * i) * (D / 8);
+#pragma unroll
+    for (int p = 0; p < 64 * D / 8; p += 256)
+        if (p + threadIdx.x < n) d[p + threadIdx.x] = s[p + threadIdx.x];
+}
+
 // Largest value of a workgroup; every thread gets it.  (The barriers also keep `red` from being overwritten too early.)
 __device__ inline float wg_max(float v, float (&red)[4]) {
     v = lanes_max<32, 1>(v);
