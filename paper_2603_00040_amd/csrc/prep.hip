@@ -41,6 +41,8 @@ __device__ inline const unsigned char* nvfp4_page_part(const unsigned char* cach
 // L is the capacity max_pages * 128 that the copies are laid out for.
 // NORM: n2 becomes the largest squared norm of the rows seen so far (in the lanes that hold a row's first block).
 // KOPS: the rows (xr) are written in the order of the forward's K operands.
+// The public outputs (codes, scales, xf_pub) are those of the public quantizer alone, which has bf16 copies and no bound (PUBLIC); sub (K smoothing), whose values
+// have no codes here, is for the others.
 template <int D, bool QUANT, bool OUT_F16, bool PACKED, bool PAGED, bool NORM, bool KOPS = false>
 __device__ __forceinline__ void prep_tile_d(
     uint16_t (*tile)[128 + 2], int bh, int l0, const uint16_t* __restrict__ x, int L, int Lp,
@@ -49,6 +51,7 @@ __device__ __forceinline__ void prep_tile_d(
 {
     static_assert(!(QUANT && PACKED), "a packed input is already quantized");
     static_assert(!PAGED || PACKED, "pages hold quantized tensors");
+    constexpr bool PUBLIC = QUANT && !OUT_F16 && !NORM;
     constexpr int nb = D / 16, NI = nb / 4;      // 16-element blocks per row, and of the 64 rows per thread
     const size_t in_base = (size_t)bh * L * D;
     int Lseq = L;
@@ -111,7 +114,7 @@ __device__ __forceinline__ void prep_tile_d(
                 v[8 + 2 * i]     = __uint_as_float(b[i] << 16);
                 v[8 + 2 * i + 1] = __uint_as_float(b[i] & 0xFFFF0000u);
             }
-            if (sub && l < L) {             // K smoothing: minus the token mean of the channel, an fp32 subtraction.
+            if (!PUBLIC && sub && l < L) {  // K smoothing: minus the token mean of the channel, an fp32 subtraction.
                 // The inputs of phi then have 24 significant bits: the two "IEEE division == real quotient" arguments
                 // below hold up to a double rounding that can move a value sitting within 2^-24 of a rounding boundary.
                 const float* sp = sub + (size_t)bh * D + cb * 16;
@@ -123,7 +126,7 @@ __device__ __forceinline__ void prep_tile_d(
         float xf[16];
         bool direct = true;                              // the values are those of q
         if constexpr (QUANT) {
-            if (sub) {
+            if (!PUBLIC && sub) {
                 direct = false;
                 float amax = 0.0f;
 #pragma unroll
@@ -143,11 +146,11 @@ __device__ __forceinline__ void prep_tile_d(
                     xf[i] = sign ? -d : d;
                 }
             } else q = phi_block16_bf16(v);
-            if (l < L && codes) {
+            if (PUBLIC && l < L && codes) {
                 uint2v c2; c2[0] = q.clo; c2[1] = q.chi;
                 *reinterpret_cast<uint2v*>(codes + ((size_t)bh * L + l) * (D / 2) + cb * 8) = c2;
             }
-            if (scales) {
+            if (PUBLIC && scales) {
                 // four neighbouring blocks of a row (four neighbouring lanes: nb is 4 or 8 and a wave starts at a multiple
                 // of 64 blocks) write their scale bytes as one dword; rows beyond L take part in the exchange and write nothing
                 uint32_t sb = q.sc & 0xFFu;
@@ -183,7 +186,7 @@ __device__ __forceinline__ void prep_tile_d(
         } else {
 #pragma unroll
             for (int i = 0; i < 8; ++i) w[i] = pack_bf16x2_cvt(xf[2 * i], xf[2 * i + 1]);
-            if (xf_pub && l < L) {
+            if (PUBLIC && xf_pub && l < L) {
                 uint4v o0, o1;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) { o0[i] = w[i]; o1[i] = w[4 + i]; }
