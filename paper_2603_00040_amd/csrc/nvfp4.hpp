@@ -5,7 +5,7 @@
 namespace aq {
 
 // A quantized block of 16: the E2M1 codes, element 2k in the low nibble of byte k of {clo, chi}, and the E4M3 scale as a value, with its byte in
-// the two low bytes of sc (what makes an fp16 pair of it, scale_f16).
+// the two low bytes of sc (of which one conversion makes an fp16 pair).
 struct Nv16 { uint32_t clo, chi, sc; float s; };
 
 // phi of one block of 16 values that are bf16 numbers (Eq. 1).
