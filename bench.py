@@ -24,7 +24,7 @@ sys.path.insert(0, ROOT)
 MFMA_PEAK_TFLOPS = 2500.0          # MI355X dense bf16/fp16 MFMA
 MFMA_FP4_PEAK_TFLOPS = 10100.0     # MI355X dense FP4 MFMA (the MX variant's products)
 MFMA_FP8_PEAK_TFLOPS = 5000.0      # MI355X dense FP8 MFMA (P V of the mixed recipe)
-KERNEL_GEMMS = {"fwd_train": 6.0, "fwd_infer": 4.0, "fwd_infer_mx": 4.0, "fwd_infer_mx_fp8pv": 4.0, "bwd_dq": 6.0, "bwd_dkdv": 8.0, "bwd_joint": 14.0}   # bwd_dkdv, bwd_joint (both passes in one launch): see main()
+KERNEL_GEMMS = {"fwd_train": 6.0, "fwd_infer": 4.0, "fwd_infer_mx": 4.0, "fwd_infer_mx_fp8pv": 4.0, "bwd_dq": 6.0, "bwd_dkdv": 8.0, "bwd_joint": 14.0, "bwd_few": 14.0}   # bwd_dkdv, bwd_joint and bwd_few (both passes in one launch): see main()
 # Sec. 3.4: peak forward throughput on B200 (NVFP4 QK + FP8 PV) at b=1, s=32768, h=32, d=128.  Another machine and
 # another recipe: context for the forward on that shape, not a target.
 PAPER_FWD_TFLOPS = {"paper_peak_fwd_shape": 2026.0}
@@ -193,7 +193,7 @@ def measure(aq, torch, np, W, w, steps, warmup, fmt="nvfp4", opts=0, ablation=0,
     gemms = dict(KERNEL_GEMMS)
     if pf_frac is not None:
         gemms["bwd_dkdv"] = 6.0 + 2.0 * pf_frac
-        gemms["bwd_joint"] = 12.0 + 2.0 * pf_frac
+        gemms["bwd_joint"] = gemms["bwd_few"] = 12.0 + 2.0 * pf_frac
     dom = max((n for n in kern_ms if n in gemms), key=lambda n: kern_ms[n])
     achieved = gemms[dom] * pair_flops / (kern_ms[dom] * 1e-3) / 1e12
     traffic = TRAFFIC_BEYOND_L2.get(w.name, {}).get(dom) if (fmt == "nvfp4" and not opts and not ablation) or dom == "fwd_infer_mx" else None

@@ -826,7 +826,7 @@ static int bwd_common(const void* q, const void* k, const void* v, const void* d
     }
     if (p_quant == 1 && !p_dump && !dkdv_counts_of(st) && bwd_few_rows(B * Hq, B * Hkv, L, causal != 0, plan.splits > 1, device_cu_count())) {
         if (launch_bwd_few(w.qb, w.kb, w.vb, dob, w.rowstat, w.bounds, B, Hq, Hkv, L, d, causal != 0, dq, dk, dv, st)) return ATTNQAT_ELAUNCH;
-        prof_mark("bwd_joint", st);
+        prof_mark("bwd_few", st);
         return ATTNQAT_OK;
     }
     if (plan.joint && p_quant != 0) {

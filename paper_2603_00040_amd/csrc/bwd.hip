@@ -1198,7 +1198,8 @@ __global__ __launch_bounds__(256) void dkdv_reduce_kernel(const float* __restric
 }
 
 // ------------------------------------------------------------------ few rows
-// Both passes for problems that leave most compute units idle (few_rows), NVFP4.  What bounds those is the chain of one workgroup, tile after tile; here a
+// Both passes for problems that leave most compute units idle (few_rows), NVFP4 (the scores of the MX form and the row factor of the two-level form have not been
+// written for it: their backwards of few rows take the joint launch).  What bounds those is the chain of one workgroup, tile after tile; here a
 // workgroup owns 32 keys (or 32 query rows), its four waves take four query tiles (key tiles) at a time, wave w tile 4 n + w for S, dP, P^F and
 // dS, and then one block of 32 columns of dK and of dV (of dQ) for the products of all four, whose P^F and dS they find in LDS: a chain is a quarter as
 // long, and every sum has the order, so every result the bits, of the kernels above.  Two barriers per four tiles; one workgroup per compute unit,

@@ -142,6 +142,13 @@ def test_joint_backward_kernels_do_not_spill():
     _check(k, r"dkdv_reduce_kernelILi(64|128)ELb[01]E", 4)
 
 
+def test_few_rows_backward_kernels_do_not_spill():
+    # bwd_few_kernel<D, CAUSAL>: operands of four tiles at a time; one workgroup, of a wavefront per SIMD, on a compute unit
+    hit = {n: v for n, v in _resources("bwd.hip").items() if re.search(r"bwd_few_kernelILi(64|128)ELb[01]E", n)}
+    assert len(hit) == 4
+    assert all(v["VGPRs Spill"] == 0 and v["SGPRs Spill"] == 0 and v["ScratchSize [bytes/lane]"] == 0 for v in hit.values()), hit
+
+
 def test_backward_of_d64_leaves_room_for_three_wavefronts():
     # (a SIMD has 512 registers; with more than 168 each, two)
     hit = _check(_resources("bwd.hip"), r"bwd_joint_kernelILi64ELb[01]ELi[123]ELb0E", 6)

@@ -27,7 +27,8 @@ def planner(tmp_path_factory):
                 '}\n'
                 'extern "C" int in_pairs(int q, int kv, int L, int d, int causal, int cus) {\n'
                 '    return aq::joint_in_pairs(aq::plan_backward(q, kv, L, d, causal != 0, cus), q, kv, L, d, causal != 0, cus);\n'
-                '}\n')
+                '}\n'
+                'extern "C" int few(int q, int kv, int L, int causal, int pieces, int cus) { return aq::few_rows(q, kv, L, causal != 0, pieces != 0, cus); }\n')
     subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-I", B.CSRC, src, "-o", lib], check=True)
     L = ctypes.CDLL(lib)
     out = (ctypes.c_longlong * 5)()
@@ -36,6 +37,7 @@ def planner(tmp_path_factory):
         L.plan(*a, out)
         return tuple(out)
     plan.in_pairs = lambda *a: bool(L.in_pairs(*a))
+    plan.few = lambda *a: bool(L.few(*a))
     return plan
 
 
@@ -101,3 +103,25 @@ def test_whole_key_tiles_of_d64_keep_to_two_workgroups(planner):
     for s in ((64, 16, 4096, 64, 0), (32, 16, 3300, 64, 0), (4, 4, 10205, 64, 0), (48, 48, 8700, 64, 0), (64, 8, 5518, 64, 1), (96, 96, 668, 64, 1), (48, 12, 16255, 64, 1),
               (2, 2, 256, 64, 0), (64, 8, 5518, 128, 0), (16, 2, 12000, 64, 0)):
         assert not planner.in_pairs(*s, 256), s
+
+
+def test_routes_of_the_shapes_that_the_gpu_tests_name(planner):
+    """Which kernel an NVFP4 backward with all the room it asks for takes: the shapes of tests/test_gpu_bwd_routes.py lie on the side of
+    few_rows that they are for."""
+    from tests.test_gpu_bwd_routes import CUT, FEW, SPARE
+
+    def route(B_, Hq, Hkv, L, d, causal):
+        _, splits, _, _, dq_first = planner(B_ * Hq, B_ * Hkv, L, d, causal, 256)
+        Lp, align = -(-L // 128) * 128, lambda n: -(-n // 256) * 256
+        nq, nk = B_ * Hq, B_ * Hkv
+        small = 2 * (nq + nk) * Lp * d * 2 + align(nq * Lp * 8) + align(3 * nq * 256) + align(nk * 32 * d * 8) + align(nk * d * 4) < 2 << 20
+        return planner.few(nq, nk, L, causal, splits > 1 and not small, 256), splits > 1, bool(dq_first), small
+    for s in FEW:
+        assert route(*s)[0], s
+    for s in CUT:
+        few, cut, _, small = route(*s)
+        assert not few and cut and not small and s[1] == s[2], s
+    assert {route(*s)[2] for s in CUT} == {False, True}
+    for s in SPARE:      # cut if there were room, and small enough to be asked for without; a plain NVFP4 backward has few rows there
+        few, cut, _, small = route(*s)
+        assert few and cut and small, s
