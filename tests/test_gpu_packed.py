@@ -28,6 +28,24 @@ def test_packed_forms_equal_the_quantizing_forms_bit_for_bit(shape, causal):
     assert torch.equal(dqp, dq) and torch.equal(dkp, dk) and torch.equal(dvp, dv)
 
 
+# Packed Q is read as fp16 rows padded to a multiple of 128, bf16 Q from where it is, quantized by the attention kernel: the same bits in its workgroups of 128 rows
+# (80 heads, L = 1000), of 256 rows (128 heads, L = 450) and of a long and a short tile of 256 (32 heads, L = 4001, causal)
+@pytest.mark.parametrize("shape,causal", [((2, 40, 8, 1000, 128), False), ((2, 40, 8, 1000, 64), True), ((2, 64, 16, 450, 128), False), ((2, 64, 16, 450, 64), False),
+                                          ((1, 32, 4, 4001, 128), True)])
+def test_packed_forward_equals_the_quantizing_one_in_whole_workgroups(shape, causal):
+    import paper_2603_00040_amd as aq
+    B, Hq, Hkv, L, d = shape
+    x = random_inputs(B, Hq, Hkv, L, d, seed=900 + L, k_chan=4, dist="t3", scale=0.5, tok_mod=50)
+    q, k, v = (to_dev(x[n]) for n in "qkv")
+    packs = [aq.attnqat_quantize(t, want_xf=False)[:2] for t in (q, k, v)]
+    oi, lsei = aq.attnqat_fwd_infer(q, k, v, causal)
+    op, lsep = aq.attnqat_fwd_infer_packed(*packs, causal, d)
+    o, lse, _ = aq.attnqat_fwd(q, k, v, causal)
+    torch.cuda.synchronize()
+    assert torch.equal(op, oi) and torch.equal(lsep, lsei)
+    assert torch.equal(o, oi) and torch.equal(lse, lsei)
+
+
 def test_packed_argument_errors():
     import paper_2603_00040_amd as aq
     L_ = aq.lib()

@@ -1,5 +1,6 @@
-"""Where the attention kernels quantize Q themselves: bit for bit what a call returns whose output lies over its Q, which takes operands that the
-preparing launch made, or a copy of Q."""
+"""Calls whose output lies over their Q, against the same call with an output of its own.  MX inference, block-sparse and paged: the attention kernel
+quantizes Q itself, or takes operands that the preparing launch made: two ways to the same bits.  NVFP4 and MX training: the kernel reads Q, or a copy of it
+(its phi(Q) is held against packed inputs, and against the oracle, elsewhere)."""
 import pytest
 import torch
 
