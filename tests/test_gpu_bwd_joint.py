@@ -9,7 +9,8 @@ pytestmark = pytest.mark.gpu
 
 
 # tiles of 32 queries and 128 keys: below, at and above their edges; one head with many keys (dQ tiles first), few kv heads with
-# many query heads (pieces span heads), whole rounds of the compute units' slots and more
+# many query heads (pieces span heads), whole rounds of the compute units' slots and more.  (NVFP4 with few rows takes another kernel, four of these shapes among
+# them: they are the joint launch's in MX; tests/test_gpu_bwd_routes.py has NVFP4 shapes that are its own)
 @pytest.mark.parametrize("B,Hq,Hkv,L,d,causal", [(1, 1, 1, 1, 64, True), (1, 2, 1, 33, 128, True), (1, 8, 1, 129, 64, False), (1, 32, 8, 777, 128, True),
                                                  (1, 12, 12, 1560, 128, False), (1, 1, 1, 4200, 128, True), (2, 16, 2, 1000, 64, True), (1, 40, 40, 1664, 64, True)])
 @pytest.mark.parametrize("mx", [False, True])
@@ -50,7 +51,8 @@ def test_joint_equals_separate_passes(B, Hq, Hkv, L, d, causal, mx):
                                                  (1, 4, 2, 1100, 128, True)])
 def test_bits_do_not_depend_on_spare_room(B, Hq, Hkv, L, d, causal):
     """Whether a key tile's query tiles are shared follows from the shape: every workspace from the size asked for on gives the same bits
-    (the first four ask for no partial sums, the last one does)."""
+    (the first four ask for no partial sums, the last one does; the first four have few rows and so no partial sums in any workspace, which
+    tests/test_gpu_bwd_routes.py has for the joint launch)."""
     import paper_2603_00040_amd as aq
     x = random_inputs(B, Hq, Hkv, L, d, seed=L)
     q, k, v, do = (to_dev(x[n]) for n in ("q", "k", "v", "do"))
