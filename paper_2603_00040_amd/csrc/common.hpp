@@ -139,7 +139,7 @@ __device__ inline float xhalf_sum(float x) {
 // Reductions over neighbouring lanes without LDS: a step of the tree x = op(x, value of lane ^ W), by DPP up to 8 and by the row and
 // half swaps from 16 on (where both lanes of a pair get op(lower, upper): op commutes).  __shfl_xor goes through the LDS, 100 - 130 cycles a step, and
 // these trees are serial: decode steps and the starts and ends of the preparing and backward kernels wait for them.  Through LDS -> here: decode step
-// of 32 sequences of 4k - 16k keys 113.0 -> 110.7 us; training step of 2 heads, L = 256, d = 64 25.3 -> 24.95 us.
+// of 32 sequences of 4k - 16k keys 113.0 -> 110.7 us (boxes drift by as much); training step of 2 heads, L = 256, d = 64 25.3 -> 24.95 us.
 template <int W, class OP>
 __device__ __forceinline__ float xor_step(float x, OP op) {
     static_assert(W == 1 || W == 2 || W == 4 || W == 8 || W == 16 || W == 32);

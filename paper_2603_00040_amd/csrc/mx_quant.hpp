@@ -109,7 +109,7 @@ __device__ inline uint4v mx_block_of_row(const uint16_t* __restrict__ x, int bh,
 // read once and never written, and a decode step has a launch less.  Otherwise src and qsc are what mx_put_operand made, group grp of 32 rows.
 // NT threads (a wave, or the waves that share the rows) read the rows in whole lines, eight values a thread; four neighbouring threads
 // form the scale of a block and a register of codes each, which they hand out through LDS (a lane that read its own 64 bytes made every load touch 64
-// lines: a decode step of 32 sequences 117 -> 122 us).  fetch() asks for the values, quantize() writes kMxQBytes<D> bytes to LDS, scale bytes
+// lines: a decode step of 32 sequences 117 -> 122 us).  fetch() asks for the values, quantize() writes kMxQOps<D> bytes to LDS, scale bytes
 // apart; a barrier of the NT threads; read() takes the operand.  Between fetch() and quantize() a kernel asks for its first keys.
 // Operands from the preparing launch -> here: block-sparse 32/8 heads, L = 8192 136 -> 129 us; 2 x 12 heads, L = 32760 6.01 -> 5.92 ms (of it four
 // moves per tile of mx_codes32); chunks of 512 of 8 sequences 319 -> 312 us; decode steps: one sequence of 3000 keys 16.7 -> 14.6 us, 4 sequences, d = 64
